@@ -4,16 +4,16 @@
 // crops them once more):
 //   h' = h + (attention(RMSNorm(h) ...)) Wo^T,   h'' = h' + (silu(n Wgate^T) * (n Wup^T)) Wdown^T,  n = RMSNorm(h').
 // Kernels: a row-wise RMSNorm, and the shared projection main loop with two epilogues (residual add; SwiGLU on a
-// gate/up feature pair held by the same lane); for few token rows, where the weight stream bounds a projection,
-// slices of the contraction + small reduce kernels (few features, long contraction) or a one-pass kernel with 32
-// weight rows per workgroup (many features).  percache_stack_reuse chains the layers; percache_kv_slice is the
+// gate/up feature pair held by the same lane); for few token rows the same epilogues on the tiles of few_rows.hpp, which
+// also take the RMSNorm in front of them.  percache_stack_reuse chains the layers; percache_kv_slice is the
 // cache slicer of Sec. 4.1.1 (cuts the K/V of a prefilled sequence at chunk boundaries into slots).
 #include <cstring>
 
-#include "gemm_tile.hpp"
+#include "few_rows.hpp"
 
 namespace {
 using pc::f32x16;
+using pc::f32x4;
 using pc::u32x4;
 using pc::gemm::BF;
 using pc::gemm::pack4;
@@ -122,135 +122,72 @@ __global__ __launch_bounds__(256, 2) void linear_swiglu_kernel(const __bf16 *__r
 }
 
 // ---------------------------------------------------------------------------------------------------
-// Few token rows (one or two token tiles): the projections are bound by the stream of the weights, and N/128
-// workgroups cannot pull it.  The contraction is therefore cut into n_k slices computed by separate workgroups:
-//   P[s][m][n] = sum over k in slice s of A[m][k] W[n][k]     (fp32, [n_k][M][N])
-// and a small second kernel adds the slices in a fixed order (deterministic) and applies the epilogue.
-// The weight rows may come from two matrices (rows >= n_split from W1): gate and up projections in one launch.
+// Few token rows: the whole contraction in one launch, see few_rows.hpp.
 // ---------------------------------------------------------------------------------------------------
-template <int NTB, int NS>
-__global__ __launch_bounds__(256, 2) void splitk_partial_kernel(const __bf16 *__restrict__ A, int lda,
-                                                                const __bf16 *__restrict__ W0, const __bf16 *__restrict__ W1,
-                                                                int n_split, int ldw, float *__restrict__ P, int M, int N,
-                                                                int k_slice) {
-  constexpr int BT = 64 * NTB;
-  __shared__ __align__(16) char lds[NS * pc::gemm::Shape<NTB>::STAGE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int wf = wave & 1, wt = wave >> 1;
-  const int l32 = lane & 31, g = lane >> 5;
-  const int f0 = blockIdx.x * BF, m0 = blockIdx.z * BT;
-  const int k0 = blockIdx.y * k_slice;
-  f32x16 acc[2][NTB];
-  pc::gemm::mainloop_deep<NTB, true, NS>(  // one token tile: every weight row is read by exactly one workgroup
-      lds,
-      [&](int row) __attribute__((always_inline)) {
-        const int n = f0 + row;
-        return (n < n_split ? W0 + (size_t)n * ldw : W1 + (size_t)(n - n_split) * ldw) + k0;
+// Y[M, N] = A[M, K] W[N, K]^T + R[M, N]   (o_proj and down projection)
+template <int NF, int NT>
+__global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void linear_residual_few_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
+                                                                                             const __bf16 *__restrict__ R, __bf16 *__restrict__ Y,
+                                                                                             int M, int N, int K, int n_wt, int n_tt) {
+  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG, PER = (NF * NT + WV - 1) / WV;
+  __shared__ __align__(16) char lds[pc::few::Tile<NF, NT, WV, NSTG, false>::LDS_BYTES];
+  int wt, tt;
+  if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
+  const int n0 = wt * 16 * NF, m0 = tt * 16 * NT;
+  auto at = [&](int b) __attribute__((always_inline)) { return (size_t)min(m0 + b % NT * 16 + l16, M - 1) * N + n0 + b / NT * 16 + g * 4; };
+  uint2 res[PER];
+  f32x4 acc[NF][NT];
+  float ss[NT];
+  pc::few::slice_product<NF, NT, WV, NSTG, false>(
+      lds, [&](int r) __attribute__((always_inline)) { return W + (size_t)(n0 + r) * K; },
+      [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, nullptr, K, wave, lane,
+      [&]() __attribute__((always_inline)) {
+#pragma unroll
+        for (int j = 0; j < PER; ++j)
+          if (wave + j * WV < NF * NT) res[j] = *(const uint2 *)(R + at(wave + j * WV));
       },
-      A + k0, lda, m0, M, k_slice, 2 * wf, 2 * wf + 1, acc);
-  float *Ps = P + (size_t)blockIdx.y * M * N;
+      acc, ss);
+  pc::few::share_slices<NF, NT, WV, NSTG, false>(lds, wave, lane, acc, ss);
 #pragma unroll
-  for (int t = 0; t < NTB; ++t) {
-    const int m_raw = m0 + (wt * NTB + t) * 32 + l32;
-    const bool ok = m_raw < M;
-    const int m = ok ? m_raw : M - 1;
-#pragma unroll
-    for (int a = 0; a < 2; ++a)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        const float4 v = {acc[a][t][q4 * 4 + 0], acc[a][t][q4 * 4 + 1], acc[a][t][q4 * 4 + 2], acc[a][t][q4 * 4 + 3]};
-        if (ok) *(float4 *)(Ps + (size_t)m * N + f0 + (2 * wf + a) * 32 + q4 * 8 + g * 4) = v;
-      }
+  for (int j = 0; j < PER; ++j) {
+    const int b = wave + j * WV;
+    if (b >= NF * NT) continue;
+    const f32x4 s = pc::few::tile_sum<NF, NT, WV>(lds, b / NT, b % NT, lane);
+    float r[4];
+    unpack4(res[j], r);
+    if (m0 + b % NT * 16 + l16 < M) *(uint2 *)(Y + at(b)) = pack4(s[0] + r[0], s[1] + r[1], s[2] + r[2], s[3] + r[3]);
   }
 }
 
-// One or two 128-token tiles and many features (the gate / up projections): one pass, no slices.  A workgroup owns 16
-// gate rows and the 16 up rows of the same features (tile rows j and j + 16), which a lane finds in its accumulators
-// r and r + 8, and all token rows of its tile (gemm_tile.hpp: mainloop_skinny).
-__global__ __launch_bounds__(256, 2) void swiglu_skinny_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ Wg,
-                                                               const __bf16 *__restrict__ Wu, __bf16 *__restrict__ Y, int M,
-                                                               int F, int K) {
-  constexpr int NS = 5;
-  __shared__ __align__(16) char lds[NS * pc::gemm::Skinny::STAGE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l32 = lane & 31, g = lane >> 5;
-  const int f0 = blockIdx.x * 16, m0 = blockIdx.y * 128;
-  f32x16 acc;
-  pc::gemm::mainloop_skinny<NS>(
-      lds, [&](int row) __attribute__((always_inline)) { return (row < 16 ? Wg : Wu) + (size_t)(f0 + (row & 15)) * K; }, A, K, m0, M, K,
-      acc);
-  const int m = m0 + wave * 32 + l32;
-  if (m >= M) return;
+// Y[M, F] = silu(n Wgate^T) * (n Wup^T) with n = RMSNorm(A; gain, eps).  Weight blocks 0 .. NF/2 - 1 of a tile are gate
+// rows, the others the up rows of the same features.
+template <int NF, int NT>
+__global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void swiglu_few_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ gain, float eps,
+                                                                                    const __bf16 *__restrict__ Wg, const __bf16 *__restrict__ Wu,
+                                                                                    __bf16 *__restrict__ Y, int M, int F, int K, int n_wt, int n_tt) {
+  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG, HALF = NF / 2;
+  __shared__ __align__(16) char lds[pc::few::Tile<NF, NT, WV, NSTG, true>::LDS_BYTES];
+  int wt, tt;
+  if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
+  const int f0 = wt * 16 * HALF, m0 = tt * 16 * NT;
+  f32x4 acc[NF][NT];
+  float ss[NT];
+  pc::few::slice_product<NF, NT, WV, NSTG, true>(
+      lds, [&](int r) __attribute__((always_inline)) { return (r < 16 * HALF ? Wg + (size_t)(f0 + r) * K : Wu + (size_t)(f0 + r - 16 * HALF) * K); },
+      [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, []() {}, acc, ss);
+  pc::few::share_slices<NF, NT, WV, NSTG, true>(lds, wave, lane, acc, ss);
 #pragma unroll
-  for (int q2 = 0; q2 < 2; ++q2) {
+  for (int b = wave; b < HALF * NT; b += WV) {
+    const int f = b / NT, t = b % NT, m = m0 + t * 16 + l16;
+    const float r = pc::few::row_factor<NF, NT, WV>(lds, t, l16, K, eps);
+    const f32x4 gate = pc::few::tile_sum<NF, NT, WV>(lds, f, t, lane) * r, up = pc::few::tile_sum<NF, NT, WV>(lds, f + HALF, t, lane) * r;
     float o[4];
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float gate = acc[q2 * 4 + e], up = acc[8 + q2 * 4 + e];
-      o[e] = gate / (1.0f + __expf(-gate)) * up;
-    }
-    *(uint2 *)(Y + (size_t)m * F + f0 + q2 * 8 + g * 4) = pack4(o[0], o[1], o[2], o[3]);
+    for (int e = 0; e < 4; ++e) o[e] = gate[e] / (1.0f + __expf(-gate[e])) * up[e];
+    if (m < M) *(uint2 *)(Y + (size_t)m * F + f0 + f * 16 + g * 4) = pack4(o[0], o[1], o[2], o[3]);
   }
-}
-
-// y = sum of slices + residual (rounded to bf16), and optionally n = RMSNorm(y) * gain on the rounded values.
-// One workgroup per row, four columns per thread and pass.
-__global__ __launch_bounds__(256) void reduce_residual_norm_kernel(const float *__restrict__ P, int n_k, int M, int N,
-                                                                   const __bf16 *__restrict__ R, __bf16 *__restrict__ Y,
-                                                                   const __bf16 *__restrict__ gain, __bf16 *__restrict__ Yn,
-                                                                   float eps) {
-  __shared__ float red[4];
-  const int row = blockIdx.x, tid = threadIdx.x;
-  const size_t slice = (size_t)M * N;
-  float ss = 0.f;
-  for (int c = tid * 4; c < N; c += 1024) {
-    const size_t at = (size_t)row * N + c;
-    float4 sum = *(const float4 *)(P + at);
-#pragma unroll 4
-    for (int s = 1; s < n_k; ++s) {
-      const float4 v = *(const float4 *)(P + s * slice + at);
-      sum.x += v.x; sum.y += v.y; sum.z += v.z; sum.w += v.w;
-    }
-    float res[4];
-    unpack4(*(const uint2 *)(R + at), res);
-    const uint2 packed = pack4(sum.x + res[0], sum.y + res[1], sum.z + res[2], sum.w + res[3]);
-    *(uint2 *)(Y + at) = packed;
-    float y[4];
-    unpack4(packed, y);
-    ss += y[0] * y[0] + y[1] * y[1] + y[2] * y[2] + y[3] * y[3];
-  }
-  if (!gain) return;
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  if ((tid & 63) == 0) red[tid >> 6] = ss;
-  __syncthreads();
-  const float r = 1.0f / sqrtf((red[0] + red[1] + red[2] + red[3]) / (float)N + eps);
-  for (int c = tid * 4; c < N; c += 1024) {
-    const size_t at = (size_t)row * N + c;
-    float y[4], gq[4];
-    unpack4(*(const uint2 *)(Y + at), y);  // this thread's own stores
-    unpack4(*(const uint2 *)(gain + c), gq);
-    *(uint2 *)(Yn + at) = pack4(y[0] * r * gq[0], y[1] * r * gq[1], y[2] * r * gq[2], y[3] * r * gq[3]);
-  }
-}
-
-// act[m][f] = silu(sum of gate slices) * (sum of up slices); slices are [n_k][M][2F] with the up half at column F.
-__global__ __launch_bounds__(256) void reduce_swiglu_kernel(const float *__restrict__ P, int n_k, int M, int F,
-                                                            __bf16 *__restrict__ Y) {
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int per_row = F / 4;
-  if (gid >= (long)M * per_row) return;
-  const int m = (int)(gid / per_row), f = (int)(gid - (long)m * per_row) * 4;
-  const size_t slice = (size_t)M * 2 * F, at = (size_t)m * 2 * F + f;
-  float4 gt = *(const float4 *)(P + at), up = *(const float4 *)(P + at + F);
-#pragma unroll 4
-  for (int s = 1; s < n_k; ++s) {
-    const float4 a = *(const float4 *)(P + s * slice + at), b = *(const float4 *)(P + s * slice + at + F);
-    gt.x += a.x; gt.y += a.y; gt.z += a.z; gt.w += a.w;
-    up.x += b.x; up.y += b.y; up.z += b.z; up.w += b.w;
-  }
-  *(uint2 *)(Y + (size_t)m * F + f) = pack4(gt.x / (1.0f + __expf(-gt.x)) * up.x, gt.y / (1.0f + __expf(-gt.y)) * up.y,
-                                            gt.z / (1.0f + __expf(-gt.z)) * up.z, gt.w / (1.0f + __expf(-gt.w)) * up.w);
 }
 
 bool aligned16(const void *p) { return ((uintptr_t)p % 16) == 0; }
@@ -280,15 +217,29 @@ pc_status launch_linear_swiglu(percache_ctx *ctx, const __bf16 *a, const __bf16 
   return PC_OK;
 }
 
-pc_status launch_reduce_residual_norm(percache_ctx *ctx, const float *part, int n_k, int M, int N, const __bf16 *res, __bf16 *y,
-                                      const __bf16 *gain, __bf16 *yn, float eps, hipStream_t s) {
-  hipLaunchKernelGGL(reduce_residual_norm_kernel, dim3(M), dim3(256), 0, s, part, n_k, M, N, res, y, gain, yn, eps);
+pc_status launch_residual_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *w, const __bf16 *res, __bf16 *y, int M, int N, int K,
+                              hipStream_t s) {
+  const pc::few::Choice c = pc::few::choose_tile(ctx->n_cu, M, N / 16, 1);
+  const int n_wt = N / (16 * c.nf), n_tt = (M + 16 * c.nt - 1) / (16 * c.nt);
+#define PC_FEW(NF, NT)                                                                                                        \
+  if (c.nf == NF && c.nt == NT)                                                                                               \
+  hipLaunchKernelGGL((linear_residual_few_kernel<NF, NT>), dim3(pc::few::grid_of(n_wt, n_tt)), dim3(64 * pc::few::Form<NF, NT>::WV), 0, s, a, w, \
+                     res, y, M, N, K, n_wt, n_tt)
+  PC_FEW(1, 1); else PC_FEW(2, 1); else PC_FEW(1, 2); else PC_FEW(2, 2); else PC_FEW(2, 4); else PC_FEW(4, 4);
+#undef PC_FEW
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
-pc_status launch_reduce_swiglu(percache_ctx *ctx, const float *part, int n_k, int M, int F, __bf16 *y, hipStream_t s) {
-  const long threads = (long)M * (F / 4);
-  hipLaunchKernelGGL(reduce_swiglu_kernel, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, s, part, n_k, M, F, y);
+pc_status launch_swiglu_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *gain, float eps, const __bf16 *wg, const __bf16 *wu, __bf16 *y, int M,
+                            int F, int K, hipStream_t s) {
+  const pc::few::Choice c = pc::few::choose_tile(ctx->n_cu, M, 2 * F / 16, 2);
+  const int n_wt = 2 * F / (16 * c.nf), n_tt = (M + 16 * c.nt - 1) / (16 * c.nt);
+#define PC_FEW(NF, NT)                                                                                                    \
+  if (c.nf == NF && c.nt == NT)                                                                                           \
+  hipLaunchKernelGGL((swiglu_few_kernel<NF, NT>), dim3(pc::few::grid_of(n_wt, n_tt)), dim3(64 * pc::few::Form<NF, NT>::WV), 0, s, a, gain, eps, \
+                     wg, wu, y, M, F, K, n_wt, n_tt)
+  PC_FEW(2, 1); else PC_FEW(2, 2); else PC_FEW(2, 4); else PC_FEW(4, 4);
+#undef PC_FEW
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
@@ -300,7 +251,6 @@ struct StackWs {
   __bf16 *attn;    // [M, Hq*D]
   __bf16 *mid;     // [M, H]
   __bf16 *act;     // [M, F]
-  float *part;     // split-k slices of the block projections (few token rows only)
   size_t total;
 };
 StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fresh, int max_chunks, int ffn) {
@@ -315,46 +265,11 @@ StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fre
   w.attn = take(M * c.n_q_heads * c.head_dim * 2);
   w.mid = take(M * c.hidden * 2);
   w.act = take(M * ffn * 2);
-  const size_t widest = (size_t)(2 * ffn > c.hidden ? 2 * ffn : c.hidden);
-  w.part = (float *)take(pc::splitk_applies((int)M) ? (size_t)pc::kMaxSplitK * M * widest * sizeof(float) : 0);
   w.total = off;
   return w;
 }
 
 }  // namespace
-
-namespace pc {
-
-// Largest number of slices that divides the k steps, leaves every workgroup at least two of them and keeps the
-// launch within one workgroup per CU (more slices only add fp32 partials to write and read back).
-int choose_split_k(int n_cu, int n_tiles, int k_steps) {
-  int best = 1;
-  for (int d = 1; d <= kMaxSplitK; ++d)
-    if (k_steps % d == 0 && k_steps / d >= 2 && (long)n_tiles * d <= n_cu) best = d;
-  return best;
-}
-
-pc_status launch_splitk_partial(percache_ctx *ctx, const __bf16 *a, int lda, const __bf16 *w0, const __bf16 *w1, int n_split,
-                                int ldw, float *part, int M, int N, int K, int n_k, hipStream_t stream) {
-  if (N % BF || n_split % BF || K % (pc::gemm::BK * n_k)) return fail(ctx, PC_ESHAPE, "split-k projection: N %d, K %d, slices %d", N, K, n_k);
-  const int k_slice = K / n_k;
-  // LDS stages: all k-steps of a workgroup in flight at once when there are up to four of them
-  const bool deep = k_slice / pc::gemm::BK > 2;
-#define PC_SPLITK(NTB, NS) \
-  hipLaunchKernelGGL((splitk_partial_kernel<NTB, NS>), grid, dim3(256), 0, stream, a, lda, w0, w1, n_split, ldw, part, M, N, k_slice)
-  if (M > 64) {
-    dim3 grid(N / BF, n_k, (M + 127) / 128);
-    if (deep) PC_SPLITK(2, 4); else PC_SPLITK(2, 2);
-  } else {
-    dim3 grid(N / BF, n_k, 1);
-    if (deep) PC_SPLITK(1, 4); else PC_SPLITK(1, 2);
-  }
-#undef PC_SPLITK
-  PC_HIP(ctx, hipGetLastError());
-  return PC_OK;
-}
-
-}  // namespace pc
 
 extern "C" {
 
@@ -485,17 +400,18 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
   for (int l = 0; l < n_layers; ++l) {
     const percache_block_weights &w = layers_host[l];
 #define PC_TRY(call) do { st = (call); if (st != PC_OK) return st; } while (0)
-    // few token rows: split-k projections, whose reduce kernels also apply the residual and the next RMSNorm
-    const bool skinny = pc::splitk_applies(M) && ffn % BF == 0;
-    if (!skinny || l == 0) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
+    // few token rows: one launch per projection, the RMSNorms folded into the projections behind them
+    const bool few = pc::few_rows(M);
+    if (!few) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
     bool v_blocked = false;
     pc::QkvExtras extras;
     extras.bias = (const __bf16 *)w.qkv_bias;
     extras.q_norm = (const __bf16 *)w.q_norm;
     extras.k_norm = (const __bf16 *)w.k_norm;
     extras.eps = eps;
-    PC_TRY(pc::launch_qkv_rope(ctx, ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k, ws.pf.v, s,
-                               skinny ? ws.pf.gemm_part : nullptr, extras, ws.pf.v_blk, &v_blocked));
+    extras.pre_norm = few ? (const __bf16 *)w.gain1 : nullptr;
+    PC_TRY(pc::launch_qkv_rope(ctx, few ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
+                               ws.pf.v, s, extras, ws.pf.v_blk, &v_blocked));
     if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
     PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v_blk, batch, t_fresh, ws.pf.table, stride, min_tiles, 0, ws.attn,
                                 ws.pf.part_o, ws.pf.part_ml, s, formats));
@@ -517,25 +433,10 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
       PC_TRY(pc::launch_kv_append(ctx, l, slot, ws.pf.k + at, ws.pf.v + at, have, t_fresh, (long)t_fresh * c.head_dim, s));
       ctx->slot_len[(size_t)l * c.n_slots + slot] = have + t_fresh;
     }
-    if (skinny) {
-      const int m_tiles = M > 128 ? 2 : 1;
-      const __bf16 *next_gain = l + 1 < n_layers ? (const __bf16 *)layers_host[l + 1].gain1 : nullptr;
-      int nk = pc::choose_split_k(ctx->n_cu, H / BF * m_tiles, A / pc::gemm::BK);
-      PC_TRY(pc::launch_splitk_partial(ctx, ws.attn, A, (const __bf16 *)w.wo, (const __bf16 *)w.wo, H, A, ws.part, (int)M, H, A, nk, s));
-      PC_TRY(launch_reduce_residual_norm(ctx, ws.part, nk, (int)M, H, h_cur, ws.mid, (const __bf16 *)w.gain2, ws.normed, eps, s));
-      if (M > 64 && ffn % 16 == 0) {
-        // many features, short contraction: one pass with 32 weight rows per workgroup beats slices + a second kernel
-        hipLaunchKernelGGL(swiglu_skinny_kernel, dim3(ffn / 16, m_tiles), dim3(256), 0, s, ws.normed, (const __bf16 *)w.w_gate,
-                           (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H);
-        PC_HIP(ctx, hipGetLastError());
-      } else {
-        nk = pc::choose_split_k(ctx->n_cu, 2 * ffn / BF * m_tiles, H / pc::gemm::BK);
-        PC_TRY(pc::launch_splitk_partial(ctx, ws.normed, H, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ffn, H, ws.part, (int)M, 2 * ffn, H, nk, s));
-        PC_TRY(launch_reduce_swiglu(ctx, ws.part, nk, (int)M, ffn, ws.act, s));
-      }
-      nk = pc::choose_split_k(ctx->n_cu, H / BF * m_tiles, ffn / pc::gemm::BK);
-      PC_TRY(pc::launch_splitk_partial(ctx, ws.act, ffn, (const __bf16 *)w.w_down, (const __bf16 *)w.w_down, H, ffn, ws.part, (int)M, H, ffn, nk, s));
-      PC_TRY(launch_reduce_residual_norm(ctx, ws.part, nk, (int)M, H, ws.mid, h_out, next_gain, ws.normed, eps, s));
+    if (few) {
+      PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
+      PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
+      PC_TRY(launch_residual_few(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
     } else {
       PC_TRY(launch_linear_residual(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
       PC_TRY(launch_rmsnorm(ctx, ws.mid, (const __bf16 *)w.gain2, ws.normed, (int)M, H, eps, s));

@@ -61,8 +61,7 @@ template <> struct Vec8<_Float16> { typedef f16x8 type; };
 // m0 .. m0 + BT - 1 (clamped to M - 1 when reading); K elements are contracted.
 // On return acc[a][t] holds features (a ? fb_hi : fb_lo) * 32 + (r/4)*8 + 4*(lane/32) + r%4 of token
 // m0 + (wt*NTB + t)*32 + lane%32 in element r.
-// NTW: the weight rows are streamed with the non-temporal policy (use when no other workgroup re-reads them soon).
-template <int NTB, bool NTW = false, class T, class WRow>
+template <int NTB, class T, class WRow>
 __device__ __forceinline__ void mainloop(char *lds, WRow w_row, const T *__restrict__ X, int ldx, int m0, int M, int K,
                                          int fb_lo, int fb_hi, f32x16 (&acc)[2][NTB]) {
   using S = Shape<NTB>;
@@ -90,7 +89,7 @@ __device__ __forceinline__ void mainloop(char *lds, WRow w_row, const T *__restr
 #pragma unroll
     for (int k = 0; k < S::W_INSTR; ++k)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(w_src[k] + kt * BK),
-                                       (__attribute__((address_space(3))) void *)(base + (wave + k * NW) * 1024), 16, 0, NTW ? 2 : 0);
+                                       (__attribute__((address_space(3))) void *)(base + (wave + k * NW) * 1024), 16, 0, 0);
 #pragma unroll
     for (int k = 0; k < S::X_INSTR; ++k)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(x_src[k] + kt * BK),
@@ -264,172 +263,6 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
   }
   wait_vmcnt0();  // (the surplus request of the last k-steps)
   __builtin_amdgcn_s_barrier();
-}
-
-// The same contraction for workgroups that own only a few k-steps (a slice of a split contraction): NS LDS stages,
-// all of them requested before the first MFMA, so that a workgroup with up to NS k-steps pays one memory latency
-// instead of one per step.  A stage is refilled (k-step kt + NS) once every wavefront has finished reading it.
-// Arguments and result as for mainloop(); the LDS buffer holds NS * Shape<NTB>::STAGE bytes.
-template <int NTB, bool NTW, int NS, class T, class WRow>
-__device__ __forceinline__ void mainloop_deep(char *lds, WRow w_row, const T *__restrict__ X, int ldx, int m0, int M,
-                                              int K, int fb_lo, int fb_hi, f32x16 (&acc)[2][NTB]) {
-  using S = Shape<NTB>;
-  using V8 = typename Vec8<T>::type;
-  static_assert(NS >= 2 && NS <= 4 && (NS - 1) * S::INSTR < 64, "stage count");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int wt = wave >> 1;
-  const int l32 = lane & 31, g = lane >> 5;
-  const T *w_src[S::W_INSTR];
-  const T *x_src[S::X_INSTR];
-#pragma unroll
-  for (int k = 0; k < S::W_INSTR; ++k) {
-    const int row = (wave + k * NW) * 8 + (lane >> 3);
-    w_src[k] = w_row(row) + (((lane & 7) ^ swz128(row)) * 8);
-  }
-#pragma unroll
-  for (int k = 0; k < S::X_INSTR; ++k) {
-    const int row = (wave + k * NW) * 8 + (lane >> 3);
-    x_src[k] = X + (size_t)min(m0 + row, M - 1) * ldx + (((lane & 7) ^ swz128(row)) * 8);
-  }
-  auto fetch = [&](int kt, int st) __attribute__((always_inline)) {
-    char *base = lds + st * S::STAGE;
-#pragma unroll
-    for (int k = 0; k < S::W_INSTR; ++k)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(w_src[k] + kt * BK),
-                                       (__attribute__((address_space(3))) void *)(base + (wave + k * NW) * 1024), 16, 0, NTW ? 2 : 0);
-#pragma unroll
-    for (int k = 0; k < S::X_INSTR; ++k)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(x_src[k] + kt * BK),
-                                       (__attribute__((address_space(3))) void *)(base + S::W_BYTES + (wave + k * NW) * 1024), 16, 0, 0);
-  };
-  int rd[BK / 16];
-#pragma unroll
-  for (int ks = 0; ks < BK / 16; ++ks) rd[ks] = ((2 * ks + g) ^ swz128(l32)) * 16;
-#pragma unroll
-  for (int a = 0; a < 2; ++a)
-#pragma unroll
-    for (int t = 0; t < NTB; ++t)
-#pragma unroll
-      for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
-
-  const int nk = K / BK;
-#pragma unroll
-  for (int s = 0; s < NS; ++s)
-    if (s < nk) fetch(s, s);
-  int st = 0;
-  for (int kt = 0; kt < nk; ++kt) {
-    // k-step kt has landed once at most the loads of the (up to NS - 1) later steps in flight are outstanding
-    const int later = min(NS - 1, nk - 1 - kt);
-    if (later >= 3) wait_vmcnt<(NS > 3 ? 3 : 0) * S::INSTR>();
-    else if (later == 2) wait_vmcnt<(NS > 2 ? 2 : 0) * S::INSTR>();
-    else if (later == 1) wait_vmcnt<S::INSTR>();
-    else wait_vmcnt0();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();
-    asm volatile("" ::: "memory");
-    const char *wl = lds + st * S::STAGE + (fb_lo * 32 + l32) * ROW;
-    const char *wh = lds + st * S::STAGE + (fb_hi * 32 + l32) * ROW;
-    const char *xb = lds + st * S::STAGE + S::W_BYTES + ((wt * NTB) * 32 + l32) * ROW;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      V8 a_lo = *(const V8 *)(wl + rd[ks]);
-      V8 a_hi = *(const V8 *)(wh + rd[ks]);
-#pragma unroll
-      for (int t = 0; t < NTB; ++t) {
-        V8 b = *(const V8 *)(xb + t * 32 * ROW + rd[ks]);
-        acc[0][t] = mma(a_lo, b, acc[0][t]);
-        acc[1][t] = mma(a_hi, b, acc[1][t]);
-      }
-    }
-    if (kt + NS < nk) {
-      asm volatile("" ::: "memory");
-      __builtin_amdgcn_s_barrier();  // every wavefront has read this stage
-      asm volatile("" ::: "memory");
-      fetch(kt + NS, st);
-    }
-    st = st + 1 == NS ? 0 : st + 1;
-  }
-}
-
-// Few token rows, many output features: the weight stream bounds the projection, and it takes many workgroups to pull
-// it.  Here a workgroup owns only 32 weight rows -- N/32 workgroups -- and up to 128 token rows over the WHOLE
-// contraction (no slices to add up afterwards); wavefront w owns token block w.  NS stages of 64 k-elements
-// (4 KB of weights + 16 KB of tokens each), NS - 1 of them in flight, one barrier per k-step.
-//   w_row(r): the K contiguous elements of the weight row that tile row r (0..31) stands for.
-//   On return acc[r] = tile row (r/4)*8 + 4*(lane/32) + r%4 of token m0 + 32*wave + lane%32.
-struct Skinny {
-  static constexpr int W_BYTES = 32 * ROW, X_BYTES = 128 * ROW, STAGE = W_BYTES + X_BYTES;
-  static constexpr int INSTR = 1 + X_BYTES / 1024 / NW;  // direct-to-LDS load instructions per wavefront and stage
-};
-template <int NS, class T, class WRow>
-__device__ __forceinline__ void mainloop_skinny(char *lds, WRow w_row, const T *__restrict__ X, int ldx, int m0, int M, int K,
-                                                f32x16 &acc) {
-  using S = Skinny;
-  using V8 = typename Vec8<T>::type;
-  static_assert(NS >= 2 && NS <= 7 && (NS - 1) * S::INSTR < 64, "stage count");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const int l32 = lane & 31, g = lane >> 5;
-  constexpr int XI = S::X_BYTES / 1024 / NW;
-  const T *w_src;
-  const T *x_src[XI];
-  {
-    const int row = wave * 8 + (lane >> 3);  // the 32 weight rows: one load instruction per wavefront
-    w_src = w_row(row) + (((lane & 7) ^ swz128(row)) * 8);
-  }
-#pragma unroll
-  for (int k = 0; k < XI; ++k) {
-    const int row = (wave + k * NW) * 8 + (lane >> 3);
-    x_src[k] = X + (size_t)min(m0 + row, M - 1) * ldx + (((lane & 7) ^ swz128(row)) * 8);
-  }
-  const int nk = K / BK;
-  auto fetch = [&](int kt, int st) __attribute__((always_inline)) {
-    char *base = lds + st * S::STAGE;
-    __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(w_src + kt * BK),
-                                     (__attribute__((address_space(3))) void *)(base + wave * 1024), 16, 0, 2);
-#pragma unroll
-    for (int k = 0; k < XI; ++k)
-      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(x_src[k] + kt * BK),
-                                       (__attribute__((address_space(3))) void *)(base + S::W_BYTES + (wave + k * NW) * 1024), 16, 0, 0);
-  };
-  int rd[BK / 16];
-#pragma unroll
-  for (int ks = 0; ks < BK / 16; ++ks) rd[ks] = ((2 * ks + g) ^ swz128(l32)) * 16;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] = 0.f;
-  // two accumulation chains (even / odd k-steps of 16): a lone chain would wait out every MFMA's latency
-  f32x16 acc_odd;
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc_odd[r] = 0.f;
-
-#pragma unroll
-  for (int s = 0; s < NS - 1; ++s)
-    if (s < nk) fetch(s, s);
-  int st = 0, fill = NS - 1;  // stage of k-step kt; stage that k-step kt + NS - 1 goes to (the one kt - 1 has left)
-  for (int kt = 0; kt < nk; ++kt) {
-    const int later = min(NS - 2, nk - 1 - kt);  // k-steps in flight behind this one
-    if (later >= 5) wait_vmcnt<(NS > 6 ? 5 : 0) * S::INSTR>();
-    else if (later == 4) wait_vmcnt<(NS > 5 ? 4 : 0) * S::INSTR>();
-    else if (later == 3) wait_vmcnt<(NS > 4 ? 3 : 0) * S::INSTR>();
-    else if (later == 2) wait_vmcnt<(NS > 3 ? 2 : 0) * S::INSTR>();
-    else if (later == 1) wait_vmcnt<(NS > 2 ? 1 : 0) * S::INSTR>();
-    else wait_vmcnt0();
-    asm volatile("" ::: "memory");
-    __builtin_amdgcn_s_barrier();  // k-step kt has landed for everyone, and everyone has left the stage of kt - 1
-    asm volatile("" ::: "memory");
-    if (kt + NS - 1 < nk) fetch(kt + NS - 1, fill);
-    const char *wb = lds + st * S::STAGE + l32 * ROW;
-    const char *xb = lds + st * S::STAGE + S::W_BYTES + (wave * 32 + l32) * ROW;
-#pragma unroll
-    for (int ks = 0; ks < BK / 16; ++ks) {
-      const V8 a = *(const V8 *)(wb + rd[ks]);
-      const V8 b = *(const V8 *)(xb + rd[ks]);
-      if (ks & 1) acc_odd = mma(a, b, acc_odd); else acc = mma(a, b, acc);
-    }
-    st = st + 1 == NS ? 0 : st + 1;
-    fill = fill + 1 == NS ? 0 : fill + 1;
-  }
-#pragma unroll
-  for (int r = 0; r < 16; ++r) acc[r] += acc_odd[r];
 }
 
 }  // namespace gemm

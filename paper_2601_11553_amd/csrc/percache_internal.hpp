@@ -132,7 +132,6 @@ struct PrefillWs {
   int32_t *table;
   __bf16 *q, *k, *v;
   __bf16 *v_blk;   // fresh V as 64-key blocks [B*Hkv][ceil(T/64)][D][64]
-  float *gemm_part;  // split-k slices of the QKV projection (few token rows only), else unused
   __bf16 *part_o;  // [rows][splits][D], normalised per split
   float *part_ml;  // [rows][splits][2]
   int max_splits;  // partitions of the key axis the partial buffers can hold
@@ -154,23 +153,19 @@ void prof_end(percache_ctx *ctx, int kind, hipStream_t stream);
 // dimension of every q / k head with gains [D] before RoPE.  Null pointers switch a part off.
 struct QkvExtras {
   const __bf16 *bias = nullptr, *q_norm = nullptr, *k_norm = nullptr;
+  const __bf16 *pre_norm = nullptr;  // gain of an RMSNorm of the input rows (few token rows only; else they come normed)
   float eps = 1e-6f;
   bool any() const { return bias || q_norm || k_norm; }
 };
-// gemm_part: workspace for the split-k path (nullptr: always the single-pass kernel)
-// v_blk / v_blk_done: if given, the launch may also write V as the 64-key blocks of launch_v_repack and says so
+// Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in.
+inline bool few_rows(long M) { return M <= 192; }
+// v_blk / v_blk_done: if given, the launch may also write V as the 64-key blocks of launch_v_repack and says so.
+// extras.pre_norm only where few_rows(batch * t_fresh).
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,
-                          hipStream_t stream, float *gemm_part = nullptr, const QkvExtras &extras = QkvExtras(),
-                          __bf16 *v_blk = nullptr, bool *v_blk_done = nullptr);
+                          hipStream_t stream, const QkvExtras &extras = QkvExtras(), __bf16 *v_blk = nullptr,
+                          bool *v_blk_done = nullptr);
 
-// Split-k projections for few token rows (see block.hip).  P[s][m][n] = sum over slice s of A[m][k] W[n][k];
-// weight rows >= n_split come from w1.  Returns the number of slices written (chosen by choose_split_k).
-constexpr int kMaxSplitK = 16;
-inline bool splitk_applies(long M) { return M <= 192; }
-int choose_split_k(int n_cu, int n_tiles, int k_steps);
-pc_status launch_splitk_partial(percache_ctx *ctx, const __bf16 *a, int lda, const __bf16 *w0, const __bf16 *w1, int n_split,
-                                int ldw, float *part, int M, int N, int K, int n_k, hipStream_t stream);
 pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, int batch, int t_fresh, hipStream_t stream);
 // formats: which slot formats the call's chunks sit in (see table_formats): bit 0 = 8-bit, bit 1 = bf16
 pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf_blk,

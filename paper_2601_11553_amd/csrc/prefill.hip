@@ -70,7 +70,7 @@ pc_status percache_qkv_rope(percache_ctx *ctx, const void *x_fresh_dev, const vo
   st = pc::upload_table(ctx, rows, p.ws.table, s);
   if (st != PC_OK) return st;
   return pc::launch_qkv_rope(ctx, (const __bf16 *)x_fresh_dev, (const __bf16 *)wqkv_dev, batch, t_fresh, p.ws.table,
-                             p.tbl_stride, (__bf16 *)q_out_dev, (__bf16 *)k_fresh_out_dev, (__bf16 *)v_fresh_out_dev, s, p.ws.gemm_part);
+                             p.tbl_stride, (__bf16 *)q_out_dev, (__bf16 *)k_fresh_out_dev, (__bf16 *)v_fresh_out_dev, s);
 }
 
 pc_status percache_attention_reuse(percache_ctx *ctx, int32_t layer, const void *q_dev, const void *k_fresh_dev,
@@ -127,7 +127,7 @@ static pc_status run_prefill(percache_ctx *ctx, int32_t layer, const void *x_fre
   __bf16 *vf = v_fresh_out_dev ? (__bf16 *)v_fresh_out_dev : p.ws.v;
   bool v_blocked = false;
   st = pc::launch_qkv_rope(ctx, (const __bf16 *)x_fresh_dev, (const __bf16 *)wqkv_dev, batch, t_fresh, p.ws.table,
-                           p.tbl_stride, p.ws.q, kf, vf, s, p.ws.gemm_part, pc::QkvExtras(), p.ws.v_blk, &v_blocked);
+                           p.tbl_stride, p.ws.q, kf, vf, s, pc::QkvExtras(), p.ws.v_blk, &v_blocked);
   if (st != PC_OK) return st;
   if (!v_blocked) st = pc::launch_v_repack(ctx, vf, p.ws.v_blk, batch, t_fresh, s);
   if (st != PC_OK) return st;

@@ -8,10 +8,11 @@
 // Tiling: the shared projection main loop (gemm_tile.hpp): a workgroup of 4 wavefronts computes 128 output
 // features x (64 or 128) tokens, and each wavefront owns a feature block together with its rotation partner
 // (m, m + D/2), so RoPE needs no cross-lane traffic.
-#include "gemm_tile.hpp"
+#include "few_rows.hpp"
 
 namespace {
 using pc::f32x16;
+using pc::f32x4;
 using pc::gemm::BF;
 using pc::gemm::pack4;
 
@@ -169,70 +170,142 @@ __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void qkv_rope_kerne
   }
 }
 
-// Few token rows (one or two 128-token tiles) without the bias / head-norm variants: one pass, no slices.  A workgroup
-// owns 32 weight rows = 16 rotation pairs of one head (rows j and j + 16 of the tile are features m and m + D/2), which a
-// lane finds in its accumulators r and r + 8, and all token rows of its tile (gemm_tile.hpp: mainloop_skinny).
-template <int D>
-__global__ __launch_bounds__(256, 2) void qkv_rope_skinny_kernel(const __bf16 *__restrict__ X, const __bf16 *__restrict__ W,
-                                                                 int M, int H, int t_fresh, int Hq, int Hkv,
-                                                                 const int32_t *__restrict__ table, int tbl_stride,
-                                                                 const float2 *__restrict__ rope, __bf16 *__restrict__ Q,
-                                                                 __bf16 *__restrict__ K, __bf16 *__restrict__ V,
-                                                                 __bf16 *__restrict__ V_blk) {
-  constexpr int NS = 5, TPH = D / 32;  // stages; tiles per head
-  __shared__ __align__(16) char lds[NS * pc::gemm::Skinny::STAGE];
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int l32 = lane & 31, g = lane >> 5;
-  const int head = blockIdx.x / TPH, sub = blockIdx.x % TPH;
-  const int m0 = blockIdx.y * 128;
-  f32x16 acc;
-  pc::gemm::mainloop_skinny<NS>(
-      lds,
-      [&](int row) __attribute__((always_inline)) {
-        return W + (size_t)(head * D + (row < 16 ? 0 : D / 2 - 16) + sub * 16 + row) * H;
-      },
-      X, H, m0, M, H, acc);
+// Few token rows: the whole projection in one launch (few_rows.hpp), the RMSNorm of the input rows folded in (NORM).
+// A tile holds 8 NF (8 at NF = 1) rotation pairs of one head: tile rows r and r + PAIRS are features m and m + D/2.  At
+// NF >= 2 a lane finds both in accumulator blocks f and f + NF/2, at NF = 1 the high half sits in lane + 32.
+// HEADNORM: the tile is a whole head (NF = D/16, NT = 1) and q and k rows are normalised over it before the rotation.
+template <int D, int NF, int NT, bool NORM, bool HEADNORM>
+__global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few_kernel(
+    const __bf16 *__restrict__ X, const __bf16 *__restrict__ W, int M, int H, int t_fresh, int Hq, int Hkv, const int32_t *__restrict__ table,
+    int tbl_stride, const float2 *__restrict__ rope, __bf16 *__restrict__ Q, __bf16 *__restrict__ K, __bf16 *__restrict__ V, pc::QkvExtras ex,
+    __bf16 *__restrict__ V_blk, int n_wt, int n_tt) {
+  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG;
+  constexpr int PAIRS = NF == 1 ? 8 : 8 * NF, TPH = D / 2 / PAIRS, NFP = NF == 1 ? 1 : NF / 2, PER = (NFP * NT + WV - 1) / WV;
+  static_assert(!HEADNORM || (NF * 16 == D && NT == 1 && NFP <= WV), "a whole head of one token block");
+  using Tile = pc::few::Tile<NF, NT, WV, NSTG, NORM>;
+  __shared__ __align__(16) char lds[Tile::LDS_BYTES];
+  int wt, tt;
+  if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
+  const int head = wt / TPH, sub = wt % TPH, m0 = tt * 16 * NT;
   __bf16 *dst;
   int hh, n_heads;
   bool rotate = true;
   if (head < Hq) { dst = Q; hh = head; n_heads = Hq; }
   else if (head < Hq + Hkv) { dst = K; hh = head - Hq; n_heads = Hkv; }
   else { dst = V; hh = head - Hq - Hkv; n_heads = Hkv; rotate = false; }
-  const int m_raw = m0 + wave * 32 + l32;
-  if (m_raw >= M) return;
-  const int b = m_raw / t_fresh, i = m_raw - b * t_fresh;
-  const int pos = table[(size_t)b * tbl_stride + 1] + i;
-  __bf16 *row = dst + (((size_t)b * n_heads + hh) * t_fresh + i) * D;
+
+  // what the epilogue needs of this wavefront's (pair block, token block) units: the cached length is asked for before the
+  // first requests, the (cos, sin) rows behind them
+  int q_b[PER], q_i[PER], l_pre[PER], first[PER];
+  float4 cs[PER][2];
 #pragma unroll
-  for (int q2 = 0; q2 < 2; ++q2) {
-    const int mm = sub * 16 + q2 * 8 + g * 4;  // first of this lane's 4 consecutive pair indices
-    float lo[4], hi[4];
-    float4 cs[2];
-    if (rotate) {
-      const float4 *csp = (const float4 *)(rope + (size_t)pos * (D / 2) + mm);
-      cs[0] = csp[0];
-      cs[1] = csp[1];
+  for (int j = 0; j < PER; ++j) {
+    const int b = min(wave + j * WV, NFP * NT - 1), m = min(m0 + b % NT * 16 + l16, M - 1);
+    q_b[j] = m / t_fresh;
+    q_i[j] = m - q_b[j] * t_fresh;
+    first[j] = sub * PAIRS + (NF == 1 ? 4 * (g & 1) : b / NT * 16 + 4 * g);  // first of this lane's 4 consecutive pairs
+    l_pre[j] = rotate ? table[(size_t)q_b[j] * tbl_stride + 1] : 0;
+  }
+  f32x4 acc[NF][NT];
+  float ss[NT];
+  pc::few::slice_product<NF, NT, WV, NSTG, NORM>(
+      lds,
+      [&](int r) __attribute__((always_inline)) {
+        return W + (size_t)(head * D + sub * PAIRS + (r < PAIRS ? r : D / 2 + r - PAIRS)) * H;
+      },
+      [&](int r) __attribute__((always_inline)) { return X + (size_t)min(m0 + r, M - 1) * H; }, ex.pre_norm, H, wave, lane,
+      [&]() __attribute__((always_inline)) {
+        if (!rotate) return;
+#pragma unroll
+        for (int j = 0; j < PER; ++j) {
+          const float4 *p = (const float4 *)(rope + (size_t)(l_pre[j] + q_i[j]) * (D / 2) + first[j]);
+          cs[j][0] = p[0];
+          cs[j][1] = p[1];
+        }
+      },
+      acc, ss);
+  pc::few::share_slices<NF, NT, WV, NSTG, NORM>(lds, wave, lane, acc, ss);
+  float head_r = 1.f;
+  const __bf16 *gain = nullptr;
+  float lo_n[4], hi_n[4];
+  if constexpr (HEADNORM) {  // one unit per wavefront: sums, bias, then the head's sum of squares over lanes and units
+    gain = head < Hq ? ex.q_norm : (head < Hq + Hkv ? ex.k_norm : nullptr);
+    float *hn = (float *)(lds + Tile::SUMS + Tile::SS);
+    static_assert(Tile::SUMS + Tile::SS + WV * 64 <= Tile::LDS_BYTES, "room for the head sums");
+    if (wave < NFP) {
+      const float r = NORM ? pc::few::row_factor<NF, NT, WV>(lds, 0, l16, H, ex.eps) : 1.f;
+      const f32x4 lo = pc::few::tile_sum<NF, NT, WV>(lds, wave, 0, lane) * r, hi = pc::few::tile_sum<NF, NT, WV>(lds, wave + NFP, 0, lane) * r;
+      float s = 0.f;
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo_n[e] = lo[e] + (ex.bias ? (float)ex.bias[(size_t)head * D + first[0] + e] : 0.f);
+        hi_n[e] = hi[e] + (ex.bias ? (float)ex.bias[(size_t)head * D + first[0] + e + D / 2] : 0.f);
+        s += lo_n[e] * lo_n[e] + hi_n[e] * hi_n[e];
+      }
+      s += __shfl_xor(s, 16, 64);
+      s += __shfl_xor(s, 32, 64);
+      if (g == 0) hn[wave * 16 + l16] = s;
     }
+    __syncthreads();
+    if (gain) {
+      float s = 0.f;
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = acc[q2 * 4 + e], c = acc[8 + q2 * 4 + e];
-      if (rotate) {
-        const float4 w4 = cs[e >> 1];
-        const float wc = (e & 1) ? w4.z : w4.x, ws = (e & 1) ? w4.w : w4.y;
-        lo[e] = a * wc - c * ws;
-        hi[e] = c * wc + a * ws;
+      for (int w = 0; w < NFP; ++w) s += hn[w * 16 + l16];
+      head_r = 1.0f / sqrtf(s / (float)D + ex.eps);
+    }
+  }
+#pragma unroll
+  for (int j = 0; j < PER; ++j) {
+    const int b = wave + j * WV;
+    if (b >= NFP * NT) continue;
+    const int t = b % NT, mm = first[j];
+    float lo[4], hi[4];
+    if constexpr (HEADNORM) {
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[e] = lo_n[e] * (gain ? head_r * (float)gain[mm + e] : 1.f);
+        hi[e] = hi_n[e] * (gain ? head_r * (float)gain[mm + e + D / 2] : 1.f);
+      }
+    } else {
+      const float r = NORM ? pc::few::row_factor<NF, NT, WV>(lds, t, l16, H, ex.eps) : 1.f;
+      f32x4 sl = pc::few::tile_sum<NF, NT, WV>(lds, NF == 1 ? 0 : b / NT, t, lane), sh;
+      if constexpr (NF == 1) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) sh[e] = __shfl_xor(sl[e], 32, 64);
       } else {
-        lo[e] = a;
-        hi[e] = c;
+        sh = pc::few::tile_sum<NF, NT, WV>(lds, b / NT + NFP, t, lane);
+      }
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        lo[e] = sl[e] * r;
+        hi[e] = sh[e] * r;
+      }
+      if (ex.bias) {
+#pragma unroll
+        for (int e = 0; e < 4; ++e) {
+          lo[e] += (float)ex.bias[(size_t)head * D + mm + e];
+          hi[e] += (float)ex.bias[(size_t)head * D + mm + e + D / 2];
+        }
       }
     }
+    if (rotate) {
+      const float wc[4] = {cs[j][0].x, cs[j][0].z, cs[j][1].x, cs[j][1].z}, ws[4] = {cs[j][0].y, cs[j][0].w, cs[j][1].y, cs[j][1].w};
+#pragma unroll
+      for (int e = 0; e < 4; ++e) {
+        const float a = lo[e], c = hi[e];
+        lo[e] = a * wc[e] - c * ws[e];
+        hi[e] = c * wc[e] + a * ws[e];
+      }
+    }
+    if (m0 + t * 16 + l16 >= M || (NF == 1 && g >= 2)) continue;
+    const int i = q_i[j];
+    __bf16 *row = dst + (((size_t)q_b[j] * n_heads + hh) * t_fresh + i) * D;
     *(uint2 *)(row + mm) = pack4(lo[0], lo[1], lo[2], lo[3]);
     *(uint2 *)(row + mm + D / 2) = pack4(hi[0], hi[1], hi[2], hi[3]);
-    if (V_blk && !rotate) {
-      // the 64-key blocks [D][64] the attention kernel reads for the fresh part (t_fresh is a multiple of 64 here:
-      // no padding to write), saving the repack launch
+    if (V_blk && !rotate) {  // also as the 64-key blocks [D][64] the attention kernel reads for the fresh part
       const int tin = i & 63;
-      __bf16 *vb = V_blk + ((((size_t)b * n_heads + hh) * (t_fresh >> 6) + (i >> 6)) * D) * 64 + (tin & ~15) + pc::blocked_key(tin & 15);
+      __bf16 *vb = V_blk + ((((size_t)q_b[j] * n_heads + hh) * ((t_fresh + 63) >> 6) + (i >> 6)) * D) * 64 + (tin & ~15) + pc::blocked_key(tin & 15);
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
         vb[(size_t)(mm + e) * 64] = (__bf16)lo[e];
@@ -240,85 +313,25 @@ __global__ __launch_bounds__(256, 2) void qkv_rope_skinny_kernel(const __bf16 *_
       }
     }
   }
-}
-
-// Epilogue of the split-k path (few token rows): adds the fp32 slices P[s][m][f] in a fixed order, rotates q and k
-// exactly as above, rounds once.  One thread per (token, head, 4 consecutive rotation pairs).
-template <int D>
-__global__ __launch_bounds__(256) void reduce_rope_kernel(const float *__restrict__ P, int n_k, int M, int F, int t_fresh, int Hq,
-                                                          int Hkv, const int32_t *__restrict__ table, int tbl_stride,
-                                                          const float2 *__restrict__ rope, __bf16 *__restrict__ Q,
-                                                          __bf16 *__restrict__ K, __bf16 *__restrict__ V, pc::QkvExtras ex,
-                                                          __bf16 *__restrict__ V_blk) {
-  constexpr int QUADS = D / 8;
-  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  const int n_heads_all = Hq + 2 * Hkv;
-  if (gid >= (long)M * n_heads_all * QUADS) return;
-  const int j = (int)(gid % QUADS);
-  const long r = gid / QUADS;
-  const int head = (int)(r % n_heads_all), m = (int)(r / n_heads_all);
-  const int mm = 4 * j;
-  const size_t slice = (size_t)M * F, at = (size_t)m * F + (size_t)head * D + mm;
-  float4 lo = *(const float4 *)(P + at), hi = *(const float4 *)(P + at + D / 2);
-#pragma unroll 4
-  for (int s = 1; s < n_k; ++s) {
-    const float4 a = *(const float4 *)(P + s * slice + at), c = *(const float4 *)(P + s * slice + at + D / 2);
-    lo.x += a.x; lo.y += a.y; lo.z += a.z; lo.w += a.w;
-    hi.x += c.x; hi.y += c.y; hi.z += c.z; hi.w += c.w;
-  }
-  const int b = m / t_fresh, i = m - b * t_fresh;
-  __bf16 *dst;
-  int hh, n_heads;
-  bool rotate = true;
-  if (head < Hq) { dst = Q; hh = head; n_heads = Hq; }
-  else if (head < Hq + Hkv) { dst = K; hh = head - Hq; n_heads = Hkv; }
-  else { dst = V; hh = head - Hq - Hkv; n_heads = Hkv; rotate = false; }
-  float l4[4] = {lo.x, lo.y, lo.z, lo.w}, h4[4] = {hi.x, hi.y, hi.z, hi.w};
-  if (ex.bias) {
+  if (V_blk && !rotate && t_fresh & 63) {
+    // zeros behind the last token of every query that ends in this tile (masked probabilities multiply them), 8 keys at a
+    // time: chunk c of a row holds keys 16 (c/2) + 4 (c%2) + {0-3, 8-11}
+    const int m_end = min(m0 + 16 * NT, M), tail = t_fresh & 63, blocks = (t_fresh + 63) >> 6;
+    for (int b = m0 / t_fresh; (b + 1) * t_fresh <= m_end; ++b) {
+      if ((b + 1) * t_fresh <= m0) continue;
+      __bf16 *vb = V_blk + (((size_t)b * n_heads + hh) * blocks + blocks - 1) * D * 64;
+      for (int u = tid; u < 2 * PAIRS * 8; u += 64 * WV) {
+        const int r = u >> 3, c = u & 7, feat = sub * PAIRS + (r < PAIRS ? r : D / 2 + r - PAIRS), k0 = 16 * (c >> 1) + 4 * (c & 1);
+        if (k0 + 11 < tail) continue;
+        __bf16 *at = vb + (size_t)feat * 64 + c * 8;
+        if (k0 >= tail) {
+          *(uint4 *)at = make_uint4(0, 0, 0, 0);
+        } else {
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      l4[e] += (float)ex.bias[(size_t)head * D + mm + e];
-      h4[e] += (float)ex.bias[(size_t)head * D + mm + e + D / 2];
-    }
-  }
-  const __bf16 *gain = head < Hq ? ex.q_norm : (head < Hq + Hkv ? ex.k_norm : nullptr);
-  if (ex.q_norm || ex.k_norm) {  // uniform: the QUADS consecutive threads of a (token, head) reduce together
-    float ss = 0.f;
-#pragma unroll
-    for (int e = 0; e < 4; ++e) ss += l4[e] * l4[e] + h4[e] * h4[e];
-#pragma unroll
-    for (int o = 1; o < QUADS; o <<= 1) ss += __shfl_xor(ss, o, 64);
-    if (gain) {
-      const float rr = 1.0f / sqrtf(ss / (float)D + ex.eps);
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        l4[e] *= rr * (float)gain[mm + e];
-        h4[e] *= rr * (float)gain[mm + e + D / 2];
+          for (int e = 0; e < 8; ++e)
+            if (k0 + (e & 3) + 8 * (e >> 2) >= tail) at[e] = (__bf16)0.f;
+        }
       }
-    }
-  }
-  if (rotate) {
-    const int pos = table[(size_t)b * tbl_stride + 1] + i;
-    const float4 *csp = (const float4 *)(rope + (size_t)pos * (D / 2) + mm);
-    const float4 c01 = csp[0], c23 = csp[1];  // (cos, sin) of pairs mm, mm+1 and mm+2, mm+3
-    const float wc[4] = {c01.x, c01.z, c23.x, c23.z}, wsn[4] = {c01.y, c01.w, c23.y, c23.w};
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      const float a = l4[e], c = h4[e];
-      l4[e] = a * wc[e] - c * wsn[e];
-      h4[e] = c * wc[e] + a * wsn[e];
-    }
-  }
-  __bf16 *row = dst + (((size_t)b * n_heads + hh) * t_fresh + i) * D;
-  *(uint2 *)(row + mm) = pack4(l4[0], l4[1], l4[2], l4[3]);
-  *(uint2 *)(row + mm + D / 2) = pack4(h4[0], h4[1], h4[2], h4[3]);
-  if (V_blk && !rotate) {  // also as the 64-key blocks [D][64] of the attention kernel (t_fresh is a multiple of 64 here)
-    const int tin = i & 63;
-    __bf16 *vb = V_blk + ((((size_t)b * n_heads + hh) * (t_fresh >> 6) + (i >> 6)) * D) * 64 + (tin & ~15) + pc::blocked_key(tin & 15);
-#pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      vb[(size_t)(mm + e) * 64] = (__bf16)l4[e];
-      vb[(size_t)(mm + e + D / 2) * 64] = (__bf16)h4[e];
     }
   }
 }
@@ -329,7 +342,7 @@ namespace pc {
 
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,
-                          hipStream_t stream, float *gemm_part, const QkvExtras &extras, __bf16 *v_blk, bool *v_blk_done) {
+                          hipStream_t stream, const QkvExtras &extras, __bf16 *v_blk, bool *v_blk_done) {
   if (v_blk_done) *v_blk_done = false;
   const percache_config &c = ctx->cfg;
   const int M = batch * t_fresh;
@@ -338,39 +351,30 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
   if ((long)F * c.hidden >= (1L << 31) || (long)M * c.hidden >= (1L << 31))
     return fail(ctx, PC_ESHAPE, "operand larger than 2^31 elements");
   const float2 *rope = (const float2 *)ctx->rope;
-  if (gemm_part && splitk_applies(M) && M > 64 && !extras.any()) {
-    // one or two 128-token tiles: weight-stream bound; one pass with 32 weight rows per workgroup (with at most 64
-    // rows the slices below are faster: they do not pay for a 128-token tile)
-    dim3 sgrid(F / 32, (M + 127) / 128);
-    __bf16 *vb = (v_blk && v_blk_done && t_fresh % 64 == 0) ? v_blk : nullptr;  // also lay V out for the attention kernel
+  if (few_rows(M)) {
+    __bf16 *vb = v_blk && v_blk_done ? v_blk : nullptr;
     if (vb) *v_blk_done = true;
+    const bool head_norm = extras.q_norm || extras.k_norm, norm = extras.pre_norm;
+    const few::Choice ch = head_norm ? few::Choice{c.head_dim / 16, 1} : few::choose_tile(ctx->n_cu, M, F / 16, 1);
+    const int n_wt = F / (16 * ch.nf), n_tt = (M + 16 * ch.nt - 1) / (16 * ch.nt);
     prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
-    if (c.head_dim == 128)
-      hipLaunchKernelGGL(qkv_rope_skinny_kernel<128>, sgrid, dim3(256), 0, stream, x, w, M, c.hidden, t_fresh, c.n_q_heads,
-                         c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, vb);
-    else
-      hipLaunchKernelGGL(qkv_rope_skinny_kernel<64>, sgrid, dim3(256), 0, stream, x, w, M, c.hidden, t_fresh, c.n_q_heads,
-                         c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, vb);
-    prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
-    PC_HIP(ctx, hipGetLastError());
-    return PC_OK;
+#define PC_FEW_K(DD, NF, NT, NN, HH)                                                                                           \
+  hipLaunchKernelGGL((qkv_rope_few_kernel<DD, NF, NT, NN, HH>), dim3(few::grid_of(n_wt, n_tt)), dim3(64 * few::Form<NF, NT>::WV), 0, stream, x, w, \
+                     M, c.hidden, t_fresh, c.n_q_heads, c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb, n_wt, n_tt)
+#define PC_FEW(DD, NF, NT)                                                                                                     \
+  if (ch.nf == NF && ch.nt == NT) {                                                                                            \
+    if (norm) PC_FEW_K(DD, NF, NT, true, false); else PC_FEW_K(DD, NF, NT, false, false);                                       \
   }
-  if (gemm_part && splitk_applies(M)) {
-    // few token rows with the bias / head-norm variants: contraction cut into slices (see block.hip)
-    const int nk = choose_split_k(ctx->n_cu, F / BF * (M > 128 ? 2 : 1), c.hidden / pc::gemm::BK);
-    prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
-    pc_status st = launch_splitk_partial(ctx, x, c.hidden, w, w, F, c.hidden, gemm_part, M, F, c.hidden, nk, stream);
-    if (st != PC_OK) return st;
-    const long threads = (long)M * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 8);
-    const dim3 rgrid((unsigned)((threads + 255) / 256));
-    __bf16 *vb = (v_blk && v_blk_done && t_fresh % 64 == 0) ? v_blk : nullptr;  // also lay V out for the attention kernel
-    if (vb) *v_blk_done = true;
-    if (c.head_dim == 128)
-      hipLaunchKernelGGL(reduce_rope_kernel<128>, rgrid, dim3(256), 0, stream, gemm_part, nk, M, F, t_fresh, c.n_q_heads,
-                         c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb);
-    else
-      hipLaunchKernelGGL(reduce_rope_kernel<64>, rgrid, dim3(256), 0, stream, gemm_part, nk, M, F, t_fresh, c.n_q_heads,
-                         c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb);
+#define PC_FEW_D(DD)                                                                                                           \
+  do {                                                                                                                         \
+    if (head_norm) {                                                                                                           \
+      if (norm) PC_FEW_K(DD, DD / 16, 1, true, true); else PC_FEW_K(DD, DD / 16, 1, false, true);                               \
+    } else PC_FEW(DD, 1, 1) else PC_FEW(DD, 2, 1) else PC_FEW(DD, 1, 2) else PC_FEW(DD, 2, 2) else PC_FEW(DD, 2, 4) else PC_FEW(DD, 4, 4) \
+  } while (0)
+    if (c.head_dim == 128) PC_FEW_D(128); else PC_FEW_D(64);
+#undef PC_FEW_D
+#undef PC_FEW
+#undef PC_FEW_K
     prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
     PC_HIP(ctx, hipGetLastError());
     return PC_OK;

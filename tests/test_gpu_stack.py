@@ -278,3 +278,40 @@ def test_projection_variants_bias_and_head_norm(D, t_fresh, which, heads):
                              extras=dict(bias=bias, q_gain=qg, k_gain=kg, eps=EPS))
     check_hidden(host(h_out[0]), ref, f"variants {which} D={D} T={t_fresh}")
     assert np.abs(host(h_out[0]) - host(plain[0])).max() > 1e-2     # the variant is not the plain block
+
+
+@pytest.mark.parametrize("D,heads,H,F,batch,t_fresh,which", [
+    (128, (16, 8), 256, 2112, 1, 1, "none"), (128, (16, 8), 256, 2112, 16, 1, "bias"), (64, (8, 4), 384, 4160, 1, 17, "none"),
+    (128, (16, 8), 256, 2112, 1, 33, "norm"), (128, (24, 8), 128, 3072, 2, 32, "none"), (128, (16, 8), 256, 2112, 5, 13, "bias"),
+    (64, (8, 4), 384, 4160, 1, 129, "norm"), (128, (24, 8), 128, 3072, 3, 64, "bias"), (64, (8, 4), 384, 64, 2, 65, "none"),
+])
+def test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which):
+    """The projections of few token rows at the edges of their tiles: every tile the launcher chooses from (1 to 4 blocks of
+    16 weight rows x 1 to 4 of 16 token rows), ragged token blocks, contractions shorter than the wavefronts' slices
+    (H = 128: two steps for eight wavefronts), several queries in a token tile (zero padding of their V blocks), the bias
+    and the head norm on top of the folded RMSNorm."""
+    (Hq, Hkv), C = heads, 64
+    w = wl.make_prefill("few", 24, "bf16", H, Hq, Hkv, D, batch, t_fresh, 1, C, batch, last_used_len=37)
+    w.slot_ids[:] = np.arange(batch, dtype=np.int32)[:, None]
+    W = wl.stack_weights(24, 0, H, Hq, Hkv, D, F)
+    g = np.random.default_rng(60 + t_fresh)
+    layer, extras = dev_layers([W])[0], dict(bias=None, q_gain=None, k_gain=None, eps=EPS)
+    if which == "bias":
+        extras["bias"] = wl.round_bf16(0.5 * g.standard_normal((Hq + 2 * Hkv) * D).astype(np.float32))
+        layer["qkv_bias"] = bf16(extras["bias"])
+    if which == "norm":
+        extras["q_gain"], extras["k_gain"] = (wl.round_bf16(1 + 0.2 * g.standard_normal(D).astype(np.float32)) for _ in range(2))
+        layer.update(q_norm=bf16(extras["q_gain"]), k_norm=bf16(extras["k_gain"]))
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=batch, slot_capacity=C,
+                  max_pos=w.max_pos, device=DEV)
+    for s_ in range(batch):
+        k, v = w.slot_kv(s_)
+        pc.percache_kv_put(0, s_, bf16(k), bf16(v))
+    h_out = pc.percache_stack_reuse([layer], F, EPS, bf16(w.X), w.slot_ids, w.used_len)
+    again = pc.percache_stack_reuse([layer], F, EPS, bf16(w.X), w.slot_ids, w.used_len)
+    torch.cuda.synchronize()
+    assert torch.equal(h_out, again)   # the partial sums meet in a fixed order
+    for b in range(batch):
+        sk, sv, ids = w.compact_store(b)
+        ref, _, _ = oracle_block(w.X[b], W, Hq, Hkv, D, w.rope_theta, sk, sv, ids, w.used_len[b], extras=extras)
+        check_hidden(host(h_out[b]), ref, f"few rows D={D} H={H} F={F} B={batch} T={t_fresh} {which} query {b}")
