@@ -388,6 +388,20 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     if (tiles < min_tiles) min_tiles = tiles;
   }
   hipStream_t s = (hipStream_t)stream;
+  // a decoding step of few rows: the attention kernel finishes q, k and v from the projection's sums and appends the fresh
+  // K/V to bf16 slots itself; (slot, tokens it holds) of every query go to the device behind the chunk lists
+  const bool decode = pc::decode_rows(c, t_fresh), raw_qkv = decode && pc::few_rows(M);
+  bool append_kernel = append_slots_host != nullptr;  // some append is left to a kernel of its own
+  if (raw_qkv && append_slots_host && !table_dev) {
+    append_kernel = false;
+    for (int b = 0; b < batch; ++b) {
+      const int slot = append_slots_host[b];
+      const bool here = slot >= 0 && !ctx->is8(slot);
+      if (slot >= 0 && !here) append_kernel = true;
+      rows.push_back(here ? slot : -1);
+      rows.push_back(here ? ctx->slot_len[slot] : 0);
+    }
+  }
   if (table_dev) {
     ws.pf.table = const_cast<int32_t *>(table_dev);  // the list is on the device already: nothing to copy
   } else {
@@ -403,18 +417,31 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     // few token rows: one launch per projection, the RMSNorms folded into the projections behind them
     const bool few = pc::few_rows(M);
     if (!few) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
-    bool v_blocked = false;
     pc::QkvExtras extras;
     extras.bias = (const __bf16 *)w.qkv_bias;
     extras.q_norm = (const __bf16 *)w.q_norm;
     extras.k_norm = (const __bf16 *)w.k_norm;
     extras.eps = eps;
     extras.pre_norm = few ? (const __bf16 *)w.gain1 : nullptr;
-    PC_TRY(pc::launch_qkv_rope(ctx, few ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
-                               ws.pf.v, s, extras, ws.pf.v_blk, &v_blocked));
-    if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
-    PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v_blk, batch, t_fresh, ws.pf.table, stride, min_tiles, 0, ws.attn,
-                                ws.pf.part_o, ws.pf.part_ml, s, formats));
+    pc::RawQkv raw;
+    if (raw_qkv) {
+      raw.sums = ws.pf.qkv_raw;
+      raw.ex = extras;
+      raw.rope = (const float2 *)ctx->rope;
+      raw.k_out = ws.pf.k;
+      raw.v_out = ws.pf.v;
+      if (append_slots_host) raw.append = ws.pf.table + (size_t)batch * stride;
+      raw.k_slots = ctx->k_store + (size_t)l * ctx->layer_stride;
+      raw.v_slots = ctx->v_store + (size_t)l * ctx->layer_stride;
+      PC_TRY(pc::launch_qkv_raw(ctx, h_cur, (const __bf16 *)w.wqkv, (int)M, extras, ws.pf.qkv_raw, s));
+    } else {
+      bool v_blocked = decode;  // (in a decoding step nobody reads V as blocks)
+      PC_TRY(pc::launch_qkv_rope(ctx, few ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
+                                 ws.pf.v, s, extras, decode ? nullptr : ws.pf.v_blk, decode ? nullptr : &v_blocked));
+      if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
+    }
+    PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v, ws.pf.v_blk, raw_qkv ? &raw : nullptr, batch, t_fresh, ws.pf.table, stride,
+                                min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats));
     for (int b = 0; b < batch && n_save > 0; ++b)
       for (int j = 0; j < n_save; ++j) {
         const int slot = save_slots_host[(size_t)b * n_save + j];
@@ -424,15 +451,12 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
         PC_TRY(pc::launch_kv_store(ctx, l, slot, ws.pf.k + at, ws.pf.v + at, cnt, (long)t_fresh * c.head_dim, s));
         ctx->slot_len[(size_t)l * c.n_slots + slot] = cnt;
       }
-    for (int b = 0; b < batch && append_slots_host; ++b) {
-      // after the attention launch in stream order: the keys it gathered from this slot are the older ones
-      const int slot = append_slots_host[b];
-      if (slot < 0) continue;
-      const int have = ctx->slot_len[(size_t)l * c.n_slots + slot];
-      const size_t at = (size_t)b * c.n_kv_heads * t_fresh * c.head_dim;
-      PC_TRY(pc::launch_kv_append(ctx, l, slot, ws.pf.k + at, ws.pf.v + at, have, t_fresh, (long)t_fresh * c.head_dim, s));
-      ctx->slot_len[(size_t)l * c.n_slots + slot] = have + t_fresh;
+    if (append_kernel) {
+      // after the attention launch in stream order: the keys it gathered from these slots are the older ones
+      PC_TRY(pc::launch_kv_append(ctx, l, append_slots_host, batch, raw_qkv, ws.pf.k, ws.pf.v, t_fresh, s));
     }
+    for (int b = 0; b < batch && append_slots_host; ++b)
+      if (append_slots_host[b] >= 0) ctx->slot_len[(size_t)l * c.n_slots + append_slots_host[b]] += t_fresh;
     if (few) {
       PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
       PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));

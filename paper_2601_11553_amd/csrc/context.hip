@@ -176,13 +176,15 @@ PrefillWs carve_prefill_ws(const percache_config &c, int n_cu, void *base, int32
   char *p = (char *)base;
   size_t off = 0;
   auto take = [&](size_t bytes) { char *r = p ? p + off : nullptr; off += align_up(bytes); return r; };
-  w.table = (int32_t *)take((size_t)batch * tbl_stride(max_chunks) * sizeof(int32_t));
+  w.table = (int32_t *)take((size_t)batch * (tbl_stride(max_chunks) + 2) * sizeof(int32_t));  // rows, then (append slot, its length)
   size_t qn = (size_t)batch * c.n_q_heads * t_fresh * c.head_dim;
   size_t kn = (size_t)batch * c.n_kv_heads * t_fresh * c.head_dim;
   w.q = (__bf16 *)take(qn * 2);
   w.k = (__bf16 *)take(kn * 2);
   w.v = (__bf16 *)take(kn * 2);
   w.v_blk = (__bf16 *)take((size_t)batch * c.n_kv_heads * ((t_fresh + kKvTile - 1) / kKvTile) * kKvTile * c.head_dim * 2);
+  const size_t M = (size_t)batch * t_fresh;
+  w.qkv_raw = (float *)take(few_rows((long)M) && decode_rows(c, t_fresh) ? M * (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * sizeof(float) : 0);
   size_t rows = (size_t)batch * c.n_q_heads * t_fresh;
   w.max_splits = max_splits_for(c, n_cu, batch, t_fresh);
   w.part_o = (__bf16 *)take(rows * w.max_splits * c.head_dim * 2);

@@ -88,12 +88,18 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(pc::u32x4 *__restrict__ sl
   }
 }
 
-// Appends n_new tokens behind the `off` tokens a slot already holds.  K: rows copied to their place.  V: every
-// position of the 64-key blocks that receive a token is rewritten from `off` on -- the new tokens, then zeros, so
-// that the padding of the last block stays finite (masked probabilities multiply it).
-__global__ __launch_bounds__(256) void kv_append_kernel(__bf16 *__restrict__ slot_k, __bf16 *__restrict__ slot_v,
-                                                        const __bf16 *__restrict__ k_new, const __bf16 *__restrict__ v_new,
-                                                        int n_heads, int off, int n_new, int D, int C, long new_head_stride) {
+// Appends n_new tokens behind the off tokens a slot already holds; blockIdx.y selects the slot of a list (one launch for
+// all queries of a decoding step).  K: rows copied to their place.  V: every position of the 64-key blocks that receive a
+// token is rewritten from off on -- the new tokens, then zeros, so that the padding of the last block stays finite
+// (masked probabilities multiply it).
+__global__ __launch_bounds__(256) void kv_append_kernel(__bf16 *__restrict__ k_store, __bf16 *__restrict__ v_store,
+                                                        const __bf16 *__restrict__ k_dense, const __bf16 *__restrict__ v_dense,
+                                                        int n_heads, SlotList slots, SlotList offs, int n_new, int D, int C, long slot_stride_elems) {
+  if (slots.slot[blockIdx.y] < 0) return;
+  const int off = offs.slot[blockIdx.y];
+  const long new_head_stride = (long)n_new * D;
+  __bf16 *slot_k = k_store + (size_t)slots.slot[blockIdx.y] * slot_stride_elems, *slot_v = v_store + (size_t)slots.slot[blockIdx.y] * slot_stride_elems;
+  const __bf16 *k_new = k_dense + (size_t)blockIdx.y * n_heads * new_head_stride, *v_new = v_dense + (size_t)blockIdx.y * n_heads * new_head_stride;
   const int tile0 = off / kKvTile, n_tiles = (off + n_new + kKvTile - 1) / kKvTile - tile0;
   const long stride = (long)gridDim.x * blockDim.x;
   const long tid0 = (long)blockIdx.x * blockDim.x + threadIdx.x;
@@ -144,22 +150,22 @@ __device__ __forceinline__ unsigned encode4(float a, float b, float c, float d) 
   return (unsigned)w;
 }
 
-// off > 0: the slot already holds `off` tokens and the dense tensors are the tokens that follow them (append).  The
+// offs: the slot already holds that many tokens and the dense tensors are the tokens that follow them (0: a put).  The
 // block that was partly filled is then quantised afresh from the values its old tokens read back as plus the new
 // tokens (its exponent is recomputed over all of them; old codes are re-rounded only if the exponent moves); the
-// launch covers the blocks from off / 64 on, and n_tok counts old and new tokens together.
+// launch covers the blocks from off / 64 on (of every entry as many as the entry with the most has).
 template <int D>
 __global__ __launch_bounds__(256) void kv_quant_kernel(uint8_t *__restrict__ slot_k, uint8_t *__restrict__ slot_v,
                                                        float *__restrict__ scale_k, float *__restrict__ scale_v,
                                                        const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v,
-                                                       int n_heads, int n_tok, int C, SlotList slots, long slot_stride_elems,
-                                                       long scale_slot_stride, long dense_head_stride, int off) {
+                                                       int n_heads, int n_new, int C, SlotList slots, long slot_stride_elems,
+                                                       long scale_slot_stride, long dense_head_stride, SlotList offs) {
   constexpr int DV = D / 8, NV = kKvTile * DV / 256;  // 8-element vectors per row; vectors per thread
   __shared__ float red[2][4];
   __shared__ __align__(16) uint8_t vt[kKvTile][D + 16];  // V codes [key][d] (padded rows), read back transposed
+  const int slot = slots.slot[blockIdx.z], off = offs.slot[blockIdx.z], n_tok = off + n_new;
   const int blk = blockIdx.x + off / kKvTile, g = blockIdx.y, tid = threadIdx.x;
-  const int slot = slots.slot[blockIdx.z];
-  if (slot < 0) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
+  if (slot < 0 || blk * kKvTile >= n_tok) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
   const size_t dense_at = ((size_t)blockIdx.z * n_heads + g) * dense_head_stride;
   const size_t slot_at = (size_t)slot * slot_stride_elems + (size_t)g * C * D;
   const size_t sc = (size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + blk;
@@ -246,7 +252,7 @@ __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restri
                                                          const float *__restrict__ scale_k, const float *__restrict__ scale_v,
                                                          __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int n_heads,
                                                          int n_tok, int C, SlotList slots, long slot_stride_elems,
-                                                         long scale_slot_stride, long dense_head_stride, int /*unused*/) {
+                                                         long scale_slot_stride, long dense_head_stride, SlotList /*unused*/) {
   constexpr int DV = D / 8, NV = kKvTile * DV / 256;
   const int blk = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
   const int slot = slots.slot[blockIdx.z];
@@ -316,7 +322,7 @@ pc_status launch_copy(percache_ctx *ctx, int layer, const int32_t *slot_list, in
 #define PC_KV8(KERNEL, DD)                                                                                                    \
   hipLaunchKernelGGL((KERNEL<DD>), grid, dim3(256), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
                      ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, n_tokens, c.slot_capacity, sl8,     \
-                     (long)ctx->slot_stride, sc_slot, dhs, 0)
+                     (long)ctx->slot_stride, sc_slot, dhs, SlotList{})
     if (kToStore) {
       if (c.head_dim == 128) PC_KV8(kv_quant_kernel, 128); else PC_KV8(kv_quant_kernel, 64);
     } else {
@@ -345,34 +351,50 @@ pc_status launch_kv_store(percache_ctx *ctx, int layer, int slot, const __bf16 *
                           long dense_head_stride, hipStream_t stream) {
   return launch_copy<true>(ctx, layer, &slot, 1, (void *)k, (void *)v, n_tokens, stream, dense_head_stride);
 }
-pc_status launch_kv_append(percache_ctx *ctx, int layer, int slot, const __bf16 *k, const __bf16 *v, int off, int n_tokens,
-                           long new_head_stride, hipStream_t stream) {
+pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v,
+                           int n_tokens, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
-  if (ctx->is8(slot)) {
-    const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
-    const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
-    SlotList sl;
-    for (int i = 0; i < 64; ++i) sl.slot[i] = i == 0 ? slot - ctx->n_slots16 : -1;
-    const int total = off + n_tokens;
-    dim3 grid((total + kKvTile - 1) / kKvTile - off / kKvTile, c.n_kv_heads, 1);
-    if (c.head_dim == 128)
-      hipLaunchKernelGGL((kv_quant_kernel<128>), grid, dim3(256), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo,
-                         ctx->k_scale + sc_off, ctx->v_scale + sc_off, k, v, c.n_kv_heads, total, c.slot_capacity, sl,
-                         (long)ctx->slot_stride, sc_slot, new_head_stride, off);
-    else
-      hipLaunchKernelGGL((kv_quant_kernel<64>), grid, dim3(256), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo,
-                         ctx->k_scale + sc_off, ctx->v_scale + sc_off, k, v, c.n_kv_heads, total, c.slot_capacity, sl,
-                         (long)ctx->slot_stride, sc_slot, new_head_stride, off);
-    PC_HIP(ctx, hipGetLastError());
-    return PC_OK;
+  const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile), head_stride = (long)n_tokens * c.head_dim;
+  for (int i0 = 0; i0 < n; i0 += 64) {
+    const int cnt = n - i0 < 64 ? n - i0 : 64;
+    SlotList sl16, sl8, offs;
+    int n16 = 0, n8 = 0, blocks8 = 0;
+    for (int i = 0; i < 64; ++i) {
+      sl16.slot[i] = sl8.slot[i] = -1;
+      offs.slot[i] = 0;
+      if (i >= cnt || slot_list[i0 + i] < 0) continue;
+      const int slot = slot_list[i0 + i], off = ctx->slot_len[(size_t)layer * c.n_slots + slot];
+      offs.slot[i] = off;
+      if (ctx->is8(slot)) {
+        sl8.slot[i] = slot - ctx->n_slots16;
+        const int blocks = (off + n_tokens + kKvTile - 1) / kKvTile - off / kKvTile;
+        if (blocks > blocks8) blocks8 = blocks;
+        ++n8;
+      } else if (!only_8bit) {
+        sl16.slot[i] = slot;
+        ++n16;
+      }
+    }
+    const __bf16 *kd = k + (size_t)i0 * c.n_kv_heads * head_stride, *vd = v + (size_t)i0 * c.n_kv_heads * head_stride;
+    if (n8) {
+      const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
+      const dim3 grid(blocks8, c.n_kv_heads, cnt);
+#define PC_APPEND8(DD)                                                                                                                  \
+  hipLaunchKernelGGL((kv_quant_kernel<DD>), grid, dim3(256), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off,      \
+                     ctx->v_scale + sc_off, kd, vd, c.n_kv_heads, n_tokens, c.slot_capacity, sl8, (long)ctx->slot_stride, sc_slot, head_stride, offs)
+      if (c.head_dim == 128) PC_APPEND8(128); else PC_APPEND8(64);
+#undef PC_APPEND8
+      PC_HIP(ctx, hipGetLastError());
+    }
+    if (n16) {
+      const size_t at = (size_t)layer * ctx->layer_stride;
+      const long work = (long)c.n_kv_heads * c.head_dim * ((n_tokens + kKvTile - 1) / kKvTile + 1) * kKvTile;
+      const long blocks = (work + 255) / 256;
+      hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks), cnt), dim3(256), 0, stream, ctx->k_store + at, ctx->v_store + at,
+                         kd, vd, c.n_kv_heads, sl16, offs, n_tokens, c.head_dim, c.slot_capacity, (long)ctx->slot_stride);
+      PC_HIP(ctx, hipGetLastError());
+    }
   }
-  const size_t at = (size_t)layer * ctx->layer_stride + (size_t)slot * ctx->slot_stride;
-  const long work = (long)c.n_kv_heads * c.head_dim * ((n_tokens + kKvTile - 1) / kKvTile + 1) * kKvTile;
-  int blocks = (int)((work + 255) / 256);
-  if (blocks > 1024) blocks = 1024;
-  hipLaunchKernelGGL(kv_append_kernel, dim3(blocks), dim3(256), 0, stream, ctx->k_store + at, ctx->v_store + at, k, v,
-                     c.n_kv_heads, off, n_tokens, c.head_dim, c.slot_capacity, new_head_stride);
-  PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
 }  // namespace pc
@@ -389,8 +411,7 @@ pc_status percache_kv_append(percache_ctx *ctx, int32_t layer, int32_t slot, con
   const int have = ctx->slot_len[(size_t)layer * c.n_slots + slot];
   if (n_tokens < 1 || have + n_tokens > c.slot_capacity)
     return pc::fail(ctx, PC_ELEN, "slot %d holds %d tokens: %d more do not fit the capacity %d", slot, have, n_tokens, c.slot_capacity);
-  st = pc::launch_kv_append(ctx, layer, slot, (const __bf16 *)k_dev, (const __bf16 *)v_dev, have, n_tokens,
-                            (long)n_tokens * c.head_dim, (hipStream_t)stream);
+  st = pc::launch_kv_append(ctx, layer, &slot, 1, false, (const __bf16 *)k_dev, (const __bf16 *)v_dev, n_tokens, (hipStream_t)stream);
   if (st != PC_OK) return st;
   ctx->slot_len[(size_t)layer * c.n_slots + slot] = have + n_tokens;
   return PC_OK;

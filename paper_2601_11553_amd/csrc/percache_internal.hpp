@@ -132,6 +132,7 @@ struct PrefillWs {
   int32_t *table;
   __bf16 *q, *k, *v;
   __bf16 *v_blk;   // fresh V as 64-key blocks [B*Hkv][ceil(T/64)][D][64]
+  float *qkv_raw;  // the projection's sums [B*T][(Hq + 2 Hkv) * D] (few rows of a decoding step only)
   __bf16 *part_o;  // [rows][splits][D], normalised per split
   float *part_ml;  // [rows][splits][2]
   int max_splits;  // partitions of the key axis the partial buffers can hold
@@ -159,6 +160,17 @@ struct QkvExtras {
 };
 // Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in.
 inline bool few_rows(long M) { return M <= 192; }
+// The projection of few token rows as fp32 sums [M][(Hq + 2 Hkv) * D], before bias, head norm and RoPE: what the attention
+// kernel of a decoding step starts from (it finishes q, k and v itself, see decode_attention.hip).
+struct RawQkv {
+  const float *sums = nullptr;
+  QkvExtras ex;
+  const float2 *rope = nullptr;
+  __bf16 *k_out = nullptr, *v_out = nullptr;      // [B, Hkv, T, D]
+  const int32_t *append = nullptr;                // per query (slot, tokens it holds), slot < 0: none; bf16 slots only
+  __bf16 *k_slots = nullptr, *v_slots = nullptr;  // the layer's bf16 store
+};
+pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream);
 // v_blk / v_blk_done: if given, the launch may also write V as the 64-key blocks of launch_v_repack and says so.
 // extras.pre_norm only where few_rows(batch * t_fresh).
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
@@ -167,10 +179,21 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
                           bool *v_blk_done = nullptr);
 
 pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, int batch, int t_fresh, hipStream_t stream);
+// Whether a call's attention takes the kernel for very few rows per kv head (decode_attention.hip), which reads the fresh V
+// as projected; every other kernel reads it as 64-key blocks.
+inline bool decode_rows(const percache_config &c, int t_fresh) { return (long)(c.n_q_heads / c.n_kv_heads) * t_fresh <= 32; }
+// vf: fresh V as projected; vf_blk: as 64-key blocks (may be null where decode_rows).
 // formats: which slot formats the call's chunks sit in (see table_formats): bit 0 = 8-bit, bit 1 = bf16
-pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf_blk,
-                           int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int max_tiles,
+// raw: q and the fresh k, v as the projection's sums instead (decode_rows only; q, kf, vf unused).
+pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
+                           const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int max_tiles,
                            int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats);
+// The first of its two launches where decode_rows; tiles: cached tiles of the shortest query.  n_splits <= 0: chosen here.
+pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, __bf16 *part_o,
+                                  float *part_ml, hipStream_t stream, int formats);
+// Number of key-axis partitions that fills `slots` resident workgroups best (at least 4 tiles in each).
+int choose_splits(int slots, long base_wgs, int min_tiles, int cap);
 inline int table_formats(const std::vector<int32_t> &rows, int stride, int batch) {
   int f = 0;
   for (int b = 0; b < batch; ++b) f |= rows[(size_t)b * stride + 3];
@@ -182,8 +205,10 @@ inline int table_formats(const std::vector<int32_t> &rows, int stride, int batch
 pc_status launch_kv_store(percache_ctx *ctx, int layer, int slot, const __bf16 *k, const __bf16 *v, int n_tokens,
                           long dense_head_stride, hipStream_t stream);
 
-// Appends n_tokens tokens behind the `off` tokens a slot holds (no validation, no slot-table update).
-pc_status launch_kv_append(percache_ctx *ctx, int layer, int slot, const __bf16 *k, const __bf16 *v, int off, int n_tokens,
-                           long new_head_stride, hipStream_t stream);
+// Appends n_tokens tokens of every dense tensor of [n][Hkv][n_tokens][D] behind the tokens that the slot of the same place
+// in the list holds (by the slot table; no validation, no slot-table update).  Negative entries are skipped, and with
+// only_8bit the bf16 slots too.
+pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v,
+                           int n_tokens, hipStream_t stream);
 
 }  // namespace pc

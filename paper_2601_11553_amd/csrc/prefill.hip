@@ -94,10 +94,12 @@ pc_status percache_attention_reuse(percache_ctx *ctx, int32_t layer, const void 
   hipStream_t s = (hipStream_t)stream;
   st = pc::upload_table(ctx, rows, p.ws.table, s);
   if (st != PC_OK) return st;
-  st = pc::launch_v_repack(ctx, (const __bf16 *)v_fresh_dev, p.ws.v_blk, batch, t_fresh, s);
-  if (st != PC_OK) return st;
-  return pc::launch_attention(ctx, layer, (const __bf16 *)q_dev, (const __bf16 *)k_fresh_dev, p.ws.v_blk,
-                              batch, t_fresh, p.ws.table, p.tbl_stride, p.min_tiles, n_splits, (__bf16 *)attn_out_dev,
+  if (!pc::decode_rows(ctx->cfg, t_fresh)) {
+    st = pc::launch_v_repack(ctx, (const __bf16 *)v_fresh_dev, p.ws.v_blk, batch, t_fresh, s);
+    if (st != PC_OK) return st;
+  }
+  return pc::launch_attention(ctx, layer, (const __bf16 *)q_dev, (const __bf16 *)k_fresh_dev, (const __bf16 *)v_fresh_dev, p.ws.v_blk,
+                              nullptr, batch, t_fresh, p.ws.table, p.tbl_stride, p.min_tiles, n_splits, (__bf16 *)attn_out_dev,
                               p.ws.part_o, p.ws.part_ml, s, pc::table_formats(rows, p.tbl_stride, batch));
 }
 
@@ -125,14 +127,27 @@ static pc_status run_prefill(percache_ctx *ctx, int32_t layer, const void *x_fre
   }
   __bf16 *kf = k_fresh_out_dev ? (__bf16 *)k_fresh_out_dev : p.ws.k;
   __bf16 *vf = v_fresh_out_dev ? (__bf16 *)v_fresh_out_dev : p.ws.v;
-  bool v_blocked = false;
+  const bool decode = pc::decode_rows(ctx->cfg, t_fresh);  // (then nobody reads V as blocks)
+  const int formats = pc::table_formats(rows, p.tbl_stride, batch);
+  if (decode && pc::few_rows((long)batch * t_fresh)) {
+    pc::RawQkv raw;
+    raw.sums = p.ws.qkv_raw;
+    raw.rope = (const float2 *)ctx->rope;
+    raw.k_out = kf;
+    raw.v_out = vf;
+    st = pc::launch_qkv_raw(ctx, (const __bf16 *)x_fresh_dev, (const __bf16 *)wqkv_dev, batch * t_fresh, pc::QkvExtras(), p.ws.qkv_raw, s);
+    if (st != PC_OK) return st;
+    return pc::launch_attention(ctx, layer, nullptr, nullptr, nullptr, nullptr, &raw, batch, t_fresh, p.ws.table, p.tbl_stride, p.min_tiles, 0,
+                                (__bf16 *)attn_out_dev, p.ws.part_o, p.ws.part_ml, s, formats);
+  }
+  bool v_blocked = decode;
   st = pc::launch_qkv_rope(ctx, (const __bf16 *)x_fresh_dev, (const __bf16 *)wqkv_dev, batch, t_fresh, p.ws.table,
-                           p.tbl_stride, p.ws.q, kf, vf, s, pc::QkvExtras(), p.ws.v_blk, &v_blocked);
+                           p.tbl_stride, p.ws.q, kf, vf, s, pc::QkvExtras(), decode ? nullptr : p.ws.v_blk, decode ? nullptr : &v_blocked);
   if (st != PC_OK) return st;
   if (!v_blocked) st = pc::launch_v_repack(ctx, vf, p.ws.v_blk, batch, t_fresh, s);
   if (st != PC_OK) return st;
-  return pc::launch_attention(ctx, layer, p.ws.q, kf, p.ws.v_blk, batch, t_fresh, p.ws.table, p.tbl_stride, p.min_tiles, 0,
-                              (__bf16 *)attn_out_dev, p.ws.part_o, p.ws.part_ml, s, pc::table_formats(rows, p.tbl_stride, batch));
+  return pc::launch_attention(ctx, layer, p.ws.q, kf, vf, p.ws.v_blk, nullptr, batch, t_fresh, p.ws.table, p.tbl_stride, p.min_tiles, 0,
+                              (__bf16 *)attn_out_dev, p.ws.part_o, p.ws.part_ml, s, formats);
 }
 
 pc_status percache_prefill_reuse(percache_ctx *ctx, int32_t layer, const void *x_fresh_dev, const void *wqkv_dev,

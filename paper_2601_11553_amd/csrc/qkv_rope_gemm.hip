@@ -336,9 +336,56 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few
   }
 }
 
+// The bare sums of few token rows, fp32 [M][N] (see RawQkv).
+template <int NF, int NT, bool NORM>
+__global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_raw_few_kernel(const __bf16 *__restrict__ X, const __bf16 *__restrict__ W,
+                                                                                      const __bf16 *__restrict__ gain, float eps, float *__restrict__ Y,
+                                                                                      int M, int N, int K, int n_wt, int n_tt) {
+  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG;
+  __shared__ __align__(16) char lds[pc::few::Tile<NF, NT, WV, NSTG, NORM>::LDS_BYTES];
+  int wt, tt;
+  if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
+  const int n0 = wt * 16 * NF, m0 = tt * 16 * NT;
+  f32x4 acc[NF][NT];
+  float ss[NT];
+  pc::few::slice_product<NF, NT, WV, NSTG, NORM>(
+      lds, [&](int r) __attribute__((always_inline)) { return W + (size_t)(n0 + r) * K; },
+      [&](int r) __attribute__((always_inline)) { return X + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, []() {}, acc, ss);
+  pc::few::share_slices<NF, NT, WV, NSTG, NORM>(lds, wave, lane, acc, ss);
+#pragma unroll
+  for (int b = wave; b < NF * NT; b += WV) {
+    const int f = b / NT, t = b % NT, m = m0 + t * 16 + l16;
+    f32x4 s = pc::few::tile_sum<NF, NT, WV>(lds, f, t, lane);
+    if (NORM) s *= pc::few::row_factor<NF, NT, WV>(lds, t, l16, K, eps);
+    if (m < M) *(f32x4 *)(Y + (size_t)m * N + n0 + f * 16 + g * 4) = s;
+  }
+}
+
 }  // namespace
 
 namespace pc {
+
+pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream) {
+  const percache_config &c = ctx->cfg;
+  const int N = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, K = c.hidden;
+  const few::Choice ch = few::choose_tile(ctx->n_cu, M, N / 16, 1);
+  const int n_wt = N / (16 * ch.nf), n_tt = (M + 16 * ch.nt - 1) / (16 * ch.nt);
+  prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
+#define PC_FEW_K(NF, NT, NN)                                                                                                        \
+  hipLaunchKernelGGL((qkv_raw_few_kernel<NF, NT, NN>), dim3(few::grid_of(n_wt, n_tt)), dim3(64 * few::Form<NF, NT>::WV), 0, stream, x, w, \
+                     extras.pre_norm, extras.eps, sums, M, N, K, n_wt, n_tt)
+#define PC_FEW(NF, NT)                                                                            \
+  if (ch.nf == NF && ch.nt == NT) {                                                               \
+    if (extras.pre_norm) PC_FEW_K(NF, NT, true); else PC_FEW_K(NF, NT, false);                     \
+  }
+  PC_FEW(1, 1) else PC_FEW(2, 1) else PC_FEW(1, 2) else PC_FEW(2, 2) else PC_FEW(2, 4) else PC_FEW(4, 4)
+#undef PC_FEW
+#undef PC_FEW_K
+  prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
+}
 
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,

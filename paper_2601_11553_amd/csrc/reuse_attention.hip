@@ -1500,11 +1500,37 @@ pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, i
   return PC_OK;
 }
 
-pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf_blk,
-                           int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int min_tiles,
+// Merges the partials of a launch whose key axis was cut into n_splits > 1 partitions.
+static pc_status launch_combine(percache_ctx *ctx, const __bf16 *part_o, const float *part_ml, int n_splits, int batch, int t_fresh, __bf16 *out,
+                                hipStream_t stream) {
+  const percache_config &c = ctx->cfg;
+  const long total_rows = (long)batch * c.n_q_heads * t_fresh;
+  const bool few_parts = n_splits <= 4;              // one lane per 16 output bytes, else four
+  long threads = total_rows * (c.head_dim / 8) * (few_parts ? 1 : 4);
+  int blocks = (int)((threads + 255) / 256);
+#define PC_COMBINE(DD, FF)                                                                                          \
+  hipLaunchKernelGGL((splitkv_combine_kernel<DD, FF>), dim3(blocks), dim3(256), 0, stream, part_o, part_ml, n_splits, \
+                   t_fresh, c.n_q_heads, c.n_kv_heads, total_rows, out)
+  if (c.head_dim == 128) { if (few_parts) PC_COMBINE(128, true); else PC_COMBINE(128, false); }
+  else { if (few_parts) PC_COMBINE(64, true); else PC_COMBINE(64, false); }
+#undef PC_COMBINE
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
+}
+
+pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
+                           const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int min_tiles,
                            int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats) {
   const percache_config &c = ctx->cfg;
   const int G = c.n_q_heads / c.n_kv_heads, R = G * t_fresh;
+  if (decode_rows(c, t_fresh)) {
+    prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
+    const pc_status st = launch_decode_attention(ctx, layer, q, kf, vf, raw, batch, t_fresh, table_dev, tbl_stride,
+                                                 min_tiles - (t_fresh + TK - 1) / TK, n_splits, out, part_o, part_ml, stream, formats);
+    if (st != PC_OK) return st;
+    prof_end(ctx, PC_KERNEL_ATTENTION, stream);
+    return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
+  }
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
   // variant that tells the formats apart tile by tile only when it names chunks of both formats
   const bool use8 = (formats & 1) && ctx->n_slots8 > 0;
@@ -1514,15 +1540,11 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   // 256-row workgroups only when there are enough of them to go round; few, short key ranges prefer more, smaller ones
   // (8-bit slots with D = 64: a tile is too small for eight wavefronts to load)
   const bool wide = R > 128 && (long)batch * c.n_kv_heads * ((R + 255) / 256) * 4 >= ctx->n_cu && !(use8 && c.head_dim == 64);
-  // at most 32 rows per kv head (decoding steps) over 8-bit slots: two wavefronts share the rows and halve every
-  // tile between them.  (Over bf16 slots such a step is bound by the key stream already, and the 4-wavefront kernel
-  // with its three loader wavefronts measures 3 % faster.)
-  const bool few = R <= 32 && use8;
   // few workgroups for the whole chip (one or two short queries): 64-row workgroups whose wavefront pairs halve every
   // tile between them -- twice the workgroups, half the dependent chain per tile
-  const bool halved = !wide && !few && !use8 && c.head_dim == 128 && R > 32 &&
+  const bool halved = !wide && !use8 && c.head_dim == 128 && R > 32 &&
                       (long)batch * c.n_kv_heads * ((R + 63) / 64) * 4 <= ctx->n_cu;
-  const int qrows = few ? 32 : wide ? 256 : halved ? 64 : 128;
+  const int qrows = wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
   const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
   if (n_splits <= 0) n_splits = choose_splits(wide ? ctx->n_cu : 2 * ctx->n_cu, (long)batch * c.n_kv_heads * q_tiles, min_tiles, cap);
@@ -1550,9 +1572,9 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
                      c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
   if (use8 && mixed) {
     if (c.head_dim == 128) {
-      if (few) PC_ATTN(128, 2, 2, true, 2, true); else if (wide) PC_ATTN(128, 8, 2, true, 1, true); else PC_ATTN(128, 4, 2, true, 1, true);
+      if (wide) PC_ATTN(128, 8, 2, true, 1, true); else PC_ATTN(128, 4, 2, true, 1, true);
     } else {
-      if (few) PC_ATTN(64, 2, 2, true, 2, true); else PC_ATTN(64, 4, 2, true, 1, true);
+      PC_ATTN(64, 4, 2, true, 1, true);
     }
   } else if (use8 && c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64 && c.slot_capacity / TK <= 32) {
     hipLaunchKernelGGL((reuse_attention_wide8_kernel<128>), grid, dim3(512), 0, stream, q, kf, vf_blk, (const uint8_t *)ks,
@@ -1560,9 +1582,9 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
                        c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml);
   } else if (use8) {
     if (c.head_dim == 128) {
-      if (few) PC_ATTN(128, 2, 2, true, 2); else if (wide) PC_ATTN(128, 8, 2, true); else PC_ATTN(128, 4, 2, true);
+      if (wide) PC_ATTN(128, 8, 2, true); else PC_ATTN(128, 4, 2, true);
     } else {
-      if (few) PC_ATTN(64, 2, 2, true, 2); else PC_ATTN(64, 4, 2, true);
+      PC_ATTN(64, 4, 2, true);
     }
   } else if (c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64) {
     hipLaunchKernelGGL((reuse_attention_wide_kernel<128>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev,
@@ -1580,20 +1602,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
 #undef PC_ATTN
   prof_end(ctx, PC_KERNEL_ATTENTION, stream);
   PC_HIP(ctx, hipGetLastError());
-  if (n_splits > 1) {
-    long total_rows = (long)batch * c.n_kv_heads * R;
-    const bool few_parts = n_splits <= 4;              // one lane per 16 output bytes, else four
-    long threads = total_rows * (c.head_dim / 8) * (few_parts ? 1 : 4);
-    int blocks = (int)((threads + 255) / 256);
-#define PC_COMBINE(DD, FF)                                                                                          \
-  hipLaunchKernelGGL((splitkv_combine_kernel<DD, FF>), dim3(blocks), dim3(256), 0, stream, part_o, part_ml, n_splits, \
-                     t_fresh, c.n_q_heads, c.n_kv_heads, total_rows, out)
-    if (c.head_dim == 128) { if (few_parts) PC_COMBINE(128, true); else PC_COMBINE(128, false); }
-    else { if (few_parts) PC_COMBINE(64, true); else PC_COMBINE(64, false); }
-#undef PC_COMBINE
-    PC_HIP(ctx, hipGetLastError());
-  }
-  return PC_OK;
+  return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
 }
 
 }  // namespace pc

@@ -7,10 +7,11 @@ import numpy as np
 import pytest
 import torch
 
+import oracle
 from paper_2601_11553_amd import workloads as wl
 from paper_2601_11553_amd.binding import Percache, PercacheError
 
-from gpu_util import DEV, bf16, host
+from gpu_util import DEV, bf16, check_close, host
 from test_gpu_stack import EPS, check_hidden, dev_layers, oracle_block
 
 pytestmark = pytest.mark.gpu
@@ -110,3 +111,85 @@ def _decode_case(batch, D, Hq, Hkv, H, F, L, C, n_c, t_prompt, n_steps, seed, fu
     with pytest.raises(PercacheError) as e:
         pc.percache_stack_decode(layers, F, EPS, x, chains, seq_slots)
     assert e.value.status == -4 and pc.percache_kv_len(0, seq_slots[-1]) == t_prompt + n_steps + (C - t_prompt - n_steps if batch == 1 else 0)
+
+
+@pytest.mark.parametrize("D,G,T,slots,n_chunks,n_splits", [
+    (128, 2, 1, "bf16", 6, 0), (128, 1, 16, "bf16", 3, 2), (128, 3, 6, "8bit", 5, 0), (128, 4, 8, "mixed", 7, 3), (64, 7, 1, "mixed", 70, 0),
+    (64, 7, 4, "bf16", 5, 4), (64, 1, 32, "8bit", 2, 0), (128, 2, 9, "mixed", 66, 0), (128, 16, 1, "8bit", 4, 2), (64, 4, 1, "bf16", 0, 0),
+])
+def test_attention_of_very_few_rows(D, G, T, slots, n_chunks, n_splits):
+    """The kernel for at most 32 rows per kv head: one and two blocks of 16 rows, several fresh tokens (causal among them, over
+    both blocks of 16 fresh keys), chunks of 1 to 128 tokens and unused ones, lists past 64 chunks, each slot format, with the
+    key axis cut as the library chooses and as forced; through the fused call (which starts from the projection's sums) and
+    through the attention call alone."""
+    g = np.random.default_rng(7000 + D + 16 * G + T)
+    Hkv, H, C, B = 2, 128, 128, 2
+    Hq, n_slots = G * Hkv, max(2, 2 * n_chunks)
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=n_slots // 2) if slots == "mixed" else {}
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=n_slots, slot_capacity=C,
+                  max_pos=n_chunks * C + T, device=DEV, **kind)
+    ids = g.permutation(n_slots)[:B * n_chunks].reshape(B, n_chunks).astype(np.int32)
+    used = np.where(g.random((B, n_chunks)) < 0.2, 0, g.integers(1, C + 1, (B, n_chunks))).astype(np.int32)
+    for s in ids.reshape(-1):
+        pc.percache_kv_put(0, int(s), bf16(g.standard_normal((Hkv, C, D))), bf16(g.standard_normal((Hkv, C, D))))
+    W = wl.round_bf16(g.standard_normal(((Hq + 2 * Hkv) * D, H)).astype(np.float32) * np.float32(0.1))
+    X = wl.round_bf16(g.standard_normal((B, T, H)).astype(np.float32))
+    kf, vf = (torch.empty((B, Hkv, T, D), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    fused = pc.percache_prefill_reuse(0, bf16(X), bf16(W), ids, used, k_fresh_out=kf, v_fresh_out=vf)
+    q, k1, v1 = pc.percache_qkv_rope(0, bf16(X), bf16(W), ids, used)
+    alone = pc.percache_attention_reuse(0, q, k1, v1, ids, used, n_splits=n_splits)
+    torch.cuda.synchronize()
+    for b in range(B):
+        kv = [pc.percache_kv_get(0, int(s)) for s in ids[b]]
+        sk = np.stack([host(k) for k, _ in kv]) if kv else np.zeros((0, Hkv, C, D), np.float32)
+        sv = np.stack([host(v) for _, v in kv]) if kv else sk.copy()
+        ref, _, _, _ = oracle.prefill_reuse(X[b], W, Hq, Hkv, D, 10000.0, sk, sv, np.arange(n_chunks, dtype=np.int32), used[b])
+        check_close(host(fused[b]), ref, f"fused D={D} G={G} T={T} {slots} query {b}")
+        check_close(host(alone[b]), ref, f"attention alone, n_splits {n_splits}, query {b}")
+        # (the two paths round the same fp32 sums, taken in another order over the slices)
+        assert np.abs(host(kf[b]) - host(k1[b])).max() <= 2.0 ** -7 * np.abs(host(k1[b])).max()
+        assert np.abs(host(vf[b]) - host(v1[b])).max() <= 2.0 ** -7 * np.abs(host(v1[b])).max()
+    pc.close()
+
+
+@pytest.mark.parametrize("slots,T", [("bf16", 1), ("bf16", 5), ("mixed", 3), ("8bit", 1)])
+def test_decode_step_appends_over_a_block_border(slots, T):
+    """Decoding steps that fill, cross and open 64-key blocks of the sequence slots, with queries that append nothing and
+    queries of both slot formats in one batch: every slot must read back what separate appends of the same K/V give."""
+    D, Hq, Hkv, H, F, C, B = 128, 4, 2, 128, 64, 192, 3
+    layer = dev_layers([wl.stack_weights(33, 0, H, Hq, Hkv, D, F)])[0]
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=2) if slots == "mixed" else {}
+    pc, twin = (Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=6, slot_capacity=C, max_pos=C,
+                         device=DEV, **kind) for _ in range(2))
+    g = np.random.default_rng(8000 + T)
+    own, start = [0, 4, 5], [63, 0, 64 - T]             # (mixed: slots 4 and 5 are 8-bit)
+    for b in (0, 2):
+        k, v = bf16(g.standard_normal((Hkv, start[b], D))), bf16(g.standard_normal((Hkv, start[b], D)))
+        for p in (pc, twin):
+            p.percache_kv_put(0, own[b], k, v)
+    for step in range(3):
+        have = [pc.percache_kv_len(0, s) for s in own]
+        n_chunks, ids = [int(n > 0) for n in have], [[s if n else 0] for s, n in zip(own, have)]
+        append = [own[0], -1 if step == 1 else own[1], own[2]]
+        x = bf16(g.standard_normal((B, T, H)))
+        pc.percache_stack_decode([layer], F, EPS, x, ids, append, n_chunks=n_chunks)
+        n = (x.float() * torch.rsqrt((x.float() ** 2).mean(-1, keepdim=True) + EPS) * layer["gain1"].float()).bfloat16()
+        _, k1, v1 = twin.percache_qkv_rope(0, n, layer["wqkv"], ids, None, n_chunks)
+        for b in range(B):
+            if append[b] < 0:
+                assert pc.percache_kv_len(0, own[b]) == have[b]
+                continue
+            twin.percache_kv_append(0, own[b], k1[b], v1[b])
+            assert pc.percache_kv_len(0, own[b]) == have[b] + T
+            got, ref = pc.percache_kv_get(0, own[b]), twin.percache_kv_get(0, own[b])
+            torch.cuda.synchronize()
+            is8 = slots == "8bit" or (slots == "mixed" and own[b] >= 4)
+            for x_got, x_ref in zip(got, ref):
+                # the two differ by a rounding of the normed row and one of the result (2^-8 each way of the largest value,
+                # at most two steps), an 8-bit code then by at most one step of 1/8
+                assert (x_got.float() - x_ref.float()).abs().max() <= (2.0 ** -3 if is8 else 2.0 ** -6) * x_ref.float().abs().max(), (step, b)
+                if not is8:
+                    assert torch.equal(x_got[:, :have[b]], x_ref[:, :have[b]])
+            twin.percache_kv_put(0, own[b], *got)       # the twin goes on from the step's own values
+    pc.close()
+    twin.close()
