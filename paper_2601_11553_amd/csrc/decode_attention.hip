@@ -58,63 +58,64 @@ struct Lds {
   static constexpr int K16 = TK * D * 2, V16 = K16, K8 = TK * D, V8 = K8;
   static constexpr int STAGE = FMT == 1 ? K8 + V8 : K16 + V16;
   static constexpr int O_ROW = D + 4;                                    // floats per output row of a wavefront (padded)
-  static constexpr int MERGE = NW * NR * 16 * (O_ROW + 2) * 4 + NR * 16 * 32 * 4;  // outputs, (m, l), fresh probabilities
+  static constexpr int MERGE = NW * NR * 16 * (O_ROW + 2) * 4 + NR * 16 * 32 * 4 + 32 * D * 2;  // outputs, (m, l), fresh probabilities, fresh V
   static constexpr int BYTES = NSTG * STAGE > MERGE ? NSTG * STAGE : MERGE;
 };
 
-// Elements 32 ks + 8 g .. +7 of one projected head row of D fp32 sums (row16: this lane's row, the four lanes g share it):
-// bias, RMSNorm over the head (gain; null: none), RoPE at pos (rope; null: none), one rounding to bf16.
+// Elements 32 ks + 8 g .. +7 of one projected head row of D fp32 sums (the four lanes g share a row): load() asks for
+// everything, finish() applies bias, RMSNorm over the head (gain; null: none) and RoPE and rounds to bf16 once.
 template <int D>
-__device__ __forceinline__ void finish_row(const float *__restrict__ raw, const __bf16 *__restrict__ bias, const __bf16 *__restrict__ gain, float eps,
-                                           const float2 *__restrict__ rope, int pos, int g, bf16x8 (&out)[D / 32]) {
-  constexpr int KS = D / 32;
+struct RawRow {
+  static constexpr int KS = D / 32;
   f32x4 x[KS][2], cs[KS / 2][4];
   bf16x8 bi[KS], gn[KS];
+  __device__ __forceinline__ void load(const float *__restrict__ sums, const __bf16 *__restrict__ bias, const __bf16 *__restrict__ gain,
+                                       const float2 *__restrict__ rope, int pos, int g) {
 #pragma unroll
-  for (int ks = 0; ks < KS; ++ks) {
-    x[ks][0] = *(const f32x4 *)(raw + ks * 32 + g * 8);
-    x[ks][1] = *(const f32x4 *)(raw + ks * 32 + g * 8 + 4);
-    if (bias) bi[ks] = *(const bf16x8 *)(bias + ks * 32 + g * 8);
-    if (gain) gn[ks] = *(const bf16x8 *)(gain + ks * 32 + g * 8);
-  }
-  if (rope) {
+    for (int ks = 0; ks < KS; ++ks) {
+      x[ks][0] = *(const f32x4 *)(sums + ks * 32 + g * 8);
+      x[ks][1] = *(const f32x4 *)(sums + ks * 32 + g * 8 + 4);
+    }
 #pragma unroll
     for (int ks = 0; ks < KS / 2; ++ks)
 #pragma unroll
       for (int h = 0; h < 4; ++h) cs[ks][h] = *(const f32x4 *)(rope + (size_t)pos * (D / 2) + ks * 32 + g * 8 + h * 2);
-  }
-  if (bias) {
 #pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] += (float)bi[ks][e];
-  }
-  if (gain) {
-    float s = 0.f;
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) s += x[ks][e >> 2][e & 3] * x[ks][e >> 2][e & 3];
-    const float r = 1.0f / sqrtf(row_sum(s) / (float)D + eps);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] *= r * (float)gn[ks][e];
-  }
-#pragma unroll
-  for (int ks = 0; ks < KS / 2; ++ks)
-#pragma unroll
-    for (int e = 0; e < 8; ++e) {
-      float lo = x[ks][e >> 2][e & 3], hi = x[ks + KS / 2][e >> 2][e & 3];
-      if (rope) {
-        const float c = cs[ks][e >> 1][2 * (e & 1)], sn = cs[ks][e >> 1][2 * (e & 1) + 1], a = lo, b = hi;
-        lo = a * c - b * sn;
-        hi = b * c + a * sn;
-      }
-      out[ks][e] = (__bf16)lo;
-      out[ks + KS / 2][e] = (__bf16)hi;
+    for (int ks = 0; ks < KS; ++ks) {
+      if (bias) bi[ks] = *(const bf16x8 *)(bias + ks * 32 + g * 8);
+      if (gain) gn[ks] = *(const bf16x8 *)(gain + ks * 32 + g * 8);
     }
-}
+  }
+  __device__ __forceinline__ void finish(bool bias, bool gain, float eps, bf16x8 (&out)[KS]) {
+    if (bias) {
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] += (float)bi[ks][e];
+    }
+    if (gain) {
+      float s = 0.f;
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) s += x[ks][e >> 2][e & 3] * x[ks][e >> 2][e & 3];
+      const float r = 1.0f / sqrtf(row_sum(s) / (float)D + eps);
+#pragma unroll
+      for (int ks = 0; ks < KS; ++ks)
+#pragma unroll
+        for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] *= r * (float)gn[ks][e];
+    }
+#pragma unroll
+    for (int ks = 0; ks < KS / 2; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {
+        const float a = x[ks][e >> 2][e & 3], b = x[ks + KS / 2][e >> 2][e & 3];
+        const float c = cs[ks][e >> 1][2 * (e & 1)], sn = cs[ks][e >> 1][2 * (e & 1) + 1];
+        out[ks][e] = (__bf16)(a * c - b * sn);
+        out[ks + KS / 2][e] = (__bf16)(b * c + a * sn);
+      }
+  }
+};
 
 // RAW: q and the fresh k, v come as the projection's fp32 sums (raw.sums) and are finished here -- by every workgroup for
 // its query rows, under the latency of its first K/V tiles, and by the one with the fresh keys for k and v, which it also
@@ -142,29 +143,51 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     my_used = e.y;
   }
   const int n_chunks = trow[0], n_tiles = trow[2];
-  const int tile_begin = (int)((long)split * n_tiles / n_splits), tile_end = (int)((long)(split + 1) * n_tiles / n_splits);
+  // the fresh keys (and what comes with them) count as two tiles of the last partition
+  const int tile_begin = min((int)((long)split * (n_tiles + 2) / n_splits), n_tiles), tile_end = min((int)((long)(split + 1) * (n_tiles + 2) / n_splits), n_tiles);
   const int n = tile_end - tile_begin;
   const bool with_fresh = split == n_splits - 1;   // this workgroup also takes the fresh keys
 
   // this lane's query rows (columns of the products) and their Q operands: elements 32 ks + 8 g .. +7; the fresh keys
-  // 16 wave .. +15 likewise
+  // 16 wave .. +15 likewise.  RAW: everything these take is asked for here, before the tiles, and finished behind them.
   const int F = (Hq + 2 * Hkv) * D;   // (RAW) width of a row of sums: q heads, k heads, v heads
   const bool fresh_mine = with_fresh && wave * 16 < T;
   int my_i[NR];
   bf16x8 q[NR][KS], kf[KS];
+  RawRow<D> rq[NR], rk;
+  f32x4 rv[2];       // (RAW) sums and bias of 8 elements of a fresh V row: the first of this thread's units (row, 8 elements)
+  bf16x8 rv_bias;
+  int app_slot = -1, app_have = 0;
+  constexpr int VPR = D / 8;
+  const float *const row0 = raw.sums + (size_t)b * T * F;
+  const int v_at = (Hq + Hkv + gkv) * D;
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
-    const int row = min(r * 16 + l16, R - 1), hg = row / T;
+    const int row = min(r * 16 + l16, R - 1), hg = row / T, head = gkv * G + hg;
     my_i[r] = row - hg * T;
-    if constexpr (!RAW) {
-      const __bf16 *p = Q + (((size_t)b * Hq + gkv * G + hg) * T + my_i[r]) * D + g * 8;
+    if constexpr (RAW) {
+      rq[r].load(row0 + (size_t)my_i[r] * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.q_norm, raw.rope, trow[1] + my_i[r], g);
+    } else {
+      const __bf16 *p = Q + (((size_t)b * Hq + head) * T + my_i[r]) * D + g * 8;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) q[r][ks] = *(const bf16x8 *)(p + ks * 32);
     }
   }
-  if constexpr (!RAW) {
-    if (fresh_mine) {
-      const __bf16 *p = Kf + (((size_t)b * Hkv + gkv) * T + min(wave * 16 + l16, T - 1)) * D + g * 8;
+  if (with_fresh) {
+    const int t = min(wave * 16 + l16, T - 1), head = Hq + gkv;
+    if constexpr (RAW) {
+      rk.load(row0 + (size_t)t * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.k_norm, raw.rope, trow[1] + t, g);
+      const int u = min(tid, T * VPR - 1);
+      const float *p = row0 + (size_t)(u / VPR) * F + v_at + u % VPR * 8;
+      rv[0] = *(const f32x4 *)p;
+      rv[1] = *(const f32x4 *)(p + 4);
+      if (raw.ex.bias) rv_bias = *(const bf16x8 *)(raw.ex.bias + v_at + u % VPR * 8);
+      if (raw.append) {
+        app_slot = raw.append[2 * b];
+        app_have = raw.append[2 * b + 1];
+      }
+    } else if (fresh_mine) {
+      const __bf16 *p = Kf + (((size_t)b * Hkv + gkv) * T + t) * D + g * 8;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8 *)(p + ks * 32);
     }
@@ -360,24 +383,10 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
 #pragma unroll
   for (int k = 0; k < NSTG - 1; ++k)
     if (k < n) request(k);
-  int app_slot = -1, app_have = 0;
   if constexpr (RAW) {
-    const int l_pre = trow[1];
-    const float *row0 = raw.sums + (size_t)b * T * F;
 #pragma unroll
-    for (int r = 0; r < NR; ++r) {
-      const int head = gkv * G + min(r * 16 + l16, R - 1) / T;
-      finish_row<D>(row0 + (size_t)my_i[r] * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.q_norm, raw.ex.eps, raw.rope,
-                    l_pre + my_i[r], g, q[r]);
-    }
-    if (with_fresh && raw.append) {
-      app_slot = raw.append[2 * b];
-      app_have = raw.append[2 * b + 1];
-    }
-    if (fresh_mine) {
-      const int t = min(wave * 16 + l16, T - 1), head = Hq + gkv;
-      finish_row<D>(row0 + (size_t)t * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.k_norm, raw.ex.eps, raw.rope, l_pre + t, g, kf);
-    }
+    for (int r = 0; r < NR; ++r) rq[r].finish(raw.ex.bias, raw.ex.q_norm, raw.ex.eps, q[r]);
+    if (with_fresh) rk.finish(raw.ex.bias, raw.ex.k_norm, raw.ex.eps, kf);
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r)
@@ -444,6 +453,45 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
   float *om = (float *)lds;                                        // [wave][row][O_ROW]
   float *ml = om + NW * NR * 16 * L::O_ROW;                        // [wave][row][2]
   float *pl = ml + NW * NR * 16 * 2;                               // [row][32]
+  __bf16 *vl = (__bf16 *)(pl + NR * 16 * 32);                      // fresh V [T][D]
+  if (with_fresh) {
+    // the fresh V rows: to LDS for the merge; RAW also where they are kept, dense and in the 64-key blocks of the slot
+    for (int u = tid; u < T * VPR; u += 64 * NW) {
+      const int t = u / VPR, dv = u - t * VPR;
+      bf16x8 v;
+      if constexpr (RAW) {
+        if (u != tid) {
+          const float *p = row0 + (size_t)t * F + v_at + dv * 8;
+          rv[0] = *(const f32x4 *)p;
+          rv[1] = *(const f32x4 *)(p + 4);
+          if (raw.ex.bias) rv_bias = *(const bf16x8 *)(raw.ex.bias + v_at + dv * 8);
+        }
+#pragma unroll
+        for (int e = 0; e < 8; ++e) v[e] = (__bf16)(rv[e >> 2][e & 3] + (raw.ex.bias ? (float)rv_bias[e] : 0.f));
+        *(bf16x8 *)(raw.v_out + (((size_t)b * Hkv + gkv) * T + t) * D + dv * 8) = v;
+        if (app_slot >= 0) {
+          const int at = app_have + t, in = at & (TK - 1);
+          __bf16 *dst = raw.v_slots + (((size_t)app_slot * Hkv + gkv) * C + (at - in)) * D + (in & ~15) + pc::blocked_key(in & 15);
+#pragma unroll
+          for (int e = 0; e < 8; ++e) dst[(dv * 8 + e) * TK] = v[e];
+        }
+      } else {
+        v = *(const bf16x8 *)(Vf + (((size_t)b * Hkv + gkv) * T + t) * D + dv * 8);
+      }
+      *(bf16x8 *)(vl + t * D + dv * 8) = v;
+    }
+    if constexpr (RAW) {
+      // a block that these tokens open gets zeros behind the last of them (its padding stays finite)
+      const int end = app_have + T, tail = end & (TK - 1);
+      if (app_slot >= 0 && tail && (app_have == 0 || (end - 1) / TK > (app_have - 1) / TK)) {
+        __bf16 *dst = raw.v_slots + (((size_t)app_slot * Hkv + gkv) * C + (end - tail)) * D;
+        for (int u = tid; u < D * TK; u += 64 * NW) {
+          const int p = u & (TK - 1);
+          if ((p & ~15) + pc::blocked_key(p & 15) >= tail) dst[u] = (__bf16)0.f;
+        }
+      }
+    }
+  }
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int row = r * 16 + l16;
@@ -457,46 +505,6 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     if (fresh_mine) *(f32x4 *)(pl + row * 32 + wave * 16 + g * 4) = pf[r];
   }
   __syncthreads();
-  constexpr int VPR = D / 8;
-  auto fresh_v = [&](int t, int dv) __attribute__((always_inline)) {   // elements 8 dv .. +7 of the fresh V row t
-    bf16x8 v;
-    if constexpr (RAW) {
-      const int at = (Hq + Hkv + gkv) * D + dv * 8;
-      const float *p = raw.sums + ((size_t)b * T + t) * F + at;
-      const f32x4 lo = *(const f32x4 *)p, hi = *(const f32x4 *)(p + 4);
-      bf16x8 bi;
-      if (raw.ex.bias) bi = *(const bf16x8 *)(raw.ex.bias + at);
-#pragma unroll
-      for (int e = 0; e < 8; ++e) v[e] = (__bf16)((e < 4 ? lo[e & 3] : hi[e & 3]) + (raw.ex.bias ? (float)bi[e] : 0.f));
-    } else {
-      v = *(const bf16x8 *)(Vf + (((size_t)b * Hkv + gkv) * T + t) * D + dv * 8);
-    }
-    return v;
-  };
-  if constexpr (RAW) {  // the fresh V as it is kept: dense, and in the 64-key blocks of the slot
-    if (with_fresh) {
-      for (int u = tid; u < T * VPR; u += 64 * NW) {
-        const int t = u / VPR, dv = u - t * VPR;
-        const bf16x8 v = fresh_v(t, dv);
-        *(bf16x8 *)(raw.v_out + (((size_t)b * Hkv + gkv) * T + t) * D + dv * 8) = v;
-        if (app_slot >= 0) {
-          const int at = app_have + t, in = at & (TK - 1);
-          __bf16 *dst = raw.v_slots + (((size_t)app_slot * Hkv + gkv) * C + (at - in)) * D + (in & ~15) + pc::blocked_key(in & 15);
-#pragma unroll
-          for (int e = 0; e < 8; ++e) dst[(dv * 8 + e) * TK] = v[e];
-        }
-      }
-      // a block that these tokens open gets zeros behind the last of them (its padding stays finite)
-      const int end = app_have + T, tail = end & (TK - 1);
-      if (app_slot >= 0 && tail && (app_have == 0 || (end - 1) / TK > (app_have - 1) / TK)) {
-        __bf16 *dst = raw.v_slots + (((size_t)app_slot * Hkv + gkv) * C + (end - tail)) * D;
-        for (int u = tid; u < D * TK; u += 64 * NW) {
-          const int p = u & (TK - 1);
-          if ((p & ~15) + pc::blocked_key(p & 15) >= tail) dst[u] = (__bf16)0.f;
-        }
-      }
-    }
-  }
   for (int u = tid; u < R * VPR; u += 64 * NW) {
     const int row = u / VPR, dv = u - row * VPR;
     float mw[NW], lw[NW], m = -INFINITY;
@@ -520,7 +528,7 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     if (with_fresh) {
       for (int t = 0; t <= i; ++t) {
         const float p = pl[row * 32 + t] * (t < 16 ? a[0] : a[1]);
-        const bf16x8 v = fresh_v(t, dv);
+        const bf16x8 v = *(const bf16x8 *)(vl + t * D + dv * 8);
 #pragma unroll
         for (int e = 0; e < 8; ++e) acc[e] += p * (float)v[e];
       }
@@ -549,9 +557,9 @@ namespace pc {
 // Partitions of the key axis: two tiles per workgroup while the whole call then fits one workgroup per CU, else as many as
 // make whole rounds of them.
 static int decode_splits(int n_cu, long base_wgs, int tiles, int cap) {
-  const long ns = (tiles + 1) / 2;
-  if (base_wgs * ns > n_cu) return choose_splits(n_cu, base_wgs, tiles, cap);
-  return (int)(ns < 1 ? 1 : ns > cap ? cap : ns);
+  const long ns = (tiles + 3) / 2;  // (the fresh keys make a partition of their own then)
+  if (base_wgs * ns > n_cu) return choose_splits(n_cu, base_wgs, tiles + 2, cap);
+  return (int)(ns > cap ? cap : ns);
 }
 
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
