@@ -142,7 +142,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void linear_resid
   pc::few::slice_product<NF, NT, WV, NSTG, false>(
       lds, [&](int r) __attribute__((always_inline)) { return W + (size_t)(n0 + r) * K; },
       [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, nullptr, K, wave, lane,
-      [&]() __attribute__((always_inline)) {
+      [&](char *, int, int) __attribute__((always_inline)) {
 #pragma unroll
         for (int j = 0; j < PER; ++j)
           if (wave + j * WV < NF * NT) res[j] = *(const uint2 *)(R + at(wave + j * WV));
@@ -158,6 +158,91 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void linear_resid
     unpack4(res[j], r);
     if (m0 + b % NT * 16 + l16 < M) *(uint2 *)(Y + at(b)) = pack4(s[0] + r[0], s[1] + r[1], s[2] + r[2], s[3] + r[3]);
   }
+}
+
+// The o_proj of a decoding step of one or two rows straight from the attention's split-KV partials: every wavefront merges the
+// rows it contracts (its slice of the heads) into LDS under the latency of its first weights, by the rule of
+// splitkv_combine_kernel (m = max m_s, weights l_s 2^(m_s - m), rounded to bf16 once), instead of a launch that merges and
+// one that reads the result back.  Lanes l and l + 32 share 8 columns of a row and take every other partition.
+constexpr int kMergeSteps = 8;   // steps of 64 columns per wavefront: up to 4096 columns
+__global__ __launch_bounds__(512) void oproj_merge_few_kernel(const __bf16 *__restrict__ part_o, const float *__restrict__ part_ml, int n_splits, int T,
+                                                              int Hkv, int G, int D, const __bf16 *__restrict__ W, const __bf16 *__restrict__ R,
+                                                              __bf16 *__restrict__ Y, int M, int N, int K, int n_wt) {
+  constexpr int WV = 8, NSTG = 2, CH = 10;
+  __shared__ __align__(16) char lds[pc::few::Tile<1, 1, WV, NSTG, false, kMergeSteps>::LDS_BYTES];
+  int wt, tt;
+  if (!pc::few::place(blockIdx.x, n_wt, 1, wt, tt)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
+  const int n0 = wt * 16;
+  const size_t at = (size_t)min(l16, M - 1) * N + n0 + g * 4;
+  uint2 res = make_uint2(0, 0);
+  f32x4 acc[1][1];
+  float ss[1];
+  pc::few::slice_product<1, 1, WV, NSTG, false, kMergeSteps>(
+      lds, [&](int r) __attribute__((always_inline)) { return W + (size_t)(n0 + r) * K; }, [](int) { return (const __bf16 *)nullptr; }, nullptr, K, wave,
+      lane,
+      [&](char *x, int s0, int n) __attribute__((always_inline)) {
+        if (wave == 0) res = *(const uint2 *)(R + at);
+        const int half = lane >> 5;
+        for (int u = lane & 31; u < M * n * 8; u += 32) {
+          const int c = u & 7, q = u >> 3, step = q % n, m = q / n;
+          const int k = (s0 + step) * 64 + c * 8, head = k / D, b = m / T, i = m - b * T;
+          const size_t prow = ((((size_t)b * Hkv + head / G) * G + head % G) * T + i) * n_splits;
+          const float2 *ml = (const float2 *)part_ml + prow;
+          const __bf16 *po = part_o + prow * D + (k - head * D);
+          float mx = -INFINITY, wsum = 0.f, a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
+          for (int sp0 = half; sp0 < n_splits; sp0 += 2 * CH) {
+            float2 e[CH];
+            pc::bf16x8 o[CH];
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+              const int sp = min(sp0 + 2 * j, n_splits - 1);
+              e[j] = ml[sp];
+              o[j] = *(const pc::bf16x8 *)(po + (size_t)sp * D);
+            }
+            float top = mx;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+              if (sp0 + 2 * j >= n_splits || !(e[j].y > 0.f)) e[j] = make_float2(-INFINITY, 0.f);   // (an empty partition has weight 0)
+              top = fmaxf(top, e[j].x);
+            }
+            const float shrink = mx == -INFINITY ? 0.f : exp2f(mx - top);
+            mx = top;
+            wsum *= shrink;
+#pragma unroll
+            for (int e8 = 0; e8 < 8; ++e8) a8[e8] *= shrink;
+#pragma unroll
+            for (int j = 0; j < CH; ++j) {
+              const float w = e[j].y > 0.f ? e[j].y * exp2f(e[j].x - top) : 0.f;
+              wsum += w;
+#pragma unroll
+              for (int e8 = 0; e8 < 8; ++e8) a8[e8] += w * (float)o[j][e8];
+            }
+          }
+          const float m2 = __shfl_xor(mx, 32, 64), both = fmaxf(mx, m2);
+          const float mine = mx == -INFINITY ? 0.f : exp2f(mx - both);
+          wsum *= mine;
+          wsum += __shfl_xor(wsum, 32, 64);
+          pc::bf16x8 v;
+          const float inv = wsum > 0.f ? 1.0f / wsum : 0.f;
+#pragma unroll
+          for (int e8 = 0; e8 < 8; ++e8) {
+            const float t = a8[e8] * mine;
+            v[e8] = (__bf16)((t + __shfl_xor(t, 32, 64)) * inv);
+          }
+          // (a store the compiler does not see: behind an ordinary one it waits for every request before each operand read)
+          const unsigned addr = (unsigned)(size_t)(__attribute__((address_space(3))) char *)x + step * 2048 + m * 128 + ((c ^ pc::gemm::swz128(m)) * 16);
+          if (half == 0) asm volatile("ds_write_b128 %0, %1" : : "v"(addr), "v"(v) : "memory");
+        }
+        asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+      },
+      acc, ss);
+  pc::few::share_slices<1, 1, WV, NSTG, false>(lds, wave, lane, acc, ss);
+  if (wave != 0 || l16 >= M) return;
+  const f32x4 s = pc::few::tile_sum<1, 1, WV>(lds, 0, 0, lane);
+  float r[4];
+  unpack4(res, r);
+  *(uint2 *)(Y + at) = pack4(s[0] + r[0], s[1] + r[1], s[2] + r[2], s[3] + r[3]);
 }
 
 // Y[M, F] = silu(n Wgate^T) * (n Wup^T) with n = RMSNorm(A; gain, eps).  Weight blocks 0 .. NF/2 - 1 of a tile are gate
@@ -176,7 +261,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void swiglu_few_k
   float ss[NT];
   pc::few::slice_product<NF, NT, WV, NSTG, true>(
       lds, [&](int r) __attribute__((always_inline)) { return (r < 16 * HALF ? Wg + (size_t)(f0 + r) * K : Wu + (size_t)(f0 + r - 16 * HALF) * K); },
-      [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, []() {}, acc, ss);
+      [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, [](char *, int, int) {}, acc, ss);
   pc::few::share_slices<NF, NT, WV, NSTG, true>(lds, wave, lane, acc, ss);
 #pragma unroll
   for (int b = wave; b < HALF * NT; b += WV) {
@@ -227,6 +312,22 @@ pc_status launch_residual_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *
                      res, y, M, N, K, n_wt, n_tt)
   PC_FEW(1, 1); else PC_FEW(2, 1); else PC_FEW(1, 2); else PC_FEW(2, 2); else PC_FEW(2, 4); else PC_FEW(4, 4);
 #undef PC_FEW
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
+}
+// Whether the o_proj of M rows merges the attention's partials itself: where a wavefront's share is at most two rounds of its
+// 32 lane pairs (8 rows x steps of 64 columns).  One row of 2048, 20 partitions: 6.4 us against 5.3 + 4.7 for the merge launch
+// and the plain kernel; eight rows of 3072 (twelve rounds): 34.7 against 4.8 + 9.2.
+bool oproj_merges(const percache_config &c, long M) {
+  const int steps = (c.n_q_heads * c.head_dim + 511) / 512;
+  return steps <= kMergeSteps && M * steps <= 8;
+}
+pc_status launch_oproj_merge(percache_ctx *ctx, const __bf16 *part_o, const float *part_ml, int n_splits, int t_fresh, const __bf16 *w,
+                             const __bf16 *res, __bf16 *y, int M, hipStream_t s) {
+  const percache_config &c = ctx->cfg;
+  const int n_wt = c.hidden / 16;
+  hipLaunchKernelGGL(oproj_merge_few_kernel, dim3(pc::few::grid_of(n_wt, 1)), dim3(512), 0, s, part_o, part_ml, n_splits, t_fresh, c.n_kv_heads,
+                     c.n_q_heads / c.n_kv_heads, c.head_dim, w, res, y, M, c.hidden, c.n_q_heads * c.head_dim, n_wt);
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
@@ -424,6 +525,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     extras.eps = eps;
     extras.pre_norm = few ? (const __bf16 *)w.gain1 : nullptr;
     pc::RawQkv raw;
+    int left_splits = 1;  // partials that the attention left for the o_proj to merge
     if (raw_qkv) {
       raw.sums = ws.pf.qkv_raw;
       raw.ex = extras;
@@ -441,7 +543,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
       if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
     }
     PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v, ws.pf.v_blk, raw_qkv ? &raw : nullptr, batch, t_fresh, ws.pf.table, stride,
-                                min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats));
+                                min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats, decode && oproj_merges(c, M) ? &left_splits : nullptr));
     for (int b = 0; b < batch && n_save > 0; ++b)
       for (int j = 0; j < n_save; ++j) {
         const int slot = save_slots_host[(size_t)b * n_save + j];
@@ -458,7 +560,8 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     for (int b = 0; b < batch && append_slots_host; ++b)
       if (append_slots_host[b] >= 0) ctx->slot_len[(size_t)l * c.n_slots + append_slots_host[b]] += t_fresh;
     if (few) {
-      PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
+      if (left_splits > 1) PC_TRY(launch_oproj_merge(ctx, ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
+      else PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
       PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
       PC_TRY(launch_residual_few(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
     } else {

@@ -32,12 +32,14 @@ using gemm::swz128;
 using gemm::wait_vmcnt;
 
 // NF, NT: 16-row blocks of weights / of tokens in a workgroup's tile.  WV: wavefronts = slices of the contraction.
-template <int NF, int NT, int WV, int NSTG, bool NORM>
+// XL > 0: the token rows are not loaded but put into LDS by the caller, XL steps of 64 k-elements per wavefront at most.
+template <int NF, int NT, int WV, int NSTG, bool NORM, int XL = 0>
 struct Tile {
-  static constexpr int W_INSTR = 2 * NF, X_INSTR = 2 * NT;                 // load instructions (8 rows x 128 bytes) per stage
+  static constexpr int W_INSTR = 2 * NF, X_INSTR = XL ? 0 : 2 * NT;        // load instructions (8 rows x 128 bytes) per stage
   static constexpr int IPS = W_INSTR + X_INSTR + (NORM ? 1 : 0);           // and the 64 gains of the stage
   static constexpr int STAGE = (W_INSTR + X_INSTR) * 1024 + (NORM ? 128 : 0);
-  static constexpr int RING = WV * NSTG * STAGE;
+  static constexpr int X_OWN = XL * NT * 2048;                              // token rows of a wavefront's slice (XL)
+  static constexpr int RING = WV * (NSTG * STAGE + X_OWN);
   static constexpr int SUMS = WV * NF * NT * 1024;                          // partial tiles (fp32), in the ring's place
   static constexpr int SS = WV * NT * 64;                                   // sums of squares
   static constexpr int LDS_BYTES = RING > SUMS + SS ? RING : SUMS + SS;
@@ -46,12 +48,13 @@ struct Tile {
 };
 
 // w_row(r) / x_row(r): the K contiguous elements of the weight row / token row that tile row r stands for.  gain: [K] (NORM
-// only).  K: a multiple of 64.  after_request() runs once, behind the first requests (loads for the epilogue).
+// only).  K: a multiple of 64.  after_request(x, s0, n) runs once, behind the first requests (loads for the epilogue); with
+// XL it also fills x, this wavefront's LDS for the token rows of its n steps from s0 on ([step][row][64], chunk ^= swz128(row)).
 // On return acc[f][t] holds this wavefront's slice of the sums, ss[t] this lane's part of its token's sum of squares.
-template <int NF, int NT, int WV, int NSTG, bool NORM, class WRow, class XRow, class After>
+template <int NF, int NT, int WV, int NSTG, bool NORM, int XL = 0, class WRow, class XRow, class After>
 __device__ __forceinline__ void slice_product(char *lds, WRow w_row, XRow x_row, const __bf16 *__restrict__ gain, int K, int wave, int lane,
                                               After after_request, f32x4 (&acc)[NF][NT], float (&ss)[NT]) {
-  using S = Tile<NF, NT, WV, NSTG, NORM>;
+  using S = Tile<NF, NT, WV, NSTG, NORM, XL>;
 #pragma unroll
   for (int f = 0; f < NF; ++f)
 #pragma unroll
@@ -60,11 +63,11 @@ __device__ __forceinline__ void slice_product(char *lds, WRow w_row, XRow x_row,
   for (int t = 0; t < NT; ++t) ss[t] = 0.f;
   const int steps = K / 64;
   const int s0 = wave * steps / WV, n = (wave + 1) * steps / WV - s0;
+  char *ring = lds + wave * (NSTG * S::STAGE + S::X_OWN), *const x_own = ring + NSTG * S::STAGE;
   if (n <= 0) {
-    after_request();
+    after_request(x_own, s0, 0);
     return;
   }
-  char *ring = lds + wave * (NSTG * S::STAGE);
   const int l16 = lane & 15, g = lane >> 4;
   const __bf16 *src[S::W_INSTR + S::X_INSTR];
 #pragma unroll
@@ -97,7 +100,7 @@ __device__ __forceinline__ void slice_product(char *lds, WRow w_row, XRow x_row,
 #pragma unroll
   for (int s = 0; s < NSTG; ++s)
     if (s < n) request(s, s);
-  after_request();
+  after_request(x_own, s0, n);
   int rd[2];
 #pragma unroll
   for (int ks = 0; ks < 2; ++ks) rd[ks] = l16 * ROW + ((4 * ks + g) ^ swz128(l16)) * 16;
@@ -109,7 +112,7 @@ __device__ __forceinline__ void slice_product(char *lds, WRow w_row, XRow x_row,
     else if (later == 1) wait_vmcnt<S::IPS>();
     else wait_vmcnt<0>();
     asm volatile("" ::: "memory");
-    const char *wb = ring + st * S::STAGE, *xb = wb + S::W_INSTR * 1024, *gb = xb + S::X_INSTR * 1024;
+    const char *wb = ring + st * S::STAGE, *xb = XL ? x_own + s * (NT * 2048) : wb + S::W_INSTR * 1024, *gb = wb + (S::W_INSTR + S::X_INSTR) * 1024;
 #pragma unroll
     for (int ks = 0; ks < 2; ++ks) {
       bf16x8 w[NF], x[NT], gn;

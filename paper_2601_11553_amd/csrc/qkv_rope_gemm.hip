@@ -215,7 +215,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few
         return W + (size_t)(head * D + sub * PAIRS + (r < PAIRS ? r : D / 2 + r - PAIRS)) * H;
       },
       [&](int r) __attribute__((always_inline)) { return X + (size_t)min(m0 + r, M - 1) * H; }, ex.pre_norm, H, wave, lane,
-      [&]() __attribute__((always_inline)) {
+      [&](char *, int, int) __attribute__((always_inline)) {
         if (!rotate) return;
 #pragma unroll
         for (int j = 0; j < PER; ++j) {
@@ -351,7 +351,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_raw_few_
   float ss[NT];
   pc::few::slice_product<NF, NT, WV, NSTG, NORM>(
       lds, [&](int r) __attribute__((always_inline)) { return W + (size_t)(n0 + r) * K; },
-      [&](int r) __attribute__((always_inline)) { return X + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, []() {}, acc, ss);
+      [&](int r) __attribute__((always_inline)) { return X + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, [](char *, int, int) {}, acc, ss);
   pc::few::share_slices<NF, NT, WV, NSTG, NORM>(lds, wave, lane, acc, ss);
 #pragma unroll
   for (int b = wave; b < NF * NT; b += WV) {

@@ -1520,7 +1520,7 @@ static pc_status launch_combine(percache_ctx *ctx, const __bf16 *part_o, const f
 
 pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
                            const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int min_tiles,
-                           int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats) {
+                           int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats, int *left_splits) {
   const percache_config &c = ctx->cfg;
   const int G = c.n_q_heads / c.n_kv_heads, R = G * t_fresh;
   if (decode_rows(c, t_fresh)) {
@@ -1529,6 +1529,10 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
                                                  min_tiles - (t_fresh + TK - 1) / TK, n_splits, out, part_o, part_ml, stream, formats);
     if (st != PC_OK) return st;
     prof_end(ctx, PC_KERNEL_ATTENTION, stream);
+    if (left_splits) {
+      *left_splits = n_splits;
+      return PC_OK;
+    }
     return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
