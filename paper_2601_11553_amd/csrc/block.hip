@@ -491,7 +491,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
   hipStream_t s = (hipStream_t)stream;
   // a decoding step of few rows: the attention kernel finishes q, k and v from the projection's sums and appends the fresh
   // K/V to bf16 slots itself; (slot, tokens it holds) of every query go to the device behind the chunk lists
-  const bool decode = pc::decode_rows(c, t_fresh), raw_qkv = decode && pc::few_rows(M);
+  const bool decode = pc::decode_rows(c, t_fresh), raw_qkv = decode && pc::few_rows(c, M);
   bool append_kernel = append_slots_host != nullptr;  // some append is left to a kernel of its own
   if (raw_qkv && append_slots_host && !table_dev) {
     append_kernel = false;
@@ -516,7 +516,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     const percache_block_weights &w = layers_host[l];
 #define PC_TRY(call) do { st = (call); if (st != PC_OK) return st; } while (0)
     // few token rows: one launch per projection, the RMSNorms folded into the projections behind them
-    const bool few = pc::few_rows(M);
+    const bool few = pc::few_rows(c, M);
     if (!few) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
     pc::QkvExtras extras;
     extras.bias = (const __bf16 *)w.qkv_bias;
@@ -539,7 +539,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     } else {
       bool v_blocked = decode;  // (in a decoding step nobody reads V as blocks)
       PC_TRY(pc::launch_qkv_rope(ctx, few ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
-                                 ws.pf.v, s, extras, decode ? nullptr : ws.pf.v_blk, decode ? nullptr : &v_blocked));
+                                 ws.pf.v, s, extras, decode ? nullptr : ws.pf.v_blk, decode ? nullptr : &v_blocked, ws.pf.qkv_raw));
       if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
     }
     PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v, ws.pf.v_blk, raw_qkv ? &raw : nullptr, batch, t_fresh, ws.pf.table, stride,

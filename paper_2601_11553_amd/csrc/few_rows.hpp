@@ -202,7 +202,7 @@ struct Choice {
   int nf, nt;
 };
 inline Choice choose_tile(int n_cu, int M, int n16, int min_nf) {
-  static const Choice cand[] = {{1, 1}, {2, 1}, {1, 2}, {2, 2}, {2, 4}, {4, 4}};
+  static const Choice cand[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}, {4, 4}};
   Choice best{0, 0};
   long best_cost = 0;
   for (const Choice &c : cand) {

@@ -132,7 +132,7 @@ struct PrefillWs {
   int32_t *table;
   __bf16 *q, *k, *v;
   __bf16 *v_blk;   // fresh V as 64-key blocks [B*Hkv][ceil(T/64)][D][64]
-  float *qkv_raw;  // the projection's sums [B*T][(Hq + 2 Hkv) * D] (few rows of a decoding step only)
+  float *qkv_raw;  // the projection's sums [B*T][(Hq + 2 Hkv) * D] (few rows only)
   __bf16 *part_o;  // [rows][splits][D], normalised per split
   float *part_ml;  // [rows][splits][2]
   int max_splits;  // partitions of the key axis the partial buffers can hold
@@ -158,8 +158,10 @@ struct QkvExtras {
   float eps = 1e-6f;
   bool any() const { return bias || q_norm || k_norm; }
 };
-// Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in.
-inline bool few_rows(long M) { return M <= 192; }
+// Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in.  Where the line
+// lies (us per layer without attention's cached part, these kernels | the 128-row tiles): width 1024: 55 | 138 at 200 rows, 77 |
+// 139 at 512, 132 | 158 at 1024, 267 | 181 at 2048; width 3072: 175 | 285 at 200, 195 | 286 at 320, 287 | 289 at 400.
+inline bool few_rows(const percache_config &c, long M) { return M <= 192 || (M <= 1024 && M * c.hidden <= 1 << 20); }
 // The projection of few token rows as fp32 sums [M][(Hq + 2 Hkv) * D], before bias, head norm and RoPE: what the attention
 // kernel of a decoding step starts from (it finishes q, k and v itself, see decode_attention.hip).
 struct RawQkv {
@@ -172,11 +174,11 @@ struct RawQkv {
 };
 pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream);
 // v_blk / v_blk_done: if given, the launch may also write V as the 64-key blocks of launch_v_repack and says so.
-// extras.pre_norm only where few_rows(batch * t_fresh).
+// extras.pre_norm only where few_rows(batch * t_fresh); raw: workspace of that case (M rows of fp32 sums) for a head norm.
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,
                           hipStream_t stream, const QkvExtras &extras = QkvExtras(), __bf16 *v_blk = nullptr,
-                          bool *v_blk_done = nullptr);
+                          bool *v_blk_done = nullptr, float *raw = nullptr);
 
 pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, int batch, int t_fresh, hipStream_t stream);
 // Whether a call's attention takes the kernel for very few rows per kv head (decode_attention.hip), which reads the fresh V

@@ -173,17 +173,16 @@ __global__ __launch_bounds__(WIDE ? 512 : 256, WIDE ? 1 : 2) void qkv_rope_kerne
 // Few token rows: the whole projection in one launch (few_rows.hpp), the RMSNorm of the input rows folded in (NORM).
 // A tile holds 8 NF (8 at NF = 1) rotation pairs of one head: tile rows r and r + PAIRS are features m and m + D/2.  At
 // NF >= 2 a lane finds both in accumulator blocks f and f + NF/2, at NF = 1 the high half sits in lane + 32.
-// HEADNORM: the tile is a whole head (NF = D/16, NT = 1) and q and k rows are normalised over it before the rotation.
-template <int D, int NF, int NT, bool NORM, bool HEADNORM>
+// (No head norm: a tile that holds a whole head would leave 32 workgroups at 32 heads -- such a projection goes through its
+// sums, see finish_rope_kernel.)
+template <int D, int NF, int NT, bool NORM>
 __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few_kernel(
     const __bf16 *__restrict__ X, const __bf16 *__restrict__ W, int M, int H, int t_fresh, int Hq, int Hkv, const int32_t *__restrict__ table,
     int tbl_stride, const float2 *__restrict__ rope, __bf16 *__restrict__ Q, __bf16 *__restrict__ K, __bf16 *__restrict__ V, pc::QkvExtras ex,
     __bf16 *__restrict__ V_blk, int n_wt, int n_tt) {
   constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG;
   constexpr int PAIRS = NF == 1 ? 8 : 8 * NF, TPH = D / 2 / PAIRS, NFP = NF == 1 ? 1 : NF / 2, PER = (NFP * NT + WV - 1) / WV;
-  static_assert(!HEADNORM || (NF * 16 == D && NT == 1 && NFP <= WV), "a whole head of one token block");
-  using Tile = pc::few::Tile<NF, NT, WV, NSTG, NORM>;
-  __shared__ __align__(16) char lds[Tile::LDS_BYTES];
+  __shared__ __align__(16) char lds[pc::few::Tile<NF, NT, WV, NSTG, NORM>::LDS_BYTES];
   int wt, tt;
   if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
@@ -226,67 +225,30 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few
       },
       acc, ss);
   pc::few::share_slices<NF, NT, WV, NSTG, NORM>(lds, wave, lane, acc, ss);
-  float head_r = 1.f;
-  const __bf16 *gain = nullptr;
-  float lo_n[4], hi_n[4];
-  if constexpr (HEADNORM) {  // one unit per wavefront: sums, bias, then the head's sum of squares over lanes and units
-    gain = head < Hq ? ex.q_norm : (head < Hq + Hkv ? ex.k_norm : nullptr);
-    float *hn = (float *)(lds + Tile::SUMS + Tile::SS);
-    static_assert(Tile::SUMS + Tile::SS + WV * 64 <= Tile::LDS_BYTES, "room for the head sums");
-    if (wave < NFP) {
-      const float r = NORM ? pc::few::row_factor<NF, NT, WV>(lds, 0, l16, H, ex.eps) : 1.f;
-      const f32x4 lo = pc::few::tile_sum<NF, NT, WV>(lds, wave, 0, lane) * r, hi = pc::few::tile_sum<NF, NT, WV>(lds, wave + NFP, 0, lane) * r;
-      float s = 0.f;
-#pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo_n[e] = lo[e] + (ex.bias ? (float)ex.bias[(size_t)head * D + first[0] + e] : 0.f);
-        hi_n[e] = hi[e] + (ex.bias ? (float)ex.bias[(size_t)head * D + first[0] + e + D / 2] : 0.f);
-        s += lo_n[e] * lo_n[e] + hi_n[e] * hi_n[e];
-      }
-      s += __shfl_xor(s, 16, 64);
-      s += __shfl_xor(s, 32, 64);
-      if (g == 0) hn[wave * 16 + l16] = s;
-    }
-    __syncthreads();
-    if (gain) {
-      float s = 0.f;
-#pragma unroll
-      for (int w = 0; w < NFP; ++w) s += hn[w * 16 + l16];
-      head_r = 1.0f / sqrtf(s / (float)D + ex.eps);
-    }
-  }
 #pragma unroll
   for (int j = 0; j < PER; ++j) {
     const int b = wave + j * WV;
     if (b >= NFP * NT) continue;
     const int t = b % NT, mm = first[j];
     float lo[4], hi[4];
-    if constexpr (HEADNORM) {
+    const float r = NORM ? pc::few::row_factor<NF, NT, WV>(lds, t, l16, H, ex.eps) : 1.f;
+    f32x4 sl = pc::few::tile_sum<NF, NT, WV>(lds, NF == 1 ? 0 : b / NT, t, lane), sh;
+    if constexpr (NF == 1) {
 #pragma unroll
-      for (int e = 0; e < 4; ++e) {
-        lo[e] = lo_n[e] * (gain ? head_r * (float)gain[mm + e] : 1.f);
-        hi[e] = hi_n[e] * (gain ? head_r * (float)gain[mm + e + D / 2] : 1.f);
-      }
+      for (int e = 0; e < 4; ++e) sh[e] = __shfl_xor(sl[e], 32, 64);
     } else {
-      const float r = NORM ? pc::few::row_factor<NF, NT, WV>(lds, t, l16, H, ex.eps) : 1.f;
-      f32x4 sl = pc::few::tile_sum<NF, NT, WV>(lds, NF == 1 ? 0 : b / NT, t, lane), sh;
-      if constexpr (NF == 1) {
+      sh = pc::few::tile_sum<NF, NT, WV>(lds, b / NT + NFP, t, lane);
+    }
 #pragma unroll
-        for (int e = 0; e < 4; ++e) sh[e] = __shfl_xor(sl[e], 32, 64);
-      } else {
-        sh = pc::few::tile_sum<NF, NT, WV>(lds, b / NT + NFP, t, lane);
-      }
+    for (int e = 0; e < 4; ++e) {
+      lo[e] = sl[e] * r;
+      hi[e] = sh[e] * r;
+    }
+    if (ex.bias) {
 #pragma unroll
       for (int e = 0; e < 4; ++e) {
-        lo[e] = sl[e] * r;
-        hi[e] = sh[e] * r;
-      }
-      if (ex.bias) {
-#pragma unroll
-        for (int e = 0; e < 4; ++e) {
-          lo[e] += (float)ex.bias[(size_t)head * D + mm + e];
-          hi[e] += (float)ex.bias[(size_t)head * D + mm + e + D / 2];
-        }
+        lo[e] += (float)ex.bias[(size_t)head * D + mm + e];
+        hi[e] += (float)ex.bias[(size_t)head * D + mm + e + D / 2];
       }
     }
     if (rotate) {
@@ -332,6 +294,78 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few
             if (k0 + (e & 3) + 8 * (e >> 2) >= tail) at[e] = (__bf16)0.f;
         }
       }
+    }
+  }
+}
+
+// From the projection's sums [M][F] to q, k and v: bias, RMSNorm over the head (gains q_norm, k_norm), RoPE, one rounding.
+// One thread per (token, head, 4 consecutive rotation pairs), the D / 8 threads of a head side by side in a wavefront.  Where V
+// is also laid out in 64-key blocks, a query's tokens are counted up to whole blocks (rows) and the surplus ones write zeros.
+// Against a projection tile that holds a whole head (32 workgroups x 256 KB of weights at 32 heads of 1024): 11.8 us at 100
+// rows; the sums 9.4 and this kernel 4.3, but at 264 rows the whole-head tiles would take three times as long, the sums 1.6 times.
+template <int D>
+__global__ __launch_bounds__(256) void finish_rope_kernel(const float *__restrict__ sums, int batch, int t_fresh, int rows, int Hq, int Hkv,
+                                                          const int32_t *__restrict__ table, int tbl_stride, const float2 *__restrict__ rope,
+                                                          __bf16 *__restrict__ Q, __bf16 *__restrict__ K, __bf16 *__restrict__ V, pc::QkvExtras ex,
+                                                          __bf16 *__restrict__ V_blk) {
+  constexpr int QUADS = D / 8;
+  const long gid = (long)blockIdx.x * blockDim.x + threadIdx.x;
+  const int n_all = Hq + 2 * Hkv;
+  if (gid >= (long)batch * rows * n_all * QUADS) return;
+  const int mm = (int)(gid % QUADS) * 4, head = (int)(gid / QUADS % n_all), row_id = (int)(gid / QUADS / n_all);
+  const int b = row_id / rows, i = row_id - b * rows;
+  const bool real = i < t_fresh;
+  if (!real && head < Hq + Hkv) return;
+  const float *src = sums + ((size_t)(b * t_fresh + min(i, t_fresh - 1)) * n_all + head) * D + mm;
+  f32x4 lo = *(const f32x4 *)src, hi = *(const f32x4 *)(src + D / 2);
+  __bf16 *dst;
+  int hh, n_heads;
+  bool rotate = true;
+  if (head < Hq) { dst = Q; hh = head; n_heads = Hq; }
+  else if (head < Hq + Hkv) { dst = K; hh = head - Hq; n_heads = Hkv; }
+  else { dst = V; hh = head - Hq - Hkv; n_heads = Hkv; rotate = false; }
+  if (ex.bias) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      lo[e] += (float)ex.bias[(size_t)head * D + mm + e];
+      hi[e] += (float)ex.bias[(size_t)head * D + mm + e + D / 2];
+    }
+  }
+  float ss = 0.f;
+#pragma unroll
+  for (int e = 0; e < 4; ++e) ss += lo[e] * lo[e] + hi[e] * hi[e];
+#pragma unroll
+  for (int o = 1; o < QUADS; o <<= 1) ss += __shfl_xor(ss, o, 64);
+  const __bf16 *gain = head < Hq ? ex.q_norm : (head < Hq + Hkv ? ex.k_norm : nullptr);
+  if (gain) {
+    const float r = 1.0f / sqrtf(ss / (float)D + ex.eps);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      lo[e] *= r * (float)gain[mm + e];
+      hi[e] *= r * (float)gain[mm + e + D / 2];
+    }
+  }
+  if (rotate) {
+    const f32x4 *p = (const f32x4 *)(rope + (size_t)(table[(size_t)b * tbl_stride + 1] + i) * (D / 2) + mm);
+    const f32x4 c01 = p[0], c23 = p[1];  // (cos, sin) of pairs mm, mm+1 and mm+2, mm+3
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const float c = e < 2 ? c01[2 * e] : c23[2 * e - 4], sn = e < 2 ? c01[2 * e + 1] : c23[2 * e - 3], x = lo[e], y = hi[e];
+      lo[e] = x * c - y * sn;
+      hi[e] = y * c + x * sn;
+    }
+  }
+  if (real) {
+    __bf16 *row = dst + (((size_t)b * n_heads + hh) * t_fresh + i) * D;
+    *(uint2 *)(row + mm) = pack4(lo[0], lo[1], lo[2], lo[3]);
+    *(uint2 *)(row + mm + D / 2) = pack4(hi[0], hi[1], hi[2], hi[3]);
+  }
+  if (V_blk && !rotate) {
+    __bf16 *vb = V_blk + (((size_t)b * n_heads + hh) * (rows >> 6) + (i >> 6)) * D * 64 + (i & 48) + pc::blocked_key(i & 15);
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      vb[(size_t)(mm + e) * 64] = (__bf16)(real ? lo[e] : 0.f);
+      vb[(size_t)(mm + e + D / 2) * 64] = (__bf16)(real ? hi[e] : 0.f);
     }
   }
 }
@@ -389,7 +423,7 @@ pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, in
 
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,
-                          hipStream_t stream, const QkvExtras &extras, __bf16 *v_blk, bool *v_blk_done) {
+                          hipStream_t stream, const QkvExtras &extras, __bf16 *v_blk, bool *v_blk_done, float *raw) {
   if (v_blk_done) *v_blk_done = false;
   const percache_config &c = ctx->cfg;
   const int M = batch * t_fresh;
@@ -398,27 +432,34 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
   if ((long)F * c.hidden >= (1L << 31) || (long)M * c.hidden >= (1L << 31))
     return fail(ctx, PC_ESHAPE, "operand larger than 2^31 elements");
   const float2 *rope = (const float2 *)ctx->rope;
-  if (few_rows(M)) {
+  if (few_rows(c, M)) {
     __bf16 *vb = v_blk && v_blk_done ? v_blk : nullptr;
     if (vb) *v_blk_done = true;
-    const bool head_norm = extras.q_norm || extras.k_norm, norm = extras.pre_norm;
-    const few::Choice ch = head_norm ? few::Choice{c.head_dim / 16, 1} : few::choose_tile(ctx->n_cu, M, F / 16, 1);
+    if (extras.q_norm || extras.k_norm) {  // the sums, then one small kernel over whole heads
+      const pc_status st = launch_qkv_raw(ctx, x, w, M, extras, raw, stream);
+      if (st != PC_OK) return st;
+      const int rows = vb ? (t_fresh + 63) / 64 * 64 : t_fresh;
+      const long threads = (long)batch * rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 8);
+#define PC_FINISH(DD)                                                                                                                   \
+  hipLaunchKernelGGL(finish_rope_kernel<DD>, dim3((unsigned)((threads + 255) / 256)), dim3(256), 0, stream, raw, batch, t_fresh, rows, c.n_q_heads, \
+                     c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb)
+      if (c.head_dim == 128) PC_FINISH(128); else PC_FINISH(64);
+#undef PC_FINISH
+      PC_HIP(ctx, hipGetLastError());
+      return PC_OK;
+    }
+    const few::Choice ch = few::choose_tile(ctx->n_cu, M, F / 16, 1);
     const int n_wt = F / (16 * ch.nf), n_tt = (M + 16 * ch.nt - 1) / (16 * ch.nt);
     prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
-#define PC_FEW_K(DD, NF, NT, NN, HH)                                                                                           \
-  hipLaunchKernelGGL((qkv_rope_few_kernel<DD, NF, NT, NN, HH>), dim3(few::grid_of(n_wt, n_tt)), dim3(64 * few::Form<NF, NT>::WV), 0, stream, x, w, \
+#define PC_FEW_K(DD, NF, NT, NN)                                                                                                \
+  hipLaunchKernelGGL((qkv_rope_few_kernel<DD, NF, NT, NN>), dim3(few::grid_of(n_wt, n_tt)), dim3(64 * few::Form<NF, NT>::WV), 0, stream, x, w, \
                      M, c.hidden, t_fresh, c.n_q_heads, c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb, n_wt, n_tt)
-#define PC_FEW(DD, NF, NT)                                                                                                     \
-  if (ch.nf == NF && ch.nt == NT) {                                                                                            \
-    if (norm) PC_FEW_K(DD, NF, NT, true, false); else PC_FEW_K(DD, NF, NT, false, false);                                       \
+#define PC_FEW(DD, NF, NT)                                                                          \
+  if (ch.nf == NF && ch.nt == NT) {                                                                 \
+    if (extras.pre_norm) PC_FEW_K(DD, NF, NT, true); else PC_FEW_K(DD, NF, NT, false);               \
   }
-#define PC_FEW_D(DD)                                                                                                           \
-  do {                                                                                                                         \
-    if (head_norm) {                                                                                                           \
-      if (norm) PC_FEW_K(DD, DD / 16, 1, true, true); else PC_FEW_K(DD, DD / 16, 1, false, true);                               \
-    } else PC_FEW(DD, 1, 1) else PC_FEW(DD, 2, 1) else PC_FEW(DD, 1, 2) else PC_FEW(DD, 2, 2) else PC_FEW(DD, 2, 4) else PC_FEW(DD, 4, 4) \
-  } while (0)
-    if (c.head_dim == 128) PC_FEW_D(128); else PC_FEW_D(64);
+#define PC_FEW_D(DD) PC_FEW(DD, 1, 1) else PC_FEW(DD, 2, 1) else PC_FEW(DD, 1, 2) else PC_FEW(DD, 2, 2) else PC_FEW(DD, 2, 4) else PC_FEW(DD, 4, 4)
+    if (c.head_dim == 128) { PC_FEW_D(128) } else { PC_FEW_D(64) }
 #undef PC_FEW_D
 #undef PC_FEW
 #undef PC_FEW_K

@@ -284,7 +284,8 @@ def test_projection_variants_bias_and_head_norm(D, t_fresh, which, heads):
     (128, (16, 8), 256, 2112, 1, 1, "none"), (128, (16, 8), 256, 2112, 16, 1, "bias"), (64, (8, 4), 384, 4160, 1, 17, "none"),
     (128, (16, 8), 256, 2112, 1, 33, "norm"), (128, (24, 8), 128, 3072, 2, 32, "none"), (128, (16, 8), 256, 2112, 5, 13, "bias"),
     (64, (8, 4), 384, 4160, 1, 129, "norm"), (128, (24, 8), 128, 3072, 3, 64, "bias"), (64, (8, 4), 384, 64, 2, 65, "none"),
-])
+    (128, (16, 8), 256, 448, 4, 256, "none"), (128, (4, 2), 1152, 64, 7, 131, "norm"), (64, (8, 4), 1152, 64, 7, 130, "norm"),   # 1024, 917, 910 rows:
+])                                                                                                # the line to the large tiles, both sides
 def test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which):
     """The projections of few token rows at the edges of their tiles: every tile the launcher chooses from (1 to 4 blocks of
     16 weight rows x 1 to 4 of 16 token rows), ragged token blocks, contractions shorter than the wavefronts' slices
