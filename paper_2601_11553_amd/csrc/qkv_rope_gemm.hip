@@ -302,7 +302,8 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_rope_few
 // One thread per (token, head, 4 consecutive rotation pairs), the D / 8 threads of a head side by side in a wavefront.  Where V
 // is also laid out in 64-key blocks, a query's tokens are counted up to whole blocks (rows) and the surplus ones write zeros.
 // Against a projection tile that holds a whole head (32 workgroups x 256 KB of weights at 32 heads of 1024): 11.8 us at 100
-// rows; the sums 9.4 and this kernel 4.3, but at 264 rows the whole-head tiles would take three times as long, the sums 1.6 times.
+// rows, where the sums take 9.4 and this kernel 4.3; with more rows the whole-head tiles, 16 rows wide, run in rounds (272 of them at
+// 264 rows of 16 heads).
 template <int D>
 __global__ __launch_bounds__(256) void finish_rope_kernel(const float *__restrict__ sums, int batch, int t_fresh, int rows, int Hq, int Hkv,
                                                           const int32_t *__restrict__ table, int tbl_stride, const float2 *__restrict__ rope,

@@ -1412,23 +1412,37 @@ __global__ __launch_bounds__(256) void splitkv_combine_kernel(const __bf16 *__re
     for (int e8 = 0; e8 < 8; ++e8)
       acc[e8] = (w[0] * (float)o[0][e8] + w[1] * (float)o[1][e8]) + (w[2] * (float)o[2][e8] + w[3] * (float)o[3][e8]);
   } else {
-  float m = -INFINITY;
-#pragma unroll 4
-  for (int s = sg; s < n_splits; s += SG) {
-    const float2 e = ml[s];
-    m = fmaxf(m, e.y > 0.f ? e.x : -INFINITY);
-  }
-  m = fmaxf(m, __shfl_xor(m, VPR, 64));
-  m = fmaxf(m, __shfl_xor(m, 2 * VPR, 64));
-#pragma unroll 4
-  for (int s = sg; s < n_splits; s += SG) {
-    const float2 e = ml[s];
-    const float w = e.y > 0.f ? e.y * exp2f(e.x - m) : 0.f;  // an empty partition has weight 0 (its output row is 0)
-    pc::bf16x8 o = *(const pc::bf16x8 *)(po + (size_t)s * D);
+    // up to four of this lane's partitions at a time, everything they take in flight at once; the four lanes agree on the
+    // maximum before the weights are formed, so a list of up to 16 partitions costs one memory latency
+    float m = -INFINITY;
+    for (int s0 = 0; s0 < n_splits; s0 += 4 * SG) {
+      float2 e[4];
+      pc::bf16x8 o[4];
 #pragma unroll
-    for (int e8 = 0; e8 < 8; ++e8) acc[e8] += w * (float)o[e8];
-    wsum += w;
-  }
+      for (int j = 0; j < 4; ++j) {
+        const int s = s0 + sg + j * SG, sc = s < n_splits ? s : 0;
+        e[j] = ml[sc];
+        o[j] = *(const pc::bf16x8 *)(po + (size_t)sc * D);
+        if (s >= n_splits) e[j].y = 0.f;   // (as an empty partition: weight 0)
+      }
+      float top = m;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) top = fmaxf(top, e[j].y > 0.f ? e[j].x : -INFINITY);
+      top = fmaxf(top, __shfl_xor(top, VPR, 64));
+      top = fmaxf(top, __shfl_xor(top, 2 * VPR, 64));
+      const float shrink = m == -INFINITY ? 0.f : exp2f(m - top);
+      m = top;
+      wsum *= shrink;
+#pragma unroll
+      for (int e8 = 0; e8 < 8; ++e8) acc[e8] *= shrink;
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const float w = e[j].y > 0.f ? e[j].y * exp2f(e[j].x - m) : 0.f;
+#pragma unroll
+        for (int e8 = 0; e8 < 8; ++e8) acc[e8] += w * (float)o[j][e8];
+        wsum += w;
+      }
+    }
 #pragma unroll
   for (int sh = VPR; sh < LPR; sh <<= 1) {
     wsum += __shfl_xor(wsum, sh, 64);
