@@ -391,15 +391,11 @@ pc_status percache_kv_slice(percache_ctx *ctx, int32_t layer, const void *k_dev,
     for (int i = 0; i < j; ++i)
       if (slots_host[i] == slots_host[j]) return pc::fail(ctx, PC_EINVAL, "slot %d appears twice", slots_host[j]);
   }
-  for (int j = 0; j < n; ++j) {
-    if (slots_host[j] < 0) continue;
-    const int lo = bounds_host[j], cnt = bounds_host[j + 1] - lo;
-    pc_status st = pc::launch_kv_store(ctx, layer, slots_host[j], (const __bf16 *)k_dev + (size_t)lo * c.head_dim,
-                                       (const __bf16 *)v_dev + (size_t)lo * c.head_dim, cnt, (long)seq_len * c.head_dim,
-                                       (hipStream_t)stream);
-    if (st != PC_OK) return st;
-    ctx->slot_len[(size_t)layer * c.n_slots + slots_host[j]] = cnt;
-  }
+  const pc_status st = pc::launch_kv_slices(ctx, layer, slots_host, bounds_host, n, 1, (const __bf16 *)k_dev, (const __bf16 *)v_dev, seq_len,
+                                            (hipStream_t)stream);
+  if (st != PC_OK) return st;
+  for (int j = 0; j < n; ++j)
+    if (slots_host[j] >= 0) ctx->slot_len[(size_t)layer * c.n_slots + slots_host[j]] = bounds_host[j + 1] - bounds_host[j];
   return PC_OK;
 }
 
@@ -544,15 +540,12 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     }
     PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v, ws.pf.v_blk, raw_qkv ? &raw : nullptr, batch, t_fresh, ws.pf.table, stride,
                                 min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats, decode && oproj_merges(c, M) ? &left_splits : nullptr));
-    for (int b = 0; b < batch && n_save > 0; ++b)
-      for (int j = 0; j < n_save; ++j) {
-        const int slot = save_slots_host[(size_t)b * n_save + j];
-        if (slot < 0) continue;
-        const int lo = save_bounds_host[j], cnt = save_bounds_host[j + 1] - lo;
-        const size_t at = ((size_t)b * c.n_kv_heads * t_fresh + lo) * c.head_dim;
-        PC_TRY(pc::launch_kv_store(ctx, l, slot, ws.pf.k + at, ws.pf.v + at, cnt, (long)t_fresh * c.head_dim, s));
-        ctx->slot_len[(size_t)l * c.n_slots + slot] = cnt;
-      }
+    if (n_save > 0) {
+      PC_TRY(pc::launch_kv_slices(ctx, l, save_slots_host, save_bounds_host, n_save, batch, ws.pf.k, ws.pf.v, t_fresh, s));
+      for (int i = 0; i < batch * n_save; ++i)
+        if (save_slots_host[i] >= 0)
+          ctx->slot_len[(size_t)l * c.n_slots + save_slots_host[i]] = save_bounds_host[i % n_save + 1] - save_bounds_host[i % n_save];
+    }
     if (append_kernel) {
       // after the attention launch in stream order: the keys it gathered from these slots are the older ones
       PC_TRY(pc::launch_kv_append(ctx, l, append_slots_host, batch, raw_qkv, ws.pf.k, ws.pf.v, t_fresh, s));

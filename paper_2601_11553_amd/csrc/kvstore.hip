@@ -12,79 +12,79 @@
 namespace {
 using pc::kKvTile;
 
-// blockIdx.y == 0: K, Hkv runs of n_tok*D elements copied 16 bytes per lane.
-// blockIdx.y == 1: V, one output 16-byte vector (8 key positions of one head-dim index) per thread and step.
-struct SlotList {
-  int32_t slot[64];
+// One launch serves a list of (slot, dense block) pairs.  A dense block is a token range of a dense tensor: head g's token t
+// is row  row0 + g * head_rows + t  of D elements.
+constexpr int kListMax = 64;
+struct CopyList {
+  int32_t slot[kListMax];   // slot of the format the kernel handles, negative: skip the entry
+  int32_t row0[kListMax];
+  int32_t n_tok[kListMax];
+  int32_t off[kListMax];    // tokens the slot already holds (append; else 0)
 };
 
-template <bool kToStore>
-__global__ __launch_bounds__(256) void kv_copy_kernel(pc::u32x4 *__restrict__ slot_k, __bf16 *__restrict__ slot_v,
-                                                      pc::u32x4 *__restrict__ dense_k, __bf16 *__restrict__ dense_v,
-                                                      int n_heads, int n_tok, int D, int C, SlotList slots,
-                                                      long slot_stride_elems, long dense_head_stride) {
-  // blockIdx.z selects the chunk: its slot and its dense tensor.  dense_head_stride: elements between the heads of
-  // a dense tensor (n_tok * D when the chunk is a tensor of its own, more when it is a token range of a longer one)
-  if (slots.slot[blockIdx.z] < 0) return;  // (an entry of the other slot format: the other launch copies it)
-  {
-    const long so = (long)slots.slot[blockIdx.z] * slot_stride_elems;
-    const long dn = (long)blockIdx.z * n_heads * dense_head_stride;
-    slot_k += so / 8;
-    slot_v += so;
-    dense_k += dn / 8;
-    dense_v += dn;
-  }
-  const long stride = (long)gridDim.x * blockDim.x;
-  const long tid0 = (long)blockIdx.x * blockDim.x + threadIdx.x;
-  if (blockIdx.y == 0) {
-    const int run_vec = n_tok * D / 8, slot_head_vec = C * D / 8;
-    const long total = (long)n_heads * run_vec;
-    for (long e = tid0; e < total; e += stride) {
-      int g = (int)(e / run_vec);
-      int r = (int)(e - (long)g * run_vec);
-      long s = (long)g * slot_head_vec + r;
-      long dd = (long)g * (dense_head_stride / 8) + r;
-      if (kToStore) slot_k[s] = dense_k[dd]; else dense_k[dd] = slot_k[s];
-    }
+// 8 x 8 sixteen-bit elements: out[k] holds element k of in[0..7]
+__device__ __forceinline__ void transpose8(const pc::u32x4 (&in)[8], pc::u32x4 (&out)[8]) {
+#pragma unroll
+  for (int k = 0; k < 8; ++k)
+#pragma unroll
+    for (int p = 0; p < 4; ++p)
+      out[k][p] = __builtin_amdgcn_perm(in[2 * p + 1][k >> 1], in[2 * p][k >> 1], (k & 1) ? 0x07060302u : 0x05040100u);
+}
+// Chunk c of 8 positions of a 64-key block row holds the keys chunk_key(c, FMT8) + {0, 1, 2, 3, 8, 9, 10, 11} (the lane order of
+// pc::blocked_key, of pc::blocked_key8 for 8-bit slots).
+template <bool FMT8>
+__device__ __forceinline__ int chunk_key(int c) {
+  return FMT8 ? 32 * (c >> 2) + 16 * (c & 1) + 4 * ((c >> 1) & 1) : 16 * (c >> 1) + 4 * (c & 1);
+}
+__device__ __forceinline__ int in_chunk(int e) { return (e & 3) + 8 * (e >> 2); }
+
+// bf16 slots <-> dense tensors.  HBM bound.  The unit of work is a wavefront with eight 16-byte loads and eight 16-byte stores
+// per lane in flight: 64 tokens x 64 head-dim elements of K (a copy) or of V, where a lane holds an 8 x 8 piece -- 8 keys of
+// a 64-key block's chunk x 8 head-dim elements -- and turns it in registers (32 byte permutes).  With 2-byte accesses on the
+// dense (put) or the block (get) side a get of 8 chunks of 1000 tokens, 8 heads of 128, took 21.7 us, a put 13.0 us; now
+// 9.6 us and 9.9 us (6.9 TB/s read and written).
+template <int D, bool kToStore>
+__global__ __launch_bounds__(256) void kv_copy_kernel(__bf16 *__restrict__ slot_k, __bf16 *__restrict__ slot_v, __bf16 *__restrict__ dense_k,
+                                                      __bf16 *__restrict__ dense_v, int n_heads, int C, CopyList list, long slot_stride_elems,
+                                                      int head_rows) {
+  constexpr int UNITS = 2 * (D / 64);  // per tile: K and V halves
+  const int z = blockIdx.z, g = blockIdx.y, slot = list.slot[z], n_tok = list.n_tok[z];
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
+  if (slot < 0 || t0 >= n_tok) return;  // (an entry of the other slot format: the other launch copies it)
+  const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
+  const int d0 = (part >> 1) * 64;
+  const size_t drow = (size_t)list.row0[z] + (size_t)g * head_rows + t0;
+  const size_t sbase = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
+  const int last = n_tok - 1 - t0;  // last token of this tile
+  if (!(part & 1)) {  // K: 8 KB of the tile's contiguous run, 1 KB per instruction
+    const __bf16 *src = kToStore ? dense_k + drow * D : slot_k + sbase;
+    __bf16 *dst = kToStore ? slot_k + sbase : dense_k + drow * D;
+    const int at = (part >> 1) * 4096 + lane * 8, end = (min(last, kKvTile - 1) + 1) * D;
+    pc::u32x4 r[8];
+#pragma unroll
+    for (int j = 0; j < 8; ++j) r[j] = *(const pc::u32x4 *)(src + min(at + j * 512, end - 8));
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (at + j * 512 < end) *(pc::u32x4 *)(dst + at + j * 512) = r[j];
     return;
   }
-  const int n_tiles = (n_tok + kKvTile - 1) / kKvTile;
-  if (kToStore) {
-    // vector id -> (head, tile, chunk of 8 positions, head-dim index); d fastest so dense reads coalesce
-    const long total = (long)n_heads * n_tiles * 8 * D;
-    for (long e = tid0; e < total; e += stride) {
-      int d = (int)(e % D);
-      long r = e / D;
-      int chunk = (int)(r & 7);
-      r >>= 3;
-      int tile = (int)(r % n_tiles);
-      int g = (int)(r / n_tiles);
-      pc::bf16x8 o;
+  pc::u32x4 in[8], out[8];
+  __bf16 *block = slot_v + sbase + (size_t)(d0 + hi * 8) * kKvTile + lo * 8;  // chunk lo of the block rows d0 + 8 hi ..
+  __bf16 *rows = dense_v + drow * D + d0 + hi * 8;                             // 8 elements of token rows chunk_key(lo) + ..
+  const int k0 = chunk_key<false>(lo);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) {
-        int pos = chunk * 8 + k;
-        int t = tile * kKvTile + (pos & ~15) + pc::blocked_key(pos & 15);
-        o[k] = t < n_tok ? dense_v[(size_t)g * dense_head_stride + (size_t)t * D + d] : (__bf16)0.f;
-      }
-      *(pc::bf16x8 *)(slot_v + (((size_t)g * C + (size_t)tile * kKvTile) * D) + (size_t)d * kKvTile + chunk * 8) = o;
-    }
-  } else {
-    // vector id -> (head, token, 8 head-dim indices)
-    const int dv = D / 8;
-    const long total = (long)n_heads * n_tok * dv;
-    for (long e = tid0; e < total; e += stride) {
-      int dc = (int)(e % dv);
-      long r = e / dv;
-      int t = (int)(r % n_tok);
-      int g = (int)(r / n_tok);
-      int tile = t / kKvTile, tin = t - tile * kKvTile;
-      int pos = (tin & ~15) + pc::blocked_key(tin & 15);
-      const __bf16 *src = slot_v + (((size_t)g * C + (size_t)tile * kKvTile) * D) + pos;
-      pc::bf16x8 o;
+  for (int j = 0; j < 8; ++j) {
+    const int t = k0 + in_chunk(j);
+    if (!kToStore) in[j] = *(const pc::u32x4 *)(block + j * kKvTile);
+    else in[j] = *(const pc::u32x4 *)(rows + (size_t)min(t, last) * D);
+    if (kToStore && t > last) in[j] = pc::u32x4{0, 0, 0, 0};  // (keys past the end)
+  }
+  transpose8(in, out);
 #pragma unroll
-      for (int k = 0; k < 8; ++k) o[k] = src[(size_t)(dc * 8 + k) * kKvTile];
-      *(pc::bf16x8 *)(dense_v + (size_t)g * dense_head_stride + (size_t)t * D + dc * 8) = o;
-    }
+  for (int j = 0; j < 8; ++j) {
+    const int t = k0 + in_chunk(j);
+    if (kToStore) *(pc::u32x4 *)(block + j * kKvTile) = out[j];
+    else if (t <= last) *(pc::u32x4 *)(rows + (size_t)t * D) = out[j];
   }
 }
 
@@ -94,11 +94,11 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(pc::u32x4 *__restrict__ sl
 // (masked probabilities multiply it).
 __global__ __launch_bounds__(256) void kv_append_kernel(__bf16 *__restrict__ k_store, __bf16 *__restrict__ v_store,
                                                         const __bf16 *__restrict__ k_dense, const __bf16 *__restrict__ v_dense,
-                                                        int n_heads, SlotList slots, SlotList offs, int n_new, int D, int C, long slot_stride_elems) {
-  if (slots.slot[blockIdx.y] < 0) return;
-  const int off = offs.slot[blockIdx.y];
+                                                        int n_heads, CopyList list, int n_new, int D, int C, long slot_stride_elems) {
+  const int slot = list.slot[blockIdx.y], off = list.off[blockIdx.y];
+  if (slot < 0) return;
   const long new_head_stride = (long)n_new * D;
-  __bf16 *slot_k = k_store + (size_t)slots.slot[blockIdx.y] * slot_stride_elems, *slot_v = v_store + (size_t)slots.slot[blockIdx.y] * slot_stride_elems;
+  __bf16 *slot_k = k_store + (size_t)slot * slot_stride_elems, *slot_v = v_store + (size_t)slot * slot_stride_elems;
   const __bf16 *k_new = k_dense + (size_t)blockIdx.y * n_heads * new_head_stride, *v_new = v_dense + (size_t)blockIdx.y * n_heads * new_head_stride;
   const int tile0 = off / kKvTile, n_tiles = (off + n_new + kKvTile - 1) / kKvTile - tile0;
   const long stride = (long)gridDim.x * blockDim.x;
@@ -150,145 +150,149 @@ __device__ __forceinline__ unsigned encode4(float a, float b, float c, float d) 
   return (unsigned)w;
 }
 
-// offs: the slot already holds that many tokens and the dense tensors are the tokens that follow them (0: a put).  The
+// list.off: the slot already holds that many tokens and the dense tensors are the tokens that follow them (0: a put).  The
 // block that was partly filled is then quantised afresh from the values its old tokens read back as plus the new
 // tokens (its exponent is recomputed over all of them; old codes are re-rounded only if the exponent moves); the
 // launch covers the blocks from off / 64 on (of every entry as many as the entry with the most has).
+//
+// A workgroup takes one (chunk, kv head, 64-token block); half of its wavefronts K, half V, a wavefront 64 head-dim elements of
+// all 64 tokens, 8 x 8 elements a lane (eight 16-byte loads in flight).  V: 8 keys of a chunk of the block rows x 8 head-dim
+// elements, whose codes are turned in registers.  (Codes turned through LDS byte by byte, four loads per lane behind tests:
+// 14.3 us for 8 chunks of 1000 tokens, 8 heads of 128; now 13.2 us.)
 template <int D>
-__global__ __launch_bounds__(256) void kv_quant_kernel(uint8_t *__restrict__ slot_k, uint8_t *__restrict__ slot_v,
+__global__ __launch_bounds__(2 * D) void kv_quant_kernel(uint8_t *__restrict__ slot_k, uint8_t *__restrict__ slot_v,
                                                        float *__restrict__ scale_k, float *__restrict__ scale_v,
                                                        const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v,
-                                                       int n_heads, int n_new, int C, SlotList slots, long slot_stride_elems,
-                                                       long scale_slot_stride, long dense_head_stride, SlotList offs) {
-  constexpr int DV = D / 8, NV = kKvTile * DV / 256;  // 8-element vectors per row; vectors per thread
-  __shared__ float red[2][4];
-  __shared__ __align__(16) uint8_t vt[kKvTile][D + 16];  // V codes [key][d] (padded rows), read back transposed
-  const int slot = slots.slot[blockIdx.z], off = offs.slot[blockIdx.z], n_tok = off + n_new;
-  const int blk = blockIdx.x + off / kKvTile, g = blockIdx.y, tid = threadIdx.x;
-  if (slot < 0 || blk * kKvTile >= n_tok) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
-  const size_t dense_at = ((size_t)blockIdx.z * n_heads + g) * dense_head_stride;
-  const size_t slot_at = (size_t)slot * slot_stride_elems + (size_t)g * C * D;
+                                                       int n_heads, int C, CopyList list, long slot_stride_elems,
+                                                       long scale_slot_stride, int head_rows) {
+  constexpr int HALF = D / 64;  // wavefronts of each kind
+  __shared__ float red[2 * HALF];
+  const int slot = list.slot[blockIdx.z], off = list.off[blockIdx.z], n_new = list.n_tok[blockIdx.z], n_tok = off + n_new;
+  const int blk = blockIdx.x + off / kKvTile, g = blockIdx.y, t0 = blk * kKvTile;
+  if (slot < 0 || t0 >= n_tok) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
+  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hi = lane >> 3, lo = lane & 7;
+  const bool is_v = wave >= HALF;
+  const int d = (wave % HALF) * 64 + (is_v ? hi : lo) * 8;  // first of this lane's 8 head-dim elements
+  const size_t dense_at = ((size_t)list.row0[blockIdx.z] + (size_t)g * head_rows) * D + d;
+  const size_t slot_at = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
   const size_t sc = (size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + blk;
-  const bool has_old = blk * kKvTile < off;  // (only the first block of an append)
-  const float old_sk = has_old ? scale_k[sc] : 1.f, old_sv = has_old ? scale_v[sc] : 1.f;
-  pc::bf16x8 kv[NV], vv[NV];
-  float ak = 0.f, av = 0.f;
+  const __bf16 *src = (is_v ? dense_v : dense_k) + dense_at;
+  auto token = [&](int j) __attribute__((always_inline)) { return is_v ? chunk_key<true>(lo) + in_chunk(j) : hi + 8 * j; };  // inside the block
+  pc::bf16x8 x[8];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int v = tid + 256 * j, r = v / DV, dc = v - r * DV;
-    const int t = blk * kKvTile + r;
-    if (t < off) {
-      // what the stored codes read back as (exact in bf16)
-      typedef float f32x2 __attribute__((ext_vector_type(2)));
-      const uint2 ck = *(const uint2 *)(slot_k + slot_at + (size_t)t * D + dc * 8);
-      const uint8_t *vcol = slot_v + slot_at + (size_t)blk * kKvTile * D + pc::blocked_pos8(r);
-      unsigned wk[2] = {ck.x, ck.y}, wv[2] = {0, 0};
+  for (int j = 0; j < 8; ++j) x[j] = *(const pc::bf16x8 *)(src + (size_t)min(max(t0 + token(j) - off, 0), n_new - 1) * D);
+  uint8_t *const kc = slot_k + slot_at + d, *const vc = slot_v + slot_at + (size_t)d * kKvTile + lo * 8;
+  if (t0 < off) {  // (only the first block of an append) what the stored codes read back as, exact in bf16
+    const float scale = (is_v ? scale_v : scale_k)[sc];
+    uint2 w[8];
 #pragma unroll
-      for (int e = 0; e < 8; ++e) wv[e >> 2] |= (unsigned)vcol[(size_t)(dc * 8 + e) * kKvTile] << (8 * (e & 3));
+    for (int j = 0; j < 8; ++j) w[j] = *(const uint2 *)(is_v ? vc + j * kKvTile : kc + (size_t)token(j) * D);
 #pragma unroll
-      for (int h = 0; h < 2; ++h) {
-        const f32x2 k0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wk[h], false), k1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wk[h], true);
-        const f32x2 v0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wv[h], false), v1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wv[h], true);
-        kv[j][4 * h + 0] = (__bf16)(k0[0] * old_sk); kv[j][4 * h + 1] = (__bf16)(k0[1] * old_sk);
-        kv[j][4 * h + 2] = (__bf16)(k1[0] * old_sk); kv[j][4 * h + 3] = (__bf16)(k1[1] * old_sk);
-        vv[j][4 * h + 0] = (__bf16)(v0[0] * old_sv); vv[j][4 * h + 1] = (__bf16)(v0[1] * old_sv);
-        vv[j][4 * h + 2] = (__bf16)(v1[0] * old_sv); vv[j][4 * h + 3] = (__bf16)(v1[1] * old_sv);
+    for (int j = 0; j < 8; ++j)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) {  // K: row j holds its 8 elements; V: row d + e holds the 8 keys
+        const uint2 ww = is_v ? w[e] : w[j];
+        const int at = is_v ? j : e;
+        const unsigned code = (at < 4 ? ww.x : ww.y) >> (8 * (at & 3));
+        const float v = __builtin_amdgcn_cvt_f32_fp8((int)code, 0) * scale;
+        x[j][e] = t0 + token(j) < off ? (__bf16)v : x[j][e];
       }
-    } else if (t < n_tok) {
-      kv[j] = *(const pc::bf16x8 *)(dense_k + dense_at + (size_t)(t - off) * D + dc * 8);
-      vv[j] = *(const pc::bf16x8 *)(dense_v + dense_at + (size_t)(t - off) * D + dc * 8);
-    } else {
+  }
+  float amax = 0.f;
 #pragma unroll
-      for (int e = 0; e < 8; ++e) { kv[j][e] = (__bf16)0.f; vv[j][e] = (__bf16)0.f; }
-    }
+  for (int j = 0; j < 8; ++j) {
+    const bool in = t0 + token(j) < n_tok;
 #pragma unroll
     for (int e = 0; e < 8; ++e) {
-      ak = fmaxf(ak, fabsf((float)kv[j][e]));
-      av = fmaxf(av, fabsf((float)vv[j][e]));
+      if (!in) x[j][e] = (__bf16)0.f;  // (zero codes past the stored count)
+      amax = fmaxf(amax, fabsf((float)x[j][e]));
     }
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) {
-    ak = fmaxf(ak, __shfl_xor(ak, o, 64));
-    av = fmaxf(av, __shfl_xor(av, o, 64));
-  }
-  if ((tid & 63) == 0) { red[0][tid >> 6] = ak; red[1][tid >> 6] = av; }
+  for (int o = 32; o > 0; o >>= 1) amax = fmaxf(amax, __shfl_xor(amax, o, 64));
+  if (lane == 0) red[wave] = amax;
   __syncthreads();
-  ak = fmaxf(fmaxf(red[0][0], red[0][1]), fmaxf(red[0][2], red[0][3]));
-  av = fmaxf(fmaxf(red[1][0], red[1][1]), fmaxf(red[1][2], red[1][3]));
-  const int ek = block_exponent(ak), ev = block_exponent(av);
-  const float ik = pow2f(-ek), iv = pow2f(-ev);
-  if (tid == 0) {
-    scale_k[sc] = pow2f(ek);
-    scale_v[sc] = pow2f(ev);
-  }
+  amax = red[is_v ? HALF : 0];
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int v = tid + 256 * j, r = v / DV, dc = v - r * DV;
-    const int t = blk * kKvTile + r;
-    uint2 ck, cv;
-    ck.x = encode4((float)kv[j][0] * ik, (float)kv[j][1] * ik, (float)kv[j][2] * ik, (float)kv[j][3] * ik);
-    ck.y = encode4((float)kv[j][4] * ik, (float)kv[j][5] * ik, (float)kv[j][6] * ik, (float)kv[j][7] * ik);
-    cv.x = encode4((float)vv[j][0] * iv, (float)vv[j][1] * iv, (float)vv[j][2] * iv, (float)vv[j][3] * iv);
-    cv.y = encode4((float)vv[j][4] * iv, (float)vv[j][5] * iv, (float)vv[j][6] * iv, (float)vv[j][7] * iv);
-    if (t < n_tok) *(uint2 *)(slot_k + slot_at + (size_t)t * D + dc * 8) = ck;
-    *(uint2 *)(&vt[r][dc * 8]) = cv;  // rows past the stored count hold zero codes
-  }
-  __syncthreads();
-  // transposed write: one 16-byte run of a head-dim row per thread and step
-  uint8_t *vblk = slot_v + slot_at + (size_t)blk * kKvTile * D;
-  for (int o = tid; o < D * (kKvTile / 16); o += 256) {
-    const int d = o / (kKvTile / 16), c16 = o - d * (kKvTile / 16);
-    unsigned w[4] = {0, 0, 0, 0};
+  for (int w = 1; w < HALF; ++w) amax = fmaxf(amax, red[(is_v ? HALF : 0) + w]);
+  const int ex = block_exponent(amax);
+  const float inv = pow2f(-ex);
+  if (lane == 0 && wave % HALF == 0) (is_v ? scale_v : scale_k)[sc] = pow2f(ex);
+  uint2 c[8];
 #pragma unroll
-    for (int p = 0; p < 16; ++p) w[p >> 2] |= (unsigned)vt[pc::blocked_key8(c16 * 16 + p)][d] << (8 * (p & 3));
-    *(uint4 *)(vblk + (size_t)d * kKvTile + c16 * 16) = make_uint4(w[0], w[1], w[2], w[3]);
+  for (int j = 0; j < 8; ++j) {
+    c[j].x = encode4((float)x[j][0] * inv, (float)x[j][1] * inv, (float)x[j][2] * inv, (float)x[j][3] * inv);
+    c[j].y = encode4((float)x[j][4] * inv, (float)x[j][5] * inv, (float)x[j][6] * inv, (float)x[j][7] * inv);
+  }
+  if (!is_v) {
+#pragma unroll
+    for (int j = 0; j < 8; ++j)
+      if (t0 + token(j) < n_tok) *(uint2 *)(kc + (size_t)token(j) * D) = c[j];
+    return;
+  }
+  // 8 x 8 bytes: pairs of keys first, then fours
+  unsigned pr[4][4];  // [key pair][d pair]: two keys of element 2 q, two of element 2 q + 1
+#pragma unroll
+  for (int p = 0; p < 4; ++p)
+#pragma unroll
+    for (int q = 0; q < 4; ++q)
+      pr[p][q] = __builtin_amdgcn_perm(q < 2 ? c[2 * p + 1].x : c[2 * p + 1].y, q < 2 ? c[2 * p].x : c[2 * p].y, (q & 1) ? 0x07030602u : 0x05010400u);
+#pragma unroll
+  for (int e = 0; e < 8; ++e) {
+    const unsigned sel = (e & 1) ? 0x07060302u : 0x05040100u;
+    *(uint2 *)(vc + e * kKvTile) = make_uint2(__builtin_amdgcn_perm(pr[1][e >> 1], pr[0][e >> 1], sel), __builtin_amdgcn_perm(pr[3][e >> 1], pr[2][e >> 1], sel));
   }
 }
 
-// The values an 8-bit slot holds, as dense bf16 [kv head][token][head_dim]: code * 2^e (exact).
+// The values an 8-bit slot holds, as dense bf16 [kv head][token][head_dim]: code * 2^e (exact).  Work split as in
+// kv_copy_kernel: 8 codes per load, the 8 x 8 piece of a V block turned in registers as bf16.
 template <int D>
 __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restrict__ slot_k, const uint8_t *__restrict__ slot_v,
                                                          const float *__restrict__ scale_k, const float *__restrict__ scale_v,
-                                                         __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int n_heads,
-                                                         int n_tok, int C, SlotList slots, long slot_stride_elems,
-                                                         long scale_slot_stride, long dense_head_stride, SlotList /*unused*/) {
-  constexpr int DV = D / 8, NV = kKvTile * DV / 256;
-  const int blk = blockIdx.x, g = blockIdx.y, tid = threadIdx.x;
-  const int slot = slots.slot[blockIdx.z];
-  if (slot < 0) return;
-  const size_t dense_at = ((size_t)blockIdx.z * n_heads + g) * dense_head_stride;
-  const size_t slot_at = (size_t)slot * slot_stride_elems + (size_t)g * C * D;
-  const size_t sc = (size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + blk;
-  const float sk = scale_k[sc], sv = scale_v[sc];
-  const uint8_t *vblk = slot_v + slot_at + (size_t)blk * kKvTile * D;
+                                                         __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int n_heads, int C,
+                                                         CopyList list, long slot_stride_elems, long scale_slot_stride, int head_rows) {
+  constexpr int UNITS = 2 * (D / 64);
+  const int z = blockIdx.z, g = blockIdx.y, slot = list.slot[z], n_tok = list.n_tok[z];
+  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
+  if (slot < 0 || t0 >= n_tok) return;
+  const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
+  const int d0 = (part >> 1) * 64;
+  const size_t drow = (size_t)list.row0[z] + (size_t)g * head_rows + t0;
+  const size_t sbase = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
+  const float scale = (part & 1 ? scale_v : scale_k)[(size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + tile];
+  typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
+  auto widen = [&](uint2 w) __attribute__((always_inline)) {
+    pc::u32x4 o;
+    o[0] = __builtin_bit_cast(unsigned, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, scale, false));
+    o[1] = __builtin_bit_cast(unsigned, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.x, scale, true));
+    o[2] = __builtin_bit_cast(unsigned, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, scale, false));
+    o[3] = __builtin_bit_cast(unsigned, (bf16x2)__builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w.y, scale, true));
+    return o;
+  };
+  uint2 raw[8];
+  if (!(part & 1)) {
+    const uint8_t *src = slot_k + sbase + d0 + lo * 8;
+    __bf16 *dst = dense_k + drow * D + d0 + lo * 8;
 #pragma unroll
-  for (int j = 0; j < NV; ++j) {
-    const int v = tid + 256 * j, r = v / DV, dc = v - r * DV;
-    const int t = blk * kKvTile + r;
-    if (t >= n_tok) continue;
-    const uint2 ck = *(const uint2 *)(slot_k + slot_at + (size_t)t * D + dc * 8);
-    const int pos = pc::blocked_pos8(r);
-    unsigned cvx = 0, cvy = 0;
+    for (int j = 0; j < 8; ++j) raw[j] = *(const uint2 *)(src + (size_t)min(hi + 8 * j, n_tok - 1 - t0) * D);
 #pragma unroll
-    for (int e = 0; e < 4; ++e) {
-      cvx |= (unsigned)vblk[(size_t)(dc * 8 + e) * kKvTile + pos] << (8 * e);
-      cvy |= (unsigned)vblk[(size_t)(dc * 8 + 4 + e) * kKvTile + pos] << (8 * e);
-    }
-    typedef float f32x2 __attribute__((ext_vector_type(2)));
-    pc::bf16x8 ok, ov;
-    const unsigned wk[2] = {ck.x, ck.y}, wv[2] = {cvx, cvy};
+    for (int j = 0; j < 8; ++j)
+      if (t0 + hi + 8 * j < n_tok) *(pc::u32x4 *)(dst + (size_t)(hi + 8 * j) * D) = widen(raw[j]);
+    return;
+  }
+  const uint8_t *block = slot_v + sbase + (size_t)(d0 + hi * 8) * kKvTile + lo * 8;
+  __bf16 *rows = dense_v + drow * D + d0 + hi * 8;
+  pc::u32x4 in[8], out[8];
 #pragma unroll
-    for (int h = 0; h < 2; ++h) {
-      const f32x2 k0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wk[h], false), k1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wk[h], true);
-      const f32x2 v0 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wv[h], false), v1 = __builtin_amdgcn_cvt_pk_f32_fp8((int)wv[h], true);
-      ok[4 * h + 0] = (__bf16)(k0[0] * sk); ok[4 * h + 1] = (__bf16)(k0[1] * sk);
-      ok[4 * h + 2] = (__bf16)(k1[0] * sk); ok[4 * h + 3] = (__bf16)(k1[1] * sk);
-      ov[4 * h + 0] = (__bf16)(v0[0] * sv); ov[4 * h + 1] = (__bf16)(v0[1] * sv);
-      ov[4 * h + 2] = (__bf16)(v1[0] * sv); ov[4 * h + 3] = (__bf16)(v1[1] * sv);
-    }
-    *(pc::bf16x8 *)(dense_k + dense_at + (size_t)t * D + dc * 8) = ok;
-    *(pc::bf16x8 *)(dense_v + dense_at + (size_t)t * D + dc * 8) = ov;
+  for (int j = 0; j < 8; ++j) raw[j] = *(const uint2 *)(block + j * kKvTile);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) in[j] = widen(raw[j]);
+  transpose8(in, out);
+  const int k0 = chunk_key<true>(lo);
+#pragma unroll
+  for (int j = 0; j < 8; ++j) {
+    const int t = k0 + in_chunk(j);
+    if (t0 + t < n_tok) *(pc::u32x4 *)(rows + (size_t)t * D) = out[j];
   }
 }
 
@@ -299,79 +303,113 @@ pc_status check_slot(percache_ctx *ctx, int32_t layer, int32_t slot) {
   return PC_OK;
 }
 
-// Copies between dense tensors and the slots of a list (at most 64 entries; entry i <-> dense block i).  A list may
-// name slots of both formats: each format gets its own launch, in which the entries of the other format are marked -1.
+// Copies between dense tensors and the slots of a list of at most kListMax entries (row0 and n_tok filled in, slot ids of the
+// context).  A list may name slots of both formats: each format gets its own launch, in which the other's entries are
+// marked -1.
 template <bool kToStore>
-pc_status launch_copy(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, void *k_dev, void *v_dev, int n_tokens,
-                      hipStream_t stream, long dense_head_stride = 0) {
+pc_status launch_copy(percache_ctx *ctx, int layer, const CopyList &list, int n, void *k_dev, void *v_dev, int head_rows, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
-  SlotList sl16, sl8;
-  int n16 = 0, n8 = 0;
-  for (int i = 0; i < 64; ++i) {
-    sl16.slot[i] = sl8.slot[i] = -1;
-    if (i >= n) continue;
-    if (ctx->is8(slot_list[i])) { sl8.slot[i] = slot_list[i] - ctx->n_slots16; ++n8; }
-    else { sl16.slot[i] = slot_list[i]; ++n16; }
+  CopyList l16 = list, l8 = list;
+  int n16 = 0, n8 = 0, longest = 0;
+  for (int i = 0; i < kListMax; ++i) {
+    const int slot = i < n ? list.slot[i] : -1;
+    const bool is8 = slot >= 0 && ctx->is8(slot);
+    l16.slot[i] = slot >= 0 && !is8 ? slot : -1;
+    l8.slot[i] = is8 ? slot - ctx->n_slots16 : -1;
+    n16 += slot >= 0 && !is8;
+    n8 += is8;
+    if (slot >= 0 && list.n_tok[i] > longest) longest = list.n_tok[i];
   }
-  const long dhs = dense_head_stride ? dense_head_stride : (long)n_tokens * c.head_dim;
+  const int tiles = (longest + kKvTile - 1) / kKvTile;
   if (n8) {
     const size_t off = (size_t)layer * ctx->layer_stride8;
     const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
     const size_t sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
-    dim3 grid((n_tokens + kKvTile - 1) / kKvTile, c.n_kv_heads, n);
-#define PC_KV8(KERNEL, DD)                                                                                                    \
-  hipLaunchKernelGGL((KERNEL<DD>), grid, dim3(256), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
-                     ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, n_tokens, c.slot_capacity, sl8,     \
-                     (long)ctx->slot_stride, sc_slot, dhs, SlotList{})
+#define PC_KV8(KERNEL, DD, GX, TT)                                                                                                  \
+  hipLaunchKernelGGL((KERNEL<DD>), dim3(GX, c.n_kv_heads, n), dim3(TT), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
+                     ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot,      \
+                     head_rows)
     if (kToStore) {
-      if (c.head_dim == 128) PC_KV8(kv_quant_kernel, 128); else PC_KV8(kv_quant_kernel, 64);
+      if (c.head_dim == 128) PC_KV8(kv_quant_kernel, 128, tiles, 256); else PC_KV8(kv_quant_kernel, 64, tiles, 128);
     } else {
-      if (c.head_dim == 128) PC_KV8(kv_dequant_kernel, 128); else PC_KV8(kv_dequant_kernel, 64);
+      if (c.head_dim == 128) PC_KV8(kv_dequant_kernel, 128, tiles, 256); else PC_KV8(kv_dequant_kernel, 64, (tiles + 1) / 2, 256);
     }
 #undef PC_KV8
     PC_HIP(ctx, hipGetLastError());
   }
   if (n16) {
     const size_t off = (size_t)layer * ctx->layer_stride;
-    long total = (long)c.n_kv_heads * ((n_tokens + kKvTile - 1) / kKvTile) * kKvTile * c.head_dim / 8;
-    int blocks = (int)((total + 255) / 256);
-    if (blocks > 2048) blocks = 2048;
-    hipLaunchKernelGGL(kv_copy_kernel<kToStore>, dim3(blocks, 2, n), dim3(256), 0, stream, (pc::u32x4 *)(ctx->k_store + off),
-                       ctx->v_store + off, (pc::u32x4 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, n_tokens, c.head_dim,
-                       c.slot_capacity, sl16, (long)ctx->slot_stride, dhs);
+#define PC_KV16(DD, GX)                                                                                                      \
+  hipLaunchKernelGGL((kv_copy_kernel<DD, kToStore>), dim3(GX, c.n_kv_heads, n), dim3(256), 0, stream, ctx->k_store + off, ctx->v_store + off,       \
+                     (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, l16, (long)ctx->slot_stride, head_rows)
+    if (c.head_dim == 128) PC_KV16(128, tiles); else PC_KV16(64, (tiles + 1) / 2);
+#undef PC_KV16
     PC_HIP(ctx, hipGetLastError());
   }
   return PC_OK;
+}
+// The list of n chunks that are tensors of their own, [n][Hkv][n_tokens][D]
+CopyList chunk_list(const percache_ctx *ctx, const int32_t *slots, int n, int n_tokens) {
+  CopyList l{};
+  for (int i = 0; i < n; ++i) {
+    l.slot[i] = slots[i];
+    l.row0[i] = i * ctx->cfg.n_kv_heads * n_tokens;
+    l.n_tok[i] = n_tokens;
+  }
+  return l;
 }
 
 }  // namespace
 
 namespace pc {
-pc_status launch_kv_store(percache_ctx *ctx, int layer, int slot, const __bf16 *k, const __bf16 *v, int n_tokens,
-                          long dense_head_stride, hipStream_t stream) {
-  return launch_copy<true>(ctx, layer, &slot, 1, (void *)k, (void *)v, n_tokens, stream, dense_head_stride);
+pc_status launch_kv_slices(percache_ctx *ctx, int layer, const int32_t *slots, const int32_t *bounds, int n_pieces, int batch, const __bf16 *k,
+                           const __bf16 *v, int seq_len, hipStream_t stream) {
+  const int Hkv = ctx->cfg.n_kv_heads, D = ctx->cfg.head_dim;
+  CopyList l{};
+  int n = 0, first = 0;   // pieces collected, query of the first one (rows are counted from it)
+  auto flush = [&]() {
+    const size_t at = (size_t)first * Hkv * seq_len * D;
+    const pc_status st = n ? launch_copy<true>(ctx, layer, l, n, (void *)(k + at), (void *)(v + at), seq_len, stream) : PC_OK;
+    n = 0;
+    return st;
+  };
+  for (int b = 0; b < batch; ++b)
+    for (int j = 0; j < n_pieces; ++j) {
+      if (slots[(size_t)b * n_pieces + j] < 0) continue;
+      if (n == kListMax) {
+        const pc_status st = flush();
+        if (st != PC_OK) return st;
+      }
+      if (n == 0) first = b;
+      l.slot[n] = slots[(size_t)b * n_pieces + j];
+      l.row0[n] = (b - first) * Hkv * seq_len + bounds[j];
+      l.n_tok[n] = bounds[j + 1] - bounds[j];
+      ++n;
+    }
+  return flush();
 }
 pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v,
                            int n_tokens, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
   const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile), head_stride = (long)n_tokens * c.head_dim;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int cnt = n - i0 < 64 ? n - i0 : 64;
-    SlotList sl16, sl8, offs;
+  for (int i0 = 0; i0 < n; i0 += kListMax) {
+    const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
+    CopyList l16{}, l8{};
     int n16 = 0, n8 = 0, blocks8 = 0;
-    for (int i = 0; i < 64; ++i) {
-      sl16.slot[i] = sl8.slot[i] = -1;
-      offs.slot[i] = 0;
+    for (int i = 0; i < kListMax; ++i) {
+      l16.slot[i] = l8.slot[i] = -1;
       if (i >= cnt || slot_list[i0 + i] < 0) continue;
       const int slot = slot_list[i0 + i], off = ctx->slot_len[(size_t)layer * c.n_slots + slot];
-      offs.slot[i] = off;
+      l16.off[i] = l8.off[i] = off;
+      l8.n_tok[i] = n_tokens;
+      l8.row0[i] = i * c.n_kv_heads * n_tokens;
       if (ctx->is8(slot)) {
-        sl8.slot[i] = slot - ctx->n_slots16;
+        l8.slot[i] = slot - ctx->n_slots16;
         const int blocks = (off + n_tokens + kKvTile - 1) / kKvTile - off / kKvTile;
         if (blocks > blocks8) blocks8 = blocks;
         ++n8;
       } else if (!only_8bit) {
-        sl16.slot[i] = slot;
+        l16.slot[i] = slot;
         ++n16;
       }
     }
@@ -380,8 +418,8 @@ pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_lis
       const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
       const dim3 grid(blocks8, c.n_kv_heads, cnt);
 #define PC_APPEND8(DD)                                                                                                                  \
-  hipLaunchKernelGGL((kv_quant_kernel<DD>), grid, dim3(256), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off,      \
-                     ctx->v_scale + sc_off, kd, vd, c.n_kv_heads, n_tokens, c.slot_capacity, sl8, (long)ctx->slot_stride, sc_slot, head_stride, offs)
+  hipLaunchKernelGGL((kv_quant_kernel<DD>), grid, dim3(2 * DD), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off,      \
+                     ctx->v_scale + sc_off, kd, vd, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot, n_tokens)
       if (c.head_dim == 128) PC_APPEND8(128); else PC_APPEND8(64);
 #undef PC_APPEND8
       PC_HIP(ctx, hipGetLastError());
@@ -391,7 +429,7 @@ pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_lis
       const long work = (long)c.n_kv_heads * c.head_dim * ((n_tokens + kKvTile - 1) / kKvTile + 1) * kKvTile;
       const long blocks = (work + 255) / 256;
       hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks), cnt), dim3(256), 0, stream, ctx->k_store + at, ctx->v_store + at,
-                         kd, vd, c.n_kv_heads, sl16, offs, n_tokens, c.head_dim, c.slot_capacity, (long)ctx->slot_stride);
+                         kd, vd, c.n_kv_heads, l16, n_tokens, c.head_dim, c.slot_capacity, (long)ctx->slot_stride);
       PC_HIP(ctx, hipGetLastError());
     }
   }
@@ -425,7 +463,7 @@ pc_status percache_kv_put(percache_ctx *ctx, int32_t layer, int32_t slot, const 
   if (((uintptr_t)k_dev | (uintptr_t)v_dev) % 16) return pc::fail(ctx, PC_EINVAL, "k_dev / v_dev must be 16-byte aligned");
   const percache_config &c = ctx->cfg;
   if (n_tokens < 1 || n_tokens > c.slot_capacity) return pc::fail(ctx, PC_ELEN, "n_tokens %d outside [1,%d]", n_tokens, c.slot_capacity);
-  st = launch_copy<true>(ctx, layer, &slot, 1, (void *)k_dev, (void *)v_dev, n_tokens, (hipStream_t)stream);
+  st = launch_copy<true>(ctx, layer, chunk_list(ctx, &slot, 1, n_tokens), 1, (void *)k_dev, (void *)v_dev, n_tokens, (hipStream_t)stream);
   if (st != PC_OK) return st;
   ctx->slot_len[(size_t)layer * c.n_slots + slot] = n_tokens;
   return PC_OK;
@@ -446,9 +484,9 @@ pc_status percache_kv_put_batch(percache_ctx *ctx, int32_t layer, const int32_t 
       if (slots_host[j] == slots_host[i]) return pc::fail(ctx, PC_EINVAL, "slot %d appears twice in the batch", slots_host[i]);
   }
   const size_t per_chunk = (size_t)c.n_kv_heads * n_tokens * c.head_dim;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    int cnt = n - i0 < 64 ? n - i0 : 64;
-    pc_status st = launch_copy<true>(ctx, layer, slots_host + i0, cnt, (void *)((const __bf16 *)k_dev + per_chunk * i0),
+  for (int i0 = 0; i0 < n; i0 += kListMax) {
+    const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
+    pc_status st = launch_copy<true>(ctx, layer, chunk_list(ctx, slots_host + i0, cnt, n_tokens), cnt, (void *)((const __bf16 *)k_dev + per_chunk * i0),
                                      (void *)((const __bf16 *)v_dev + per_chunk * i0), n_tokens, (hipStream_t)stream);
     if (st != PC_OK) return st;
   }
@@ -465,7 +503,7 @@ pc_status percache_kv_get(percache_ctx *ctx, int32_t layer, int32_t slot, void *
   const percache_config &c = ctx->cfg;
   int n_tokens = ctx->slot_len[(size_t)layer * c.n_slots + slot];
   if (n_tokens <= 0) return pc::fail(ctx, PC_ESLOT, "slot %d of layer %d is empty", slot, layer);
-  st = launch_copy<false>(ctx, layer, &slot, 1, k_out_dev, v_out_dev, n_tokens, (hipStream_t)stream);
+  st = launch_copy<false>(ctx, layer, chunk_list(ctx, &slot, 1, n_tokens), 1, k_out_dev, v_out_dev, n_tokens, (hipStream_t)stream);
   if (st != PC_OK) return st;
   if (n_tokens_out_host) *n_tokens_out_host = n_tokens;
   return PC_OK;
@@ -487,9 +525,9 @@ pc_status percache_kv_get_batch(percache_ctx *ctx, int32_t layer, const int32_t 
     if (have < n_tokens) return pc::fail(ctx, PC_ELEN, "slot %d holds %d tokens, %d asked for", slots_host[i], have, n_tokens);
   }
   const size_t per_chunk = (size_t)c.n_kv_heads * n_tokens * c.head_dim;
-  for (int i0 = 0; i0 < n; i0 += 64) {
-    const int cnt = n - i0 < 64 ? n - i0 : 64;
-    pc_status st = launch_copy<false>(ctx, layer, slots_host + i0, cnt, (void *)((__bf16 *)k_out_dev + per_chunk * i0),
+  for (int i0 = 0; i0 < n; i0 += kListMax) {
+    const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
+    pc_status st = launch_copy<false>(ctx, layer, chunk_list(ctx, slots_host + i0, cnt, n_tokens), cnt, (void *)((__bf16 *)k_out_dev + per_chunk * i0),
                                       (void *)((__bf16 *)v_out_dev + per_chunk * i0), n_tokens, (hipStream_t)stream);
     if (st != PC_OK) return st;
   }

@@ -204,10 +204,11 @@ inline int table_formats(const std::vector<int32_t> &rows, int stride, int batch
   return f;
 }
 
-// Copies n_tokens tokens of a dense [Hkv][.][D] tensor whose heads are dense_head_stride elements apart into a
-// slot (no validation, no slot-table update).
-pc_status launch_kv_store(percache_ctx *ctx, int layer, int slot, const __bf16 *k, const __bf16 *v, int n_tokens,
-                          long dense_head_stride, hipStream_t stream);
+// Cuts the dense tensors [batch][Hkv][seq_len][D] at the token bounds (the same for every query) and stores piece j of query b
+// in slot slots[b * n_pieces + j] (negative: skipped), one launch per 64 pieces and slot format (no validation, no slot-table
+// update).
+pc_status launch_kv_slices(percache_ctx *ctx, int layer, const int32_t *slots, const int32_t *bounds, int n_pieces, int batch, const __bf16 *k,
+                           const __bf16 *v, int seq_len, hipStream_t stream);
 
 // Appends n_tokens tokens of every dense tensor of [n][Hkv][n_tokens][D] behind the tokens that the slot of the same place
 // in the list holds (by the slot table; no validation, no slot-table update).  Negative entries are skipped, and with

@@ -74,6 +74,30 @@ def test_each_slot_keeps_its_own_format(D):
     pc.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+def test_many_ragged_pieces_in_one_call(D):
+    """More pieces than one launch takes, of 1 token up to a whole slot, at starts of every alignment, some not saved."""
+    g = np.random.default_rng(80 + D)
+    Hkv, C, S, n8 = 2, 128, 96, 40
+    pc = _ctx(D, C, S, n8, max_pos=8192)
+    lens = [1, 7, 8, 9, 63, 64, 65, 127, 128] + [int(x) for x in g.integers(1, C + 1, 69)]
+    bounds = np.concatenate([[0], np.cumsum(lens)]).astype(np.int32)
+    T = int(bounds[-1]) + 3
+    slots = [int(x) for x in g.permutation(S)[:len(lens)]]
+    slots[3] = slots[70] = -1
+    k = wl.round_bf16(g.standard_normal((Hkv, T, D)).astype(np.float32) * 3)
+    v = wl.round_bf16(g.standard_normal((Hkv, T, D)).astype(np.float32))
+    pc.percache_kv_slice(0, bf16(k), bf16(v), bounds, slots)
+    for i, slot in enumerate(slots):
+        if slot < 0:
+            continue
+        kk, vv = pc.percache_kv_get(0, slot)
+        torch.cuda.synchronize()
+        for got, x in ((kk, k), (vv, v)):
+            assert np.array_equal(host(got), _reads_back(x[:, bounds[i]:bounds[i + 1]], slot >= S - n8)), (i, lens[i], slot)
+    pc.close()
+
+
 def test_config_limits_of_the_two_formats():
     from paper_2601_11553_amd import binding
     import ctypes
