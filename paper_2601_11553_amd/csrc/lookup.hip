@@ -148,6 +148,7 @@ struct RowScan {
   uint8_t *stale;          // [N] out: best_sim > kth
   int p0;                  // index of this pass's first probe
   int first;               // 1: first pass (outputs are overwritten), 0: merged with the previous passes
+  int padded;              // probes of the pass rounded up to whole tiles (of a row of NaN similarities the first padding probe wins)
 };
 
 template <int NPB, int CHB, int NSTG, int K>
@@ -694,18 +695,24 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
 // load instruction brings two contiguous 512-byte runs; NSTG - 1 stages in flight).  One barrier per stage: it
 // publishes the stage that has landed and retires the one just multiplied.  A lane ends up with 16 rows of one
 // probe per block, scales them by the rows' inverse norms and keeps a running sorted list, as in the kernel above.
+// Per-row mode (K == 0, see RowScan): the operands swap sides, so a lane holds ONE row and 16 probes; the wavefronts'
+// candidates of a block meet in LDS and are written out one block later, behind a barrier that is there anyway, by the
+// wavefronts in turn.  The thresholds sit in LDS beside the inverse norms: a load from memory in front of the decision
+// would drain the ring.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kWideProbes = 128;
 constexpr int kWideStages = 8;
-constexpr int kWideChunk = 512;             // bytes of a row per stage
+constexpr int kWideChunk = 512;             // bytes of a row per stage (256 where they do not divide a row)
 constexpr int kWideMaxBlocksPerWg = 192;    // 6144 rows: bounds the LDS copy of the inverse norms (24 KB)
+constexpr int kScanMaxBlocksPerWg = 80;     // per-row mode: of the inverse norms and the thresholds (20 KB), beside the candidates
+constexpr int kScanHead = kScanMaxBlocksPerWg * 32 * 8 + 2 * 4 * 32 * (int)sizeof(Best);
 
-template <int D_EMB, int K>
+template <int D_EMB, int K, int CHB = kWideChunk>
 __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm,
                                                              int N, const _Float16 *__restrict__ probes, int n_probes, int per_wg,
-                                                             Best *__restrict__ partial) {
+                                                             Best *__restrict__ partial, RowScan rs) {
   extern __shared__ __align__(16) char smem[];
-  constexpr int CHB = kWideChunk, NSTG = kWideStages;
+  constexpr int NSTG = kWideStages;
   constexpr int CHUNKS = D_EMB * 2 / CHB;  // stages per row block
   constexpr int CS = CHB / 32;             // MFMA k-steps (16 elements) per stage
   constexpr int STG = 32 * CHB;            // bytes per stage
@@ -718,10 +725,25 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 
   // inverse norms of this workgroup's rows (zero beyond N), then the ring
   float *inv_lds = (float *)smem;
-  char *ring = smem + kWideMaxBlocksPerWg * 32 * sizeof(float);
+  float *kth_lds = inv_lds + kScanMaxBlocksPerWg * 32;                  // (K == 0)
+  Best *cand = (Best *)(kth_lds + kScanMaxBlocksPerWg * 32);            // (K == 0) [block parity][wavefront][row]
+  char *ring = smem + (K == 0 ? kScanHead : kWideMaxBlocksPerWg * 32 * (int)sizeof(float));
   for (int r = tid; r < per_wg * 32; r += 256) {
     const int row = rb_begin * 32 + r;
     inv_lds[r] = row < N ? inv_norm[row] : 0.f;
+    if (K == 0) kth_lds[r] = row < N ? rs.kth[row] : 0.f;
+  }
+  // per-row mode: inverse norms of the probes this lane meets (-inf marks a padding probe)
+  const bool idle = wave * 32 >= n_probes;  // nothing but padding: this wavefront only loads
+  float pinv[K == 0 ? 16 : 1];
+  if constexpr (K == 0) {
+#pragma unroll
+    for (int r = 0; r < 16; ++r) {
+      const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
+      pinv[r] = p < n_probes ? rs.probe_inv[p] : -INFINITY;
+    }
+#pragma unroll
+    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(pinv[r]));
   }
   // this lane's probe: elements [16 ks + 8 g2, +8) for every k-step (zero for a padding probe)
   f16x8 pq[D_EMB / 16];
@@ -741,11 +763,11 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
   PC_LOOKUP_WAIT_VMCNT(0);
   __syncthreads();
 
-  // load instruction i of a stage (i = wave + 4 k): stage bytes [1024 i, +1024) = rows 2i, 2i+1
+  // load instruction i of a stage (i = wave + 4 k): stage bytes [1024 i, +1024) = whole rows
   int ld_row[IPS], ld_col[IPS];
 #pragma unroll
   for (int k = 0; k < IPS; ++k) {
-    const int row = (wave + 4 * k) * 2 + (lane >> 5), pc = lane & 31;
+    const int row = (wave + 4 * k) * (1024 / CHB) + lane / (CHB / 16), pc = lane % (CHB / 16);
     ld_row[k] = row;
     ld_col[k] = (pc ^ (row & 15)) * 8;  // element offset of the logical 16-byte chunk this lane fetches
   }
@@ -762,8 +784,28 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
   for (int s = 0; s < CS; ++s) rd_off[s] = l32 * CHB + (((2 * s + g2) ^ (l32 & 15)) * 16);
 
-  TopK<K> best;
+  TopK<(K > 0 ? K : 1)> best;
   best.clear();
+  // (K == 0) the candidates of a block whose barrier has passed: one row per lane of the wavefront whose turn it is
+  auto write_rows = [&](int rb) __attribute__((always_inline)) {
+    if ((rb & 3) != wave || g2 != 0) return;
+    const int row = rb * 32 + l32;
+    Best b = cand[((rb & 1) * 4) * 32 + l32];
+#pragma unroll
+    for (int w = 1; w < 4; ++w) {
+      const Best o = cand[((rb & 1) * 4 + w) * 32 + l32];
+      if (better(o.s, o.idx, b.s, b.idx)) b = o;
+    }
+    if (row >= N) return;
+    if (!rs.first) {
+      const Best o{rs.best_sim[row], rs.best_new[row]};
+      if (!better(b.s, b.idx, o.s, o.idx)) b = o;
+    }
+    rs.best_sim[row] = b.s;
+    rs.best_new[row] = b.idx;
+    rs.stale[row] = b.s > kth_lds[(rb - rb_begin) * 32 + l32] ? 1 : 0;
+  };
+  if (K == 0 && idle && g2 == 0) cand[wave * 32 + l32] = cand[(4 + wave) * 32 + l32] = Best{-INFINITY, INT_MAX};
   const int rb_last = rb_end - 1;
   if (rb_begin < rb_end) {
     // flat sequence of (row block, chunk) items; loads go out unconditionally (past the end they repeat the last
@@ -789,12 +831,18 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
         // the oldest stage in flight has landed (mine), then (barrier) everyone's; the barrier also says that the
         // stage multiplied last is free for the next load
         PC_LOOKUP_WAIT_VMCNT((NSTG - 2) * IPS);
+        if (K == 0 && c == 0) asm volatile("s_waitcnt lgkmcnt(0)");  // (the last block's candidates are in LDS)
         asm volatile("" ::: "memory");
         __builtin_amdgcn_s_barrier();
         asm volatile("" ::: "memory");
         issue(min(prb, rb_last), pch, ist);
         advance(prb, pch);
         ist = ist + 1 == NSTG ? 0 : ist + 1;
+        if (K == 0 && c == 0 && rb > rb_begin) write_rows(rb - 1);
+        if (K == 0 && idle) {
+          st = st + 1 == NSTG ? 0 : st + 1;
+          continue;
+        }
         // all of the stage's operands are asked for before its first MFMA (left to itself the compiler reads one
         // operand, waits, multiplies: one LDS latency per MFMA instead of one per stage)
         const char *abase = ring + st * STG;
@@ -802,10 +850,28 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
         for (int s = 0; s < CS; ++s) av[s] = *(const f16x8 *)(abase + rd_off[s]);
 #pragma unroll
-        for (int s = 0; s < CS; ++s) acc[s & 1] = __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s], pq[c * CS + s], acc[s & 1], 0, 0, 0);
+        for (int s = 0; s < CS; ++s)
+          acc[s & 1] = K == 0 ? __builtin_amdgcn_mfma_f32_32x32x16_f16(pq[c * CS + s], av[s], acc[s & 1], 0, 0, 0)
+                              : __builtin_amdgcn_mfma_f32_32x32x16_f16(av[s], pq[c * CS + s], acc[s & 1], 0, 0, 0);
         __builtin_amdgcn_sched_group_barrier(0x100, CS, 0);
         __builtin_amdgcn_sched_group_barrier(0x008, CS, 0);
         st = st + 1 == NSTG ? 0 : st + 1;
+      }
+      if constexpr (K == 0) {
+        // element r of the product: row l32 of the block, probe wave*32 + (r/4)*8 + 4*g2 + r%4 (ascending: the lowest wins ties)
+        if (idle) continue;
+        const float inv = inv_lds[(rb - rb_begin) * 32 + l32];
+        Best b{-INFINITY, INT_MAX};
+#pragma unroll
+        for (int r = 0; r < 16; ++r) {
+          const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
+          const float s = pinv[r] == -INFINITY ? -INFINITY : (acc[0][r] + acc[1][r]) * inv * pinv[r];
+          if (better(s, rs.p0 + p, b.s, b.idx) && p < rs.padded) b = Best{s, rs.p0 + p};
+        }
+        const Best o{__shfl_xor(b.s, 32, 64), __shfl_xor(b.idx, 32, 64)};
+        if (better(o.s, o.idx, b.s, b.idx)) b = o;
+        if (g2 == 0) cand[((rb & 1) * 4 + wave) * 32 + l32] = b;
+        continue;
       }
       // element r of the product: row (r/4)*8 + 4*g2 + r%4 of the block, probe wave*32 + l32
 #pragma unroll
@@ -820,11 +886,17 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
       }
     }
     PC_LOOKUP_WAIT_VMCNT(0);
+    if constexpr (K == 0) {
+      __syncthreads();
+      write_rows(rb_last);
+    }
   }
+  if constexpr (K == 0) return;  // per-row mode: everything has been written
   // the two lanes of a probe hold different rows: merge (K rounds of "best head wins and is popped")
-  Best *out = partial + ((size_t)blockIdx.x * kWideProbes + wave * 32 + l32) * K;
+  constexpr int KL = K > 0 ? K : 1;
+  Best *out = partial + ((size_t)blockIdx.x * kWideProbes + wave * 32 + l32) * KL;
 #pragma unroll
-  for (int j = 0; j < K; ++j) {
+  for (int j = 0; j < KL; ++j) {
     float s = best.s[0];
     int i = best.i[0];
     const float s2 = __shfl_xor(s, 32, 64);
@@ -893,6 +965,9 @@ int max_stream_grid(const percache_ctx *ctx) {
 
 constexpr int kMaxTopK = 8;
 constexpr int kBatchedFrom = 32;  // more probes than one streaming pass takes: the 128-probe pass or the matrix-product kernel
+// Per-row scan: more new embeddings than one streaming pass takes go through 128-probe passes.  200k rows, streaming passes | 128-probe
+// passes, us: width 384 82 | 66 at 33 to 64, 164 | 70 at 128; width 1024 139 | 103 at 64, 280 | 118 at 128, 490 | 234 at 200.
+constexpr int kScanWideFrom = 32;
 constexpr int kWideUpTo = 128;    // one such pass; beyond it the matrix-product kernel is the faster one
 
 // Launch shape of the 256-row kernel: probe tiles x groups of consecutive 256-row bank tiles, one workgroup per CU (a
@@ -942,6 +1017,26 @@ pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStre
                          : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs);
 }
 
+// Per-row scan of up to 128 new embeddings in one pass of the bank.
+bool scan_in_wide_passes(int n_new, int d) { return n_new > kScanWideFrom && (d == 384 || d == 512 || d == 768 || d == 1024); }
+pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, const _Float16 *pp, int np, const RowScan &rs) {
+  const int n_blocks = (N + 31) / 32;
+  int grid = ctx->n_cu < n_blocks ? ctx->n_cu : n_blocks;
+  int per_wg = (n_blocks + grid - 1) / grid;
+  if (per_wg > kScanMaxBlocksPerWg) per_wg = kScanMaxBlocksPerWg;
+  grid = (n_blocks + per_wg - 1) / per_wg;
+#define PC_SCAN(DD, CC)                                                                                               \
+  do {                                                                                                                \
+    constexpr int lds = kScanHead + kWideStages * 32 * CC;                                                            \
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, 0, CC>, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, 0, CC>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, (Best *)nullptr, rs); \
+  } while (0)
+  if (d == 384) PC_SCAN(384, 256); else if (d == 512) PC_SCAN(512, 512); else if (d == 768) PC_SCAN(768, 512); else PC_SCAN(1024, 512);
+#undef PC_SCAN
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
+}
+
 // k best rows per probe (k == 1: the query-level match with its hit flag; hit_out may be null otherwise)
 pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes, float tau, int k, int32_t *idx_out_dev,
                      float *sim_out_dev, uint8_t *hit_out_dev, void *workspace_dev, size_t workspace_bytes, void *stream) {
@@ -977,7 +1072,7 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
 #define PC_WIDE(DD, KK)                                                                                               \
   do {                                                                                                                \
     PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, KK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, partial); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, partial, RowScan{}); \
   } while (0)
     for (int p0 = 0; p0 < n_probes; p0 += kWideProbes) {
       const int np = n_probes - p0 < kWideProbes ? n_probes - p0 : kWideProbes;
@@ -1142,12 +1237,20 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
   const _Float16 *probes = (const _Float16 *)new_emb_dev;
   hipLaunchKernelGGL(inv_norm_kernel, dim3((n_new + 3) / 4), dim3(256), 0, st, probes, probe_inv, n_new, d);
   PC_HIP(ctx, hipGetLastError());
+  int p0 = 0;
+  // (one kernel for all passes of a call: equal embeddings then have equal sums, and the lower index wins)
+  for (; p0 < n_new && scan_in_wide_passes(n_new, d); p0 += kWideProbes) {
+    const int np = n_new - p0 < kWideProbes ? n_new - p0 : kWideProbes;
+    const RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0, (np - 1) % 32 < 16 ? (np + 15) / 16 * 16 : (np + 31) / 32 * 32};
+    const pc_status ls = launch_scan_wide(ctx, st, N, d, probes + (size_t)p0 * d, np, rs);
+    if (ls != PC_OK) return ls;
+  }
   const int pass_probes = stream_shape(ctx, 2, N).lds <= kMaxLds ? kPassProbes : 16;
-  for (int p0 = 0; p0 < n_new; p0 += pass_probes) {
+  for (; p0 < n_new; p0 += pass_probes) {
     const int np = n_new - p0 < pass_probes ? n_new - p0 : pass_probes;
     const int npb = np <= 16 ? 1 : 2;
     StreamShape sh = stream_shape(ctx, npb, N);
-    RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
+    RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0, npb * 16};
     pc_status ls = launch_pass<0>(ctx, sh, npb, st, N, d, probes + (size_t)p0 * d, np, nullptr, rs);
     if (ls != PC_OK) return ls;
     PC_HIP(ctx, hipGetLastError());

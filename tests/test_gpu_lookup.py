@@ -328,3 +328,28 @@ def test_refresh_scan_vs_oracle(dim, n_new):
     assert np.array_equal(st[margin], o_stale[margin])
     assert st[pick].all()                                                             # a near copy of a query enters its top-k
     print(f"refresh scan: {int(st.sum())}/{st.size} stored queries outdated, {loose} near-tie indices", flush=True)
+
+
+@pytest.mark.parametrize("dim,n_new,rows", [(384, 33, 22309), (512, 64, 8192), (768, 128, 16385), (1024, 129, 31), (1024, 100, 30000)])
+def test_refresh_scan_wide_passes(dim, n_new, rows):
+    """More than 32 new chunks: 128 a pass of the bank, several row blocks per workgroup, a ragged last one, exact ties."""
+    g = np.random.default_rng(rows + n_new)
+    bank = wl.round_f16(g.standard_normal((rows, dim)).astype(np.float32))
+    new = wl.round_f16(g.standard_normal((n_new, dim)).astype(np.float32))
+    new[n_new - 1] = new[3]                                       # the same similarity twice: the lower index wins
+    bank[rows // 2] = new[3]
+    bank[rows - 1] = 0.0                                          # a zero row: every similarity is 0
+    kth = torch.full((rows,), 0.1, device=DEV)
+    qctx = _ctx(rows, dim)
+    qctx.percache_bank_put(0, f16(bank))
+    best_sim, best_new, stale = qctx.percache_bank_refresh_scan(f16(new), kth)
+    torch.cuda.synchronize()
+    bs, bn, st = best_sim.cpu().numpy(), best_new.cpu().numpy(), stale.cpu().numpy()
+    o_sim, o_new, o_stale = oracle.refresh_scan(bank, new, kth.cpu().numpy())
+    assert np.abs(bs - o_sim).max() < 2e-5
+    assert bn[rows // 2] == 3 and bn[rows - 1] == 0 and bs[rows - 1] == 0.0
+    for j in np.nonzero(bn != o_new)[0]:                          # only near-ties may differ
+        s = oracle.similarities(new, bank[j])
+        assert o_sim[j] - s[bn[j]] < 2e-5
+    margin = np.abs(o_sim - 0.1) > 2e-5
+    assert np.array_equal(st[margin], o_stale[margin])
