@@ -617,7 +617,8 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
 
   const int xcd = blockIdx.x & 7, jj0 = blockIdx.x >> 3;
-  const int sg = (jj0 / q_tiles) * 8 + xcd, qt = jj0 % q_tiles;
+  // (the rows that see most of the fresh tiles first: they would make a long tail)
+  const int sg = (jj0 / q_tiles) * 8 + xcd, qt = q_tiles - 1 - jj0 % q_tiles;
   if (sg >= n_groups) return;
   const int split = sg % n_splits, bg = sg / n_splits;
   const int gkv = bg % Hkv, b = bg / Hkv;
@@ -651,6 +652,13 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   const int row_c = row_ok ? my_row : R - 1;   // (wavefronts past the last row compute on the last row and write nothing)
   const int hg = row_c / T, my_i = row_c - hg * T;
   const int head = gkv * G + hg;
+  // A fresh tile is masked only if it reaches past the first token among this wavefront's rows (which may run over into the
+  // next head) and skipped if it starts behind the last; a wavefront without rows skips every tile (first token -1 of a
+  // cached one included).
+  const int w_first = row_first + __builtin_amdgcn_readfirstlane(wave) * 32, w_last = min(w_first + 31, R - 1);
+  const bool one_head = w_first / T == w_last / T;
+  const int mask_from = one_head ? max(w_first % T - (TK - 1), -1) : -1;
+  const int i_hi = w_first >= R ? -2 : one_head ? w_last % T : T - 1;
 
   bf16x8 qf[KS];
   {
@@ -808,7 +816,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
 #pragma unroll
       for (int db = 0; db < DB; ++db) vop0[db][c2] = *(const bf16x8 *)(vb + (db * 32 + l32) * L::V_ROW + v_rd[c2]);
     const int t_valid = min(TK, q_rem), t_t0 = q_t0;
-    if (__builtin_expect(t_valid < TK || t_t0 >= 0, 0)) {
+    if (__builtin_expect(t_valid < TK || t_t0 > mask_from, 0)) {
       int t_lane = g2 * 4;
       asm volatile("" : "+v"(t_lane));   // (keeps the 32 per-element key indices out of loop-invariant registers)
       const int lim_valid = t_valid - t_lane;
@@ -899,7 +907,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   asm volatile("" ::: "memory");
   int st = 0;
   for (int t = 0; t < n; ++t) {
-    tile(st);
+    if (q_t0 <= i_hi) tile(st);
     step_compute_cursor();
     PC_WAIT_VMCNT(0);   // the share of tile t+1
     if (wave < NLD && t + 2 < n) request_next(st >= 1 ? st - 1 : NSTAGE - 1);
@@ -964,7 +972,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
   char *const codes = lds + 2 * L::STAGE;
 
   const int xcd = blockIdx.x & 7, jj0 = blockIdx.x >> 3;
-  const int sg = (jj0 / q_tiles) * 8 + xcd, qt = jj0 % q_tiles;
+  const int sg = (jj0 / q_tiles) * 8 + xcd, qt = q_tiles - 1 - jj0 % q_tiles;
   if (sg >= n_groups) return;
   const int split = sg % n_splits, bg = sg / n_splits;
   const int gkv = bg % Hkv, b = bg / Hkv;
@@ -998,6 +1006,13 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
   const int row_c = row_ok ? my_row : R - 1;   // (wavefronts past the last row compute on the last row and write nothing)
   const int hg = row_c / T, my_i = row_c - hg * T;
   const int head = gkv * G + hg;
+  // A fresh tile is masked only if it reaches past the first token among this wavefront's rows (which may run over into the
+  // next head) and skipped if it starts behind the last; a wavefront without rows skips every tile (first token -1 of a
+  // cached one included).
+  const int w_first = row_first + __builtin_amdgcn_readfirstlane(wave) * 32, w_last = min(w_first + 31, R - 1);
+  const bool one_head = w_first / T == w_last / T;
+  const int mask_from = one_head ? max(w_first % T - (TK - 1), -1) : -1;
+  const int i_hi = w_first >= R ? -2 : one_head ? w_last % T : T - 1;
 
   bf16x8 qf[KS];
   {
@@ -1222,7 +1237,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
 #pragma unroll
       for (int db = 0; db < DB; ++db) vop0[db][c2] = *(const bf16x8 *)(vb + (db * 32 + l32) * L::V_ROW + v_rd[c2]);
     const int t_valid = m_valid, t_t0 = m_t0;
-    if (__builtin_expect(t_valid < TK || t_t0 >= 0, 0)) {
+    if (__builtin_expect(t_valid < TK || t_t0 > mask_from, 0)) {
       int t_lane = g2 * 4;
       asm volatile("" : "+v"(t_lane));   // (keeps the 32 per-element key indices out of loop-invariant registers)
       const int lim_valid = t_valid - t_lane;
@@ -1328,7 +1343,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
     m_valid = nx_valid;
     m_t0 = nx_t0;
     if (t + 1 < n) make_ready(cs, (t + 1) & 1, nx_valid, nx_t0);
-    tile(t & 1);
+    if (m_t0 <= i_hi) tile(t & 1);
     __builtin_amdgcn_s_waitcnt(0);
     // the code stage of tile t (emptied at the top of iteration t-1, or in the prologue) takes tile t+3
     if (wave < NLD && n_cached_left > 0) { request_codes(cs >= 1 ? cs - 1 : NCST - 1); --n_cached_left; }
@@ -1565,6 +1580,12 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   const int qrows = wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
   const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
+  // A prompt with more fresh than cached tiles: the workgroups are of unequal length as it is and go heaviest first, so more
+  // workgroups than CUs even out without partitions (4224 fresh rows x 16 heads over nothing cached, 264 workgroups, layer of a
+  // stack: 1 partition 360 us, 2 363, 4 373 with a merge of 14; before, lightest first and every fresh tile masked: 411 to 421).
+  const int fresh_tiles = (t_fresh + TK - 1) / TK;
+  const bool uneven = wide && 2 * fresh_tiles > min_tiles && (long)batch * c.n_kv_heads * q_tiles >= ctx->n_cu;
+  if (n_splits <= 0 && uneven) n_splits = 1;
   if (n_splits <= 0) n_splits = choose_splits(wide ? ctx->n_cu : 2 * ctx->n_cu, (long)batch * c.n_kv_heads * q_tiles, min_tiles, cap);
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;

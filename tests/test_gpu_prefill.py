@@ -285,6 +285,26 @@ def test_long_context_kernel_on_ragged_lists(t_fresh, n_splits, head_dim):
     pc.close()
 
 
+@pytest.mark.parametrize("t_fresh,n_splits,head_dim,kv_fp8", [(601, 0, 128, False), (704, 3, 128, False), (1025, 0, 64, False), (601, 0, 128, True)])
+def test_long_context_kernel_on_long_fresh_parts(t_fresh, n_splits, head_dim, kv_fp8):
+    """More fresh than cached keys: tiles a wavefront masks, takes whole or skips by its first and last token, row blocks
+    that straddle two of the three heads and wavefronts without rows (3 x 601 = 7 x 256 + 11, 3 x 1025 = 12 x 256 + 3)."""
+    from oracle import kv_fp8 as fp8
+    w = wl.make_prefill("wide_fresh", 33, "bf16", 128, 24, 8, head_dim, 1, t_fresh, 2, 128, 4)
+    w.used_len[0] = [65, 0]
+    pc = make_ctx(w, kv_fp8=kv_fp8)
+    fill_slots(pc, w, w.slot_ids.reshape(-1))
+    q, kf, vf = pc.percache_qkv_rope(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)
+    out = pc.percache_attention_reuse(0, q, kf, vf, w.slot_ids, w.used_len, n_splits=n_splits)
+    torch.cuda.synchronize()
+    sk, sv, ids = w.compact_store(0)
+    if kv_fp8:
+        sk, sv = (np.stack([fp8.round_trip(wl.round_bf16(x)) for x in a]) for a in (sk, sv))
+    O, _, _, _ = oracle.prefill_reuse(w.X[0], w.Wqkv, w.n_q_heads, w.n_kv_heads, w.head_dim, w.rope_theta, sk, sv, ids, w.used_len[0])
+    check_close(host(out[0]), O, f"long fresh part T={t_fresh} splits={n_splits} D={head_dim} 8-bit={kv_fp8}")
+    pc.close()
+
+
 @pytest.mark.parametrize("t_fresh,n_splits,n16", [(70, 0, 0), (100, 3, 0), (256, 1, 0), (70, 2, 3), (192, 0, 3)])
 def test_long_context_kernel_over_8bit_slots(t_fresh, n_splits, n16):
     """The long-context launch shape over 8-bit slots: every chunk of the call in an 8-bit slot (a store of 8-bit slots
