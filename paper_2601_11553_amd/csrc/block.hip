@@ -19,6 +19,8 @@ using pc::gemm::BF;
 using pc::gemm::pack4;
 using pc::gemm::unpack4;
 
+constexpr int kXcds = 8;
+
 // ---------------------------------------------------------------------------------------------------
 // y = x / sqrt(mean(x^2) + eps) * gain; one wavefront per row, fp32 arithmetic, bf16 in and out.
 // ---------------------------------------------------------------------------------------------------
@@ -82,6 +84,36 @@ __global__ __launch_bounds__(256, 2) void linear_residual_kernel(const __bf16 *_
           *(uint2 *)(Y + at) = pack4(acc[a][t][q4 * 4 + 0] + res[0], acc[a][t][q4 * 4 + 1] + res[1],
                                    acc[a][t][q4 * 4 + 2] + res[2], acc[a][t][q4 * 4 + 3] + res[3]);
       }
+  }
+}
+
+// The same for a launch of at most one workgroup per CU, on mainloop_deep.  Consecutive tiles (features first) sit on one XCD, so
+// that its L2 holds few token rows.
+template <int NTB, int NSTG>
+__global__ __launch_bounds__(512) void linear_residual_deep_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
+                                                                   const __bf16 *__restrict__ R, __bf16 *__restrict__ Y, int M, int N, int K) {
+  constexpr int BT = 64 * NTB;
+  __shared__ __align__(16) char lds[pc::gemm::DeepShape<NTB, NSTG>::LDS_BYTES];
+  const int n_ft = N / BF, tile = (int)(blockIdx.x % kXcds) * (int)(gridDim.x / kXcds) + (int)(blockIdx.x / kXcds);
+  if (tile >= n_ft * ((M + BT - 1) / BT)) return;
+  const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6);
+  const int wf = wave & 1, wt = (wave >> 1) & 1, kh = wave >> 2;
+  const int l32 = lane & 31, g = lane >> 5;
+  const int f0 = tile % n_ft * BF, m0 = tile / n_ft * BT;
+  f32x16 sum[NTB];
+  pc::gemm::mainloop_deep<NTB, NSTG>(lds, [&](int row) __attribute__((always_inline)) { return W + (size_t)(f0 + row) * K; }, A, K, m0, M, K,
+                                     2 * wf, 2 * wf + 1, wt, sum);
+#pragma unroll
+  for (int t = 0; t < NTB; ++t) {
+    const int m = m0 + (wt * NTB + t) * 32 + l32;
+    if (m >= M) continue;
+#pragma unroll
+    for (int q4 = 0; q4 < 4; ++q4) {
+      const size_t at = (size_t)m * N + f0 + (2 * wf + kh) * 32 + q4 * 8 + g * 4;
+      float res[4];
+      unpack4(*(const uint2 *)(R + at), res);
+      *(uint2 *)(Y + at) = pack4(sum[t][q4 * 4 + 0] + res[0], sum[t][q4 * 4 + 1] + res[1], sum[t][q4 * 4 + 2] + res[2], sum[t][q4 * 4 + 3] + res[3]);
+    }
   }
 }
 
@@ -283,8 +315,26 @@ pc_status launch_rmsnorm(percache_ctx *ctx, const __bf16 *x, const __bf16 *gain,
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
+// Token rows per tile of linear_residual_deep_kernel where its tiles go to the CUs in one round, else 0: there the two-stage
+// loop has about one workgroup per CU and waits out every stage's round trip; in several rounds its two workgroups per CU cover
+// each other.  4224 rows x 1024 features, 192-token tiles (176 of them; of 128 tokens they are 264): 33 us over 2048 elements and
+// 44 over 3072, where the two-stage loop took 50 on average (0.68 us a k-step, 10 TB/s of operands out of L2, is what bounds it).
+int deep_tokens(int n_cu, int M, int N) {
+  for (int bt = 128; bt <= 192; bt += 64)
+    if (M > bt && (long)(N / BF) * ((M + bt - 1) / bt) <= n_cu) return bt;
+  return 0;
+}
 pc_status launch_linear_residual(percache_ctx *ctx, const __bf16 *a, const __bf16 *w, const __bf16 *res, __bf16 *y, int M,
                                  int N, int K, hipStream_t s) {
+  const int deep = deep_tokens(ctx->n_cu, M, N);
+  if (deep) {
+    const int tiles = N / BF * ((M + deep - 1) / deep);
+    const dim3 grid((tiles + kXcds - 1) / kXcds * kXcds);
+    if (deep == 128) hipLaunchKernelGGL((linear_residual_deep_kernel<2, 4>), grid, dim3(512), 0, s, a, w, res, y, M, N, K);
+    else hipLaunchKernelGGL((linear_residual_deep_kernel<3, 4>), grid, dim3(512), 0, s, a, w, res, y, M, N, K);
+    PC_HIP(ctx, hipGetLastError());
+    return PC_OK;
+  }
   const bool big = M > 64 * 3;
   dim3 grid(N / BF, big ? (M + 127) / 128 : (M + 63) / 64);
   if (big) hipLaunchKernelGGL(linear_residual_kernel<2>, grid, dim3(256), 0, s, a, w, res, y, M, N, K);

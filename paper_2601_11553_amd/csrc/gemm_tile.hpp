@@ -38,6 +38,13 @@ __device__ __forceinline__ void wait_vmcnt() {
   __builtin_amdgcn_s_waitcnt((N & 0xf) | (7 << 4) | (15 << 8) | (((N >> 4) & 3) << 14));
 }
 
+// the same with lgkmcnt(0)
+template <int N>
+__device__ __forceinline__ void wait_vmcnt_lds() {
+  static_assert(N >= 0 && N < 64, "vmcnt is a 6-bit field");
+  __builtin_amdgcn_s_waitcnt((N & 0xf) | (7 << 4) | (((N >> 4) & 3) << 14));
+}
+
 __device__ __forceinline__ uint2 pack4(float a, float b, float c, float d) {
   bf16x4 v = {(__bf16)a, (__bf16)b, (__bf16)c, (__bf16)d};
   return __builtin_bit_cast(uint2, v);
@@ -263,6 +270,127 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
   }
   wait_vmcnt0();  // (the surplus request of the last k-steps)
   __builtin_amdgcn_s_barrier();
+}
+
+// The same tile (128 features x 64*NTB tokens) for a launch of at most one workgroup per CU, where nobody else covers the
+// round trip of a stage (0.6 to 1.1 us against 0.3 to 0.4 us of MFMA work per k-step): 8 wavefronts and a ring of NSTG stages,
+// all of them requested ahead; the one barrier of a k-step sits between its halves, where the rest of its stage is in registers.  Wavefronts w and w + 4 own the same block of the tile and take one half of every stage's
+// k-elements each (kh = w >> 2), so a SIMD has two instruction streams at no more operand reads per MFMA; their sums meet
+// once, in LDS: on return acc[t] holds the whole sums of feature block kh (of fb_lo, fb_hi) in the layout of mainloop.
+template <int NTB, int NSTG>
+struct DeepShape {
+  static constexpr int NWV = 8, BT = 64 * NTB;
+  static constexpr int W_BYTES = BF * ROW, X_BYTES = BT * ROW, STAGE = W_BYTES + X_BYTES;
+  static constexpr int W_INSTR = W_BYTES / 1024 / NWV, X_INSTR = X_BYTES / 1024 / NWV, INSTR = W_INSTR + X_INSTR;
+  static constexpr int LDS_BYTES = NSTG * STAGE;
+  static_assert(NSTG >= 3 && NSTG <= 4 && (NSTG - 1) * INSTR < 64, "vmcnt");
+  static_assert(NWV * NTB * 4096 <= LDS_BYTES && LDS_BYTES <= 160 * 1024, "LDS of a CU; the exchanged sums take the ring's place");
+};
+
+template <int NTB, int NSTG, class T, class WRow>
+__device__ __forceinline__ void mainloop_deep(char *lds, WRow w_row, const T *__restrict__ X, int ldx, int m0, int M, int K,
+                                              int fb_lo, int fb_hi, int wt, f32x16 (&sum)[NTB]) {
+  using S = DeepShape<NTB, NSTG>;
+  using V8 = typename Vec8<T>::type;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), kh = wave >> 2;
+  const int l32 = lane & 31, g = lane >> 5;
+  const T *src[S::INSTR];
+#pragma unroll
+  for (int k = 0; k < S::INSTR; ++k) {
+    const int row = (wave + (k < S::W_INSTR ? k : k - S::W_INSTR) * S::NWV) * 8 + (lane >> 3);
+    src[k] = (k < S::W_INSTR ? w_row(row) : X + (size_t)min(m0 + row, M - 1) * ldx) + (((lane & 7) ^ swz128(row)) * 8);
+  }
+  auto fetch = [&](int kt, int st) __attribute__((always_inline)) {
+    char *base = lds + st * S::STAGE;
+#pragma unroll
+    for (int k = 0; k < S::INSTR; ++k)
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[k] + kt * BK),
+                                       (__attribute__((address_space(3))) void *)(base + (k < S::W_INSTR ? 0 : S::W_BYTES) +
+                                                                                  (wave + (k < S::W_INSTR ? k : k - S::W_INSTR) * S::NWV) * 1024),
+                                       16, 0, 0);
+  };
+  f32x16 acc[2][NTB];
+#pragma unroll
+  for (int a = 0; a < 2; ++a)
+#pragma unroll
+    for (int t = 0; t < NTB; ++t)
+#pragma unroll
+      for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
+  int rd[2];  // this wavefront's half of a row: k-elements 32 kh .. +31
+#pragma unroll
+  for (int ks = 0; ks < 2; ++ks) rd[ks] = ((2 * (2 * kh + ks) + g) ^ swz128(l32)) * 16;
+  const int lo_off = (fb_lo * 32 + l32) * ROW, hi_off = (fb_hi * 32 + l32) * ROW, x_off = S::W_BYTES + ((wt * NTB) * 32 + l32) * ROW;
+
+  V8 oa[2][2], ob[2][NTB];  // operands of the two k-halves (16 elements each) of this wavefront's share of a stage
+  auto read_ops = [&](int ks, int st) __attribute__((always_inline)) {
+    const char *base = lds + st * S::STAGE + rd[ks];
+    oa[ks][0] = *(const V8 *)(base + lo_off);
+    oa[ks][1] = *(const V8 *)(base + hi_off);
+#pragma unroll
+    for (int t = 0; t < NTB; ++t) ob[ks][t] = *(const V8 *)(base + x_off + t * 32 * ROW);
+  };
+  auto mma_ops = [&](int ks) __attribute__((always_inline)) {
+#pragma unroll
+    for (int t = 0; t < NTB; ++t) {
+      acc[0][t] = mma(oa[ks][0], ob[ks][t], acc[0][t]);
+      acc[1][t] = mma(oa[ks][1], ob[ks][t], acc[1][t]);
+    }
+  };
+  // one MFMA, one LDS read, ... and `loads` request instructions among them
+  auto interleave = [&](int loads) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 2 * NTB; ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      if (i < NTB + 2) __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
+      if (i < loads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
+  };
+  const int nk = K / BK;
+#pragma unroll
+  for (int k = 0; k < NSTG; ++k) fetch(min(k, nk - 1), k);  // (past the last k-step: the last one again, into a stage nobody reads)
+  wait_vmcnt<(NSTG - 1) * S::INSTR>();
+  asm volatile("" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+  read_ops(0, 0);
+  int st = 0;
+  for (int kt = 0; kt < nk; ++kt) {
+    const int next = st + 1 == NSTG ? 0 : st + 1;
+    read_ops(1, st);
+    mma_ops(0);
+    interleave(0);
+    // (lgkmcnt 0) every read of this stage is in registers, and k-step kt + 1 has landed: behind the barrier the stage is free
+    wait_vmcnt_lds<(NSTG - 2) * S::INSTR>();
+    asm volatile("" ::: "memory");
+    __builtin_amdgcn_s_barrier();
+    asm volatile("" ::: "memory");
+    fetch(min(kt + NSTG, nk - 1), st);
+    read_ops(0, next);  // (past the last k-step: whatever that stage holds, never multiplied)
+    mma_ops(1);
+    interleave(S::INSTR);
+    st = next;
+  }
+  wait_vmcnt<0>();  // (the surplus requests)
+  // each wavefront hands the block that it does not keep to its partner
+  __syncthreads();
+  f32x4 *const give = (f32x4 *)(lds + wave * (NTB * 4096)), *const take = (f32x4 *)(lds + (wave ^ 4) * (NTB * 4096));
+#pragma unroll
+  for (int t = 0; t < NTB; ++t) {
+    const f32x16 v = kh ? acc[0][t] : acc[1][t];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) give[(t * 4 + q) * 64 + lane] = f32x4{v[4 * q], v[4 * q + 1], v[4 * q + 2], v[4 * q + 3]};
+  }
+  __syncthreads();
+#pragma unroll
+  for (int t = 0; t < NTB; ++t) {
+    sum[t] = kh ? acc[1][t] : acc[0][t];
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      const f32x4 o = take[(t * 4 + q) * 64 + lane];
+#pragma unroll
+      for (int e = 0; e < 4; ++e) sum[t][4 * q + e] += o[e];
+    }
+  }
 }
 
 }  // namespace gemm

@@ -316,3 +316,37 @@ def test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which):
         sk, sv, ids = w.compact_store(b)
         ref, _, _ = oracle_block(w.X[b], W, Hq, Hkv, D, w.rope_theta, sk, sv, ids, w.used_len[b], extras=extras)
         check_hidden(host(h_out[b]), ref, f"few rows D={D} H={H} F={F} B={batch} T={t_fresh} {which} query {b}")
+
+
+@pytest.mark.parametrize("H,F,batch,t_fresh", [
+    (256, 64, 5, 209),     # 1045 rows: 128-token tiles, the last one of 21 rows, a contraction of one k-step
+    (256, 448, 4, 272),    # 1088 rows: half a tile at the end, seven k-steps
+    (1152, 192, 4, 911),   # 3644 rows of 9 feature tiles: 192-token tiles (29 of 128 would be 261 on 256 CUs), three k-steps
+    (1152, 64, 4, 896),    # 3584 rows: 252 tiles of 128 tokens
+    (1152, 64, 1, 5441),   # 29 tiles of 192 tokens are 261 again: the tiles of two workgroups per CU
+])
+def test_residual_projection_in_one_round(H, F, batch, t_fresh):
+    """o_proj and down projection on either side of the lines between their tiles, against the block in fp32."""
+    Hq, Hkv, D, C = 4, 2, 64, 64
+    w = wl.make_prefill("round", 25, "bf16", H, Hq, Hkv, D, batch, t_fresh, 1, C, batch, last_used_len=37)
+    w.slot_ids[:] = np.arange(batch, dtype=np.int32)[:, None]
+    W = wl.stack_weights(25, 0, H, Hq, Hkv, D, F)
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=batch, slot_capacity=C,
+                  max_pos=w.max_pos, device=DEV)
+    for s_ in range(batch):
+        k, v = w.slot_kv(s_)
+        pc.percache_kv_put(0, s_, bf16(k), bf16(v))
+    layer = dev_layers([W])[0]
+    h_out = pc.percache_stack_reuse([layer], F, EPS, bf16(w.X), w.slot_ids, w.used_len)
+    # what the two projections start from, by the library's own attention: the fp32 reference covers the rest of the block
+    x = bf16(w.X).float()
+    gain = lambda name: layer[name].float()
+    norm = lambda y, g: (y / (y.pow(2).mean(-1, keepdim=True) + EPS).sqrt() * g).bfloat16()
+    attn = pc.percache_prefill_reuse(0, norm(x, gain("gain1")), layer["wqkv"], w.slot_ids, w.used_len)
+    attn = attn[0] if isinstance(attn, tuple) else attn
+    mid = (attn.reshape(batch, t_fresh, Hq * D).float() @ gain("wo").T + x).bfloat16().float()
+    n = norm(mid, gain("gain2")).float()
+    act = (torch.nn.functional.silu(n @ gain("w_gate").T) * (n @ gain("w_up").T)).bfloat16().float()
+    ref = act @ gain("w_down").T + mid
+    torch.cuda.synchronize()
+    check_hidden(host(h_out).reshape(-1, H), ref.cpu().numpy().reshape(-1, H), f"H={H} F={F} rows={batch * t_fresh}")
