@@ -197,7 +197,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void linear_resid
 // splitkv_combine_kernel (m = max m_s, weights l_s 2^(m_s - m), rounded to bf16 once), instead of a launch that merges and
 // one that reads the result back.  Lanes l and l + 32 share 8 columns of a row and take every other partition.
 constexpr int kMergeSteps = 8;   // steps of 64 columns per wavefront: up to 4096 columns
-__global__ __launch_bounds__(512) void oproj_merge_few_kernel(const __bf16 *__restrict__ part_o, const float *__restrict__ part_ml, int n_splits, int T,
+__global__ __launch_bounds__(512) void oproj_merge_few_kernel(const float *__restrict__ part_o, const float *__restrict__ part_ml, int n_splits, int T,
                                                               int Hkv, int G, int D, const __bf16 *__restrict__ W, const __bf16 *__restrict__ R,
                                                               __bf16 *__restrict__ Y, int M, int N, int K, int n_wt) {
   constexpr int WV = 8, NSTG = 2, CH = 10;
@@ -221,21 +221,24 @@ __global__ __launch_bounds__(512) void oproj_merge_few_kernel(const __bf16 *__re
           const int k = (s0 + step) * 64 + c * 8, head = k / D, b = m / T, i = m - b * T;
           const size_t prow = ((((size_t)b * Hkv + head / G) * G + head % G) * T + i) * n_splits;
           const float2 *ml = (const float2 *)part_ml + prow;
-          const __bf16 *po = part_o + prow * D + (k - head * D);
+          const float *po = part_o + prow * D + (k - head * D);
           float mx = -INFINITY, wsum = 0.f, a8[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
-          for (int sp0 = half; sp0 < n_splits; sp0 += 2 * CH) {
+          for (int r0 = 0; r0 < n_splits; r0 += 2 * CH) {
             float2 e[CH];
-            pc::bf16x8 o[CH];
+            f32x4 o[CH][2];
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-              const int sp = min(sp0 + 2 * j, n_splits - 1);
+              if (r0 + 2 * j >= n_splits) break;
+              const int sp = min(r0 + half + 2 * j, n_splits - 1);
               e[j] = ml[sp];
-              o[j] = *(const pc::bf16x8 *)(po + (size_t)sp * D);
+              o[j][0] = *(const f32x4 *)(po + (size_t)sp * D);
+              o[j][1] = *(const f32x4 *)(po + (size_t)sp * D + 4);
             }
             float top = mx;
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
-              if (sp0 + 2 * j >= n_splits || !(e[j].y > 0.f)) e[j] = make_float2(-INFINITY, 0.f);   // (an empty partition has weight 0)
+              if (r0 + 2 * j >= n_splits) break;
+              if (r0 + half + 2 * j >= n_splits || !(e[j].y > 0.f)) e[j] = make_float2(-INFINITY, 0.f);   // (an empty partition has weight 0)
               top = fmaxf(top, e[j].x);
             }
             const float shrink = mx == -INFINITY ? 0.f : exp2f(mx - top);
@@ -245,10 +248,11 @@ __global__ __launch_bounds__(512) void oproj_merge_few_kernel(const __bf16 *__re
             for (int e8 = 0; e8 < 8; ++e8) a8[e8] *= shrink;
 #pragma unroll
             for (int j = 0; j < CH; ++j) {
+              if (r0 + 2 * j >= n_splits) break;
               const float w = e[j].y > 0.f ? e[j].y * exp2f(e[j].x - top) : 0.f;
               wsum += w;
 #pragma unroll
-              for (int e8 = 0; e8 < 8; ++e8) a8[e8] += w * (float)o[j][e8];
+              for (int e8 = 0; e8 < 8; ++e8) a8[e8] += w * o[j][e8 >> 2][e8 & 3];
             }
           }
           const float m2 = __shfl_xor(mx, 32, 64), both = fmaxf(mx, m2);
@@ -372,7 +376,7 @@ bool oproj_merges(const percache_config &c, long M) {
   const int steps = (c.n_q_heads * c.head_dim + 511) / 512;
   return steps <= kMergeSteps && M * steps <= 8;
 }
-pc_status launch_oproj_merge(percache_ctx *ctx, const __bf16 *part_o, const float *part_ml, int n_splits, int t_fresh, const __bf16 *w,
+pc_status launch_oproj_merge(percache_ctx *ctx, const float *part_o, const float *part_ml, int n_splits, int t_fresh, const __bf16 *w,
                              const __bf16 *res, __bf16 *y, int M, hipStream_t s) {
   const percache_config &c = ctx->cfg;
   const int n_wt = c.hidden / 16;
@@ -603,7 +607,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     for (int b = 0; b < batch && append_slots_host; ++b)
       if (append_slots_host[b] >= 0) ctx->slot_len[(size_t)l * c.n_slots + append_slots_host[b]] += t_fresh;
     if (few) {
-      if (left_splits > 1) PC_TRY(launch_oproj_merge(ctx, ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
+      if (left_splits > 1) PC_TRY(launch_oproj_merge(ctx, (const float *)ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
       else PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
       PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
       PC_TRY(launch_residual_few(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));

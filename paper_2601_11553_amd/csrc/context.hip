@@ -187,7 +187,7 @@ PrefillWs carve_prefill_ws(const percache_config &c, int n_cu, void *base, int32
   w.qkv_raw = (float *)take(few_rows(c, (long)M) ? M * (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * sizeof(float) : 0);
   size_t rows = (size_t)batch * c.n_q_heads * t_fresh;
   w.max_splits = max_splits_for(c, n_cu, batch, t_fresh);
-  w.part_o = (__bf16 *)take(rows * w.max_splits * c.head_dim * 2);
+  w.part_o = take(rows * w.max_splits * c.head_dim * (decode_rows(c, t_fresh) ? 4 : 2));
   w.part_ml = (float *)take(rows * w.max_splits * 2 * sizeof(float));
   w.total = off;
   return w;

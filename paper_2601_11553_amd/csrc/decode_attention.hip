@@ -128,7 +128,7 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf, pc::RawQkv raw, const __bf16 *k16,
     const __bf16 *v16, const uint8_t *__restrict__ k8, const uint8_t *__restrict__ v8, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table, int tbl_stride, int T, int Hq, int Hkv, int C,
-    int n_splits, float scale_log2e, __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
+    int n_splits, float scale_log2e, __bf16 *__restrict__ out, float *__restrict__ part_o, float *__restrict__ part_ml) {
   using L = Lds<D, FMT, NR>;
   constexpr int KS = D / 32, DB = D / 16;
   __shared__ __align__(16) char lds[L::BYTES];
@@ -536,14 +536,19 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
       }
     }
     const float inv = l > 0.f ? 1.0f / l : 0.f;
-    bf16x8 v;
 #pragma unroll
-    for (int e = 0; e < 8; ++e) v[e] = (__bf16)(acc[e] * inv);
+    for (int e = 0; e < 8; ++e) acc[e] *= inv;
     if (n_splits == 1) {
+      bf16x8 v;
+#pragma unroll
+      for (int e = 0; e < 8; ++e) v[e] = (__bf16)acc[e];
       *(bf16x8 *)(out + ((size_t)b * T + i) * ((size_t)Hq * D) + (size_t)(gkv * G + hg) * D + dv * 8) = v;
     } else {
       const size_t prow = (((size_t)b * Hkv + gkv) * R + row) * n_splits + split;
-      *(bf16x8 *)(part_o + prow * D + dv * 8) = v;
+      // fp32: even a call of a few tiles is cut here, and its sums are rounded to bf16 once, behind the merge
+      float *po = part_o + prow * D + dv * 8;
+      *(f32x4 *)po = f32x4{acc[0], acc[1], acc[2], acc[3]};
+      *(f32x4 *)(po + 4) = f32x4{acc[4], acc[5], acc[6], acc[7]};
       if (dv == 0) {
         part_ml[prow * 2] = m;
         part_ml[prow * 2 + 1] = l;
@@ -565,7 +570,7 @@ static int decode_splits(int n_cu, long base_wgs, int tiles, int cap) {
 }
 
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
-                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, __bf16 *part_o,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, float *part_o,
                                   float *part_ml, hipStream_t stream, int formats) {
   const percache_config &c = ctx->cfg;
   const int R = c.n_q_heads / c.n_kv_heads * t_fresh;

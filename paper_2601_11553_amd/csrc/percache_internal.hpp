@@ -133,7 +133,7 @@ struct PrefillWs {
   __bf16 *q, *k, *v;
   __bf16 *v_blk;   // fresh V as 64-key blocks [B*Hkv][ceil(T/64)][D][64]
   float *qkv_raw;  // the projection's sums [B*T][(Hq + 2 Hkv) * D] (few rows only)
-  __bf16 *part_o;  // [rows][splits][D], normalised per split
+  void *part_o;    // [rows][splits][D], normalised per split; fp32 where decode_rows, else bf16
   float *part_ml;  // [rows][splits][2]
   int max_splits;  // partitions of the key axis the partial buffers can hold
   size_t total;
@@ -190,11 +190,11 @@ inline bool decode_rows(const percache_config &c, int t_fresh) { return (long)(c
 // left_splits (decode_rows only): the caller merges the partials itself; set to their number, at 1 the result is in out.
 pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
                            const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int max_tiles,
-                           int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats,
+                           int n_splits, __bf16 *out, void *part_o, float *part_ml, hipStream_t stream, int formats,
                            int *left_splits = nullptr);
 // The first of its two launches where decode_rows; tiles: cached tiles of the shortest query.  n_splits <= 0: chosen here.
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
-                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, __bf16 *part_o,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, float *part_o,
                                   float *part_ml, hipStream_t stream, int formats);
 // Number of key-axis partitions that fills `slots` resident workgroups best (at least 4 tiles in each).
 int choose_splits(int slots, long base_wgs, int min_tiles, int cap);

@@ -1389,8 +1389,9 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
 // s = sg, sg + 4, ..., and the four partial sums meet through lane shuffles.
 // FEW (at most four partitions): one lane per 16 output bytes takes all of them, four independent loads in flight,
 // and adds them up in the order the shuffles would, (0 + 1) + (2 + 3), so both forms give the same bits.
-template <int D, bool FEW>
-__global__ __launch_bounds__(256) void splitkv_combine_kernel(const __bf16 *__restrict__ part_o,
+// P: type of the partials (fp32 behind decode_attention_kernel, bf16 behind the others).
+template <int D, bool FEW, class P>
+__global__ __launch_bounds__(256) void splitkv_combine_kernel(const P *__restrict__ part_o,
                                                               const float *__restrict__ part_ml, int n_splits, int T,
                                                               int Hq, int Hkv, long total_rows,
                                                               __bf16 *__restrict__ out) {
@@ -1402,18 +1403,19 @@ __global__ __launch_bounds__(256) void splitkv_combine_kernel(const __bf16 *__re
   const bool live = prow_raw < total_rows;
   const long prow = live ? prow_raw : total_rows - 1;
   const float2 *ml = (const float2 *)part_ml + prow * n_splits;
-  const __bf16 *po = part_o + prow * n_splits * D + dv * 8;
+  const P *po = part_o + prow * n_splits * D + dv * 8;
+  typedef P p8 __attribute__((ext_vector_type(8)));
   float wsum = 0.f;
   float acc[8] = {0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f, 0.f};
   if constexpr (FEW) {
 #pragma clang fp contract(off)  // products rounded before the sums, as in the other form
     float2 e[4];
-    pc::bf16x8 o[4];
+    p8 o[4];
 #pragma unroll
     for (int s = 0; s < 4; ++s) {
       const int sc = s < n_splits ? s : 0;
       e[s] = ml[sc];
-      o[s] = *(const pc::bf16x8 *)(po + (size_t)sc * D);
+      o[s] = *(const p8 *)(po + (size_t)sc * D);
       if (s >= n_splits) e[s].y = 0.f;
     }
     float m = -INFINITY;
@@ -1432,12 +1434,12 @@ __global__ __launch_bounds__(256) void splitkv_combine_kernel(const __bf16 *__re
     float m = -INFINITY;
     for (int s0 = 0; s0 < n_splits; s0 += 4 * SG) {
       float2 e[4];
-      pc::bf16x8 o[4];
+      p8 o[4];
 #pragma unroll
       for (int j = 0; j < 4; ++j) {
         const int s = s0 + sg + j * SG, sc = s < n_splits ? s : 0;
         e[j] = ml[sc];
-        o[j] = *(const pc::bf16x8 *)(po + (size_t)sc * D);
+        o[j] = *(const p8 *)(po + (size_t)sc * D);
         if (s >= n_splits) e[j].y = 0.f;   // (as an empty partition: weight 0)
       }
       float top = m;
@@ -1530,7 +1532,8 @@ pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, i
 }
 
 // Merges the partials of a launch whose key axis was cut into n_splits > 1 partitions.
-static pc_status launch_combine(percache_ctx *ctx, const __bf16 *part_o, const float *part_ml, int n_splits, int batch, int t_fresh, __bf16 *out,
+template <class P>
+static pc_status launch_combine(percache_ctx *ctx, const P *part_o, const float *part_ml, int n_splits, int batch, int t_fresh, __bf16 *out,
                                 hipStream_t stream) {
   const percache_config &c = ctx->cfg;
   const long total_rows = (long)batch * c.n_q_heads * t_fresh;
@@ -1538,7 +1541,7 @@ static pc_status launch_combine(percache_ctx *ctx, const __bf16 *part_o, const f
   long threads = total_rows * (c.head_dim / 8) * (few_parts ? 1 : 4);
   int blocks = (int)((threads + 255) / 256);
 #define PC_COMBINE(DD, FF)                                                                                          \
-  hipLaunchKernelGGL((splitkv_combine_kernel<DD, FF>), dim3(blocks), dim3(256), 0, stream, part_o, part_ml, n_splits, \
+  hipLaunchKernelGGL((splitkv_combine_kernel<DD, FF, P>), dim3(blocks), dim3(256), 0, stream, part_o, part_ml, n_splits, \
                    t_fresh, c.n_q_heads, c.n_kv_heads, total_rows, out)
   if (c.head_dim == 128) { if (few_parts) PC_COMBINE(128, true); else PC_COMBINE(128, false); }
   else { if (few_parts) PC_COMBINE(64, true); else PC_COMBINE(64, false); }
@@ -1549,10 +1552,11 @@ static pc_status launch_combine(percache_ctx *ctx, const __bf16 *part_o, const f
 
 pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
                            const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int min_tiles,
-                           int n_splits, __bf16 *out, __bf16 *part_o, float *part_ml, hipStream_t stream, int formats, int *left_splits) {
+                           int n_splits, __bf16 *out, void *part_dev, float *part_ml, hipStream_t stream, int formats, int *left_splits) {
   const percache_config &c = ctx->cfg;
   const int G = c.n_q_heads / c.n_kv_heads, R = G * t_fresh;
   if (decode_rows(c, t_fresh)) {
+    float *part_o = (float *)part_dev;
     prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
     const pc_status st = launch_decode_attention(ctx, layer, q, kf, vf, raw, batch, t_fresh, table_dev, tbl_stride,
                                                  min_tiles - (t_fresh + TK - 1) / TK, n_splits, out, part_o, part_ml, stream, formats);
@@ -1564,6 +1568,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     }
     return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
+  __bf16 *part_o = (__bf16 *)part_dev;
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
   // variant that tells the formats apart tile by tile only when it names chunks of both formats
   const bool use8 = (formats & 1) && ctx->n_slots8 > 0;
