@@ -5,15 +5,16 @@
 // head has a few dozen 64-key tiles in all, and a workgroup that walks several of them one after the other, three of its
 // four wavefronts only loading because 32-row tiles are the unit of work, spends its time waiting.  Here:
 //   - the key range is cut finely: a workgroup gets about two tiles when the call is small, and all of them are requested
-//     at once (a ring of four stages, direct global->LDS loads by all four wavefronts);
+//     at once (a ring of four stages, direct global->LDS loads by all four wavefronts); a long call counts on two workgroups per
+//     CU where two rings fit its LDS;
 //   - the wavefronts share the tile by KEYS: wavefront w takes keys 16 w .. 16 w + 15 for all rows (scores by the
 //     16x16x32 product with the keys on the M side, values by the 16x16x16 one, whose B operand is exactly the layout the
 //     scores come out in), each with its own running maximum, sum and output; they merge once, through LDS;
 //   - the few fresh keys need no V blocks: their probabilities are applied to the V rows as they were projected, in the
 //     merge.
 // One query, 8 kv heads, 38 tiles (bf16, D = 128): 8.6 us with q, k and v finished here, 7.1 from finished ones (the general
-// kernel 13.6, behind a V repack of 2.4 and in front of an append launch of 2.8 per query); 8 queries x 8 kv heads x about 200
-// tiles: 66-68 us either way, 6.4 TB/s of keys and values.
+// kernel 13.6, behind a V repack of 2.4 and in front of an append launch of 2.8 per query); 8 queries x 8 kv heads x 256 tiles:
+// 87 us of bf16 slots (6.2 TB/s of keys and values), 53 of 8-bit ones (5.1; the general kernel 62), 70 of mixed ones (73).
 #include "percache_internal.hpp"
 
 namespace {
@@ -23,7 +24,7 @@ using pc::f32x4;
 using pc::kKvTile;
 using pc::kTblHeader;
 
-constexpr int TK = kKvTile, NW = 4, NSTG = 4;
+constexpr int TK = kKvTile, NW = 4;
 constexpr float kSumLimit = 4.f * 256.f;  // 4 probabilities of a lane and tile, each at most 2^8 against the reference
 
 #define PC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xf) | (7 << 4) | (15 << 8) | ((((n) >> 4) & 3) << 14))
@@ -55,8 +56,10 @@ __device__ __forceinline__ bf16x8 codes8(uint2 w, float scale) {
 }
 
 // FMT: 0 every cached chunk of the call sits in a bf16 slot, 1 in an 8-bit slot, 2 some of each.  NR: blocks of 16 rows.
-template <int D, int FMT, int NR>
+// TWO: the form of long calls in which two workgroups share a CU (see launch_decode_attention).
+template <int D, int FMT, int NR, bool TWO>
 struct Lds {
+  static constexpr int NSTG = TWO && FMT == 2 ? 2 : 4;                   // stages of the ring
   static constexpr int K16 = TK * D * 2, V16 = K16, K8 = TK * D, V8 = K8;
   static constexpr int STAGE = FMT == 1 ? K8 + V8 : K16 + V16;
   static constexpr int O_ROW = D + 4;                                    // floats per output row of a wavefront (padded)
@@ -123,14 +126,14 @@ struct RawRow {
 // its query rows, under the latency of its first K/V tiles, and by the one with the fresh keys for k and v, which it also
 // writes: dense (k_out, v_out) and, where the query has a bf16 slot to append to, behind the tokens that slot holds.  The
 // keys of that slot read by this launch are the older ones (lengths come from the chunk list).
-template <int D, int FMT, int NR, bool RAW>
-__global__ __launch_bounds__(256) void decode_attention_kernel(
+template <int D, int FMT, int NR, bool RAW, bool TWO>
+__global__ __launch_bounds__(256, (FMT == 1 && NR == 1) || TWO ? 2 : 1) void decode_attention_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf, pc::RawQkv raw, const __bf16 *k16,
     const __bf16 *v16, const uint8_t *__restrict__ k8, const uint8_t *__restrict__ v8, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table, int tbl_stride, int T, int Hq, int Hkv, int C,
     int n_splits, float scale_log2e, __bf16 *__restrict__ out, float *__restrict__ part_o, float *__restrict__ part_ml) {
-  using L = Lds<D, FMT, NR>;
-  constexpr int KS = D / 32, DB = D / 16;
+  using L = Lds<D, FMT, NR, TWO>;
+  constexpr int KS = D / 32, DB = D / 16, NSTG = L::NSTG;
   __shared__ __align__(16) char lds[L::BYTES];
   const int split = blockIdx.x % n_splits, bg = blockIdx.x / n_splits, gkv = bg % Hkv, b = bg / Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6), l16 = lane & 15, g = lane >> 4;
@@ -156,19 +159,27 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
   const bool fresh_mine = with_fresh && wave * 16 < T;
   int my_i[NR];
   bf16x8 q[NR][KS], kf[KS];
-  RawRow<D> rq[NR], rk;
+  RawRow<D> rq[TWO ? 1 : NR], rk;   // (TWO: one row block at a time, the others behind the first tiles: half the registers)
   f32x4 rv[2];       // (RAW) sums and bias of 8 elements of a fresh V row: the first of this thread's units (row, 8 elements)
   bf16x8 rv_bias;
   int app_slot = -1, app_have = 0;
   constexpr int VPR = D / 8;
   const float *const row0 = raw.sums + (size_t)b * T * F;
   const int v_at = (Hq + Hkv + gkv) * D;
+  auto load_q = [&](RawRow<D> &x, int r) __attribute__((always_inline)) {
+    const int head = gkv * G + min(r * 16 + l16, R - 1) / T;
+    x.load(row0 + (size_t)my_i[r] * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.q_norm, raw.rope, trow[1] + my_i[r], g);
+  };
+  auto load_k = [&](RawRow<D> &x) __attribute__((always_inline)) {
+    const int t = min(wave * 16 + l16, T - 1), head = Hq + gkv;
+    x.load(row0 + (size_t)t * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.k_norm, raw.rope, trow[1] + t, g);
+  };
 #pragma unroll
   for (int r = 0; r < NR; ++r) {
     const int row = min(r * 16 + l16, R - 1), hg = row / T, head = gkv * G + hg;
     my_i[r] = row - hg * T;
     if constexpr (RAW) {
-      rq[r].load(row0 + (size_t)my_i[r] * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.q_norm, raw.rope, trow[1] + my_i[r], g);
+      if (!TWO || r == 0) load_q(rq[TWO ? 0 : r], r);
     } else {
       const __bf16 *p = Q + (((size_t)b * Hq + head) * T + my_i[r]) * D + g * 8;
 #pragma unroll
@@ -176,19 +187,19 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     }
   }
   if (with_fresh) {
-    const int t = min(wave * 16 + l16, T - 1), head = Hq + gkv;
     if constexpr (RAW) {
-      rk.load(row0 + (size_t)t * F + head * D, raw.ex.bias ? raw.ex.bias + head * D : nullptr, raw.ex.k_norm, raw.rope, trow[1] + t, g);
+      if (!TWO) load_k(rk);
       const int u = min(tid, T * VPR - 1);
       const float *p = row0 + (size_t)(u / VPR) * F + v_at + u % VPR * 8;
-      rv[0] = *(const f32x4 *)p;
-      rv[1] = *(const f32x4 *)(p + 4);
-      if (raw.ex.bias) rv_bias = *(const bf16x8 *)(raw.ex.bias + v_at + u % VPR * 8);
+      if (!TWO) rv[0] = *(const f32x4 *)p;
+      if (!TWO) rv[1] = *(const f32x4 *)(p + 4);
+      if (!TWO && raw.ex.bias) rv_bias = *(const bf16x8 *)(raw.ex.bias + v_at + u % VPR * 8);
       if (raw.append) {
         app_slot = raw.append[2 * b];
         app_have = raw.append[2 * b + 1];
       }
     } else if (fresh_mine) {
+      const int t = min(wave * 16 + l16, T - 1);
       const __bf16 *p = Kf + (((size_t)b * Hkv + gkv) * T + t) * D + g * 8;
 #pragma unroll
       for (int ks = 0; ks < KS; ++ks) kf[ks] = *(const bf16x8 *)(p + ks * 32);
@@ -387,8 +398,20 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
     if (k < n) request(k);
   if constexpr (RAW) {
 #pragma unroll
-    for (int r = 0; r < NR; ++r) rq[r].finish(raw.ex.bias, raw.ex.q_norm, raw.ex.eps, q[r]);
-    if (with_fresh) rk.finish(raw.ex.bias, raw.ex.k_norm, raw.ex.eps, kf);
+    for (int r = 0; r < NR; ++r) {
+      if (TWO && r > 0) {
+        asm volatile("" ::: "memory");   // (one row block in registers at a time)
+        load_q(rq[0], r);
+      }
+      rq[TWO ? 0 : r].finish(raw.ex.bias, raw.ex.q_norm, raw.ex.eps, q[r]);
+    }
+    if (with_fresh) {
+      if (TWO) {
+        asm volatile("" ::: "memory");
+        load_k(rk);
+      }
+      rk.finish(raw.ex.bias, raw.ex.k_norm, raw.ex.eps, kf);
+    }
   }
 #pragma unroll
   for (int r = 0; r < NR; ++r)
@@ -462,7 +485,7 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
       const int t = u / VPR, dv = u - t * VPR;
       bf16x8 v;
       if constexpr (RAW) {
-        if (u != tid) {
+        if (TWO || u != tid) {
           const float *p = row0 + (size_t)t * F + v_at + dv * 8;
           rv[0] = *(const f32x4 *)p;
           rv[1] = *(const f32x4 *)(p + 4);
@@ -561,11 +584,12 @@ __global__ __launch_bounds__(256) void decode_attention_kernel(
 
 namespace pc {
 
-// Partitions of the key axis: two tiles per workgroup while the whole call then fits one workgroup per CU, else as many as
-// make whole rounds of them.
-static int decode_splits(int n_cu, long base_wgs, int tiles, int cap) {
+// Partitions of the key axis: two tiles per workgroup while the whole call then fits one workgroup per CU (finer ones cost the
+// merge more than they give: one query over 64 8-bit tiles of a 3B-shaped layer, 61 us in 33 partitions, 58 in 16), else as many
+// as make whole rounds of the `slots` workgroups that the chip holds at once.
+static int decode_splits(int n_cu, int slots, long base_wgs, int tiles, int cap) {
   const long ns = (tiles + 3) / 2;  // (the fresh keys make a partition of their own then)
-  if (base_wgs * ns > n_cu) return choose_splits(n_cu, base_wgs, tiles + 2, cap);
+  if (base_wgs * ns > n_cu) return choose_splits(slots, base_wgs, tiles + 2, cap);
   return (int)(ns > cap ? cap : ns);
 }
 
@@ -580,17 +604,29 @@ pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q,
   const size_t sc = (size_t)layer * ctx->n_slots8 * c.n_kv_heads * (c.slot_capacity / TK);
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)c.head_dim);
   const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
-  if (n_splits <= 0) n_splits = decode_splits(ctx->n_cu, (long)batch * c.n_kv_heads, tiles, cap);
+  // Two workgroups share a CU except over bf16 slots at D = 128, whose ring alone takes 128 KB.  The resident workgroups are what
+  // keeps the stream of codes busy: 8 queries x 8 kv heads x 256 tiles of 8-bit slots 87 us with one per CU, 53 with two (3 rows;
+  // 24 rows 107 | 64), of mixed slots 87 | 70 (104 | 79).
+  const long base = (long)batch * c.n_kv_heads;
+  const int slots = c.head_dim == 128 && fmt == 0 ? ctx->n_cu : 2 * ctx->n_cu;
+  if (n_splits <= 0) n_splits = decode_splits(ctx->n_cu, slots, base, tiles, cap);
   if (n_splits > cap) n_splits = cap;
-  const dim3 grid((unsigned)(batch * c.n_kv_heads * n_splits));
+  const dim3 grid((unsigned)(base * n_splits));
+  // the form that lets a second workgroup in, where the usual one does not (rings of mixed tiles, two row blocks finished at
+  // once) and there is a second one: it asks for less ahead, which a call of few tiles would wait out
+  const bool two = c.head_dim == 128 && base * n_splits > ctx->n_cu && (fmt == 2 || (fmt == 1 && raw && R > 16));
   const RawQkv rq = raw ? *raw : RawQkv{};
-#define PC_DEC(DD, FF, RR, WW)                                                                                                      \
-  hipLaunchKernelGGL((decode_attention_kernel<DD, FF, RR, WW>), grid, dim3(64 * NW), 0, stream, q, kf, vf, rq, k16, v16, k8, v8, ctx->k_scale + sc, \
+#define PC_DEC(DD, FF, RR, WW, TT)                                                                                                      \
+  hipLaunchKernelGGL((decode_attention_kernel<DD, FF, RR, WW, TT>), grid, dim3(64 * NW), 0, stream, q, kf, vf, rq, k16, v16, k8, v8, ctx->k_scale + sc, \
                      ctx->v_scale + sc, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits,        \
                      scale_log2e, out, part_o, part_ml)
-#define PC_DEC_F(DD, RR, WW)                                                                                     \
-  do {                                                                                                          \
-    if (fmt == 0) PC_DEC(DD, 0, RR, WW); else if (fmt == 1) PC_DEC(DD, 1, RR, WW); else PC_DEC(DD, 2, RR, WW);   \
+#define PC_DEC_F(DD, RR, WW)                                                                                                             \
+  do {                                                                                                                                   \
+    if constexpr (DD == 128) {                                                                                                            \
+      if (two && fmt == 2) { PC_DEC(DD, 2, RR, WW, true); break; }                                                                        \
+      if constexpr (RR == 2 && WW) { if (two) { PC_DEC(DD, 1, RR, WW, true); break; } }                                                         \
+    }                                                                                                                                    \
+    if (fmt == 0) PC_DEC(DD, 0, RR, WW, false); else if (fmt == 1) PC_DEC(DD, 1, RR, WW, false); else PC_DEC(DD, 2, RR, WW, false);       \
   } while (0)
 #define PC_DEC_D(DD)                                                                                \
   do {                                                                                              \

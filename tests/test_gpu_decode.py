@@ -223,3 +223,32 @@ def test_partitions_cost_no_precision(D, G, T, tiles):
     assert not torch.equal(auto, one)                 # (the library does cut these)
     assert e_auto <= 1.06 * e_one, (e_auto, e_one)
     pc.close()
+
+
+@pytest.mark.parametrize("slots,T", [("8bit", 1), ("8bit", 24), ("mixed", 1), ("mixed", 24), ("mixed", 32)])
+def test_long_calls_with_two_workgroups_per_cu(slots, T):
+    """More workgroups than CUs over 8-bit and mixed slots: rings of two stages, row blocks finished one after the other behind
+    the first tiles, ragged chunks (64 kv heads, partitions of 4 and 5 tiles)."""
+    g = np.random.default_rng(7800 + T)
+    Hkv, D, H, C, n_chunks = 64, 128, 128, 128, 12
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=n_chunks // 2)
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hkv, n_kv_heads=Hkv, head_dim=D, n_slots=n_chunks, slot_capacity=C,
+                  max_pos=n_chunks * C + T, device=DEV, **kind)
+    ids = g.permutation(n_chunks).astype(np.int32)[None]
+    used = np.where(np.arange(n_chunks) % 5 == 4, 1, g.integers(65, C + 1, n_chunks)).astype(np.int32)[None]
+    for s in range(n_chunks):
+        pc.percache_kv_put(0, s, bf16(g.standard_normal((Hkv, C, D))), bf16(g.standard_normal((Hkv, C, D))))
+    W = wl.round_bf16(g.standard_normal((3 * Hkv * D, H)).astype(np.float32) * np.float32(0.1))
+    X = wl.round_bf16(g.standard_normal((1, T, H)).astype(np.float32))
+    kf, vf = (torch.empty((1, Hkv, T, D), dtype=torch.bfloat16, device=DEV) for _ in range(2))
+    fused = pc.percache_prefill_reuse(0, bf16(X), bf16(W), ids, used, k_fresh_out=kf, v_fresh_out=vf)
+    q, k1, v1 = pc.percache_qkv_rope(0, bf16(X), bf16(W), ids, used)
+    alone = pc.percache_attention_reuse(0, q, k1, v1, ids, used)
+    torch.cuda.synchronize()
+    sk, sv = (np.stack(x) for x in zip(*[[host(t) for t in pc.percache_kv_get(0, int(s))] for s in ids[0]]))
+    ref, _, _, _ = oracle.prefill_reuse(X[0], W, Hkv, Hkv, D, 10000.0, sk, sv, np.arange(n_chunks, dtype=np.int32), used[0])
+    check_close(host(fused[0]), ref, f"fused {slots} T={T}")
+    check_close(host(alone[0]), ref, f"attention alone {slots} T={T}")
+    for got, want in ((kf, k1), (vf, v1)):   # (the same fp32 sums, taken in another order over the slices)
+        assert np.abs(host(got) - host(want)).max() <= 2.0 ** -7 * np.abs(host(want)).max()
+    pc.close()
