@@ -192,9 +192,10 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
                            const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int max_tiles,
                            int n_splits, __bf16 *out, void *part_o, float *part_ml, hipStream_t stream, int formats,
                            int *left_splits = nullptr);
-// The first of its two launches where decode_rows; tiles: cached tiles of the shortest query.  n_splits <= 0: chosen here.
+// The first of its two launches where decode_rows; tiles: cached tiles of the shortest query.  n_splits <= 0: chosen here
+// (merged_apart: a launch of its own merges the partials, not the o_proj).
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
-                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, __bf16 *out, float *part_o,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, bool merged_apart, __bf16 *out, float *part_o,
                                   float *part_ml, hipStream_t stream, int formats);
 // Number of key-axis partitions that fills `slots` resident workgroups best (at least 4 tiles in each).
 int choose_splits(int slots, long base_wgs, int min_tiles, int cap);

@@ -1559,7 +1559,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     float *part_o = (float *)part_dev;
     prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
     const pc_status st = launch_decode_attention(ctx, layer, q, kf, vf, raw, batch, t_fresh, table_dev, tbl_stride,
-                                                 min_tiles - (t_fresh + TK - 1) / TK, n_splits, out, part_o, part_ml, stream, formats);
+                                                 min_tiles - (t_fresh + TK - 1) / TK, n_splits, !left_splits, out, part_o, part_ml, stream, formats);
     if (st != PC_OK) return st;
     prof_end(ctx, PC_KERNEL_ATTENTION, stream);
     if (left_splits) {
