@@ -541,7 +541,9 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
   hipStream_t s = (hipStream_t)stream;
   // a decoding step of few rows: the attention kernel finishes q, k and v from the projection's sums and appends the fresh
   // K/V to bf16 slots itself; (slot, tokens it holds) of every query go to the device behind the chunk lists
-  const bool decode = pc::decode_rows(c, t_fresh), raw_qkv = decode && pc::few_rows(c, M);
+  const bool decode = pc::decode_rows(c, t_fresh);
+  bool raw_qkv = decode;  // (the sums of every layer)
+  for (int l = 0; l < n_layers; ++l) raw_qkv = raw_qkv && pc::few_rows_qkv(ctx, M, layers_host[l].q_norm || layers_host[l].k_norm);
   bool append_kernel = append_slots_host != nullptr;  // some append is left to a kernel of its own
   if (raw_qkv && append_slots_host && !table_dev) {
     append_kernel = false;
@@ -566,14 +568,14 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     const percache_block_weights &w = layers_host[l];
 #define PC_TRY(call) do { st = (call); if (st != PC_OK) return st; } while (0)
     // few token rows: one launch per projection, the RMSNorms folded into the projections behind them
-    const bool few = pc::few_rows(c, M);
-    if (!few) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
+    const bool few = pc::few_rows(c, M), few_qkv = pc::few_rows_qkv(ctx, M, w.q_norm || w.k_norm);
+    if (!few_qkv) PC_TRY(launch_rmsnorm(ctx, h_cur, (const __bf16 *)w.gain1, ws.normed, (int)M, H, eps, s));
     pc::QkvExtras extras;
     extras.bias = (const __bf16 *)w.qkv_bias;
     extras.q_norm = (const __bf16 *)w.q_norm;
     extras.k_norm = (const __bf16 *)w.k_norm;
     extras.eps = eps;
-    extras.pre_norm = few ? (const __bf16 *)w.gain1 : nullptr;
+    extras.pre_norm = few_qkv ? (const __bf16 *)w.gain1 : nullptr;
     pc::RawQkv raw;
     int left_splits = 1;  // partials that the attention left for the o_proj to merge
     if (raw_qkv) {
@@ -588,7 +590,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
       PC_TRY(pc::launch_qkv_raw(ctx, h_cur, (const __bf16 *)w.wqkv, (int)M, extras, ws.pf.qkv_raw, s));
     } else {
       bool v_blocked = decode;  // (in a decoding step nobody reads V as blocks)
-      PC_TRY(pc::launch_qkv_rope(ctx, few ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
+      PC_TRY(pc::launch_qkv_rope(ctx, few_qkv ? h_cur : ws.normed, (const __bf16 *)w.wqkv, batch, t_fresh, ws.pf.table, stride, ws.pf.q, ws.pf.k,
                                  ws.pf.v, s, extras, decode ? nullptr : ws.pf.v_blk, decode ? nullptr : &v_blocked, ws.pf.qkv_raw));
       if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
     }
@@ -609,14 +611,17 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     if (few) {
       if (left_splits > 1) PC_TRY(launch_oproj_merge(ctx, (const float *)ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
       else PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
-      PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
-      PC_TRY(launch_residual_few(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
     } else {
       PC_TRY(launch_linear_residual(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
+    }
+    if (few && pc::few::pays(ctx->n_cu, M, 2 * ffn / 16, 2, 16)) {
+      PC_TRY(launch_swiglu_few(ctx, ws.mid, (const __bf16 *)w.gain2, eps, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
+    } else {
       PC_TRY(launch_rmsnorm(ctx, ws.mid, (const __bf16 *)w.gain2, ws.normed, (int)M, H, eps, s));
       PC_TRY(launch_linear_swiglu(ctx, ws.normed, (const __bf16 *)w.w_gate, (const __bf16 *)w.w_up, ws.act, (int)M, ffn, H, s));
-      PC_TRY(launch_linear_residual(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
     }
+    if (few) PC_TRY(launch_residual_few(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
+    else PC_TRY(launch_linear_residual(ctx, ws.act, (const __bf16 *)w.w_down, ws.mid, h_out, (int)M, H, ffn, s));
 #undef PC_TRY
     h_cur = h_out;
   }

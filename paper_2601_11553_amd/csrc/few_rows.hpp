@@ -200,19 +200,26 @@ inline unsigned grid_of(int n_wt, int n_tt) { return (unsigned)((n_wt + 7) / 8 *
 // smallest NF.  The candidates are the tiles the kernels are instantiated for; a tie takes the first.
 struct Choice {
   int nf, nt;
+  long cost;
 };
 inline Choice choose_tile(int n_cu, int M, int n16, int min_nf) {
-  static const Choice cand[] = {{1, 1}, {1, 2}, {2, 1}, {2, 2}, {2, 4}, {4, 4}};
-  Choice best{0, 0};
-  long best_cost = 0;
+  static const Choice cand[] = {{1, 1, 0}, {1, 2, 0}, {2, 1, 0}, {2, 2, 0}, {2, 4, 0}, {4, 4, 0}};
+  Choice best{0, 0, 0};
   for (const Choice &c : cand) {
     if (c.nf < min_nf || n16 % c.nf) continue;
     const long tiles = (long)(n16 / c.nf) * ((M + 16 * c.nt - 1) / (16 * c.nt));
     const long cost = (tiles + n_cu - 1) / n_cu * (c.nf + c.nt);
-    if (!best.nf || cost < best_cost) { best = c; best_cost = cost; }
+    if (!best.nf || cost < best.cost) best = Choice{c.nf, c.nt, cost};
   }
   return best;
 }
+// Whether a projection with a norm in front (or none) is faster here than on the 128-row tiles behind a norm kernel: these read
+// 64 rows of weights and of tokens per workgroup and round, so beyond two rounds of the largest tile (cost 16) the 128-row
+// tiles win.  us at width 1024: gate and up projections of ffn 3072 20 in two rounds (320 rows), 29 in three (512), 55 in six (1000)
+// against 14 to 21 and 5 for the norm; QKV of 4096 features 13 | 21 | 30 in one, two, three rounds (256, 512, 640 rows) against 17
+// and 5; width 3072, 200 rows: gate and up (four rounds) 75 against 49 and 6, QKV (two) 38 against 49 and 6.  Up to 128 rows a
+// token tile of the other kernels is mostly padding.
+inline bool pays(int n_cu, long M, int n16, int min_nf, long max_cost) { return M <= 128 || choose_tile(n_cu, (int)M, n16, min_nf).cost <= max_cost; }
 // wavefronts and stages of a tile: what fits beside a second workgroup on the CU at one token block, else one per CU
 template <int NF, int NT>
 struct Form {

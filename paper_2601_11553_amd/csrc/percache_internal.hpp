@@ -154,13 +154,14 @@ void prof_end(percache_ctx *ctx, int kind, hipStream_t stream);
 // dimension of every q / k head with gains [D] before RoPE.  Null pointers switch a part off.
 struct QkvExtras {
   const __bf16 *bias = nullptr, *q_norm = nullptr, *k_norm = nullptr;
-  const __bf16 *pre_norm = nullptr;  // gain of an RMSNorm of the input rows (few token rows only; else they come normed)
+  const __bf16 *pre_norm = nullptr;  // gain of an RMSNorm of the input rows (few_rows_qkv only; else they come normed)
   float eps = 1e-6f;
   bool any() const { return bias || q_norm || k_norm; }
 };
-// Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in.  Where the line
-// lies (us per layer without attention's cached part, these kernels | the 128-row tiles): width 1024: 55 | 138 at 200 rows, 77 |
-// 139 at 512, 132 | 158 at 1024, 267 | 181 at 2048; width 3072: 175 | 285 at 200, 195 | 286 at 320, 287 | 289 at 400.
+// Few token rows take the kernels of few_rows.hpp, in which the RMSNorm in front of a projection is folded in: o_proj and down
+// projection all of them, QKV (few_rows_qkv) and gate / up where that pays (few::pays).  Where the line of the former lies, us
+// against the 128-row tiles: width 1024, ffn 3072: 8 | 35 at 200 rows, 11 | 38 at 512, 16 | 38 at 1000; width 3072: 37 | 112 at 200
+// rows, 34 | 113 at 320.
 inline bool few_rows(const percache_config &c, long M) { return M <= 192 || (M <= 1024 && M * c.hidden <= 1 << 20); }
 // The projection of few token rows as fp32 sums [M][(Hq + 2 Hkv) * D], before bias, head norm and RoPE: what the attention
 // kernel of a decoding step starts from (it finishes q, k and v itself, see decode_attention.hip).
@@ -172,9 +173,11 @@ struct RawQkv {
   const int32_t *append = nullptr;                // per query (slot, tokens it holds), slot < 0: none; bf16 slots only
   __bf16 *k_slots = nullptr, *v_slots = nullptr;  // the layer's bf16 store
 };
+// Whether the QKV projection of M rows takes those kernels (head_norm: with an RMSNorm over the heads of q or k).
+bool few_rows_qkv(const percache_ctx *ctx, long M, bool head_norm);
 pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream);
 // v_blk / v_blk_done: if given, the launch may also write V as the 64-key blocks of launch_v_repack and says so.
-// extras.pre_norm only where few_rows(batch * t_fresh); raw: workspace of that case (M rows of fp32 sums) for a head norm.
+// extras.pre_norm only where few_rows_qkv; raw: workspace of that case (M rows of fp32 sums) for a head norm.
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
                           const int32_t *table_dev, int tbl_stride, __bf16 *q, __bf16 *k, __bf16 *v,
                           hipStream_t stream, const QkvExtras &extras = QkvExtras(), __bf16 *v_blk = nullptr,

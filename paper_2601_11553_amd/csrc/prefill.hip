@@ -129,7 +129,7 @@ static pc_status run_prefill(percache_ctx *ctx, int32_t layer, const void *x_fre
   __bf16 *vf = v_fresh_out_dev ? (__bf16 *)v_fresh_out_dev : p.ws.v;
   const bool decode = pc::decode_rows(ctx->cfg, t_fresh);  // (then nobody reads V as blocks)
   const int formats = pc::table_formats(rows, p.tbl_stride, batch);
-  if (decode && pc::few_rows(ctx->cfg, (long)batch * t_fresh)) {
+  if (decode && pc::few_rows_qkv(ctx, (long)batch * t_fresh, false)) {
     pc::RawQkv raw;
     raw.sums = p.ws.qkv_raw;
     raw.rope = (const float2 *)ctx->rope;

@@ -401,6 +401,14 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void qkv_raw_few_
 
 namespace pc {
 
+// With a head norm finish_rope_kernel comes on top, which at width 1024 the second round no longer pays for (4096 features, us:
+// 11 and 6 at 256 rows, 20 and 9 at 512, against 17 and 5 for the norm in front); from width 1536 on it does (2048 features, 640
+// rows: 24 and 6 against 28 and 5).
+bool few_rows_qkv(const percache_ctx *ctx, long M, bool head_norm) {
+  const percache_config &c = ctx->cfg;
+  return few_rows(c, M) && few::pays(ctx->n_cu, M, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim / 16, 1, head_norm && c.hidden < 1536 ? 8 : 16);
+}
+
 pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
   const int N = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, K = c.hidden;
@@ -433,7 +441,7 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
   if ((long)F * c.hidden >= (1L << 31) || (long)M * c.hidden >= (1L << 31))
     return fail(ctx, PC_ESHAPE, "operand larger than 2^31 elements");
   const float2 *rope = (const float2 *)ctx->rope;
-  if (few_rows(c, M)) {
+  if (few_rows_qkv(ctx, M, extras.q_norm || extras.k_norm)) {
     __bf16 *vb = v_blk && v_blk_done ? v_blk : nullptr;
     if (vb) *v_blk_done = true;
     if (extras.q_norm || extras.k_norm) {  // the sums, then one small kernel over whole heads

@@ -318,6 +318,47 @@ def test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which):
         check_hidden(host(h_out[b]), ref, f"few rows D={D} H={H} F={F} B={batch} T={t_fresh} {which} query {b}")
 
 
+@pytest.mark.parametrize("D,heads,H,F,batch,t_fresh,which", [
+    (64, (8, 4), 384, 4160, 1, 193, "norm"),     # gate / up in three rounds of the few-row tiles: the large ones; QKV in one
+    (128, (24, 8), 128, 64, 2, 130, "bias"),     # QKV of 5120 features in two rounds
+    (128, (24, 8), 128, 64, 3, 160, "none"),     # ... in three: the large tiles behind a norm of their own, gate / up not
+    (128, (16, 8), 256, 64, 1, 320, "norm"),     # ... with a head norm in two: the large tiles too
+    (128, (24, 8), 128, 6400, 1, 129, "bias"),   # one row past 128: gate / up in two rounds
+    (128, (24, 8), 128, 11008, 1, 128, "norm"),  # 128 rows: three rounds, few-row tiles all the same
+])
+def test_each_projection_on_its_side_of_the_few_row_line(D, heads, H, F, batch, t_fresh, which):
+    """A layer in which some projections take the few-row tiles, with the norm in front folded in, and others the large ones
+    behind a norm kernel."""
+    test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which)
+
+
+def test_decoding_step_of_many_queries():
+    """520 queries decode at once: the sums of a QKV projection of 5120 features would take three rounds, so q, k and v come
+    finished from the large tiles, and an append launch takes the new K/V (more slots than one of its lists holds)."""
+    D, Hq, Hkv, H, F, C, B = 128, 24, 8, 128, 64, 64, 520
+    W = wl.stack_weights(26, 0, H, Hq, Hkv, D, F)
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=B, slot_capacity=C, max_pos=C, device=DEV)
+    g = np.random.default_rng(26)
+    k, v = (bf16(g.standard_normal((64, Hkv, 37, D))) for _ in range(2))
+    for s0 in range(0, B, 64):
+        n = min(64, B - s0)
+        pc.percache_kv_put_batch(0, list(range(s0, s0 + n)), k[:n], v[:n])
+    x = wl.round_bf16(g.standard_normal((B, 1, H)).astype(np.float32))
+    out = pc.percache_stack_decode(dev_layers([W]), F, EPS, bf16(x), np.arange(B, dtype=np.int32)[:, None], list(range(B)))
+    torch.cuda.synchronize()
+    for b in (0, 1, 63, 64, 130, 319, 511, 519):
+        sk, sv = host(k[b % 64])[None], host(v[b % 64])[None]
+        ref, ks, vs = oracle_block(x[b], W, Hq, Hkv, D, 10000.0, sk, sv, np.zeros(1, np.int32), np.array([37], np.int32))
+        check_hidden(host(out[b]), ref, f"query {b} of {B}")
+        kk, vv = pc.percache_kv_get(0, b)
+        torch.cuda.synchronize()
+        assert pc.percache_kv_len(0, b) == 38 and torch.equal(kk[:, :37], k[b % 64]) and torch.equal(vv[:, :37], v[b % 64])
+        # one rounding of the normed row and one of the result: two steps of 2^-8 of the largest value
+        for got, want in ((host(kk)[:, 37], np.asarray(ks)[:, -1]), (host(vv)[:, 37], np.asarray(vs)[:, -1])):
+            assert np.abs(got - want).max() <= 2.0 ** -6 * np.abs(want).max()
+    pc.close()
+
+
 @pytest.mark.parametrize("H,F,batch,t_fresh", [
     (256, 64, 5, 209),     # 1045 rows: 128-token tiles, the last one of 21 rows, a contraction of one k-step
     (256, 448, 4, 272),    # 1088 rows: half a tile at the end, seven k-steps
