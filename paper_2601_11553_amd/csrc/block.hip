@@ -364,7 +364,7 @@ pc_status launch_residual_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *
   if (c.nf == NF && c.nt == NT)                                                                                               \
   hipLaunchKernelGGL((linear_residual_few_kernel<NF, NT>), dim3(pc::few::grid_of(n_wt, n_tt)), dim3(64 * pc::few::Form<NF, NT>::WV), 0, s, a, w, \
                      res, y, M, N, K, n_wt, n_tt)
-  PC_FEW(1, 1); else PC_FEW(2, 1); else PC_FEW(1, 2); else PC_FEW(2, 2); else PC_FEW(2, 4); else PC_FEW(4, 4);
+  PC_FEW(1, 1); else PC_FEW(2, 1); else PC_FEW(1, 2); else PC_FEW(2, 2); else PC_FEW(2, 3); else PC_FEW(2, 4); else PC_FEW(4, 3); else PC_FEW(4, 4);
 #undef PC_FEW
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
@@ -393,7 +393,7 @@ pc_status launch_swiglu_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *ga
   if (c.nf == NF && c.nt == NT)                                                                                           \
   hipLaunchKernelGGL((swiglu_few_kernel<NF, NT>), dim3(pc::few::grid_of(n_wt, n_tt)), dim3(64 * pc::few::Form<NF, NT>::WV), 0, s, a, gain, eps, \
                      wg, wu, y, M, F, K, n_wt, n_tt)
-  PC_FEW(2, 1); else PC_FEW(2, 2); else PC_FEW(2, 4); else PC_FEW(4, 4);
+  PC_FEW(2, 1); else PC_FEW(2, 2); else PC_FEW(2, 3); else PC_FEW(2, 4); else PC_FEW(4, 3); else PC_FEW(4, 4);
 #undef PC_FEW
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;

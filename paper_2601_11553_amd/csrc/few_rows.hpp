@@ -197,16 +197,18 @@ inline unsigned grid_of(int n_wt, int n_tt) { return (unsigned)((n_wt + 7) / 8 *
 // Tile of a launch over M token rows and n16 blocks of 16 weight rows: (NF, NT) with the least time, taken as rounds of
 // one workgroup per CU times the rows a workgroup reads.  Measured at 128 rows x (N x K): 4096 x 1024 (2,4) 6.2, (4,4)
 // 8.0, (2,2) 8.3, (1,2) 11.9 us -- costs 6, 8, 8, 12; 6144 x 1024 (4,4) 8.4, (2,4) 10.9 -- 8, 12.  min_nf: the caller's
-// smallest NF.  The candidates are the tiles the kernels are instantiated for; a tie takes the first.
+// smallest NF.  The candidates are the tiles the kernels are instantiated for; a tie takes the first.  48-row token tiles save the
+// padding of the 64-row ones at 65 to 96 rows and their like (layer of width 3072 with head norms, 80 rows: 125 us with 64-row tiles,
+// 112 with these); beyond 256 rows there is little of it and they read the weights more often (width 896, 400 rows: 77 | 86).
 struct Choice {
   int nf, nt;
   long cost;
 };
 inline Choice choose_tile(int n_cu, int M, int n16, int min_nf) {
-  static const Choice cand[] = {{1, 1, 0}, {1, 2, 0}, {2, 1, 0}, {2, 2, 0}, {2, 4, 0}, {4, 4, 0}};
+  static const Choice cand[] = {{1, 1, 0}, {1, 2, 0}, {2, 1, 0}, {2, 2, 0}, {2, 3, 0}, {2, 4, 0}, {4, 3, 0}, {4, 4, 0}};
   Choice best{0, 0, 0};
   for (const Choice &c : cand) {
-    if (c.nf < min_nf || n16 % c.nf) continue;
+    if (c.nf < min_nf || n16 % c.nf || (c.nt == 3 && M > 256)) continue;
     const long tiles = (long)(n16 / c.nf) * ((M + 16 * c.nt - 1) / (16 * c.nt));
     const long cost = (tiles + n_cu - 1) / n_cu * (c.nf + c.nt);
     if (!best.nf || cost < best.cost) best = Choice{c.nf, c.nt, cost};

@@ -422,7 +422,7 @@ pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, in
   if (ch.nf == NF && ch.nt == NT) {                                                               \
     if (extras.pre_norm) PC_FEW_K(NF, NT, true); else PC_FEW_K(NF, NT, false);                     \
   }
-  PC_FEW(1, 1) else PC_FEW(2, 1) else PC_FEW(1, 2) else PC_FEW(2, 2) else PC_FEW(2, 4) else PC_FEW(4, 4)
+  PC_FEW(1, 1) else PC_FEW(2, 1) else PC_FEW(1, 2) else PC_FEW(2, 2) else PC_FEW(2, 3) else PC_FEW(2, 4) else PC_FEW(4, 3) else PC_FEW(4, 4)
 #undef PC_FEW
 #undef PC_FEW_K
   prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
@@ -467,7 +467,7 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
   if (ch.nf == NF && ch.nt == NT) {                                                                 \
     if (extras.pre_norm) PC_FEW_K(DD, NF, NT, true); else PC_FEW_K(DD, NF, NT, false);               \
   }
-#define PC_FEW_D(DD) PC_FEW(DD, 1, 1) else PC_FEW(DD, 2, 1) else PC_FEW(DD, 1, 2) else PC_FEW(DD, 2, 2) else PC_FEW(DD, 2, 4) else PC_FEW(DD, 4, 4)
+#define PC_FEW_D(DD) PC_FEW(DD, 1, 1) else PC_FEW(DD, 2, 1) else PC_FEW(DD, 1, 2) else PC_FEW(DD, 2, 2) else PC_FEW(DD, 2, 3) else PC_FEW(DD, 2, 4) else PC_FEW(DD, 4, 3) else PC_FEW(DD, 4, 4)
     if (c.head_dim == 128) { PC_FEW_D(128) } else { PC_FEW_D(64) }
 #undef PC_FEW_D
 #undef PC_FEW

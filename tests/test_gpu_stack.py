@@ -332,6 +332,17 @@ def test_each_projection_on_its_side_of_the_few_row_line(D, heads, H, F, batch, 
     test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which)
 
 
+@pytest.mark.parametrize("D,heads,H,F,batch,t_fresh,which", [
+    (128, (24, 8), 128, 3072, 1, 40, "norm"), (128, (24, 8), 128, 3072, 2, 35, "norm"), (128, (24, 8), 128, 3072, 1, 45, "bias"),
+    (128, (24, 8), 128, 3072, 5, 15, "none"), (64, (48, 16), 128, 3072, 1, 96, "none"), (64, (48, 16), 128, 64, 3, 48, "bias"),
+    (128, (4, 2), 3072, 64, 1, 90, "none"), (128, (4, 2), 3072, 64, 3, 48, "bias"),
+])
+def test_token_tiles_of_48_rows(D, heads, H, F, batch, t_fresh, which):
+    """32 and 64 weight rows x 48 token rows, in QKV (finished and as sums), gate / up and the residual projections: 40, 45 and
+    48 rows in one token tile, 70 to 96 in two, 144 in three, several queries in a tile."""
+    test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which)
+
+
 def test_decoding_step_of_many_queries():
     """520 queries decode at once: the sums of a QKV projection of 5120 features would take three rounds, so q, k and v come
     finished from the large tiles, and an append launch takes the new K/V (more slots than one of its lists holds)."""
