@@ -13,13 +13,27 @@ namespace {
 using pc::kKvTile;
 
 // One launch serves a list of (slot, dense block) pairs.  A dense block is a token range of a dense tensor: head g's token t
-// is row  row0 + g * head_rows + t  of D elements.
+// is row  row0 + g * head_rows + t  of D elements.  Only as many entries are filled in as the launch has (grid z).  The lists are
+// kernel arguments: a call of a few short chunks costs what its launch costs, so chunks that are tensors of their own travel
+// as slot ids alone, and short append lists in 128 bytes (a put of one chunk 8.2 us, host bound; with 1 KB lists copied twice 8.8).
 constexpr int kListMax = 64;
-struct CopyList {
-  int32_t slot[kListMax];   // slot of the format the kernel handles, negative: skip the entry
-  int32_t row0[kListMax];
-  int32_t n_tok[kListMax];
-  int32_t off[kListMax];    // tokens the slot already holds (append; else 0)
+struct Entry {
+  int32_t slot;    // slot of the format the kernel handles, negative: skip the entry
+  int32_t row0;
+  int32_t n_tok;
+  int32_t off;     // tokens the slot already holds (append; else 0)
+};
+struct ChunkList {   // chunks of n_tok tokens, chunk i from row i * row_step on
+  int32_t slots[kListMax];
+  int32_t n_tok, row_step;
+  __host__ __device__ Entry at(int i) const { return {slots[i], i * row_step, n_tok, 0}; }
+  void set_slot(int i, int32_t slot) { slots[i] = slot; }
+};
+template <int N>
+struct PieceList {
+  Entry entry[N];
+  __host__ __device__ Entry at(int i) const { return entry[i]; }
+  void set_slot(int i, int32_t slot) { entry[i].slot = slot; }
 };
 
 // 8 x 8 sixteen-bit elements: out[k] holds element k of in[0..7]
@@ -43,17 +57,18 @@ __device__ __forceinline__ int in_chunk(int e) { return (e & 3) + 8 * (e >> 2); 
 // a 64-key block's chunk x 8 head-dim elements -- and turns it in registers (32 byte permutes).  With 2-byte accesses on the
 // dense (put) or the block (get) side a get of 8 chunks of 1000 tokens, 8 heads of 128, took 21.7 us, a put 13.0 us; now
 // 9.6 us and 9.9 us (6.9 TB/s read and written).
-template <int D, bool kToStore>
+template <int D, bool kToStore, class List>
 __global__ __launch_bounds__(256) void kv_copy_kernel(__bf16 *__restrict__ slot_k, __bf16 *__restrict__ slot_v, __bf16 *__restrict__ dense_k,
-                                                      __bf16 *__restrict__ dense_v, int n_heads, int C, CopyList list, long slot_stride_elems,
+                                                      __bf16 *__restrict__ dense_v, int n_heads, int C, List list, long slot_stride_elems,
                                                       int head_rows) {
   constexpr int UNITS = 2 * (D / 64);  // per tile: K and V halves
-  const int z = blockIdx.z, g = blockIdx.y, slot = list.slot[z], n_tok = list.n_tok[z];
+  const Entry e = list.at(blockIdx.z);
+  const int g = blockIdx.y, slot = e.slot, n_tok = e.n_tok;
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
   if (slot < 0 || t0 >= n_tok) return;  // (an entry of the other slot format: the other launch copies it)
   const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
   const int d0 = (part >> 1) * 64;
-  const size_t drow = (size_t)list.row0[z] + (size_t)g * head_rows + t0;
+  const size_t drow = (size_t)e.row0 + (size_t)g * head_rows + t0;
   const size_t sbase = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
   const int last = n_tok - 1 - t0;  // last token of this tile
   if (!(part & 1)) {  // K: 8 KB of the tile's contiguous run, 1 KB per instruction
@@ -92,10 +107,12 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(__bf16 *__restrict__ slot_
 // all queries of a decoding step).  K: rows copied to their place.  V: every position of the 64-key blocks that receive a
 // token is rewritten from off on -- the new tokens, then zeros, so that the padding of the last block stays finite
 // (masked probabilities multiply it).
+template <class List>
 __global__ __launch_bounds__(256) void kv_append_kernel(__bf16 *__restrict__ k_store, __bf16 *__restrict__ v_store,
                                                         const __bf16 *__restrict__ k_dense, const __bf16 *__restrict__ v_dense,
-                                                        int n_heads, CopyList list, int n_new, int D, int C, long slot_stride_elems) {
-  const int slot = list.slot[blockIdx.y], off = list.off[blockIdx.y];
+                                                        int n_heads, List list, int n_new, int D, int C, long slot_stride_elems) {
+  const Entry ent = list.at(blockIdx.y);
+  const int slot = ent.slot, off = ent.off;
   if (slot < 0) return;
   const long new_head_stride = (long)n_new * D;
   __bf16 *slot_k = k_store + (size_t)slot * slot_stride_elems, *slot_v = v_store + (size_t)slot * slot_stride_elems;
@@ -150,7 +167,7 @@ __device__ __forceinline__ unsigned encode4(float a, float b, float c, float d) 
   return (unsigned)w;
 }
 
-// list.off: the slot already holds that many tokens and the dense tensors are the tokens that follow them (0: a put).  The
+// Entry::off: the slot already holds that many tokens and the dense tensors are the tokens that follow them (0: a put).  The
 // block that was partly filled is then quantised afresh from the values its old tokens read back as plus the new
 // tokens (its exponent is recomputed over all of them; old codes are re-rounded only if the exponent moves); the
 // launch covers the blocks from off / 64 on (of every entry as many as the entry with the most has).
@@ -159,21 +176,22 @@ __device__ __forceinline__ unsigned encode4(float a, float b, float c, float d) 
 // all 64 tokens, 8 x 8 elements a lane (eight 16-byte loads in flight).  V: 8 keys of a chunk of the block rows x 8 head-dim
 // elements, whose codes are turned in registers.  (Codes turned through LDS byte by byte, four loads per lane behind tests:
 // 14.3 us for 8 chunks of 1000 tokens, 8 heads of 128; now 13.2 us.)
-template <int D>
+template <int D, class List>
 __global__ __launch_bounds__(2 * D) void kv_quant_kernel(uint8_t *__restrict__ slot_k, uint8_t *__restrict__ slot_v,
                                                        float *__restrict__ scale_k, float *__restrict__ scale_v,
                                                        const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v,
-                                                       int n_heads, int C, CopyList list, long slot_stride_elems,
+                                                       int n_heads, int C, List list, long slot_stride_elems,
                                                        long scale_slot_stride, int head_rows) {
   constexpr int HALF = D / 64;  // wavefronts of each kind
   __shared__ float red[2 * HALF];
-  const int slot = list.slot[blockIdx.z], off = list.off[blockIdx.z], n_new = list.n_tok[blockIdx.z], n_tok = off + n_new;
+  const Entry ent = list.at(blockIdx.z);
+  const int slot = ent.slot, off = ent.off, n_new = ent.n_tok, n_tok = off + n_new;
   const int blk = blockIdx.x + off / kKvTile, g = blockIdx.y, t0 = blk * kKvTile;
   if (slot < 0 || t0 >= n_tok) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hi = lane >> 3, lo = lane & 7;
   const bool is_v = wave >= HALF;
   const int d = (wave % HALF) * 64 + (is_v ? hi : lo) * 8;  // first of this lane's 8 head-dim elements
-  const size_t dense_at = ((size_t)list.row0[blockIdx.z] + (size_t)g * head_rows) * D + d;
+  const size_t dense_at = ((size_t)ent.row0 + (size_t)g * head_rows) * D + d;
   const size_t slot_at = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
   const size_t sc = (size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + blk;
   const __bf16 *src = (is_v ? dense_v : dense_k) + dense_at;
@@ -246,18 +264,19 @@ __global__ __launch_bounds__(2 * D) void kv_quant_kernel(uint8_t *__restrict__ s
 
 // The values an 8-bit slot holds, as dense bf16 [kv head][token][head_dim]: code * 2^e (exact).  Work split as in
 // kv_copy_kernel: 8 codes per load, the 8 x 8 piece of a V block turned in registers as bf16.
-template <int D>
+template <int D, class List>
 __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restrict__ slot_k, const uint8_t *__restrict__ slot_v,
                                                          const float *__restrict__ scale_k, const float *__restrict__ scale_v,
                                                          __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int n_heads, int C,
-                                                         CopyList list, long slot_stride_elems, long scale_slot_stride, int head_rows) {
+                                                         List list, long slot_stride_elems, long scale_slot_stride, int head_rows) {
   constexpr int UNITS = 2 * (D / 64);
-  const int z = blockIdx.z, g = blockIdx.y, slot = list.slot[z], n_tok = list.n_tok[z];
+  const Entry e = list.at(blockIdx.z);
+  const int g = blockIdx.y, slot = e.slot, n_tok = e.n_tok;
   const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
   if (slot < 0 || t0 >= n_tok) return;
   const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
   const int d0 = (part >> 1) * 64;
-  const size_t drow = (size_t)list.row0[z] + (size_t)g * head_rows + t0;
+  const size_t drow = (size_t)e.row0 + (size_t)g * head_rows + t0;
   const size_t sbase = (size_t)slot * slot_stride_elems + ((size_t)g * C + t0) * D;
   const float scale = (part & 1 ? scale_v : scale_k)[(size_t)slot * scale_slot_stride + (size_t)g * (C / kKvTile) + tile];
   typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
@@ -303,31 +322,23 @@ pc_status check_slot(percache_ctx *ctx, int32_t layer, int32_t slot) {
   return PC_OK;
 }
 
-// Copies between dense tensors and the slots of a list of at most kListMax entries (row0 and n_tok filled in, slot ids of the
-// context).  A list may name slots of both formats: each format gets its own launch, in which the other's entries are
-// marked -1.
-template <bool kToStore>
-pc_status launch_copy(percache_ctx *ctx, int layer, const CopyList &list, int n, void *k_dev, void *v_dev, int head_rows, hipStream_t stream) {
+// Copies between dense tensors and the n slots of a list (slot ids of the context), its longest entry of `longest` tokens.  A list may
+// name slots of both formats: each format gets its own launch, in which the other's entries are marked -1.
+template <bool kToStore, class List>
+pc_status launch_copy(percache_ctx *ctx, int layer, List &list, int n, int longest, void *k_dev, void *v_dev, int head_rows, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
-  CopyList l16 = list, l8 = list;
-  int n16 = 0, n8 = 0, longest = 0;
-  for (int i = 0; i < kListMax; ++i) {
-    const int slot = i < n ? list.slot[i] : -1;
-    const bool is8 = slot >= 0 && ctx->is8(slot);
-    l16.slot[i] = slot >= 0 && !is8 ? slot : -1;
-    l8.slot[i] = is8 ? slot - ctx->n_slots16 : -1;
-    n16 += slot >= 0 && !is8;
-    n8 += is8;
-    if (slot >= 0 && list.n_tok[i] > longest) longest = list.n_tok[i];
-  }
+  int32_t ids[kListMax];
+  int n8 = 0;
+  for (int i = 0; i < n; ++i) n8 += ctx->is8(ids[i] = list.at(i).slot);
   const int tiles = (longest + kKvTile - 1) / kKvTile;
   if (n8) {
+    for (int i = 0; i < n; ++i) list.set_slot(i, ctx->is8(ids[i]) ? ids[i] - ctx->n_slots16 : -1);
     const size_t off = (size_t)layer * ctx->layer_stride8;
     const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
     const size_t sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
 #define PC_KV8(KERNEL, DD, GX, TT)                                                                                                  \
-  hipLaunchKernelGGL((KERNEL<DD>), dim3(GX, c.n_kv_heads, n), dim3(TT), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
-                     ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot,      \
+  hipLaunchKernelGGL((KERNEL<DD, List>), dim3(GX, c.n_kv_heads, n), dim3(TT), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
+                     ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, list, (long)ctx->slot_stride, sc_slot,    \
                      head_rows)
     if (kToStore) {
       if (c.head_dim == 128) PC_KV8(kv_quant_kernel, 128, tiles, 256); else PC_KV8(kv_quant_kernel, 64, tiles, 128);
@@ -337,26 +348,65 @@ pc_status launch_copy(percache_ctx *ctx, int layer, const CopyList &list, int n,
 #undef PC_KV8
     PC_HIP(ctx, hipGetLastError());
   }
-  if (n16) {
+  if (n8 < n) {
+    for (int i = 0; i < n; ++i) list.set_slot(i, ctx->is8(ids[i]) ? -1 : ids[i]);
     const size_t off = (size_t)layer * ctx->layer_stride;
 #define PC_KV16(DD, GX)                                                                                                      \
-  hipLaunchKernelGGL((kv_copy_kernel<DD, kToStore>), dim3(GX, c.n_kv_heads, n), dim3(256), 0, stream, ctx->k_store + off, ctx->v_store + off,       \
-                     (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, l16, (long)ctx->slot_stride, head_rows)
+  hipLaunchKernelGGL((kv_copy_kernel<DD, kToStore, List>), dim3(GX, c.n_kv_heads, n), dim3(256), 0, stream, ctx->k_store + off, ctx->v_store + off,       \
+                     (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, list, (long)ctx->slot_stride, head_rows)
     if (c.head_dim == 128) PC_KV16(128, tiles); else PC_KV16(64, (tiles + 1) / 2);
 #undef PC_KV16
     PC_HIP(ctx, hipGetLastError());
   }
   return PC_OK;
 }
-// The list of n chunks that are tensors of their own, [n][Hkv][n_tokens][D]
-CopyList chunk_list(const percache_ctx *ctx, const int32_t *slots, int n, int n_tokens) {
-  CopyList l{};
+// The n chunks of a list that are tensors of their own, [n][Hkv][n_tokens][D]
+template <bool kToStore>
+pc_status copy_chunks(percache_ctx *ctx, int layer, const int32_t *slots, int n, int n_tokens, void *k_dev, void *v_dev, hipStream_t stream) {
+  ChunkList l;
+  for (int i = 0; i < n; ++i) l.slots[i] = slots[i];
+  l.n_tok = n_tokens;
+  l.row_step = ctx->cfg.n_kv_heads * n_tokens;
+  return launch_copy<kToStore>(ctx, layer, l, n, n_tokens, k_dev, v_dev, n_tokens, stream);
+}
+
+// launch_kv_append for a list of at most N slots
+template <int N>
+pc_status append_list(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v, int n_tokens,
+                      hipStream_t stream) {
+  const percache_config &c = ctx->cfg;
+  const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
+  PieceList<N> l16, l8;
+  int n16 = 0, n8 = 0, blocks8 = 0;
   for (int i = 0; i < n; ++i) {
-    l.slot[i] = slots[i];
-    l.row0[i] = i * ctx->cfg.n_kv_heads * n_tokens;
-    l.n_tok[i] = n_tokens;
+    const int slot = slot_list[i], off = slot < 0 ? 0 : ctx->slot_len[(size_t)layer * c.n_slots + slot];
+    const bool is8 = slot >= 0 && ctx->is8(slot), is16 = slot >= 0 && !is8 && !only_8bit;
+    l8.entry[i] = {is8 ? slot - ctx->n_slots16 : -1, i * c.n_kv_heads * n_tokens, n_tokens, off};
+    l16.entry[i] = {is16 ? slot : -1, 0, 0, off};
+    n8 += is8;
+    n16 += is16;
+    const int blocks = (off + n_tokens + kKvTile - 1) / kKvTile - off / kKvTile;
+    if (is8 && blocks > blocks8) blocks8 = blocks;
   }
-  return l;
+  if (n8) {
+    const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
+    const dim3 grid(blocks8, c.n_kv_heads, n);
+#define PC_APPEND8(DD)                                                                                                                       \
+  hipLaunchKernelGGL((kv_quant_kernel<DD, PieceList<N>>), grid, dim3(2 * DD), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off, \
+                     ctx->v_scale + sc_off, k, v, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot, n_tokens)
+    if (c.head_dim == 128) PC_APPEND8(128); else PC_APPEND8(64);
+#undef PC_APPEND8
+    PC_HIP(ctx, hipGetLastError());
+  }
+  if (n16) {
+    const size_t at = (size_t)layer * ctx->layer_stride;
+    const long work = (long)c.n_kv_heads * c.head_dim * ((n_tokens + kKvTile - 1) / kKvTile + 1) * kKvTile;
+    const long blocks = (work + 255) / 256;
+    hipLaunchKernelGGL((kv_append_kernel<PieceList<N>>), dim3((unsigned)(blocks > 1024 ? 1024 : blocks), n), dim3(256), 0, stream, ctx->k_store + at,
+                       ctx->v_store + at, k, v, c.n_kv_heads, l16, n_tokens, c.head_dim, c.slot_capacity, (long)ctx->slot_stride);
+    PC_HIP(ctx, hipGetLastError());
+  }
+  return PC_OK;
 }
 
 }  // namespace
@@ -365,12 +415,12 @@ namespace pc {
 pc_status launch_kv_slices(percache_ctx *ctx, int layer, const int32_t *slots, const int32_t *bounds, int n_pieces, int batch, const __bf16 *k,
                            const __bf16 *v, int seq_len, hipStream_t stream) {
   const int Hkv = ctx->cfg.n_kv_heads, D = ctx->cfg.head_dim;
-  CopyList l{};
-  int n = 0, first = 0;   // pieces collected, query of the first one (rows are counted from it)
+  PieceList<kListMax> l;
+  int n = 0, first = 0, longest = 0;   // pieces collected, query of the first one (rows are counted from it), tokens of the longest
   auto flush = [&]() {
     const size_t at = (size_t)first * Hkv * seq_len * D;
-    const pc_status st = n ? launch_copy<true>(ctx, layer, l, n, (void *)(k + at), (void *)(v + at), seq_len, stream) : PC_OK;
-    n = 0;
+    const pc_status st = n ? launch_copy<true>(ctx, layer, l, n, longest, (void *)(k + at), (void *)(v + at), seq_len, stream) : PC_OK;
+    n = longest = 0;
     return st;
   };
   for (int b = 0; b < batch; ++b)
@@ -381,57 +431,20 @@ pc_status launch_kv_slices(percache_ctx *ctx, int layer, const int32_t *slots, c
         if (st != PC_OK) return st;
       }
       if (n == 0) first = b;
-      l.slot[n] = slots[(size_t)b * n_pieces + j];
-      l.row0[n] = (b - first) * Hkv * seq_len + bounds[j];
-      l.n_tok[n] = bounds[j + 1] - bounds[j];
-      ++n;
+      const int tokens = bounds[j + 1] - bounds[j];
+      l.entry[n++] = {slots[(size_t)b * n_pieces + j], (b - first) * Hkv * seq_len + bounds[j], tokens, 0};
+      if (tokens > longest) longest = tokens;
     }
   return flush();
 }
 pc_status launch_kv_append(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v,
                            int n_tokens, hipStream_t stream) {
-  const percache_config &c = ctx->cfg;
-  const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile), head_stride = (long)n_tokens * c.head_dim;
+  const size_t per_slot = (size_t)ctx->cfg.n_kv_heads * n_tokens * ctx->cfg.head_dim;
   for (int i0 = 0; i0 < n; i0 += kListMax) {
     const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
-    CopyList l16{}, l8{};
-    int n16 = 0, n8 = 0, blocks8 = 0;
-    for (int i = 0; i < kListMax; ++i) {
-      l16.slot[i] = l8.slot[i] = -1;
-      if (i >= cnt || slot_list[i0 + i] < 0) continue;
-      const int slot = slot_list[i0 + i], off = ctx->slot_len[(size_t)layer * c.n_slots + slot];
-      l16.off[i] = l8.off[i] = off;
-      l8.n_tok[i] = n_tokens;
-      l8.row0[i] = i * c.n_kv_heads * n_tokens;
-      if (ctx->is8(slot)) {
-        l8.slot[i] = slot - ctx->n_slots16;
-        const int blocks = (off + n_tokens + kKvTile - 1) / kKvTile - off / kKvTile;
-        if (blocks > blocks8) blocks8 = blocks;
-        ++n8;
-      } else if (!only_8bit) {
-        l16.slot[i] = slot;
-        ++n16;
-      }
-    }
-    const __bf16 *kd = k + (size_t)i0 * c.n_kv_heads * head_stride, *vd = v + (size_t)i0 * c.n_kv_heads * head_stride;
-    if (n8) {
-      const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
-      const dim3 grid(blocks8, c.n_kv_heads, cnt);
-#define PC_APPEND8(DD)                                                                                                                  \
-  hipLaunchKernelGGL((kv_quant_kernel<DD>), grid, dim3(2 * DD), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off,      \
-                     ctx->v_scale + sc_off, kd, vd, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot, n_tokens)
-      if (c.head_dim == 128) PC_APPEND8(128); else PC_APPEND8(64);
-#undef PC_APPEND8
-      PC_HIP(ctx, hipGetLastError());
-    }
-    if (n16) {
-      const size_t at = (size_t)layer * ctx->layer_stride;
-      const long work = (long)c.n_kv_heads * c.head_dim * ((n_tokens + kKvTile - 1) / kKvTile + 1) * kKvTile;
-      const long blocks = (work + 255) / 256;
-      hipLaunchKernelGGL(kv_append_kernel, dim3((unsigned)(blocks > 1024 ? 1024 : blocks), cnt), dim3(256), 0, stream, ctx->k_store + at, ctx->v_store + at,
-                         kd, vd, c.n_kv_heads, l16, n_tokens, c.head_dim, c.slot_capacity, (long)ctx->slot_stride);
-      PC_HIP(ctx, hipGetLastError());
-    }
+    const pc_status st = cnt <= 8 ? append_list<8>(ctx, layer, slot_list + i0, cnt, only_8bit, k + i0 * per_slot, v + i0 * per_slot, n_tokens, stream)
+                                  : append_list<kListMax>(ctx, layer, slot_list + i0, cnt, only_8bit, k + i0 * per_slot, v + i0 * per_slot, n_tokens, stream);
+    if (st != PC_OK) return st;
   }
   return PC_OK;
 }
@@ -463,7 +476,7 @@ pc_status percache_kv_put(percache_ctx *ctx, int32_t layer, int32_t slot, const 
   if (((uintptr_t)k_dev | (uintptr_t)v_dev) % 16) return pc::fail(ctx, PC_EINVAL, "k_dev / v_dev must be 16-byte aligned");
   const percache_config &c = ctx->cfg;
   if (n_tokens < 1 || n_tokens > c.slot_capacity) return pc::fail(ctx, PC_ELEN, "n_tokens %d outside [1,%d]", n_tokens, c.slot_capacity);
-  st = launch_copy<true>(ctx, layer, chunk_list(ctx, &slot, 1, n_tokens), 1, (void *)k_dev, (void *)v_dev, n_tokens, (hipStream_t)stream);
+  st = copy_chunks<true>(ctx, layer, &slot, 1, n_tokens, (void *)k_dev, (void *)v_dev, (hipStream_t)stream);
   if (st != PC_OK) return st;
   ctx->slot_len[(size_t)layer * c.n_slots + slot] = n_tokens;
   return PC_OK;
@@ -486,8 +499,8 @@ pc_status percache_kv_put_batch(percache_ctx *ctx, int32_t layer, const int32_t 
   const size_t per_chunk = (size_t)c.n_kv_heads * n_tokens * c.head_dim;
   for (int i0 = 0; i0 < n; i0 += kListMax) {
     const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
-    pc_status st = launch_copy<true>(ctx, layer, chunk_list(ctx, slots_host + i0, cnt, n_tokens), cnt, (void *)((const __bf16 *)k_dev + per_chunk * i0),
-                                     (void *)((const __bf16 *)v_dev + per_chunk * i0), n_tokens, (hipStream_t)stream);
+    pc_status st = copy_chunks<true>(ctx, layer, slots_host + i0, cnt, n_tokens, (void *)((const __bf16 *)k_dev + per_chunk * i0),
+                                     (void *)((const __bf16 *)v_dev + per_chunk * i0), (hipStream_t)stream);
     if (st != PC_OK) return st;
   }
   for (int i = 0; i < n; ++i) ctx->slot_len[(size_t)layer * c.n_slots + slots_host[i]] = n_tokens;
@@ -503,7 +516,7 @@ pc_status percache_kv_get(percache_ctx *ctx, int32_t layer, int32_t slot, void *
   const percache_config &c = ctx->cfg;
   int n_tokens = ctx->slot_len[(size_t)layer * c.n_slots + slot];
   if (n_tokens <= 0) return pc::fail(ctx, PC_ESLOT, "slot %d of layer %d is empty", slot, layer);
-  st = launch_copy<false>(ctx, layer, chunk_list(ctx, &slot, 1, n_tokens), 1, k_out_dev, v_out_dev, n_tokens, (hipStream_t)stream);
+  st = copy_chunks<false>(ctx, layer, &slot, 1, n_tokens, k_out_dev, v_out_dev, (hipStream_t)stream);
   if (st != PC_OK) return st;
   if (n_tokens_out_host) *n_tokens_out_host = n_tokens;
   return PC_OK;
@@ -527,8 +540,8 @@ pc_status percache_kv_get_batch(percache_ctx *ctx, int32_t layer, const int32_t 
   const size_t per_chunk = (size_t)c.n_kv_heads * n_tokens * c.head_dim;
   for (int i0 = 0; i0 < n; i0 += kListMax) {
     const int cnt = n - i0 < kListMax ? n - i0 : kListMax;
-    pc_status st = launch_copy<false>(ctx, layer, chunk_list(ctx, slots_host + i0, cnt, n_tokens), cnt, (void *)((__bf16 *)k_out_dev + per_chunk * i0),
-                                      (void *)((__bf16 *)v_out_dev + per_chunk * i0), n_tokens, (hipStream_t)stream);
+    pc_status st = copy_chunks<false>(ctx, layer, slots_host + i0, cnt, n_tokens, (void *)((__bf16 *)k_out_dev + per_chunk * i0),
+                                      (void *)((__bf16 *)v_out_dev + per_chunk * i0), (hipStream_t)stream);
     if (st != PC_OK) return st;
   }
   return PC_OK;
