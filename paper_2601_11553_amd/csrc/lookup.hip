@@ -144,11 +144,10 @@ struct RowScan {
   const float *probe_inv;  // [n_probes] inverse norms of the probes
   const float *kth;        // [N] similarity a new chunk must exceed for row j (the row's current k-th best)
   float *best_sim;         // [N] out: best similarity over all new chunks so far
-  int32_t *best_new;       // [N] out: index of that chunk
+  int32_t *best_new;       // [N] out: index of that chunk, -1 while none has a similarity that is a number
   uint8_t *stale;          // [N] out: best_sim > kth
   int p0;                  // index of this pass's first probe
   int first;               // 1: first pass (outputs are overwritten), 0: merged with the previous passes
-  int padded;              // probes of the pass rounded up to whole tiles (of a row of NaN similarities the first padding probe wins)
 };
 
 template <int NPB, int CHB, int NSTG, int K>
@@ -271,9 +270,9 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
       for (int pb = 0; pb < NPB; ++pb)
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const float c = pinv[pb][e] == -INFINITY ? -INFINITY : acc[pb][e] * inv * pinv[pb][e];
+          const float c = acc[pb][e] * inv * pinv[pb][e];
           const int p = rs.p0 + pb * 16 + g * 4 + e;
-          if (better(c, p, s, pi)) { s = c; pi = p; }
+          if (pinv[pb][e] != -INFINITY && better(c, p, s, pi)) { s = c; pi = p; }  // (a padding probe is no candidate, nor is a NaN)
         }
 #pragma unroll
       for (int o = 16; o < 64; o <<= 1) {
@@ -284,7 +283,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
       if (row < N && g == 0) {
         if (!rs.first && !better(s, pi, rs.best_sim[row], rs.best_new[row])) { s = rs.best_sim[row]; pi = rs.best_new[row]; }
         rs.best_sim[row] = s;
-        rs.best_new[row] = pi;
+        rs.best_new[row] = pi == INT_MAX ? -1 : pi;
         rs.stale[row] = s > rs.kth[row] ? 1 : 0;
       }
     }
@@ -802,7 +801,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
       if (!better(b.s, b.idx, o.s, o.idx)) b = o;
     }
     rs.best_sim[row] = b.s;
-    rs.best_new[row] = b.idx;
+    rs.best_new[row] = b.idx == INT_MAX ? -1 : b.idx;
     rs.stale[row] = b.s > kth_lds[(rb - rb_begin) * 32 + l32] ? 1 : 0;
   };
   if (K == 0 && idle && g2 == 0) cand[wave * 32 + l32] = cand[(4 + wave) * 32 + l32] = Best{-INFINITY, INT_MAX};
@@ -865,8 +864,8 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
           const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
-          const float s = pinv[r] == -INFINITY ? -INFINITY : (acc[0][r] + acc[1][r]) * inv * pinv[r];
-          if (better(s, rs.p0 + p, b.s, b.idx) && p < rs.padded) b = Best{s, rs.p0 + p};
+          const float s = (acc[0][r] + acc[1][r]) * inv * pinv[r];
+          if (pinv[r] != -INFINITY && better(s, rs.p0 + p, b.s, b.idx)) b = Best{s, rs.p0 + p};
         }
         const Best o{__shfl_xor(b.s, 32, 64), __shfl_xor(b.idx, 32, 64)};
         if (better(o.s, o.idx, b.s, b.idx)) b = o;
@@ -1241,7 +1240,7 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
   // (one kernel for all passes of a call: equal embeddings then have equal sums, and the lower index wins)
   for (; p0 < n_new && scan_in_wide_passes(n_new, d); p0 += kWideProbes) {
     const int np = n_new - p0 < kWideProbes ? n_new - p0 : kWideProbes;
-    const RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0, (np - 1) % 32 < 16 ? (np + 15) / 16 * 16 : (np + 31) / 32 * 32};
+    const RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
     const pc_status ls = launch_scan_wide(ctx, st, N, d, probes + (size_t)p0 * d, np, rs);
     if (ls != PC_OK) return ls;
   }
@@ -1250,7 +1249,7 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
     const int np = n_new - p0 < pass_probes ? n_new - p0 : pass_probes;
     const int npb = np <= 16 ? 1 : 2;
     StreamShape sh = stream_shape(ctx, npb, N);
-    RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0, npb * 16};
+    RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
     pc_status ls = launch_pass<0>(ctx, sh, npb, st, N, d, probes + (size_t)p0 * d, np, nullptr, rs);
     if (ls != PC_OK) return ls;
     PC_HIP(ctx, hipGetLastError());

@@ -353,3 +353,30 @@ def test_refresh_scan_wide_passes(dim, n_new, rows):
         assert o_sim[j] - s[bn[j]] < 2e-5
     margin = np.abs(o_sim - 0.1) > 2e-5
     assert np.array_equal(st[margin], o_stale[margin])
+
+
+@pytest.mark.parametrize("dim,n_new", [(384, 5), (384, 32), (384, 33), (512, 100), (1024, 64), (768, 130), (640, 40), (640, 16)])
+def test_refresh_scan_rows_and_chunks_that_are_not_numbers(dim, n_new):
+    """Bank rows with a NaN or an infinity have no similarity: index -1, similarity -inf, not outdated; a new chunk with a NaN
+    takes no part.  One and several passes, streaming and 128-probe ones, with and without padding probes."""
+    rows = 300
+    g = np.random.default_rng(dim + n_new)
+    bank = wl.round_f16(g.standard_normal((rows, dim)).astype(np.float32))
+    new = wl.round_f16(g.standard_normal((n_new, dim)).astype(np.float32))
+    bad = [0, 17, 130, rows - 1]
+    bank[bad, 3] = [np.nan, np.inf, -np.inf, np.nan]
+    new[2, dim - 1] = np.nan
+    qctx = _ctx(rows, dim)
+    qctx.percache_bank_put(0, f16(bank))
+    best_sim, best_new, stale = qctx.percache_bank_refresh_scan(f16(new), torch.full((rows,), 0.05, device=DEV))
+    torch.cuda.synchronize()
+    bs, bn, st = best_sim.cpu().numpy(), best_new.cpu().numpy(), stale.cpu().numpy()
+    assert (bn[bad] == -1).all() and (bs[bad] == -np.inf).all() and (st[bad] == 0).all()
+    good = np.setdiff1d(np.arange(rows), bad)
+    e, c = bank[good].astype(np.float64), new.astype(np.float64)
+    sims = (e @ c.T) / (np.linalg.norm(e, axis=1)[:, None] * np.linalg.norm(c, axis=1)[None])
+    sims[:, 2] = -np.inf
+    assert np.abs(bs[good] - sims.max(1)).max() < 2e-5
+    assert np.abs(sims[np.arange(len(good)), bn[good]] - sims.max(1)).max() < 2e-5
+    clear = np.abs(sims.max(1) - 0.05) > 2e-5
+    assert np.array_equal(st[good][clear] == 1, sims.max(1)[clear] > 0.05)
