@@ -512,6 +512,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
   const int formats = pc::table_formats(rows, pc::tbl_stride(max_chunks), batch);
   const long M = (long)batch * t_fresh;
   if (M * (long)(ffn > c.hidden ? ffn : c.hidden) >= (1L << 31)) return pc::fail(ctx, PC_ESHAPE, "activation larger than 2^31 elements");
+  if ((long)(c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim * c.hidden >= (1L << 31)) return pc::fail(ctx, PC_ESHAPE, "operand larger than 2^31 elements");
   for (int b = 0; b < batch && n_save > 0; ++b) {
     for (int j = 0; j < n_save; ++j) {
       const int lo = save_bounds_host[j], hi = save_bounds_host[j + 1], slot = save_slots_host[(size_t)b * n_save + j];

@@ -402,3 +402,22 @@ def test_residual_projection_in_one_round(H, F, batch, t_fresh):
     ref = act @ gain("w_down").T + mid
     torch.cuda.synchronize()
     check_hidden(host(h_out).reshape(-1, H), ref.cpu().numpy().reshape(-1, H), f"H={H} F={F} rows={batch * t_fresh}")
+
+
+def test_oversized_projection_is_refused_before_anything_runs():
+    """A QKV weight of 2^31 elements is past what the kernels index: every call that projects refuses it, few rows or many (the
+    pointers here are to a few bytes, nothing may read them)."""
+    H, Hq, Hkv, D = 32768, 480, 16, 128          # (30 query rows per kv head: the decode attention's at one token)
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=1, slot_capacity=64, max_pos=64, device=DEV)
+    stub = torch.zeros(64, dtype=torch.bfloat16, device=DEV)
+    layer = dict(gain1=stub, wqkv=stub, wo=stub, gain2=stub, w_gate=stub, w_up=stub, w_down=stub)
+    for t in (1, 4):
+        x = torch.zeros((1, t, H), dtype=torch.bfloat16, device=DEV)
+        for call in (lambda: pc.percache_stack_reuse([layer], 64, EPS, x),
+                     lambda: pc.percache_stack_decode([layer], 64, EPS, x, np.zeros((1, 0), np.int32), [0]),
+                     lambda: pc.percache_prefill_reuse(0, x, stub)):
+            with pytest.raises(PercacheError) as e:
+                call()
+            assert e.value.status == -2
+    assert pc.percache_kv_len(0, 0) == 0
+    pc.close()
