@@ -125,9 +125,10 @@ struct RawRow {
 // RAW: q and the fresh k, v come as the projection's fp32 sums (raw.sums) and are finished here -- by every workgroup for
 // its query rows, under the latency of its first K/V tiles, and by the one with the fresh keys for k and v, which it also
 // writes: dense (k_out, v_out) and, where the query has a bf16 slot to append to, behind the tokens that slot holds.  The
-// keys of that slot read by this launch are the older ones (lengths come from the chunk list).
+// keys of that slot read by this launch, for this query or another, are the older ones: lengths come from the chunk list, K rows
+// past the end are not read and V positions past it are cleared after the read (compute), which may see the new ones.
 template <int D, int FMT, int NR, bool RAW, bool TWO>
-__global__ __launch_bounds__(256, (FMT == 1 && NR == 1) || TWO ? 2 : 1) void decode_attention_kernel(
+__global__ __launch_bounds__(256, (FMT == 1 && (NR == 1 || !RAW)) || TWO ? 2 : 1) void decode_attention_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf, pc::RawQkv raw, const __bf16 *k16,
     const __bf16 *v16, const uint8_t *__restrict__ k8, const uint8_t *__restrict__ v8, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table, int tbl_stride, int T, int Hq, int Hkv, int C,
@@ -379,6 +380,15 @@ __global__ __launch_bounds__(256, (FMT == 1 && NR == 1) || TWO ? 2 : 1) void dec
       for (int r = 0; r < NR; ++r)
 #pragma unroll
         for (int e = 0; e < 4; ++e) s[r][e] = wave * 16 + g * 4 + e < valid ? s[r][e] : -INFINITY;
+      // the values of keys past the end too: their probabilities are 0, but what stands there need not be finite -- the V of
+      // tokens beyond the used length, or of one that another workgroup of this launch is appending
+      const int left = valid - wave * 16 - g * 4;
+      const uint2 keep = make_uint2((left > 0 ? 0xffffu : 0u) | (left > 1 ? 0xffff0000u : 0u), (left > 2 ? 0xffffu : 0u) | (left > 3 ? 0xffff0000u : 0u));
+#pragma unroll
+      for (int db = 0; db < DB; ++db) {
+        const uint2 w = __builtin_bit_cast(uint2, vop[db]);
+        vop[db] = __builtin_bit_cast(bf16x4, make_uint2(w.x & keep.x, w.y & keep.y));
+      }
     }
     typedef short s16x4 __attribute__((ext_vector_type(4)));
 #pragma unroll

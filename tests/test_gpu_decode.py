@@ -252,3 +252,55 @@ def test_long_calls_with_two_workgroups_per_cu(slots, T):
     for got, want in ((kf, k1), (vf, v1)):   # (the same fp32 sums, taken in another order over the slices)
         assert np.abs(host(got) - host(want)).max() <= 2.0 ** -7 * np.abs(host(want)).max()
     pc.close()
+
+
+@pytest.mark.parametrize("D,G,slots", [(128, 2, "bf16"), (64, 7, "bf16"), (128, 20, "bf16"), (128, 3, "mixed"), (64, 1, "8bit")])
+def test_what_stands_behind_the_used_length_takes_no_part(D, G, slots):
+    """Tokens of a chunk beyond the used length hold infinities and NaN (8-bit slots: NaN codes): the few-row attention over the
+    tokens in front of them is finite and right."""
+    g = np.random.default_rng(7900 + D + G)
+    Hkv, C, H, n_chunks = 2, 128, 128, 4
+    Hq = G * Hkv
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=2) if slots == "mixed" else {}
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=n_chunks, slot_capacity=C, max_pos=n_chunks * C + 1,
+                  device=DEV, **kind)
+    used = np.array([[33, 64, 97, 1]], np.int32)
+    k, v = (wl.round_bf16(g.standard_normal((n_chunks, Hkv, C, D)).astype(np.float32)) for _ in range(2))
+    for s in range(n_chunks):
+        stale = np.arange(C) >= used[0, s]
+        kk, vv = k[s].copy(), v[s].copy()
+        # (a block of an 8-bit slot shares one scale: there only NaN, which leaves the scale alone)
+        kk[:, stale], vv[:, stale] = np.nan, np.nan if slots != "bf16" else np.inf
+        pc.percache_kv_put(0, s, bf16(kk), bf16(vv))
+    q, kf, vf = (bf16(g.standard_normal((1, n, 1, D))) for n in (Hq, Hkv, Hkv))
+    out = pc.percache_attention_reuse(0, q, kf, vf, np.arange(n_chunks, dtype=np.int32)[None], used)
+    torch.cuda.synchronize()
+    got = [pc.percache_kv_get(0, s) for s in range(n_chunks)]
+    ck, cv = (torch.cat([host_t.double().cpu()[:, :used[0, s]] for s, host_t in enumerate(x)] + [f[0].double().cpu()], 1)
+              for x, f in zip(zip(*got), (kf, vf)))
+    p = ((q[0].double().cpu() @ ck.repeat_interleave(G, 0).transpose(1, 2)) / D ** 0.5).softmax(-1)
+    check_close(host(out[0]).reshape(-1), (p @ cv.repeat_interleave(G, 0)).reshape(-1).numpy(), f"D={D} G={G} {slots}")
+    pc.close()
+
+
+def test_a_query_that_appends_what_is_not_a_number_spoils_no_other():
+    """Two queries share a prefix slot in one decoding step; the first appends to it, and its hidden row is infinite: its own
+    output is not a number, the other's is what it is without the first."""
+    D, Hq, Hkv, H, F, C = 128, 4, 2, 128, 64, 128
+    layer = dev_layers([wl.stack_weights(34, 0, H, Hq, Hkv, D, F)])[0]
+    g = np.random.default_rng(8100)
+    k, v = (bf16(g.standard_normal((Hkv, 77, D))) for _ in range(2))
+    x = bf16(g.standard_normal((2, 1, H)))
+    outs = []
+    for bad in (False, True):
+        pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=2, slot_capacity=C, max_pos=C, device=DEV)
+        pc.percache_kv_put(0, 0, k, v)
+        h = x.clone()
+        if bad:
+            h[0] = float("inf")
+        outs.append(pc.percache_stack_decode([layer], F, EPS, h, [[0], [0]], [0, -1]).clone())
+        torch.cuda.synchronize()
+        assert pc.percache_kv_len(0, 0) == 78
+        pc.close()
+    assert not torch.isfinite(outs[1][0]).all()
+    assert torch.equal(outs[0][1], outs[1][1])
