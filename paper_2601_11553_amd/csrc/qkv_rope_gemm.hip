@@ -409,12 +409,12 @@ bool few_rows_qkv(const percache_ctx *ctx, long M, bool head_norm) {
   return few_rows(c, M) && few::pays(ctx->n_cu, M, (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim / 16, 1, head_norm && c.hidden < 1536 ? 8 : 16);
 }
 
-pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream) {
+// (no timing events: the callers bracket the whole projection)
+static pc_status launch_sums(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
   const int N = (c.n_q_heads + 2 * c.n_kv_heads) * c.head_dim, K = c.hidden;
   const few::Choice ch = few::choose_tile(ctx->n_cu, M, N / 16, 1);
   const int n_wt = N / (16 * ch.nf), n_tt = (M + 16 * ch.nt - 1) / (16 * ch.nt);
-  prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
 #define PC_FEW_K(NF, NT, NN)                                                                                                        \
   hipLaunchKernelGGL((qkv_raw_few_kernel<NF, NT, NN>), dim3(few::grid_of(n_wt, n_tt)), dim3(64 * few::Form<NF, NT>::WV), 0, stream, x, w, \
                      extras.pre_norm, extras.eps, sums, M, N, K, n_wt, n_tt)
@@ -425,9 +425,14 @@ pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, in
   PC_FEW(1, 1) else PC_FEW(2, 1) else PC_FEW(1, 2) else PC_FEW(2, 2) else PC_FEW(2, 3) else PC_FEW(2, 4) else PC_FEW(4, 3) else PC_FEW(4, 4)
 #undef PC_FEW
 #undef PC_FEW_K
-  prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
+}
+pc_status launch_qkv_raw(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int M, const QkvExtras &extras, float *sums, hipStream_t stream) {
+  prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
+  const pc_status st = launch_sums(ctx, x, w, M, extras, sums, stream);
+  if (st == PC_OK) prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
+  return st;
 }
 
 pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, int batch, int t_fresh,
@@ -445,7 +450,8 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
     __bf16 *vb = v_blk && v_blk_done ? v_blk : nullptr;
     if (vb) *v_blk_done = true;
     if (extras.q_norm || extras.k_norm) {  // the sums, then one small kernel over whole heads
-      const pc_status st = launch_qkv_raw(ctx, x, w, M, extras, raw, stream);
+      prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
+      const pc_status st = launch_sums(ctx, x, w, M, extras, raw, stream);
       if (st != PC_OK) return st;
       const int rows = vb ? (t_fresh + 63) / 64 * 64 : t_fresh;
       const long threads = (long)batch * rows * (c.n_q_heads + 2 * c.n_kv_heads) * (c.head_dim / 8);
@@ -454,6 +460,7 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
                      c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb)
       if (c.head_dim == 128) PC_FINISH(128); else PC_FINISH(64);
 #undef PC_FINISH
+      prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
       PC_HIP(ctx, hipGetLastError());
       return PC_OK;
     }
