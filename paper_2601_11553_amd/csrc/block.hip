@@ -55,10 +55,10 @@ __global__ __launch_bounds__(256) void rmsnorm_kernel(const __bf16 *__restrict__
 // ---------------------------------------------------------------------------------------------------
 // Y[M, N] = A[M, K] W[N, K]^T + R[M, N]   (o_proj and down projection with the residual add fused)
 // ---------------------------------------------------------------------------------------------------
-template <int NTB>
 __global__ __launch_bounds__(256, 2) void linear_residual_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ W,
                                                                  const __bf16 *__restrict__ R, __bf16 *__restrict__ Y, int M,
                                                                  int N, int K) {
+  constexpr int NTB = 2;
   constexpr int BT = 64 * NTB;
   __shared__ __align__(16) char lds[pc::gemm::Shape<NTB>::LDS_BYTES];
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
@@ -339,10 +339,7 @@ pc_status launch_linear_residual(percache_ctx *ctx, const __bf16 *a, const __bf1
     PC_HIP(ctx, hipGetLastError());
     return PC_OK;
   }
-  const bool big = M > 64 * 3;
-  dim3 grid(N / BF, big ? (M + 127) / 128 : (M + 63) / 64);
-  if (big) hipLaunchKernelGGL(linear_residual_kernel<2>, grid, dim3(256), 0, s, a, w, res, y, M, N, K);
-  else hipLaunchKernelGGL(linear_residual_kernel<1>, grid, dim3(256), 0, s, a, w, res, y, M, N, K);
+  hipLaunchKernelGGL(linear_residual_kernel, dim3(N / BF, (M + 127) / 128), dim3(256), 0, s, a, w, res, y, M, N, K);
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }

@@ -79,8 +79,8 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(unsigned w0, unsigned w1, float 
 // walked in the order  32 j + 16 g2 + 8 jj  (k-step 2 j + jj, lane half g2) by K, Q and the fresh bf16 K alike.
 // The fresh tiles stay bf16.  KV8 kernels run with two stages.
 // KSP = 2: two wavefronts share a 32-row block and take one 32-key block of every tile each (separate running
-// maximum / sum / output, merged through LDS at the end); for the cases with few rows per kv head, where the per-tile
-// chain of one wavefront, not the key stream, would set the pace.
+// maximum / sum / output, merged through LDS at the end); for launches of few workgroups over bf16 slots, where the
+// per-tile chain of one wavefront, not the key stream, would set the pace.
 template <int D, int NW, int NSTAGE, bool KV8 = false, int KSP = 1, bool MIXED = false>
 __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
@@ -98,7 +98,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
   constexpr int NT = 64 * NW;      // threads
   constexpr int QROWS = 32 * NW / KSP;   // query rows per workgroup
   constexpr int NKB = 2 / KSP;           // 32-key blocks of a tile per wavefront
-  static_assert(KSP == 1 || (KSP == 2 && NW % 2 == 0), "key split over one or two wavefronts");
+  static_assert(KSP == 1 || (KSP == 2 && NW % 2 == 0 && !KV8), "key split over one or two wavefronts, bf16 slots");
   constexpr int AHEAD = NSTAGE - 1;  // tiles in flight ahead of the one being computed
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
 
@@ -256,7 +256,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
 #pragma unroll
     for (int j = 0; j < KS / 2; ++j) k8_rd[j] = ((2 * j + g2) ^ swz8(K8_ROW, l32)) * 16;
 #pragma unroll
-    for (int J = 0; J < NKB; ++J) v8_rd[J] = ((2 * (kb0 + J) + g2) ^ swz8(V8_ROW, l32)) * 16;
+    for (int J = 0; J < NKB; ++J) v8_rd[J] = ((2 * J + g2) ^ swz8(V8_ROW, l32)) * 16;
   }
   // is8: the tile holds 8-bit codes (a chunk in an 8-bit slot); fresh tiles and chunks in bf16 slots are bf16 tiles.
   // A context may hold slots of both formats: ids below n_slots16 are bf16 slots of k_store16 / v_store16.
@@ -388,7 +388,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
     for (int kbk = 0; kbk < NKB; ++kbk)
 #pragma unroll
       for (int r = 0; r < 16; ++r) s_acc[kbk][r] = 0.f;
-    const char *kbw = kb + kb0 * 32 * (KV8 && td.is8 ? K8_ROW : L::K_ROW);  // this wavefront's key rows
+    const char *kbw = kb + kb0 * 32 * L::K_ROW;  // this wavefront's key rows
     if (KV8 && td.is8) {
       // 8-bit tile: one 16-byte read per key block and pair of k-steps, turned into two bf16 operands
 #pragma unroll
@@ -1580,7 +1580,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   const bool wide = R > 128 && (long)batch * c.n_kv_heads * ((R + 255) / 256) * 4 >= ctx->n_cu && !(use8 && c.head_dim == 64);
   // few workgroups for the whole chip (one or two short queries): 64-row workgroups whose wavefront pairs halve every
   // tile between them -- twice the workgroups, half the dependent chain per tile
-  const bool halved = !wide && !use8 && c.head_dim == 128 && R > 32 &&
+  const bool halved = !wide && !use8 && c.head_dim == 128 &&
                       (long)batch * c.n_kv_heads * ((R + 63) / 64) * 4 <= ctx->n_cu;
   const int qrows = wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
