@@ -304,3 +304,85 @@ def test_a_query_that_appends_what_is_not_a_number_spoils_no_other():
         pc.close()
     assert not torch.isfinite(outs[1][0]).all()
     assert torch.equal(outs[0][1], outs[1][1])
+
+
+@pytest.mark.parametrize("D,heads,B,T,which,slots", [
+    (128, (16, 8), 2, 1, "qk", "bf16"), (128, (16, 8), 1, 3, "qk bias", "bf16"), (128, (24, 8), 1, 9, "qk bias", "bf16"), (64, (14, 2), 3, 1, "qk bias", "bf16"),
+    (64, (14, 2), 2, 4, "qk", "bf16"), (128, (16, 8), 2, 1, "q", "bf16"), (64, (8, 4), 2, 5, "k bias", "bf16"), (128, (16, 8), 2, 2, "qk bias", "8bit"),
+    (64, (14, 2), 2, 3, "qk", "8bit"), (128, (64, 64), 1, 24, "qk bias", "8bit"), (128, (64, 64), 1, 24, "qk", "mixed"), (128, (64, 64), 1, 2, "qk", "mixed"),
+])
+def test_decoding_step_with_head_norms(D, heads, B, T, which, slots):
+    """q and the fresh k with bias and head norms finished inside the decode attention: one and two row blocks, gains of q or k
+    alone, the forms of long calls (64 kv heads); hidden states and the K/V that were appended, against the oracle's block."""
+    (Hq, Hkv), H, F, C = heads, 128, 64, 64
+    long = heads == (64, 64)
+    n_chunks = 20 if long else 2
+    g = np.random.default_rng(8200 + D + 7 * T + Hq)
+    W = wl.stack_weights(35, 0, H, Hq, Hkv, D, F)
+    W.Wo = W.Wo * np.float32(4)    # (the attention's share of the output: a gain read at the wrong place is off by 4 % or more)
+    layer, extras = dev_layers([W])[0], dict(bias=None, q_gain=None, k_gain=None, eps=EPS)
+    for name, arg in (("q", "q_gain"), ("k", "k_gain")):
+        if name in which.split()[0]:
+            extras[arg] = wl.round_bf16(1 + 0.3 * g.standard_normal(D).astype(np.float32))
+            layer[name + "_norm"] = bf16(extras[arg])
+    if "bias" in which:
+        extras["bias"] = wl.round_bf16(0.5 * g.standard_normal((Hq + 2 * Hkv) * D).astype(np.float32))
+        layer["qkv_bias"] = bf16(extras["bias"])
+    n_slots = B * (n_chunks + 1)
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=n_slots // 2) if slots == "mixed" else {}
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=n_slots, slot_capacity=C,
+                  max_pos=(n_chunks + 1) * C, device=DEV, **kind)
+    chain = np.arange(n_slots, dtype=np.int32).reshape(B, n_chunks + 1)
+    own, have = [int(s) for s in chain[:, -1]], 37
+    for s in chain.reshape(-1):
+        n = have if int(s) in own else C
+        pc.percache_kv_put(0, int(s), bf16(g.standard_normal((Hkv, n, D))), bf16(g.standard_normal((Hkv, n, D)) + 2 * g.standard_normal((Hkv, 1, D))))
+    kept = [[tuple(host(t) for t in pc.percache_kv_get(0, int(s))) for s in row] for row in chain]
+    x = wl.round_bf16(g.standard_normal((B, T, H)).astype(np.float32))
+    out = pc.percache_stack_decode([layer], F, EPS, bf16(x), chain, own)
+    torch.cuda.synchronize()
+    for b in range(B):
+        sk, sv = (np.zeros((n_chunks + 1, Hkv, C, D), np.float32) for _ in range(2))
+        used = np.array([C] * n_chunks + [have], np.int32)
+        for c in range(n_chunks + 1):
+            sk[c, :, :used[c]], sv[c, :, :used[c]] = kept[b][c]
+        ref, k, v = oracle_block(x[b], W, Hq, Hkv, D, 10000.0, sk, sv, np.arange(n_chunks + 1, dtype=np.int32), used, extras=extras)
+        check_hidden(host(out[b]), ref, f"D={D} heads {heads} T={T} {which} {slots} query {b}")
+        assert pc.percache_kv_len(0, own[b]) == have + T
+        is8 = slots == "8bit" or (slots == "mixed" and own[b] >= n_slots - n_slots // 2)
+        for got, want in zip(pc.percache_kv_get(0, own[b]), (k, v)):
+            want = np.asarray(want)[:, -T:]
+            # one rounding of the normed row and one of the result (two steps of 2^-8 of the largest value each way), an 8-bit
+            # code then by at most one step of 1/8
+            assert np.abs(host(got)[:, have:] - want).max() <= (2.0 ** -3 if is8 else 2.0 ** -6) * np.abs(want).max(), (b, is8)
+    pc.close()
+
+
+@pytest.mark.parametrize("B,T,tiles", [(1, 1, 45), (1, 1, 83), (1, 1, 120), (2, 1, 45), (1, 2, 90), (2, 1, 120)])
+def test_o_proj_merges_long_partition_lists(B, T, tiles):
+    """Decoding steps of one and two rows over 45 to 120 cached tiles of two kv heads: the o_proj merges 24 to 61 partitions, 20 a
+    round, with the largest scores in the first, the last and the middle chunks."""
+    D, Hq, Hkv, H, F, C = 128, 16, 2, 256, 64, 320
+    W = wl.stack_weights(36, 0, H, Hq, Hkv, D, F)
+    W.Wo = W.Wo * np.float32(4)     # (the attention's share of the output; with the chunks' mean values below, a chunk left out or
+    n_chunks = -(-tiles * 64 // C)
+    g = np.random.default_rng(8300 + tiles + B)
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=B * n_chunks, slot_capacity=C,
+                  max_pos=n_chunks * C + T, device=DEV)
+    used = np.full((B, n_chunks), C, np.int32)
+    used[:, -1] = tiles * 64 - (n_chunks - 1) * C - 11
+    x = wl.round_bf16(g.standard_normal((B, T, H)).astype(np.float32))
+    for loud in ((0,), (n_chunks - 1,), (n_chunks // 2, 1)):
+        sk, sv = (wl.round_bf16(g.standard_normal((B, n_chunks, Hkv, C, D)).astype(np.float32)) for _ in range(2))
+        sv = wl.round_bf16(sv + 2 * g.standard_normal((B, n_chunks, Hkv, 1, D)).astype(np.float32))   # counted twice is off by 4 % or more)
+        for c in range(n_chunks):
+            sk[:, c] = wl.round_bf16(sk[:, c] * np.float32(2.0 if c in loud else 0.3))
+        for b in range(B):
+            for c in range(n_chunks):
+                pc.percache_kv_put(0, b * n_chunks + c, bf16(sk[b, c]), bf16(sv[b, c]))
+        out = pc.percache_stack_decode(dev_layers([W]), F, EPS, bf16(x), np.arange(B * n_chunks, dtype=np.int32).reshape(B, -1), [-1] * B, used_len=used)
+        torch.cuda.synchronize()
+        for b in range(B):
+            ref, _, _ = oracle_block(x[b], W, Hq, Hkv, D, 10000.0, sk[b], sv[b], np.arange(n_chunks, dtype=np.int32), used[b])
+            check_hidden(host(out[b]), ref, f"{tiles} tiles, loud chunks {loud}, B={B} T={T} query {b}")
+    pc.close()
