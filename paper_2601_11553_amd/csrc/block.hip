@@ -366,12 +366,14 @@ pc_status launch_residual_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
-// Whether the o_proj of M rows merges the attention's partials itself: where a wavefront's share is at most two rounds of its
-// 32 lane pairs (8 rows x steps of 64 columns).  One row of 2048, 20 partitions: 6.4 us against 5.3 + 4.7 for the merge launch
-// and the plain kernel; eight rows of 3072 (twelve rounds): 34.7 against 4.8 + 9.2.
-bool oproj_merges(const percache_config &c, long M) {
+// Up to how many of the attention's partials the o_proj of M rows merges itself (0: none): where a wavefront's share is at most
+// two rounds of its 32 lane pairs (8 rows x steps of 64 columns) and the partials of all of them, which every workgroup reads, at
+// most 80.  Layer of one row of 2048 (4 steps), the o_proj merging | a merge launch of its own, us: 9 partitions 29.4 | 31.7, 20
+// 31.0 | 32.0, 31 32.7 | 32.6; two rows 5 30.0 | 31.2, 11 31.7 | 31.4, 16 33.1 | 32.1; one row of 3072 (6) 14 54.8 | 54.1.  The
+// kernels at 20 partitions: 7.1 against 3.7 + 4.8.
+int oproj_merge_limit(const percache_config &c, long M) {
   const int steps = (c.n_q_heads * c.head_dim + 511) / 512;
-  return steps <= kMergeSteps && M * steps <= 8;
+  return steps <= kMergeSteps && M * steps <= 8 ? (int)(80 / (M * steps)) : 0;
 }
 pc_status launch_oproj_merge(percache_ctx *ctx, const float *part_o, const float *part_ml, int n_splits, int t_fresh, const __bf16 *w,
                              const __bf16 *res, __bf16 *y, int M, hipStream_t s) {
@@ -575,7 +577,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     extras.eps = eps;
     extras.pre_norm = few_qkv ? (const __bf16 *)w.gain1 : nullptr;
     pc::RawQkv raw;
-    int left_splits = 1;  // partials that the attention left for the o_proj to merge
+    int left_splits = oproj_merge_limit(c, M);  // most partials, then those that the attention left, for the o_proj to merge
     if (raw_qkv) {
       raw.sums = ws.pf.qkv_raw;
       raw.ex = extras;
@@ -593,7 +595,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
       if (!v_blocked) PC_TRY(pc::launch_v_repack(ctx, ws.pf.v, ws.pf.v_blk, batch, t_fresh, s));
     }
     PC_TRY(pc::launch_attention(ctx, l, ws.pf.q, ws.pf.k, ws.pf.v, ws.pf.v_blk, raw_qkv ? &raw : nullptr, batch, t_fresh, ws.pf.table, stride,
-                                min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats, decode && oproj_merges(c, M) ? &left_splits : nullptr));
+                                min_tiles, 0, ws.attn, ws.pf.part_o, ws.pf.part_ml, s, formats, decode && left_splits > 0 ? &left_splits : nullptr));
     if (n_save > 0) {
       PC_TRY(pc::launch_kv_slices(ctx, l, save_slots_host, save_bounds_host, n_save, batch, ws.pf.k, ws.pf.v, t_fresh, s));
       for (int i = 0; i < batch * n_save; ++i)
@@ -607,7 +609,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     for (int b = 0; b < batch && append_slots_host; ++b)
       if (append_slots_host[b] >= 0) ctx->slot_len[(size_t)l * c.n_slots + append_slots_host[b]] += t_fresh;
     if (few) {
-      if (left_splits > 1) PC_TRY(launch_oproj_merge(ctx, (const float *)ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
+      if (decode && left_splits > 1) PC_TRY(launch_oproj_merge(ctx, (const float *)ws.pf.part_o, ws.pf.part_ml, left_splits, t_fresh, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, s));
       else PC_TRY(launch_residual_few(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));
     } else {
       PC_TRY(launch_linear_residual(ctx, ws.attn, (const __bf16 *)w.wo, h_cur, ws.mid, (int)M, H, A, s));

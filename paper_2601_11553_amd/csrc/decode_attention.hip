@@ -597,19 +597,19 @@ namespace pc {
 // Partitions of the key axis: two tiles per workgroup while the whole call then fits one workgroup per CU (finer ones cost the
 // merge more than they give: one query over 64 8-bit tiles of a 3B-shaped layer, 61 us in 33 partitions, 58 in 16), else as many
 // as make whole rounds of the `slots` workgroups that the chip holds at once with four tiles or more in each -- and, where a launch
-// of its own merges them (merged_apart), at least one workgroup per CU: four tiles each would be half of that just past the
+// of its own merges them (more than merge_limit), at least one workgroup per CU: four tiles each would be half of that just past the
 // line (layer of a query 16 heads / 8 kv heads over 64 tiles: 17.3 us in 16 partitions, 16.4 in 32; 8 queries over 8 tiles 16.7 |
 // 15.2; 8-bit slots 16.5 | 15.3 and 16.0 | 14.7).  The o_proj that merges by itself pays more per partition than that gives (a
 // step of the same query over 64 tiles 32.8 | 33.8, of two over 32 tiles 33.3 | 34.0).
-static int decode_splits(int n_cu, int slots, long base_wgs, int tiles, int cap, bool merged_apart) {
+static int decode_splits(int n_cu, int slots, long base_wgs, int tiles, int cap, int merge_limit) {
   const int ns = (tiles + 3) / 2 < cap ? (tiles + 3) / 2 : cap;  // (the fresh keys make a partition of their own then)
   if (base_wgs * ns <= n_cu) return ns;
   const int n = choose_splits(slots, base_wgs, tiles + 2, cap), round = (int)(n_cu / base_wgs);
-  return merged_apart && n < round ? round : n;
+  return n > merge_limit && n < round ? round : n;
 }
 
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
-                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, bool merged_apart, __bf16 *out, float *part_o,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, int merge_limit, __bf16 *out, float *part_o,
                                   float *part_ml, hipStream_t stream, int formats) {
   const percache_config &c = ctx->cfg;
   const int R = c.n_q_heads / c.n_kv_heads * t_fresh;
@@ -624,7 +624,7 @@ pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q,
   // 24 rows 107 | 64), of mixed slots 87 | 70 (104 | 79).
   const long base = (long)batch * c.n_kv_heads;
   const int slots = c.head_dim == 128 && fmt == 0 ? ctx->n_cu : 2 * ctx->n_cu;
-  if (n_splits <= 0) n_splits = decode_splits(ctx->n_cu, slots, base, tiles, cap, merged_apart);
+  if (n_splits <= 0) n_splits = decode_splits(ctx->n_cu, slots, base, tiles, cap, merge_limit);
   if (n_splits > cap) n_splits = cap;
   const dim3 grid((unsigned)(base * n_splits));
   // the form that lets a second workgroup in, where the usual one does not (rings of mixed tiles, two row blocks finished at

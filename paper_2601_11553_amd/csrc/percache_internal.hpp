@@ -190,15 +190,16 @@ inline bool decode_rows(const percache_config &c, int t_fresh) { return (long)(c
 // vf: fresh V as projected; vf_blk: as 64-key blocks (may be null where decode_rows).
 // formats: which slot formats the call's chunks sit in (see table_formats): bit 0 = 8-bit, bit 1 = bf16
 // raw: q and the fresh k, v as the projection's sums instead (decode_rows only; q, kf, vf unused).
-// left_splits (decode_rows only): the caller merges the partials itself; set to their number, at 1 the result is in out.
+// left_splits (decode_rows only): in, the most partials that the caller would merge itself; out, the number left to it, at 1 the
+// result is in out.
 pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const __bf16 *vf_blk,
                            const RawQkv *raw, int batch, int t_fresh, const int32_t *table_dev, int tbl_stride, int max_tiles,
                            int n_splits, __bf16 *out, void *part_o, float *part_ml, hipStream_t stream, int formats,
                            int *left_splits = nullptr);
 // The first of its two launches where decode_rows; tiles: cached tiles of the shortest query.  n_splits <= 0: chosen here
-// (merged_apart: a launch of its own merges the partials, not the o_proj).
+// (merge_limit: up to so many partials are left to the o_proj, more are merged by a launch of their own).
 pc_status launch_decode_attention(percache_ctx *ctx, int layer, const __bf16 *q, const __bf16 *kf, const __bf16 *vf, const RawQkv *raw, int batch, int t_fresh,
-                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, bool merged_apart, __bf16 *out, float *part_o,
+                                  const int32_t *table_dev, int tbl_stride, int tiles, int &n_splits, int merge_limit, __bf16 *out, float *part_o,
                                   float *part_ml, hipStream_t stream, int formats);
 // Number of key-axis partitions that fills `slots` resident workgroups best (at least 4 tiles in each).
 int choose_splits(int slots, long base_wgs, int min_tiles, int cap);

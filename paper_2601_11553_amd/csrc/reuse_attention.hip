@@ -1559,14 +1559,12 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     float *part_o = (float *)part_dev;
     prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
     const pc_status st = launch_decode_attention(ctx, layer, q, kf, vf, raw, batch, t_fresh, table_dev, tbl_stride,
-                                                 min_tiles - (t_fresh + TK - 1) / TK, n_splits, !left_splits, out, part_o, part_ml, stream, formats);
+                                                 min_tiles - (t_fresh + TK - 1) / TK, n_splits, left_splits ? *left_splits : 0, out, part_o, part_ml, stream, formats);
     if (st != PC_OK) return st;
     prof_end(ctx, PC_KERNEL_ATTENTION, stream);
-    if (left_splits) {
-      *left_splits = n_splits;
-      return PC_OK;
-    }
-    return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
+    const bool left = left_splits && n_splits <= *left_splits;
+    if (left_splits) *left_splits = left ? n_splits : 1;
+    return n_splits > 1 && !left ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
   __bf16 *part_o = (__bf16 *)part_dev;
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their

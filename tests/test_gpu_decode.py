@@ -358,13 +358,15 @@ def test_decoding_step_with_head_norms(D, heads, B, T, which, slots):
     pc.close()
 
 
-@pytest.mark.parametrize("B,T,tiles", [(1, 1, 45), (1, 1, 83), (1, 1, 120), (2, 1, 45), (1, 2, 90), (2, 1, 120)])
-def test_o_proj_merges_long_partition_lists(B, T, tiles):
+@pytest.mark.parametrize("B,T,tiles,Hq", [(1, 1, 45, 4), (1, 1, 83, 4), (1, 1, 120, 4), (2, 1, 45, 4), (1, 2, 74, 4), (2, 1, 83, 4), (1, 1, 38, 16), (1, 1, 40, 16)])
+def test_o_proj_merges_long_partition_lists(B, T, tiles, Hq):
     """Decoding steps of one and two rows over 45 to 120 cached tiles of two kv heads: the o_proj merges 24 to 61 partitions, 20 a
-    round, with the largest scores in the first, the last and the middle chunks."""
-    D, Hq, Hkv, H, F, C = 128, 16, 2, 256, 64, 320
+    round, with the largest scores in the first, the last and the middle chunks.  83 tiles of two queries and 40 of 16 heads lie past what
+    it merges: 43 and 21 partitions, against 40 and 20."""
+    D, Hkv, H, F, C = 128, 2, 256, 64, 320
     W = wl.stack_weights(36, 0, H, Hq, Hkv, D, F)
-    W.Wo = W.Wo * np.float32(4)     # (the attention's share of the output; with the chunks' mean values below, a chunk left out or
+    # (the attention's share of the output; with the chunks' mean values below, a chunk left out or counted twice is off by 10 % or more)
+    W.Wo = W.Wo * np.float32(8 if Hq == 4 else 4)
     n_chunks = -(-tiles * 64 // C)
     g = np.random.default_rng(8300 + tiles + B)
     pc = Percache(n_layers=1, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=B * n_chunks, slot_capacity=C,
@@ -374,7 +376,7 @@ def test_o_proj_merges_long_partition_lists(B, T, tiles):
     x = wl.round_bf16(g.standard_normal((B, T, H)).astype(np.float32))
     for loud in ((0,), (n_chunks - 1,), (n_chunks // 2, 1)):
         sk, sv = (wl.round_bf16(g.standard_normal((B, n_chunks, Hkv, C, D)).astype(np.float32)) for _ in range(2))
-        sv = wl.round_bf16(sv + 2 * g.standard_normal((B, n_chunks, Hkv, 1, D)).astype(np.float32))   # counted twice is off by 4 % or more)
+        sv = wl.round_bf16(sv + 2 * g.standard_normal((B, n_chunks, Hkv, 1, D)).astype(np.float32))
         for c in range(n_chunks):
             sk[:, c] = wl.round_bf16(sk[:, c] * np.float32(2.0 if c in loud else 0.3))
         for b in range(B):
