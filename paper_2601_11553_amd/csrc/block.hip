@@ -366,14 +366,15 @@ pc_status launch_residual_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
-// Up to how many of the attention's partials the o_proj of M rows merges itself (0: none): where a wavefront's share is at most
-// two rounds of its 32 lane pairs (8 rows x steps of 64 columns) and the partials of all of them, which every workgroup reads, at
-// most 80.  Layer of one row of 2048 (4 steps), the o_proj merging | a merge launch of its own, us: 9 partitions 29.4 | 31.7, 20
-// 31.0 | 32.0, 31 32.7 | 32.6; two rows 5 30.0 | 31.2, 11 31.7 | 31.4, 16 33.1 | 32.1; one row of 3072 (6) 14 54.8 | 54.1.  The
-// kernels at 20 partitions: 7.1 against 3.7 + 4.8.
+// Up to how many of the attention's partials the o_proj of M rows merges itself (0: none).  A wavefront's share is M * steps * 8
+// pieces of 8 columns (steps of 64 columns), 32 to a round of its lane pairs, and every workgroup reads all the partials: 30 where
+// that is one round, 10 where it is two.  Layer, the o_proj merging | a merge launch of its own, us: one row of 2048 (one round) 11
+// partitions 29.5 | 31.2, 25 32.4 | 33.2, 29 33.0 | 33.0, 31 32.8 | 32.6; of 896 13 29.8 | 31.0, 31 31.6 | 31.7, 61 35.4 | 34.2; two rows
+// of 2048 (two rounds) 7 30.4 | 31.0, 11 31.7 | 31.9, 13 32.3 | 32.1, 16 33.2 | 32.2; one of 3072 9 54.6 | 54.7, 11 54.7 | 54.4, 19
+// 56.5 | 55.1.
 int oproj_merge_limit(const percache_config &c, long M) {
   const int steps = (c.n_q_heads * c.head_dim + 511) / 512;
-  return steps <= kMergeSteps && M * steps <= 8 ? (int)(80 / (M * steps)) : 0;
+  return steps > kMergeSteps || M * steps > 8 ? 0 : M * steps <= 4 ? 30 : 10;
 }
 pc_status launch_oproj_merge(percache_ctx *ctx, const float *part_o, const float *part_ml, int n_splits, int t_fresh, const __bf16 *w,
                              const __bf16 *res, __bf16 *y, int M, hipStream_t s) {

@@ -358,11 +358,12 @@ def test_decoding_step_with_head_norms(D, heads, B, T, which, slots):
     pc.close()
 
 
-@pytest.mark.parametrize("B,T,tiles,Hq", [(1, 1, 45, 4), (1, 1, 83, 4), (1, 1, 120, 4), (2, 1, 45, 4), (1, 2, 74, 4), (2, 1, 83, 4), (1, 1, 38, 16), (1, 1, 40, 16)])
+@pytest.mark.parametrize("B,T,tiles,Hq", [(1, 1, 45, 4), (1, 1, 57, 4), (1, 1, 59, 4), (1, 1, 120, 4), (2, 1, 45, 4), (1, 2, 57, 4), (2, 1, 83, 4), (1, 1, 40, 16),
+                                          (1, 1, 57, 16), (1, 1, 59, 16), (2, 1, 17, 16), (1, 2, 19, 16)])
 def test_o_proj_merges_long_partition_lists(B, T, tiles, Hq):
-    """Decoding steps of one and two rows over 45 to 120 cached tiles of two kv heads: the o_proj merges 24 to 61 partitions, 20 a
-    round, with the largest scores in the first, the last and the middle chunks.  83 tiles of two queries and 40 of 16 heads lie past what
-    it merges: 43 and 21 partitions, against 40 and 20."""
+    """Decoding steps of one and two rows over 17 to 120 cached tiles of two kv heads: the o_proj merges up to 30 partitions, 20 at a
+    time, and up to 10 of two rows of 16 heads, with the largest scores in the first, the last and the middle chunks.  59 tiles and more,
+    and 19 of two rows of 16 heads, lie past what it merges: 31 and 11 partitions."""
     D, Hkv, H, F, C = 128, 2, 256, 64, 320
     W = wl.stack_weights(36, 0, H, Hq, Hkv, D, F)
     # (the attention's share of the output; with the chunks' mean values below, a chunk left out or counted twice is off by 10 % or more)
