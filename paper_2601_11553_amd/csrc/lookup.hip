@@ -195,12 +195,12 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) best[pb].clear();
   // per-row mode: the product is taken the other way round (probes on the M side), so a lane holds ONE row (r16) and
-  // the probes pb*16 + 4g + 0..3; their inverse norms (-inf marks padding probes)
+  // the probes pb*16 + 4g + 0..3; their inverse norms (a padding probe's is a NaN, which no comparison picks)
   float pinv[NPB][4];
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb)
 #pragma unroll
-    for (int e = 0; e < 4; ++e) pinv[pb][e] = (K == 0 && pb * 16 + g * 4 + e < n_probes) ? rs.probe_inv[pb * 16 + g * 4 + e] : -INFINITY;
+    for (int e = 0; e < 4; ++e) pinv[pb][e] = (K == 0 && pb * 16 + g * 4 + e < n_probes) ? rs.probe_inv[pb * 16 + g * 4 + e] : __builtin_nanf("");
 
   // load instruction i of a stage: lane lands at stage byte 1024 i + 16 lane = (row, physical chunk)
   int ld_row[IPS], ld_col[IPS];
@@ -272,7 +272,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
         for (int e = 0; e < 4; ++e) {
           const float c = acc[pb][e] * inv * pinv[pb][e];
           const int p = rs.p0 + pb * 16 + g * 4 + e;
-          if (pinv[pb][e] != -INFINITY && better(c, p, s, pi)) { s = c; pi = p; }  // (a padding probe is no candidate, nor is a NaN)
+          if (better(c, p, s, pi)) { s = c; pi = p; }
         }
 #pragma unroll
       for (int o = 16; o < 64; o <<= 1) {
@@ -732,14 +732,14 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
     inv_lds[r] = row < N ? inv_norm[row] : 0.f;
     if (K == 0) kth_lds[r] = row < N ? rs.kth[row] : 0.f;
   }
-  // per-row mode: inverse norms of the probes this lane meets (-inf marks a padding probe)
+  // per-row mode: inverse norms of the probes this lane meets (a padding probe's is a NaN, which no comparison picks)
   const bool idle = wave * 32 >= n_probes;  // nothing but padding: this wavefront only loads
   float pinv[K == 0 ? 16 : 1];
   if constexpr (K == 0) {
 #pragma unroll
     for (int r = 0; r < 16; ++r) {
       const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
-      pinv[r] = p < n_probes ? rs.probe_inv[p] : -INFINITY;
+      pinv[r] = p < n_probes ? rs.probe_inv[p] : __builtin_nanf("");
     }
 #pragma unroll
     for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(pinv[r]));
@@ -865,7 +865,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
         for (int r = 0; r < 16; ++r) {
           const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
           const float s = (acc[0][r] + acc[1][r]) * inv * pinv[r];
-          if (pinv[r] != -INFINITY && better(s, rs.p0 + p, b.s, b.idx)) b = Best{s, rs.p0 + p};
+          if (better(s, rs.p0 + p, b.s, b.idx)) b = Best{s, rs.p0 + p};
         }
         const Best o{__shfl_xor(b.s, 32, 64), __shfl_xor(b.idx, 32, 64)};
         if (better(o.s, o.idx, b.s, b.idx)) b = o;
