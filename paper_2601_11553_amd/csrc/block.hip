@@ -192,7 +192,7 @@ __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void linear_resid
   }
 }
 
-// The o_proj of a decoding step of one or two rows straight from the attention's split-KV partials: every wavefront merges the
+// The o_proj of a decoding step of a few rows straight from the attention's split-KV partials: every wavefront merges the
 // rows it contracts (its slice of the heads) into LDS under the latency of its first weights, by the rule of
 // splitkv_combine_kernel (m = max m_s, weights l_s 2^(m_s - m), rounded to bf16 once), instead of a launch that merges and
 // one that reads the result back.  Lanes l and l + 32 share 8 columns of a row and take every other partition.

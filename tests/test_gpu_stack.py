@@ -60,8 +60,8 @@ def test_one_block_vs_oracle(D, t_fresh, used_last):
 
 @pytest.mark.parametrize("seed", list(range(16)))
 def test_seeded_random_block_shapes(seed):
-    """One block with every size drawn from a seed: the token-row count decides which projection kernels run (slices
-    of the contraction, the one-pass kernels for few rows, the 64/128-token tiles), the rest varies head size, GQA
+    """One block with every size drawn from a seed: the token-row count decides which projection kernels run (the
+    few-row tiles or the tiles for many rows, each projection by its own line), the rest varies head size, GQA
     ratio, widths, chunk lists and the projection variants."""
     g = np.random.default_rng(4000 + seed)
     D = int(g.choice([64, 128]))
