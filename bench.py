@@ -33,7 +33,7 @@ PEAK_HBM_GBS = 8000.0       # MI355X HBM3E
 
 # HBM bytes per launch of the attention kernel on this workload, from rocprofv3 FETCH_SIZE / WRITE_SIZE runs scaled
 # by a 1 GiB copy (summary under profiles/).  Valid only for the kernel source the counters were taken with.
-ATTN_TRAFFIC = {"source_sha256_16": "e611ef23623c4215", "read_bytes": 2 * 317801.7 * 1024, "write_bytes": 55296.0 * 1024}
+ATTN_TRAFFIC = {"source_sha256_16": "48f8280648363ae5", "read_bytes": 2 * 325508.1 * 1024, "write_bytes": 55303.1 * 1024}
 
 
 def attention_traffic():
@@ -431,7 +431,7 @@ def main():
     kth = torch.full((N,), 0.5, dtype=torch.float32, device=dev)
     st_scan = _stats(torch, lambda: pc.percache_bank_refresh_scan(new64, kth), 50, 3)
     look["topk_P8_k8"] = dict(st_topk, bank_GBps=round(bank_bytes / (st_topk["median_ms"] * 1e-3) / 1e9, 1))
-    look["refresh_scan_64_new"] = dict(st_scan, passes_of_the_bank=2, bank_GBps=round(2 * bank_bytes / (st_scan["median_ms"] * 1e-3) / 1e9, 1))
+    look["refresh_scan_64_new"] = dict(st_scan, passes_of_the_bank=1, bank_GBps=round(bank_bytes / (st_scan["median_ms"] * 1e-3) / 1e9, 1))
 
     # ------------------------------------------------------------------ the K/V store itself: 16 whole chunks written / read
     # (their contents are overwritten with other N(0,1) values: nothing after this point compares outputs)
