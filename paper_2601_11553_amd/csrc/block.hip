@@ -9,6 +9,7 @@
 // cache slicer of Sec. 4.1.1 (cuts the K/V of a prefilled sequence at chunk boundaries into slots).
 #include <cstring>
 
+#include "decode_stack.hpp"
 #include "few_rows.hpp"
 
 namespace {
@@ -406,6 +407,7 @@ struct StackWs {
   __bf16 *attn;    // [M, Hq*D]
   __bf16 *mid;     // [M, H]
   __bf16 *act;     // [M, F]
+  void *steps;     // of a step in one launch (decode_stack.hip)
   size_t total;
 };
 StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fresh, int max_chunks, int ffn) {
@@ -420,6 +422,7 @@ StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fre
   w.attn = take(M * c.n_q_heads * c.head_dim * 2);
   w.mid = take(M * c.hidden * 2);
   w.act = take(M * ffn * 2);
+  w.steps = take(pc::stackdec::workspace_bytes(c, ctx->n_cu, batch, t_fresh, ffn));
   w.total = off;
   return w;
 }
@@ -534,10 +537,11 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
 
   StackWs ws = carve_stack_ws(ctx, workspace_dev, batch, t_fresh, max_chunks, ffn);
   const int stride = pc::tbl_stride(max_chunks);
-  int min_tiles = INT32_MAX;
+  int min_tiles = INT32_MAX, max_cached = 0;
   for (int b = 0; b < batch; ++b) {
     int tiles = rows[(size_t)b * stride + 2] + (t_fresh + pc::kKvTile - 1) / pc::kKvTile;
     if (tiles < min_tiles) min_tiles = tiles;
+    if (rows[(size_t)b * stride + 2] > max_cached) max_cached = rows[(size_t)b * stride + 2];
   }
   hipStream_t s = (hipStream_t)stream;
   // a decoding step of few rows: the attention kernel finishes q, k and v from the projection's sums and appends the fresh
@@ -556,9 +560,32 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
       rows.push_back(here ? ctx->slot_len[slot] : 0);
     }
   }
-  if (table_dev) {
-    ws.pf.table = const_cast<int32_t *>(table_dev);  // the list is on the device already: nothing to copy
-  } else {
+  if (table_dev) ws.pf.table = const_cast<int32_t *>(table_dev);  // the list is on the device already: nothing to copy
+  // (the kernels whose timing was asked for are launched one by one)
+  if (raw_qkv && !(ctx->prof_mask & 6) && pc::stackdec::takes(c, ctx->n_cu, batch, t_fresh, max_cached)) {
+    const __bf16 *k, *v;
+    size_t dense;
+    st = pc::stackdec::launch(ctx, layers_host, n_layers, ffn, eps, (const __bf16 *)h_in_dev, batch, t_fresh, table_dev ? nullptr : &rows, ws.pf.table,
+                              stride, append_slots_host && !table_dev, max_cached, formats, (__bf16 *)h_out_dev, ws.steps, &k, &v, &dense, s);
+    if (st != PC_OK) return st;
+    for (int l = 0; l < n_layers; ++l) {
+      if (n_save > 0) {
+        st = pc::launch_kv_slices(ctx, l, save_slots_host, save_bounds_host, n_save, batch, k + l * dense, v + l * dense, t_fresh, s);
+        if (st != PC_OK) return st;
+        for (int i = 0; i < batch * n_save; ++i)
+          if (save_slots_host[i] >= 0)
+            ctx->slot_len[(size_t)l * c.n_slots + save_slots_host[i]] = save_bounds_host[i % n_save + 1] - save_bounds_host[i % n_save];
+      }
+      if (append_kernel) {
+        st = pc::launch_kv_append(ctx, l, append_slots_host, batch, true, k + l * dense, v + l * dense, t_fresh, s);
+        if (st != PC_OK) return st;
+      }
+      for (int b = 0; b < batch && append_slots_host; ++b)
+        if (append_slots_host[b] >= 0) ctx->slot_len[(size_t)l * c.n_slots + append_slots_host[b]] += t_fresh;
+    }
+    return PC_OK;
+  }
+  if (!table_dev) {
     st = pc::upload_table(ctx, rows, ws.pf.table, s);
     if (st != PC_OK) return st;
   }

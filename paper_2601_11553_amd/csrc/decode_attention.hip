@@ -15,7 +15,7 @@
 // One query, 8 kv heads, 38 tiles (bf16, D = 128): 8.6 us with q, k and v finished here, 7.1 from finished ones (the general
 // kernel 13.6, behind a V repack of 2.4 and in front of an append launch of 2.8 per query); 8 queries x 8 kv heads x 256 tiles:
 // 87 us of bf16 slots (6.2 TB/s of keys and values), 53 of 8-bit ones (5.1; the general kernel 62), 70 of mixed ones (73).
-#include "percache_internal.hpp"
+#include "decode_common.hpp"
 
 namespace {
 using pc::bf16x4;
@@ -23,37 +23,17 @@ using pc::bf16x8;
 using pc::f32x4;
 using pc::kKvTile;
 using pc::kTblHeader;
+using pc::dec::codes4;
+using pc::dec::codes8;
+using pc::dec::fast_exp2;
+using pc::dec::RawRow;
+using pc::dec::row_max;
+using pc::dec::row_sum;
 
 constexpr int TK = kKvTile, NW = 4;
 constexpr float kSumLimit = 4.f * 256.f;  // 4 probabilities of a lane and tile, each at most 2^8 against the reference
 
 #define PC_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xf) | (7 << 4) | (15 << 8) | ((((n) >> 4) & 3) << 14))
-
-__device__ __forceinline__ float fast_exp2(float x) { return __builtin_amdgcn_exp2f(x); }
-// over the four lanes (l, l + 16, l + 32, l + 48) that share a query row
-__device__ __forceinline__ float row_max(float x) {
-  x = fmaxf(x, __shfl_xor(x, 16, 64));
-  return fmaxf(x, __shfl_xor(x, 32, 64));
-}
-__device__ __forceinline__ float row_sum(float x) {
-  x += __shfl_xor(x, 16, 64);
-  return x + __shfl_xor(x, 32, 64);
-}
-
-// E4M3 codes times a power-of-two scale -> bf16 (exact)
-typedef __bf16 bf16x2 __attribute__((ext_vector_type(2)));
-__device__ __forceinline__ bf16x4 codes4(unsigned w, float scale) {
-  union { bf16x2 p[2]; bf16x4 v; } u;
-  u.p[0] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, scale, false);
-  u.p[1] = __builtin_amdgcn_cvt_scalef32_pk_bf16_fp8(w, scale, true);
-  return u.v;
-}
-__device__ __forceinline__ bf16x8 codes8(uint2 w, float scale) {
-  union { bf16x4 p[2]; bf16x8 v; } u;
-  u.p[0] = codes4(w.x, scale);
-  u.p[1] = codes4(w.y, scale);
-  return u.v;
-}
 
 // FMT: 0 every cached chunk of the call sits in a bf16 slot, 1 in an 8-bit slot, 2 some of each.  NR: blocks of 16 rows.
 // TWO: the form of long calls in which two workgroups share a CU (see launch_decode_attention).
@@ -65,61 +45,6 @@ struct Lds {
   static constexpr int O_ROW = D + 4;                                    // floats per output row of a wavefront (padded)
   static constexpr int MERGE = NW * NR * 16 * (O_ROW + 2) * 4 + NR * 16 * 32 * 4 + 32 * D * 2;  // outputs, (m, l), fresh probabilities, fresh V
   static constexpr int BYTES = NSTG * STAGE > MERGE ? NSTG * STAGE : MERGE;
-};
-
-// Elements 32 ks + 8 g .. +7 of one projected head row of D fp32 sums (the four lanes g share a row): load() asks for
-// everything, finish() applies bias, RMSNorm over the head (gain; null: none) and RoPE and rounds to bf16 once.
-template <int D>
-struct RawRow {
-  static constexpr int KS = D / 32;
-  f32x4 x[KS][2], cs[KS / 2][4];
-  bf16x8 bi[KS], gn[KS];
-  __device__ __forceinline__ void load(const float *__restrict__ sums, const __bf16 *__restrict__ bias, const __bf16 *__restrict__ gain,
-                                       const float2 *__restrict__ rope, int pos, int g) {
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      x[ks][0] = *(const f32x4 *)(sums + ks * 32 + g * 8);
-      x[ks][1] = *(const f32x4 *)(sums + ks * 32 + g * 8 + 4);
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS / 2; ++ks)
-#pragma unroll
-      for (int h = 0; h < 4; ++h) cs[ks][h] = *(const f32x4 *)(rope + (size_t)pos * (D / 2) + ks * 32 + g * 8 + h * 2);
-#pragma unroll
-    for (int ks = 0; ks < KS; ++ks) {
-      if (bias) bi[ks] = *(const bf16x8 *)(bias + ks * 32 + g * 8);
-      if (gain) gn[ks] = *(const bf16x8 *)(gain + ks * 32 + g * 8);
-    }
-  }
-  __device__ __forceinline__ void finish(bool bias, bool gain, float eps, bf16x8 (&out)[KS]) {
-    if (bias) {
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] += (float)bi[ks][e];
-    }
-    if (gain) {
-      float s = 0.f;
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) s += x[ks][e >> 2][e & 3] * x[ks][e >> 2][e & 3];
-      const float r = 1.0f / sqrtf(row_sum(s) / (float)D + eps);
-#pragma unroll
-      for (int ks = 0; ks < KS; ++ks)
-#pragma unroll
-        for (int e = 0; e < 8; ++e) x[ks][e >> 2][e & 3] *= r * (float)gn[ks][e];
-    }
-#pragma unroll
-    for (int ks = 0; ks < KS / 2; ++ks)
-#pragma unroll
-      for (int e = 0; e < 8; ++e) {
-        const float a = x[ks][e >> 2][e & 3], b = x[ks + KS / 2][e >> 2][e & 3];
-        const float c = cs[ks][e >> 1][2 * (e & 1)], sn = cs[ks][e >> 1][2 * (e & 1) + 1];
-        out[ks][e] = (__bf16)(a * c - b * sn);
-        out[ks + KS / 2][e] = (__bf16)(b * c + a * sn);
-      }
-  }
 };
 
 // RAW: q and the fresh k, v come as the projection's fp32 sums (raw.sums) and are finished here -- by every workgroup for

@@ -389,3 +389,86 @@ def test_o_proj_merges_long_partition_lists(B, T, tiles, Hq):
             ref, _, _ = oracle_block(x[b], W, Hq, Hkv, D, 10000.0, sk[b], sv[b], np.arange(n_chunks, dtype=np.int32), used[b])
             check_hidden(host(out[b]), ref, f"{tiles} tiles, loud chunks {loud}, B={B} T={T} query {b}")
     pc.close()
+
+
+def _step_inputs(H, Hq, Hkv, D, F, L, variant, g):
+    Ws = []
+    for _ in range(L):
+        n = (Hq + 2 * Hkv) * D
+        w = dict(gain1=1 + 0.1 * g.standard_normal(H), wqkv=0.02 * g.standard_normal((n, H)), wo=0.02 * g.standard_normal((H, Hq * D)),
+                 gain2=1 + 0.1 * g.standard_normal(H), w_gate=0.02 * g.standard_normal((F, H)), w_up=0.02 * g.standard_normal((F, H)),
+                 w_down=0.02 * g.standard_normal((H, F)))
+        if variant == "bias":
+            w["qkv_bias"] = 0.5 * g.standard_normal(n)
+        if variant == "norm":
+            w.update(q_norm=1 + 0.1 * g.standard_normal(D), k_norm=1 + 0.1 * g.standard_normal(D))
+        Ws.append({k: bf16(v.astype(np.float32)) for k, v in w.items()})
+    return Ws
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,D,F,L,B,T,chunks,C,slots,variant", [
+    (128, 2, 1, 64, 64, 1, 1, 1, 0, 64, "bf16", "plain"),        # wavefronts without a slice, nothing cached, one piece
+    (256, 4, 2, 128, 512, 2, 4, 1, 3, 128, "8bit", "norm"),
+    (1024, 16, 8, 128, 3072, 2, 1, 1, 6, 512, "mixed", "norm"),
+    (896, 14, 2, 64, 4864, 2, 1, 2, 5, 192, "mixed", "bias"),
+    (896, 14, 2, 64, 4864, 34, 1, 1, 70, 64, "bf16", "bias"),    # two launches of layers, chunks past the 64th, one row past kRowCols
+    (3072, 24, 8, 128, 8192, 1, 3, 1, 4, 320, "bf16", "plain"),  # contractions in chunks
+    (384, 16, 1, 128, 192, 2, 1, 1, 16, 1024, "bf16", "plain"),  # 16 rows per kv head, four tiles to a piece
+    (256, 4, 4, 128, 320, 2, 1, 4, 2, 128, "8bit", "plain"),
+])
+def test_step_in_one_launch_against_one_by_one(H, Hq, Hkv, D, F, L, B, T, chunks, C, slots, variant):
+    """Steps of a few rows take all layers in one launch unless the QKV or attention kernels' times were asked for.  Both round the same
+    values to bf16, in other orders of summation: per layer about six roundings that two runs may take differently, 2^-9 / sqrt(3) each, carried
+    on with a factor of about 1.5: 4.2e-3 sqrt(layers); the bound is 6e-3 sqrt(layers).  The first layer's K/V must agree to one rounding."""
+    g = np.random.default_rng(17)
+    Ws = _step_inputs(H, Hq, Hkv, D, F, L, variant, g)
+    n_slots = B * chunks + 2 * B
+    kind = dict(kv_fp8=True) if slots == "8bit" else dict(n_slots_8bit=n_slots // 2) if slots == "mixed" else {}
+    pc = Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=n_slots, slot_capacity=C, max_pos=chunks * C + C + 3 * T,
+                  device=DEV, **kind)
+    ids = [int(x) for x in g.permutation(n_slots)]
+    if slots == "mixed":   # the two runs' own slots of the same format
+        ids = sorted(ids)
+    lists = [ids[2 * B + b * chunks: 2 * B + (b + 1) * chunks] for b in range(B)]
+    own = [ids[:B], ids[B:2 * B]]
+    for s in [s for row in lists for s in row]:
+        n = int(g.integers(1, C + 1))
+        for layer in range(L):
+            pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, n, D))), bf16(g.standard_normal((Hkv, n, D))))
+    xs = [bf16(g.standard_normal((B, T, H))) for _ in range(3)]
+    outs = []
+    for way in (0, 1):
+        pc.percache_profile_enable(way == 1, [2])
+        outs.append([host(pc.percache_stack_decode(Ws, F, EPS, x, [lists[b] + ([own[way][b]] if i else []) for b in range(B)], own[way]))
+                     for i, x in enumerate(xs)])
+    pc.percache_profile_enable(False)
+    for i, (a, b) in enumerate(zip(*outs)):
+        check_hidden(a, b, f"step {i} in one launch against one by one", rel_max=2.0 ** -4 * max(1, L) ** 0.5, rel_fro=6e-3 * L ** 0.5)
+    for b in range(B):
+        assert pc.percache_kv_len(0, own[0][b]) == pc.percache_kv_len(L - 1, own[0][b]) == 3 * T
+        for x, y in zip(pc.percache_kv_get(0, own[0][b]), pc.percache_kv_get(0, own[1][b])):
+            check_hidden(host(x), host(y), "first layer's K/V", rel_max=2.0 ** -4 if slots != "bf16" else 2.0 ** -7)
+
+
+def test_steps_on_two_streams_at_once():
+    """Two programs' steps queued on two streams, neither waiting for the other: each result is the one it has alone, bit for bit."""
+    g = np.random.default_rng(5)
+    H, Hq, Hkv, D, F, L = 256, 4, 2, 64, 512, 6
+    Ws = _step_inputs(H, Hq, Hkv, D, F, L, "plain", g)
+    pcs = [Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=4, slot_capacity=128, max_pos=512, device=DEV) for _ in range(2)]
+    for pc in pcs:
+        for layer in range(L):
+            for s in range(3):
+                pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, 100, D))), bf16(g.standard_normal((Hkv, 100, D))))
+    xs = [bf16(g.standard_normal((1, 1, H))) for _ in range(2)]
+    alone = [pc.percache_stack_decode(Ws, F, EPS, x, [[0, 1, 2]], [-1]) for pc, x in zip(pcs, xs)]
+    torch.cuda.synchronize()
+    streams = [torch.cuda.Stream() for _ in range(2)]
+    outs = [[], []]
+    for _ in range(20):
+        for i in (0, 1):
+            with torch.cuda.stream(streams[i]):
+                outs[i].append(pcs[i].percache_stack_decode(Ws, F, EPS, xs[i], [[0, 1, 2]], [-1]))
+    torch.cuda.synchronize()
+    for i in (0, 1):
+        assert all(torch.equal(o, alone[i]) for o in outs[i])
