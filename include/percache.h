@@ -19,10 +19,12 @@
  *     enqueued before it, and slot lengths already recorded for it, stay as they are.
  *   - Work is enqueued on the caller's stream (a hipStream_t passed as void*; NULL = the default
  *     stream) and is complete once the caller synchronises that stream.  Only percache_create
- *     synchronises the device.  Calls that take a chunk list as HOST arrays copy a small table to the
- *     device through a ring of 16 pinned staging buffers: the 17th such call in flight waits on the host
- *     for the oldest copy (hipEventSynchronize), a longer list than any before re-allocates the ring
- *     (hipHostMalloc), and such a call cannot be captured into a HIP graph with live contents.  The calls
+ *     synchronises the device.  Calls that take a chunk list as HOST arrays bring a small table to the
+ *     device: up to 832 words (batch x (4 + 2 max_chunks)) as a launch argument, a longer one through a
+ *     ring of 16 pinned staging buffers, where the 17th such call in flight waits on the host
+ *     for the oldest copy (hipEventSynchronize) and a longer list than any before re-allocates the ring
+ *     (hipHostMalloc).  Captured into a HIP graph such a call keeps the list it was captured with, or, staged,
+ *     whatever the ring holds at the replay.  The calls
  *     that take a device-resident chunk table (percache_chunk_table_put once, then *_table calls) do
  *     none of this: they enqueue kernels only, wait for nothing, allocate nothing, and can be captured.
  *   - One context serves one stream at a time; concurrent calls on one context are not safe, with one

@@ -79,6 +79,10 @@ pc_status fail(percache_ctx *ctx, pc_status st, const char *fmt, ...) {
   return st;
 }
 
+__global__ __launch_bounds__(256) void list_kernel(int32_t *dst, int n, const ListWords lists) {
+  for (int i = threadIdx.x; i < n; i += 256) dst[i] = lists.v[i];
+}
+
 pc_status build_chunk_table(percache_ctx *ctx, int32_t layer, int32_t batch, int32_t t_fresh,
                             const int32_t *slot_ids, const int32_t *used_len, const int32_t *n_chunks,
                             int32_t max_chunks, std::vector<int32_t> &rows) {
@@ -117,6 +121,15 @@ pc_status build_chunk_table(percache_ctx *ctx, int32_t layer, int32_t batch, int
 }
 
 pc_status upload_table(percache_ctx *ctx, const std::vector<int32_t> &rows, int32_t *dst_dev, hipStream_t stream) {
+  // Lists that fit a launch's arguments travel as such.  The staged copy is a kernel too (2.6 us), behind a change of queues, and the host
+  // waits for the events that guard its ring: one query's layer over 4 chunks, 64 tokens, 26.7 us a call with it, 22.9 without.
+  if (rows.size() <= (size_t)kListWords) {
+    ListWords lists;
+    memcpy(lists.v, rows.data(), rows.size() * sizeof(int32_t));
+    hipLaunchKernelGGL(list_kernel, dim3(1), dim3(256), 0, stream, dst_dev, (int)rows.size(), lists);
+    PC_HIP(ctx, hipGetLastError());
+    return PC_OK;
+  }
   if (rows.size() > ctx->stage_ints) {
     // grow every ring entry (host allocation only); wait for copies still reading the old ones
     for (int i = 0; i < kStageRing; ++i) {

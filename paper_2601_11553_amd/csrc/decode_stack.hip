@@ -933,12 +933,9 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_stack_kernel(const Args
 
 // What a step needs before its first launch: the buffers of the hand-over filled with ones, the counters at zero, the chunk lists, and
 // the first layer's input handed over (workgroup m: row m).
-struct Lists {
-  int32_t v[pc::stackdec::kListWords];
-};
 __global__ __launch_bounds__(256) void decode_stack_begin_kernel(u32x4 *fill, size_t n_fill, unsigned *tickets, int n_tickets, int32_t *table, int n_list,
                                                                  const __bf16 *__restrict__ h_in, const __bf16 *__restrict__ gain, int M, int H, __bf16 *h,
-                                                                 float *h_b, const Lists lists) {
+                                                                 float *h_b, const pc::ListWords lists) {
   const u32x4 ones = {EMPTY, EMPTY, EMPTY, EMPTY};
   for (size_t i = (size_t)blockIdx.x * 256 + threadIdx.x; i < n_fill; i += (size_t)gridDim.x * 256) fill[i] = ones;
   if (blockIdx.x == 0) {
@@ -1100,8 +1097,8 @@ pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_
     const pc_status st = upload_table(ctx, *rows, table, stream);
     if (st != PC_OK) return st;
   }
-  static_assert(sizeof(Lists) + 64 <= 4096 && sizeof(Args) <= 4096, "launch arguments");
-  Lists lists;
+  static_assert(sizeof(ListWords) + 64 <= 4096 && sizeof(Args) <= 4096, "launch arguments");
+  ListWords lists;
   const int n_list = inline_list ? (int)rows->size() : 0;
   memset(&lists, 0, sizeof lists);
   if (n_list) memcpy(lists.v, rows->data(), (size_t)n_list * 4);

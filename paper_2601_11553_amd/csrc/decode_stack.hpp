@@ -11,7 +11,6 @@ constexpr int kRing = 64 * 1024;     // LDS of a workgroup's weights in flight, 
 constexpr int kMaxRows = 4;          // token rows
 constexpr int kMaxQueryRows = 16;    // query rows per kv head
 constexpr int kMaxLayers = 32;       // per launch (their pointers are launch arguments)
-constexpr int kListWords = 832;      // chunk lists that travel as launch arguments
 
 struct LayerPtrs {
   const __bf16 *gain1, *wqkv, *wo, *gain2, *w_gate, *w_up, *w_down, *qkv_bias, *q_norm, *k_norm;

@@ -53,6 +53,12 @@ inline int tbl_stride(int max_chunks) { return kTblHeader + 2 * (max_chunks > 0 
 
 constexpr int kStageRing = 16;
 
+// Chunk lists as a launch argument (4096 bytes are what a launch takes).
+constexpr int kListWords = 832;
+struct ListWords {
+  int32_t v[kListWords];
+};
+
 // Size of the file-scope scratch array behind the entry points that allocate nothing.
 constexpr size_t kStaticScratchBytes = 1u << 20;
 

@@ -102,3 +102,20 @@ def test_stack_from_a_device_table_captured_into_a_graph():
                 diff = (out.float() - eager.float()).abs().max().item()
                 assert diff <= 2.0 ** -7 * eager.float().abs().max().item(), (n_list, rep, diff)
     pc.close()
+
+
+@pytest.mark.parametrize("batch,chunks", [(1, 0), (1, 1), (8, 50), (8, 51), (13, 64)])
+def test_lists_arrive_whole_as_launch_arguments_and_staged(batch, chunks):
+    """8 queries x 50 chunks are 832 words, what a launch's arguments take; one chunk more is copied through the staging ring."""
+    g = np.random.default_rng(batch * 100 + chunks)
+    n_slots = max(chunks, 1)
+    pc = Percache(n_layers=1, hidden=128, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=n_slots, slot_capacity=64, max_pos=8192, device=DEV)
+    lens = [int(x) for x in g.integers(1, 65, n_slots)]
+    for s in range(n_slots):
+        pc.percache_kv_put(0, s, bf16(g.standard_normal((1, lens[s], 64))), bf16(g.standard_normal((1, lens[s], 64))))
+    ids = np.stack([g.permutation(n_slots)[:chunks] for _ in range(batch)]).astype(np.int32).reshape(batch, chunks)
+    table = pc.percache_chunk_table_put(ids)
+    got = table.cpu().numpy().view(np.int32).reshape(-1)[:batch * (4 + 2 * chunks)].reshape(batch, -1)
+    used = np.asarray(lens)[ids] if chunks else np.zeros((batch, 0), np.int64)
+    assert (got[:, 0] == chunks).all() and (got[:, 1] == used.sum(1)).all() and (got[:, 2] == chunks).all()
+    assert (got[:, 3] == (2 if chunks else 0)).all() and (got[:, 4::2] == ids).all() and (got[:, 5::2] == used).all()
