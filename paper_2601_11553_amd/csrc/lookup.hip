@@ -4,6 +4,8 @@
 // The bank is streamed from HBM exactly once per pass of up to 32 probes.  The dot products run on the
 // fp16 matrix cores (16x16x32, fp32 accumulate) only because they perform the cross-lane reduction for
 // free; the kernel is bound by the HBM stream of the bank, not by arithmetic.
+#include <atomic>
+#include <chrono>
 #include <climits>
 #include <cmath>
 
@@ -95,10 +97,23 @@ constexpr int kMaxBlocksPerWg = 128;  // 2048 rows: bounds the LDS copy of the i
 template <int CHB>
 __device__ __forceinline__ int row_swz(int row) { return CHB >= 256 ? (row & 15) : ((row >> 1) & 7); }
 
+// The merge of the workgroups' lists inside the launch that makes them (null marks: by lookup_finalize_kernel).  Every workgroup stores its
+// lists straight to memory (device scope) and then a mark, a number that no other call uses; the last one waits for all the marks, merges, and
+// clears them, so that a captured call can be replayed.  It holds one CU while it waits for workgroups that wait for nothing.
+struct InLaunch {
+  unsigned long long *marks;   // [workgroups], whatever they hold
+  unsigned long long mark;
+  float tau;
+  int k;
+  int32_t *idx_out;
+  float *sim_out;
+  uint8_t *hit_out;
+};
+
 // Merge of the per-lane lists of one workgroup: the four lanes that share a probe (K rounds of "best head wins and
 // is popped"), then the four wavefronts through LDS; the workgroup's lists go to partial[blockIdx.x][NPB*16][KL].
 template <int NPB, int KL>
-__device__ __forceinline__ void merge_workgroup_lists(TopK<KL> (&best)[NPB], char *smem, Best *__restrict__ partial) {
+__device__ __forceinline__ void merge_workgroup_lists(TopK<KL> (&best)[NPB], char *smem, Best *__restrict__ partial, bool in_launch = false) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int r16 = lane & 15, g = lane >> 4;
   __syncthreads();  // probes no longer needed: reuse LDS for the cross-wave step
@@ -133,7 +148,77 @@ __device__ __forceinline__ void merge_workgroup_lists(TopK<KL> (&best)[NPB], cha
       }
 #pragma unroll
       for (int w = 0; w < 4; ++w) head[w] += (w == from);
-      partial[((size_t)blockIdx.x * (NPB * 16) + tid) * KL + j] = b;
+      Best *to = partial + ((size_t)blockIdx.x * (NPB * 16) + tid) * KL + j;
+      if (in_launch) __hip_atomic_store((unsigned long long *)to, __builtin_bit_cast(unsigned long long, b), __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+      else *to = b;
+    }
+  }
+}
+
+// See InLaunch; a wavefront a probe.  The sums of the probe's norm are added up as lookup_finalize_kernel does.
+template <int K>
+__device__ __forceinline__ void merge_in_launch(const InLaunch &f, const Best *partial, int stride, const _Float16 *__restrict__ probes, int n_probes, int d) {
+  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
+  asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the lists are in memory
+  __syncthreads();
+  if (tid == 0) __hip_atomic_store(f.marks + blockIdx.x, f.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if ((int)blockIdx.x != n - 1) return;
+  for (int w = tid; w < n; w += 256)
+    for (int tries = 0; tries < 1 << 18; ++tries) {   // (a fraction of a second: no wait gets there, the others were started first)
+      if (__hip_atomic_load(f.marks + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == f.mark) break;
+      __builtin_amdgcn_s_sleep(2);
+    }
+  __syncthreads();
+  for (int w = tid; w < n; w += 256) __hip_atomic_store(f.marks + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  for (int p = wave; p < n_probes; p += 4) {
+    const u32x4 *src = (const u32x4 *)(probes + (size_t)p * d);
+    float tot = 0.f;
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float ss = 0.f;
+      for (int v = q * 64 + lane; v < d / 8; v += 256) {
+        const f16x8 h = __builtin_bit_cast(f16x8, src[v]);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      tot += ss;
+    }
+    TopK<K> mine;
+    mine.clear();
+    for (int w = lane; w < n; w += 64) {
+      const unsigned long long *lst = (const unsigned long long *)(partial + ((size_t)w * stride + p) * K);
+      Best b[K];
+#pragma unroll
+      for (int j = 0; j < K; ++j) b[j] = __builtin_bit_cast(Best, __hip_atomic_load(lst + j, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT));
+#pragma unroll
+      for (int j = 0; j < K; ++j) {
+        if (w == lane) {   // (the first list as it stands: it is sorted)
+          mine.s[j] = b[j].idx != INT_MAX ? b[j].s : -INFINITY;
+          mine.i[j] = b[j].idx;
+        } else if (b[j].idx != INT_MAX) {
+          mine.insert(b[j].s, b[j].idx);
+        }
+      }
+    }
+    const float inv = tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
+    for (int j = 0; j < f.k; ++j) {
+      float s = mine.s[0];
+      int i = mine.i[0];
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const float s2 = __shfl_xor(s, o, 64);
+        const int i2 = __shfl_xor(i, o, 64);
+        if (better(s2, i2, s, i)) { s = s2; i = i2; }
+      }
+      mine.pop_if(i != INT_MAX && mine.i[0] == i);
+      if (lane == 0) {
+        const float sim = i == INT_MAX ? -INFINITY : s * inv;
+        f.idx_out[(size_t)p * f.k + j] = i == INT_MAX ? -1 : i;
+        f.sim_out[(size_t)p * f.k + j] = sim;
+        if (f.hit_out && j == 0) f.hit_out[p] = sim > f.tau ? 1 : 0;
+      }
     }
   }
 }
@@ -154,7 +239,7 @@ template <int NPB, int CHB, int NSTG, int K>
 __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__restrict__ bank,
                                                             const float *__restrict__ inv_norm, int N, int d,
                                                             const _Float16 *__restrict__ probes, int n_probes,
-                                                            int per_wg, int ring_off, Best *__restrict__ partial, RowScan rs) {
+                                                            int per_wg, int ring_off, Best *__restrict__ partial, RowScan rs, InLaunch in_launch) {
   extern __shared__ __align__(16) char smem[];
   constexpr int CS = CHB / 64;           // MFMA k-steps (32 elements) per chunk
   constexpr int STG = 16 * CHB;          // bytes per stage
@@ -323,7 +408,10 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
 
   if (K == 0) return;  // per-row mode: everything has been written
-  merge_workgroup_lists<NPB, KL>(best, smem, partial);
+  merge_workgroup_lists<NPB, KL>(best, smem, partial, NPB == 1 && in_launch.marks);
+  if constexpr (NPB == 1 && K > 0) {
+    if (in_launch.marks) merge_in_launch<KL>(in_launch, partial, NPB * 16, probes, n_probes, d);
+  }
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -992,28 +1080,28 @@ bool big_tiles_pay(int n_probes) {
 
 template <int NPB, int CHB, int NSTG, int K>
 pc_status launch_stream(percache_ctx *ctx, const StreamShape &sh, hipStream_t st, int N, int d, const _Float16 *pp, int np,
-                        Best *partial, const RowScan &rs) {
+                        Best *partial, const RowScan &rs, const InLaunch &il) {
   static bool big_lds_set = false;  // dynamic LDS above 64 KB must be opted into once per kernel
   if (!big_lds_set) {
     PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_stream_kernel<NPB, CHB, NSTG, K>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds));
     big_lds_set = true;
   }
   hipLaunchKernelGGL((lookup_stream_kernel<NPB, CHB, NSTG, K>), dim3(sh.grid), dim3(256), sh.lds, st, ctx->bank, ctx->bank_inv, N, d,
-                     pp, np, sh.per_wg, sh.ring_off, partial, rs);
+                     pp, np, sh.per_wg, sh.ring_off, partial, rs, il);
   return PC_OK;
 }
 
 template <int K>
 pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStream_t st, int N, int d, const _Float16 *pp, int np,
-                      Best *partial, const RowScan &rs = RowScan{}) {
+                      Best *partial, const RowScan &rs = RowScan{}, const InLaunch &il = InLaunch{}) {
   if (npb == 1 && sh.nstg == 3)
-    return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs)
-           : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs)
-                           : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs);
-  if (npb == 1) return launch_stream<1, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs);  // only the widest rows (512-byte chunks) get here
-  return sh.chb == 128   ? launch_stream<2, 128, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs)
-         : sh.chb == 256 ? launch_stream<2, 256, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs)
-                         : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs);
+    return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
+           : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
+                           : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);
+  if (npb == 1) return launch_stream<1, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);  // only the widest rows (512-byte chunks) get here
+  return sh.chb == 128   ? launch_stream<2, 128, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
+         : sh.chb == 256 ? launch_stream<2, 256, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
+                         : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);
 }
 
 // Per-row scan of up to 128 new embeddings in one pass of the bank.
@@ -1034,6 +1122,13 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
 #undef PC_SCAN
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
+}
+
+// A number for the marks of a call that no other call uses (from a start that a workspace's contents will not hold by chance).
+constexpr int kInLaunchUpTo = 8;
+unsigned long long next_mark() {
+  static std::atomic<unsigned long long> counter{std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull | 1};
+  return counter.fetch_add(2, std::memory_order_relaxed);
 }
 
 // k best rows per probe (k == 1: the query-level match with its hit flag; hit_out may be null otherwise)
@@ -1137,16 +1232,25 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     int npb = np <= 16 ? 1 : 2;
     StreamShape sh = stream_shape(ctx, npb, N);
     const _Float16 *pp = probes + (size_t)p0 * d;
+    uint8_t *hit = hit_out_dev ? hit_out_dev + p0 : nullptr;
+    // A short pass over a small bank merges its lists itself (the marks behind the lists, which one probe block leaves room for): what it saves is a
+    // launch, what it costs is that one workgroup merges for all probes.  us a call, apart | here, 1000 to 2000 rows of width 768: best row of
+    // 1 probe 11.3 | 8.2, of 8 11.3 | 10.1; 3 best of 1 14.3 | 11.5, of 8 14.8 | 14.5; 8 best of 1 18.0 | 16.0, of 8 18.4 | 23.0.  With more lists
+    // than lanes (20 000 rows, 256 lists): best row of 1 11.3 | 9.7, of 8 11.5 | 12.1, 3 best of 1 14.1 | 14.7, of 8 14.4 | 20.8; behind a long stream
+    // the merge apart is hidden already (200 000 rows 66.5 | 67.2).
+    InLaunch il{};
+    if (sh.grid <= 64 && (n_probes <= 4 || (n_probes <= kInLaunchUpTo && k <= 4)) && workspace_dev != ctx->static_scratch)
+      il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : k <= 4 ? 4 : kMaxTopK)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit};
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     // (up to four best rows out of lists of four: what the pass spends on a list of eight shows beside the stream, us a pass, eight | four: 3 best
     // of 1000 rows of width 768 12.9 | 10.7, of 50 000 of width 1024 27.1 | 23.3, of 200 000 71.6 | 68.1, 24 probes 82.7 | 75.3)
-    pc_status ls = k == 1   ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial)
-                   : k <= 4 ? launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial)
-                            : launch_pass<kMaxTopK>(ctx, sh, npb, st, N, d, pp, np, partial);
+    pc_status ls = k == 1   ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
+                   : k <= 4 ? launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
+                            : launch_pass<kMaxTopK>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il);
     if (ls != PC_OK) return ls;
     pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
     PC_HIP(ctx, hipGetLastError());
-    uint8_t *hit = hit_out_dev ? hit_out_dev + p0 : nullptr;
+    if (il.marks) continue;
     if (k == 1)
       hipLaunchKernelGGL(lookup_finalize_kernel<1>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, sh.grid, npb * 16, pp, d, tau, 1,
                          idx_out_dev + p0, sim_out_dev + p0, hit);

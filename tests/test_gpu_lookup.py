@@ -380,3 +380,40 @@ def test_refresh_scan_rows_and_chunks_that_are_not_numbers(dim, n_new):
     assert np.abs(sims[np.arange(len(good)), bn[good]] - sims.max(1)).max() < 2e-5
     clear = np.abs(sims.max(1) - 0.05) > 2e-5
     assert np.array_equal(st[good][clear] == 1, sims.max(1)[clear] > 0.05)
+
+
+@pytest.mark.parametrize("rows,dim,k", [(1, 64, 1), (15, 384, 8), (2000, 768, 3), (4096, 768, 1), (4097, 768, 4), (4033, 128, 5), (4096, 2048, 2)])
+def test_merge_inside_the_launch_equals_the_merge_apart(rows, dim, k):
+    """Calls of up to 8 probes over at most 64 workgroups' rows merge their lists inside the launch, others in a launch of their own: the same
+    bits, whatever the workspace held, and again from a captured call replayed between eager ones."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + dim)
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=1, slot_capacity=64, max_pos=64, bank_capacity=rows, emb_dim=dim,
+                  device=DEV)
+    bank = torch.randn((rows, dim), generator=g, device=DEV).half()
+    bank[rows // 2] = bank[0]                                  # a tie
+    pc.percache_bank_put(0, bank)
+    probes = torch.randn((16, dim), generator=g, device=DEV).half()
+    probes[0] = bank[0]
+    probes[5] = 0
+
+    def call(p):
+        return pc.percache_lookup(p, 0.3) if k == 1 else pc.percache_lookup_topk(p, k)
+    apart = [t.clone() for t in call(probes)]                  # 16 probes
+    for n in (1, 3, 8, 9):
+        for fill in (0, 255):
+            pc._lookup_ws.fill_(fill)
+            assert all(torch.equal(a[:n], b) for a, b in zip(apart, call(probes[:n].contiguous()))), (n, fill)
+    few = probes[2:7].contiguous()
+    call(few)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        out = call(few)
+    for _ in range(4):
+        for t in out:
+            t.zero_()
+        graph.replay()
+        call(probes[:1].contiguous())
+        torch.cuda.synchronize()
+        assert all(torch.equal(a[2:7], b) for a, b in zip(apart, out))
