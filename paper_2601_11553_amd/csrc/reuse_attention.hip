@@ -606,25 +606,37 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
 //     bf16 values the PV product multiplies by at most 2^-9 relative, the rounding of one probability.)
 //   - LDS is touched by the requests and by operand reads only: with an ordinary LDS store or an LDS object of another
 //     kind in the kernel, the compiler places a wait for all outstanding requests before the first operand read.
-template <int D>
+//
+// PAIR: 128 rows a workgroup; wavefronts w and w + 4 have the same rows and take every other tile, two tiles an iteration from a ring of
+// two pairs, and merge through LDS.  For prompts whose row blocks see very different numbers of keys (a whole prompt prefilled): twice the
+// workgroups, each half as long, even out where the longest 256-row block alone takes twice the mean
+// (the rule and its figures: launch_attention).
+template <int D, bool PAIR = false>
 __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const __bf16 *__restrict__ k_store, const __bf16 *__restrict__ v_store, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
     __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
   using L = Lds<D>;
-  constexpr int NW = 8, NLD = 4, NSTAGE = 3, KS = D / 16, DB = D / 32, QROWS = 32 * NW;
+  constexpr int NLD = 4, NSTAGE = PAIR ? 4 : 3, KS = D / 16, DB = D / 32, QROWS = PAIR ? 128 : 256;
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
 
   const int xcd = blockIdx.x & 7, jj0 = blockIdx.x >> 3;
   // (the rows that see most of the fresh tiles first: they would make a long tail)
-  const int sg = (jj0 / q_tiles) * 8 + xcd, qt = q_tiles - 1 - jj0 % q_tiles;
+  int sg = (jj0 / q_tiles) * 8 + xcd, qt = q_tiles - 1 - jj0 % q_tiles;
+  if constexpr (PAIR) {   // of all heads of the group: the last blocks of every head, then those before them, ...
+    const int G = Hq / Hkv, per_head = (q_tiles + G - 1) / G, j = jj0 % (per_head * G), lo = j % G * per_head;
+    sg = jj0 / (per_head * G) * 8 + xcd;
+    qt = min(lo + per_head, q_tiles) - 1 - j / G;
+    if (qt < lo) return;
+  }
   if (sg >= n_groups) return;
   const int split = sg % n_splits, bg = sg / n_splits;
   const int gkv = bg % Hkv, b = bg / Hkv;
   const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g2 = lane >> 5;
   const int G = Hq / Hkv, R = G * T;
+  const int row_wave = PAIR ? wave & 3 : wave, odd = PAIR ? wave >> 2 : 0;   // PAIR: this wavefront's tiles are odd, odd + 2, ...
 
   // chunk list: lane c keeps (slot, used length) of chunk c (at most 64 chunks)
   const int32_t *trow = table + (size_t)b * tbl_stride;
@@ -645,9 +657,9 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   const int n_tiles = n_cached_tiles + i_max / TK + 1;
   const int tile_begin = (int)((long)split * n_tiles / n_splits);
   const int tile_end = (int)((long)(split + 1) * n_tiles / n_splits);
-  const int n = tile_end - tile_begin;
+  const int n_all = tile_end - tile_begin, n = PAIR ? (n_all - odd + 1) / 2 : n_all;   // this wavefront's
 
-  const int my_row = row_first + wave * 32 + l32;
+  const int my_row = row_first + row_wave * 32 + l32;
   const bool row_ok = my_row < R;
   const int row_c = row_ok ? my_row : R - 1;   // (wavefronts past the last row compute on the last row and write nothing)
   const int hg = row_c / T, my_i = row_c - hg * T;
@@ -655,7 +667,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   // A fresh tile is masked only if it reaches past the first token among this wavefront's rows (which may run over into the
   // next head) and skipped if it starts behind the last; a wavefront without rows skips every tile (first token -1 of a
   // cached one included).
-  const int w_first = row_first + __builtin_amdgcn_readfirstlane(wave) * 32, w_last = min(w_first + 31, R - 1);
+  const int w_first = row_first + __builtin_amdgcn_readfirstlane(row_wave) * 32, w_last = min(w_first + 31, R - 1);
   const bool one_head = w_first / T == w_last / T;
   const int mask_from = one_head ? max(w_first % T - (TK - 1), -1) : -1;
   const int i_hi = w_first >= R ? -2 : one_head ? w_last % T : T - 1;
@@ -707,10 +719,11 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
       const int up = __shfl_up(incl, sh, 64);
       if (lane >= sh) incl += up;
     }
-    const int first = __popcll(__ballot(incl <= tile_begin && lane < n_chunks));   // chunks wholly before tile_begin
+    const int my_begin = tile_begin + odd;
+    const int first = __popcll(__ballot(incl <= my_begin && lane < n_chunks));   // chunks wholly before it
     const int before = __builtin_amdgcn_readlane(incl - my_tiles, min(first, 63));
     enter_chunk(first);   // (a chunk found this way has keys: its tile count is positive)
-    const int off = first < n_chunks ? tile_begin - before : tile_begin - n_cached_tiles;
+    const int off = first < n_chunks ? my_begin - before : my_begin - n_cached_tiles;
     c_k += (size_t)off * (TK * D);
     c_v += (size_t)off * (TK * D);
     c_rem -= off * TK;
@@ -771,18 +784,19 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
 #pragma unroll
       for (int k = 0; k < K_INSTR; ++k)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kp + (unsigned)(min(k_row[k], valid - 1) * D + k_col[k]) * 2u),
-                                         (__attribute__((address_space(3))) void *)(kb + (wave + k * NLD) * 1024), 16, 0, kKvAux);
+                                         (__attribute__((address_space(3))) void *)(kb + ((wave & (NLD - 1)) + k * NLD) * 1024), 16, 0, kKvAux);
     } else {
 #pragma unroll
       for (int k = 0; k < K_INSTR; ++k)
         __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(kp + k_off[k]),
-                                         (__attribute__((address_space(3))) void *)(kb + (wave + k * NLD) * 1024), 16, 0, kKvAux);
+                                         (__attribute__((address_space(3))) void *)(kb + ((wave & (NLD - 1)) + k * NLD) * 1024), 16, 0, kKvAux);
     }
 #pragma unroll
     for (int k = 0; k < V_INSTR; ++k)
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(vp + v_off[k]),
-                                       (__attribute__((address_space(3))) void *)(kb + L::K_BYTES + (wave + k * NLD) * 1024), 16, 0, kKvAux);
+                                       (__attribute__((address_space(3))) void *)(kb + L::K_BYTES + ((wave & (NLD - 1)) + k * NLD) * 1024), 16, 0, kKvAux);
     step_cursor();
+    if (PAIR) step_cursor();
   };
 
   // ---- one tile: S^T = K Q^T, softmax against the lazily refreshed reference exponent, O^T += V^T P^T
@@ -896,7 +910,9 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   // ---- pipeline: tile t is computed from stage t % 3; tiles t+1 and t+2 are in flight or landed.  At the end of
   // iteration t wavefronts 0..3 wait for their share of tile t+1 (requested an iteration ago), request tile t+2 into
   // the stage that iteration t-1 read, and the barrier publishes tile t+1.
-  if (wave < NLD) {
+  if constexpr (PAIR) {
+    if (n > 0) request_next(odd);
+  } else if (wave < NLD) {
     if (n > 0) request_next(0);
     if (n > 1) request_next(1);
   }
@@ -905,16 +921,59 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
   PC_WAIT_VMCNT(0);
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  int st = 0;
-  for (int t = 0; t < n; ++t) {
-    if (q_t0 <= i_hi) tile(st);
-    step_compute_cursor();
-    PC_WAIT_VMCNT(0);   // the share of tile t+1
-    if (wave < NLD && t + 2 < n) request_next(st >= 1 ? st - 1 : NSTAGE - 1);
-    asm volatile("" ::: "memory");
+  if constexpr (PAIR) {
+    // iteration t: the pair of tiles 2 t, 2 t + 1 is computed from stages 2 (t & 1) + 0, 1 while the next pair lands in the others
+    for (int t = 0; t < (n_all + 1) / 2; ++t) {
+      if (t + 1 < n) request_next(2 * ((t + 1) & 1) + odd);
+      if (t < n && q_t0 <= i_hi) tile(2 * (t & 1) + odd);
+      step_compute_cursor();
+      step_compute_cursor();
+      PC_WAIT_VMCNT(0);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+    }
+    // the odd wavefronts' sums and outputs through LDS (stores the compiler does not see, see above), then added up in fp32
+    const unsigned to = (unsigned)(size_t)(__attribute__((address_space(3))) char *)lds + (row_wave * 64 + lane) * 16;
+    constexpr unsigned STEP = 4 * 64 * 16;
+    if (odd) {
+      typedef float f32x4_ __attribute__((ext_vector_type(4)));
+#pragma unroll
+      for (int i = 0; i < DB * 4; ++i) {
+        const f32x4_ v = {o_acc[i / 4][i % 4 * 4], o_acc[i / 4][i % 4 * 4 + 1], o_acc[i / 4][i % 4 * 4 + 2], o_acc[i / 4][i % 4 * 4 + 3]};
+        asm volatile("ds_write_b128 %0, %1" : : "v"(to + i * STEP), "v"(v) : "memory");
+      }
+      const f32x4_ v = {m_ref, l_run, 0.f, 0.f};
+      asm volatile("ds_write_b128 %0, %1" : : "v"(to + DB * 4 * STEP), "v"(v) : "memory");
+      asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+    }
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    st = st + 1 == NSTAGE ? 0 : st + 1;
+    if (odd) return;
+    const pc::f32x4 *from = (const pc::f32x4 *)(lds + (row_wave * 64 + lane) * 16);
+    const pc::f32x4 e = from[DB * 4 * STEP / 16];
+    const float m = fmaxf(m_ref, e[0]);
+    const float a0 = m_ref == -INFINITY ? 0.f : fast_exp2(m_ref - m), a1 = e[0] == -INFINITY ? 0.f : fast_exp2(e[0] - m);
+    m_ref = m;
+    l_run = l_run * a0 + e[1] * a1;
+#pragma unroll
+    for (int i = 0; i < DB * 4; ++i) {
+      const pc::f32x4 v = from[i * (STEP / 16)];
+#pragma unroll
+      for (int x = 0; x < 4; ++x) o_acc[i / 4][i % 4 * 4 + x] = o_acc[i / 4][i % 4 * 4 + x] * a0 + v[x] * a1;
+    }
+  } else {
+    int st = 0;
+    for (int t = 0; t < n; ++t) {
+      if (q_t0 <= i_hi) tile(st);
+      step_compute_cursor();
+      PC_WAIT_VMCNT(0);   // the share of tile t+1
+      if (wave < NLD && t + 2 < n) request_next(st >= 1 ? st - 1 : NSTAGE - 1);
+      asm volatile("" ::: "memory");
+      __builtin_amdgcn_s_barrier();
+      asm volatile("" ::: "memory");
+      st = st + 1 == NSTAGE ? 0 : st + 1;
+    }
   }
 
   const float l_tot = pair_sum(l_run);
@@ -1580,15 +1639,23 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   // tile between them -- twice the workgroups, half the dependent chain per tile
   const bool halved = !wide && !use8 && c.head_dim == 128 &&
                       (long)batch * c.n_kv_heads * ((R + 63) / 64) * 4 <= ctx->n_cu;
-  const int qrows = wide ? 256 : halved ? 64 : 128;
+  const int fresh_tiles = (t_fresh + TK - 1) / TK;
+  // A prompt with more fresh than cached tiles whose 256-row blocks leave CUs idle, or about fill them with blocks of very different length:
+  // 128-row blocks shared by two sets of wavefronts, longest first, no partitions.  us an attention call, 256-row blocks | these: width 1024, 1150
+  // rows (72 blocks) 35.1 | 35.4, 2176 (136) 60.8 | 50.5, 3100 (200) 92.7 | 79.7, 4224 (264) 119 | 114, 8192 (512) 279 | 329, 4 x 1000 (256)
+  // 49.4 | 57.0, 2500 over 2 chunks (160) 98 | 82; 24 heads, 1100 rows (104) 40.5 | 35.5, 2176 (208) 67.3 | 55.1, 4224 (400) 152 | 154; 14 heads of 64,
+  // 4224 rows (232) 194 | 182.
+  const long blocks128 = (long)batch * c.n_kv_heads * ((R + 127) / 128), blocks256 = (long)batch * c.n_kv_heads * ((R + 255) / 256);
+  const bool pair = n_splits <= 0 && wide && !use8 && (tbl_stride - kTblHeader) / 2 <= 64 && 2 * fresh_tiles > min_tiles && blocks128 * 8 >= ctx->n_cu * 5L &&
+                    blocks256 * 10 <= ctx->n_cu * (fresh_tiles >= 32 ? 11L : 8L);
+  const int qrows = pair ? 128 : wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
   const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
   // A prompt with more fresh than cached tiles: the workgroups are of unequal length as it is and go heaviest first, so more
   // workgroups than CUs even out without partitions (4224 fresh rows x 16 heads over nothing cached, 264 workgroups, layer of a
   // stack: 1 partition 360 us, 2 363, 4 373 with a merge of 14; before, lightest first and every fresh tile masked: 411 to 421).
-  const int fresh_tiles = (t_fresh + TK - 1) / TK;
   const bool uneven = wide && 2 * fresh_tiles > min_tiles && (long)batch * c.n_kv_heads * q_tiles >= ctx->n_cu;
-  if (n_splits <= 0 && uneven) n_splits = 1;
+  if (n_splits <= 0 && (uneven || pair)) n_splits = 1;
   if (n_splits <= 0) n_splits = choose_splits(wide ? ctx->n_cu : 2 * ctx->n_cu, (long)batch * c.n_kv_heads * q_tiles, min_tiles, cap);
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;
@@ -1606,12 +1673,17 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   }
   const float scale_log2e = 1.4426950408889634f / sqrtf((float)c.head_dim);
   const int n_groups = batch * c.n_kv_heads * n_splits;
-  dim3 grid((unsigned)(((n_groups + 7) / 8) * 8 * q_tiles));
+  const int blocks = pair ? (q_tiles + G - 1) / G * G : q_tiles;   // (a few more than there are: as many for every head of the group)
+  dim3 grid((unsigned)(((n_groups + 7) / 8) * 8 * blocks));
   prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
 #define PC_ATTN(DD, NWW, NS, ...)                                                                                     \
   hipLaunchKernelGGL((reuse_attention_kernel<DD, NWW, NS, ##__VA_ARGS__>), grid, dim3(64 * NWW), 0, stream, q, kf,     \
                      vf_blk, ks, vs, ksc, vsc, k16, v16, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, \
                      c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
+#define PC_WIDE_P(DD, PP)                                                                                                       \
+  hipLaunchKernelGGL((reuse_attention_wide_kernel<DD, PP>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev, tbl_stride, \
+                     t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
+#define PC_WIDE(DD) do { if (pair) PC_WIDE_P(DD, true); else PC_WIDE_P(DD, false); } while (0)
   if (use8 && mixed) {
     if (c.head_dim == 128) {
       if (wide) PC_ATTN(128, 8, 2, true, 1, true); else PC_ATTN(128, 4, 2, true, 1, true);
@@ -1629,18 +1701,16 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
       PC_ATTN(64, 4, 2, true);
     }
   } else if (c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64) {
-    hipLaunchKernelGGL((reuse_attention_wide_kernel<128>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev,
-                       tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups,
-                       scale_log2e, out, part_o, part_ml);
+    PC_WIDE(128);
   } else if (c.head_dim == 128) {
     if (wide) PC_ATTN(128, 8, 2); else if (halved) PC_ATTN(128, 4, 2, false, 2); else PC_ATTN(128, 4, 2);
   } else if (wide && (tbl_stride - kTblHeader) / 2 <= 64) {
-    hipLaunchKernelGGL((reuse_attention_wide_kernel<64>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev,
-                       tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups,
-                       scale_log2e, out, part_o, part_ml);
+    PC_WIDE(64);
   } else {
     if (wide) PC_ATTN(64, 8, 4); else PC_ATTN(64, 4, 4);
   }
+#undef PC_WIDE
+#undef PC_WIDE_P
 #undef PC_ATTN
   prof_end(ctx, PC_KERNEL_ATTENTION, stream);
   PC_HIP(ctx, hipGetLastError());

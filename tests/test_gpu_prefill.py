@@ -285,6 +285,31 @@ def test_long_context_kernel_on_ragged_lists(t_fresh, n_splits, head_dim):
     pc.close()
 
 
+@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch", [(330, 16, 8, 128, 4), (257, 24, 8, 128, 4), (64 * 5, 8, 8, 128, 8), (181, 14, 2, 64, 8), (1290, 2, 1, 128, 17)])
+def test_prompts_on_shared_128_row_blocks(t_fresh, Hq, Hkv, D, batch):
+    """Launches whose fresh part outweighs the cached one and whose 256-row blocks would leave CUs idle: 128-row blocks whose two sets of
+    wavefronts take every other tile -- ragged, unused and one-key chunks, an odd and an even number of tiles, one tile in all, blocks that
+    straddle heads, heads with unequal numbers of blocks."""
+    n_c, C = 3, 128
+    w = wl.make_prefill("pair", 77, "bf16", 128, Hq, Hkv, D, batch, t_fresh, n_c, C, 8)
+    g = np.random.default_rng(4)
+    w.used_len[:] = g.integers(1, C + 1, size=(batch, n_c))
+    w.used_len[0] = [128, 128, 128]
+    w.used_len[1] = [0, 65, 1]
+    w.used_len[2] = [0, 0, 0]
+    n_chunks = [3, 3, 3, 0] + [int(x) for x in g.integers(0, n_c + 1, size=batch - 4)]
+    pc = make_ctx(w)
+    fill_slots(pc, w, w.slot_ids.reshape(-1))
+    q, kf, vf = pc.percache_qkv_rope(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len, n_chunks=n_chunks)
+    out = pc.percache_attention_reuse(0, q, kf, vf, w.slot_ids, w.used_len, n_chunks=n_chunks)
+    torch.cuda.synchronize()
+    for b in range(min(batch, 5)):
+        sk, sv, ids = w.compact_store(b)
+        O, _, _, _ = oracle.prefill_reuse(w.X[b], w.Wqkv, w.n_q_heads, w.n_kv_heads, w.head_dim, w.rope_theta, sk, sv, ids[:n_chunks[b]], w.used_len[b][:n_chunks[b]])
+        check_close(host(out[b]), O, f"128-row blocks T={t_fresh} b={b} chunks={list(w.used_len[b][:n_chunks[b]])}")
+    pc.close()
+
+
 @pytest.mark.parametrize("t_fresh,n_splits,head_dim,kv_fp8", [(601, 0, 128, False), (704, 3, 128, False), (1025, 0, 64, False), (601, 0, 128, True)])
 def test_long_context_kernel_on_long_fresh_parts(t_fresh, n_splits, head_dim, kv_fp8):
     """More fresh than cached keys: tiles a wavefront masks, takes whole or skips by its first and last token, row blocks
