@@ -986,12 +986,12 @@ static Blocks blocks_of(const percache_config &c, int M, int ffn, int n_splits) 
 static size_t dense_elems(const percache_config &c, int M) { return align_up((size_t)M * c.n_kv_heads * c.head_dim, 128); }
 
 // Which steps take this path: beyond a few rows the rows themselves (polled by every workgroup, read out of LDS by every wavefront) cost what
-// the launches did.  us a layer, launch by launch | here: width 1024, 2 rows 34.7 | 33.4 (64 tiles each), 3 rows 32.0 | 32.1, 4 rows 33.0 |
-// 31.1, 2 x 2 rows 31.5 | 26.7, 6 rows 34.8 | 37.7, 8 rows 38.4 | 40.1; width 896, 2 rows 29.1 | 25.4, 4 rows 31.1 | 28.6, 8 rows 32.6 | 32.5;
-// width 3072, 2 rows 61.7 | 58.1, 3 rows 63.7 | 62.9, 4 rows 64.7 | 68.4.
+// the launches did.  us a layer, launch by launch | here: width 1024, 2 rows 30.3 | 24.3 (12 tiles each), 35.3 | 33.8 (64 tiles), 3 rows
+// 32.5 | 28.8, 4 rows 34.1 | 31.3, 2 x 2 rows 31.8 | 26.7, 6 rows 34.8 | 37.7, 8 rows 38.4 | 40.1; width 896, 2 rows 29.1 | 25.4, 4 rows
+// 31.2 | 28.7, 8 rows 32.6 | 32.5; width 3072, 1 row 53.9 | 46.2, 2 rows 55.7 | 58.1, 3 rows 57.6 | 63.4.
 static bool shape_fits(const percache_config &c, int32_t batch, int32_t t_fresh) {
   const long R = (long)(c.n_q_heads / c.n_kv_heads) * t_fresh, M = (long)batch * t_fresh;
-  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > (M > 1 ? 9216 : 1 << 20)) return false;
+  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > (M > 1 ? 4096 : 1 << 20)) return false;
   // the merge of the wavefronts' outputs, in the ring's place
   return (size_t)kWaves * R * (c.head_dim + 6) * 4 + R * 64 <= (size_t)kRing;
 }
