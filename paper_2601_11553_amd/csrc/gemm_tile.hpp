@@ -148,7 +148,7 @@ __device__ __forceinline__ void mainloop(char *lds, WRow w_row, const T *__restr
 // The same main loop for a workgroup of 8 wavefronts on 256 weight rows x 64*NTB tokens: two 128-row halves side by
 // side over one token tile, so the token rows are brought in once for twice the features (L2 -> LDS bytes per flop
 // drop by a third at NTB = 3).  Wavefront w: half w >> 2, feature blocks (fb_lo, fb_hi) counted over all 8 blocks of
-// 32 rows, token group wt.  One workgroup per CU (2 x 56 KB of LDS at NTB = 3).
+// 32 rows, token group wt.  One workgroup per CU (2 x 56 KB of LDS at NTB = 3, 2 x 72 KB at 5).
 template <int NTB>
 struct WideShape {
   static constexpr int NWV = 8, BFW = 256;
@@ -171,31 +171,36 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
   using S = WideShape<NTB>;
   using V8 = typename Vec8<T>::type;
   static_assert(BK == 64, "four quarters of 16 k-elements");
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int l32 = lane & 31, g = lane >> 5;
   const bool loads_w = wave < 4;
   constexpr int W_PER = S::W_BYTES / 1024 / 4, X_PER = S::X_BYTES / 1024 / 4;  // instructions per wavefront and stage
-  static_assert(W_PER == 8 && X_PER <= 8 && X_PER >= 4, "request split below");
-  const T *src[8];
+  constexpr int PER = X_PER > W_PER ? X_PER : W_PER, PART = (PER + 2) / 3;          // requested in three parts
+  static_assert(W_PER == 8 && X_PER >= 4, "request split below");
+  // (one scalar base and 32-bit lane offsets: pointers of their own would not leave room for the operands of 320 tokens)
+  const char *const base = (const char *)(loads_w ? w_row(0) : X);
+  unsigned src[PER];
 #pragma unroll
-  for (int k = 0; k < 8; ++k) {
+  for (int k = 0; k < PER; ++k) {
     const int row = ((wave & 3) * (loads_w ? W_PER : X_PER) + (k < (loads_w ? W_PER : X_PER) ? k : 0)) * 8 + (lane >> 3);
-    src[k] = (loads_w ? w_row(row) : X + (size_t)min(m0 + row, M - 1) * ldx) + (((lane & 7) ^ swz128(row)) * 8);
+    const T *at = (loads_w ? w_row(row) : X + (size_t)min(m0 + row, M - 1) * ldx) + (((lane & 7) ^ swz128(row)) * 8);
+    src[k] = (unsigned)((const char *)at - base);
   }
   char *const dst = lds + (loads_w ? 0 : S::W_BYTES) + (wave & 3) * (loads_w ? W_PER : X_PER) * 1024;
   const int nk = K / BK;
   int f_kt = 0;  // the k-step the next request brings (past the last one: the last one again, into a stage nobody reads)
   // instructions k0 .. k1 - 1 of that request (a token wavefront has fewer: the surplus is skipped)
   auto request_part = [&](int st, int k0, int k1) __attribute__((always_inline)) {
+    const char *const from = base + (size_t)f_kt * (BK * sizeof(T));
     if (loads_w) {
 #pragma unroll
-      for (int k = k0; k < k1; ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[k] + f_kt * BK),
+      for (int k = k0; k < (k1 < W_PER ? k1 : W_PER); ++k)
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + src[k]),
                                          (__attribute__((address_space(3))) void *)(dst + st * S::STAGE + k * 1024), 16, 0, 0);
     } else {
 #pragma unroll
       for (int k = k0; k < (k1 < X_PER ? k1 : X_PER); ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[k] + f_kt * BK),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + src[k]),
                                          (__attribute__((address_space(3))) void *)(dst + st * S::STAGE + k * 1024), 16, 0, 0);
     }
   };
@@ -237,23 +242,23 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
 #pragma unroll
       for (int r = 0; r < 16; ++r) acc[a][t][r] = 0.f;
 
-  request_part(0, 0, 8);
+  request_part(0, 0, PER);
   advance();
   wait_vmcnt0();
   __builtin_amdgcn_s_barrier();
   asm volatile("" ::: "memory");
-  request_part(1, 0, 3);  // (the rest of it under the first two quarters below)
+  request_part(1, 0, PART);  // (the rest of it under the first two quarters below)
   read_ops(0, 0, 0);
   for (int kt = 0; kt < nk; ++kt) {
     const int st = kt & 1;
-    request_part(st ^ 1, 3, 6);
+    request_part(st ^ 1, PART, 2 * PART);
     read_ops(1, st, 1);
     mma_ops(0);
-    interleave(3);
-    request_part(st ^ 1, 6, 8);
+    interleave(PART);
+    request_part(st ^ 1, 2 * PART, PER);
     read_ops(0, st, 2);
     mma_ops(1);
-    interleave(2);
+    interleave(PER - 2 * PART);
     advance();
     read_ops(1, st, 3);
     mma_ops(0);
@@ -263,10 +268,10 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
     asm volatile("" ::: "memory");
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
-    request_part(st, 0, 3);    // k-step kt + 2
-    read_ops(0, st ^ 1, 0);    // (past the last k-step: whatever the other stage holds, never multiplied)
+    request_part(st, 0, PART);  // k-step kt + 2
+    read_ops(0, st ^ 1, 0);     // (past the last k-step: whatever the other stage holds, never multiplied)
     mma_ops(1);
-    interleave(3);
+    interleave(PART);
   }
   wait_vmcnt0();  // (the surplus request of the last k-steps)
   __builtin_amdgcn_s_barrier();

@@ -495,18 +495,30 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
       if (best < 0 || cost < best) { best = cost; ntb = cand; }
     }
   }
-  // Two heads per workgroup (8 wavefronts, one workgroup per CU) when all its tiles fit one round: the token rows
-  // are brought into LDS once for twice the features.
+  // Two heads per workgroup (8 wavefronts, one workgroup per CU) while all its tiles fit one round: the token rows are
+  // brought into LDS once for twice the features.  The narrowest of 192, 256 and 320 tokens that does it; against the
+  // tiles above (one head, up to 192 tokens, rounds of 2 * n_cu), us a launch:
+  //   4096 features, K = 1024: 3700 rows 46 | 49, 4096 rows 48 | 51, 4224 rows 52.3 | 54.1, 5120 rows 55.5 | 65.0
+  //   5120 features, K = 3072: 2560 rows 85 | 101, 3072 rows 94 | 108, 3800 rows 112 | 142
+  // 320 tokens take 252 registers a lane of the 256, and 147 KB of LDS: there is no wider one.
   const int n_heads_all = c.n_q_heads + 2 * c.n_kv_heads;
   __bf16 *vb_large = (v_blk && v_blk_done && t_fresh % 64 == 0) ? v_blk : nullptr;  // the large tiles lay V out for the attention kernel too
   if (vb_large) *v_blk_done = true;
-  if (c.head_dim == 128 && !extras.any() && n_heads_all % 2 == 0 && M >= 1024 &&
-      (long)(n_heads_all / 2) * ((M + 191) / 192) <= ctx->n_cu) {
-    constexpr int lds_bytes = pc::gemm::WideShape<3>::LDS_BYTES;
-    PC_HIP(ctx, hipFuncSetAttribute((const void *)qkv_rope_kernel<128, 3, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
-    prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);
-    hipLaunchKernelGGL((qkv_rope_kernel<128, 3, false, true>), dim3(n_heads_all / 2, (M + 191) / 192), dim3(512), lds_bytes, stream, x, w, M,
-                       c.hidden, t_fresh, c.n_q_heads, c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb_large);
+  int wide = 0;   // its 64-token blocks
+  if (c.head_dim == 128 && !extras.any() && n_heads_all % 2 == 0 && M >= 1024)
+    for (int cand = 3; cand <= 5 && !wide; ++cand)
+      if ((long)(n_heads_all / 2) * ((M + 64 * cand - 1) / (64 * cand)) <= ctx->n_cu) wide = cand;
+  if (wide) {
+#define PC_WIDE(NN)                                                                                                                                  \
+  do {                                                                                                                                               \
+    constexpr int lds_bytes = pc::gemm::WideShape<NN>::LDS_BYTES;                                                                                     \
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)qkv_rope_kernel<128, NN, false, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));      \
+    prof_begin(ctx, PC_KERNEL_QKV_ROPE, stream);                                                                                                     \
+    hipLaunchKernelGGL((qkv_rope_kernel<128, NN, false, true>), dim3(n_heads_all / 2, (M + 64 * NN - 1) / (64 * NN)), dim3(512), lds_bytes, stream, x, w, \
+                       M, c.hidden, t_fresh, c.n_q_heads, c.n_kv_heads, table_dev, tbl_stride, rope, q, k, v, extras, vb_large);                       \
+  } while (0)
+    if (wide == 3) PC_WIDE(3); else if (wide == 4) PC_WIDE(4); else PC_WIDE(5);
+#undef PC_WIDE
     prof_end(ctx, PC_KERNEL_QKV_ROPE, stream);
     PC_HIP(ctx, hipGetLastError());
     return PC_OK;

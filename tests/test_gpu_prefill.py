@@ -126,6 +126,31 @@ def test_qkv_rope_matches_oracle(shape):
     pc.close()
 
 
+@pytest.mark.parametrize("hidden,n_q_heads,n_kv_heads,batch,t_fresh", [
+    (64, 28, 2, 25, 128),    # 256 tokens: one k-step, 13 token tiles, the last one of half its rows
+    (192, 30, 1, 1, 4096),   # 256 tokens: every tile whole, an odd number of k-steps
+    (128, 28, 2, 11, 384),   # 320 tokens: prompts that straddle tiles, 64 rows in the last one
+    (192, 36, 2, 3, 1101),   # 320 tokens: 20 x 11 tiles, ragged prompts
+])
+def test_two_head_tiles_of_256_and_320_tokens(hidden, n_q_heads, n_kv_heads, batch, t_fresh):
+    """Projections whose 192-token two-head tiles would take a second round of the CUs: q, k and v against the oracle; where the prompts are
+    whole 64-key blocks the tiles lay V out for the attention themselves, which then reads the same values as from the packed copy."""
+    w = wl.make_prefill("proj_wide", 5, "bf16", hidden, n_q_heads, n_kv_heads, 128, batch, t_fresh, 1, 64, 4)
+    pc = make_ctx(w)
+    fill_slots(pc, w, w.slot_ids.reshape(-1))
+    q, k, v = pc.percache_qkv_rope(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)
+    apart = pc.percache_attention_reuse(0, q, k, v, w.slot_ids, w.used_len)
+    whole = pc.percache_prefill_reuse(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)
+    torch.cuda.synchronize()
+    for b in range(batch):
+        Q, K, V = oracle.qkv_rope(w.X[b], w.Wqkv, w.n_q_heads, w.n_kv_heads, w.head_dim, int(w.l_pre[b]), w.rope_theta)
+        check_close(host(q[b]), Q, f"q b={b}")
+        check_close(host(k[b]), K, f"k b={b}")
+        check_close(host(v[b]), V, f"v b={b}")
+    assert torch.equal(apart, whole)
+    pc.close()
+
+
 # --------------------------------------------------------------------------- config 0 (tiny layer, D = 64)
 def _config0_store():
     w = wl.config0("bf16")
