@@ -123,15 +123,11 @@ __global__ __launch_bounds__(512) void linear_residual_deep_kernel(const __bf16 
 // features; wavefront wf owns gate block wf and up block wf + 2, so both halves of a product sit in one lane.
 // ---------------------------------------------------------------------------------------------------
 template <int NTB>
-__global__ __launch_bounds__(256, 2) void linear_swiglu_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ Wg,
-                                                               const __bf16 *__restrict__ Wu, __bf16 *__restrict__ Y, int M,
-                                                               int F, int K) {
-  constexpr int BT = 64 * NTB;
-  __shared__ __align__(16) char lds[pc::gemm::Shape<NTB>::LDS_BYTES];
+__device__ __forceinline__ void swiglu_tile(char *lds, const __bf16 *__restrict__ A, const __bf16 *__restrict__ Wg, const __bf16 *__restrict__ Wu,
+                                            __bf16 *__restrict__ Y, int f0, int m0, int M, int F, int K) {
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
   const int wf = wave & 1, wt = wave >> 1;
   const int l32 = lane & 31, g = lane >> 5;
-  const int f0 = blockIdx.x * (BF / 2), m0 = blockIdx.y * BT;
   f32x16 acc[2][NTB];
   pc::gemm::mainloop<NTB>(
       lds, [&](int row) __attribute__((always_inline)) { return (row < 64 ? Wg : Wu) + (size_t)(f0 + (row & 63)) * K; }, A, K, m0, M, K,
@@ -152,6 +148,20 @@ __global__ __launch_bounds__(256, 2) void linear_swiglu_kernel(const __bf16 *__r
       if (ok) *(uint2 *)(Y + (size_t)m * F + f0 + wf * 32 + q4 * 8 + g * 4) = pack4(o[0], o[1], o[2], o[3]);
     }
   }
+}
+// Token tiles of 64 * NTB rows, the first n_tall of them 64 rows taller (swiglu_tall); dynamic LDS: Shape<NTB or NTB + 1>::LDS_BYTES.
+template <int NTB, bool TALL>
+__global__ __launch_bounds__(256, 2) void linear_swiglu_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ Wg,
+                                                               const __bf16 *__restrict__ Wu, __bf16 *__restrict__ Y, int M,
+                                                               int F, int K, int n_tall) {
+  extern __shared__ __align__(16) char lds[];
+  const int f0 = blockIdx.x * (BF / 2), y = blockIdx.y;
+  if constexpr (TALL)
+    if (y < n_tall) {
+      swiglu_tile<NTB + 1>(lds, A, Wg, Wu, Y, f0, y * 64 * (NTB + 1), M, F, K);
+      return;
+    }
+  swiglu_tile<NTB>(lds, A, Wg, Wu, Y, f0, 64 * (NTB * y + (TALL ? n_tall : 0)), M, F, K);
 }
 
 // ---------------------------------------------------------------------------------------------------
@@ -344,12 +354,28 @@ pc_status launch_linear_residual(percache_ctx *ctx, const __bf16 *a, const __bf1
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
+// How many of the first token tiles take 192 rows instead of 128, where that saves the launch its last round of two workgroups per CU (a
+// taller tile costs the slot it is in half a tile, the round a whole one for the few tiles left over).  us a layer, 128 rows | with taller
+// ones: width 1024, 1300 rows (48 feature tiles, 528 tiles) 148.5 | 142, 1900 163.4 | 160.3, 4224 (1584 tiles, 2 taller) 291 | 287; width 896,
+// 1024 rows 102.6 | 99.0; width 3072, 2176 601 | 589, 4224 1187 | 1165.
+int swiglu_tall(int n_cu, int M, int fx) {
+  const long slots = 2L * n_cu, nb = (M + 63) / 64, rounds = ((nb + 1) / 2 * fx + slots - 1) / slots;
+  const long column = (rounds - 1) * slots / fx, tall = nb - 2 * column;   // (token tiles of a feature tile that one round less has room for)
+  return column > 0 && tall > 0 && tall <= column && tall * fx <= slots ? (int)tall : 0;
+}
 pc_status launch_linear_swiglu(percache_ctx *ctx, const __bf16 *a, const __bf16 *wg, const __bf16 *wu, __bf16 *y, int M, int F,
                                int K, hipStream_t s) {
-  const bool big = M > 64 * 3;
-  dim3 grid(F / (BF / 2), big ? (M + 127) / 128 : (M + 63) / 64);
-  if (big) hipLaunchKernelGGL(linear_swiglu_kernel<2>, grid, dim3(256), 0, s, a, wg, wu, y, M, F, K);
-  else hipLaunchKernelGGL(linear_swiglu_kernel<1>, grid, dim3(256), 0, s, a, wg, wu, y, M, F, K);
+  const int fx = F / (BF / 2);
+  if (M <= 64 * 3) {
+    hipLaunchKernelGGL((linear_swiglu_kernel<1, false>), dim3(fx, (M + 63) / 64), dim3(256), pc::gemm::Shape<1>::LDS_BYTES, s, a, wg, wu, y, M, F, K, 0);
+  } else if (const int tall = swiglu_tall(ctx->n_cu, M, fx)) {
+    constexpr int lds_bytes = pc::gemm::Shape<3>::LDS_BYTES;
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)linear_swiglu_kernel<2, true>, hipFuncAttributeMaxDynamicSharedMemorySize, lds_bytes));
+    const int rest = (M + 63) / 64 - 3 * tall;
+    hipLaunchKernelGGL((linear_swiglu_kernel<2, true>), dim3(fx, tall + (rest > 0 ? (rest + 1) / 2 : 0)), dim3(256), lds_bytes, s, a, wg, wu, y, M, F, K, tall);
+  } else {
+    hipLaunchKernelGGL((linear_swiglu_kernel<2, false>), dim3(fx, (M + 127) / 128), dim3(256), pc::gemm::Shape<2>::LDS_BYTES, s, a, wg, wu, y, M, F, K, 0);
+  }
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }

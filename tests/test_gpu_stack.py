@@ -404,6 +404,18 @@ def test_residual_projection_in_one_round(H, F, batch, t_fresh):
     check_hidden(host(h_out).reshape(-1, H), ref.cpu().numpy().reshape(-1, H), f"H={H} F={F} rows={batch * t_fresh}")
 
 
+@pytest.mark.parametrize("H,F,batch,t_fresh", [
+    (128, 3072, 1, 1281),   # 21 blocks of 64 rows over 48 feature tiles: one token tile of 192 rows, 9 of 128, one row in the last block
+    (256, 3072, 3, 640),    # 30 blocks: 192-row tiles only
+    (128, 3072, 4, 787),    # 50 blocks, two full rounds: 8 tiles of 192 rows, 13 of 128, the last block of 12 rows
+    (128, 4864, 2, 513),    # 76 feature tiles, 17 blocks: 5 tiles of 192 rows, one of 128
+    (384, 1088, 4, 1013),   # 17 feature tiles, 64 blocks: 4 tiles of 192 rows, 26 of 128, six k-steps
+])
+def test_gate_up_tiles_of_two_heights(H, F, batch, t_fresh):
+    """gate/up launches whose 128-row tiles alone would leave a few for a round of their own."""
+    test_residual_projection_in_one_round(H, F, batch, t_fresh)
+
+
 def test_oversized_projection_is_refused_before_anything_runs():
     """A QKV weight of 2^31 elements is past what the kernels index: every call that projects refuses it, few rows or many (the
     pointers here are to a few bytes, nothing may read them)."""
