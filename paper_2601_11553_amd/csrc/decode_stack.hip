@@ -991,7 +991,8 @@ static size_t dense_elems(const percache_config &c, int M) { return align_up((si
 // 31.2 | 28.7, 8 rows 32.6 | 32.5; width 3072, 1 row 53.9 | 46.2, 2 rows 55.7 | 58.1, 3 rows 57.6 | 63.4.
 static bool shape_fits(const percache_config &c, int32_t batch, int32_t t_fresh) {
   const long R = (long)(c.n_q_heads / c.n_kv_heads) * t_fresh, M = (long)batch * t_fresh;
-  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > (M > 1 ? 4096 : 1 << 20)) return false;
+  // (one row of any width that a model has: past 390 000 columns the row's sums of squares would take all of LDS)
+  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > (M > 1 ? 4096 : 1 << 18)) return false;
   // the merge of the wavefronts' outputs, in the ring's place
   return (size_t)kWaves * R * (c.head_dim + 6) * 4 + R * 64 <= (size_t)kRing;
 }
