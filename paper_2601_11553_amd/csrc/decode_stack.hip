@@ -1009,8 +1009,15 @@ size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_
 }
 
 // (at most four tiles, two rounds, to a piece: more of them want the ring of decode_attention_kernel)
+// Several rows: only while the pieces leave a third of the CUs to the items around them -- past that the pieces of one layer hold the
+// workgroups that should have its o_proj and gate/up weights on their way.  us a step of two layers, launch by launch | here (pieces for 256 CUs):
+// width 1024, 2 rows 257 | 223 (160), 260 | 262 (216), 3 rows 258 | 227 (144), 262 | 271 (240), 306 | 350 (512), 4 rows 259 | 259 (192),
+// 283 | 311 (448); width 896, 2 rows 271 | 250 (168), 280 | 284 (232), 3 rows 267 | 246 (156), 273 | 293 (204), 4 rows 266 | 256 (144),
+// 269 | 291 (208), 289 | 340 (464).  One row keeps its gain up to a piece a CU (width 1024, 100 tiles 289 | 250).
 bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int max_tiles) {
-  return shape_fits(c, batch, t_fresh) && max_tiles + 2 <= 4 * splits_for(c, n_cu, batch, t_fresh, max_tiles);
+  if (!shape_fits(c, batch, t_fresh)) return false;
+  const int ns = splits_for(c, n_cu, batch, t_fresh, max_tiles);
+  return max_tiles + 2 <= 4 * ns && (batch * t_fresh == 1 || 3L * batch * c.n_kv_heads * ns <= 2L * n_cu);
 }
 
 template <int D>
