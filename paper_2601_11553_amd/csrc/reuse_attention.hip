@@ -1644,10 +1644,13 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   // 128-row blocks shared by two sets of wavefronts, longest first, no partitions.  us an attention call, 256-row blocks | these: width 1024, 1150
   // rows (72 blocks) 35.1 | 35.4, 2176 (136) 60.8 | 50.5, 3100 (200) 92.7 | 79.7, 4224 (264) 119 | 114, 8192 (512) 279 | 329, 4 x 1000 (256)
   // 49.4 | 57.0, 2500 over 2 chunks (160) 98 | 82; 24 heads, 1100 rows (104) 40.5 | 35.5, 2176 (208) 67.3 | 55.1, 4224 (400) 152 | 154; 14 heads of 64,
-  // 4224 rows (232) 194 | 182.
+  // 4224 rows (232) 194 | 182.  At head size 64 only where 256-row blocks would not be cut into partitions, whose merge is cheap there: a layer's
+  // prefill, width 896 and 14 heads, 1964 rows (108 blocks) 188 | 192, 2564 (142) 208 | 246, 3364 (184) 237 | 305, but 3564 (196, one
+  // partition) 352 | 316.
   const long blocks128 = (long)batch * c.n_kv_heads * ((R + 127) / 128), blocks256 = (long)batch * c.n_kv_heads * ((R + 255) / 256);
   const bool pair = n_splits <= 0 && wide && !use8 && (tbl_stride - kTblHeader) / 2 <= 64 && 2 * fresh_tiles > min_tiles && blocks128 * 8 >= ctx->n_cu * 5L &&
-                    blocks256 * 10 <= ctx->n_cu * (fresh_tiles >= 32 ? 11L : 8L);
+                    blocks256 * 10 <= ctx->n_cu * (fresh_tiles >= 32 ? 11L : 8L) &&
+                    (c.head_dim == 128 || choose_splits(ctx->n_cu, blocks256, min_tiles, max_splits_for(c, ctx->n_cu, batch, t_fresh)) == 1);
   const int qrows = pair ? 128 : wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
   const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);

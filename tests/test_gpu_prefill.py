@@ -310,7 +310,7 @@ def test_long_context_kernel_on_ragged_lists(t_fresh, n_splits, head_dim):
     pc.close()
 
 
-@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch", [(330, 16, 8, 128, 4), (257, 24, 8, 128, 4), (64 * 5, 8, 8, 128, 8), (181, 14, 2, 64, 8), (1290, 2, 1, 128, 17)])
+@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch", [(330, 16, 8, 128, 4), (257, 24, 8, 128, 4), (64 * 5, 8, 8, 128, 8), (181, 14, 2, 64, 8), (905, 14, 2, 64, 4), (1290, 2, 1, 128, 17)])
 def test_prompts_on_shared_128_row_blocks(t_fresh, Hq, Hkv, D, batch):
     """Launches whose fresh part outweighs the cached one and whose 256-row blocks would leave CUs idle: 128-row blocks whose two sets of
     wavefronts take every other tile -- ragged, unused and one-key chunks, an odd and an even number of tiles, one tile in all, blocks that
