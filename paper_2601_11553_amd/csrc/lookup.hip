@@ -98,10 +98,14 @@ template <int CHB>
 __device__ __forceinline__ int row_swz(int row) { return CHB >= 256 ? (row & 15) : ((row >> 1) & 7); }
 
 // The merge of the workgroups' lists inside the launch that makes them (null marks: by lookup_finalize_kernel).  Every workgroup stores its
-// lists straight to memory (device scope) and then a mark, a number that no other call uses; the last one waits for all the marks, merges, and
-// clears them, so that a captured call can be replayed.  It holds one CU while it waits for workgroups that wait for nothing.
+// lists straight to memory (device scope), then a mark, a number that no other call uses, and then looks at the marks of all: who finds them
+// all there merges.  Nobody waits for another workgroup, so it does not matter in which order they were started.  The workgroup whose mark
+// is the last one to reach memory finds all of them (it looks behind its own store) unless another one that did has cleared them; two that
+// arrive together may both merge, and write the same values.  Who merges clears the marks, every one of which has arrived by then: a captured
+// call finds none of its last replay.
+constexpr int kInLaunchGrid = 64;   // (one lane looks at one mark)
 struct InLaunch {
-  unsigned long long *marks;   // [workgroups], whatever they hold
+  unsigned long long *marks;   // [workgroups, at most kInLaunchGrid], whatever they hold
   unsigned long long mark;
   float tau;
   int k;
@@ -157,19 +161,21 @@ __device__ __forceinline__ void merge_workgroup_lists(TopK<KL> (&best)[NPB], cha
 
 // See InLaunch; a wavefront a probe.  The sums of the probe's norm are added up as lookup_finalize_kernel does.
 template <int K>
-__device__ __forceinline__ void merge_in_launch(const InLaunch &f, const Best *partial, int stride, const _Float16 *__restrict__ probes, int n_probes, int d) {
+__device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, const Best *partial, int stride, const _Float16 *__restrict__ probes, int n_probes,
+                                                int d) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the lists are in memory
   __syncthreads();
-  if (tid == 0) __hip_atomic_store(f.marks + blockIdx.x, f.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
-  if ((int)blockIdx.x != n - 1) return;
-  for (int w = tid; w < n; w += 256)
-    for (int tries = 0; tries < 1 << 18; ++tries) {   // (a fraction of a second: no wait gets there, the others were started first)
-      if (__hip_atomic_load(f.marks + w, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) == f.mark) break;
-      __builtin_amdgcn_s_sleep(2);
-    }
+  if (wave == 0) {
+    if (lane == 0) __hip_atomic_store(f.marks + blockIdx.x, f.mark, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+    asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // this one's mark too, before it looks
+    const unsigned long long seen = lane < n ? __hip_atomic_load(f.marks + lane, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT) : f.mark;
+    if (lane == 0) *(int *)smem = 0;
+    if (__ballot(seen != f.mark) == 0 && lane == 0) *(int *)smem = 1;
+  }
   __syncthreads();
-  for (int w = tid; w < n; w += 256) __hip_atomic_store(f.marks + w, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
+  if (!*(const int *)smem) return;
+  if (tid < n) __hip_atomic_store(f.marks + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int p = wave; p < n_probes; p += 4) {
     const u32x4 *src = (const u32x4 *)(probes + (size_t)p * d);
     float tot = 0.f;
@@ -410,7 +416,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   if (K == 0) return;  // per-row mode: everything has been written
   merge_workgroup_lists<NPB, KL>(best, smem, partial, NPB == 1 && in_launch.marks);
   if constexpr (NPB == 1 && K > 0) {
-    if (in_launch.marks) merge_in_launch<KL>(in_launch, partial, NPB * 16, probes, n_probes, d);
+    if (in_launch.marks) merge_in_launch<KL>(in_launch, smem, partial, NPB * 16, probes, n_probes, d);
   }
 }
 
@@ -1239,7 +1245,7 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     // than lanes (20 000 rows, 256 lists): best row of 1 11.3 | 9.7, of 8 11.5 | 12.1, 3 best of 1 14.1 | 14.7, of 8 14.4 | 20.8; behind a long stream
     // the merge apart is hidden already (200 000 rows 66.5 | 67.2).
     InLaunch il{};
-    if (sh.grid <= 64 && (n_probes <= 4 || (n_probes <= kInLaunchUpTo && k <= 4)) && workspace_dev != ctx->static_scratch)
+    if (sh.grid <= kInLaunchGrid && (n_probes <= 4 || (n_probes <= kInLaunchUpTo && k <= 4)) && workspace_dev != ctx->static_scratch)
       il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : k <= 4 ? 4 : kMaxTopK)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit};
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     // (up to four best rows out of lists of four: what the pass spends on a list of eight shows beside the stream, us a pass, eight | four: 3 best

@@ -417,3 +417,47 @@ def test_merge_inside_the_launch_equals_the_merge_apart(rows, dim, k):
         call(probes[:1].contiguous())
         torch.cuda.synchronize()
         assert all(torch.equal(a[2:7], b) for a, b in zip(apart, out))
+
+
+@pytest.mark.parametrize("rows,dim,k", [(4096, 768, 1), (4096, 768, 3), (2000, 2048, 8)])
+def test_merge_inside_the_launch_beside_kernels_that_hold_the_cus(rows, dim, k):
+    """Lookups whose workgroups get a CU only as another stream's long workgroups leave theirs, in whatever order that is: the bits of the call
+    alone, and no mark is left behind the lists for a later call with the same one (a captured call's)."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + dim)
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=1, slot_capacity=64, max_pos=64, bank_capacity=rows, emb_dim=dim,
+                  device=DEV)
+    pc.percache_bank_put(0, torch.randn((rows, dim), generator=g, device=DEV).half())
+    probes = torch.randn((4, dim), generator=g, device=DEV).half()
+
+    def call():
+        return pc.percache_lookup(probes, 0.05) if k == 1 else pc.percache_lookup_topk(probes, k)
+    alone = [t.clone() for t in call()]
+    pc._lookup_ws.fill_(255)
+    torch.cuda.synchronize()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        captured = call()
+    other = Percache(n_layers=1, hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=1, slot_capacity=64, max_pos=64, device=DEV)
+    kv = torch.randn((8 << 20) // 2, generator=g, device=DEV).bfloat16()
+    side = torch.cuda.Stream()
+    with torch.cuda.stream(side):
+        other.percache_peak_attention_tile_loop(kv, 16)
+    torch.cuda.synchronize()
+    outs = []
+    for i in range(8):
+        with torch.cuda.stream(side):
+            for tiles in (700, 64):      # (of a millisecond, of a tenth)
+                other.percache_peak_attention_tile_loop(kv, tiles)
+        for _ in range(6):
+            outs.append(call())
+            graph.replay()
+            outs.append([t.clone() for t in captured])
+    torch.cuda.synchronize()
+    for out in outs:
+        assert all(torch.equal(a, b) for a, b in zip(alone, out))
+    n_wg = min(torch.cuda.get_device_properties(0).multi_processor_count, -(-(-(-rows // 16)) // 4))
+    at = (-pc._lookup_ws.data_ptr()) % 256 + n_wg * 16 * (1 if k == 1 else 4 if k <= 4 else 8) * 8
+    assert n_wg <= 64 and not pc._lookup_ws[at:at + n_wg * 8].any()
+    pc.close()
+    other.close()
