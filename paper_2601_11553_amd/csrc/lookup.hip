@@ -100,9 +100,8 @@ __device__ __forceinline__ int row_swz(int row) { return CHB >= 256 ? (row & 15)
 // The merge of the workgroups' lists inside the launch that makes them (null marks: by lookup_finalize_kernel).  Every workgroup stores its
 // lists straight to memory (device scope), then a mark, a number that no other call uses, and then looks at the marks of all: who finds them
 // all there merges.  Nobody waits for another workgroup, so it does not matter in which order they were started.  The workgroup whose mark
-// is the last one to reach memory finds all of them (it looks behind its own store) unless another one that did has cleared them; two that
-// arrive together may both merge, and write the same values.  Who merges clears the marks, every one of which has arrived by then: a captured
-// call finds none of its last replay.
+// is the last one to reach memory finds all of them (it looks behind its own store); others that arrive with it may too, and write the same
+// values.
 constexpr int kInLaunchGrid = 64;   // (one lane looks at one mark)
 struct InLaunch {
   unsigned long long *marks;   // [workgroups, at most kInLaunchGrid], whatever they hold
@@ -175,7 +174,6 @@ __device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, c
   }
   __syncthreads();
   if (!*(const int *)smem) return;
-  if (tid < n) __hip_atomic_store(f.marks + tid, 0ull, __ATOMIC_RELAXED, __HIP_MEMORY_SCOPE_AGENT);
   for (int p = wave; p < n_probes; p += 4) {
     const u32x4 *src = (const u32x4 *)(probes + (size_t)p * d);
     float tot = 0.f;
@@ -414,8 +412,9 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
 
   if (K == 0) return;  // per-row mode: everything has been written
-  merge_workgroup_lists<NPB, KL>(best, smem, partial, NPB == 1 && in_launch.marks);
-  if constexpr (NPB == 1 && K > 0) {
+  constexpr bool CAN_MERGE = NPB == 1 && K > 0 && K <= 4;
+  merge_workgroup_lists<NPB, KL>(best, smem, partial, CAN_MERGE && in_launch.marks);
+  if constexpr (CAN_MERGE) {
     if (in_launch.marks) merge_in_launch<KL>(in_launch, smem, partial, NPB * 16, probes, n_probes, d);
   }
 }
@@ -1130,8 +1129,14 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
   return PC_OK;
 }
 
+constexpr int kInLaunchProbes = 4;   // (one wavefront of the merging workgroup each)
+bool being_captured(hipStream_t st) {
+  hipStreamCaptureStatus status = hipStreamCaptureStatusNone;
+  if (hipStreamIsCapturing(st, &status) == hipSuccess) return status != hipStreamCaptureStatusNone;
+  (void)hipGetLastError();
+  return true;
+}
 // A number for the marks of a call that no other call uses (from a start that a workspace's contents will not hold by chance).
-constexpr int kInLaunchUpTo = 8;
 unsigned long long next_mark() {
   static std::atomic<unsigned long long> counter{std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull | 1};
   return counter.fetch_add(2, std::memory_order_relaxed);
@@ -1240,13 +1245,15 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     const _Float16 *pp = probes + (size_t)p0 * d;
     uint8_t *hit = hit_out_dev ? hit_out_dev + p0 : nullptr;
     // A short pass over a small bank merges its lists itself (the marks behind the lists, which one probe block leaves room for): what it saves is a
-    // launch, what it costs is that one workgroup merges for all probes.  us a call, apart | here, 1000 to 2000 rows of width 768: best row of
-    // 1 probe 11.3 | 8.2, of 8 11.3 | 10.1; 3 best of 1 14.3 | 11.5, of 8 14.8 | 14.5; 8 best of 1 18.0 | 16.0, of 8 18.4 | 23.0.  With more lists
-    // than lanes (20 000 rows, 256 lists): best row of 1 11.3 | 9.7, of 8 11.5 | 12.1, 3 best of 1 14.1 | 14.7, of 8 14.4 | 20.8; behind a long stream
-    // the merge apart is hidden already (200 000 rows 66.5 | 67.2).
+    // launch, a third of the host's work, what it costs is 0.7 us of the GPU's and, past a probe a wavefront, a second round.  us a call, calls one after
+    // the other, the merge apart | here, 2000 rows of width 768: best row of 1 probe 11.6 | 8.7, of 4 11.6 | 8.9, of 8 10.7 | 10.8, 4 best of 1 13.8 | 12.2,
+    // of 8 14.0 | 16.3; 4096 rows of width 1024: best row of 1 11.7 | 9.6, 5 best of 4 17.2 | 17.6; of width 2048, where the GPU is behind the host
+    // either way: best row of 1 11.7 | 12.5.  Waited for: 2000 rows of width 768, best row of 1 23.7 | 24.0, 4 best of 1 about 31 | 30.5.  A captured
+    // call has paid for its launches (best row of 1 8.1 | 8.8, 4 best of 4 12.7 | 12.9), and so no mark is ever used twice.  With more lists than
+    // lanes (20 000 rows, 256 lists) the merge here is the slower one from two best on, and behind a long stream the launch apart is hidden.
     InLaunch il{};
-    if (sh.grid <= kInLaunchGrid && (n_probes <= 4 || (n_probes <= kInLaunchUpTo && k <= 4)) && workspace_dev != ctx->static_scratch)
-      il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : k <= 4 ? 4 : kMaxTopK)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit};
+    if (sh.grid <= kInLaunchGrid && n_probes <= kInLaunchProbes && k <= 4 && d <= 1024 && workspace_dev != ctx->static_scratch && !being_captured(st))
+      il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : 4)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit};
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     // (up to four best rows out of lists of four: what the pass spends on a list of eight shows beside the stream, us a pass, eight | four: 3 best
     // of 1000 rows of width 768 12.9 | 10.7, of 50 000 of width 1024 27.1 | 23.3, of 200 000 71.6 | 68.1, 24 probes 82.7 | 75.3)

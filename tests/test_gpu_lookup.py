@@ -384,8 +384,8 @@ def test_refresh_scan_rows_and_chunks_that_are_not_numbers(dim, n_new):
 
 @pytest.mark.parametrize("rows,dim,k", [(1, 64, 1), (15, 384, 8), (2000, 768, 3), (4096, 768, 1), (4097, 768, 4), (4033, 128, 5), (4096, 2048, 2)])
 def test_merge_inside_the_launch_equals_the_merge_apart(rows, dim, k):
-    """Calls of up to 8 probes over at most 64 workgroups' rows merge their lists inside the launch, others in a launch of their own: the same
-    bits, whatever the workspace held, and again from a captured call replayed between eager ones."""
+    """Calls of up to 4 probes over at most 64 workgroups' rows merge their lists of up to 4 inside the launch, others and captured ones in a launch of
+    their own: the same bits, whatever the workspace held, and again from a captured call replayed between eager ones."""
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + dim)
     pc = Percache(n_layers=1, hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=1, slot_capacity=64, max_pos=64, bank_capacity=rows, emb_dim=dim,
@@ -400,11 +400,11 @@ def test_merge_inside_the_launch_equals_the_merge_apart(rows, dim, k):
     def call(p):
         return pc.percache_lookup(p, 0.3) if k == 1 else pc.percache_lookup_topk(p, k)
     apart = [t.clone() for t in call(probes)]                  # 16 probes
-    for n in (1, 3, 8, 9):
+    for n in (1, 3, 4, 5, 9):
         for fill in (0, 255):
             pc._lookup_ws.fill_(fill)
             assert all(torch.equal(a[:n], b) for a, b in zip(apart, call(probes[:n].contiguous()))), (n, fill)
-    few = probes[2:7].contiguous()
+    few = probes[2:6].contiguous()
     call(few)
     torch.cuda.synchronize()
     graph = torch.cuda.CUDAGraph()
@@ -416,13 +416,13 @@ def test_merge_inside_the_launch_equals_the_merge_apart(rows, dim, k):
         graph.replay()
         call(probes[:1].contiguous())
         torch.cuda.synchronize()
-        assert all(torch.equal(a[2:7], b) for a, b in zip(apart, out))
+        assert all(torch.equal(a[2:6], b) for a, b in zip(apart, out))
 
 
-@pytest.mark.parametrize("rows,dim,k", [(4096, 768, 1), (4096, 768, 3), (2000, 2048, 8)])
+@pytest.mark.parametrize("rows,dim,k", [(4096, 768, 1), (4096, 768, 3), (2000, 1024, 4), (2000, 2048, 8)])
 def test_merge_inside_the_launch_beside_kernels_that_hold_the_cus(rows, dim, k):
     """Lookups whose workgroups get a CU only as another stream's long workgroups leave theirs, in whatever order that is: the bits of the call
-    alone, and no mark is left behind the lists for a later call with the same one (a captured call's)."""
+    alone, eager and captured."""
     g = torch.Generator(device=DEV)
     g.manual_seed(rows + dim)
     pc = Percache(n_layers=1, hidden=64, n_q_heads=2, n_kv_heads=1, head_dim=64, n_slots=1, slot_capacity=64, max_pos=64, bank_capacity=rows, emb_dim=dim,
@@ -456,8 +456,5 @@ def test_merge_inside_the_launch_beside_kernels_that_hold_the_cus(rows, dim, k):
     torch.cuda.synchronize()
     for out in outs:
         assert all(torch.equal(a, b) for a, b in zip(alone, out))
-    n_wg = min(torch.cuda.get_device_properties(0).multi_processor_count, -(-(-(-rows // 16)) // 4))
-    at = (-pc._lookup_ws.data_ptr()) % 256 + n_wg * 16 * (1 if k == 1 else 4 if k <= 4 else 8) * 8
-    assert n_wg <= 64 and not pc._lookup_ws[at:at + n_wg * 8].any()
     pc.close()
     other.close()
