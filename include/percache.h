@@ -329,7 +329,10 @@ typedef struct {
  *           j of query b is stored in slot save_slots_host[b * n_save + j] of that layer (negative: skipped).
  *           Save slots must be distinct and must not be read by this call.  With n_chunks == 0 this is the
  *           population pass: an ordinary prefill that fills the cache.
- *   workspace_dev        >= percache_stack_workspace_bytes(ctx, batch, t_fresh, max_chunks, ffn), 256-byte aligned */
+ *   workspace_dev        >= percache_stack_workspace_bytes(ctx, batch, t_fresh, max_chunks, ffn), 256-byte aligned.
+ *           Calls of up to 4 token rows ask for more than longer ones may: room to hand activations on inside one launch
+ *           for all layers.  A workspace that was sized for a call of more rows with as many chunks is taken as well;
+ *           where it leaves no such room, the step runs launch by launch (equal up to rounding, and slower). */
 size_t percache_stack_workspace_bytes(const percache_ctx *ctx, int32_t batch, int32_t t_fresh, int32_t max_chunks,
                                       int32_t ffn);
 pc_status percache_stack_reuse(percache_ctx *ctx, const percache_block_weights *layers_host, int32_t n_layers,

@@ -176,6 +176,7 @@ class Percache:
             raise PercacheError(st, self.lib.percache_last_error(None).decode())
         self.ctx = out
         self._ws = None
+        self._step_ws = None
         self._lookup_ws = None
 
     # ------------------------------------------------------------------ helpers
@@ -200,6 +201,16 @@ class Percache:
             self._ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
         p = (self._ws.data_ptr() + 255) // 256 * 256
         return p
+
+    def _stack_workspace(self, batch: int, t_fresh: int, nbytes: int):
+        """Steps of up to 4 rows, which ask for more than the prompt before them, have a tensor of their own: a prompt's stays where a captured
+        call has it."""
+        import torch
+        if batch * t_fresh > 4:
+            return self._workspace(nbytes)
+        if self._step_ws is None or self._step_ws.numel() < nbytes + 256:
+            self._step_ws = torch.empty(nbytes + 256, dtype=torch.uint8, device=self.device)
+        return (self._step_ws.data_ptr() + 255) // 256 * 256
 
     def percache_profile_enable(self, on=True, kernels=None):
         """``kernels``: the kinds to bracket with events (default: all three)."""
@@ -414,7 +425,7 @@ class Percache:
         batch, t_fresh, _ = h_in.shape
         arr = weights if weights is not None else self._weights(layers)
         need = self.percache_stack_workspace_bytes(batch, t_fresh, table.max_chunks, ffn)
-        ws = self._workspace(need)
+        ws = self._stack_workspace(batch, t_fresh, need)
         self._check(self.lib.percache_stack_reuse_table(self.ctx, arr, len(layers), ffn, eps, _ptr(h_in), batch, t_fresh,
                                                         _ptr(table), _ptr(h_out), ws, need, _stream()))
         return arr
@@ -476,7 +487,7 @@ class Percache:
         if h_out is None:
             h_out = torch.empty_like(h_in)
         need = self.percache_stack_workspace_bytes(batch, t_fresh, max_chunks, ffn)
-        ws = self._workspace(need)
+        ws = self._stack_workspace(batch, t_fresh, need)
         self._check(self.lib.percache_stack_reuse(self.ctx, arr, len(layers), ffn, eps, _ptr(h_in), batch, t_fresh, ids_p,
                                                   ul_p, nc_p, max_chunks, sb_p, ss_p, n_save, _ptr(h_out), ws, need,
                                                   _stream()))
@@ -493,7 +504,7 @@ class Percache:
         if h_out is None:
             h_out = torch.empty_like(h_in)
         need = self.percache_stack_workspace_bytes(batch, n_new, max_chunks, ffn)
-        ws = self._workspace(need)
+        ws = self._stack_workspace(batch, n_new, need)
         self._check(self.lib.percache_stack_decode(self.ctx, arr, len(layers), ffn, eps, _ptr(h_in), batch, n_new, ids_p, ul_p,
                                                    nc_p, max_chunks, ap_p, _ptr(h_out), ws, need, _stream()))
         return h_out

@@ -433,8 +433,8 @@ struct StackWs {
   __bf16 *attn;    // [M, Hq*D]
   __bf16 *mid;     // [M, H]
   __bf16 *act;     // [M, F]
-  void *steps;     // of a step in one launch (decode_stack.hip)
-  size_t total;
+  void *steps;     // behind them, where there is room: of a step in one launch (decode_stack.hip)
+  size_t total;    // without that
 };
 StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fresh, int max_chunks, int ffn) {
   const percache_config &c = ctx->cfg;
@@ -448,9 +448,15 @@ StackWs carve_stack_ws(const percache_ctx *ctx, void *base, int batch, int t_fre
   w.attn = take(M * c.n_q_heads * c.head_dim * 2);
   w.mid = take(M * c.hidden * 2);
   w.act = take(M * ffn * 2);
-  w.steps = take(pc::stackdec::workspace_bytes(c, ctx->n_cu, batch, t_fresh, ffn));
   w.total = off;
+  w.steps = p ? p + off : nullptr;
   return w;
+}
+// Bytes behind it that a step over the longest list of max_chunks chunks takes for all layers in one launch (0: no such step).
+size_t steps_bytes(const percache_ctx *ctx, int batch, int t_fresh, int max_chunks, int ffn) {
+  const percache_config &c = ctx->cfg;
+  const long tiles = (long)max_chunks * (c.slot_capacity / pc::kKvTile);
+  return pc::align_up(pc::stackdec::workspace_bytes(c, ctx->n_cu, batch, t_fresh, ffn, c.n_layers, tiles < INT32_MAX / 2 ? (int)tiles : INT32_MAX / 2));
 }
 
 }  // namespace
@@ -484,7 +490,7 @@ pc_status percache_kv_slice(percache_ctx *ctx, int32_t layer, const void *k_dev,
 
 size_t percache_stack_workspace_bytes(const percache_ctx *ctx, int32_t batch, int32_t t_fresh, int32_t max_chunks, int32_t ffn) {
   if (!ctx || batch < 1 || t_fresh < 1 || max_chunks < 0 || ffn < 1) return 0;
-  return carve_stack_ws(ctx, nullptr, batch, t_fresh, max_chunks, ffn).total;
+  return carve_stack_ws(ctx, nullptr, batch, t_fresh, max_chunks, ffn).total + steps_bytes(ctx, batch, t_fresh, max_chunks, ffn);
 }
 
 static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *layers_host, int32_t n_layers, int32_t ffn,
@@ -557,11 +563,9 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
         if (save_slots_host[k] == slot) return pc::fail(ctx, PC_EINVAL, "save slot %d appears twice", slot);
     }
   }
-  const size_t need = percache_stack_workspace_bytes(ctx, batch, t_fresh, max_chunks, ffn);
-  if (!workspace_dev || workspace_bytes < need) return pc::fail(ctx, PC_ENOMEM, "stack workspace has %zu bytes, need %zu", workspace_bytes, need);
-  if ((uintptr_t)workspace_dev % pc::kAlign) return pc::fail(ctx, PC_EINVAL, "workspace must be 256-byte aligned");
-
   StackWs ws = carve_stack_ws(ctx, workspace_dev, batch, t_fresh, max_chunks, ffn);
+  if (!workspace_dev || workspace_bytes < ws.total) return pc::fail(ctx, PC_ENOMEM, "stack workspace has %zu bytes, need %zu", workspace_bytes, ws.total);
+  if ((uintptr_t)workspace_dev % pc::kAlign) return pc::fail(ctx, PC_EINVAL, "workspace must be 256-byte aligned");
   const int stride = pc::tbl_stride(max_chunks);
   int min_tiles = INT32_MAX, max_cached = 0;
   for (int b = 0; b < batch; ++b) {
@@ -587,8 +591,10 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
     }
   }
   if (table_dev) ws.pf.table = const_cast<int32_t *>(table_dev);  // the list is on the device already: nothing to copy
-  // (the kernels whose timing was asked for are launched one by one)
-  if (raw_qkv && !(ctx->prof_mask & 6) && pc::stackdec::takes(c, ctx->n_cu, batch, t_fresh, max_cached)) {
+  // (the kernels whose timing was asked for are launched one by one, and so are those of a call whose workspace, one sized for another call,
+  // has no room for the hand-over)
+  if (raw_qkv && !(ctx->prof_mask & 6) && pc::stackdec::takes(c, ctx->n_cu, batch, t_fresh, max_cached) &&
+      workspace_bytes - ws.total >= pc::stackdec::workspace_bytes(c, ctx->n_cu, batch, t_fresh, ffn, n_layers, max_cached)) {
     const __bf16 *k, *v;
     size_t dense;
     st = pc::stackdec::launch(ctx, layers_host, n_layers, ffn, eps, (const __bf16 *)h_in_dev, batch, t_fresh, table_dev ? nullptr : &rows, ws.pf.table,

@@ -1001,11 +1001,11 @@ static int splits_for(const percache_config &c, int n_cu, int32_t batch, int32_t
   return want < cap ? want : cap;
 }
 
-size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn) {
+size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles) {
   if (!shape_fits(c, batch, t_fresh)) return 0;
   const int M = batch * t_fresh;
-  const Blocks b = blocks_of(c, M, ffn, max_splits_for(c, n_cu, batch, t_fresh));
-  return kAlign + (c.n_layers * b.total + b.head()) * 4 + (size_t)c.n_layers * 2 * dense_elems(c, M) * 2;
+  const Blocks b = blocks_of(c, M, ffn, splits_for(c, n_cu, batch, t_fresh, max_tiles));
+  return kAlign + (n_layers * b.total + b.head()) * 4 + (size_t)n_layers * 2 * dense_elems(c, M) * 2;
 }
 
 // (at most four tiles, two rounds, to a piece: more of them want the ring of decode_attention_kernel)

@@ -43,8 +43,8 @@ struct Args {
   int x_steps, x_bytes, x_share_log2;       // LDS of a wavefront's token rows; lanes that share 8 columns in the merge
 };
 
-// Workspace of a step through n_layers layers (0: the shape does not take this path).
-size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn);
+// Workspace of a step through n_layers layers over queries of at most max_tiles cached 64-key tiles (0: the shape does not take this path).
+size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles);
 // Whether a step over queries of at most max_tiles cached 64-key tiles takes it.
 bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int max_tiles);
 // The step.  rows: the chunk lists and, behind them, (slot, tokens) per query if append.  table: where they go (with_rows) or stand.

@@ -9,7 +9,7 @@ import torch
 
 import oracle
 from paper_2601_11553_amd import workloads as wl
-from paper_2601_11553_amd.binding import Percache, PercacheError
+from paper_2601_11553_amd.binding import Percache, PercacheError, _host_i32
 
 from gpu_util import DEV, bf16, check_close, host
 from test_gpu_stack import EPS, check_hidden, dev_layers, oracle_block
@@ -472,3 +472,51 @@ def test_steps_on_two_streams_at_once():
     torch.cuda.synchronize()
     for i in (0, 1):
         assert all(torch.equal(o, alone[i]) for o in outs[i])
+
+
+def test_step_in_a_workspace_sized_for_a_longer_call():
+    """28 layers hand on more between their parts than 6 fresh tokens need as workspace: a step in a buffer of the longer call's size is taken,
+    launch by launch, one byte less than that takes is refused, and a step leaves the workspace that the binding holds for prompts where it is."""
+    g = np.random.default_rng(23)
+    H, Hq, Hkv, D, F, L, C = 256, 8, 4, 64, 512, 28, 512
+    Ws = _step_inputs(H, Hq, Hkv, D, F, L, "plain", g)
+    pc = Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=7, slot_capacity=C, max_pos=8 * C, device=DEV)
+    for layer in range(L):
+        for s in range(6):
+            pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, C, D))), bf16(g.standard_normal((Hkv, C, D))))
+    x = bf16(g.standard_normal((1, 1, H)))
+    whole = pc.percache_stack_decode(Ws, F, EPS, x, [range(6)], [-1])
+    full, longer = (pc.percache_stack_workspace_bytes(1, t, 6, F) for t in (1, 6))
+    assert longer < full
+    arr = pc._weights(Ws)
+    keep, ids_p, _, n_p, _ = pc._chunk_args(1, [range(6)], None, None)
+    none, none_p = _host_i32([-1])
+    out = torch.empty_like(x)
+
+    def step(n_bytes):
+        buf = torch.full((n_bytes + 512,), 173, dtype=torch.uint8, device=DEV)
+        at = (-buf.data_ptr()) % 256
+        st = pc.lib.percache_stack_decode(pc.ctx, arr, L, F, EPS, x.data_ptr(), 1, 1, ids_p, None, n_p, 6, none_p, out.data_ptr(),
+                                          buf.data_ptr() + at, n_bytes, torch.cuda.current_stream().cuda_stream)
+        torch.cuda.synchronize()
+        assert (buf[:at] == 173).all() and (buf[at + n_bytes:] == 173).all()
+        return st
+    out.zero_()
+    assert step(longer) == 0
+    check_hidden(host(out), host(whole), "step in the smaller workspace", rel_max=2.0 ** -4 * L ** 0.5, rel_fro=6e-3 * L ** 0.5)   # (as below)
+    one_by_one = out.clone()
+    lo, hi = 0, longer            # the least that is taken: what the launches one by one need
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        if step(mid) == 0:
+            hi = mid
+        else:
+            lo = mid
+    assert step(hi - 1) == -5 and step(hi) == 0 and torch.equal(out, one_by_one)
+    assert step(full) == 0 and torch.equal(out, whole)
+    h = bf16(g.standard_normal((1, 6, H)))
+    pc.percache_stack_reuse(Ws, F, EPS, h, [range(6)])
+    held = pc._ws.data_ptr()
+    pc.percache_stack_decode(Ws, F, EPS, x, [range(6)], [-1])
+    assert pc._ws.data_ptr() == held
+    pc.close()
