@@ -983,6 +983,8 @@ static Blocks blocks_of(const percache_config &c, int M, int ffn, int n_splits) 
   b.total = 2 * b.head() + b.qsum + b.part + b.attn + b.act;
   return b;
 }
+// one counter a launch
+static size_t ticket_bytes(int n_layers) { return align_up((size_t)((n_layers + kMaxLayers - 1) / kMaxLayers) * sizeof(unsigned)); }
 static size_t dense_elems(const percache_config &c, int M) { return align_up((size_t)M * c.n_kv_heads * c.head_dim, 128); }
 
 // Which steps take this path: beyond a few rows the rows themselves (polled by every workgroup, read out of LDS by every wavefront) cost what
@@ -1005,7 +1007,7 @@ size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_
   if (!shape_fits(c, batch, t_fresh)) return 0;
   const int M = batch * t_fresh;
   const Blocks b = blocks_of(c, M, ffn, splits_for(c, n_cu, batch, t_fresh, max_tiles));
-  return kAlign + (n_layers * b.total + b.head()) * 4 + (size_t)n_layers * 2 * dense_elems(c, M) * 2;
+  return ticket_bytes(n_layers) + (n_layers * b.total + b.head()) * 4 + (size_t)n_layers * 2 * dense_elems(c, M) * 2;
 }
 
 // (at most four tiles, two rounds, to a piece: more of them want the ring of decode_attention_kernel)
@@ -1035,7 +1037,7 @@ pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_
   const int ns = splits_for(c, ctx->n_cu, batch, t_fresh, max_tiles);
   const Blocks b = blocks_of(c, M, ffn, ns);
   unsigned *const tickets = (unsigned *)ws;
-  char *p = (char *)ws + kAlign;
+  char *p = (char *)ws + ticket_bytes(n_layers);
   Args a;
   memset(&a, 0, sizeof a);
   float *words = (float *)p;

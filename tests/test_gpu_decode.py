@@ -520,3 +520,23 @@ def test_step_in_a_workspace_sized_for_a_longer_call():
     pc.percache_stack_decode(Ws, F, EPS, x, [range(6)], [-1])
     assert pc._ws.data_ptr() == held
     pc.close()
+
+
+def test_step_through_more_than_64_launches_of_layers():
+    """2080 layers are 65 launches in a row, each with a counter of its own in front of the first layer's input.  All but six layers add nothing
+    (their output weights are zeros), so the result is that of the launches one by one up to the rounding of six layers."""
+    g = np.random.default_rng(29)
+    H, Hq, Hkv, D, F, L = 128, 2, 1, 64, 64, 2080
+    live = dict(zip((0, 31, 32, 2047, 2048, L - 1), _step_inputs(H, Hq, Hkv, D, F, 6, "plain", g)))
+    still = {k: torch.zeros_like(v) if k in ("wo", "w_down") else v for k, v in live[0].items()}
+    Ws = [live.get(l, still) for l in range(L)]
+    pc = Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=1, slot_capacity=64, max_pos=64, device=DEV)
+    x = bf16(g.standard_normal((1, 1, H)))
+    one = pc.percache_stack_decode(Ws, F, EPS, x, np.zeros((1, 0), np.int32), [-1])
+    torch.cuda.synchronize()
+    pc.percache_profile_enable(True, [2])
+    each = pc.percache_stack_decode(Ws, F, EPS, x, np.zeros((1, 0), np.int32), [-1])
+    pc.percache_profile_enable(False)
+    assert not torch.equal(one, x)
+    check_hidden(host(one), host(each), "2080 layers", rel_max=2.0 ** -4 * 6 ** 0.5, rel_fro=6e-3 * 6 ** 0.5)   # (as above)
+    pc.close()
