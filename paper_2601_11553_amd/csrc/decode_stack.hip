@@ -1023,10 +1023,12 @@ bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, i
 }
 
 template <int D>
-static void launch_kernel(int fmt, dim3 grid, size_t lds, hipStream_t s, const Args &a) {
-  if (fmt == 0) hipLaunchKernelGGL((decode_stack_kernel<D, 0>), grid, dim3(64 * kWaves), lds, s, a);
-  else if (fmt == 1) hipLaunchKernelGGL((decode_stack_kernel<D, 1>), grid, dim3(64 * kWaves), lds, s, a);
-  else hipLaunchKernelGGL((decode_stack_kernel<D, 2>), grid, dim3(64 * kWaves), lds, s, a);
+static pc_status launch_kernel(percache_ctx *ctx, int fmt, dim3 grid, size_t lds, hipStream_t s, const Args &a) {
+  void (*const kernel)(Args) = fmt == 0 ? decode_stack_kernel<D, 0> : fmt == 1 ? decode_stack_kernel<D, 1> : decode_stack_kernel<D, 2>;
+  PC_HIP(ctx, hipFuncSetAttribute((const void *)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds));   // (above 64 KB it must be opted into)
+  hipLaunchKernelGGL(kernel, grid, dim3(64 * kWaves), lds, s, a);
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
 }
 
 pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_layers, int ffn, float eps, const __bf16 *h_in, int batch, int t_fresh,
@@ -1148,8 +1150,8 @@ pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_
     a.first_item = 0;
     a.n_items = n * a.per_layer;
     const int grid = a.n_items < ctx->n_cu ? a.n_items : ctx->n_cu;
-    if (D == 128) launch_kernel<128>(fmt, dim3(grid), lds, stream, a); else launch_kernel<64>(fmt, dim3(grid), lds, stream, a);
-    PC_HIP(ctx, hipGetLastError());
+    const pc_status st = D == 128 ? launch_kernel<128>(ctx, fmt, dim3(grid), lds, stream, a) : launch_kernel<64>(ctx, fmt, dim3(grid), lds, stream, a);
+    if (st != PC_OK) return st;
   }
   return PC_OK;
 }
