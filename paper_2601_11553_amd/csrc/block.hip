@@ -593,7 +593,7 @@ static pc_status run_stack(percache_ctx *ctx, const percache_block_weights *laye
   if (table_dev) ws.pf.table = const_cast<int32_t *>(table_dev);  // the list is on the device already: nothing to copy
   // (the kernels whose timing was asked for are launched one by one, and so are those of a call whose workspace, one sized for another call,
   // has no room for the hand-over)
-  if (raw_qkv && !(ctx->prof_mask & 6) && pc::stackdec::takes(c, ctx->n_cu, batch, t_fresh, max_cached) &&
+  if (raw_qkv && !(ctx->prof_mask & 6) && pc::stackdec::takes(c, ctx->n_cu, batch, t_fresh, ffn, n_layers, max_cached) &&
       workspace_bytes - ws.total >= pc::stackdec::workspace_bytes(c, ctx->n_cu, batch, t_fresh, ffn, n_layers, max_cached)) {
     const __bf16 *k, *v;
     size_t dense;

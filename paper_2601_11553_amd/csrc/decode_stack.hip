@@ -151,7 +151,7 @@ __device__ __forceinline__ void project(const KArgs &a, char *lds, WRow w_row, R
   constexpr int STAGE = 2048 * NF, NSTG = kRing / kWaves / STAGE, INSTR = 2 * NF;
   unsigned *const ticket = pinned(a.ticket);
   const int M = pinned(a.M), steps = K / 64, s0 = wave * steps / kWaves, n = (wave + 1) * steps / kWaves - s0;
-  const int xc = pinned(a.x_steps), row_bytes = M * 128;   // LDS of a step of the token rows
+  const int row_bytes = M * 128;   // LDS of a step of the token rows
   char *const ring = lds + wave * (kRing / kWaves), *const xs = lds + kRing + wave * a.x_bytes;
   const int l16 = lane & 15, g = lane >> 4;
 #pragma unroll
@@ -255,86 +255,84 @@ __device__ __forceinline__ void project(const KArgs &a, char *lds, WRow w_row, R
   gate(ticket, before, wave);
   bool first = true;
   int st = 0;
-  for (int c0 = 0; c0 < n || first; c0 += xc) {   // (a wavefront without a slice still waits for more())
-    const int cn = max(0, min(xc, n - c0)), per = normed ? 12 : 8, pieces = M * cn * per;   // of 16 bytes; a step
-    constexpr int U = 4;
-    for (int u0 = 0; u0 < pieces || first; u0 += 64 * U) {
-      const bool need_more = first && waits_more;
-      unsigned off[U], at[U];
-      bool sq[U];
+  const int per = normed ? 12 : 8, pieces = M * n * per;   // of 16 bytes; a step
+  constexpr int U = 4;
+  for (int u0 = 0; u0 < pieces || first; u0 += 64 * U) {   // (a wavefront without a slice still waits for more())
+    const bool need_more = first && waits_more;
+    unsigned off[U], at[U];
+    bool sq[U];
 #pragma unroll
-      for (int k = 0; k < U; ++k) {
-        const int u = u0 + 64 * k + lane, q = u / per, c = u - q * per, m = M > 1 && cn > 0 ? q / cn : 0, step = q - m * cn, s = s0 + c0 + step;
-        sq[k] = c >= 8;
-        const int blk = m * (K / 16) + s * 4 + (sq[k] ? c - 8 : c >> 1);
-        off[k] = u >= pieces ? kNowhere : normed ? (unsigned)(blk * kBlock + (sq[k] ? 32 : (c & 1) * 16)) : (unsigned)((m * K + s * 64 + c * 8) * 2);
-        at[k] = sq[k] ? lds_addr((const char *)(squares + blk)) : lds_addr(xs + step * row_bytes + m * 128 + (c ^ swz128(m)) * 16);
-      }
-      u32x4 v[U];
-#pragma unroll
-      for (int k = 0; k < U; ++k) v[k] = u32x4{EMPTY, EMPTY, EMPTY, EMPTY};
-      {
-        Waiting w;
-        bool all = u0 + 64 >= pieces;   // one load's worth in all, or the first is there: ask for everything
-        for (int tries = 0;; ++tries) {
-          bool bad = false;
-#pragma unroll
-          for (int k = 0; k < U; ++k)
-            if (u0 + 64 * k < pieces && (k == 0 || all)) v[k] = ask(x, off[k]);
-          if (need_more && all) bad = more();
-#pragma unroll
-          for (int k = 0; k < U; ++k)
-            if (u0 + 64 * k < pieces && (k == 0 || all)) bad = bad || v[k][0] == EMPTY || (!sq[k] && missing(v[k]));
-          const bool there = __ballot(bad) == 0;
-          if ((there && all) || given_up(tries, ticket)) break;
-          if (there) all = true;
-          else pause<2>();
-        }
-      }
-#pragma unroll
-      for (int k = 0; k < U; ++k) {
-        if (off[k] == kNowhere) continue;
-        if (sq[k]) asm volatile("ds_write_b32 %0, %1" : : "v"(at[k]), "v"(v[k][0]) : "memory");
-        else lds_put(at[k], v[k]);
-      }
-      first = false;
+    for (int k = 0; k < U; ++k) {
+      const int u = u0 + 64 * k + lane, q = u / per, c = u - q * per, m = M > 1 && n > 0 ? q / n : 0, step = q - m * n, s = s0 + step;
+      sq[k] = c >= 8;
+      const int blk = m * (K / 16) + s * 4 + (sq[k] ? c - 8 : c >> 1);
+      off[k] = u >= pieces ? kNowhere : normed ? (unsigned)(blk * kBlock + (sq[k] ? 32 : (c & 1) * 16)) : (unsigned)((m * K + s * 64 + c * 8) * 2);
+      at[k] = sq[k] ? lds_addr((const char *)(squares + blk)) : lds_addr(xs + step * row_bytes + m * 128 + (c ^ swz128(m)) * 16);
     }
-    asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
-    for (int s = c0; s < c0 + cn; s += 2) {   // two steps at a time: all their operands on the way before the first product
-      const bool two = s + 1 < c0 + cn;
-      const int last = two ? s + 1 : s, later = min(s + NSTG, n) - 1 - last;   // stages in flight behind these
-      if (later >= 3) wait_vmcnt<(NSTG > 3 ? 3 : 0) * INSTR>();
-      else if (later == 2) wait_vmcnt<(NSTG > 2 ? 2 : 0) * INSTR>();
-      else if (later == 1) wait_vmcnt<INSTR>();
-      else wait_vmcnt<0>();
+    u32x4 v[U];
+#pragma unroll
+    for (int k = 0; k < U; ++k) v[k] = u32x4{EMPTY, EMPTY, EMPTY, EMPTY};
+    {
+      Waiting w;
+      bool all = u0 + 64 >= pieces;   // one load's worth in all, or the first is there: ask for everything
+      for (int tries = 0;; ++tries) {
+        bool bad = false;
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+          if (u0 + 64 * k < pieces && (k == 0 || all)) v[k] = ask(x, off[k]);
+        if (need_more && all) bad = more();
+#pragma unroll
+        for (int k = 0; k < U; ++k)
+          if (u0 + 64 * k < pieces && (k == 0 || all)) bad = bad || v[k][0] == EMPTY || (!sq[k] && missing(v[k]));
+        const bool there = __ballot(bad) == 0;
+        if ((there && all) || given_up(tries, ticket)) break;
+        if (there) all = true;
+        else pause<2>();
+      }
+    }
+#pragma unroll
+    for (int k = 0; k < U; ++k) {
+      if (off[k] == kNowhere) continue;
+      if (sq[k]) asm volatile("ds_write_b32 %0, %1" : : "v"(at[k]), "v"(v[k][0]) : "memory");
+      else lds_put(at[k], v[k]);
+    }
+    first = false;
+  }
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  for (int s = 0; s < n; s += 2) {   // two steps at a time: all their operands on the way before the first product
+    const bool two = s + 1 < n;
+    const int last = two ? s + 1 : s, later = min(s + NSTG, n) - 1 - last;   // stages in flight behind these
+    if (later >= 3) wait_vmcnt<(NSTG > 3 ? 3 : 0) * INSTR>();
+    else if (later == 2) wait_vmcnt<(NSTG > 2 ? 2 : 0) * INSTR>();
+    else if (later == 1) wait_vmcnt<INSTR>();
+    else wait_vmcnt<0>();
+    asm volatile("" ::: "memory");
+    const int st2 = st + 1 == NSTG ? 0 : st + 1;
+    bf16x8 w[NF][4], xv[4];
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k >= 2 && !two) break;
+      const char *wb = ring + (k < 2 ? st : st2) * STAGE, *xb = xs + (s + k / 2) * row_bytes;
+      xv[k] = *(const bf16x8 *)(xb + xr[k & 1]);
+#pragma unroll
+      for (int f = 0; f < NF; ++f) w[f][k] = *(const bf16x8 *)(wb + f * 2048 + rd[k & 1]);
+    }
+#pragma unroll
+    for (int k = 0; k < 4; ++k) {
+      if (k >= 2 && !two) break;
+#pragma unroll
+      for (int f = 0; f < NF; ++f) {
+        f32x4 &to = k & 1 ? odd[f] : acc[f];
+        to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f][k], xv[k], to, 0, 0, 0);
+      }
+    }
+    if (s + NSTG < n) {
+      __builtin_amdgcn_s_waitcnt(0xf | (7 << 4) | (3 << 14));  // every read of the stages is in registers (lgkmcnt 0)
       asm volatile("" ::: "memory");
-      const int st2 = st + 1 == NSTG ? 0 : st + 1;
-      bf16x8 w[NF][4], xv[4];
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k >= 2 && !two) break;
-        const char *wb = ring + (k < 2 ? st : st2) * STAGE, *xb = xs + (s - c0 + k / 2) * row_bytes;
-        xv[k] = *(const bf16x8 *)(xb + xr[k & 1]);
-#pragma unroll
-        for (int f = 0; f < NF; ++f) w[f][k] = *(const bf16x8 *)(wb + f * 2048 + rd[k & 1]);
-      }
-#pragma unroll
-      for (int k = 0; k < 4; ++k) {
-        if (k >= 2 && !two) break;
-#pragma unroll
-        for (int f = 0; f < NF; ++f) {
-          f32x4 &to = k & 1 ? odd[f] : acc[f];
-          to = __builtin_amdgcn_mfma_f32_16x16x32_bf16(w[f][k], xv[k], to, 0, 0, 0);
-        }
-      }
-      if (s + NSTG < n) {
-        __builtin_amdgcn_s_waitcnt(0xf | (7 << 4) | (3 << 14));  // every read of the stages is in registers (lgkmcnt 0)
-        asm volatile("" ::: "memory");
-        request(s + NSTG, st);
-        if (two && s + 1 + NSTG < n) request(s + 1 + NSTG, st2);
-      }
-      st = two ? (st2 + 1 == NSTG ? 0 : st2 + 1) : st2;
+      request(s + NSTG, st);
+      if (two && s + 1 + NSTG < n) request(s + 1 + NSTG, st2);
     }
+    st = two ? (st2 + 1 == NSTG ? 0 : st2 + 1) : st2;
   }
 #pragma unroll
   for (int f = 0; f < NF; ++f) acc[f] += odd[f];
@@ -365,7 +363,7 @@ __device__ __forceinline__ f32x4 sum_of(const char *lds, int f, int lane) {
 // token row from those of the wavefronts.  (v_rsq_f32: 1 ulp, as a root and a division have)
 __device__ __forceinline__ float norm_factor(const float *squares, int m, int M, int H, int g, float inv_h, float eps) {
   float s = 0.f;
-  if (M == 1 && H <= kRowCols) {
+  if (M == 1) {   // (at most kRowCols columns)
     const f32x4 a = *(const f32x4 *)squares, b = *(const f32x4 *)(squares + 4);
     s = ((a[0] + a[1]) + (a[2] + a[3])) + ((b[0] + b[1]) + (b[2] + b[3]));
   } else {
@@ -987,14 +985,23 @@ static Blocks blocks_of(const percache_config &c, int M, int ffn, int n_splits) 
 static size_t ticket_bytes(int n_layers) { return align_up((size_t)((n_layers + kMaxLayers - 1) / kMaxLayers) * sizeof(unsigned)); }
 static size_t dense_elems(const percache_config &c, int M) { return align_up((size_t)M * c.n_kv_heads * c.head_dim, 128); }
 
-// Which steps take this path: beyond a few rows the rows themselves (polled by every workgroup, read out of LDS by every wavefront) cost what
-// the launches did.  us a layer, launch by launch | here: width 1024, 2 rows 30.3 | 24.3 (12 tiles each), 35.3 | 33.8 (64 tiles), 3 rows
-// 32.5 | 28.8, 4 rows 34.1 | 31.3, 2 x 2 rows 31.8 | 26.7, 6 rows 34.8 | 37.7, 8 rows 38.4 | 40.1; width 896, 2 rows 29.1 | 25.4, 4 rows
-// 31.2 | 28.7, 8 rows 32.6 | 32.5; width 3072, 1 row 53.9 | 46.2, 2 rows 55.7 | 58.1, 3 rows 57.6 | 63.4.
-static bool shape_fits(const percache_config &c, int32_t batch, int32_t t_fresh) {
-  const long R = (long)(c.n_q_heads / c.n_kv_heads) * t_fresh, M = (long)batch * t_fresh;
-  // (one row of any width that a model has: past 390 000 columns the row's sums of squares would take all of LDS)
-  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > (M > 1 ? 4096 : 1 << 18)) return false;
+// Which steps take this path.  The chain of launches costs 6 to 8 us a layer more than the items, a step's beginning (the fill, the loads of a
+// cold launch) 6.5 once; what takes the gain away is rows that every workgroup polls and reads out of LDS, items that leave a round of workgroups
+// half empty, and pieces of the key axis past a round of them (takes).  us a layer, launch by launch | here, two cached tiles a query unless said:
+//   layers: one row of width 1024, one layer 24.6 | 23.9, at 24 tiles 26.7 | 26.7, at 60 29.0 | 31.1; two layers 25.1 | 21.5, eight 25.6 | 19.8; of width
+//   896, one layer 24.8 | 26.1, two 25.3 | 23.6; four rows of width 1024, two layers 27.3 | 27.0, four 27.6 | 25.7; two of width 512, one 18.4 | 20.8,
+//   two 19.1 | 18.0, four 19.6 | 16.7; one row of width 4096, 38 tiles, two layers 85.3 | 86.9, four 86.0 | 85.5.
+//   width, one row, eight layers: 3072 51.0 | 44.5, 4096 82.6 | 78.9, 5120 (320 items on 256 CUs) 107 | 115, 8192 280 | 276; between gate/up and down
+//   14 336 columns gain (width 4096), 18 944 do not (3584) 86.5 | 88.2.  Two rows of 2048, two layers 37.0 | 38.0.
+//   rows times the widest contraction: 9216 (three rows of width 1024) four layers 27.6 | 25.2, 9728 (two tokens of a query, width 896) four layers 25.9 |
+//   26.3, eight 26.2 | 25.6, 12 288 (three rows of width 1280) eight layers 29.6 | 25.8, 14 592 (three of width 896) four layers 27.0 | 26.9, 17 920 (two
+//   of width 1536) eight layers 39.8 | 40.0.
+constexpr int kMaxWidth = 4096, kMaxContraction = 16384;
+static bool shape_fits(const percache_config &c, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers) {
+  const long R = (long)(c.n_q_heads / c.n_kv_heads) * t_fresh, M = (long)batch * t_fresh, A = (long)c.n_q_heads * c.head_dim;
+  if (R > kMaxQueryRows || M > kMaxRows || M * c.hidden > kMaxWidth) return false;
+  if (M * (ffn > A ? ffn : A) > (M == 1 ? kMaxContraction : n_layers < 8 ? 9216 : 12288)) return false;
+  if (n_layers < (M == 1 && c.hidden <= 3072 ? 2 : 4)) return false;
   // the merge of the wavefronts' outputs, in the ring's place
   return (size_t)kWaves * R * (c.head_dim + 6) * 4 + R * 64 <= (size_t)kRing;
 }
@@ -1004,22 +1011,31 @@ static int splits_for(const percache_config &c, int n_cu, int32_t batch, int32_t
 }
 
 size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles) {
-  if (!shape_fits(c, batch, t_fresh)) return 0;
+  if (!shape_fits(c, batch, t_fresh, ffn, n_layers)) return 0;
   const int M = batch * t_fresh;
   const Blocks b = blocks_of(c, M, ffn, splits_for(c, n_cu, batch, t_fresh, max_tiles));
   return ticket_bytes(n_layers) + (n_layers * b.total + b.head()) * 4 + (size_t)n_layers * 2 * dense_elems(c, M) * 2;
 }
 
-// (at most four tiles, two rounds, to a piece: more of them want the ring of decode_attention_kernel)
-// Several rows: only while the pieces leave a third of the CUs to the items around them -- past that the pieces of one layer hold the
-// workgroups that should have its o_proj and gate/up weights on their way.  us a step of two layers, launch by launch | here (pieces for 256 CUs):
-// width 1024, 2 rows 257 | 223 (160), 260 | 262 (216), 3 rows 258 | 227 (144), 262 | 271 (240), 306 | 350 (512), 4 rows 259 | 259 (192),
-// 283 | 311 (448); width 896, 2 rows 271 | 250 (168), 280 | 284 (232), 3 rows 267 | 246 (156), 273 | 293 (204), 4 rows 266 | 256 (144),
-// 269 | 291 (208), 289 | 340 (464).  One row keeps its gain up to a piece a CU (width 1024, 100 tiles 289 | 250).
-bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int max_tiles) {
-  if (!shape_fits(c, batch, t_fresh)) return false;
-  const int ns = splits_for(c, n_cu, batch, t_fresh, max_tiles);
-  return max_tiles + 2 <= 4 * ns && (batch * t_fresh == 1 || 3L * batch * c.n_kv_heads * ns <= 2L * n_cu);
+// At most four tiles, two rounds, to a piece: more of them want the ring of decode_attention_kernel.  The pieces of a layer hold the workgroups
+// that should have its o_proj and gate/up weights on their way, and the merge of a kv head's pieces is one workgroup's.  us a layer, launch by
+// launch | here, 256 CUs:
+//   pieces, one row, four layers: width 1024, 248 30.5 | 27.9, 408 32.5 | 30.0, 512 33.6 | 33.6, 16 heads of 64, 320 27.1 | 26.3, 496 28.7 | 28.9; width
+//   2048, 248 40.7 | 37.9, 408 43.0 | 42.6, 512 44.2 | 46.0; width 2560, 160 55.8 | 53.3, 248 56.7 | 56.8, 328 57.9 | 59.8; width 3072, 248 54.1 |
+//   50.6, 408 56.0 | 55.3, 512 57.0 | 60.3; width 4096, 248 86.6 | 87.2, 328 87.9 | 89.8.
+//   two layers: width 1024, 160 28.2 | 24.9, 408 32.2 | 31.2, 512 33.4 | 35.0; width 2560, 160 55.3 | 55.1, 248 56.4 | 58.6.
+//   several rows, four layers, width 1024: two rows, 160 28.8 | 26.2, three 168 29.0 | 28.3, three tokens of a query, 104 29.0 | 27.8, 160 30.1 | 30.4, two
+//   over 16 heads of 64, 64 24.9 | 24.1, 160 26.1 | 27.0; three rows over nothing cached 24.4 | 24.6.
+//   floats that a merge reads (rows x head size x pieces of a kv head), four layers: one row, 48 000 51.5 | 50.3, 55 000 38.1 | 33.8, 63 000 52.4 | 54.0, 73 000
+//   39.3 | 37.9, 91 000 39.8 | 39.5; several, 26 000 31.3 | 30.3, 38 000 32.2 | 32.1, 40 000 31.4 | 32.5.
+bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles) {
+  if (!shape_fits(c, batch, t_fresh, ffn, n_layers)) return false;
+  const int M = batch * t_fresh, ns = splits_for(c, n_cu, batch, t_fresh, max_tiles);
+  const long pieces = (long)batch * c.n_kv_heads * ns, merge = (long)(c.n_q_heads / c.n_kv_heads) * t_fresh * c.head_dim * ns;
+  if (max_tiles + 2 > 4 * ns) return false;
+  if (M > 1) return max_tiles > 0 && pieces * 8 <= n_cu * 5L && merge <= 32768;
+  const int eighths = n_layers < 4 ? 5 : c.hidden <= 1024 ? 14 : 8;   // of n_cu
+  return pieces * 8 <= (long)n_cu * eighths && merge <= 57344;
 }
 
 template <int D>
@@ -1094,12 +1110,11 @@ pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_
   a.n_g = ffn / 16;
   a.per_layer = a.n_q + a.n_t + a.n_x + 2 * a.n_o + a.n_g;
   while ((64 * kWaves >> (a.x_share_log2 + 1)) >= R * (D / 8) && a.x_share_log2 < 5 && (1 << a.x_share_log2) < ns) ++a.x_share_log2;
-  // LDS: the ring and the token rows of a chunk of the contraction; one workgroup a CU (two, which reach further ahead but wait in twice the
+  // LDS: the ring and the token rows of the widest contraction; one workgroup a CU (two, which reach further ahead but wait in twice the
   // number: width 1024, one row 24.5 us a layer against 23.5, four rows 33.4 against 31.3)
-  const int widest = c.hidden > ffn ? (c.hidden > A ? c.hidden : A) : (ffn > A ? ffn : A), need = (widest / 64 + kWaves - 1) / kWaves, step = M * 128, sq = M * (c.hidden / 16) * 4 + 32;
-  const int room = (160 * 1024 - kRing - 512 - sq) / kWaves / step;
-  a.x_steps = need < room ? need : room;
-  a.x_bytes = a.x_steps * step;
+  const int widest = c.hidden > ffn ? (c.hidden > A ? c.hidden : A) : (ffn > A ? ffn : A), sq = M * (c.hidden / 16) * 4 + 32;
+  static_assert(kRing + kMaxContraction * 2 + kWaves * kMaxRows * 128 + kMaxWidth / 4 + 512 <= 160 * 1024 && kMaxWidth <= kRowCols, "LDS of the rows");
+  a.x_bytes = (widest / 64 + kWaves - 1) / kWaves * M * 128;
   const size_t rows_lds = (size_t)kWaves * a.x_bytes, qkv_lds = (size_t)(R + 2 * t_fresh) * D * 2;   // (q, k and v of an attention item stand there too)
   const size_t lds = kRing + (rows_lds + sq > qkv_lds ? rows_lds + sq : qkv_lds);
 

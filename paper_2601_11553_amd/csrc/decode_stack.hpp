@@ -40,13 +40,13 @@ struct Args {
   int M, T, H, Hq, Hkv, ffn, C, n_slots16, tbl_stride, n_splits, n_layers, out_layer;
   int n_q, n_t, n_x, n_o, n_g, per_layer;   // items of a layer
   int first_item, n_items;                  // of this launch
-  int x_steps, x_bytes, x_share_log2;       // LDS of a wavefront's token rows; lanes that share 8 columns in the merge
+  int x_bytes, x_share_log2;                // LDS of a wavefront's token rows; lanes that share 8 columns in the merge
 };
 
 // Workspace of a step through n_layers layers over queries of at most max_tiles cached 64-key tiles (0: the shape does not take this path).
 size_t workspace_bytes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles);
-// Whether a step over queries of at most max_tiles cached 64-key tiles takes it.
-bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int max_tiles);
+// Whether a step through n_layers layers over queries of at most max_tiles cached 64-key tiles takes it.
+bool takes(const percache_config &c, int n_cu, int32_t batch, int32_t t_fresh, int32_t ffn, int n_layers, int max_tiles);
 // The step.  rows: the chunk lists and, behind them, (slot, tokens) per query if append.  table: where they go (with_rows) or stand.
 pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_layers, int ffn, float eps, const __bf16 *h_in, int batch, int t_fresh,
                  const std::vector<int32_t> *rows, int32_t *table, int tbl_stride, bool append, int max_tiles, int formats, __bf16 *h_out, void *ws,

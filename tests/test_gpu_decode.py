@@ -406,15 +406,51 @@ def _step_inputs(H, Hq, Hkv, D, F, L, variant, g):
     return Ws
 
 
+def _one_launch_room(pc, Ws, F, B, T, max_chunks):
+    """Where in a step's workspace the part of the one launch for all layers begins, which nothing else writes: the least size that a call is not
+    refused for.  (Asked with a misaligned pointer: refused for that next, so nothing runs.)"""
+    arr = pc._weights(Ws)
+    keep, ids_p, _, n_p, _ = pc._chunk_args(B, np.zeros((B, max_chunks), np.int32), None, [0] * B)
+    own, own_p = _host_i32([-1] * B)
+    buf = torch.zeros(16, dtype=torch.uint8, device=DEV)
+
+    def status(n_bytes):
+        return pc.lib.percache_stack_decode(pc.ctx, arr, len(Ws), F, EPS, buf.data_ptr(), B, T, ids_p, None, n_p, max_chunks, own_p, buf.data_ptr(),
+                                            (buf.data_ptr() + 255) // 256 * 256 + 16, n_bytes, None)
+    lo, hi = 0, pc.percache_stack_workspace_bytes(B, T, max_chunks, F)
+    assert status(hi) == -1
+    while hi - lo > 1:
+        mid = (lo + hi) // 2
+        st = status(mid)
+        assert st in (-1, -5)
+        lo, hi = (mid, hi) if st == -5 else (lo, mid)
+    return hi
+
+
+def _in_one_launch(pc, Ws, F, B, T, max_chunks, step):
+    """Whether step(), a call of that shape, took all layers in one launch: then the first word of that launch's workspace, its counter of items, is not as
+    it was."""
+    pc._stack_workspace(B, T, pc.percache_stack_workspace_bytes(B, T, max_chunks, F))
+    pc._step_ws.fill_(173)
+    step()
+    torch.cuda.synchronize()
+    at = (-pc._step_ws.data_ptr()) % 256 + _one_launch_room(pc, Ws, F, B, T, max_chunks)
+    return bool((pc._step_ws[at:at + 4] != 173).any())
+
+
 @pytest.mark.parametrize("H,Hq,Hkv,D,F,L,B,T,chunks,C,slots,variant", [
-    (128, 2, 1, 64, 64, 1, 1, 1, 0, 64, "bf16", "plain"),        # wavefronts without a slice, nothing cached, one piece
-    (256, 4, 2, 128, 512, 2, 4, 1, 3, 128, "8bit", "norm"),
-    (1024, 16, 8, 128, 3072, 2, 1, 1, 6, 512, "mixed", "norm"),
-    (896, 14, 2, 64, 4864, 2, 1, 2, 5, 192, "mixed", "bias"),
+    (128, 2, 1, 64, 64, 2, 1, 1, 0, 64, "bf16", "plain"),        # wavefronts without a slice, nothing cached, one piece
+    (256, 4, 2, 128, 512, 4, 4, 1, 3, 128, "8bit", "norm"),
+    (1024, 16, 8, 128, 3072, 4, 1, 1, 6, 512, "mixed", "norm"),
+    (896, 14, 2, 64, 4864, 8, 1, 2, 5, 192, "mixed", "bias"),
     (896, 14, 2, 64, 4864, 34, 1, 1, 70, 64, "bf16", "bias"),    # two launches of layers, chunks past the 64th, one row past kRowCols
-    (3072, 24, 8, 128, 8192, 1, 3, 1, 4, 320, "bf16", "plain"),  # contractions in chunks
-    (384, 16, 1, 128, 192, 2, 1, 1, 16, 1024, "bf16", "plain"),  # 16 rows per kv head, four tiles to a piece
-    (256, 4, 4, 128, 320, 2, 1, 4, 2, 128, "8bit", "plain"),
+    (3072, 24, 8, 128, 8192, 2, 1, 1, 4, 320, "bf16", "plain"),
+    (128, 2, 1, 64, 16384, 2, 1, 1, 1, 64, "bf16", "plain"),     # the widest contraction
+    (1024, 16, 8, 128, 3072, 8, 4, 1, 2, 128, "bf16", "plain"),  # the widest of four rows
+    (384, 14, 1, 64, 192, 2, 1, 1, 16, 960, "bf16", "plain"),    # 240 tiles: four to a piece, the longest merge
+    (384, 15, 1, 128, 192, 2, 1, 1, 6, 192, "mixed", "norm"),    # the most query rows of a kv head at either head size
+    (256, 16, 1, 64, 192, 2, 1, 1, 6, 192, "8bit", "plain"),
+    (256, 4, 4, 128, 320, 4, 1, 4, 2, 128, "8bit", "plain"),
 ])
 def test_step_in_one_launch_against_one_by_one(H, Hq, Hkv, D, F, L, B, T, chunks, C, slots, variant):
     """Steps of a few rows take all layers in one launch unless the QKV or attention kernels' times were asked for.  Both round the same
@@ -432,15 +468,17 @@ def test_step_in_one_launch_against_one_by_one(H, Hq, Hkv, D, F, L, B, T, chunks
     lists = [ids[2 * B + b * chunks: 2 * B + (b + 1) * chunks] for b in range(B)]
     own = [ids[:B], ids[B:2 * B]]
     for s in [s for row in lists for s in row]:
-        n = int(g.integers(1, C + 1))
+        n = int(g.integers(C - 63 if C > 512 else 1, C + 1))
         for layer in range(L):
             pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, n, D))), bf16(g.standard_normal((Hkv, n, D))))
     xs = [bf16(g.standard_normal((B, T, H))) for _ in range(3)]
-    outs = []
+    outs = [[], []]
     for way in (0, 1):
         pc.percache_profile_enable(way == 1, [2])
-        outs.append([host(pc.percache_stack_decode(Ws, F, EPS, x, [lists[b] + ([own[way][b]] if i else []) for b in range(B)], own[way]))
-                     for i, x in enumerate(xs)])
+        for i, x in enumerate(xs):
+            took = _in_one_launch(pc, Ws, F, B, T, chunks + (i > 0), lambda: outs[way].append(host(
+                pc.percache_stack_decode(Ws, F, EPS, x, [lists[b] + ([own[way][b]] if i else []) for b in range(B)], own[way]))))
+            assert took == (way == 0), (way, i)
     pc.percache_profile_enable(False)
     for i, (a, b) in enumerate(zip(*outs)):
         check_hidden(a, b, f"step {i} in one launch against one by one", rel_max=2.0 ** -4 * max(1, L) ** 0.5, rel_fro=6e-3 * L ** 0.5)
@@ -448,6 +486,39 @@ def test_step_in_one_launch_against_one_by_one(H, Hq, Hkv, D, F, L, B, T, chunks
         assert pc.percache_kv_len(0, own[0][b]) == pc.percache_kv_len(L - 1, own[0][b]) == 3 * T
         for x, y in zip(pc.percache_kv_get(0, own[0][b]), pc.percache_kv_get(0, own[1][b])):
             check_hidden(host(x), host(y), "first layer's K/V", rel_max=2.0 ** -4 if slots != "bf16" else 2.0 ** -7)
+
+
+@pytest.mark.parametrize("H,Hq,Hkv,D,F,L,B,T,tiles,one", [
+    (1024, 16, 8, 128, 3072, 1, 1, 1, 2, False), (1024, 16, 8, 128, 3072, 2, 1, 1, 38, True), (1024, 16, 8, 128, 3072, 2, 1, 1, 39, False),
+    (1024, 16, 8, 128, 3072, 4, 1, 1, 110, True), (1024, 16, 8, 128, 3072, 4, 1, 1, 111, False),
+    (2048, 16, 8, 128, 2048, 4, 1, 1, 62, True), (2048, 16, 8, 128, 2048, 4, 1, 1, 63, False),
+    (3072, 2, 1, 64, 128, 2, 1, 1, 2, True), (3200, 2, 1, 64, 128, 2, 1, 1, 2, False), (4096, 2, 1, 64, 128, 4, 1, 1, 2, True), (4224, 2, 1, 64, 128, 4, 1, 1, 2, False),
+    (256, 2, 1, 64, 16384, 2, 1, 1, 2, True), (256, 2, 1, 64, 16448, 2, 1, 1, 2, False),
+    (256, 4, 2, 64, 256, 3, 2, 1, 2, False), (256, 4, 2, 64, 256, 4, 2, 1, 2, True), (256, 4, 2, 64, 256, 4, 2, 1, 0, False),
+    (256, 4, 2, 64, 4608, 4, 2, 1, 2, True), (256, 4, 2, 64, 4672, 4, 2, 1, 2, False), (256, 4, 2, 64, 6144, 8, 2, 1, 2, True), (256, 4, 2, 64, 6208, 8, 2, 1, 2, False),
+    (256, 16, 8, 64, 256, 4, 2, 1, 18, True), (256, 16, 8, 64, 256, 4, 2, 1, 19, False),
+])
+def test_which_steps_take_one_launch(H, Hq, Hkv, D, F, L, B, T, tiles, one):
+    """Both sides of every line of the rule (256 CUs), and the same result up to rounding on either.  (Weights of few distinct layers.)"""
+    if torch.cuda.get_device_properties(0).multi_processor_count != 256:
+        pytest.skip("the lines lie elsewhere")
+    g = np.random.default_rng(31)
+    Ws = _step_inputs(H, Hq, Hkv, D, F, 1, "plain", g) * L
+    C = max(64, tiles * 64)
+    pc = Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=B, slot_capacity=C, max_pos=C + T, device=DEV)
+    for layer in range(L if tiles else 0):
+        for s in range(B):
+            pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, C, D))), bf16(g.standard_normal((Hkv, C, D))))
+    x = bf16(g.standard_normal((B, T, H)))
+    lists = np.arange(B, dtype=np.int32).reshape(B, 1) if tiles else np.zeros((B, 0), np.int32)
+    outs = []
+    assert _in_one_launch(pc, Ws, F, B, T, lists.shape[1], lambda: outs.append(pc.percache_stack_decode(Ws, F, EPS, x, lists, [-1] * B))) == one
+    pc.percache_profile_enable(True, [2])
+    ref = pc.percache_stack_decode(Ws, F, EPS, x, lists, [-1] * B)
+    pc.percache_profile_enable(False)
+    check_hidden(host(outs[0]), host(ref), f"{tiles} tiles", rel_max=2.0 ** -4 * L ** 0.5, rel_fro=6e-3 * L ** 0.5)
+    assert one or torch.equal(outs[0], ref)
+    pc.close()
 
 
 def test_steps_on_two_streams_at_once():
@@ -461,8 +532,9 @@ def test_steps_on_two_streams_at_once():
             for s in range(3):
                 pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, 100, D))), bf16(g.standard_normal((Hkv, 100, D))))
     xs = [bf16(g.standard_normal((1, 1, H))) for _ in range(2)]
-    alone = [pc.percache_stack_decode(Ws, F, EPS, x, [[0, 1, 2]], [-1]) for pc, x in zip(pcs, xs)]
-    torch.cuda.synchronize()
+    alone = []
+    for pc, x in zip(pcs, xs):
+        assert _in_one_launch(pc, Ws, F, 1, 1, 3, lambda: alone.append(pc.percache_stack_decode(Ws, F, EPS, x, [[0, 1, 2]], [-1])))
     streams = [torch.cuda.Stream() for _ in range(2)]
     outs = [[], []]
     for _ in range(20):
@@ -488,32 +560,25 @@ def test_step_in_a_workspace_sized_for_a_longer_call():
     whole = pc.percache_stack_decode(Ws, F, EPS, x, [range(6)], [-1])
     full, longer = (pc.percache_stack_workspace_bytes(1, t, 6, F) for t in (1, 6))
     assert longer < full
+    least = _one_launch_room(pc, Ws, F, 1, 1, 6)
     arr = pc._weights(Ws)
     keep, ids_p, _, n_p, _ = pc._chunk_args(1, [range(6)], None, None)
     none, none_p = _host_i32([-1])
     out = torch.empty_like(x)
 
-    def step(n_bytes):
+    def step(n_bytes, one):
         buf = torch.full((n_bytes + 512,), 173, dtype=torch.uint8, device=DEV)
         at = (-buf.data_ptr()) % 256
-        st = pc.lib.percache_stack_decode(pc.ctx, arr, L, F, EPS, x.data_ptr(), 1, 1, ids_p, None, n_p, 6, none_p, out.data_ptr(),
-                                          buf.data_ptr() + at, n_bytes, torch.cuda.current_stream().cuda_stream)
+        out.zero_()
+        assert pc.lib.percache_stack_decode(pc.ctx, arr, L, F, EPS, x.data_ptr(), 1, 1, ids_p, None, n_p, 6, none_p, out.data_ptr(),
+                                            buf.data_ptr() + at, n_bytes, torch.cuda.current_stream().cuda_stream) == 0
         torch.cuda.synchronize()
         assert (buf[:at] == 173).all() and (buf[at + n_bytes:] == 173).all()
-        return st
-    out.zero_()
-    assert step(longer) == 0
-    check_hidden(host(out), host(whole), "step in the smaller workspace", rel_max=2.0 ** -4 * L ** 0.5, rel_fro=6e-3 * L ** 0.5)   # (as below)
-    one_by_one = out.clone()
-    lo, hi = 0, longer            # the least that is taken: what the launches one by one need
-    while hi - lo > 1:
-        mid = (lo + hi) // 2
-        if step(mid) == 0:
-            hi = mid
-        else:
-            lo = mid
-    assert step(hi - 1) == -5 and step(hi) == 0 and torch.equal(out, one_by_one)
-    assert step(full) == 0 and torch.equal(out, whole)
+        assert bool((buf[at + least:at + least + 4] != 173).any()) == one
+        return out.clone()
+    one_by_one = step(longer, False)
+    check_hidden(host(one_by_one), host(whole), "step in the smaller workspace", rel_max=2.0 ** -4 * L ** 0.5, rel_fro=6e-3 * L ** 0.5)   # (as above)
+    assert torch.equal(step(least, False), one_by_one) and torch.equal(step(full, True), whole)
     h = bf16(g.standard_normal((1, 6, H)))
     pc.percache_stack_reuse(Ws, F, EPS, h, [range(6)])
     held = pc._ws.data_ptr()
@@ -538,5 +603,6 @@ def test_step_through_more_than_64_launches_of_layers():
     each = pc.percache_stack_decode(Ws, F, EPS, x, np.zeros((1, 0), np.int32), [-1])
     pc.percache_profile_enable(False)
     assert not torch.equal(one, x)
+    assert _in_one_launch(pc, Ws, F, 1, 1, 0, lambda: pc.percache_stack_decode(Ws, F, EPS, x, np.zeros((1, 0), np.int32), [-1]))
     check_hidden(host(one), host(each), "2080 layers", rel_max=2.0 ** -4 * 6 ** 0.5, rel_fro=6e-3 * 6 ** 0.5)   # (as above)
     pc.close()
