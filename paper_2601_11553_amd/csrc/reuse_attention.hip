@@ -1590,6 +1590,33 @@ pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, i
   return PC_OK;
 }
 
+// Whether a prompt with more fresh than cached tiles (of its shortest query) takes 128-row blocks, each shared by two sets of wavefronts, longest first,
+// no partitions, where it would take 256-row blocks: the blocks of a kv head are of very different length, and half as long ones even that out.
+// us a call (with a projection of 64 columns), 256-row blocks | these, on 256 CUs, nothing cached unless said:
+//   The kv heads must come out even over the XCDs, since a head's blocks stay on one: 16 heads over 8 kv heads, 2500 rows 99.8 | 89.7; 14 over 2, 2500 rows,
+//   partitions of the key axis on all XCDs against two of them 99.6 | 169.  At head size 64 prompts of more than 24 tiles that are not cut into
+//   partitions gain all the same: 14 over 2, 4224 rows 212 | 201, 2 x 1985 98 | 83, but 3 x 1300 57 | 62.
+//   Where the 256-row blocks would be cut into partitions, their merge goes: 16 over 8, 2 x 1300 87 | 64; 24 over 8, 2 x 1000 89 | 64, over one cached chunk of
+//   512 tokens 102 | 81; 16 over 16, 2050 over 4 chunks 125 | 133 (so: at most a third cached, two thirds in more than one round of blocks, up to 16
+//   tiles any).
+//   Else up to 16 tiles only in one round: 8 x 256 39 | 36, 6 x 400 51 | 57 (the launch has as many blocks for every head of a group, so those that
+//   stand for nothing count: 24 over 8, 6 x 192, 288 of them, 36 | 42); from 16 to 32 the tail of the second round takes the gain away, 28 over 4, 2 x 900
+//   65 | 74; from 32 in less than two rounds, 16 over 8, 3600 rows 136 | 121, over 4 chunks of 512 tokens 197 | 190, 4000 over 4 chunks (504 blocks) 202 | 209, 16 over
+//   16, 2 x 1985 (512) 107 | 111; with nothing cached from 48 tiles a few blocks more, 16 over 8, 4224 rows (528) 148 | 139, 2 x 2050 106 | 105, 32 over 8, 2050
+//   rows 100 | 106.
+static bool pair_pays(const percache_config &c, int n_cu, int batch, int t_fresh, int cached, int cap) {
+  const int G = c.n_q_heads / c.n_kv_heads, R = G * t_fresh, fresh = (t_fresh + TK - 1) / TK;
+  const long heads = (long)batch * c.n_kv_heads, blocks = heads * ((R + 127) / 128), blocks256 = heads * ((R + 255) / 256);
+  if (cached >= fresh || blocks * 8 < n_cu * 5L) return false;
+  const bool one_part = blocks256 >= n_cu || choose_splits(n_cu, blocks256, fresh + cached, cap) == 1;
+  if (heads % 8) return c.head_dim == 64 && one_part && cached == 0 && fresh > 24 && blocks < 2L * n_cu;
+  if (!one_part) return fresh <= 16 || 3 * cached <= (blocks >= n_cu ? 2 : 1) * fresh;
+  if (fresh <= 16) return heads * (((R + 127) / 128 + G - 1) / G * G) <= n_cu;
+  if (fresh < 32) return false;
+  if (blocks < 2L * n_cu) return 3 * cached <= (4 * blocks <= 7L * n_cu ? 2 : 1) * fresh;
+  return fresh >= 48 && cached == 0 && 16 * blocks <= 34L * n_cu;
+}
+
 // Merges the partials of a launch whose key axis was cut into n_splits > 1 partitions.
 template <class P>
 static pc_status launch_combine(percache_ctx *ctx, const P *part_o, const float *part_ml, int n_splits, int batch, int t_fresh, __bf16 *out,
@@ -1640,20 +1667,10 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   const bool halved = !wide && !use8 && c.head_dim == 128 &&
                       (long)batch * c.n_kv_heads * ((R + 63) / 64) * 4 <= ctx->n_cu;
   const int fresh_tiles = (t_fresh + TK - 1) / TK;
-  // A prompt with more fresh than cached tiles whose 256-row blocks leave CUs idle, or about fill them with blocks of very different length:
-  // 128-row blocks shared by two sets of wavefronts, longest first, no partitions.  us an attention call, 256-row blocks | these: width 1024, 1150
-  // rows (72 blocks) 35.1 | 35.4, 2176 (136) 60.8 | 50.5, 3100 (200) 92.7 | 79.7, 4224 (264) 119 | 114, 8192 (512) 279 | 329, 4 x 1000 (256)
-  // 49.4 | 57.0, 2500 over 2 chunks (160) 98 | 82; 24 heads, 1100 rows (104) 40.5 | 35.5, 2176 (208) 67.3 | 55.1, 4224 (400) 152 | 154; 14 heads of 64,
-  // 4224 rows (232) 194 | 182.  At head size 64 only where 256-row blocks would not be cut into partitions, whose merge is cheap there: a layer's
-  // prefill, width 896 and 14 heads, 1964 rows (108 blocks) 188 | 192, 2564 (142) 208 | 246, 3364 (184) 237 | 305, but 3564 (196, one
-  // partition) 352 | 316.
-  const long blocks128 = (long)batch * c.n_kv_heads * ((R + 127) / 128), blocks256 = (long)batch * c.n_kv_heads * ((R + 255) / 256);
-  const bool pair = n_splits <= 0 && wide && !use8 && (tbl_stride - kTblHeader) / 2 <= 64 && 2 * fresh_tiles > min_tiles && blocks128 * 8 >= ctx->n_cu * 5L &&
-                    blocks256 * 10 <= ctx->n_cu * (fresh_tiles >= 32 ? 11L : 8L) &&
-                    (c.head_dim == 128 || choose_splits(ctx->n_cu, blocks256, min_tiles, max_splits_for(c, ctx->n_cu, batch, t_fresh)) == 1);
+  const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
+  const bool pair = n_splits <= 0 && wide && !use8 && (tbl_stride - kTblHeader) / 2 <= 64 && pair_pays(c, ctx->n_cu, batch, t_fresh, min_tiles - fresh_tiles, cap);
   const int qrows = pair ? 128 : wide ? 256 : halved ? 64 : 128;
   const int q_tiles = (R + qrows - 1) / qrows;
-  const int cap = max_splits_for(c, ctx->n_cu, batch, t_fresh);
   // A prompt with more fresh than cached tiles: the workgroups are of unequal length as it is and go heaviest first, so more
   // workgroups than CUs even out without partitions (4224 fresh rows x 16 heads over nothing cached, 264 workgroups, layer of a
   // stack: 1 partition 360 us, 2 363, 4 373 with a merge of 14; before, lightest first and every fresh tile masked: 411 to 421).
