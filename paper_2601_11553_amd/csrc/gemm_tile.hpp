@@ -177,30 +177,36 @@ __device__ __forceinline__ void mainloop_wide(char *lds, WRow w_row, const T *__
   constexpr int W_PER = S::W_BYTES / 1024 / 4, X_PER = S::X_BYTES / 1024 / 4;  // instructions per wavefront and stage
   constexpr int PER = X_PER > W_PER ? X_PER : W_PER, PART = (PER + 2) / 3;          // requested in three parts
   static_assert(W_PER == 8 && X_PER >= 4, "request split below");
-  // (one scalar base and 32-bit lane offsets: pointers of their own would not leave room for the operands of 320 tokens)
+  // From 256 tokens on one scalar base and 32-bit lane offsets: pointers would not leave room for the operands of 320, and take 1 us more of 45 at 256.
+  // At 192 pointers: 24 heads over 8, 2176 rows of width 512 25.9 us, with offsets 26.3; 6 over 1, 2048 rows of width 1024 28.1 against 28.7.
+  constexpr bool POINTERS = NTB < 4;
   const char *const base = (const char *)(loads_w ? w_row(0) : X);
-  unsigned src[PER];
+  typename std::conditional<POINTERS, const T *, unsigned>::type src[PER];
 #pragma unroll
   for (int k = 0; k < PER; ++k) {
     const int row = ((wave & 3) * (loads_w ? W_PER : X_PER) + (k < (loads_w ? W_PER : X_PER) ? k : 0)) * 8 + (lane >> 3);
     const T *at = (loads_w ? w_row(row) : X + (size_t)min(m0 + row, M - 1) * ldx) + (((lane & 7) ^ swz128(row)) * 8);
-    src[k] = (unsigned)((const char *)at - base);
+    if constexpr (POINTERS) src[k] = at;
+    else src[k] = (unsigned)((const char *)at - base);
   }
   char *const dst = lds + (loads_w ? 0 : S::W_BYTES) + (wave & 3) * (loads_w ? W_PER : X_PER) * 1024;
   const int nk = K / BK;
   int f_kt = 0;  // the k-step the next request brings (past the last one: the last one again, into a stage nobody reads)
   // instructions k0 .. k1 - 1 of that request (a token wavefront has fewer: the surplus is skipped)
   auto request_part = [&](int st, int k0, int k1) __attribute__((always_inline)) {
-    const char *const from = base + (size_t)f_kt * (BK * sizeof(T));
+    auto from = [&](int k) __attribute__((always_inline)) {
+      if constexpr (POINTERS) return (const char *)(src[k] + f_kt * BK);
+      else return base + (size_t)f_kt * (BK * sizeof(T)) + src[k];
+    };
     if (loads_w) {
 #pragma unroll
       for (int k = k0; k < (k1 < W_PER ? k1 : W_PER); ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + src[k]),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from(k)),
                                          (__attribute__((address_space(3))) void *)(dst + st * S::STAGE + k * 1024), 16, 0, 0);
     } else {
 #pragma unroll
       for (int k = k0; k < (k1 < X_PER ? k1 : X_PER); ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from + src[k]),
+        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(from(k)),
                                          (__attribute__((address_space(3))) void *)(dst + st * S::STAGE + k * 1024), 16, 0, 0);
     }
   };
