@@ -500,14 +500,21 @@ pc_status launch_qkv_rope(percache_ctx *ctx, const __bf16 *x, const __bf16 *w, i
   // tiles above (one head, up to 192 tokens, rounds of 2 * n_cu), us a launch:
   //   4096 features, K = 1024: 3700 rows 46 | 49, 4096 rows 48 | 51, 4224 rows 52.3 | 54.1, 5120 rows 55.5 | 65.0
   //   5120 features, K = 3072: 2560 rows 85 | 101, 3072 rows 94 | 108, 3800 rows 112 | 142
-  // 320 tokens take 252 registers a lane of the 256, and 147 KB of LDS: there is no wider one.
+  // 320 tokens take 252 registers a lane of the 256, and 147 KB of LDS: there is no wider one.  Narrow contractions are bound by the ends of the
+  // tiles, which the smaller ones hide behind each other, and so do tiles that leave a quarter of the CUs idle:
+  //   256 tokens, 24 heads over 8, 2560 rows: K = 128 22.9 | 21.3, 512 32.0 | 31.0, 768 37.2 | 38.6; 32 over 8, 2048 rows (192 tiles), K = 1024 42.9 | 41.1
+  //   320 tokens, 16 heads over 8, 4600 rows: K = 128 28.7 | 26.5, 384 35.2 | 34.7, 512 38.8 | 39.0, 768 46.0 | 48.0
   const int n_heads_all = c.n_q_heads + 2 * c.n_kv_heads;
   __bf16 *vb_large = (v_blk && v_blk_done && t_fresh % 64 == 0) ? v_blk : nullptr;  // the large tiles lay V out for the attention kernel too
   if (vb_large) *v_blk_done = true;
   int wide = 0;   // its 64-token blocks
   if (c.head_dim == 128 && !extras.any() && n_heads_all % 2 == 0 && M >= 1024)
-    for (int cand = 3; cand <= 5 && !wide; ++cand)
-      if ((long)(n_heads_all / 2) * ((M + 64 * cand - 1) / (64 * cand)) <= ctx->n_cu) wide = cand;
+    for (int cand = 3; cand <= 5; ++cand) {
+      const long tiles = (long)(n_heads_all / 2) * ((M + 64 * cand - 1) / (64 * cand));
+      if (tiles > ctx->n_cu) continue;
+      if (cand == 3 || (tiles * 4 > ctx->n_cu * 3L && c.hidden >= (cand == 4 ? 768 : 512))) wide = cand;
+      break;
+    }
   if (wide) {
 #define PC_WIDE(NN)                                                                                                                                  \
   do {                                                                                                                                               \

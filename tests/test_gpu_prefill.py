@@ -126,19 +126,25 @@ def test_qkv_rope_matches_oracle(shape):
     pc.close()
 
 
-@pytest.mark.parametrize("hidden,n_q_heads,n_kv_heads,batch,t_fresh", [
-    (64, 28, 2, 25, 128),    # 256 tokens: one k-step, 13 token tiles, the last one of half its rows
-    (192, 30, 1, 1, 4096),   # 256 tokens: every tile whole, an odd number of k-steps
-    (128, 28, 2, 11, 384),   # 320 tokens: prompts that straddle tiles, 64 rows in the last one
-    (192, 36, 2, 3, 1101),   # 320 tokens: 20 x 11 tiles, ragged prompts
+@pytest.mark.parametrize("hidden,n_q_heads,n_kv_heads,batch,t_fresh,blocks", [
+    (768, 28, 2, 25, 128, 4),    # 256 tokens: 13 token tiles, the last one of half its rows
+    (832, 30, 1, 1, 4096, 4),    # every tile whole, an odd number of k-steps
+    (512, 28, 2, 11, 384, 5),    # 320 tokens: prompts that straddle tiles, 64 rows in the last one
+    (576, 36, 2, 3, 1101, 5),    # 20 x 11 tiles, ragged prompts, an odd number of k-steps
+    (704, 28, 2, 25, 128, 0), (512, 16, 8, 1, 4096, 0), (448, 28, 2, 11, 384, 0), (768, 44, 2, 1, 2048, 0),   # contractions too narrow, a quarter of the CUs idle
+    (64, 28, 2, 23, 128, 3),     # 192 tokens: one k-step
 ])
-def test_two_head_tiles_of_256_and_320_tokens(hidden, n_q_heads, n_kv_heads, batch, t_fresh):
+def test_two_head_tiles_of_256_and_320_tokens(hidden, n_q_heads, n_kv_heads, batch, t_fresh, blocks):
     """Projections whose 192-token two-head tiles would take a second round of the CUs: q, k and v against the oracle; where the prompts are
     whole 64-key blocks the tiles lay V out for the attention themselves, which then reads the same values as from the packed copy."""
     w = wl.make_prefill("proj_wide", 5, "bf16", hidden, n_q_heads, n_kv_heads, 128, batch, t_fresh, 1, 64, 4)
     pc = make_ctx(w)
     fill_slots(pc, w, w.slot_ids.reshape(-1))
-    q, k, v = pc.percache_qkv_rope(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)
+    outs = []
+    names = kernels_of(lambda: outs.append(pc.percache_qkv_rope(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)))
+    two_heads = [n for n in names if "qkv_rope_kernelILi128E" in n and "ELb1E" in n]
+    assert bool(two_heads) == bool(blocks) and all(f"qkv_rope_kernelILi128ELi{blocks}E" in n for n in two_heads), names
+    q, k, v = outs[0]
     apart = pc.percache_attention_reuse(0, q, k, v, w.slot_ids, w.used_len)
     whole = pc.percache_prefill_reuse(0, bf16(w.X), bf16(w.Wqkv), w.slot_ids, w.used_len)
     torch.cuda.synchronize()
