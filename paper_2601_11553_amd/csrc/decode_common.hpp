@@ -63,11 +63,6 @@ struct RawRow {
       x[ks][0] = *(const f32x4 *)(sums + ks * 32 + g * 8);
       x[ks][1] = *(const f32x4 *)(sums + ks * 32 + g * 8 + 4);
     }
-    load_rest(bias, gain, rope, pos, g);
-  }
-  // all but the sums
-  __device__ __forceinline__ void load_rest(const __bf16 *__restrict__ bias, const __bf16 *__restrict__ gain, const float2 *__restrict__ rope, int pos,
-                                            int g) {
 #pragma unroll
     for (int ks = 0; ks < KS / 2; ++ks)
 #pragma unroll

@@ -337,8 +337,8 @@ __device__ __forceinline__ void project(const KArgs &a, char *lds, WRow w_row, R
 #pragma unroll
   for (int f = 0; f < NF; ++f) acc[f] += odd[f];
 }
-// The next item, taken when the present one has all it waits for: a workgroup that held a second one while it waits would keep that one's
-// loads from being asked for by a workgroup that is free.  By wavefront 1, which has no results to hand over.
+// The next item, taken when the present one has all it waits for (but see merge): a workgroup that held a second one while it waits would keep
+// that one's loads from being asked for by a workgroup that is free.  By wavefront 1, which has no results to hand over.
 __device__ __forceinline__ void claim(unsigned *ticket, int wave, int lane, unsigned &next) {
   typedef __attribute__((address_space(1))) unsigned *G;
   G t = (G)ticket;
@@ -743,7 +743,9 @@ __device__ __forceinline__ void attend(const KArgs &a, char *lds, int layer, int
 
 // ---------------------------------------------------------------------------------------------------
 // X: the pieces of one kv head's rows merged, by the rule of splitkv_combine_kernel.  `share` neighbouring lanes have 8 columns of a row and
-// take every share-th piece.
+// take every share-th piece.  The next item is taken before the pieces are there: behind them a layer of width 3072 is slower (12 tiles 47.8 us, behind
+// them 48.4), most are as fast (width 1024, 38 tiles 23.9 either way); but where the QKV items just fill the CUs nobody else is free for the o_proj's,
+// and it would be the better way (width 2048, 24 tiles 34.5 | 32.3, 1024 over 60 tiles 27.8 | 24.7).
 // ---------------------------------------------------------------------------------------------------
 template <int D>
 __device__ __forceinline__ void merge(const KArgs &a, int layer, int bg, int wave, int lane, unsigned &next) {
@@ -854,8 +856,8 @@ __global__ __launch_bounds__(64 * kWaves, 2) void decode_stack_kernel(const Args
     unsigned *const ticket = pinned(a.ticket);
     const float eps = pinned(a.eps), inv_h = pinned(a.inv_h);
     unsigned next = 0;
-    const int at = a.first_item + item, layer = at / a.per_layer;
-    int id = at - layer * a.per_layer;
+    const int layer = item / a.per_layer;
+    int id = item - layer * a.per_layer;
     const KLayer &w = a.w[layer];
     const size_t blk = layer * a.s_word;
     float *const squares = (float *)(lds + kRing + kWaves * a.x_bytes);   // [M][H / 16] sums of squares of the token rows
@@ -1162,7 +1164,6 @@ pc_status launch(percache_ctx *ctx, const percache_block_weights *layers, int n_
     a.h_out = h_out;
     a.out_layer = l0 + n == n_layers ? n - 1 : -1;
     a.ticket = tickets + k;
-    a.first_item = 0;
     a.n_items = n * a.per_layer;
     const int grid = a.n_items < ctx->n_cu ? a.n_items : ctx->n_cu;
     const pc_status st = D == 128 ? launch_kernel<128>(ctx, fmt, dim3(grid), lds, stream, a) : launch_kernel<64>(ctx, fmt, dim3(grid), lds, stream, a);

@@ -39,7 +39,7 @@ struct Args {
   float eps, inv_h, scale_log2e;
   int M, T, H, Hq, Hkv, ffn, C, n_slots16, tbl_stride, n_splits, n_layers, out_layer;
   int n_q, n_t, n_x, n_o, n_g, per_layer;   // items of a layer
-  int first_item, n_items;                  // of this launch
+  int n_items;                              // of this launch
   int x_bytes, x_share_log2;                // LDS of a wavefront's token rows; lanes that share 8 columns in the merge
 };
 
