@@ -371,7 +371,9 @@ pc_status percache_stack_decode(percache_ctx *ctx, const percache_block_weights 
  * 2 reuse attention (main kernel, without the split merge).
  * on: 0 switches the events off, 1 brackets all three kinds, any other value is a mask in which bit (kernel + 1)
  * selects a kind (4 = the projection only, 8 = attention only, ...): an event pair costs a few microseconds on the
- * stream, so a caller that times a whole step asks only for the kernel it needs. */
+ * stream, so a caller that times a whole step asks only for the kernel it needs.  A step that would take all its layers
+ * in one launch goes launch by launch while kind 1 or 2 is timed: the figures are those of the kernels timed, which is not
+ * what such a step takes otherwise.  Where a lookup merges its lists inside the launch of its pass, kind 0 includes that. */
 typedef enum { PC_KERNEL_LOOKUP = 0, PC_KERNEL_QKV_ROPE = 1, PC_KERNEL_ATTENTION = 2 } pc_kernel;
 pc_status percache_profile_enable(percache_ctx *ctx, int32_t on);
 pc_status percache_profile_read(percache_ctx *ctx, int32_t kernel, float *sum_ms_host, int32_t *count_host);

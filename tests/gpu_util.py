@@ -47,13 +47,3 @@ def fill_slots(pc, w, slots, layer=0):
     for s, (k, v) in kv.items():
         pc.percache_kv_put(layer, s, bf16(k), bf16(v))
     return kv
-
-
-def kernels_of(call):
-    """Names of the kernels that call() launches."""
-    from torch.profiler import ProfilerActivity, profile
-    torch.cuda.synchronize()
-    with profile(activities=[ProfilerActivity.CUDA]) as p:
-        call()
-        torch.cuda.synchronize()
-    return [e.name for e in p.events() if e.device_type == torch.autograd.DeviceType.CUDA]
