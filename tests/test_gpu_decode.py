@@ -546,6 +546,41 @@ def test_steps_on_two_streams_at_once():
         assert all(torch.equal(o, alone[i]) for o in outs[i])
 
 
+@pytest.mark.parametrize("B,L", [(1, 34), (2, 4)])
+def test_step_in_one_launch_captured(B, L):
+    """A step from a device table captured once and replayed between eager calls: the captured list bit for bit every time (its counters and hand-over buffers
+    are set anew by the replay itself), then lists of other lengths written into the table, longer ones and an empty one among them."""
+    g = np.random.default_rng(37)
+    H, Hq, Hkv, D, F, C, n_c = 256, 4, 2, 64, 320, 320, 6
+    Ws = _step_inputs(H, Hq, Hkv, D, F, 2, "norm", g) * (L // 2)
+    pc = Percache(n_layers=L, hidden=H, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=B * n_c, slot_capacity=C, max_pos=n_c * C + 1, device=DEV)
+    for layer in range(L):
+        for s in range(B * n_c):
+            pc.percache_kv_put(layer, s, bf16(g.standard_normal((Hkv, C, D))), bf16(g.standard_normal((Hkv, C, D))))
+    x, out = bf16(g.standard_normal((B, 1, H))), bf16(np.zeros((B, 1, H)))
+    ids = np.arange(B * n_c, dtype=np.int32).reshape(B, n_c)
+    lists = [g.integers(1, 130, (B, n_c)), np.full((B, n_c), C), np.zeros((B, n_c), np.int64), g.integers(0, C + 1, (B, n_c))]
+    table = pc.percache_chunk_table_put(ids, lists[0])
+    arr = pc.percache_stack_reuse_table(Ws, F, EPS, x, table, out)
+    assert _in_one_launch(pc, Ws, F, B, 1, n_c, lambda: pc.percache_stack_reuse_table(Ws, F, EPS, x, table, out, weights=arr))
+    eager = out.clone()
+    graph = torch.cuda.CUDAGraph()
+    with torch.cuda.graph(graph):
+        pc.percache_stack_reuse_table(Ws, F, EPS, x, table, out, weights=arr)
+    for used in lists:
+        pc.percache_chunk_table_put(ids, used, table=table)
+        ref = pc.percache_stack_reuse(Ws, F, EPS, x, ids, used)
+        for _ in range(3):
+            pc._step_ws.fill_(int(g.integers(0, 256)))
+            out.zero_()
+            graph.replay()
+            torch.cuda.synchronize()
+            if used is lists[0]:
+                assert torch.equal(out, eager)
+            check_hidden(host(out), host(ref), "replayed", rel_max=2.0 ** -4 * L ** 0.5, rel_fro=6e-3 * L ** 0.5)   # (as above)
+    pc.close()
+
+
 def test_step_in_a_workspace_sized_for_a_longer_call():
     """28 layers hand on more between their parts than 6 fresh tokens need as workspace: a step in a buffer of the longer call's size is taken,
     launch by launch, one byte less than that takes is refused, and a step leaves the workspace that the binding holds for prompts where it is."""

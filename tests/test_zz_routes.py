@@ -79,3 +79,16 @@ def test_which_prompts_take_shared_128_row_blocks(t_fresh, Hq, Hkv, D, batch, ch
     ref = pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=2)
     check_close(host(outs[0]), host(ref), f"T={t_fresh} batch {batch} chunks {chunks}")
     pc.close()
+
+
+@pytest.mark.parametrize("tiles,merged", [(45, True), (57, True), (59, False)])
+def test_which_steps_merge_their_partials_in_the_o_proj(tiles, merged):
+    """One layer, one row of 4 heads: launch by launch, up to 30 partials merged by the o_proj itself."""
+    D, Hkv, H, F = 128, 2, 256, 64
+    pc = Percache(n_layers=1, hidden=H, n_q_heads=4, n_kv_heads=Hkv, head_dim=D, n_slots=1, slot_capacity=tiles * 64, max_pos=tiles * 64 + 1, device=DEV)
+    z = lambda *s: torch.zeros(s, device=DEV).bfloat16()  # noqa: E731
+    pc.percache_kv_put(0, 0, z(Hkv, tiles * 64, D), z(Hkv, tiles * 64, D))
+    w = dict(gain1=z(H), wqkv=z(8 * D, H), wo=z(H, 4 * D), gain2=z(H), w_gate=z(F, H), w_up=z(F, H), w_down=z(H, F))
+    names = _kernels_of(lambda: pc.percache_stack_decode([w], F, 1e-6, z(1, 1, H), [[0]], [-1]))
+    assert any("decode_attention_kernel" in n for n in names) and any("oproj_merge_few_kernel" in n for n in names) == merged, names
+    pc.close()
