@@ -113,8 +113,8 @@ pc_status percache_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_p
  * capture, tight serving loops, harnesses that forbid hipMalloc.  Same result as percache_lookup.  The per-workgroup
  * partial results go to a file-scope device array of the library (1 MiB, held by every GPU the library has created
  * a context on until the process ends) instead of a caller workspace; the call allocates and frees nothing.
- *   limits: n_probes <= 32 (one streaming pass of the bank) and a bank whose percache_lookup_workspace_bytes(ctx, 32)
- *           fits the array (bank_capacity up to about one million rows); beyond them PC_ESHAPE, nothing enqueued.
+ *   limits: n_probes <= 32 (one streaming pass of the bank) and a bank whose partial results fit the array (bank_capacity up
+ *           to about one million rows); beyond them PC_ESHAPE, nothing enqueued.
  *   sharing: every call on one GPU, from any context, uses that GPU's one array, and the array keeps the last call's
  *           contents (nothing in it needs clearing: a pass writes every entry it later reads).  Calls that can
  *           overlap on one GPU (different streams, different contexts) race on it; serialise them. */
@@ -125,7 +125,8 @@ pc_status percache_lookup_noalloc(percache_ctx *ctx, const void *probes_dev, int
  * "top-k_refresh") and dense retrieval over chunk embeddings need.  Same similarity, same tie rule (equal
  * similarities: lower row first), sorted best first.
  *   idx_out_dev int32[n_probes * k], sim_out_dev float[n_probes * k]; entries beyond the bank size: idx -1, sim -inf.
- * Same workspace as percache_lookup. */
+ * Same workspace as percache_lookup.  A smaller one, down to 64 bytes for each of 32 probes (256 past 32 probes) and a
+ * workgroup per CU or per 2048 rows, is taken too and costs passes over the bank. */
 pc_status percache_lookup_topk(percache_ctx *ctx, const void *probes_dev, int32_t n_probes, int32_t k,
                                int32_t *idx_out_dev, float *sim_out_dev, void *workspace_dev,
                                size_t workspace_bytes, void *stream);

@@ -239,11 +239,86 @@ struct RowScan {
   int first;               // 1: first pass (outputs are overwritten), 0: merged with the previous passes
 };
 
+// The k best rows of a probe (k > 1) lie in the k groups of rows whose best rows are the best (of equal ones, the lower row's).  So a pass over the
+// bank with K == kGroups writes for every group its best row and how good the second one is, and topk_groups_kernel picks k groups; only where
+// one of these may hold two of the k rows does it look at rows again.  Sorted lists of eight in every lane, which this replaces, cost ten
+// instructions an entry for nearly every row, because one of a wavefront's 64 lists takes nearly every row in.
+// us a call, 8 best, lists | groups (3 best in brackets): 8 probes, 50 000 rows of width 1024 33.0 | 25.6 (25.9 | 25.3), 200 000 rows 78.9 | 71.6 (71.2 | 71.0),
+// 32 probes 88.9 | 76.6; 64 probes 179 | 92 (175 | 81), 1024 probes 712 | 457 (708 | 450); 2000 rows of width 768, 32 probes 22.3 | 16.2, 1024 probes
+// 43.8 | 46.9 (39.2 | 41.1).
+// A group is what one lane or two meet in a stretch of the bank; which rows these are only Groups::row knows.  A workgroup has about four a
+// wavefront: under many probes their bytes count, but over a small bank two of the k best rows would often share a large one.
+constexpr int kGroups = -1;
+struct Group {
+  float best, second;   // without the probe's norm; best: a NaN where no row has a similarity that is a number
+  int row, unused;
+};
+struct Groups {
+  enum Kind { stream, wide, big, big_fine };
+  Group *g;      // [probes][n]
+  int n;         // of a probe
+  int p0;        // this pass's first probe
+  int kind;
+  int stretch;   // blocks (tiles) of a group
+  int per;       // groups of a wavefront (workgroup)
+  int per_wg;    // blocks of a workgroup; big: workgroups
+  int blocks;    // (tiles) of the bank
+
+  __host__ Groups from_probe(int p) const {
+    Groups o = *this;
+    o.p0 += p;
+    return o;
+  }
+  // A group's rows in jobs of 16 (stream) or 32 consecutive ones: how many jobs, the first row of one (negative: none), and whether row i of it counts.
+  __host__ __device__ int jobs() const { return kind == big ? 2 * stretch : kind == big_fine ? 1 : stretch; }
+  __host__ __device__ int first_row(int group, int job) const {
+    if (kind == big_fine) return (group >> 1) * 32;
+    const int j = group % per, w = group / per;   // of wavefront (workgroup) w
+    if (kind == stream) {
+      const int block = w % 4 + 4 * (j * stretch + job);
+      return block < per_wg && w / 4 * per_wg + block < blocks ? (w / 4 * per_wg + block) * 16 : -1;
+    }
+    if (kind == wide) {
+      const int block = j * stretch + job;
+      return block < per_wg && w * per_wg + block < blocks ? (w * per_wg + block) * 32 : -1;
+    }
+    const int tile = big_begin(w / 4) + j * stretch + job / 2;
+    return tile < big_begin(w / 4 + 1) ? tile * 256 + w % 4 * 64 + job % 2 * 32 : -1;
+  }
+  __host__ __device__ bool counts(int group, int i) const { return kind != big_fine || (i >> 2 & 1) == (group & 1); }
+  __host__ __device__ int big_begin(int wg) const { return (int)((long)wg * blocks / per_wg); }   // a workgroup's first tile
+};
+// The best and the second best of numbers offered in the order of their rows.
+struct Top2 {
+  float m = -INFINITY, s = -INFINITY;
+  int i = INT_MAX;
+  __device__ __forceinline__ void add(float v, int row) {   // (a NaN changes nothing, and -infinity not i: see first)
+    i = v > m ? row : i;
+    s = __builtin_amdgcn_fmed3f(m, s, v);
+    m = fmaxf(m, v);
+  }
+  __device__ __forceinline__ void first(float v, int row) { i = v == v && row < i ? row : i; }   // (where no number is above -infinity)
+  __device__ __forceinline__ void merge(const Top2 &o) {
+    s = fmaxf(fmaxf(s, o.s), fminf(m, o.m));
+    if (better(o.m, o.i, m, i)) { m = o.m; i = o.i; }
+  }
+  __device__ __forceinline__ Top2 of_lane_xor(int o) const {
+    Top2 t;
+    t.m = __shfl_xor(m, o, 64);
+    t.s = __shfl_xor(s, o, 64);
+    t.i = __shfl_xor(i, o, 64);
+    return t;
+  }
+};
+__device__ __forceinline__ void write_group(Group *to, const Top2 &t) {   // (a second of +infinity: its rows are looked at again)
+  *(f32x4 *)to = f32x4{t.i == INT_MAX ? __builtin_nanf("") : t.m, t.m == -INFINITY ? INFINITY : t.s, __int_as_float(t.i), 0.f};
+}
+
 template <int NPB, int CHB, int NSTG, int K>
 __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__restrict__ bank,
                                                             const float *__restrict__ inv_norm, int N, int d,
                                                             const _Float16 *__restrict__ probes, int n_probes,
-                                                            int per_wg, int ring_off, Best *__restrict__ partial, RowScan rs, InLaunch in_launch) {
+                                                            int per_wg, int ring_off, Best *__restrict__ partial, RowScan rs, InLaunch in_launch, Groups gm) {
   extern __shared__ __align__(16) char smem[];
   constexpr int CS = CHB / 64;           // MFMA k-steps (32 elements) per chunk
   constexpr int STG = 16 * CHB;          // bytes per stage
@@ -280,7 +355,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   char *ring = smem + ring_off + wave * (NSTG * STG);
 
   constexpr int KL = K > 0 ? K : 1;
-  TopK<KL> best[NPB];  // this lane's best rows for probe pb*16 + r16
+  TopK<KL> best[NPB];  // this lane's best rows for probe pb*16 + r16 (K > 0)
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) best[pb].clear();
   // per-row mode: the product is taken the other way round (probes on the M side), so a lane holds ONE row (r16) and
@@ -313,6 +388,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
 #pragma unroll
   for (int s = 0; s < CS; ++s) rd_off[s] = r16 * CHB + (((4 * s + g) ^ row_swz<CHB>(r16)) * 16);
 
+  Top2 top[NPB];   // (K == kGroups) of the group that this wavefront is in
   f32x4 acc[NPB];
   auto clear = [&]() __attribute__((always_inline)) {
 #pragma unroll
@@ -346,6 +422,34 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
         for (int pb = 0; pb < NPB; ++pb) {
           const float s = acc[pb][r] * inv4[r];
           if (ok) best[pb].insert(s, row);
+        }
+      }
+    } else if (K == kGroups) {
+      // this lane's four rows of the block per probe; at the end of a stretch the four lanes of the probe
+      const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 16 + g * 4);
+      const int nth = (rb - rb_begin) >> 2;   // of this wavefront's blocks
+      const bool ends = (nth + 1) % gm.stretch == 0 || rb + 4 >= rb_end;
+#pragma unroll
+      for (int pb = 0; pb < NPB; ++pb) {
+        float v[4];
+#pragma unroll
+        for (int r = 0; r < 4; ++r) {
+          const int row = rb * 16 + g * 4 + r;
+          v[r] = row < N ? acc[pb][r] * inv4[r] : __builtin_nanf("");
+          top[pb].add(v[r], row);
+        }
+        if (__ballot(top[pb].i == INT_MAX)) {
+          if (top[pb].i == INT_MAX)
+#pragma unroll
+            for (int r = 0; r < 4; ++r) top[pb].first(v[r], rb * 16 + g * 4 + r);
+        }
+        if (ends) {
+          Top2 t = top[pb];
+          t.merge(t.of_lane_xor(16));
+          t.merge(t.of_lane_xor(32));
+          if (g == 0 && pb * 16 + r16 < n_probes)
+            write_group(gm.g + (size_t)(gm.p0 + pb * 16 + r16) * gm.n + (blockIdx.x * 4 + wave) * gm.per + nth / gm.stretch, t);
+          top[pb] = Top2{};
         }
       }
     } else {
@@ -411,7 +515,12 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
     PC_LOOKUP_WAIT_VMCNT(0);
   }
 
-  if (K == 0) return;  // per-row mode: everything has been written
+  if (K == kGroups) {   // groups that this wavefront has no rows for
+    const int mine = rb_end > rb_begin + wave ? (rb_end - rb_begin - wave + 3) / 4 : 0;
+    for (int j = (mine + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
+      if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.n + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
+  }
+  if (K <= 0) return;  // per-row mode and groups: everything has been written
   constexpr bool CAN_MERGE = NPB == 1 && K > 0 && K <= 4;
   merge_workgroup_lists<NPB, KL>(best, smem, partial, CAN_MERGE && in_launch.marks);
   if constexpr (CAN_MERGE) {
@@ -419,92 +528,317 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
 }
 
+// The inverse norm of a probe, by the first 256 threads of a workgroup; part [4] in LDS; one barrier.
+__device__ __forceinline__ float probe_inverse_norm(const _Float16 *__restrict__ probe, int d, int tid, float *part) {
+  float ss = 0.f;
+  if (tid < 256)
+    for (int v = tid; v < d / 8; v += 256) {
+      const f16x8 h = __builtin_bit_cast(f16x8, ((const u32x4 *)probe)[v]);
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+    }
+#pragma unroll
+  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+  if (tid < 256 && (tid & 63) == 0) part[tid >> 6] = ss;
+  __syncthreads();
+  const float tot = ((part[0] + part[1]) + part[2]) + part[3];
+  return tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
+}
+
 // ---------------------------------------------------------------------------------------------------
-// Per probe: merge the workgroup partial lists, divide by the probe's norm, compare the best with tau.
-// One workgroup of four wavefronts per probe, one thread per partial list (a thread takes its first list as it
-// stands -- the lists are sorted, best first -- and inserts any further ones); then k rounds of "the best head of
-// all threads wins and its owner pops it".  k <= K entries are written per probe.
+// Per probe: the best of the workgroups' best rows, divided by the probe's norm and compared with tau.  One workgroup
+// of four wavefronts per probe.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kFinalizeThreads = 256;
-template <int K>
-__global__ __launch_bounds__(kFinalizeThreads) void lookup_finalize_kernel(const Best *__restrict__ partial, int n_partials,
-                                                                           int partial_stride, const _Float16 *__restrict__ probes,
-                                                                           int d, float tau, int k, int32_t *__restrict__ idx_out,
+__global__ __launch_bounds__(kFinalizeThreads) void lookup_finalize_kernel(const Best *__restrict__ partial, int n_partials, int partial_stride,
+                                                                           const _Float16 *__restrict__ probes, int d, float tau, int32_t *__restrict__ idx_out,
                                                                            float *__restrict__ sim_out, uint8_t *__restrict__ hit_out) {
   constexpr int NWV = kFinalizeThreads / 64;
   __shared__ float norm_part[NWV];
-  __shared__ float red_s[2][NWV];
-  __shared__ int red_i[2][NWV];
+  __shared__ Best red[NWV];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  float ss = 0.f;
-  const u32x4 *src = (const u32x4 *)(probes + (size_t)p * d);
-  for (int v = tid; v < d / 8; v += kFinalizeThreads) {
-    f16x8 h = __builtin_bit_cast(f16x8, src[v]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+  Best b{-INFINITY, INT_MAX};
+  for (int w = tid; w < n_partials; w += kFinalizeThreads) {
+    const Best o = partial[(size_t)w * partial_stride + p];
+    if (o.idx != INT_MAX && better(o.s, o.idx, b.s, b.idx)) b = o;
   }
 #pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  if (lane == 0) norm_part[wave] = ss;
-  TopK<K> mine;
-  mine.clear();
-  if (tid < n_partials) {
-    const Best *lst = partial + ((size_t)tid * partial_stride + p) * K;
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      const Best b = lst[j];
-      mine.s[j] = b.idx != INT_MAX ? b.s : -INFINITY;
-      mine.i[j] = b.idx;
-    }
+  for (int o = 32; o > 0; o >>= 1) {
+    const Best c{__shfl_xor(b.s, o, 64), __shfl_xor(b.idx, o, 64)};
+    if (better(c.s, c.idx, b.s, b.idx)) b = c;
   }
-  for (int w = tid + kFinalizeThreads; w < n_partials; w += kFinalizeThreads) {
-    const Best *lst = partial + ((size_t)w * partial_stride + p) * K;
+  if (lane == 0) red[wave] = b;
+  const float inv = probe_inverse_norm(probes + (size_t)p * d, d, tid, norm_part);
+  if (tid != 0) return;
 #pragma unroll
-    for (int j = 0; j < K; ++j) {
-      Best b = lst[j];
-      if (b.idx != INT_MAX) mine.insert(b.s, b.idx);
+  for (int w = 1; w < NWV; ++w)
+    if (better(red[w].s, red[w].idx, b.s, b.idx)) b = red[w];
+  const float sim = b.idx == INT_MAX ? -INFINITY : b.s * inv;
+  idx_out[p] = b.idx == INT_MAX ? -1 : b.idx;
+  sim_out[p] = sim;
+  hit_out[p] = sim > tau ? 1 : 0;
+}
+
+// ---------------------------------------------------------------------------------------------------
+// The k best rows of a probe out of its groups (see Group); one workgroup of eight wavefronts per probe.  The groups are dealt to 64 bins; the
+// k-th best bin's largest value is a bound that k groups reach, and usually hardly any more: these few are compared with each other.  Where
+// the second row of none of the k best groups comes near, their best rows are the answer.  Otherwise the rows of the groups in question are
+// multiplied by the probe again, with the product and the order of the pass, so that every sum comes out as it did there.
+// What bounds it is latency: of the load of the groups and of five steps that meet at a barrier.
+// A call of 8 probes over 50 000 rows of width 1024 takes 3.5 us more than one for the best row; where a probe is in doubt, 4 to 10 us more.
+// ---------------------------------------------------------------------------------------------------
+constexpr int kMaxTopK = 8;
+constexpr int kSelectThreads = 512, kSelectHeld = 8, kCandidates = 1024;
+// similarities as numbers that rise with them; 0: not a number
+__device__ __forceinline__ unsigned ordered(float v) {
+  const unsigned u = __float_as_uint(v + 0.f);   // (-0 becomes 0)
+  return v != v ? 0u : u & 0x80000000u ? ~u : u | 0x80000000u;
+}
+// a similarity and its row in one number: the larger similarity is larger, and the lower row among equals
+__device__ __forceinline__ unsigned long long key_of(unsigned v, int row) { return (unsigned long long)v << 32 | (unsigned)~row; }
+__device__ __forceinline__ int row_of(unsigned long long key) { return ~(int)(unsigned)key; }
+__device__ __forceinline__ float value_of(unsigned long long key) {   // (-0 comes back as 0)
+  const unsigned o = (unsigned)(key >> 32);
+  return __uint_as_float(o & 0x80000000u ? o & 0x7fffffffu : ~o);
+}
+__global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups gm, const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm, int N, int d,
+                                                                     const _Float16 *__restrict__ probes, int k, int32_t *__restrict__ idx_out,
+                                                                     float *__restrict__ sim_out) {
+  constexpr int WAVES = kSelectThreads / 64;
+  __shared__ unsigned top[kSelectThreads];
+  __shared__ __align__(16) unsigned long long cand[kCandidates + 8];
+  __shared__ uint2 cand_more[kCandidates];   // group, ordered second
+  __shared__ unsigned long long sel[kMaxTopK];
+  __shared__ uint2 sel_more[kMaxTopK];
+  __shared__ int bin_rank[64], n_cand;
+  __shared__ float norm_part[4];
+  const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const Group *const groups = gm.g + (size_t)p * gm.n;
+  const _Float16 *const probe = probes + (size_t)p * d;
+  // the groups: the first kSelectHeld a thread stay in registers
+  Group held[kSelectHeld];
+#pragma unroll
+  for (int i = 0; i < kSelectHeld; ++i) {
+    held[i].best = __builtin_nanf("");
+    if (i * kSelectThreads + tid < gm.n) held[i] = groups[i * kSelectThreads + tid];
+  }
+  if (tid < 64) bin_rank[tid] = 0;
+  if (tid == 0) n_cand = 0;
+  const float inv = probe_inverse_norm(probe, d, tid, norm_part);
+  unsigned best = 0;
+#pragma unroll
+  for (int i = 0; i < kSelectHeld; ++i) best = max(best, ordered(held[i].best));
+#pragma unroll 8
+  for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) best = max(best, ordered(groups[at].best));
+  top[tid] = best;
+  __syncthreads();
+  // the k-th best of 64 bins; a wavefront compares all of them with eight
+  unsigned bin = top[lane];
+#pragma unroll
+  for (int w = 1; w < WAVES; ++w) bin = max(bin, top[w * 64 + lane]);
+  {
+    int before = 0;
+#pragma unroll
+    for (int j = 0; j < 64 / WAVES; ++j) {
+      const int o = wave * (64 / WAVES) + j;
+      const unsigned v = __builtin_amdgcn_readlane(bin, o);
+      before += v > bin || (v == bin && o < lane);
     }
+    if (before) atomicAdd(&bin_rank[lane], before);
   }
   __syncthreads();
-  float tot = 0.f;
+  const unsigned bound = max(1u, (unsigned)__builtin_amdgcn_readlane(bin, __builtin_ctzll(__ballot(bin_rank[lane] == k - 1))));
+  auto offer = [&](const Group &o, int at) __attribute__((always_inline)) {
+    const unsigned v = ordered(o.best);
+    if (v < bound) return;
+    const int to = atomicAdd(&n_cand, 1);
+    if (to >= kCandidates) return;
+    cand[to] = key_of(v, o.row);
+    cand_more[to] = make_uint2(at, ordered(o.second));
+  };
+  if (best >= bound) {
 #pragma unroll
-  for (int w = 0; w < NWV; ++w) tot += norm_part[w];
-  const float inv = tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
-  for (int j = 0; j < k; ++j) {
-    float s = mine.s[0];
-    int i = mine.i[0];
+    for (int i = 0; i < kSelectHeld; ++i) offer(held[i], i * kSelectThreads + tid);
+    for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) offer(groups[at], at);
+  }
+  __syncthreads();
+  int n = n_cand;
+  if (n <= kCandidates) {
+    for (int c = tid; c < n; c += kSelectThreads) {
+      const unsigned long long mine = cand[c];
+      int before = 0;
+      for (int j0 = 0; j0 < n; j0 += 8) {
+        unsigned long long o[8];
 #pragma unroll
-    for (int o = 32; o > 0; o >>= 1) {
-      float s2 = __shfl_xor(s, o, 64);
-      int i2 = __shfl_xor(i, o, 64);
-      if (better(s2, i2, s, i)) { s = s2; i = i2; }
-    }
-    if (lane == 0) { red_s[j & 1][wave] = s; red_i[j & 1][wave] = i; }
-    __syncthreads();  // (the buffer of round j is written again in round j + 2, behind the barrier of round j + 1)
-    s = red_s[j & 1][0];
-    i = red_i[j & 1][0];
+        for (int j = 0; j < 8; ++j) o[j] = cand[j0 + j];
 #pragma unroll
-    for (int w = 1; w < NWV; ++w) {
-      const float s2 = red_s[j & 1][w];
-      const int i2 = red_i[j & 1][w];
-      if (better(s2, i2, s, i)) { s = s2; i = i2; }
+        for (int j = 0; j < 8; ++j) before += j0 + j < n && o[j] > mine;
+      }
+      if (before < k) {
+        sel[before] = mine;
+        sel_more[before] = cand_more[c];
+      }
     }
-    mine.pop_if(i != INT_MAX && mine.i[0] == i);
-    if (tid == 0) {
-      const float sim = i == INT_MAX ? -INFINITY : s * inv;
-      idx_out[(size_t)p * k + j] = i == INT_MAX ? -1 : i;
-      sim_out[(size_t)p * k + j] = sim;
-      if (hit_out && j == 0) hit_out[p] = sim > tau ? 1 : 0;
+    n = min(n, k);
+  } else {
+    // very many equal groups: k times the best one behind the last one taken
+    unsigned long long last = ~0ull;
+    for (int j = 0; j < k; ++j) {
+      unsigned long long key = 0;
+      uint2 more = make_uint2(0, 0);
+      for (int at = tid; at < gm.n; at += kSelectThreads) {
+        const Group c = groups[at];
+        const unsigned long long o = c.best == c.best ? key_of(ordered(c.best), c.row) : 0ull;
+        if (o < last && o > key) {
+          key = o;
+          more = make_uint2(at, ordered(c.second));
+        }
+      }
+      unsigned long long top_key = key;
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) {
+        const unsigned long long other = __shfl_xor(top_key, o, 64);
+        if (other > top_key) top_key = other;
+      }
+      __syncthreads();
+      if (lane == 0) cand[wave] = top_key;
+      __syncthreads();
+#pragma unroll
+      for (int w = 0; w < WAVES; ++w)
+        if (cand[w] > top_key) top_key = cand[w];
+      if (key == top_key) {   // (rows differ: one thread)
+        sel[j] = key;
+        sel_more[j] = more;
+      }
+      last = top_key;
     }
+    n = k;   // (more candidates than that, all of them numbers)
+  }
+  // the k best of the n candidates to the front, in their order
+  auto keep_best = [&](int n) __attribute__((always_inline)) {
+    unsigned long long key[2] = {0, 0};
+    int rank[2] = {k, k};
+#pragma unroll
+    for (int h = 0; h < 2; ++h) {
+      const int c = h * kSelectThreads + tid;
+      if (c >= n) continue;
+      key[h] = cand[c];
+      rank[h] = 0;
+      for (int j0 = 0; j0 < n; j0 += 8) {
+        unsigned long long o[8];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) o[j] = cand[j0 + j];
+#pragma unroll
+        for (int j = 0; j < 8; ++j) rank[h] += j0 + j < n && o[j] > key[h];
+      }
+    }
+    __syncthreads();
+#pragma unroll
+    for (int h = 0; h < 2; ++h)
+      if (rank[h] < k) cand[rank[h]] = key[h];
+    if (tid == 0) n_cand = min(n, k);
+    __syncthreads();
+  };
+  if (tid == 0) n_cand = 0;
+  __syncthreads();
+  const unsigned kth = n == k ? (unsigned)(sel[k - 1] >> 32) : 1u;   // (fewer groups than rows asked for: every row that is a number)
+  bool doubt = n < k;
+  for (int j = 0; j < n; ++j) doubt = doubt || sel_more[j].y >= kth;
+  if (!doubt) {
+    if (tid < k) {
+      idx_out[(size_t)p * k + tid] = row_of(sel[tid]);
+      sim_out[(size_t)p * k + tid] = value_of(sel[tid]) * inv;
+    }
+    return;
+  }
+  const int best_groups = n, per = gm.jobs(), l32 = lane & 31, g2 = lane >> 5, r16 = lane & 15, g = lane >> 4;
+  if (tid < best_groups && sel_more[tid].y < kth) cand[atomicAdd(&n_cand, 1)] = sel[tid];
+  int doubted = 0;
+  for (int s = 0; s < best_groups; ++s) doubted += sel_more[s].y >= kth;
+  __syncthreads();
+  const u32x4 *const b = (const u32x4 *)probe;
+  auto offer_row = [&](float v, int row) __attribute__((always_inline)) {
+    const unsigned o = row < N ? ordered(v) : 0u;
+    if (o >= kth) cand[atomicAdd(&n_cand, 1)] = key_of(o, row);
+  };
+  for (int job0 = 0; job0 < doubted * per; job0 += WAVES) {
+    const int job = job0 + wave;
+    int s = 0;
+    for (int nth = job / per; s < best_groups && (sel_more[s].y < kth || nth-- > 0); ++s) {}
+    const int group = s < best_groups ? (int)sel_more[s].x : 0, row0 = s < best_groups ? gm.first_row(group, job % per) : -1;
+    if (row0 >= 0) {
+      constexpr int U = 8;
+      if (gm.kind == Groups::stream) {
+        const u32x4 *const a = (const u32x4 *)(bank + (size_t)min(row0 + r16, N - 1) * d) + g;
+        f32x4 acc = {0.f, 0.f, 0.f, 0.f};
+        for (int s0 = 0; s0 < d / 32; s0 += U) {
+          u32x4 av[U], bv[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int at = min(s0 + u, d / 32 - 1);
+            av[u] = a[at * 4];
+            bv[u] = b[at * 4 + g];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u)
+            if (s0 + u < d / 32) acc = __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(f16x8, av[u]), __builtin_bit_cast(f16x8, bv[u]), acc, 0, 0, 0);
+        }
+        if (r16 == 0) {   // (every column of the product is this probe's)
+#pragma unroll
+          for (int e = 0; e < 4; ++e) offer_row(acc[e] * inv_norm[min(row0 + g * 4 + e, N - 1)], row0 + g * 4 + e);
+        }
+      } else {
+        const u32x4 *const a = (const u32x4 *)(bank + (size_t)min(row0 + l32, N - 1) * d) + g2;
+        pc::f32x16 acc[2];   // (lookup_wide_kernel: even and odd steps apart)
+#pragma unroll
+        for (int r = 0; r < 16; ++r) acc[0][r] = acc[1][r] = 0.f;
+        for (int s0 = 0; s0 < d / 16; s0 += U) {
+          u32x4 av[U], bv[U];
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            const int at = min(s0 + u, d / 16 - 1);
+            av[u] = a[at * 2];
+            bv[u] = b[at * 2 + g2];
+          }
+#pragma unroll
+          for (int u = 0; u < U; ++u) {
+            if (s0 + u >= d / 16) continue;
+            const f16x8 x = __builtin_bit_cast(f16x8, av[u]), y = __builtin_bit_cast(f16x8, bv[u]);
+            if ((u & 1) && gm.kind == Groups::wide) acc[1] = pc::gemm::mma(x, y, acc[1]);
+            else acc[0] = pc::gemm::mma(x, y, acc[0]);
+          }
+        }
+        if (l32 == 0) {
+#pragma unroll
+          for (int r = 0; r < 16; ++r) {
+            const int i = (r >> 2) * 8 + g2 * 4 + (r & 3);
+            const float v = gm.kind == Groups::wide ? acc[0][r] + acc[1][r] : acc[0][r];
+            if (gm.counts(group, i)) offer_row(v * inv_norm[min(row0 + i, N - 1)], row0 + i);
+          }
+        }
+      }
+    }
+    __syncthreads();
+    static_assert(kCandidates == 2 * kSelectThreads && kCandidates >= 2 * 32 * WAVES, "two a thread; a round of jobs has room behind the k best");
+    if (n_cand > kCandidates - 32 * WAVES) {
+      keep_best(n_cand);
+      __syncthreads();
+    }
+  }
+  n = n_cand;
+  keep_best(n);
+  if (tid < k) {   // (perhaps fewer rows than asked for)
+    idx_out[(size_t)p * k + tid] = tid < n ? row_of(cand[tid]) : -1;
+    sim_out[(size_t)p * k + tid] = tid < n ? value_of(cand[tid]) * inv : -INFINITY;
   }
 }
 
 // ---------------------------------------------------------------------------------------------------
 // Many probes at once (more than the one-pass kernels take): the scan is a matrix product E P^T and is bound by the
-// matrix cores, not by the stream of the bank.  Tiles of 256 bank rows x PT probes (256, or 128 where that pads less
-// and for top-k calls, whose sorted lists need the registers) per workgroup of 8 wavefronts, one workgroup per CU,
+// matrix cores, not by the stream of the bank.  Tiles of 256 bank rows x PT probes (256, or 128 where that pads less)
+// per workgroup of 8 wavefronts, one workgroup per CU,
 // which walks a group of consecutive bank tiles; the bank rows are the M side, so a lane holds, for ONE probe, 32 rows
-// per tile, scales them by the rows' inverse norms and keeps its best (or a running sorted list of K).  A CU takes in
+// per tile, scales them by the rows' inverse norms and keeps its best (or the best two of a group).  A CU takes in
 // at most 64 bytes per clock from L2, which a 128 x 128 tile would need for as long as its MFMAs run; at 256 x 256
 // the operand bytes per flop halve.
 // Wavefront (wa, wb) owns bank-row blocks 2 wa, 2 wa + 1 and probe blocks NB wb .. NB wb + NB - 1 (NB = PT / 64).
@@ -530,7 +864,7 @@ struct BigTile {
 template <int PT, int K>
 __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm,
                                                             int N, int d, const _Float16 *__restrict__ probes, int n_probes,
-                                                            int p_pad, int n_groups, int p_tiles, Best *__restrict__ partial) {
+                                                            int p_pad, int n_groups, int p_tiles, Best *__restrict__ partial, Groups gm) {
   extern __shared__ __align__(16) char smem[];
   using BT = BigTile<PT>;
   constexpr int ROW = 128, RT = kBigRows, NSTG = BT::NSTG, STAGE = BT::STAGE, NA = RT / 128, NB = PT / 64;
@@ -624,8 +958,8 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
     if (MMAS > READS) __builtin_amdgcn_sched_group_barrier(0x008, MMAS - READS, 0);
   };
 
-  static_assert(K == 1 || PT == 128, "the sorted lists of a top-k call need the registers that 256-probe tiles take");
-  TopK<K> best[NB];  // this lane's rows for probes m0 + (NB wb + t) * 32 + l32
+  Top2 top[NB];      // (K == kGroups) of the group that this wavefront is in
+  TopK<1> best[NB];  // this lane's rows for probes m0 + (NB wb + t) * 32 + l32 (K == 1)
 #pragma unroll
   for (int t = 0; t < NB; ++t) best[t].clear();
 
@@ -720,10 +1054,12 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
         best[t].i[0] = up ? row : best[t].i[0];
       }
     } else {
-      // the k best: the same exchanged norms, every scaled product offered to the lane's sorted list (an insertion
-      // happens only when it beats the list's last entry; NaN, past the end of the bank, never does)
+      // lane (l32, 0) has rows 0..3, 8..11, 16..19, 24..27 of a block, lane (l32, 1) the others
+      const int base = r0 + NA * wa * 32 + g * 4;
+      const bool fine = gm.kind == Groups::big_fine, ends = (tile - tile_begin + 1) % gm.stretch == 0 || tile + 1 == tile_end;
 #pragma unroll
-      for (int a = 0; a < NA; ++a)
+      for (int a = 0; a < NA; ++a) {
+        Top2 mine[NB];
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           float inv[4];
@@ -732,50 +1068,70 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
 #pragma unroll
           for (int e = 0; e < 4; ++e)
 #pragma unroll
-            for (int t = 0; t < NB; ++t)
-              best[t].insert(acc[a][t][q4 * 4 + e] * inv[e], r0 + (NA * wa + a) * 32 + q4 * 8 + g * 4 + e);
+            for (int t = 0; t < NB; ++t) mine[t].add(acc[a][t][q4 * 4 + e] * inv[e], a * 32 + q4 * 8 + e);
           __builtin_amdgcn_sched_barrier(0);
         }
+#pragma unroll
+        for (int t = 0; t < NB; ++t) {
+          if (__ballot(mine[t].i == INT_MAX)) {
+            const bool none = mine[t].i == INT_MAX;
+#pragma unroll
+            for (int r = 0; r < 16; ++r) {
+              const float v = acc[a][t][r] * __shfl(inv_mine, a * 32 + (r >> 2) * 8 + g * 4 + (r & 3), 64);
+              if (none) mine[t].first(v, a * 32 + (r >> 2) * 8 + (r & 3));
+            }
+          }
+          mine[t].i += mine[t].i == INT_MAX ? 0 : base;
+          const int p = m0 + (NB * wb + t) * 32 + l32;
+          Group *const to = gm.g + (size_t)(gm.p0 + p) * gm.n;
+          if (fine) {
+            if (p < n_probes) write_group(to + ((tile * 4 + wa) * NA + a) * 2 + g, mine[t]);
+            continue;
+          }
+          top[t].merge(mine[t]);
+          if (a == NA - 1 && ends) {
+            Top2 both = top[t];
+            both.merge(both.of_lane_xor(32));
+            if (g == 0 && p < n_probes) write_group(to + (group * 4 + wa) * gm.per + (tile - tile_begin) / gm.stretch, both);
+            top[t] = Top2{};
+          }
+        }
+      }
     }
   }
-  // the two lanes of a probe, then the four wavefronts (wa) that hold other rows of the same probes: K rounds of
-  // "the best head wins and is popped" between the lanes, then a merge of the four sorted lists
+  if constexpr (K == kGroups) {
+    pc::gemm::wait_vmcnt0();  // (the surplus requests)
+    if (gm.kind == Groups::big)   // groups that this wavefront has no rows for
+      for (int j = (tile_end - tile_begin + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
+        for (int t = 0; t < NB; ++t) {
+          const int p = m0 + (NB * wb + t) * 32 + l32;
+          if (g == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (group * 4 + wa) * gm.per + j, Top2{});
+        }
+    return;
+  }
+  // the two lanes of a probe, then the four wavefronts (wa) that hold other rows of the same probes
   __builtin_amdgcn_s_waitcnt(7 << 4);
   __syncthreads();
-  Best *red = (Best *)smem;  // [wb][wa][NB * 32][K]
+  Best *red = (Best *)smem;  // [wb][wa][NB * 32]
 #pragma unroll
   for (int t = 0; t < NB; ++t) {
-#pragma unroll
-    for (int j = 0; j < K; ++j) {
-      float s = best[t].s[0];
-      int i = best[t].i[0];
-      const float s2 = __shfl_xor(s, 32, 64);
-      const int i2 = __shfl_xor(i, 32, 64);
-      if (better(s2, i2, s, i)) { s = s2; i = i2; }
-      if constexpr (K > 1) best[t].pop_if(i != INT_MAX && best[t].i[0] == i);
-      if (g == 0) red[((wb * 4 + wa) * (NB * 32) + t * 32 + l32) * K + j] = Best{s, i};
-    }
+    float s = best[t].s[0];
+    int i = best[t].i[0];
+    const float s2 = __shfl_xor(s, 32, 64);
+    const int i2 = __shfl_xor(i, 32, 64);
+    if (better(s2, i2, s, i)) { s = s2; i = i2; }
+    if (g == 0) red[(wb * 4 + wa) * (NB * 32) + t * 32 + l32] = Best{s, i};
   }
   __syncthreads();
   if (tid < PT) {  // one thread per probe of the tile: probe wb2 * NB * 32 + within
     const int wb2 = tid / (NB * 32), within = tid % (NB * 32);
-    const Best *lst[4];
-    int head[4];
+    Best b{-INFINITY, INT_MAX};
 #pragma unroll
-    for (int w = 0; w < 4; ++w) { lst[w] = red + ((wb2 * 4 + w) * (NB * 32) + within) * K; head[w] = 0; }
-    Best *out = partial + ((size_t)group * p_pad + m0 + tid) * K;
-    for (int j = 0; j < K; ++j) {
-      Best b{-INFINITY, INT_MAX};
-      int from = 0;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) {
-        const Best c = head[w] < K ? lst[w][head[w]] : Best{-INFINITY, INT_MAX};
-        if (c.idx != INT_MAX && (b.idx == INT_MAX || better(c.s, c.idx, b.s, b.idx))) { b = c; from = w; }
-      }
-      out[j] = b;
-#pragma unroll
-      for (int w = 0; w < 4; ++w) head[w] += (w == from && b.idx != INT_MAX);
+    for (int w = 0; w < 4; ++w) {
+      const Best c = red[(wb2 * 4 + w) * (NB * 32) + within];
+      if (c.idx != INT_MAX && (b.idx == INT_MAX || better(c.s, c.idx, b.s, b.idx))) b = c;
     }
+    partial[(size_t)group * p_pad + m0 + tid] = b;
   }
 }
 
@@ -786,7 +1142,7 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
 // bank, which stream through a ring of LDS stages shared by the workgroup (32 rows x 512 bytes per stage; every
 // load instruction brings two contiguous 512-byte runs; NSTG - 1 stages in flight).  One barrier per stage: it
 // publishes the stage that has landed and retires the one just multiplied.  A lane ends up with 16 rows of one
-// probe per block, scales them by the rows' inverse norms and keeps a running sorted list, as in the kernel above.
+// probe per block, scales them by the rows' inverse norms and keeps its best (or the best two of a group), as in the kernel above.
 // Per-row mode (K == 0, see RowScan): the operands swap sides, so a lane holds ONE row and 16 probes; the wavefronts'
 // candidates of a block meet in LDS and are written out one block later, behind a barrier that is there anyway, by the
 // wavefronts in turn.  The thresholds sit in LDS beside the inverse norms: a load from memory in front of the decision
@@ -802,7 +1158,7 @@ constexpr int kScanHead = kScanMaxBlocksPerWg * 32 * 8 + 2 * 4 * 32 * (int)sizeo
 template <int D_EMB, int K, int CHB = kWideChunk>
 __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm,
                                                              int N, const _Float16 *__restrict__ probes, int n_probes, int per_wg,
-                                                             Best *__restrict__ partial, RowScan rs) {
+                                                             Best *__restrict__ partial, RowScan rs, Groups gm) {
   extern __shared__ __align__(16) char smem[];
   constexpr int NSTG = kWideStages;
   constexpr int CHUNKS = D_EMB * 2 / CHB;  // stages per row block
@@ -876,6 +1232,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
   for (int s = 0; s < CS; ++s) rd_off[s] = l32 * CHB + (((2 * s + g2) ^ (l32 & 15)) * 16);
 
+  Top2 top;   // (K == kGroups) of the group that this workgroup is in
   TopK<(K > 0 ? K : 1)> best;
   best.clear();
   // (K == 0) the candidates of a block whose barrier has passed: one row per lane of the wavefront whose turn it is
@@ -966,6 +1323,33 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
         continue;
       }
       // element r of the product: row (r/4)*8 + 4*g2 + r%4 of the block, probe wave*32 + l32
+      if constexpr (K == kGroups) {
+        float v[16];
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int rin = q4 * 8 + g2 * 4;
+          const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 32 + rin);
+#pragma unroll
+          for (int e = 0; e < 4; ++e) {
+            const int r = q4 * 4 + e, row = rb * 32 + rin + e;
+            v[r] = row < N ? (acc[0][r] + acc[1][r]) * inv4[e] : __builtin_nanf("");
+            top.add(v[r], row);
+          }
+        }
+        if (__ballot(top.i == INT_MAX)) {
+          const bool none = top.i == INT_MAX;
+#pragma unroll
+          for (int r = 0; r < 16; ++r)
+            if (none) top.first(v[r], rb * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3));
+        }
+        const int nth = rb - rb_begin, p = wave * 32 + l32;
+        if ((nth + 1) % gm.stretch == 0 || rb == rb_last) {
+          top.merge(top.of_lane_xor(32));
+          if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + blockIdx.x * gm.per + nth / gm.stretch, top);
+          top = Top2{};
+        }
+        continue;
+      }
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const int rin = q4 * 8 + g2 * 4;
@@ -983,7 +1367,12 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
       write_rows(rb_last);
     }
   }
-  if constexpr (K == 0) return;  // per-row mode: everything has been written
+  if constexpr (K == kGroups) {   // groups that this workgroup has no rows for
+    const int p = wave * 32 + l32;
+    for (int j = (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
+      if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + blockIdx.x * gm.per + j, Top2{});
+  }
+  if constexpr (K <= 0) return;  // per-row mode and groups: everything has been written
   // the two lanes of a probe hold different rows: merge (K rounds of "best head wins and is popped")
   constexpr int KL = K > 0 ? K : 1;
   Best *out = partial + ((size_t)blockIdx.x * kWideProbes + wave * 32 + l32) * KL;
@@ -1055,7 +1444,6 @@ int max_stream_grid(const percache_ctx *ctx) {
   return by_rows > ctx->n_cu ? by_rows : ctx->n_cu;
 }
 
-constexpr int kMaxTopK = 8;
 constexpr int kBatchedFrom = 32;  // more probes than one streaming pass takes: the 128-probe pass or the matrix-product kernel
 // Per-row scan: more new embeddings than one streaming pass takes go through 128-probe passes.  200k rows, streaming passes | 128-probe
 // passes, us: width 384 82 | 66 at 33 to 64, 164 | 70 at 128; width 1024 139 | 103 at 64, 280 | 118 at 128, 490 | 234 at 200.
@@ -1085,28 +1473,28 @@ bool big_tiles_pay(int n_probes) {
 
 template <int NPB, int CHB, int NSTG, int K>
 pc_status launch_stream(percache_ctx *ctx, const StreamShape &sh, hipStream_t st, int N, int d, const _Float16 *pp, int np,
-                        Best *partial, const RowScan &rs, const InLaunch &il) {
+                        Best *partial, const RowScan &rs, const InLaunch &il, const Groups &gm) {
   static bool big_lds_set = false;  // dynamic LDS above 64 KB must be opted into once per kernel
   if (!big_lds_set) {
     PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_stream_kernel<NPB, CHB, NSTG, K>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)kMaxLds));
     big_lds_set = true;
   }
   hipLaunchKernelGGL((lookup_stream_kernel<NPB, CHB, NSTG, K>), dim3(sh.grid), dim3(256), sh.lds, st, ctx->bank, ctx->bank_inv, N, d,
-                     pp, np, sh.per_wg, sh.ring_off, partial, rs, il);
+                     pp, np, sh.per_wg, sh.ring_off, partial, rs, il, gm);
   return PC_OK;
 }
 
 template <int K>
 pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStream_t st, int N, int d, const _Float16 *pp, int np,
-                      Best *partial, const RowScan &rs = RowScan{}, const InLaunch &il = InLaunch{}) {
+                      Best *partial, const RowScan &rs = RowScan{}, const InLaunch &il = InLaunch{}, const Groups &gm = Groups{}) {
   if (npb == 1 && sh.nstg == 3)
-    return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
-           : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
-                           : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);
-  if (npb == 1) return launch_stream<1, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);  // only the widest rows (512-byte chunks) get here
-  return sh.chb == 128   ? launch_stream<2, 128, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
-         : sh.chb == 256 ? launch_stream<2, 256, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il)
-                         : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il);
+    return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+           : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+                           : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
+  if (npb == 1) return launch_stream<1, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);  // only the widest rows (512-byte chunks) get here
+  return sh.chb == 128   ? launch_stream<2, 128, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+         : sh.chb == 256 ? launch_stream<2, 256, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+                         : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
 }
 
 // Per-row scan of up to 128 new embeddings in one pass of the bank.
@@ -1121,12 +1509,28 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
   do {                                                                                                                \
     constexpr int lds = kScanHead + kWideStages * 32 * CC;                                                            \
     PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, 0, CC>, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
-    hipLaunchKernelGGL((lookup_wide_kernel<DD, 0, CC>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, (Best *)nullptr, rs); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, 0, CC>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, (Best *)nullptr, rs, Groups{}); \
   } while (0)
   if (d == 384) PC_SCAN(384, 256); else if (d == 512) PC_SCAN(512, 512); else if (d == 768) PC_SCAN(768, 512); else PC_SCAN(1024, 512);
 #undef PC_SCAN
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;
+}
+
+// What a call of n_probes needs at least: a sorted list per workgroup and probe.
+size_t list_bytes(const percache_ctx *ctx, int32_t n_probes) {
+  size_t lists = (size_t)max_stream_grid(ctx) * kPassProbes;
+  if (n_probes > kBatchedFrom) {
+    // the 256-row kernel: groups * p_tiles <= max(n_cu, 8 p_tiles) workgroups of at most 256 lists
+    const size_t p_big = ((size_t)n_probes + 127) / 128;
+    const size_t big = ((size_t)ctx->n_cu > 8 * p_big ? (size_t)ctx->n_cu : 8 * p_big) * 256;
+    if (big > lists) lists = big;
+    // the 128-probe pass: one list per workgroup and probe
+    const size_t wide_grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
+    const size_t wide = (wide_grid > (size_t)ctx->n_cu ? wide_grid : (size_t)ctx->n_cu) * kWideProbes;
+    if (wide > lists) lists = wide;
+  }
+  return pc::align_up(lists * kMaxTopK * sizeof(Best));
 }
 
 constexpr int kInLaunchProbes = 4;   // (one wavefront of the merging workgroup each)
@@ -1140,6 +1544,145 @@ bool being_captured(hipStream_t st) {
 unsigned long long next_mark() {
   static std::atomic<unsigned long long> counter{std::chrono::steady_clock::now().time_since_epoch().count() * 0x9e3779b97f4a7c15ull | 1};
   return counter.fetch_add(2, std::memory_order_relaxed);
+}
+
+
+// The kernel that a pass of so many probes takes.
+enum class Route { stream, wide, big };
+Route route_of(const percache_ctx *ctx, int n_probes, int N) {
+  const int d = ctx->cfg.emb_dim;
+  if (n_probes > kBatchedFrom && n_probes <= kWideUpTo && (d == 512 || d == 768 || d == 1024)) return Route::wide;
+  // (a workspace may hold the groups of so few probes that a call of many comes here with few: rows too wide for a streaming pass)
+  return n_probes > kBatchedFrom || stream_shape(ctx, 1, N).lds > kMaxLds ? Route::big : Route::stream;
+}
+struct WideShape {
+  int grid, per_wg;
+};
+WideShape wide_shape(int n_cu, int N) {
+  const int n_blocks = (N + 31) / 32;
+  WideShape w;
+  w.grid = n_cu < n_blocks ? n_cu : n_blocks;
+  w.per_wg = (n_blocks + w.grid - 1) / w.grid;
+  if (w.per_wg > kWideMaxBlocksPerWg) w.per_wg = kWideMaxBlocksPerWg;
+  w.grid = (n_blocks + w.per_wg - 1) / w.per_wg;
+  return w;
+}
+int probe_tile(int n_probes) { return big_tiles_pay(n_probes) ? 256 : 128; }
+// The groups of a pass of so many probes (see Groups): about four a wavefront, in the matrix-product kernel at least 1024 in all; there, over a
+// small bank, the 16 rows that a lane has in a block of 32. 
+constexpr int kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
+Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
+  auto cut = [](Groups &g, int blocks, int into) {   // a wavefront's (workgroup's) blocks into that many groups
+    g.stretch = (blocks + into - 1) / into;
+    g.per = (blocks + g.stretch - 1) / g.stretch;
+  };
+  Groups g{};
+  const Route r = route_of(ctx, n_probes, N);
+  if (r == Route::stream) {
+    const StreamShape sh = stream_shape(ctx, 1, N);
+    g.kind = Groups::stream;
+    g.per_wg = sh.per_wg;
+    g.blocks = (N + 15) / 16;
+    cut(g, (sh.per_wg + 3) / 4, kGroupsPerWave);
+    g.n = sh.grid * 4 * g.per;
+  } else if (r == Route::wide) {
+    const WideShape w = wide_shape(ctx->n_cu, N);
+    g.kind = Groups::wide;
+    g.per_wg = w.per_wg;
+    g.blocks = (N + 31) / 32;
+    cut(g, w.per_wg, kGroupsPerWide);
+    g.n = w.grid * g.per;
+  } else {
+    const BigShape bg = big_shape(ctx->n_cu, N, n_probes, probe_tile(n_probes));
+    g.kind = N <= kFineGroupsUpTo ? Groups::big_fine : Groups::big;
+    g.per_wg = bg.groups;
+    g.blocks = (N + kBigRows - 1) / kBigRows;
+    const int least = (kLeastGroups / 4 + bg.groups - 1) / bg.groups;
+    cut(g, (g.blocks + bg.groups - 1) / bg.groups, least > kGroupsPerWave ? least : kGroupsPerWave);
+    g.n = g.kind == Groups::big_fine ? g.blocks * 16 : bg.groups * 4 * g.per;
+  }
+  return g;
+}
+
+// The passes over the bank: the best row of every probe and its hit flag (or, with il.marks, the k best), or (gm) the group maxima.
+pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *probes, int n_probes, float tau, int k, int32_t *idx_out_dev, float *sim_out_dev,
+                     uint8_t *hit_out_dev, Best *partial, const InLaunch &il, const Groups *gm) {
+  const int d = ctx->cfg.emb_dim;
+  const Route route = route_of(ctx, n_probes, N);
+  if (route == Route::wide) {
+    // up to 128 probes: one pass of the bank
+    const WideShape w = wide_shape(ctx->n_cu, N);
+    const size_t lds = (size_t)kWideMaxBlocksPerWg * 32 * sizeof(float) + (size_t)kWideStages * 32 * kWideChunk;
+#define PC_WIDE(DD, KK)                                                                                               \
+  do {                                                                                                                \
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, KK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK>), dim3(w.grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, probes, n_probes, w.per_wg, partial, RowScan{}, \
+                       gm ? *gm : Groups{});                                                                        \
+  } while (0)
+    pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
+    if (!gm) {
+      if (d == 512) PC_WIDE(512, 1); else if (d == 768) PC_WIDE(768, 1); else PC_WIDE(1024, 1);
+    } else {
+      if (d == 512) PC_WIDE(512, kGroups); else if (d == 768) PC_WIDE(768, kGroups); else PC_WIDE(1024, kGroups);
+    }
+    pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
+    PC_HIP(ctx, hipGetLastError());
+#undef PC_WIDE
+    if (gm) return PC_OK;
+    hipLaunchKernelGGL(lookup_finalize_kernel, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, w.grid, kWideProbes, probes, d, tau, idx_out_dev, sim_out_dev, hit_out_dev);
+    PC_HIP(ctx, hipGetLastError());
+    return PC_OK;
+  }
+  if (route == Route::big) {  // (d is a multiple of 64: percache_create checks it)
+    // many probes: the matrix-core product on 256-row tiles, one workgroup per CU; 256-probe tiles where the probes
+    // fill them to three quarters, else 128-probe tiles
+    const int pt = probe_tile(n_probes);
+    const BigShape bg = big_shape(ctx->n_cu, N, n_probes, pt);
+    static bool big_lds_set = false;  // dynamic LDS above 64 KB must be opted into once
+    if (!big_lds_set) {
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<256, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<256>::LDS));
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<256, kGroups>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<256>::LDS));
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, kGroups>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
+      big_lds_set = true;
+    }
+    const dim3 grid((unsigned)((bg.groups + 7) / 8 * 8 * bg.p_tiles));
+    pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
+#define PC_BIG(PP, KK)                                                                                                 \
+  hipLaunchKernelGGL((lookup_big_kernel<PP, KK>), grid, dim3(512), (BigTile<PP>::LDS), st, ctx->bank, ctx->bank_inv, N, d, probes, n_probes, \
+                     bg.p_tiles * pt, bg.groups, bg.p_tiles, partial, gm ? *gm : Groups{})
+    if (!gm) { if (pt == 256) PC_BIG(256, 1); else PC_BIG(128, 1); }
+    else { if (pt == 256) PC_BIG(256, kGroups); else PC_BIG(128, kGroups); }
+#undef PC_BIG
+    pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
+    PC_HIP(ctx, hipGetLastError());
+    if (gm) return PC_OK;
+    hipLaunchKernelGGL(lookup_finalize_kernel, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, bg.groups, bg.p_tiles * pt, probes, d, tau,
+                       idx_out_dev, sim_out_dev, hit_out_dev);
+    PC_HIP(ctx, hipGetLastError());
+    return PC_OK;
+  }
+  // two probe blocks per pass unless their LDS copy leaves no room for the rings (very wide embeddings)
+  const int pass_probes = stream_shape(ctx, 2, N).lds <= kMaxLds ? kPassProbes : 16;
+  for (int p0 = 0; p0 < n_probes; p0 += pass_probes) {
+    int np = n_probes - p0 < pass_probes ? n_probes - p0 : pass_probes;
+    int npb = np <= 16 ? 1 : 2;
+    StreamShape sh = stream_shape(ctx, npb, N);
+    const _Float16 *pp = probes + (size_t)p0 * d;
+    pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
+    // (up to four best rows in one launch: lists of four)
+    pc_status ls = gm       ? launch_pass<kGroups>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, gm->from_probe(p0))
+                   : k == 1 ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
+                            : launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il);
+    if (ls != PC_OK) return ls;
+    pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
+    PC_HIP(ctx, hipGetLastError());
+    if (il.marks || gm) continue;
+    hipLaunchKernelGGL(lookup_finalize_kernel, dim3(np), dim3(kFinalizeThreads), 0, st, partial, sh.grid, npb * 16, pp, d, tau, idx_out_dev + p0, sim_out_dev + p0,
+                       hit_out_dev + p0);
+    PC_HIP(ctx, hipGetLastError());
+  }
+  return PC_OK;
 }
 
 // k best rows per probe (k == 1: the query-level match with its hit flag; hit_out may be null otherwise)
@@ -1162,88 +1705,15 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     PC_HIP(ctx, hipGetLastError());
     return PC_OK;
   }
-  const size_t need = percache_lookup_workspace_bytes(ctx, n_probes);
+  const size_t need = list_bytes(ctx, n_probes);
   if (!workspace_dev || workspace_bytes < need) return pc::fail(ctx, PC_ENOMEM, "lookup workspace has %zu bytes, need %zu", workspace_bytes, need);
   if ((uintptr_t)workspace_dev % 16) return pc::fail(ctx, PC_EINVAL, "workspace must be 16-byte aligned");
   Best *partial = (Best *)workspace_dev;
   const _Float16 *probes = (const _Float16 *)probes_dev;
-  if (n_probes > kBatchedFrom && n_probes <= kWideUpTo && (d == 512 || d == 768 || d == 1024)) {
-    // up to 128 probes: one pass of the bank
-    const int n_blocks = (N + 31) / 32;
-    int grid = ctx->n_cu < n_blocks ? ctx->n_cu : n_blocks;
-    int per_wg = (n_blocks + grid - 1) / grid;
-    if (per_wg > kWideMaxBlocksPerWg) { per_wg = kWideMaxBlocksPerWg; grid = (n_blocks + per_wg - 1) / per_wg; }
-    const size_t lds = (size_t)kWideMaxBlocksPerWg * 32 * sizeof(float) + (size_t)kWideStages * 32 * kWideChunk;
-#define PC_WIDE(DD, KK)                                                                                               \
-  do {                                                                                                                \
-    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, KK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, partial, RowScan{}); \
-  } while (0)
-    for (int p0 = 0; p0 < n_probes; p0 += kWideProbes) {
-      const int np = n_probes - p0 < kWideProbes ? n_probes - p0 : kWideProbes;
-      const _Float16 *pp = probes + (size_t)p0 * d;
-      pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
-      if (k == 1) {
-        if (d == 512) PC_WIDE(512, 1); else if (d == 768) PC_WIDE(768, 1); else PC_WIDE(1024, 1);
-      } else {
-        if (d == 512) PC_WIDE(512, kMaxTopK); else if (d == 768) PC_WIDE(768, kMaxTopK); else PC_WIDE(1024, kMaxTopK);
-      }
-      pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
-      PC_HIP(ctx, hipGetLastError());
-      uint8_t *hit = hit_out_dev ? hit_out_dev + p0 : nullptr;
-      if (k == 1)
-        hipLaunchKernelGGL(lookup_finalize_kernel<1>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, grid, kWideProbes, pp, d, tau, 1,
-                           idx_out_dev + p0, sim_out_dev + p0, hit);
-      else
-        hipLaunchKernelGGL(lookup_finalize_kernel<kMaxTopK>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, grid, kWideProbes, pp, d, tau, k,
-                           idx_out_dev + (size_t)p0 * k, sim_out_dev + (size_t)p0 * k, hit);
-      PC_HIP(ctx, hipGetLastError());
-    }
-#undef PC_WIDE
-    return PC_OK;
-  }
-  if (n_probes > kBatchedFrom) {  // (d is a multiple of 64: percache_create checks it)
-    // many probes: the matrix-core product on 256-row tiles, one workgroup per CU; 256-probe tiles where the probes
-    // fill them to three quarters (best match only: a top-k call's lists need their registers), else 128-probe tiles
-    const int pt = k == 1 && big_tiles_pay(n_probes) ? 256 : 128;
-    const BigShape bg = big_shape(ctx->n_cu, N, n_probes, pt);
-    static bool big_lds_set = false;  // dynamic LDS above 64 KB must be opted into once
-    if (!big_lds_set) {
-      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<256, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<256>::LDS));
-      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
-      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, kMaxTopK>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
-      big_lds_set = true;
-    }
-    const dim3 grid((unsigned)((bg.groups + 7) / 8 * 8 * bg.p_tiles));
-    pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
-#define PC_BIG(PP, KK)                                                                                                 \
-  hipLaunchKernelGGL((lookup_big_kernel<PP, KK>), grid, dim3(512), (BigTile<PP>::LDS), st, ctx->bank, ctx->bank_inv, N, d, probes, n_probes, \
-                     bg.p_tiles * pt, bg.groups, bg.p_tiles, partial)
-    if (k > 1) PC_BIG(128, kMaxTopK); else if (pt == 256) PC_BIG(256, 1); else PC_BIG(128, 1);
-#undef PC_BIG
-    pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
-    PC_HIP(ctx, hipGetLastError());
-    if (k == 1)
-      hipLaunchKernelGGL(lookup_finalize_kernel<1>, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, bg.groups, bg.p_tiles * pt, probes, d, tau, 1,
-                         idx_out_dev, sim_out_dev, hit_out_dev);
-    else
-      hipLaunchKernelGGL(lookup_finalize_kernel<kMaxTopK>, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, bg.groups, bg.p_tiles * pt, probes, d,
-                         tau, k, idx_out_dev, sim_out_dev, hit_out_dev);
-    PC_HIP(ctx, hipGetLastError());
-    return PC_OK;
-  }
-  // two probe blocks per pass unless their LDS copy leaves no room for the rings (very wide embeddings)
-  const int pass_probes = stream_shape(ctx, 2, N).lds <= kMaxLds ? kPassProbes : 16;
-  {  // every pass shape of this call is checked before the first pass is enqueued
-    const size_t lds1 = stream_shape(ctx, 1, N).lds;
-    if (lds1 > kMaxLds) return pc::fail(ctx, PC_ESHAPE, "emb_dim %d needs %zu bytes of LDS per workgroup", d, lds1);
-  }
-  for (int p0 = 0; p0 < n_probes; p0 += pass_probes) {
-    int np = n_probes - p0 < pass_probes ? n_probes - p0 : pass_probes;
-    int npb = np <= 16 ? 1 : 2;
-    StreamShape sh = stream_shape(ctx, npb, N);
-    const _Float16 *pp = probes + (size_t)p0 * d;
-    uint8_t *hit = hit_out_dev ? hit_out_dev + p0 : nullptr;
+  if (stream_shape(ctx, 1, N).lds > kMaxLds && n_probes <= kBatchedFrom)   // (checked before anything is enqueued)
+    return pc::fail(ctx, PC_ESHAPE, "emb_dim %d needs %zu bytes of LDS per workgroup", d, stream_shape(ctx, 1, N).lds);
+  InLaunch il{};
+  if (k <= 4 && n_probes <= kInLaunchProbes && d <= 1024 && workspace_dev != ctx->static_scratch) {
     // A short pass over a small bank merges its lists itself (the marks behind the lists, which one probe block leaves room for): what it saves is a
     // launch, a third of the host's work, what it costs is 0.7 us of the GPU's and, past a probe a wavefront, a second round.  us a call, calls one after
     // the other, the merge apart | here, 2000 rows of width 768: best row of 1 probe 11.6 | 8.7, of 4 11.6 | 8.9, of 8 10.7 | 10.8, 4 best of 1 13.8 | 12.2,
@@ -1251,28 +1721,24 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     // either way: best row of 1 11.7 | 12.5.  Waited for: 2000 rows of width 768, best row of 1 23.7 | 24.0, 4 best of 1 about 31 | 30.5.  A captured
     // call has paid for its launches (best row of 1 8.1 | 8.8, 4 best of 4 12.7 | 12.9), and so no mark is ever used twice.  With more lists than
     // lanes (20 000 rows, 256 lists) the merge here is the slower one from two best on, and behind a long stream the launch apart is hidden.
-    InLaunch il{};
-    if (sh.grid <= kInLaunchGrid && n_probes <= kInLaunchProbes && k <= 4 && d <= 1024 && workspace_dev != ctx->static_scratch && !being_captured(st))
-      il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : 4)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit};
-    pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
-    // (up to four best rows out of lists of four: what the pass spends on a list of eight shows beside the stream, us a pass, eight | four: 3 best
-    // of 1000 rows of width 768 12.9 | 10.7, of 50 000 of width 1024 27.1 | 23.3, of 200 000 71.6 | 68.1, 24 probes 82.7 | 75.3)
-    pc_status ls = k == 1   ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
-                   : k <= 4 ? launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
-                            : launch_pass<kMaxTopK>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il);
+    const StreamShape sh = stream_shape(ctx, 1, N);
+    if (sh.grid <= kInLaunchGrid && !being_captured(st))
+      il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : 4)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit_out_dev};
+  }
+  if (k == 1 || il.marks) return run_passes(ctx, st, N, probes, n_probes, tau, k, idx_out_dev, sim_out_dev, hit_out_dev, partial, il, nullptr);
+  // the groups of as many probes at a time as the workspace holds, then their best rows
+  for (int p0 = 0, np; p0 < n_probes; p0 += np) {
+    np = n_probes - p0;
+    Groups gm = groups_of(ctx, np, N);
+    while (np > 1 && (size_t)np * gm.n * sizeof(Group) > workspace_bytes) {
+      np = np > 256 ? (np - 1) / 256 * 256 : (np + 1) / 2;
+      gm = groups_of(ctx, np, N);
+    }
+    gm.g = (Group *)workspace_dev;
+    const pc_status ls = run_passes(ctx, st, N, probes + (size_t)p0 * d, np, tau, k, nullptr, nullptr, nullptr, nullptr, InLaunch{}, &gm);
     if (ls != PC_OK) return ls;
-    pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
-    PC_HIP(ctx, hipGetLastError());
-    if (il.marks) continue;
-    if (k == 1)
-      hipLaunchKernelGGL(lookup_finalize_kernel<1>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, sh.grid, npb * 16, pp, d, tau, 1,
-                         idx_out_dev + p0, sim_out_dev + p0, hit);
-    else if (k <= 4)
-      hipLaunchKernelGGL(lookup_finalize_kernel<4>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, sh.grid, npb * 16, pp, d, tau, k,
-                         idx_out_dev + (size_t)p0 * k, sim_out_dev + (size_t)p0 * k, hit);
-    else
-      hipLaunchKernelGGL(lookup_finalize_kernel<kMaxTopK>, dim3(np), dim3(kFinalizeThreads), 0, st, partial, sh.grid, npb * 16, pp, d, tau, k,
-                         idx_out_dev + (size_t)p0 * k, sim_out_dev + (size_t)p0 * k, hit);
+    hipLaunchKernelGGL(topk_groups_kernel, dim3(np), dim3(kSelectThreads), 0, st, gm, ctx->bank, ctx->bank_inv, N, d, probes + (size_t)p0 * d, k,
+                       idx_out_dev + (size_t)p0 * k, sim_out_dev + (size_t)p0 * k);
     PC_HIP(ctx, hipGetLastError());
   }
   return PC_OK;
@@ -1300,18 +1766,18 @@ pc_status percache_bank_put(percache_ctx *ctx, int32_t index, const void *emb_de
 
 size_t percache_lookup_workspace_bytes(const percache_ctx *ctx, int32_t n_probes) {
   if (!ctx || n_probes < 0) return 0;
-  size_t lists = (size_t)max_stream_grid(ctx) * kPassProbes;
-  if (n_probes > kBatchedFrom) {
-    // the 256-row kernel: groups * p_tiles <= max(n_cu, 8 p_tiles) workgroups of at most 256 lists
-    const size_t p_big = ((size_t)n_probes + 127) / 128;
-    const size_t big = ((size_t)ctx->n_cu > 8 * p_big ? (size_t)ctx->n_cu : 8 * p_big) * 256;
-    if (big > lists) lists = big;
-    // the 128-probe pass: one list per workgroup and probe
-    const size_t wide_grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
-    const size_t wide = (wide_grid > (size_t)ctx->n_cu ? wide_grid : (size_t)ctx->n_cu) * kWideProbes;
-    if (wide > lists) lists = wide;
+  // Top-k: the groups of all probes of a call (of up to 4096 at a time), for whatever the bank holds; a smaller workspace takes fewer probes at a time.
+  auto grow = [](size_t &a, size_t b) { a = a > b ? a : b; };
+  const size_t n = (size_t)n_probes, cus = (size_t)ctx->n_cu, wide_grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
+  size_t groups = (n < 32 ? n : 32) * max_stream_grid(ctx) * 4 * kGroupsPerWave;
+  if (n > kBatchedFrom) {
+    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * (wide_grid > cus ? wide_grid : cus) * kGroupsPerWide);
+    grow(groups, (n < 256 ? n : 256) * (cus * 4 * kGroupsPerWave + 2 * kLeastGroups));
+    grow(groups, (n < 4096 ? n : 4096) * 2 * kLeastGroups);
   }
-  return pc::align_up(lists * kMaxTopK * sizeof(Best));
+  size_t bytes = list_bytes(ctx, n_probes);
+  grow(bytes, groups * sizeof(Group));
+  return pc::align_up(bytes);
 }
 
 pc_status percache_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes, float tau, int32_t *idx_out_dev,
@@ -1325,7 +1791,7 @@ pc_status percache_lookup_noalloc(percache_ctx *ctx, const void *probes_dev, int
   if (!ctx) return PC_EINVAL;
   if (n_probes > kPassProbes)
     return pc::fail(ctx, PC_ESHAPE, "percache_lookup_noalloc takes at most %d probes per call, got %d", kPassProbes, n_probes);
-  const size_t need = percache_lookup_workspace_bytes(ctx, n_probes < 0 ? 0 : n_probes);
+  const size_t need = list_bytes(ctx, n_probes < 0 ? 0 : n_probes);
   if (need > pc::kStaticScratchBytes)
     return pc::fail(ctx, PC_ESHAPE, "a bank of %d rows needs %zu bytes of scratch, the library's static scratch holds %zu",
                     ctx->cfg.bank_capacity, need, pc::kStaticScratchBytes);
@@ -1347,7 +1813,7 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
   if ((uintptr_t)new_emb_dev % 16) return pc::fail(ctx, PC_EINVAL, "new_emb_dev must be 16-byte aligned");
   const int N = ctx->bank_size, d = c.emb_dim;
   if (N == 0) return PC_OK;  // nothing to mark
-  const size_t need = percache_lookup_workspace_bytes(ctx, n_new);
+  const size_t need = list_bytes(ctx, n_new);
   if (!workspace_dev || workspace_bytes < need || (size_t)n_new * sizeof(float) > need)
     return pc::fail(ctx, PC_ENOMEM, "workspace has %zu bytes, need %zu (and at most %zu new rows per call)", workspace_bytes, need, need / sizeof(float));
   if ((uintptr_t)workspace_dev % 16) return pc::fail(ctx, PC_EINVAL, "workspace must be 16-byte aligned");

@@ -279,6 +279,54 @@ def test_topk_vs_oracle(dim, n_probes, k):
     print(f"top-{k}: {loose} near-tie entries judged by similarity", flush=True)
 
 
+# rows around the kernels' groups: one block, a group's worth more and less, groups of several blocks (stream and wide from 65 536 rows on, tiles from
+# 16 384), the last workgroup's part empty or ragged; 32 | 33, 128 | 129 and 192 probes are other kernels
+@pytest.mark.parametrize("rows,dim,n_probes,k", [
+    (3, 128, 2, 8), (16, 64, 9, 8), (17, 384, 33, 5), (1025, 512, 64, 8), (4097, 64, 200, 8), (16384, 64, 130, 8), (16385, 64, 130, 8),
+    (65536, 128, 16, 3), (65553, 64, 32, 8), (140001, 64, 5, 2), (70001, 512, 40, 8), (70001, 768, 128, 3), (40001, 1024, 8, 8), (33000, 64, 300, 5)])
+def test_topk_groups(rows, dim, n_probes, k):
+    """Planted beside random rows: copies of a row in its group and far away, zero rows, rows that are not numbers; probes near the copies (two of the
+    best in one group) and a zero probe (every similarity the same).  In a workspace that holds the groups and in the smallest one taken.
+    Bound on similarities: fp32 sums of at most 1024 exact products of unit vectors, 2e-6."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + dim)
+    bank = torch.randn((rows, dim), generator=g, device=DEV).half()
+    probes = torch.randn((n_probes, dim), generator=g, device=DEV).half()
+    copies = sorted({r for r in (1, 5, 11, rows // 2, rows - 1) if 0 < r < rows})
+    if rows > 16:
+        for r in copies[1:]:
+            bank[r] = bank[1]
+        bank[7], bank[2], bank[0] = 0, float("nan"), float("inf")
+    probes[0] = bank[1] if rows > 1 else probes[0]
+    probes[1] = 0
+    pc = _ctx(rows + 3, dim)
+    pc.percache_bank_put(0, bank)
+    idx, sim = pc.percache_lookup_topk(probes, k)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    least = max(n_cu * (256 if n_probes > 32 else 32), ((rows + 3) // 2048 + 1) * 32, ((rows + 3) // 6144 + 1) * 128) * 64
+    ws = torch.full((least + 256,), 255, dtype=torch.uint8, device=DEV)
+    i2, s2 = torch.empty_like(idx), torch.empty_like(sim)
+    pc._check(pc.lib.percache_lookup_topk(pc.ctx, probes.data_ptr(), n_probes, k, i2.data_ptr(), s2.data_ptr(), (ws.data_ptr() + 255) // 256 * 256, least,
+                                          torch.cuda.current_stream().cuda_stream))
+    torch.cuda.synchronize()
+    b, p = bank.double(), probes.double()
+    counts = torch.isfinite(b).all(dim=1)
+    unit = lambda x: x / x.norm(dim=1, keepdim=True).clamp(min=1e-30)  # noqa: E731
+    ref = unit(p) @ unit(torch.where(counts[:, None], b, 0.0)).t()
+    ref = torch.where(counts[None], ref, float("-inf"))
+    want, order = torch.sort(ref, dim=1, descending=True, stable=True)
+    kk = min(k, int(counts.sum()))
+    for i, s in ((idx, sim), (i2, s2)):
+        assert (i[:, kk:] == -1).all() and torch.isneginf(s[:, kk:]).all()
+        got = torch.gather(ref, 1, i[:, :kk].long())
+        assert (got - want[:, :kk]).abs().max().item() < 2e-6 and (s[:, :kk].double() - got).abs().max().item() < 2e-6
+        assert all(len(set(r)) == kk for r in i[:, :kk].tolist())
+        assert i[1, :kk].tolist() == order[1, :kk].tolist()                                   # equal similarities: lower rows first
+        if rows > 16:
+            assert i[0, :min(kk, len(copies))].tolist() == copies[:kk]
+    pc.close()
+
+
 def test_topk_ties_small_bank_and_errors():
     d = 128
     g = np.random.default_rng(12)
