@@ -94,6 +94,16 @@ constexpr int kProbePad = 32;  // bytes added to every probe row in LDS (measure
 constexpr int kMaxBlocksPerWg = 128;  // 2048 rows: bounds the LDS copy of the inverse norms (8 KB)
 #define PC_LOOKUP_WAIT_VMCNT(n) __builtin_amdgcn_s_waitcnt(((n) & 0xf) | (7 << 4) | (15 << 8) | ((((n) >> 4) & 3) << 14))
 
+// LDS stores that the compiler does not see: in front of an ordinary one it waits for every direct load to LDS that is on its way.
+__device__ __forceinline__ unsigned lds_addr(const void *p) { return (unsigned)(size_t)(__attribute__((address_space(3))) const char *)(const char *)p; }
+__device__ __forceinline__ void lds_put(const void *p, u32x4 v) { asm volatile("ds_write_b128 %0, %1" : : "v"(lds_addr(p)), "v"(v) : "memory"); }
+__device__ __forceinline__ void lds_put(const void *p, float v) { asm volatile("ds_write_b32 %0, %1" : : "v"(lds_addr(p)), "v"(v) : "memory"); }
+__device__ __forceinline__ void lds_barrier() {   // (not __syncthreads, which waits for these loads too)
+  asm volatile("s_waitcnt lgkmcnt(0)" ::: "memory");
+  __builtin_amdgcn_s_barrier();
+  asm volatile("" ::: "memory");
+}
+
 template <int CHB>
 __device__ __forceinline__ int row_swz(int row) { return CHB >= 256 ? (row & 15) : ((row >> 1) & 7); }
 
@@ -158,10 +168,9 @@ __device__ __forceinline__ void merge_workgroup_lists(TopK<KL> (&best)[NPB], cha
   }
 }
 
-// See InLaunch; a wavefront a probe.  The sums of the probe's norm are added up as lookup_finalize_kernel does.
+// See InLaunch; a wavefront a probe, the sum of whose squares it brings.
 template <int K>
-__device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, const Best *partial, int stride, const _Float16 *__restrict__ probes, int n_probes,
-                                                int d) {
+__device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, const Best *partial, int stride, int n_probes, float tot) {
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6, n = gridDim.x;
   asm volatile("s_waitcnt vmcnt(0)" ::: "memory");   // the lists are in memory
   __syncthreads();
@@ -174,21 +183,8 @@ __device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, c
   }
   __syncthreads();
   if (!*(const int *)smem) return;
-  for (int p = wave; p < n_probes; p += 4) {
-    const u32x4 *src = (const u32x4 *)(probes + (size_t)p * d);
-    float tot = 0.f;
-#pragma unroll
-    for (int q = 0; q < 4; ++q) {
-      float ss = 0.f;
-      for (int v = q * 64 + lane; v < d / 8; v += 256) {
-        const f16x8 h = __builtin_bit_cast(f16x8, src[v]);
-#pragma unroll
-        for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
-      }
-#pragma unroll
-      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-      tot += ss;
-    }
+  const int p = wave;   // (at most kInLaunchProbes)
+  if (p < n_probes) {
     TopK<K> mine;
     mine.clear();
     for (int w = lane; w < n; w += 64) {
@@ -230,7 +226,6 @@ __device__ __forceinline__ void merge_in_launch(const InLaunch &f, char *smem, c
 // Arguments of the per-row mode (K == 0): instead of the best rows per probe, the best PROBE per bank row is
 // written (cache refresh, Sec. 4.1.3: does any new chunk enter a stored query's top-k?).
 struct RowScan {
-  const float *probe_inv;  // [n_probes] inverse norms of the probes
   const float *kth;        // [N] similarity a new chunk must exceed for row j (the row's current k-th best)
   float *best_sim;         // [N] out: best similarity over all new chunks so far
   int32_t *best_new;       // [N] out: index of that chunk, -1 while none has a similarity that is a number
@@ -263,6 +258,7 @@ struct Groups {
   int per;       // groups of a wavefront (workgroup)
   int per_wg;    // blocks of a workgroup; big: workgroups
   int blocks;    // (tiles) of the bank
+  int sets;      // wide: sets of 32 rows in a block, a group of its own each
 
   __host__ Groups from_probe(int p) const {
     Groups o = *this;
@@ -280,7 +276,7 @@ struct Groups {
     }
     if (kind == wide) {
       const int block = j * stretch + job;
-      return block < per_wg && w * per_wg + block < blocks ? (w * per_wg + block) * 32 : -1;
+      return block < per_wg && w / sets * per_wg + block < blocks ? ((w / sets * per_wg + block) * sets + w % sets) * 32 : -1;
     }
     const int tile = big_begin(w / 4) + j * stretch + job / 2;
     return tile < big_begin(w / 4 + 1) ? tile * 256 + w % 4 * 64 + job % 2 * 32 : -1;
@@ -336,36 +332,8 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   const int rb_begin = blockIdx.x * per_wg;
   const int rb_end = min(n_blocks, rb_begin + per_wg);
 
-  // stage probes (zero rows beyond n_probes) and this workgroup's inverse norms (zero beyond N)
-  const int vec_per_row = d / 8;
-  for (int v = tid; v < NPB * 16 * vec_per_row; v += 256) {
-    int p = v / vec_per_row, c = v - p * vec_per_row;
-    u32x4 val = {0, 0, 0, 0};
-    if (p < n_probes) val = ((const u32x4 *)(probes + (size_t)p * d))[c];
-    *(u32x4 *)(smem + (size_t)p * row_bytes + c * 16) = val;
-  }
-  float *inv_lds = (float *)(smem + (size_t)NPB * 16 * row_bytes);
-  for (int r = tid; r < per_wg * 16; r += 256) {
-    int row = rb_begin * 16 + r;
-    inv_lds[r] = row < N ? inv_norm[row] : 0.f;
-  }
-  __syncthreads();
-
   const int chunks = d * 2 / CHB;
   char *ring = smem + ring_off + wave * (NSTG * STG);
-
-  constexpr int KL = K > 0 ? K : 1;
-  TopK<KL> best[NPB];  // this lane's best rows for probe pb*16 + r16 (K > 0)
-#pragma unroll
-  for (int pb = 0; pb < NPB; ++pb) best[pb].clear();
-  // per-row mode: the product is taken the other way round (probes on the M side), so a lane holds ONE row (r16) and
-  // the probes pb*16 + 4g + 0..3; their inverse norms (a padding probe's is a NaN, which no comparison picks)
-  float pinv[NPB][4];
-#pragma unroll
-  for (int pb = 0; pb < NPB; ++pb)
-#pragma unroll
-    for (int e = 0; e < 4; ++e) pinv[pb][e] = (K == 0 && pb * 16 + g * 4 + e < n_probes) ? rs.probe_inv[pb * 16 + g * 4 + e] : __builtin_nanf("");
-
   // load instruction i of a stage: lane lands at stage byte 1024 i + 16 lane = (row, physical chunk)
   int ld_row[IPS], ld_col[IPS];
 #pragma unroll
@@ -383,6 +351,108 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
                                        (__attribute__((address_space(3))) void *)(ring + st * STG + i * 1024), 16, 0, kBankLoadAux);
     }
   };
+  auto advance = [&](int &rb_, int &c_) __attribute__((always_inline)) {
+    if (++c_ == chunks) { c_ = 0; rb_ += 4; }
+  };
+  // flat pipeline over this wavefront's (row block, chunk) items.  Loads are issued unconditionally (past the
+  // end they re-read the last block into a stage nobody will read), so exactly AHEAD items are outstanding
+  // behind the one about to be multiplied and a partial vmcnt wait is exact.
+  int rb = rb_begin + wave, c = 0, prb = rb, pch = 0, ist = 0;
+  const int rb_last = rb_end - 1;
+
+  // Probes (zero rows beyond n_probes) and this workgroup's inverse norms (zero beyond N) to LDS, eight loads a thread at a time; the ring's first
+  // stages are asked for behind the last of these loads, in front of the wait for them: one memory latency, not three.  us a call, one after the
+  // other | like this: best of 200 000 rows of width 1024, 16 probes 67.1 | 65.2, of 50 000 22.3 | 21.4, 32 probes of 200 000 of width 384 32.5 | 30.3.
+  const int vec_per_row = d / 8, n_vec = n_probes * vec_per_row;
+  float *inv_lds = (float *)(smem + (size_t)NPB * 16 * row_bytes);
+  float row_inv[4];
+#pragma unroll
+  for (int e = 0; e < 4; ++e) row_inv[e] = inv_norm[min(rb_begin * 16 + e * 256 + tid, N - 1)];
+  u32x4 val[8];
+  auto fetch = [&](int v0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) val[i] = ((const u32x4 *)probes)[min(v0 + i * 256 + tid, n_vec - 1)];
+  };
+  auto keep = [&](int v0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int i = 0; i < 8; ++i) {
+      const int v = v0 + i * 256 + tid, p = v / vec_per_row, c = v - p * vec_per_row;
+      if (p < NPB * 16) lds_put(smem + (size_t)p * row_bytes + c * 16, p < n_probes ? val[i] : u32x4{0, 0, 0, 0});
+    }
+  };
+  int v0 = 0;
+  for (; v0 + 2048 < NPB * 16 * vec_per_row; v0 += 2048) {
+    fetch(v0);
+    keep(v0);
+  }
+  fetch(v0);
+  __builtin_amdgcn_sched_barrier(0);   // (in this order: the wait for these leaves the ring's loads alone)
+#pragma unroll
+  for (int k = 0; k < AHEAD; ++k) {   // (also without a block of its own: rows of the bank that nobody reads)
+    issue(min(prb, rb_last), pch, ist);
+    advance(prb, pch);
+    ist = ist + 1 == NSTG ? 0 : ist + 1;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  PC_LOOKUP_WAIT_VMCNT(AHEAD * IPS);   // (left to itself the compiler waits for the ring as well)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    const int r = e * 256 + tid;
+    if (r < per_wg * 16) lds_put(inv_lds + r, rb_begin * 16 + r < N ? row_inv[e] : 0.f);
+  }
+  keep(v0);
+  for (int r = 1024 + tid; r < per_wg * 16; r += 256) {
+    const int row = rb_begin * 16 + r;
+    lds_put(inv_lds + r, row < N ? inv_norm[row] : 0.f);
+  }
+  lds_barrier();
+
+  constexpr int KL = K > 0 ? K : 1;
+  TopK<KL> best[NPB];  // this lane's best rows for probe pb*16 + r16 (K > 0)
+#pragma unroll
+  for (int pb = 0; pb < NPB; ++pb) best[pb].clear();
+  // sum of squares of the probe that this wavefront merges (see InLaunch), in the order of probe_inverse_norm
+  constexpr bool CAN_MERGE = NPB == 1 && K > 0 && K <= 4;
+  float merge_sum = 0.f;
+  if (CAN_MERGE && in_launch.marks) {
+#pragma unroll
+    for (int q = 0; q < 4; ++q) {
+      float ss = 0.f;
+      for (int v = q * 64 + lane; v < vec_per_row; v += 256) {
+        const f16x8 h = *(const f16x8 *)(smem + (size_t)wave * row_bytes + v * 16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+      }
+#pragma unroll
+      for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
+      merge_sum += ss;
+    }
+  }
+  // per-row mode: the product is taken the other way round (probes on the M side), so a lane holds ONE row (r16) and
+  // the probes pb*16 + 4g + 0..3; their inverse norms (a padding probe's is a NaN, which no comparison picks).  Sixteen (eight) lanes add up
+  // a probe's squares, from LDS while the ring's first stages are on their way; the norms go to the rows' padding.
+  float pinv[NPB][4];
+  if constexpr (K == 0) {
+    constexpr int LP = 16 / NPB;
+    const int p = tid / LP;
+    {
+      float ss = 0.f;
+      for (int v = tid % LP; v < vec_per_row; v += LP) {
+        const f16x8 h = *(const f16x8 *)(smem + (size_t)p * row_bytes + v * 16);
+#pragma unroll
+        for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+      }
+#pragma unroll
+      for (int o = 1; o < LP; o <<= 1) ss += __shfl_xor(ss, o, 64);
+      if (tid % LP == 0) lds_put(smem + (size_t)p * row_bytes + d * 2, p >= n_probes ? __builtin_nanf("") : ss > 0.f ? 1.0f / sqrtf(ss) : 0.f);
+    }
+    lds_barrier();
+#pragma unroll
+    for (int pb = 0; pb < NPB; ++pb)
+#pragma unroll
+      for (int e = 0; e < 4; ++e) pinv[pb][e] = *(const float *)(smem + (size_t)(pb * 16 + g * 4 + e) * row_bytes + d * 2);
+  }
+
   // swizzled byte offsets of this lane's operand reads inside a stage
   int rd_off[CS];
 #pragma unroll
@@ -481,24 +551,8 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
       }
     }
   };
-  auto advance = [&](int &rb_, int &c_) __attribute__((always_inline)) {
-    if (++c_ == chunks) { c_ = 0; rb_ += 4; }
-  };
-
-  // flat pipeline over this wavefront's (row block, chunk) items.  Loads are issued unconditionally (past the
-  // end they re-read the last block into a stage nobody will read), so exactly AHEAD items are outstanding
-  // behind the one about to be multiplied and a partial vmcnt wait is exact.
-  int rb = rb_begin + wave, c = 0;
-  int prb = rb, pch = 0;
-  const int rb_last = rb_end - 1;
   if (rb < rb_end) {
-    int st = 0, ist = 0;
-#pragma unroll
-    for (int k = 0; k < AHEAD; ++k) {
-      issue(min(prb, rb_last), pch, ist);
-      advance(prb, pch);
-      ist = ist + 1 == NSTG ? 0 : ist + 1;
-    }
+    int st = 0;
     clear();
     while (true) {
       issue(min(prb, rb_last), pch, ist);  // overwrites the stage multiplied in the previous iteration
@@ -512,8 +566,8 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
       st = st + 1 == NSTG ? 0 : st + 1;
       if (rb >= rb_end) break;
     }
-    PC_LOOKUP_WAIT_VMCNT(0);
   }
+  PC_LOOKUP_WAIT_VMCNT(0);
 
   if (K == kGroups) {   // groups that this wavefront has no rows for
     const int mine = rb_end > rb_begin + wave ? (rb_end - rb_begin - wave + 3) / 4 : 0;
@@ -521,10 +575,9 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
       if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.n + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
   }
   if (K <= 0) return;  // per-row mode and groups: everything has been written
-  constexpr bool CAN_MERGE = NPB == 1 && K > 0 && K <= 4;
   merge_workgroup_lists<NPB, KL>(best, smem, partial, CAN_MERGE && in_launch.marks);
   if constexpr (CAN_MERGE) {
-    if (in_launch.marks) merge_in_launch<KL>(in_launch, smem, partial, NPB * 16, probes, n_probes, d);
+    if (in_launch.marks) merge_in_launch<KL>(in_launch, smem, partial, NPB * 16, n_probes, merge_sum);
   }
 }
 
@@ -1143,32 +1196,36 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
 // load instruction brings two contiguous 512-byte runs; NSTG - 1 stages in flight).  One barrier per stage: it
 // publishes the stage that has landed and retires the one just multiplied.  A lane ends up with 16 rows of one
 // probe per block, scales them by the rows' inverse norms and keeps its best (or the best two of a group), as in the kernel above.
+// RS sets of 32 rows a block: up to 64 probes leave two of the four wavefronts without any, so these take another 32 rows (RS = 2): half the
+// arithmetic a row, and half the barriers, of stages twice as large.  200 000 rows of width 1024, 64 probes: best row 90 us | 74, per-row mode 101 | 73
+// (3 of them an earlier launch for the probes' norms, which the wavefronts now take from the registers that hold the probes).
 // Per-row mode (K == 0, see RowScan): the operands swap sides, so a lane holds ONE row and 16 probes; the wavefronts'
 // candidates of a block meet in LDS and are written out one block later, behind a barrier that is there anyway, by the
 // wavefronts in turn.  The thresholds sit in LDS beside the inverse norms: a load from memory in front of the decision
 // would drain the ring.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kWideProbes = 128;
-constexpr int kWideStages = 8;
+constexpr int kWideStages = 8;              // of 32 rows; half as many of 64
 constexpr int kWideChunk = 512;             // bytes of a row per stage (256 where they do not divide a row)
 constexpr int kWideMaxBlocksPerWg = 192;    // 6144 rows: bounds the LDS copy of the inverse norms (24 KB)
 constexpr int kScanMaxBlocksPerWg = 80;     // per-row mode: of the inverse norms and the thresholds (20 KB), beside the candidates
 constexpr int kScanHead = kScanMaxBlocksPerWg * 32 * 8 + 2 * 4 * 32 * (int)sizeof(Best);
 
-template <int D_EMB, int K, int CHB = kWideChunk>
+template <int D_EMB, int K, int RS, int CHB = kWideChunk>
 __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm,
                                                              int N, const _Float16 *__restrict__ probes, int n_probes, int per_wg,
                                                              Best *__restrict__ partial, RowScan rs, Groups gm) {
   extern __shared__ __align__(16) char smem[];
-  constexpr int NSTG = kWideStages;
+  constexpr int NSTG = kWideStages / RS, BR = 32 * RS, NG = 4 / RS;   // rows of a block, wavefronts with probes of their own
   constexpr int CHUNKS = D_EMB * 2 / CHB;  // stages per row block
   constexpr int CS = CHB / 32;             // MFMA k-steps (16 elements) per stage
-  constexpr int STG = 32 * CHB;            // bytes per stage
+  constexpr int STG = BR * CHB;            // bytes per stage
   constexpr int IPS = STG / 1024 / 4;      // load instructions per stage and wavefront
   static_assert(D_EMB * 2 % CHB == 0, "row must be a whole number of chunks");
   const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const int l32 = lane & 31, g2 = lane >> 5;
-  const int n_blocks = (N + 31) / 32;
+  const int pg = wave % NG, set = wave / NG;   // this wavefront's probes, and its 32 rows of a block
+  const int n_blocks = (N + BR - 1) / BR;
   const int rb_begin = blockIdx.x * per_wg, rb_end = min(n_blocks, rb_begin + per_wg);
 
   // inverse norms of this workgroup's rows (zero beyond N), then the ring
@@ -1176,41 +1233,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
   float *kth_lds = inv_lds + kScanMaxBlocksPerWg * 32;                  // (K == 0)
   Best *cand = (Best *)(kth_lds + kScanMaxBlocksPerWg * 32);            // (K == 0) [block parity][wavefront][row]
   char *ring = smem + (K == 0 ? kScanHead : kWideMaxBlocksPerWg * 32 * (int)sizeof(float));
-  for (int r = tid; r < per_wg * 32; r += 256) {
-    const int row = rb_begin * 32 + r;
-    inv_lds[r] = row < N ? inv_norm[row] : 0.f;
-    if (K == 0) kth_lds[r] = row < N ? rs.kth[row] : 0.f;
-  }
-  // per-row mode: inverse norms of the probes this lane meets (a padding probe's is a NaN, which no comparison picks)
-  const bool idle = wave * 32 >= n_probes;  // nothing but padding: this wavefront only loads
-  float pinv[K == 0 ? 16 : 1];
-  if constexpr (K == 0) {
-#pragma unroll
-    for (int r = 0; r < 16; ++r) {
-      const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
-      pinv[r] = p < n_probes ? rs.probe_inv[p] : __builtin_nanf("");
-    }
-#pragma unroll
-    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(pinv[r]));
-  }
-  // this lane's probe: elements [16 ks + 8 g2, +8) for every k-step (zero for a padding probe)
-  f16x8 pq[D_EMB / 16];
-  {
-    const int p = wave * 32 + l32;
-    const u32x4 *src = (const u32x4 *)(probes + (size_t)min(p, n_probes - 1) * D_EMB);
-#pragma unroll
-    for (int ks = 0; ks < D_EMB / 16; ++ks) {
-      u32x4 raw = src[2 * ks + g2];
-      if (p >= n_probes) raw = u32x4{0, 0, 0, 0};
-      pq[ks] = __builtin_bit_cast(f16x8, raw);
-    }
-  }
-  // (the probes' loads must not be counted by the ring's partial waits below)
-#pragma unroll
-  for (int ks = 0; ks < D_EMB / 16; ++ks) asm volatile("" : "+v"(pq[ks]));
-  PC_LOOKUP_WAIT_VMCNT(0);
-  __syncthreads();
-
+  const bool idle = pg * 32 >= n_probes;  // nothing but padding: this wavefront only loads
   // load instruction i of a stage (i = wave + 4 k): stage bytes [1024 i, +1024) = whole rows
   int ld_row[IPS], ld_col[IPS];
 #pragma unroll
@@ -1223,26 +1246,105 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
     const _Float16 *base = bank + chunk * (CHB / 2);
 #pragma unroll
     for (int k = 0; k < IPS; ++k) {
-      const int row = min(rb * 32 + ld_row[k], N - 1);
+      const int row = min(rb * BR + ld_row[k], N - 1);
       __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(base + (size_t)row * D_EMB + ld_col[k]),
                                        (__attribute__((address_space(3))) void *)(ring + st * STG + (wave + 4 * k) * 1024), 16, 0, kBankLoadAux);
     }
   };
+  // The first stages are asked for behind the probes and the norms but in front of the wait for them: all of these are one memory latency.
+  // Four rows' norms a thread at a time (one by one they are a latency each).
+  float row_inv[4], row_kth[4];
+  auto fetch_rows = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int row = min(rb_begin * BR + r0 + e * 256 + tid, N - 1);
+      row_inv[e] = inv_norm[row];
+      if (K == 0) row_kth[e] = rs.kth[row];
+    }
+  };
+  auto keep_rows = [&](int r0) __attribute__((always_inline)) {
+#pragma unroll
+    for (int e = 0; e < 4; ++e) {
+      const int r = r0 + e * 256 + tid;
+      if (r >= per_wg * BR) continue;
+      lds_put(inv_lds + r, rb_begin * BR + r < N ? row_inv[e] : 0.f);
+      if (K == 0) lds_put(kth_lds + r, rb_begin * BR + r < N ? row_kth[e] : 0.f);
+    }
+  };
+  fetch_rows(0);
+  // this lane's probe: elements [16 ks + 8 g2, +8) for every k-step (zero for a padding probe)
+  f16x8 pq[D_EMB / 16];
+  {
+    const int p = pg * 32 + l32;
+    const u32x4 *src = (const u32x4 *)(probes + (size_t)min(p, n_probes - 1) * D_EMB);
+#pragma unroll
+    for (int ks = 0; ks < D_EMB / 16; ++ks) pq[ks] = __builtin_bit_cast(f16x8, src[2 * ks + g2]);
+  }
+  const int rb_last = rb_end - 1;
+  int prb = rb_begin, pch = 0, ist = 0, st = 0;
+  auto advance = [&](int &rb_, int &c_) __attribute__((always_inline)) {
+    if (++c_ == CHUNKS) { c_ = 0; ++rb_; }
+  };
+  // flat sequence of (row block, chunk) items; loads go out unconditionally (past the end they repeat the last
+  // block into a stage nobody reads), so the count of loads in flight is the same at every wait
+  __builtin_amdgcn_sched_barrier(0);
+#pragma unroll
+  for (int k = 0; k < NSTG - 1; ++k) {
+    issue(min(prb, rb_last), pch, ist);
+    advance(prb, pch);
+    ist = ist + 1 == NSTG ? 0 : ist + 1;
+  }
+  __builtin_amdgcn_sched_barrier(0);
+  PC_LOOKUP_WAIT_VMCNT((NSTG - 1) * IPS);   // (left to itself the compiler waits for the ring as well, or moves a load behind it)
+#pragma unroll
+  for (int e = 0; e < 4; ++e) {
+    asm volatile("" : "+v"(row_inv[e]));
+    if (K == 0) asm volatile("" : "+v"(row_kth[e]));
+  }
+  keep_rows(0);
+  for (int r0 = 1024; r0 < per_wg * BR; r0 += 1024) {
+    fetch_rows(r0);
+    keep_rows(r0);
+  }
+  if (pg * 32 + l32 >= n_probes) {
+#pragma unroll
+    for (int ks = 0; ks < D_EMB / 16; ++ks) pq[ks] = f16x8{};
+  }
+#pragma unroll
+  for (int ks = 0; ks < D_EMB / 16; ++ks) asm volatile("" : "+v"(pq[ks]));
+  // per-row mode: inverse norms of the probes this lane meets (a padding probe's is a NaN, which no comparison picks)
+  float pinv[K == 0 ? 16 : 1];
+  if constexpr (K == 0) {
+    float ss[4] = {0.f, 0.f, 0.f, 0.f};
+#pragma unroll
+    for (int ks = 0; ks < D_EMB / 16; ++ks)
+#pragma unroll
+      for (int e = 0; e < 8; ++e) ss[e & 3] += (float)pq[ks][e] * (float)pq[ks][e];
+    float tot = (ss[0] + ss[1]) + (ss[2] + ss[3]);
+    tot += __shfl_xor(tot, 32, 64);
+    const float inv = pg * 32 + l32 >= n_probes ? __builtin_nanf("") : tot > 0.f ? 1.0f / sqrtf(tot) : 0.f;
+#pragma unroll
+    for (int r = 0; r < 16; ++r) pinv[r] = __shfl(inv, (r >> 2) * 8 + g2 * 4 + (r & 3), 64);
+#pragma unroll
+    for (int r = 0; r < 16; ++r) asm volatile("" : "+v"(pinv[r]));
+  }
+  lds_barrier();
+
   int rd_off[CS];  // swizzled byte offsets of this lane's operand reads inside a stage
 #pragma unroll
-  for (int s = 0; s < CS; ++s) rd_off[s] = l32 * CHB + (((2 * s + g2) ^ (l32 & 15)) * 16);
+  for (int s = 0; s < CS; ++s) rd_off[s] = (set * 32 + l32) * CHB + (((2 * s + g2) ^ (l32 & 15)) * 16);
 
   Top2 top;   // (K == kGroups) of the group that this workgroup is in
-  TopK<(K > 0 ? K : 1)> best;
+  TopK<1> best;
   best.clear();
   // (K == 0) the candidates of a block whose barrier has passed: one row per lane of the wavefront whose turn it is
   auto write_rows = [&](int rb) __attribute__((always_inline)) {
-    if ((rb & 3) != wave || g2 != 0) return;
-    const int row = rb * 32 + l32;
-    Best b = cand[((rb & 1) * 4) * 32 + l32];
+    if ((rb & 3) != wave || lane >= BR) return;
+    const int row = rb * BR + lane;
+    Best b = cand[(rb & 1) * 128 + lane];
 #pragma unroll
-    for (int w = 1; w < 4; ++w) {
-      const Best o = cand[((rb & 1) * 4 + w) * 32 + l32];
+    for (int w = 1; w < NG; ++w) {
+      const Best o = cand[(rb & 1) * 128 + w * BR + lane];
       if (better(o.s, o.idx, b.s, b.idx)) b = o;
     }
     if (row >= N) return;
@@ -1252,23 +1354,10 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
     }
     rs.best_sim[row] = b.s;
     rs.best_new[row] = b.idx == INT_MAX ? -1 : b.idx;
-    rs.stale[row] = b.s > kth_lds[(rb - rb_begin) * 32 + l32] ? 1 : 0;
+    rs.stale[row] = b.s > kth_lds[(rb - rb_begin) * BR + lane] ? 1 : 0;
   };
-  if (K == 0 && idle && g2 == 0) cand[wave * 32 + l32] = cand[(4 + wave) * 32 + l32] = Best{-INFINITY, INT_MAX};
-  const int rb_last = rb_end - 1;
+  if (K == 0 && idle && g2 == 0) cand[pg * BR + set * 32 + l32] = cand[128 + pg * BR + set * 32 + l32] = Best{-INFINITY, INT_MAX};
   if (rb_begin < rb_end) {
-    // flat sequence of (row block, chunk) items; loads go out unconditionally (past the end they repeat the last
-    // block into a stage nobody reads), so the count of loads in flight is the same at every wait
-    int prb = rb_begin, pch = 0, ist = 0, st = 0;
-    auto advance = [&](int &rb_, int &c_) __attribute__((always_inline)) {
-      if (++c_ == CHUNKS) { c_ = 0; ++rb_; }
-    };
-#pragma unroll
-    for (int k = 0; k < NSTG - 1; ++k) {
-      issue(min(prb, rb_last), pch, ist);
-      advance(prb, pch);
-      ist = ist + 1 == NSTG ? 0 : ist + 1;
-    }
     for (int rb = rb_begin; rb < rb_end; ++rb) {
       pc::f32x16 acc[2];  // two accumulation chains: an MFMA does not wait for the one before it
 #pragma unroll
@@ -1309,17 +1398,17 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
       if constexpr (K == 0) {
         // element r of the product: row l32 of the block, probe wave*32 + (r/4)*8 + 4*g2 + r%4 (ascending: the lowest wins ties)
         if (idle) continue;
-        const float inv = inv_lds[(rb - rb_begin) * 32 + l32];
+        const float inv = inv_lds[(rb - rb_begin) * BR + set * 32 + l32];
         Best b{-INFINITY, INT_MAX};
 #pragma unroll
         for (int r = 0; r < 16; ++r) {
-          const int p = wave * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
+          const int p = pg * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3);
           const float s = (acc[0][r] + acc[1][r]) * inv * pinv[r];
           if (better(s, rs.p0 + p, b.s, b.idx)) b = Best{s, rs.p0 + p};
         }
         const Best o{__shfl_xor(b.s, 32, 64), __shfl_xor(b.idx, 32, 64)};
         if (better(o.s, o.idx, b.s, b.idx)) b = o;
-        if (g2 == 0) cand[((rb & 1) * 4 + wave) * 32 + l32] = b;
+        if (g2 == 0) cand[(rb & 1) * 128 + pg * BR + set * 32 + l32] = b;
         continue;
       }
       // element r of the product: row (r/4)*8 + 4*g2 + r%4 of the block, probe wave*32 + l32
@@ -1328,10 +1417,10 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
         for (int q4 = 0; q4 < 4; ++q4) {
           const int rin = q4 * 8 + g2 * 4;
-          const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 32 + rin);
+          const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * BR + set * 32 + rin);
 #pragma unroll
           for (int e = 0; e < 4; ++e) {
-            const int r = q4 * 4 + e, row = rb * 32 + rin + e;
+            const int r = q4 * 4 + e, row = rb * BR + set * 32 + rin + e;
             v[r] = row < N ? (acc[0][r] + acc[1][r]) * inv4[e] : __builtin_nanf("");
             top.add(v[r], row);
           }
@@ -1340,12 +1429,12 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
           const bool none = top.i == INT_MAX;
 #pragma unroll
           for (int r = 0; r < 16; ++r)
-            if (none) top.first(v[r], rb * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3));
+            if (none) top.first(v[r], rb * BR + set * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3));
         }
-        const int nth = rb - rb_begin, p = wave * 32 + l32;
+        const int nth = rb - rb_begin, p = pg * 32 + l32;
         if ((nth + 1) % gm.stretch == 0 || rb == rb_last) {
           top.merge(top.of_lane_xor(32));
-          if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + blockIdx.x * gm.per + nth / gm.stretch, top);
+          if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (blockIdx.x * RS + set) * gm.per + nth / gm.stretch, top);
           top = Top2{};
         }
         continue;
@@ -1353,56 +1442,33 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
 #pragma unroll
       for (int q4 = 0; q4 < 4; ++q4) {
         const int rin = q4 * 8 + g2 * 4;
-        const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 32 + rin);
+        const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * BR + set * 32 + rin);
 #pragma unroll
         for (int e = 0; e < 4; ++e) {
-          const int row = rb * 32 + rin + e;
+          const int row = rb * BR + set * 32 + rin + e;
           if (row < N) best.insert((acc[0][q4 * 4 + e] + acc[1][q4 * 4 + e]) * inv4[e], row);
         }
       }
     }
-    PC_LOOKUP_WAIT_VMCNT(0);
     if constexpr (K == 0) {
       __syncthreads();
       write_rows(rb_last);
     }
   }
+  PC_LOOKUP_WAIT_VMCNT(0);
   if constexpr (K == kGroups) {   // groups that this workgroup has no rows for
-    const int p = wave * 32 + l32;
+    const int p = pg * 32 + l32;
     for (int j = (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
-      if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + blockIdx.x * gm.per + j, Top2{});
+      if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (blockIdx.x * RS + set) * gm.per + j, Top2{});
   }
   if constexpr (K <= 0) return;  // per-row mode and groups: everything has been written
-  // the two lanes of a probe hold different rows: merge (K rounds of "best head wins and is popped")
-  constexpr int KL = K > 0 ? K : 1;
-  Best *out = partial + ((size_t)blockIdx.x * kWideProbes + wave * 32 + l32) * KL;
-#pragma unroll
-  for (int j = 0; j < KL; ++j) {
-    float s = best.s[0];
-    int i = best.i[0];
-    const float s2 = __shfl_xor(s, 32, 64);
-    const int i2 = __shfl_xor(i, 32, 64);
-    if (better(s2, i2, s, i)) { s = s2; i = i2; }
-    best.pop_if(i != INT_MAX && best.i[0] == i);
-    if (g2 == 0) out[j] = Best{s, i};
-  }
-}
-
-// inverse L2 norms of n embedding rows (0 for a zero row); one wavefront per row
-__global__ __launch_bounds__(256) void inv_norm_kernel(const _Float16 *__restrict__ src, float *__restrict__ inv_norm, int n, int d) {
-  const int lane = threadIdx.x & 63;
-  const int row = blockIdx.x * 4 + (threadIdx.x >> 6);
-  if (row >= n) return;
-  const u32x4 *s = (const u32x4 *)(src + (size_t)row * d);
-  float ss = 0.f;
-  for (int v = lane; v < d / 8; v += 64) {
-    f16x8 h = __builtin_bit_cast(f16x8, s[v]);
-#pragma unroll
-    for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
-  }
-#pragma unroll
-  for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
-  if (lane == 0) inv_norm[row] = ss > 0.f ? 1.0f / sqrtf(ss) : 0.f;
+  // the two lanes of a probe hold different rows
+  float s = best.s[0];
+  int i = best.i[0];
+  const float s2 = __shfl_xor(s, 32, 64);
+  const int i2 = __shfl_xor(i, 32, 64);
+  if (better(s2, i2, s, i)) { s = s2; i = i2; }
+  if (g2 == 0) partial[((size_t)blockIdx.x * RS + set) * (NG * 32) + pg * 32 + l32] = Best{s, i};
 }
 
 __global__ void lookup_empty_kernel(int n_out, int n_probes, int32_t *idx_out, float *sim_out, uint8_t *hit_out) {
@@ -1446,7 +1512,7 @@ int max_stream_grid(const percache_ctx *ctx) {
 
 constexpr int kBatchedFrom = 32;  // more probes than one streaming pass takes: the 128-probe pass or the matrix-product kernel
 // Per-row scan: more new embeddings than one streaming pass takes go through 128-probe passes.  200k rows, streaming passes | 128-probe
-// passes, us: width 384 82 | 66 at 33 to 64, 164 | 70 at 128; width 1024 139 | 103 at 64, 280 | 118 at 128, 490 | 234 at 200.
+// passes, us: width 384 75 | 43 at 33 to 64, 164 | 70 at 128; width 1024 138 | 73 at 64, 280 | 113 at 128, 490 | 228 at 200.
 constexpr int kScanWideFrom = 32;
 constexpr int kWideUpTo = 128;    // one such pass; beyond it the matrix-product kernel is the faster one
 
@@ -1497,25 +1563,6 @@ pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStre
                          : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
 }
 
-// Per-row scan of up to 128 new embeddings in one pass of the bank.
-bool scan_in_wide_passes(int n_new, int d) { return n_new > kScanWideFrom && (d == 384 || d == 512 || d == 768 || d == 1024); }
-pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, const _Float16 *pp, int np, const RowScan &rs) {
-  const int n_blocks = (N + 31) / 32;
-  int grid = ctx->n_cu < n_blocks ? ctx->n_cu : n_blocks;
-  int per_wg = (n_blocks + grid - 1) / grid;
-  if (per_wg > kScanMaxBlocksPerWg) per_wg = kScanMaxBlocksPerWg;
-  grid = (n_blocks + per_wg - 1) / per_wg;
-#define PC_SCAN(DD, CC)                                                                                               \
-  do {                                                                                                                \
-    constexpr int lds = kScanHead + kWideStages * 32 * CC;                                                            \
-    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, 0, CC>, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
-    hipLaunchKernelGGL((lookup_wide_kernel<DD, 0, CC>), dim3(grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, per_wg, (Best *)nullptr, rs, Groups{}); \
-  } while (0)
-  if (d == 384) PC_SCAN(384, 256); else if (d == 512) PC_SCAN(512, 512); else if (d == 768) PC_SCAN(768, 512); else PC_SCAN(1024, 512);
-#undef PC_SCAN
-  PC_HIP(ctx, hipGetLastError());
-  return PC_OK;
-}
 
 // What a call of n_probes needs at least: a sorted list per workgroup and probe.
 size_t list_bytes(const percache_ctx *ctx, int32_t n_probes) {
@@ -1556,17 +1603,41 @@ Route route_of(const percache_ctx *ctx, int n_probes, int N) {
   return n_probes > kBatchedFrom || stream_shape(ctx, 1, N).lds > kMaxLds ? Route::big : Route::stream;
 }
 struct WideShape {
-  int grid, per_wg;
+  int sets, grid, per_wg;   // per_wg: blocks of sets x 32 rows
 };
-WideShape wide_shape(int n_cu, int N) {
-  const int n_blocks = (N + 31) / 32;
+WideShape wide_shape(int n_cu, int N, int n_probes, int max_blocks = kWideMaxBlocksPerWg) {
   WideShape w;
+  // us a call, one set | two: best of 200 000 rows of width 1024, 64 probes 91 | 75, 50 000 rows 33.5 | 30.1, 20 000 of width 512 14.3 | 15.2, 2000 of
+  // width 768 12.1 | 13.6: under four blocks of 32 rows a CU, blocks of 64 leave CUs without one.
+  w.sets = n_probes <= kWideProbes / 2 && N >= 4 * 32 * n_cu ? 2 : 1;
+  const int n_blocks = (N + 32 * w.sets - 1) / (32 * w.sets);
   w.grid = n_cu < n_blocks ? n_cu : n_blocks;
   w.per_wg = (n_blocks + w.grid - 1) / w.grid;
-  if (w.per_wg > kWideMaxBlocksPerWg) w.per_wg = kWideMaxBlocksPerWg;
+  if (w.per_wg > max_blocks / w.sets) w.per_wg = max_blocks / w.sets;
   w.grid = (n_blocks + w.per_wg - 1) / w.per_wg;
   return w;
 }
+// Per-row scan of up to 128 new embeddings in one pass of the bank.
+bool scan_in_wide_passes(int n_new, int d) { return n_new > kScanWideFrom && (d == 384 || d == 512 || d == 768 || d == 1024); }
+pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, const _Float16 *pp, int np, const RowScan &rs) {
+  const WideShape w = wide_shape(ctx->n_cu, N, np, kScanMaxBlocksPerWg);
+#define PC_SCAN_SETS(DD, RS, CC)                                                                                      \
+  do {                                                                                                                \
+    constexpr int lds = kScanHead + kWideStages * 32 * CC;                                                            \
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, 0, RS, CC>, hipFuncAttributeMaxDynamicSharedMemorySize, lds)); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, 0, RS, CC>), dim3(w.grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, pp, np, w.per_wg, (Best *)nullptr, rs, Groups{}); \
+  } while (0)
+#define PC_SCAN(DD, CC)                                                                                               \
+  do {                                                                                                                \
+    if (w.sets == 2) PC_SCAN_SETS(DD, 2, CC); else PC_SCAN_SETS(DD, 1, CC);                                           \
+  } while (0)
+  if (d == 384) PC_SCAN(384, 256); else if (d == 512) PC_SCAN(512, 512); else if (d == 768) PC_SCAN(768, 512); else PC_SCAN(1024, 512);
+#undef PC_SCAN
+#undef PC_SCAN_SETS
+  PC_HIP(ctx, hipGetLastError());
+  return PC_OK;
+}
+
 int probe_tile(int n_probes) { return big_tiles_pay(n_probes) ? 256 : 128; }
 // The groups of a pass of so many probes (see Groups): about four a wavefront, in the matrix-product kernel at least 1024 in all; there, over a
 // small bank, the 16 rows that a lane has in a block of 32. 
@@ -1586,12 +1657,13 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     cut(g, (sh.per_wg + 3) / 4, kGroupsPerWave);
     g.n = sh.grid * 4 * g.per;
   } else if (r == Route::wide) {
-    const WideShape w = wide_shape(ctx->n_cu, N);
+    const WideShape w = wide_shape(ctx->n_cu, N, n_probes);
     g.kind = Groups::wide;
     g.per_wg = w.per_wg;
-    g.blocks = (N + 31) / 32;
-    cut(g, w.per_wg, kGroupsPerWide);
-    g.n = w.grid * g.per;
+    g.sets = w.sets;
+    g.blocks = (N + 32 * w.sets - 1) / (32 * w.sets);
+    cut(g, w.per_wg, kGroupsPerWide / w.sets);
+    g.n = w.grid * w.sets * g.per;
   } else {
     const BigShape bg = big_shape(ctx->n_cu, N, n_probes, probe_tile(n_probes));
     g.kind = N <= kFineGroupsUpTo ? Groups::big_fine : Groups::big;
@@ -1611,13 +1683,17 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
   const Route route = route_of(ctx, n_probes, N);
   if (route == Route::wide) {
     // up to 128 probes: one pass of the bank
-    const WideShape w = wide_shape(ctx->n_cu, N);
+    const WideShape w = wide_shape(ctx->n_cu, N, n_probes);
     const size_t lds = (size_t)kWideMaxBlocksPerWg * 32 * sizeof(float) + (size_t)kWideStages * 32 * kWideChunk;
+#define PC_WIDE_SETS(DD, KK, RS)                                                                                      \
+  do {                                                                                                                \
+    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, KK, RS>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
+    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK, RS>), dim3(w.grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, probes, n_probes, w.per_wg, partial, RowScan{}, \
+                       gm ? *gm : Groups{});                                                                          \
+  } while (0)
 #define PC_WIDE(DD, KK)                                                                                               \
   do {                                                                                                                \
-    PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_wide_kernel<DD, KK>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)lds)); \
-    hipLaunchKernelGGL((lookup_wide_kernel<DD, KK>), dim3(w.grid), dim3(256), lds, st, ctx->bank, ctx->bank_inv, N, probes, n_probes, w.per_wg, partial, RowScan{}, \
-                       gm ? *gm : Groups{});                                                                        \
+    if (w.sets == 2) PC_WIDE_SETS(DD, KK, 2); else PC_WIDE_SETS(DD, KK, 1);                                           \
   } while (0)
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     if (!gm) {
@@ -1628,8 +1704,9 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
     pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
     PC_HIP(ctx, hipGetLastError());
 #undef PC_WIDE
+#undef PC_WIDE_SETS
     if (gm) return PC_OK;
-    hipLaunchKernelGGL(lookup_finalize_kernel, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, w.grid, kWideProbes, probes, d, tau, idx_out_dev, sim_out_dev, hit_out_dev);
+    hipLaunchKernelGGL(lookup_finalize_kernel, dim3(n_probes), dim3(kFinalizeThreads), 0, st, partial, w.grid * w.sets, kWideProbes / w.sets, probes, d, tau, idx_out_dev, sim_out_dev, hit_out_dev);
     PC_HIP(ctx, hipGetLastError());
     return PC_OK;
   }
@@ -1822,15 +1899,12 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
     if (lds1 > kMaxLds) return pc::fail(ctx, PC_ESHAPE, "emb_dim %d needs %zu bytes of LDS per workgroup", d, lds1);
   }
   hipStream_t st = (hipStream_t)stream;
-  float *probe_inv = (float *)workspace_dev;
   const _Float16 *probes = (const _Float16 *)new_emb_dev;
-  hipLaunchKernelGGL(inv_norm_kernel, dim3((n_new + 3) / 4), dim3(256), 0, st, probes, probe_inv, n_new, d);
-  PC_HIP(ctx, hipGetLastError());
   int p0 = 0;
   // (one kernel for all passes of a call: equal embeddings then have equal sums, and the lower index wins)
   for (; p0 < n_new && scan_in_wide_passes(n_new, d); p0 += kWideProbes) {
     const int np = n_new - p0 < kWideProbes ? n_new - p0 : kWideProbes;
-    const RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
+    const RowScan rs{kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
     const pc_status ls = launch_scan_wide(ctx, st, N, d, probes + (size_t)p0 * d, np, rs);
     if (ls != PC_OK) return ls;
   }
@@ -1839,7 +1913,7 @@ pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev,
     const int np = n_new - p0 < pass_probes ? n_new - p0 : pass_probes;
     const int npb = np <= 16 ? 1 : 2;
     StreamShape sh = stream_shape(ctx, npb, N);
-    RowScan rs{probe_inv + p0, kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
+    RowScan rs{kth_sim_dev, best_sim_out_dev, best_new_out_dev, stale_out_dev, p0, p0 == 0 ? 1 : 0};
     pc_status ls = launch_pass<0>(ctx, sh, npb, st, N, d, probes + (size_t)p0 * d, np, nullptr, rs);
     if (ls != PC_OK) return ls;
     PC_HIP(ctx, hipGetLastError());

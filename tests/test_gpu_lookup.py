@@ -327,6 +327,42 @@ def test_topk_groups(rows, dim, n_probes, k):
     pc.close()
 
 
+# from 32 768 rows on (256 CUs) 33 to 64 probes take blocks of two sets of 32 rows; the last block without a second set, with one row of it, whole
+@pytest.mark.parametrize("rows,dim,n_probes", [(32768, 512, 33), (32769, 1024, 64), (32801, 768, 64), (49152, 512, 40), (33000, 384, 50)])
+def test_two_sets_of_rows_a_block(rows, dim, n_probes):
+    """Best rows and the refresh scan against 64 bits; equal rows in both sets and in other workgroups: the lowest one, of equal new chunks the lower one.
+    Bound: fp32 sums of at most 1024 exact products of unit vectors, 2e-6."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows)
+    bank = torch.randn((rows, dim), generator=g, device=DEV).half()
+    probes = torch.randn((n_probes, dim), generator=g, device=DEV).half()
+    for r in (70, 99, rows // 2, rows - 1):
+        bank[r] = bank[40]
+    bank[64], bank[rows - 2] = 0, float("nan")
+    probes[n_probes - 1], probes[n_probes - 2] = bank[40], bank[40]
+    probes[0] = 0
+    pc = _ctx(rows, dim)
+    pc.percache_bank_put(0, bank)
+    kth = torch.full((rows,), 0.1, device=DEV)
+    idx, sim, hit = pc.percache_lookup(probes, 0.1)
+    best, new, stale = pc.percache_bank_refresh_scan(probes, kth)
+    torch.cuda.synchronize()
+    b, p = bank.double(), probes.double()
+    unit = lambda x: x / x.norm(dim=1, keepdim=True).clamp(min=1e-30)  # noqa: E731
+    ref = unit(p) @ unit(torch.nan_to_num(b)).t()
+    ref[:, rows - 2] = float("-inf")
+    got = torch.gather(ref, 1, idx.long()[:, None])[:, 0]
+    assert (ref.max(dim=1).values - got).max().item() < 2e-6 and (sim.double() - got).abs().max().item() < 2e-6
+    assert idx[n_probes - 1].item() == 40 and idx[0].item() == 0 and torch.equal(hit.bool(), sim > 0.1)
+    ok = torch.arange(rows, device=DEV) != rows - 2
+    got = torch.gather(ref, 0, new.long().clamp(min=0)[None])[0]
+    assert (ref.max(dim=0).values - got)[ok].max().item() < 2e-6 and (best.double() - got)[ok].abs().max().item() < 2e-6
+    assert new[rows - 2].item() == -1 and torch.isneginf(best[rows - 2]) and stale[rows - 2].item() == 0
+    assert all(new[r].item() == n_probes - 2 for r in (40, 70, 99, rows // 2, rows - 1)) and new[64].item() == 0
+    assert torch.equal(stale.bool()[ok], (best > kth)[ok])
+    pc.close()
+
+
 def test_topk_ties_small_bank_and_errors():
     d = 128
     g = np.random.default_rng(12)
