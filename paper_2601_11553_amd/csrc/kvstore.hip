@@ -18,7 +18,7 @@ using pc::kKvTile;
 // as slot ids alone, and short append lists in 128 bytes (a put of one chunk 8.2 us, host bound; with 1 KB lists copied twice 8.8).
 constexpr int kListMax = 64;
 struct Entry {
-  int32_t slot;    // slot of the format the kernel handles, negative: skip the entry
+  int32_t slot;    // slot of the format the kernel handles (kv_mixed_kernel: of the context), negative: skip the entry
   int32_t row0;
   int32_t n_tok;
   int32_t off;     // tokens the slot already holds (append; else 0)
@@ -57,15 +57,19 @@ __device__ __forceinline__ int in_chunk(int e) { return (e & 3) + 8 * (e >> 2); 
 // a 64-key block's chunk x 8 head-dim elements -- and turns it in registers (32 byte permutes).  With 2-byte accesses on the
 // dense (put) or the block (get) side a get of 8 chunks of 1000 tokens, 8 heads of 128, took 21.7 us, a put 13.0 us; now
 // 9.6 us and 9.9 us (6.9 TB/s read and written).
-template <int D, bool kToStore, class List>
-__global__ __launch_bounds__(256) void kv_copy_kernel(__bf16 *__restrict__ slot_k, __bf16 *__restrict__ slot_v, __bf16 *__restrict__ dense_k,
-                                                      __bf16 *__restrict__ dense_v, int n_heads, int C, List list, long slot_stride_elems,
-                                                      int head_rows) {
+struct Store16 {
+  __bf16 *k, *v;
+  long slot_stride;
+};
+template <int D, bool kToStore>
+__device__ __forceinline__ void copy_unit(const Store16 &st, __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int C, const Entry &e, int slot, int g,
+                                          int unit, int head_rows) {
   constexpr int UNITS = 2 * (D / 64);  // per tile: K and V halves
-  const Entry e = list.at(blockIdx.z);
-  const int g = blockIdx.y, slot = e.slot, n_tok = e.n_tok;
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
-  if (slot < 0 || t0 >= n_tok) return;  // (an entry of the other slot format: the other launch copies it)
+  __bf16 *const __restrict__ slot_k = st.k, *const __restrict__ slot_v = st.v;
+  const long slot_stride_elems = st.slot_stride;
+  const int n_tok = e.n_tok;
+  const int tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
+  if (slot < 0 || t0 >= n_tok) return;
   const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
   const int d0 = (part >> 1) * 64;
   const size_t drow = (size_t)e.row0 + (size_t)g * head_rows + t0;
@@ -101,6 +105,11 @@ __global__ __launch_bounds__(256) void kv_copy_kernel(__bf16 *__restrict__ slot_
     if (kToStore) *(pc::u32x4 *)(block + j * kKvTile) = out[j];
     else if (t <= last) *(pc::u32x4 *)(rows + (size_t)t * D) = out[j];
   }
+}
+template <int D, bool kToStore, class List>
+__global__ __launch_bounds__(256) void kv_copy_kernel(Store16 st, __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int C, List list, int head_rows) {
+  const Entry e = list.at(blockIdx.z);
+  copy_unit<D, kToStore>(st, dense_k, dense_v, C, e, e.slot, blockIdx.y, blockIdx.x * 4 + (threadIdx.x >> 6), head_rows);
 }
 
 // Appends n_new tokens behind the off tokens a slot already holds; blockIdx.y selects the slot of a list (one launch for
@@ -176,18 +185,22 @@ __device__ __forceinline__ unsigned encode4(float a, float b, float c, float d) 
 // all 64 tokens, 8 x 8 elements a lane (eight 16-byte loads in flight).  V: 8 keys of a chunk of the block rows x 8 head-dim
 // elements, whose codes are turned in registers.  (Codes turned through LDS byte by byte, four loads per lane behind tests:
 // 14.3 us for 8 chunks of 1000 tokens, 8 heads of 128; now 13.2 us.)
-template <int D, class List>
-__global__ __launch_bounds__(2 * D) void kv_quant_kernel(uint8_t *__restrict__ slot_k, uint8_t *__restrict__ slot_v,
-                                                       float *__restrict__ scale_k, float *__restrict__ scale_v,
-                                                       const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v,
-                                                       int n_heads, int C, List list, long slot_stride_elems,
-                                                       long scale_slot_stride, int head_rows) {
+struct Store8 {
+  uint8_t *k, *v;
+  float *k_scale, *v_scale;
+  long slot_stride, scale_stride;
+};
+template <int D>
+__device__ __forceinline__ void quant_block(const Store8 &st, const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v, int C, const Entry &ent,
+                                            int slot, int g, int head_rows) {
   constexpr int HALF = D / 64;  // wavefronts of each kind
   __shared__ float red[2 * HALF];
-  const Entry ent = list.at(blockIdx.z);
-  const int slot = ent.slot, off = ent.off, n_new = ent.n_tok, n_tok = off + n_new;
-  const int blk = blockIdx.x + off / kKvTile, g = blockIdx.y, t0 = blk * kKvTile;
-  if (slot < 0 || t0 >= n_tok) return;  // (a bf16 slot: the other launch copies it; the whole workgroup leaves)
+  uint8_t *const __restrict__ slot_k = st.k, *const __restrict__ slot_v = st.v;
+  float *const __restrict__ scale_k = st.k_scale, *const __restrict__ scale_v = st.v_scale;
+  const long slot_stride_elems = st.slot_stride, scale_slot_stride = st.scale_stride;
+  const int off = ent.off, n_new = ent.n_tok, n_tok = off + n_new;
+  const int blk = blockIdx.x + off / kKvTile, t0 = blk * kKvTile;
+  if (slot < 0 || t0 >= n_tok) return;  // (the whole workgroup leaves)
   const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6, hi = lane >> 3, lo = lane & 7;
   const bool is_v = wave >= HALF;
   const int d = (wave % HALF) * 64 + (is_v ? hi : lo) * 8;  // first of this lane's 8 head-dim elements
@@ -262,17 +275,24 @@ __global__ __launch_bounds__(2 * D) void kv_quant_kernel(uint8_t *__restrict__ s
   }
 }
 
+template <int D, class List>
+__global__ __launch_bounds__(2 * D) void kv_quant_kernel(Store8 st, const __bf16 *__restrict__ dense_k, const __bf16 *__restrict__ dense_v, int C, List list,
+                                                         int head_rows) {
+  const Entry e = list.at(blockIdx.z);
+  quant_block<D>(st, dense_k, dense_v, C, e, e.slot, blockIdx.y, head_rows);
+}
+
 // The values an 8-bit slot holds, as dense bf16 [kv head][token][head_dim]: code * 2^e (exact).  Work split as in
 // kv_copy_kernel: 8 codes per load, the 8 x 8 piece of a V block turned in registers as bf16.
-template <int D, class List>
-__global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restrict__ slot_k, const uint8_t *__restrict__ slot_v,
-                                                         const float *__restrict__ scale_k, const float *__restrict__ scale_v,
-                                                         __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int n_heads, int C,
-                                                         List list, long slot_stride_elems, long scale_slot_stride, int head_rows) {
+template <int D>
+__device__ __forceinline__ void dequant_unit(const Store8 &st, __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int C, const Entry &e, int slot, int g,
+                                             int unit, int head_rows) {
   constexpr int UNITS = 2 * (D / 64);
-  const Entry e = list.at(blockIdx.z);
-  const int g = blockIdx.y, slot = e.slot, n_tok = e.n_tok;
-  const int unit = blockIdx.x * 4 + (threadIdx.x >> 6), tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
+  const uint8_t *const __restrict__ slot_k = st.k, *const __restrict__ slot_v = st.v;
+  const float *const __restrict__ scale_k = st.k_scale, *const __restrict__ scale_v = st.v_scale;
+  const long slot_stride_elems = st.slot_stride, scale_slot_stride = st.scale_stride;
+  const int n_tok = e.n_tok;
+  const int tile = unit / UNITS, part = unit % UNITS, t0 = tile * kKvTile;
   if (slot < 0 || t0 >= n_tok) return;
   const int lane = threadIdx.x & 63, hi = lane >> 3, lo = lane & 7;
   const int d0 = (part >> 1) * 64;
@@ -315,6 +335,26 @@ __global__ __launch_bounds__(256) void kv_dequant_kernel(const uint8_t *__restri
   }
 }
 
+template <int D, class List>
+__global__ __launch_bounds__(256) void kv_dequant_kernel(Store8 st, __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int C, List list, int head_rows) {
+  const Entry e = list.at(blockIdx.z);
+  dequant_unit<D>(st, dense_k, dense_v, C, e, e.slot, blockIdx.y, blockIdx.x * 4 + (threadIdx.x >> 6), head_rows);
+}
+
+// A list that names slots of both formats (ids of the context, the 8-bit ones from n_slots16 on): a workgroup takes one 64-token tile of one head, in
+// whichever format its slot has.  One launch instead of one per format, and the conversions of the 8-bit slots, which alone reach 3.5 to 4 TB/s, run
+// beside the copies.  16 chunks of 1000 tokens, 8 heads of 128, half of them 8-bit, put and got: a launch a format 53.0 us, one 47.5 (4.9 TB/s read and
+// written, what a large copy reaches).
+template <int D, bool kToStore, class List>
+__global__ __launch_bounds__(2 * D) void kv_mixed_kernel(Store16 s16, Store8 s8, int n_slots16, __bf16 *__restrict__ dense_k, __bf16 *__restrict__ dense_v, int C,
+                                                         List list, int head_rows) {
+  const Entry e = list.at(blockIdx.z);
+  const int unit = blockIdx.x * (2 * D / 64) + (threadIdx.x >> 6);
+  if (e.slot < n_slots16) copy_unit<D, kToStore>(s16, dense_k, dense_v, C, e, e.slot, blockIdx.y, unit, head_rows);
+  else if (kToStore) quant_block<D>(s8, dense_k, dense_v, C, e, e.slot - n_slots16, blockIdx.y, head_rows);
+  else dequant_unit<D>(s8, dense_k, dense_v, C, e, e.slot - n_slots16, blockIdx.y, unit, head_rows);
+}
+
 pc_status check_slot(percache_ctx *ctx, int32_t layer, int32_t slot) {
   if (!ctx) return PC_EINVAL;
   if (layer < 0 || layer >= ctx->cfg.n_layers) return pc::fail(ctx, PC_ESLOT, "layer %d out of range [0,%d)", layer, ctx->cfg.n_layers);
@@ -322,42 +362,46 @@ pc_status check_slot(percache_ctx *ctx, int32_t layer, int32_t slot) {
   return PC_OK;
 }
 
-// Copies between dense tensors and the n slots of a list (slot ids of the context), its longest entry of `longest` tokens.  A list may
-// name slots of both formats: each format gets its own launch, in which the other's entries are marked -1.
+Store16 store16(const percache_ctx *ctx, int layer) {
+  const size_t off = (size_t)layer * ctx->layer_stride;
+  return {ctx->k_store + off, ctx->v_store + off, (long)ctx->slot_stride};
+}
+Store8 store8(const percache_ctx *ctx, int layer) {
+  const size_t off = (size_t)layer * ctx->layer_stride8;
+  const long sc_slot = (long)ctx->cfg.n_kv_heads * (ctx->cfg.slot_capacity / kKvTile);
+  const size_t sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
+  return {ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, ctx->v_scale + sc_off, (long)ctx->slot_stride, sc_slot};
+}
+
+// Copies between dense tensors and the n slots of a list (slot ids of the context), its longest entry of `longest` tokens.
 template <bool kToStore, class List>
 pc_status launch_copy(percache_ctx *ctx, int layer, List &list, int n, int longest, void *k_dev, void *v_dev, int head_rows, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
-  int32_t ids[kListMax];
+  __bf16 *const k = (__bf16 *)k_dev, *const v = (__bf16 *)v_dev;
   int n8 = 0;
-  for (int i = 0; i < n; ++i) n8 += ctx->is8(ids[i] = list.at(i).slot);
+  for (int i = 0; i < n; ++i) n8 += ctx->is8(list.at(i).slot);
   const int tiles = (longest + kKvTile - 1) / kKvTile;
-  if (n8) {
-    for (int i = 0; i < n; ++i) list.set_slot(i, ctx->is8(ids[i]) ? ids[i] - ctx->n_slots16 : -1);
-    const size_t off = (size_t)layer * ctx->layer_stride8;
-    const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
-    const size_t sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
-#define PC_KV8(KERNEL, DD, GX, TT)                                                                                                  \
-  hipLaunchKernelGGL((KERNEL<DD, List>), dim3(GX, c.n_kv_heads, n), dim3(TT), 0, stream, ctx->k8_store + off, ctx->v8_store + off, ctx->k_scale + sc_off, \
-                     ctx->v_scale + sc_off, (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, list, (long)ctx->slot_stride, sc_slot,    \
-                     head_rows)
+  auto grid = [&](int x) { return dim3(x, c.n_kv_heads, n); };
+  const bool d128 = c.head_dim == 128;
+  if (n8 && n8 < n) {
+    if (d128) hipLaunchKernelGGL((kv_mixed_kernel<128, kToStore, List>), grid(tiles), dim3(256), 0, stream, store16(ctx, layer), store8(ctx, layer), ctx->n_slots16, k, v, c.slot_capacity, list, head_rows);
+    else hipLaunchKernelGGL((kv_mixed_kernel<64, kToStore, List>), grid(tiles), dim3(128), 0, stream, store16(ctx, layer), store8(ctx, layer), ctx->n_slots16, k, v, c.slot_capacity, list, head_rows);
+  } else if (n8) {
+    for (int i = 0; i < n; ++i) list.set_slot(i, list.at(i).slot - ctx->n_slots16);
+    const Store8 st = store8(ctx, layer);
     if (kToStore) {
-      if (c.head_dim == 128) PC_KV8(kv_quant_kernel, 128, tiles, 256); else PC_KV8(kv_quant_kernel, 64, tiles, 128);
+      if (d128) hipLaunchKernelGGL((kv_quant_kernel<128, List>), grid(tiles), dim3(256), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
+      else hipLaunchKernelGGL((kv_quant_kernel<64, List>), grid(tiles), dim3(128), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
     } else {
-      if (c.head_dim == 128) PC_KV8(kv_dequant_kernel, 128, tiles, 256); else PC_KV8(kv_dequant_kernel, 64, (tiles + 1) / 2, 256);
+      if (d128) hipLaunchKernelGGL((kv_dequant_kernel<128, List>), grid(tiles), dim3(256), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
+      else hipLaunchKernelGGL((kv_dequant_kernel<64, List>), grid((tiles + 1) / 2), dim3(256), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
     }
-#undef PC_KV8
-    PC_HIP(ctx, hipGetLastError());
+  } else {
+    const Store16 st = store16(ctx, layer);
+    if (d128) hipLaunchKernelGGL((kv_copy_kernel<128, kToStore, List>), grid(tiles), dim3(256), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
+    else hipLaunchKernelGGL((kv_copy_kernel<64, kToStore, List>), grid((tiles + 1) / 2), dim3(256), 0, stream, st, k, v, c.slot_capacity, list, head_rows);
   }
-  if (n8 < n) {
-    for (int i = 0; i < n; ++i) list.set_slot(i, ctx->is8(ids[i]) ? -1 : ids[i]);
-    const size_t off = (size_t)layer * ctx->layer_stride;
-#define PC_KV16(DD, GX)                                                                                                      \
-  hipLaunchKernelGGL((kv_copy_kernel<DD, kToStore, List>), dim3(GX, c.n_kv_heads, n), dim3(256), 0, stream, ctx->k_store + off, ctx->v_store + off,       \
-                     (__bf16 *)k_dev, (__bf16 *)v_dev, c.n_kv_heads, c.slot_capacity, list, (long)ctx->slot_stride, head_rows)
-    if (c.head_dim == 128) PC_KV16(128, tiles); else PC_KV16(64, (tiles + 1) / 2);
-#undef PC_KV16
-    PC_HIP(ctx, hipGetLastError());
-  }
+  PC_HIP(ctx, hipGetLastError());
   return PC_OK;
 }
 // The n chunks of a list that are tensors of their own, [n][Hkv][n_tokens][D]
@@ -375,7 +419,6 @@ template <int N>
 pc_status append_list(percache_ctx *ctx, int layer, const int32_t *slot_list, int n, bool only_8bit, const __bf16 *k, const __bf16 *v, int n_tokens,
                       hipStream_t stream) {
   const percache_config &c = ctx->cfg;
-  const long sc_slot = (long)c.n_kv_heads * (c.slot_capacity / kKvTile);
   PieceList<N> l16, l8;
   int n16 = 0, n8 = 0, blocks8 = 0;
   for (int i = 0; i < n; ++i) {
@@ -389,13 +432,9 @@ pc_status append_list(percache_ctx *ctx, int layer, const int32_t *slot_list, in
     if (is8 && blocks > blocks8) blocks8 = blocks;
   }
   if (n8) {
-    const size_t lo = (size_t)layer * ctx->layer_stride8, sc_off = (size_t)layer * ctx->n_slots8 * sc_slot;
     const dim3 grid(blocks8, c.n_kv_heads, n);
-#define PC_APPEND8(DD)                                                                                                                       \
-  hipLaunchKernelGGL((kv_quant_kernel<DD, PieceList<N>>), grid, dim3(2 * DD), 0, stream, ctx->k8_store + lo, ctx->v8_store + lo, ctx->k_scale + sc_off, \
-                     ctx->v_scale + sc_off, k, v, c.n_kv_heads, c.slot_capacity, l8, (long)ctx->slot_stride, sc_slot, n_tokens)
-    if (c.head_dim == 128) PC_APPEND8(128); else PC_APPEND8(64);
-#undef PC_APPEND8
+    if (c.head_dim == 128) hipLaunchKernelGGL((kv_quant_kernel<128, PieceList<N>>), grid, dim3(256), 0, stream, store8(ctx, layer), k, v, c.slot_capacity, l8, n_tokens);
+    else hipLaunchKernelGGL((kv_quant_kernel<64, PieceList<N>>), grid, dim3(128), 0, stream, store8(ctx, layer), k, v, c.slot_capacity, l8, n_tokens);
     PC_HIP(ctx, hipGetLastError());
   }
   if (n16) {

@@ -98,6 +98,31 @@ def test_many_ragged_pieces_in_one_call(D):
     pc.close()
 
 
+@pytest.mark.parametrize("D", [64, 128])
+@pytest.mark.parametrize("n", [1, 63, 64, 65, 129])
+def test_batches_of_both_formats_equal_batches_of_one(D, n):
+    """Lists that name both kinds of slots (one launch for both), put and got, bit for bit what a list of each kind stores and returns."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(D + n)
+    k, v = (torch.randn((5, 3, n, D), generator=g, device=DEV).bfloat16() for _ in range(2))
+    slots = [6, 0, 4, 5, 2]                                   # slots 4 to 6 are 8-bit
+    outs = []
+    for lists in ([[0, 1, 2, 3, 4]], [[1, 4], [0, 2, 3]]):
+        pc = _ctx(D, 192, 7, 3, Hkv=3)
+        for i in lists:
+            pc.percache_kv_put_batch(0, [slots[j] for j in i], k[i].contiguous(), v[i].contiguous())
+        got = [torch.empty_like(k), torch.empty_like(v)]
+        for i in lists:
+            part = pc.percache_kv_get_batch(0, [slots[j] for j in i], n)
+            for o, p in zip(got, part):
+                o[i] = p
+        torch.cuda.synchronize()
+        outs.append(got)
+        pc.close()
+    assert torch.equal(outs[0][0], outs[1][0]) and torch.equal(outs[0][1], outs[1][1])
+    assert torch.equal(outs[0][0][[1, 4]], k[[1, 4]])
+
+
 def test_config_limits_of_the_two_formats():
     from paper_2601_11553_amd import binding
     import ctypes
