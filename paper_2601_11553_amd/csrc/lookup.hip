@@ -250,8 +250,9 @@ struct Group {
 };
 struct Groups {
   enum Kind { stream, wide, big, big_fine };
-  Group *g;      // [probes][n]
+  Group *g;      // [probes][pitch]
   int n;         // of a probe
+  int pitch;     // an odd number of 128-byte lines: 32 probes' groups go to as many places
   int p0;        // this pass's first probe
   int kind;
   int stretch;   // blocks (tiles) of a group
@@ -518,7 +519,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
           t.merge(t.of_lane_xor(16));
           t.merge(t.of_lane_xor(32));
           if (g == 0 && pb * 16 + r16 < n_probes)
-            write_group(gm.g + (size_t)(gm.p0 + pb * 16 + r16) * gm.n + (blockIdx.x * 4 + wave) * gm.per + nth / gm.stretch, t);
+            write_group(gm.g + (size_t)(gm.p0 + pb * 16 + r16) * gm.pitch + (blockIdx.x * 4 + wave) * gm.per + nth / gm.stretch, t);
           top[pb] = Top2{};
         }
       }
@@ -572,7 +573,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   if (K == kGroups) {   // groups that this wavefront has no rows for
     const int mine = rb_end > rb_begin + wave ? (rb_end - rb_begin - wave + 3) / 4 : 0;
     for (int j = (mine + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
-      if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.n + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
+      if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.pitch + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
   }
   if (K <= 0) return;  // per-row mode and groups: everything has been written
   merge_workgroup_lists<NPB, KL>(best, smem, partial, CAN_MERGE && in_launch.marks);
@@ -666,7 +667,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   __shared__ int bin_rank[64], n_cand;
   __shared__ float norm_part[4];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
-  const Group *const groups = gm.g + (size_t)p * gm.n;
+  const Group *const groups = gm.g + (size_t)p * gm.pitch;
   const _Float16 *const probe = probes + (size_t)p * d;
   // the groups: the first kSelectHeld a thread stay in registers
   Group held[kSelectHeld];
@@ -902,7 +903,13 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
 // workgroup's tiles: the operands of the next 16 k-elements are read from LDS while the MFMAs of the current ones
 // run, and the one barrier of a k-step sits before its last quarter -- there every wavefront has read the rest of the
 // current stage into registers (so the stage can be requested again, NSTG k-steps ahead) and the next stage has
-// landed (its first operands are read under that last quarter's MFMAs).
+// landed (its first operands are read under that last quarter's MFMAs).  The request goes out in two parts, behind the
+// operand reads of that quarter and of the next one: every wavefront its share of rows and probes alike, so that no
+// branch keeps the requests from between the MFMAs, and the last of them has two quarters to land in (three parts, the
+// last under the quarter in front of the wait, rows and probes by different wavefronts: 1024 probes, 200 000 rows of
+// width 1024, 390 us; now 381).  Tried on it: four wavefronts of 128 x 128 (a third of the LDS reads fewer, one
+// instruction stream a SIMD) 433; the whole request under one quarter, or priorities that differ between the wavefronts
+// of a SIMD: no change.
 // ---------------------------------------------------------------------------------------------------
 constexpr int kBigRows = 256;
 template <int PT>
@@ -910,7 +917,8 @@ struct BigTile {
   static constexpr int A_BYTES = kBigRows * 128, B_BYTES = PT * 128, STAGE = A_BYTES + B_BYTES;
   static constexpr int NSTG = 160 * 1024 / STAGE;
   static constexpr int LDS = NSTG * STAGE;
-  static constexpr int A_PER = A_BYTES / 1024 / 4, B_PER = B_BYTES / 1024 / 4;  // request instructions per wavefront and stage
+  static constexpr int A_PER = A_BYTES / 1024 / 8, B_PER = B_BYTES / 1024 / 8;  // request instructions per wavefront and stage
+  static constexpr int PER = A_PER + B_PER, PART = PER / 2;                     // requested in two parts
   static_assert((PT == 256 || PT == 128) && NSTG >= 2 && NSTG <= 5, "tile");
 };
 
@@ -926,7 +934,7 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
   const int xcd = blockIdx.x & 7, jj = blockIdx.x >> 3;
   const int group = (jj / p_tiles) * 8 + xcd, p_tile = jj % p_tiles;
   if (group >= n_groups) return;
-  const int tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
+  const int tid = threadIdx.x, lane = tid & 63, wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int wa = wave & 3, wb = wave >> 2;
   const int l32 = lane & 31, g = lane >> 5;
   const int n_tiles = (N + RT - 1) / RT;
@@ -934,36 +942,34 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
   const int m0 = p_tile * PT;
   const int nk = d / 64;
 
-  // requests: instruction i of a half-stage fills its bytes [1024 i, 1024 i + 1024), i.e. rows 8 i .. 8 i + 7;
-  // wavefronts 0-3 bring the bank rows (A_PER instructions each), 4-7 the probes (B_PER each)
-  const bool loads_bank = wave < 4;
-  const int per = loads_bank ? BT::A_PER : BT::B_PER;
-  const int my_row = (wave & 3) * per * 8 + (lane >> 3);  // + 8 k
+  // requests: instruction i of a half-stage fills its bytes [1024 i, 1024 i + 1024), i.e. rows 8 i .. 8 i + 7; every wavefront brings
+  // A_PER of the bank rows' and B_PER of the probes', from a scalar base and 32-bit lane offsets (the bank's from its tile on)
   const int my_chunk = lane & 7;
-  const _Float16 *src[8];
+  unsigned off[BT::PER];
   int f_tile = tile_begin, f_kt = 0;  // what the next request brings
+  const char *a_base = nullptr;
   auto aim = [&]() __attribute__((always_inline)) {
+    a_base = (const char *)(bank + (size_t)f_tile * RT * d);
 #pragma unroll
-    for (int k = 0; k < 8; ++k) {
-      const int row = my_row + 8 * (k < per ? k : 0);
-      const size_t at = loads_bank ? (size_t)min(f_tile * RT + row, N - 1) : (size_t)min(m0 + row, n_probes - 1);
-      src[k] = (loads_bank ? bank : probes) + at * d + ((my_chunk ^ pc::gemm::swz128(row)) * 8);
+    for (int k = 0; k < BT::A_PER; ++k) {
+      const int row = (wave * BT::A_PER + k) * 8 + (lane >> 3);
+      off[k] = (unsigned)((min(f_tile * RT + row, N - 1) - f_tile * RT) * d + ((my_chunk ^ pc::gemm::swz128(row)) * 8)) * 2u;
     }
   };
-  char *const dst = smem + (loads_bank ? 0 : BT::A_BYTES) + (wave & 3) * per * 1024;
-  // instructions k0 .. k1 - 1 of the request for k-step (f_tile, f_kt) into ring slot `slot` (a wavefront has A_PER
-  // or B_PER of them: the surplus is skipped)
+#pragma unroll
+  for (int k = 0; k < BT::B_PER; ++k) {
+    const int row = (wave * BT::B_PER + k) * 8 + (lane >> 3);
+    off[BT::A_PER + k] = (unsigned)((min(m0 + row, n_probes - 1) - m0) * d + ((my_chunk ^ pc::gemm::swz128(row)) * 8)) * 2u;
+  }
+  const char *const b_base = (const char *)(probes + (size_t)m0 * d);
+  // instructions k0 .. k1 - 1 of the request for k-step (f_tile, f_kt) into ring slot `slot`
   auto request_part = [&](int slot, int k0, int k1) __attribute__((always_inline)) {
-    if (loads_bank) {
 #pragma unroll
-      for (int k = k0; k < (k1 < BT::A_PER ? k1 : BT::A_PER); ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[k] + f_kt * 64),
-                                         (__attribute__((address_space(3))) void *)(dst + slot * STAGE + k * 1024), 16, 0, 0);
-    } else {
-#pragma unroll
-      for (int k = k0; k < (k1 < BT::B_PER ? k1 : BT::B_PER); ++k)
-        __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)(src[k] + f_kt * 64),
-                                         (__attribute__((address_space(3))) void *)(dst + slot * STAGE + k * 1024), 16, 0, 0);
+    for (int k = k0; k < k1; ++k) {
+      const bool a = k < BT::A_PER;
+      __builtin_amdgcn_global_load_lds((const __attribute__((address_space(1))) void *)((a ? a_base : b_base) + (size_t)f_kt * 128 + off[k]),
+                                       (__attribute__((address_space(3))) void *)(smem + slot * STAGE + (a ? (wave * BT::A_PER + k) * 1024 : BT::A_BYTES + (wave * BT::B_PER + k - BT::A_PER) * 1024)),
+                                       16, 0, 0);
     }
   };
   // on to the next k-step; past the last one the cursor stays on valid rows (requests made then land in a slot that
@@ -973,7 +979,8 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
       f_kt = 0;
       if (f_tile + 1 < tile_end) {
         ++f_tile;
-        if (loads_bank) aim();
+        a_base += (size_t)RT * d * 2;
+        if (f_tile + 1 == n_tiles) aim();   // (rows past the end)
       }
     }
   };
@@ -1006,9 +1013,12 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
     for (int i = 0; i < (READS < MMAS ? READS : MMAS); ++i) {
       __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
       __builtin_amdgcn_sched_group_barrier(0x100, 1, 0);
-      if ((i & 1) == 0 && i / 2 < loads) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
     }
-    if (MMAS > READS) __builtin_amdgcn_sched_group_barrier(0x008, MMAS - READS, 0);
+#pragma unroll
+    for (int i = 0; i < (MMAS > READS ? MMAS - READS : 0); ++i) {
+      __builtin_amdgcn_sched_group_barrier(0x008, 1, 0);
+      for (int l = loads * i / (MMAS - READS); l < loads * (i + 1) / (MMAS - READS); ++l) __builtin_amdgcn_sched_group_barrier(0x020, 1, 0);
+    }
   };
 
   Top2 top[NB];      // (K == kGroups) of the group that this wavefront is in
@@ -1018,17 +1028,17 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
 
   if (tile_begin < tile_end) {  // the first k-step, then whole requests for the next NSTG - 2 and the first part of one more
     aim();
-    request_part(0, 0, 8);
+    request_part(0, 0, BT::PER);
     advance();
     pc::gemm::wait_vmcnt0();
     __builtin_amdgcn_s_barrier();
     asm volatile("" ::: "memory");
 #pragma unroll
     for (int s2 = 1; s2 < NSTG - 1; ++s2) {
-      request_part(s2, 0, 8);
+      request_part(s2, 0, BT::PER);
       advance();
     }
-    request_part(NSTG - 1, 0, 3);  // (the rest of it under the first two quarters below)
+    request_part(NSTG - 1, 0, BT::PART);  // (the rest of it under the first quarter below)
     read_ops(0, 0, 0);
   }
   int slot = 0;  // ring slot of this k-step
@@ -1044,31 +1054,27 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
     for (int kt = 0; kt < nk; ++kt) {
       const int slot_prev = slot == 0 ? NSTG - 1 : slot - 1, slot_next = slot == NSTG - 1 ? 0 : slot + 1;
       // a request was begun behind the last barrier, into the slot that k-step gave up: the rest of its instructions
-      request_part(slot_prev, 3, 6);
       read_ops(1, slot, 1);
+      request_part(slot_prev, BT::PART, BT::PER);
       mma_ops(0);
-      interleave(3);
-      request_part(slot_prev, 6, 8);
+      interleave(BT::PER - BT::PART);
+      advance();
       read_ops(0, slot, 2);
       mma_ops(1);
-      interleave(2);
-      advance();
+      interleave(0);
       read_ops(1, slot, 3);
       mma_ops(0);
       interleave(0);
       // every read of this stage is in registers and this wavefront's part of the next stage has landed: all of its
       // requests but the NSTG - 2 latest ones, which are for later k-steps
-      constexpr int LEAVE_A = (NSTG - 2) * BT::A_PER, LEAVE_B = (NSTG - 2) * BT::B_PER;  // (vmcnt: bits 3:0 and 15:14)
-      static_assert(LEAVE_A < 64 && LEAVE_B < 64, "vmcnt");
-      if (loads_bank) __builtin_amdgcn_s_waitcnt((LEAVE_A & 0xf) | (7 << 4) | ((LEAVE_A >> 4) << 14));
-      else __builtin_amdgcn_s_waitcnt((LEAVE_B & 0xf) | (7 << 4) | ((LEAVE_B >> 4) << 14));
+      pc::gemm::wait_vmcnt_lds<(NSTG - 2) * BT::PER>();
       asm volatile("" ::: "memory");
       __builtin_amdgcn_s_barrier();
       asm volatile("" ::: "memory");
-      request_part(slot, 0, 3);       // the k-step NSTG ahead (past the end: see advance())
       read_ops(0, slot_next, 0);      // (past the last k-step: whatever that slot holds, never multiplied)
+      request_part(slot, 0, BT::PART);       // the k-step NSTG ahead (past the end: see advance())
       mma_ops(1);
-      interleave(3);
+      interleave(BT::PART);
       slot = slot_next;
     }
     // cosines of this tile's rows (up to the probe's own norm, which the finalize kernel divides by)
@@ -1110,44 +1116,39 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
       // lane (l32, 0) has rows 0..3, 8..11, 16..19, 24..27 of a block, lane (l32, 1) the others
       const int base = r0 + NA * wa * 32 + g * 4;
       const bool fine = gm.kind == Groups::big_fine, ends = (tile - tile_begin + 1) % gm.stretch == 0 || tile + 1 == tile_end;
+      float inv[NA][16];
 #pragma unroll
-      for (int a = 0; a < NA; ++a) {
-        Top2 mine[NB];
+      for (int a = 0; a < NA; ++a)
 #pragma unroll
-        for (int q4 = 0; q4 < 4; ++q4) {
-          float inv[4];
+        for (int r = 0; r < 16; ++r) inv[a][r] = __shfl(inv_mine, a * 32 + (r >> 2) * 8 + g * 4 + (r & 3), 64);
+      // (probes outside: one best and second best at a time; in the other order they spill)
 #pragma unroll
-          for (int e = 0; e < 4; ++e) inv[e] = __shfl(inv_mine, a * 32 + q4 * 8 + g * 4 + e, 64);
+      for (int t = 0; t < NB; ++t) {
+        const int p = m0 + (NB * wb + t) * 32 + l32;
+        Group *const to = gm.g + (size_t)(gm.p0 + p) * gm.pitch;
 #pragma unroll
-          for (int e = 0; e < 4; ++e)
+        for (int a = 0; a < NA; ++a) {
+          Top2 mine;
 #pragma unroll
-            for (int t = 0; t < NB; ++t) mine[t].add(acc[a][t][q4 * 4 + e] * inv[e], a * 32 + q4 * 8 + e);
+          for (int r = 0; r < 16; ++r) mine.add(acc[a][t][r] * inv[a][r], a * 32 + (r >> 2) * 8 + (r & 3));
+          if (__ballot(mine.i == INT_MAX)) {
+            if (mine.i == INT_MAX)
+#pragma unroll
+              for (int r = 0; r < 16; ++r) mine.first(acc[a][t][r] * inv[a][r], a * 32 + (r >> 2) * 8 + (r & 3));
+          }
+          mine.i += mine.i == INT_MAX ? 0 : base;
+          if (fine) {
+            if (p < n_probes) write_group(to + ((tile * 4 + wa) * NA + a) * 2 + g, mine);
+          } else {
+            top[t].merge(mine);
+          }
           __builtin_amdgcn_sched_barrier(0);
         }
-#pragma unroll
-        for (int t = 0; t < NB; ++t) {
-          if (__ballot(mine[t].i == INT_MAX)) {
-            const bool none = mine[t].i == INT_MAX;
-#pragma unroll
-            for (int r = 0; r < 16; ++r) {
-              const float v = acc[a][t][r] * __shfl(inv_mine, a * 32 + (r >> 2) * 8 + g * 4 + (r & 3), 64);
-              if (none) mine[t].first(v, a * 32 + (r >> 2) * 8 + (r & 3));
-            }
-          }
-          mine[t].i += mine[t].i == INT_MAX ? 0 : base;
-          const int p = m0 + (NB * wb + t) * 32 + l32;
-          Group *const to = gm.g + (size_t)(gm.p0 + p) * gm.n;
-          if (fine) {
-            if (p < n_probes) write_group(to + ((tile * 4 + wa) * NA + a) * 2 + g, mine[t]);
-            continue;
-          }
-          top[t].merge(mine[t]);
-          if (a == NA - 1 && ends) {
-            Top2 both = top[t];
-            both.merge(both.of_lane_xor(32));
-            if (g == 0 && p < n_probes) write_group(to + (group * 4 + wa) * gm.per + (tile - tile_begin) / gm.stretch, both);
-            top[t] = Top2{};
-          }
+        if (!fine && ends) {
+          Top2 both = top[t];
+          both.merge(both.of_lane_xor(32));
+          if (g == 0 && p < n_probes) write_group(to + (group * 4 + wa) * gm.per + (tile - tile_begin) / gm.stretch, both);
+          top[t] = Top2{};
         }
       }
     }
@@ -1158,7 +1159,7 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
       for (int j = (tile_end - tile_begin + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
         for (int t = 0; t < NB; ++t) {
           const int p = m0 + (NB * wb + t) * 32 + l32;
-          if (g == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (group * 4 + wa) * gm.per + j, Top2{});
+          if (g == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.pitch + (group * 4 + wa) * gm.per + j, Top2{});
         }
     return;
   }
@@ -1434,7 +1435,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
         const int nth = rb - rb_begin, p = pg * 32 + l32;
         if ((nth + 1) % gm.stretch == 0 || rb == rb_last) {
           top.merge(top.of_lane_xor(32));
-          if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (blockIdx.x * RS + set) * gm.per + nth / gm.stretch, top);
+          if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.pitch + (blockIdx.x * RS + set) * gm.per + nth / gm.stretch, top);
           top = Top2{};
         }
         continue;
@@ -1459,7 +1460,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
   if constexpr (K == kGroups) {   // groups that this workgroup has no rows for
     const int p = pg * 32 + l32;
     for (int j = (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
-      if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.n + (blockIdx.x * RS + set) * gm.per + j, Top2{});
+      if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.pitch + (blockIdx.x * RS + set) * gm.per + j, Top2{});
   }
   if constexpr (K <= 0) return;  // per-row mode and groups: everything has been written
   // the two lanes of a probe hold different rows
@@ -1673,6 +1674,7 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     cut(g, (g.blocks + bg.groups - 1) / bg.groups, least > kGroupsPerWave ? least : kGroupsPerWave);
     g.n = g.kind == Groups::big_fine ? g.blocks * 16 : bg.groups * 4 * g.per;
   }
+  g.pitch = ((g.n + 7) / 8 | 1) * 8;
   return g;
 }
 
@@ -1807,7 +1809,7 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
   for (int p0 = 0, np; p0 < n_probes; p0 += np) {
     np = n_probes - p0;
     Groups gm = groups_of(ctx, np, N);
-    while (np > 1 && (size_t)np * gm.n * sizeof(Group) > workspace_bytes) {
+    while (np > 1 && (size_t)np * gm.pitch * sizeof(Group) > workspace_bytes) {
       np = np > 256 ? (np - 1) / 256 * 256 : (np + 1) / 2;
       gm = groups_of(ctx, np, N);
     }
@@ -1846,11 +1848,12 @@ size_t percache_lookup_workspace_bytes(const percache_ctx *ctx, int32_t n_probes
   // Top-k: the groups of all probes of a call (of up to 4096 at a time), for whatever the bank holds; a smaller workspace takes fewer probes at a time.
   auto grow = [](size_t &a, size_t b) { a = a > b ? a : b; };
   const size_t n = (size_t)n_probes, cus = (size_t)ctx->n_cu, wide_grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
-  size_t groups = (n < 32 ? n : 32) * max_stream_grid(ctx) * 4 * kGroupsPerWave;
+  auto pitch = [](size_t groups) { return groups + 16; };
+  size_t groups = (n < 32 ? n : 32) * pitch(max_stream_grid(ctx) * 4 * kGroupsPerWave);
   if (n > kBatchedFrom) {
-    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * (wide_grid > cus ? wide_grid : cus) * kGroupsPerWide);
-    grow(groups, (n < 256 ? n : 256) * (cus * 4 * kGroupsPerWave + 2 * kLeastGroups));
-    grow(groups, (n < 4096 ? n : 4096) * 2 * kLeastGroups);
+    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * pitch((wide_grid > cus ? wide_grid : cus) * kGroupsPerWide));
+    grow(groups, (n < 256 ? n : 256) * pitch(cus * 4 * kGroupsPerWave + 2 * kLeastGroups));
+    grow(groups, (n < 4096 ? n : 4096) * pitch(2 * kLeastGroups));
   }
   size_t bytes = list_bytes(ctx, n_probes);
   grow(bytes, groups * sizeof(Group));
