@@ -239,8 +239,8 @@ struct RowScan {
 // one of these may hold two of the k rows does it look at rows again.  Sorted lists of eight in every lane, which this replaces, cost ten
 // instructions an entry for nearly every row, because one of a wavefront's 64 lists takes nearly every row in.
 // us a call, 8 best, lists | groups (3 best in brackets): 8 probes, 50 000 rows of width 1024 33.0 | 25.6 (25.9 | 25.3), 200 000 rows 78.9 | 71.6 (71.2 | 71.0),
-// 32 probes 88.9 | 76.6; 64 probes 179 | 92 (175 | 81), 1024 probes 712 | 457 (708 | 450); 2000 rows of width 768, 32 probes 22.3 | 16.2, 1024 probes
-// 43.8 | 46.9 (39.2 | 41.1).
+// 32 probes 88.9 | 76.6; 64 probes 179 | 78 (175 | 77), 1024 probes 712 | 437 (708 | 432); 2000 rows of width 768, 32 probes 22.3 | 16.2, 1024 probes
+// 43.8 | 43 (39.2 | 41).
 // A group is what one lane or two meet in a stretch of the bank; which rows these are only Groups::row knows.  A workgroup has about four a
 // wavefront: under many probes their bytes count, but over a small bank two of the k best rows would often share a large one.
 constexpr int kGroups = -1;
@@ -249,8 +249,8 @@ struct Group {
   int row, unused;
 };
 struct Groups {
-  enum Kind { stream, wide, big, big_fine };
-  Group *g;      // [probes][pitch]
+  enum Kind { stream, wide, wide_rows, big, big_fine };
+  Group *g;      // [probes][pitch] (wide_rows: the similarities alone, four to a Group's place)
   int n;         // of a probe
   int pitch;     // an odd number of 128-byte lines: 32 probes' groups go to as many places
   int p0;        // this pass's first probe
@@ -261,15 +261,17 @@ struct Groups {
   int blocks;    // (tiles) of the bank
   int sets;      // wide: sets of 32 rows in a block, a group of its own each
 
+  __device__ float *rows(int p) const { return (float *)(g + (size_t)p * pitch); }
   __host__ Groups from_probe(int p) const {
     Groups o = *this;
     o.p0 += p;
     return o;
   }
   // A group's rows in jobs of 16 (stream) or 32 consecutive ones: how many jobs, the first row of one (negative: none), and whether row i of it counts.
-  __host__ __device__ int jobs() const { return kind == big ? 2 * stretch : kind == big_fine ? 1 : stretch; }
+  __host__ __device__ int jobs() const { return kind == big ? 2 * stretch : kind == big_fine || kind == wide_rows ? 1 : stretch; }
   __host__ __device__ int first_row(int group, int job) const {
     if (kind == big_fine) return (group >> 1) * 32;
+    if (kind == wide_rows) return group / 32 * 32;
     const int j = group % per, w = group / per;   // of wavefront (workgroup) w
     if (kind == stream) {
       const int block = w % 4 + 4 * (j * stretch + job);
@@ -282,7 +284,7 @@ struct Groups {
     const int tile = big_begin(w / 4) + j * stretch + job / 2;
     return tile < big_begin(w / 4 + 1) ? tile * 256 + w % 4 * 64 + job % 2 * 32 : -1;
   }
-  __host__ __device__ bool counts(int group, int i) const { return kind != big_fine || (i >> 2 & 1) == (group & 1); }
+  __host__ __device__ bool counts(int group, int i) const { return kind == big_fine ? (i >> 2 & 1) == (group & 1) : kind != wide_rows || i == group % 32; }
   __host__ __device__ int big_begin(int wg) const { return (int)((long)wg * blocks / per_wg); }   // a workgroup's first tile
 };
 // The best and the second best of numbers offered in the order of their rows.
@@ -412,7 +414,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   TopK<KL> best[NPB];  // this lane's best rows for probe pb*16 + r16 (K > 0)
 #pragma unroll
   for (int pb = 0; pb < NPB; ++pb) best[pb].clear();
-  // sum of squares of the probe that this wavefront merges (see InLaunch), in the order of probe_inverse_norm
+  // sum of squares of the probe that this wavefront merges (see InLaunch), in the order of inverse_norm
   constexpr bool CAN_MERGE = NPB == 1 && K > 0 && K <= 4;
   float merge_sum = 0.f;
   if (CAN_MERGE && in_launch.marks) {
@@ -582,8 +584,9 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
 }
 
-// The inverse norm of a probe, by the first 256 threads of a workgroup; part [4] in LDS; one barrier.
-__device__ __forceinline__ float probe_inverse_norm(const _Float16 *__restrict__ probe, int d, int tid, float *part) {
+// The inverse norm of a probe, by the first 256 threads of a workgroup: a thread's share of the squares, to be asked for before other loads are
+// waited for, then their sum (part [4] in LDS; one barrier).
+__device__ __forceinline__ float probe_squares(const _Float16 *__restrict__ probe, int d, int tid) {
   float ss = 0.f;
   if (tid < 256)
     for (int v = tid; v < d / 8; v += 256) {
@@ -591,6 +594,9 @@ __device__ __forceinline__ float probe_inverse_norm(const _Float16 *__restrict__
 #pragma unroll
       for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
     }
+  return ss;
+}
+__device__ __forceinline__ float inverse_norm(float ss, int tid, float *part) {
 #pragma unroll
   for (int o = 32; o > 0; o >>= 1) ss += __shfl_xor(ss, o, 64);
   if (tid < 256 && (tid & 63) == 0) part[tid >> 6] = ss;
@@ -612,7 +618,12 @@ __global__ __launch_bounds__(kFinalizeThreads) void lookup_finalize_kernel(const
   __shared__ Best red[NWV];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   Best b{-INFINITY, INT_MAX};
-  for (int w = tid; w < n_partials; w += kFinalizeThreads) {
+  // (the first list's row is on its way while the probe's squares are)
+  Best first = b;
+  if (tid < n_partials) first = partial[(size_t)tid * partial_stride + p];
+  const float ss = probe_squares(probes + (size_t)p * d, d, tid);
+  if (first.idx != INT_MAX && better(first.s, first.idx, b.s, b.idx)) b = first;
+  for (int w = tid + kFinalizeThreads; w < n_partials; w += kFinalizeThreads) {
     const Best o = partial[(size_t)w * partial_stride + p];
     if (o.idx != INT_MAX && better(o.s, o.idx, b.s, b.idx)) b = o;
   }
@@ -622,7 +633,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void lookup_finalize_kernel(const
     if (better(c.s, c.idx, b.s, b.idx)) b = c;
   }
   if (lane == 0) red[wave] = b;
-  const float inv = probe_inverse_norm(probes + (size_t)p * d, d, tid, norm_part);
+  const float inv = inverse_norm(ss, tid, norm_part);
   if (tid != 0) return;
 #pragma unroll
   for (int w = 1; w < NWV; ++w)
@@ -670,20 +681,26 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   const Group *const groups = gm.g + (size_t)p * gm.pitch;
   const _Float16 *const probe = probes + (size_t)p * d;
   // the groups: the first kSelectHeld a thread stay in registers
+  const float *const rows = gm.rows(p);
+  auto group_at = [&](int at) __attribute__((always_inline)) {
+    if (gm.kind != Groups::wide_rows) return groups[at];
+    const float v = rows[at];
+    return Group{v, v == -INFINITY ? INFINITY : -INFINITY, at, 0};
+  };
   Group held[kSelectHeld];
 #pragma unroll
   for (int i = 0; i < kSelectHeld; ++i) {
     held[i].best = __builtin_nanf("");
-    if (i * kSelectThreads + tid < gm.n) held[i] = groups[i * kSelectThreads + tid];
+    if (i * kSelectThreads + tid < gm.n) held[i] = group_at(i * kSelectThreads + tid);
   }
   if (tid < 64) bin_rank[tid] = 0;
   if (tid == 0) n_cand = 0;
-  const float inv = probe_inverse_norm(probe, d, tid, norm_part);
+  const float inv = inverse_norm(probe_squares(probe, d, tid), tid, norm_part);
   unsigned best = 0;
 #pragma unroll
   for (int i = 0; i < kSelectHeld; ++i) best = max(best, ordered(held[i].best));
 #pragma unroll 8
-  for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) best = max(best, ordered(groups[at].best));
+  for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) best = max(best, ordered(group_at(at).best));
   top[tid] = best;
   __syncthreads();
   // the k-th best of 64 bins; a wavefront compares all of them with eight
@@ -713,7 +730,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   if (best >= bound) {
 #pragma unroll
     for (int i = 0; i < kSelectHeld; ++i) offer(held[i], i * kSelectThreads + tid);
-    for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) offer(groups[at], at);
+    for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) offer(group_at(at), at);
   }
   __syncthreads();
   int n = n_cand;
@@ -741,7 +758,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
       unsigned long long key = 0;
       uint2 more = make_uint2(0, 0);
       for (int at = tid; at < gm.n; at += kSelectThreads) {
-        const Group c = groups[at];
+        const Group c = group_at(at);
         const unsigned long long o = c.best == c.best ? key_of(ordered(c.best), c.row) : 0ull;
         if (o < last && o > key) {
           key = o;
@@ -858,7 +875,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
           for (int u = 0; u < U; ++u) {
             if (s0 + u >= d / 16) continue;
             const f16x8 x = __builtin_bit_cast(f16x8, av[u]), y = __builtin_bit_cast(f16x8, bv[u]);
-            if ((u & 1) && gm.kind == Groups::wide) acc[1] = pc::gemm::mma(x, y, acc[1]);
+            if ((u & 1) && (gm.kind == Groups::wide || gm.kind == Groups::wide_rows)) acc[1] = pc::gemm::mma(x, y, acc[1]);
             else acc[0] = pc::gemm::mma(x, y, acc[0]);
           }
         }
@@ -866,7 +883,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int i = (r >> 2) * 8 + g2 * 4 + (r & 3);
-            const float v = gm.kind == Groups::wide ? acc[0][r] + acc[1][r] : acc[0][r];
+            const float v = gm.kind == Groups::wide || gm.kind == Groups::wide_rows ? acc[0][r] + acc[1][r] : acc[0][r];
             if (gm.counts(group, i)) offer_row(v * inv_norm[min(row0 + i, N - 1)], row0 + i);
           }
         }
@@ -1426,6 +1443,15 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
             top.add(v[r], row);
           }
         }
+        if (gm.kind == Groups::wide_rows) {
+          const int p = pg * 32 + l32, row0 = rb * BR + set * 32 + g2 * 4;   // (the pitch leaves room for the last block's quad)
+          if (p < n_probes) {
+#pragma unroll
+            for (int q4 = 0; q4 < 4; ++q4)
+              if (row0 + q4 * 8 < N) *(f32x4 *)(gm.rows(gm.p0 + p) + row0 + q4 * 8) = f32x4{v[q4 * 4], v[q4 * 4 + 1], v[q4 * 4 + 2], v[q4 * 4 + 3]};
+          }
+          continue;
+        }
         if (__ballot(top.i == INT_MAX)) {
           const bool none = top.i == INT_MAX;
 #pragma unroll
@@ -1459,7 +1485,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
   PC_LOOKUP_WAIT_VMCNT(0);
   if constexpr (K == kGroups) {   // groups that this workgroup has no rows for
     const int p = pg * 32 + l32;
-    for (int j = (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
+    for (int j = gm.kind == Groups::wide ? (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch : gm.per; j < gm.per; ++j)
       if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.pitch + (blockIdx.x * RS + set) * gm.per + j, Top2{});
   }
   if constexpr (K <= 0) return;  // per-row mode and groups: everything has been written
@@ -1642,7 +1668,7 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
 int probe_tile(int n_probes) { return big_tiles_pay(n_probes) ? 256 : 128; }
 // The groups of a pass of so many probes (see Groups): about four a wavefront, in the matrix-product kernel at least 1024 in all; there, over a
 // small bank, the 16 rows that a lane has in a block of 32. 
-constexpr int kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
+constexpr int kRowsUpTo = 8192, kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
 Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
   auto cut = [](Groups &g, int blocks, int into) {   // a wavefront's (workgroup's) blocks into that many groups
     g.stretch = (blocks + into - 1) / into;
@@ -1665,6 +1691,12 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     g.blocks = (N + 32 * w.sets - 1) / (32 * w.sets);
     cut(g, w.per_wg, kGroupsPerWide / w.sets);
     g.n = w.grid * w.sets * g.per;
+    // Every row a group: no probe is ever in doubt, which over so few rows one of them would nearly always be.  us a call, 8 best, groups | rows: 67 probes
+    // over 2273 rows of width 768 23.0 | 14.9, over 6000 22.8 | 18.0; past 8192 rows topk_groups_kernel reads the similarities twice and gains nothing.
+    if (N <= kRowsUpTo) {
+      g.kind = Groups::wide_rows;
+      g.n = N;
+    }
   } else {
     const BigShape bg = big_shape(ctx->n_cu, N, n_probes, probe_tile(n_probes));
     g.kind = N <= kFineGroupsUpTo ? Groups::big_fine : Groups::big;
@@ -1674,7 +1706,8 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     cut(g, (g.blocks + bg.groups - 1) / bg.groups, least > kGroupsPerWave ? least : kGroupsPerWave);
     g.n = g.kind == Groups::big_fine ? g.blocks * 16 : bg.groups * 4 * g.per;
   }
-  g.pitch = ((g.n + 7) / 8 | 1) * 8;
+  const int places = g.kind == Groups::wide_rows ? (g.n + 3) / 4 : g.n;
+  g.pitch = ((places + 7) / 8 | 1) * 8;
   return g;
 }
 
@@ -1852,6 +1885,7 @@ size_t percache_lookup_workspace_bytes(const percache_ctx *ctx, int32_t n_probes
   size_t groups = (n < 32 ? n : 32) * pitch(max_stream_grid(ctx) * 4 * kGroupsPerWave);
   if (n > kBatchedFrom) {
     grow(groups, (n < kWideUpTo ? n : kWideUpTo) * pitch((wide_grid > cus ? wide_grid : cus) * kGroupsPerWide));
+    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * pitch(kRowsUpTo / 4));
     grow(groups, (n < 256 ? n : 256) * pitch(cus * 4 * kGroupsPerWave + 2 * kLeastGroups));
     grow(groups, (n < 4096 ? n : 4096) * pitch(2 * kLeastGroups));
   }
