@@ -1580,6 +1580,47 @@ int choose_splits(int slots_in, long base_wgs, int min_tiles, int cap) {
   return best;
 }
 
+// What one of the attention kernels takes per 64-key tile of a workgroup, us: where a CU has one workgroup, and how many times that where it has two
+// (0: the long-context kernels, one workgroup a CU), measured on 256 CUs.
+struct TilePace {
+  double tile, second;
+};
+// Partitions of the key axis of a launch of n_bg kv heads (of all queries) x q_tiles blocks, by an estimate of its time:
+//   a workgroup's tiles, one after the other; two workgroups on a CU slow each other down, more go in rounds (a kv head's partition stays on an XCD,
+//   so it is the fullest XCD that counts); then the merge's launch and its bytes, written and read.
+// Drawn from 160 launches, 1 to 8 queries, head sizes 64 and 128, bf16, 8-bit and mixed slots, 7 to 257 tiles, each at up to 14 partition counts: the
+// estimate's choice takes 0.1 % more than the best count on average, 3 % at most.  The rule before it (choose_splits) filled two workgroups a CU where
+// the kernel allows two and kept four tiles a partition.  76 other launches against it: 1.087 times as fast on average, 0.973 to 1.77.
+// us a projection of 512 columns and attention, before | now: 16 heads over
+// 8, 100 rows over 36 tiles 27.0 | 23.2, 235 rows over 32 30.0 | 26.7, 55 over 6, mixed slots 26.2 | 18.2; 24 over 8, 2 x 74 rows over 40 31.3 | 28.8; 14 over 2
+// of 64, 42 rows over 20, 8-bit slots 21.2 | 15.8; 28 over 4, 3 x 256 rows over 16 59.7 | 44.1 (252 workgroups, but 35 on the fullest XCD).
+static int choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_tiles, int tiles, double merge_us, int cap) {
+  auto estimate = [&](int ns) {
+    const long wgs = (n_bg * ns + 7) / 8 * 8 * q_tiles;
+    double t;
+    if (pace.second == 0) {
+      t = (double)((wgs + n_cu - 1) / n_cu) * (pace.tile * tiles / ns + 4.0);   // (4: from a workgroup's start to its first tile, and its epilogue)
+    } else {
+      const double one = pace.tile * (0.42 * ((tiles + ns - 1) / ns) + 0.58 * tiles / ns), two = one * pace.second;   // (the longest partition, and the mean one)
+      const long rounds = wgs / (2 * n_cu), rest = wgs % (2 * n_cu);
+      t = rounds * two + (rest == 0 ? 0.0 : rest <= n_cu ? one : two) + (wgs > 2 * n_cu ? 3.0 : 0.0);
+    }
+    if (ns > 1) t += (ns <= 4 ? 2.2 : ns <= 16 ? 3.3 : 4.5) + merge_us * ns;   // (how many partials a lane of the merge has in flight)
+    return t;
+  };
+  // (the count of the rule before it unless another one promises more than the estimate errs by)
+  int best = choose_splits(pace.second == 0 ? n_cu : 2 * n_cu, n_bg * q_tiles, tiles, cap);
+  double least = estimate(best) - 0.7;
+  for (int ns = 1; ns <= cap && ns <= tiles; ++ns) {
+    const double t = estimate(ns);
+    if (t < least - 1e-9) {
+      least = t;
+      best = ns;
+    }
+  }
+  return best;
+}
+
 pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, int batch, int t_fresh, hipStream_t stream) {
   const percache_config &c = ctx->cfg;
   const int ft = (t_fresh + TK - 1) / TK;
@@ -1676,7 +1717,14 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   // stack: 1 partition 360 us, 2 363, 4 373 with a merge of 14; before, lightest first and every fresh tile masked: 411 to 421).
   const bool uneven = wide && 2 * fresh_tiles > min_tiles && (long)batch * c.n_kv_heads * q_tiles >= ctx->n_cu;
   if (n_splits <= 0 && (uneven || pair)) n_splits = 1;
-  if (n_splits <= 0) n_splits = choose_splits(wide ? ctx->n_cu : 2 * ctx->n_cu, (long)batch * c.n_kv_heads * q_tiles, min_tiles, cap);
+  if (n_splits <= 0) {
+    const bool d128 = c.head_dim == 128;
+    const TilePace pace = wide ? TilePace{!d128 ? 1.0 : mixed ? 3.0 : use8 ? 2.0 : 1.8, 0}
+                          : halved ? TilePace{0.79, 1.58}
+                          : d128 ? (use8 ? TilePace{1.17, 1.12} : TilePace{1.16, 1.51}) : use8 ? TilePace{1.12, 1.05} : TilePace{0.68, 1.07};
+    const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's partials, written and read at 5.4 TB/s
+    n_splits = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, merge_us, cap);
+  }
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;
   const float *ksc = nullptr, *vsc = nullptr;

@@ -10,7 +10,7 @@ import torch
 
 import oracle
 from paper_2601_11553_amd import workloads as wl
-from paper_2601_11553_amd.binding import PercacheError
+from paper_2601_11553_amd.binding import Percache, PercacheError
 
 from gpu_util import DEV, bf16, check_close, fill_slots, host, make_ctx
 
@@ -252,6 +252,29 @@ def test_seeded_random_shapes(seed):
             sv = np.stack([kv_fp8.round_trip(wl.round_bf16(x)) if e else x for x, e in zip(sv, is8)])
         O, _, _, _ = oracle.prefill_reuse(w.X[b], w.Wqkv, w.n_q_heads, w.n_kv_heads, w.head_dim, w.rope_theta, sk, sv, ids, w.used_len[b])
         check_close(host(out[b]), O, f"seed {seed} (D={D} G={G} Hkv={Hkv} B={batch} T={t_fresh} chunks={n_chunks}x{C} slots mode {mode}) b={b}")
+    pc.close()
+
+
+# (fresh rows, heads, kv heads, head size, queries, chunks, chunk tokens, 8-bit slots): partitions of one or two tiles, as many as tiles, past 16, kv heads
+# that do not come out even over the XCDs, 256-row blocks
+@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch,n_chunks,C,n8", [
+    (100, 16, 8, 128, 1, 3, 256, 0), (40, 4, 2, 128, 1, 6, 64, 0), (23, 14, 2, 64, 1, 3, 256, 6), (45, 16, 8, 128, 1, 5, 1024, 6), (55, 16, 8, 128, 1, 3, 128, 2),
+    (20, 16, 8, 128, 1, 16, 256, 0), (256, 28, 4, 128, 3, 2, 512, 0), (203, 24, 8, 128, 6, 2, 192, 12)])
+def test_partition_counts_chosen_by_the_library(t_fresh, Hq, Hkv, D, batch, n_chunks, C, n8):
+    """The library's own partition counts against one partition: the same attention up to the rounding of partials to bf16."""
+    S = batch * n_chunks
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=S, slot_capacity=C, max_pos=t_fresh + C * n_chunks, n_slots_8bit=min(n8, S),
+                  device=DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(t_fresh + D)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    for s in range(S):
+        n = C - 7 * (s % 5)
+        pc.percache_kv_put(0, s, rnd(Hkv, n, D), rnd(Hkv, n, D))
+    q, kf, vf = rnd(batch, Hq, t_fresh, D), rnd(batch, Hkv, t_fresh, D), rnd(batch, Hkv, t_fresh, D)
+    ids = np.arange(S, dtype=np.int32).reshape(batch, n_chunks)
+    own, one = (pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=n) for n in (0, 1))
+    check_close(host(own), host(one), f"T={t_fresh} heads {Hq} over {Hkv} of {D}, {batch} x {n_chunks} chunks")
     pc.close()
 
 
