@@ -298,27 +298,29 @@ template <int NF, int NT>
 __global__ __launch_bounds__((64 * pc::few::Form<NF, NT>::WV)) void swiglu_few_kernel(const __bf16 *__restrict__ A, const __bf16 *__restrict__ gain, float eps,
                                                                                     const __bf16 *__restrict__ Wg, const __bf16 *__restrict__ Wu,
                                                                                     __bf16 *__restrict__ Y, int M, int F, int K, int n_wt, int n_tt) {
-  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG, HALF = NF / 2;
+  // a tile's weight rows: FEAT of the gate, then the up rows of the same features; four features x 16 tokens are a unit of the epilogue
+  constexpr int WV = pc::few::Form<NF, NT>::WV, NSTG = pc::few::Form<NF, NT>::NSTG, FEAT = 8 * NF, QUADS = FEAT / 4;
+  static_assert(QUADS * NT % 4 == 0, "units of whole wavefronts");
   __shared__ __align__(16) char lds[pc::few::Tile<NF, NT, WV, NSTG, true>::LDS_BYTES];
   int wt, tt;
   if (!pc::few::place(blockIdx.x, n_wt, n_tt, wt, tt)) return;
   const int lane = threadIdx.x & 63, wave = __builtin_amdgcn_readfirstlane(threadIdx.x >> 6), l16 = lane & 15, g = lane >> 4;
-  const int f0 = wt * 16 * HALF, m0 = tt * 16 * NT;
+  const int f0 = wt * FEAT, m0 = tt * 16 * NT;
   f32x4 acc[NF][NT];
   float ss[NT];
   pc::few::slice_product<NF, NT, WV, NSTG, true>(
-      lds, [&](int r) __attribute__((always_inline)) { return (r < 16 * HALF ? Wg + (size_t)(f0 + r) * K : Wu + (size_t)(f0 + r - 16 * HALF) * K); },
+      lds, [&](int r) __attribute__((always_inline)) { return (r < FEAT ? Wg + (size_t)(f0 + r) * K : Wu + (size_t)(f0 + r - FEAT) * K); },
       [&](int r) __attribute__((always_inline)) { return A + (size_t)min(m0 + r, M - 1) * K; }, gain, K, wave, lane, [](char *, int, int) {}, acc, ss);
   pc::few::share_slices<NF, NT, WV, NSTG, true>(lds, wave, lane, acc, ss);
 #pragma unroll
-  for (int b = wave; b < HALF * NT; b += WV) {
-    const int f = b / NT, t = b % NT, m = m0 + t * 16 + l16;
+  for (int b = wave; b < QUADS * NT / 4; b += WV) {
+    const int t = (b * 4 + g) / QUADS, q = (b * 4 + g) % QUADS, qu = q + QUADS, m = m0 + t * 16 + l16;
     const float r = pc::few::row_factor<NF, NT, WV>(lds, t, l16, K, eps);
-    const f32x4 gate = pc::few::tile_sum<NF, NT, WV>(lds, f, t, lane) * r, up = pc::few::tile_sum<NF, NT, WV>(lds, f + HALF, t, lane) * r;
+    const f32x4 gate = pc::few::tile_sum<NF, NT, WV>(lds, q / 4, t, q % 4 * 16 + l16) * r, up = pc::few::tile_sum<NF, NT, WV>(lds, qu / 4, t, qu % 4 * 16 + l16) * r;
     float o[4];
 #pragma unroll
     for (int e = 0; e < 4; ++e) o[e] = gate[e] / (1.0f + __expf(-gate[e])) * up[e];
-    if (m < M) *(uint2 *)(Y + (size_t)m * F + f0 + f * 16 + g * 4) = pack4(o[0], o[1], o[2], o[3]);
+    if (m < M) *(uint2 *)(Y + (size_t)m * F + f0 + q * 4) = pack4(o[0], o[1], o[2], o[3]);
   }
 }
 
@@ -414,13 +416,13 @@ pc_status launch_oproj_merge(percache_ctx *ctx, const float *part_o, const float
 }
 pc_status launch_swiglu_few(percache_ctx *ctx, const __bf16 *a, const __bf16 *gain, float eps, const __bf16 *wg, const __bf16 *wu, __bf16 *y, int M,
                             int F, int K, hipStream_t s) {
-  const pc::few::Choice c = pc::few::choose_tile(ctx->n_cu, M, 2 * F / 16, 2);
+  const pc::few::Choice c = pc::few::choose_tile(ctx->n_cu, M, 2 * F / 16, 2, true);
   const int n_wt = 2 * F / (16 * c.nf), n_tt = (M + 16 * c.nt - 1) / (16 * c.nt);
 #define PC_FEW(NF, NT)                                                                                                    \
   if (c.nf == NF && c.nt == NT)                                                                                           \
   hipLaunchKernelGGL((swiglu_few_kernel<NF, NT>), dim3(pc::few::grid_of(n_wt, n_tt)), dim3(64 * pc::few::Form<NF, NT>::WV), 0, s, a, gain, eps, \
                      wg, wu, y, M, F, K, n_wt, n_tt)
-  PC_FEW(2, 1); else PC_FEW(2, 2); else PC_FEW(2, 3); else PC_FEW(2, 4); else PC_FEW(4, 3); else PC_FEW(4, 4);
+  PC_FEW(2, 1); else PC_FEW(2, 2); else PC_FEW(2, 3); else PC_FEW(2, 4); else PC_FEW(3, 4); else PC_FEW(4, 3); else PC_FEW(4, 4);
 #undef PC_FEW
   PC_HIP(ctx, hipGetLastError());
   return PC_OK;

@@ -200,15 +200,17 @@ inline unsigned grid_of(int n_wt, int n_tt) { return (unsigned)((n_wt + 7) / 8 *
 // smallest NF.  The candidates are the tiles the kernels are instantiated for; a tie takes the first.  48-row token tiles save the
 // padding of the 64-row ones at 65 to 96 rows and their like (layer of width 3072 with head norms, 80 rows: 125 us with 64-row tiles,
 // 112 with these); beyond 256 rows there is little of it and they read the weights more often (width 896, 400 rows: 77 | 86).
+// three: 48 weight rows x 64 token rows too (24 features of gate and up).  Where 64 weight rows leave CUs without a workgroup these fill them with 7/8
+// of the bytes each: gate and up of ffn 3072 at 65 to 128 rows, 192 workgroups | 256: 28 layers of width 1024 over 128 rows 1541 | 1525 us.
 struct Choice {
   int nf, nt;
   long cost;
 };
-inline Choice choose_tile(int n_cu, int M, int n16, int min_nf) {
-  static const Choice cand[] = {{1, 1, 0}, {1, 2, 0}, {2, 1, 0}, {2, 2, 0}, {2, 3, 0}, {2, 4, 0}, {4, 3, 0}, {4, 4, 0}};
+inline Choice choose_tile(int n_cu, int M, int n16, int min_nf, bool three = false) {
+  static const Choice cand[] = {{1, 1, 0}, {1, 2, 0}, {2, 1, 0}, {2, 2, 0}, {2, 3, 0}, {2, 4, 0}, {3, 4, 0}, {4, 3, 0}, {4, 4, 0}};
   Choice best{0, 0, 0};
   for (const Choice &c : cand) {
-    if (c.nf < min_nf || n16 % c.nf || (c.nt == 3 && M > 256)) continue;
+    if (c.nf < min_nf || n16 % c.nf || (c.nf == 3 && !three) || (c.nt == 3 && M > 256)) continue;
     const long tiles = (long)(n16 / c.nf) * ((M + 16 * c.nt - 1) / (16 * c.nt));
     const long cost = (tiles + n_cu - 1) / n_cu * (c.nf + c.nt);
     if (!best.nf || cost < best.cost) best = Choice{c.nf, c.nt, cost};
@@ -226,7 +228,7 @@ inline bool pays(int n_cu, long M, int n16, int min_nf, long max_cost) { return 
 template <int NF, int NT>
 struct Form {
   static constexpr int WV = (NF == 1 || (NF == 2 && NT == 2)) ? 8 : 4;
-  static constexpr int NSTG = NF == 1 && NT == 1 ? 2 : NF == 1 ? 3 : (NF == 2 && NT == 2) || NF >= 4 ? 2 : 3;
+  static constexpr int NSTG = NF == 1 && NT == 1 ? 2 : NF == 1 ? 3 : (NF == 2 && NT == 2) || NF >= 3 ? 2 : 3;
 };
 
 }  // namespace few

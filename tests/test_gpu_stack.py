@@ -343,6 +343,13 @@ def test_token_tiles_of_48_rows(D, heads, H, F, batch, t_fresh, which):
     test_few_token_row_tiles(D, heads, H, F, batch, t_fresh, which)
 
 
+@pytest.mark.parametrize("H,F,batch,t_fresh", [(128, 3072, 1, 65), (256, 3072, 2, 64), (384, 1536, 1, 250), (128, 6144, 3, 41)])
+def test_gate_up_tiles_of_24_features(H, F, batch, t_fresh):
+    """48 weight rows x 64 token rows in gate / up: one token row past a tile, whole tiles of several queries, four token tiles with a ragged
+    last one, two rounds of workgroups."""
+    test_few_token_row_tiles(64, (4, 2), H, F, batch, t_fresh, "none")
+
+
 def test_decoding_step_of_many_queries():
     """520 queries decode at once: the sums of a QKV projection of 5120 features would take three rounds, so q, k and v come
     finished from the large tiles, and an append launch takes the new K/V (more slots than one of its lists holds)."""
