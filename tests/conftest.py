@@ -1,3 +1,4 @@
+import gc
 import os
 import sys
 
@@ -25,3 +26,10 @@ def pytest_collection_modifyitems(config, items):
     for item in items:
         if "gpu" in item.keywords:
             item.add_marker(skip)
+
+
+@pytest.fixture(autouse=True, scope="module")
+def no_garbage_of_other_modules():
+    # Caught exceptions keep their frames, and these their tensors, until a collection; one amid a test that compares amounts of memory shows as
+    # memory that the call under test gave back.
+    gc.collect()

@@ -449,7 +449,7 @@ def test_timing_of_a_projection_covers_its_head_norm():
     layer = dev_layers([wl.stack_weights(27, 0, H, Hq, Hkv, D, F)])[0]
     normed = dict(layer, q_norm=torch.ones(D, dtype=torch.bfloat16, device=DEV), k_norm=torch.ones(D, dtype=torch.bfloat16, device=DEV))
     x, ms = torch.randn((1, T, H), device=DEV).bfloat16(), []
-    for w in (layer, normed, layer, normed):          # (the first round warms up)
+    for w in (layer, normed) * 4:                     # (the first round warms up)
         pc.percache_profile_enable(True, kernels=[1])
         for _ in range(8):
             pc.percache_stack_reuse([w] * L, F, EPS, x)
@@ -457,6 +457,7 @@ def test_timing_of_a_projection_covers_its_head_norm():
         pc.percache_profile_enable(False)
         assert n == 8 * L
         ms.append(t / n)
-    # 10 us against 9 for the sums and 5 for the rest
-    assert ms[3] > 1.2 * ms[2], ms
+    # 10 us against 9 for the sums and 5 for the rest, 3 more between the events: 12.3 | 15.6; the least of three rounds, because one that the host
+    # interrupts comes out as 14 against 15.6
+    assert min(ms[3::2]) > 1.2 * min(ms[2::2]), ms
     pc.close()
