@@ -1591,7 +1591,8 @@ pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStre
 }
 
 
-// What a call of n_probes needs at least: a sorted list per workgroup and probe.
+// What a call of n_probes needs at least: eight rows a workgroup and probe, of which a call for the best row uses one.  A top-k call that is given no
+// more than this keeps the groups of as many probes as fit and takes its probes in several turns.
 size_t list_bytes(const percache_ctx *ctx, int32_t n_probes) {
   size_t lists = (size_t)max_stream_grid(ctx) * kPassProbes;
   if (n_probes > kBatchedFrom) {

@@ -216,8 +216,7 @@ inline int table_formats(const std::vector<int32_t> &rows, int stride, int batch
 }
 
 // Cuts the dense tensors [batch][Hkv][seq_len][D] at the token bounds (the same for every query) and stores piece j of query b
-// in slot slots[b * n_pieces + j] (negative: skipped), one launch per 64 pieces and slot format (no validation, no slot-table
-// update).
+// in slot slots[b * n_pieces + j] (negative: skipped), one launch per 64 pieces (no validation, no slot-table update).
 pc_status launch_kv_slices(percache_ctx *ctx, int layer, const int32_t *slots, const int32_t *bounds, int n_pieces, int batch, const __bf16 *k,
                            const __bf16 *v, int seq_len, hipStream_t stream);
 
