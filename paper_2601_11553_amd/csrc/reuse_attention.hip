@@ -72,6 +72,31 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(unsigned w0, unsigned w1, float 
   return u.v;
 }
 
+// A lane's part of one partition's output for row prow, normalised: in fp32 or (a rounding more, half the bytes of the merge) in bf16; which of them is
+// choose_partitions' matter.
+template <int D>
+__device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], float inv, void *part_o, bool f32, size_t prow, int g2) {
+  if (f32) {
+    float *po = (float *)part_o + prow * D;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4)
+        *(pc::f32x4 *)(po + db * 32 + q4 * 8 + g2 * 4) =
+            pc::f32x4{o_acc[db][q4 * 4 + 0] * inv, o_acc[db][q4 * 4 + 1] * inv, o_acc[db][q4 * 4 + 2] * inv, o_acc[db][q4 * 4 + 3] * inv};
+  } else {
+    __bf16 *po = (__bf16 *)part_o + prow * D;
+#pragma unroll
+    for (int db = 0; db < D / 32; ++db)
+#pragma unroll
+      for (int q4 = 0; q4 < 4; ++q4) {
+        pc::bf16x4 v = {(__bf16)(o_acc[db][q4 * 4 + 0] * inv), (__bf16)(o_acc[db][q4 * 4 + 1] * inv),
+                        (__bf16)(o_acc[db][q4 * 4 + 2] * inv), (__bf16)(o_acc[db][q4 * 4 + 3] * inv)};
+        *(pc::bf16x4 *)(po + db * 32 + q4 * 8 + g2 * 4) = v;
+      }
+  }
+}
+
 // NW wavefronts per workgroup (32 query rows each), NSTAGE LDS stages of one K tile + one V block.
 // KV8: the store holds 8-bit slots (E4M3 codes, one power-of-two scale per kv head and 64-token block; layouts in
 // kvstore.hip).  Such a tile takes half a stage; a lane's 16-byte LDS read then carries the operands of two
@@ -88,7 +113,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
     const float *__restrict__ v_scale, const __bf16 *__restrict__ k_store16, const __bf16 *__restrict__ v_store16, int n_slots16,
     const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
   static_assert(!KV8 || NSTAGE == 2, "8-bit slots: two stages (the waits assume one tile in flight)");
   const __bf16 *k_store = (const __bf16 *)k_store_any, *v_store = (const __bf16 *)v_store_any;
   const uint8_t *k8_store = (const uint8_t *)k_store_any, *v8_store = (const uint8_t *)v_store_any;
@@ -570,17 +595,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    // partial outputs are normalised per split and kept in bf16: they are convex combinations of V rows, and the
-    // merge weights them in fp32, so this costs one extra bf16 rounding and halves the merge traffic
-    __bf16 *po = part_o + prow * D;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        pc::bf16x4 v = {(__bf16)(o_acc[db][q4 * 4 + 0] * inv), (__bf16)(o_acc[db][q4 * 4 + 1] * inv),
-                        (__bf16)(o_acc[db][q4 * 4 + 2] * inv), (__bf16)(o_acc[db][q4 * 4 + 3] * inv)};
-        *(pc::bf16x4 *)(po + db * 32 + q4 * 8 + g2 * 4) = v;
-      }
+    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -616,7 +631,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const __bf16 *__restrict__ k_store, const __bf16 *__restrict__ v_store, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NLD = 4, NSTAGE = PAIR ? 4 : 3, KS = D / 16, DB = D / 32, QROWS = PAIR ? 128 : 256;
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
@@ -991,15 +1006,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    __bf16 *po = part_o + prow * D;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        pc::bf16x4 v = {(__bf16)(o_acc[db][q4 * 4 + 0] * inv), (__bf16)(o_acc[db][q4 * 4 + 1] * inv),
-                        (__bf16)(o_acc[db][q4 * 4 + 2] * inv), (__bf16)(o_acc[db][q4 * 4 + 3] * inv)};
-        *(pc::bf16x4 *)(po + db * 32 + q4 * 8 + g2 * 4) = v;
-      }
+    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -1022,7 +1029,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
     const uint8_t *__restrict__ k_store, const uint8_t *__restrict__ v_store, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NW = 8, NLD = 4, KS = D / 16, DB = D / 32, QROWS = 32 * NW;
   constexpr int K8_ROW = D, V8_ROW = TK, K8_BYTES = TK * K8_ROW, V8_BYTES = D * V8_ROW, CST = K8_BYTES + V8_BYTES, NCST = 3;
@@ -1427,15 +1434,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    __bf16 *po = part_o + prow * D;
-#pragma unroll
-    for (int db = 0; db < DB; ++db)
-#pragma unroll
-      for (int q4 = 0; q4 < 4; ++q4) {
-        pc::bf16x4 v = {(__bf16)(o_acc[db][q4 * 4 + 0] * inv), (__bf16)(o_acc[db][q4 * 4 + 1] * inv),
-                        (__bf16)(o_acc[db][q4 * 4 + 2] * inv), (__bf16)(o_acc[db][q4 * 4 + 3] * inv)};
-        *(pc::bf16x4 *)(po + db * 32 + q4 * 8 + g2 * 4) = v;
-      }
+    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -1448,7 +1447,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
 // s = sg, sg + 4, ..., and the four partial sums meet through lane shuffles.
 // FEW (at most four partitions): one lane per 16 output bytes takes all of them, four independent loads in flight,
 // and adds them up in the order the shuffles would, (0 + 1) + (2 + 3), so both forms give the same bits.
-// P: type of the partials (fp32 behind decode_attention_kernel, bf16 behind the others).
+// P: type of the partials (fp32 behind decode_attention_kernel; behind the others see choose_partitions).
 template <int D, bool FEW, class P>
 __global__ __launch_bounds__(256) void splitkv_combine_kernel(const P *__restrict__ part_o,
                                                               const float *__restrict__ part_ml, int n_splits, int T,
@@ -1588,13 +1587,21 @@ struct TilePace {
 // Partitions of the key axis of a launch of n_bg kv heads (of all queries) x q_tiles blocks, by an estimate of its time:
 //   a workgroup's tiles, one after the other; two workgroups on a CU slow each other down, more go in rounds (a kv head's partition stays on an XCD,
 //   so it is the fullest XCD that counts); then the merge's launch and its bytes, written and read.
-// Drawn from 160 launches, 1 to 8 queries, head sizes 64 and 128, bf16, 8-bit and mixed slots, 7 to 257 tiles, each at up to 14 partition counts: the
-// estimate's choice takes 0.1 % more than the best count on average, 3 % at most.  The rule before it (choose_splits) filled two workgroups a CU where
-// the kernel allows two and kept four tiles a partition.  76 other launches against it: 1.087 times as fast on average, 0.973 to 1.77.
-// us a projection of 512 columns and attention, before | now: 16 heads over
-// 8, 100 rows over 36 tiles 27.0 | 23.2, 235 rows over 32 30.0 | 26.7, 55 over 6, mixed slots 26.2 | 18.2; 24 over 8, 2 x 74 rows over 40 31.3 | 28.8; 14 over 2
-// of 64, 42 rows over 20, 8-bit slots 21.2 | 15.8; 28 over 4, 3 x 256 rows over 16 59.7 | 44.1 (252 workgroups, but 35 on the fullest XCD).
-static int choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_tiles, int tiles, double merge_us, int cap) {
+// Drawn from 160 launches, 1 to 8 queries, head sizes 64 and 128, bf16, 8-bit and mixed slots, 7 to 257 tiles, each at up to 14 partition counts.  The rule
+// before it (choose_splits) filled two workgroups a CU where the kernel allows two and kept four tiles a partition.
+// Partials in bf16 are a rounding more, which weighs the less the more of them there are: against 64 bits, attention in one partition errs by 2.3e-3, in
+// 2 or 3 by 2.85e-3, in 16 by 2.7e-3.  So no count takes bf16 partials where choose_splits needed none or more of them: they are fp32 there (2.3e-3), at
+// twice the bytes, and as many as the workspace of the bf16 ones holds.
+// 76 launches against choose_splits: 1.074 times as fast on average (1.078 with bf16 partials everywhere).  us a call of attention alone, its count | this
+// one: 16 heads over 8, 55 rows over 6 tiles, mixed slots 24.5 | 18.0, 116 over 14 of 8 bits 23.2 | 20.0; 28 over 4, 8 rows over 29 tiles 21.3 | 16.2, 3 x 256
+// over 20 52.5 | 41.2 (bf16 38.4; choose_splits' 252 workgroups are 35 on the fullest XCD), 220 over 44 43.4 | 34.8 (33.2); 14 over 2 of 64, 25 over 9, 8 bits 19.8 | 16.0.
+struct Partitions {
+  int n;
+  bool f32;
+};
+static Partitions choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_tiles, int tiles, double merge_us, int cap) {
+  const int least_bf16 = choose_splits(pace.second == 0 ? n_cu : 2 * n_cu, n_bg * q_tiles, tiles, cap);
+  auto in_f32 = [&](int ns) { return ns > 1 && (least_bf16 == 1 || ns < least_bf16); };
   auto estimate = [&](int ns) {
     const long wgs = (n_bg * ns + 7) / 8 * 8 * q_tiles;
     double t;
@@ -1605,20 +1612,21 @@ static int choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_ti
       const long rounds = wgs / (2 * n_cu), rest = wgs % (2 * n_cu);
       t = rounds * two + (rest == 0 ? 0.0 : rest <= n_cu ? one : two) + (wgs > 2 * n_cu ? 3.0 : 0.0);
     }
-    if (ns > 1) t += (ns <= 4 ? 2.2 : ns <= 16 ? 3.3 : 4.5) + merge_us * ns;   // (how many partials a lane of the merge has in flight)
+    if (ns > 1) t += (ns <= 4 ? 2.2 : ns <= 16 ? 3.3 : 4.5) + merge_us * ns * (in_f32(ns) ? 2 : 1);   // (how many partials a lane of the merge has in flight)
     return t;
   };
   // (the count of the rule before it unless another one promises more than the estimate errs by)
-  int best = choose_splits(pace.second == 0 ? n_cu : 2 * n_cu, n_bg * q_tiles, tiles, cap);
+  int best = least_bf16;
   double least = estimate(best) - 0.7;
   for (int ns = 1; ns <= cap && ns <= tiles; ++ns) {
+    if (in_f32(ns) && 2 * ns > cap) continue;
     const double t = estimate(ns);
     if (t < least - 1e-9) {
       least = t;
       best = ns;
     }
   }
-  return best;
+  return {best, in_f32(best)};
 }
 
 pc_status launch_v_repack(percache_ctx *ctx, const __bf16 *vf, __bf16 *vf_blk, int batch, int t_fresh, hipStream_t stream) {
@@ -1693,7 +1701,8 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     if (left_splits) *left_splits = left ? n_splits : 1;
     return n_splits > 1 && !left ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
-  __bf16 *part_o = (__bf16 *)part_dev;
+  void *const part_o = part_dev;
+  bool part_f32 = false;   // (a count that the caller asked for: bf16)
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
   // variant that tells the formats apart tile by tile only when it names chunks of both formats
   const bool use8 = (formats & 1) && ctx->n_slots8 > 0;
@@ -1722,8 +1731,10 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     const TilePace pace = wide ? TilePace{!d128 ? 1.0 : mixed ? 3.0 : use8 ? 2.0 : 1.8, 0}
                           : halved ? TilePace{0.79, 1.58}
                           : d128 ? (use8 ? TilePace{1.17, 1.12} : TilePace{1.16, 1.51}) : use8 ? TilePace{1.12, 1.05} : TilePace{0.68, 1.07};
-    const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's partials, written and read at 5.4 TB/s
-    n_splits = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, merge_us, cap);
+    const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's bf16 partials, written and read at 5.4 TB/s
+    const Partitions parts = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, merge_us, cap);
+    n_splits = parts.n;
+    part_f32 = parts.f32;
   }
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;
@@ -1747,10 +1758,10 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
 #define PC_ATTN(DD, NWW, NS, ...)                                                                                     \
   hipLaunchKernelGGL((reuse_attention_kernel<DD, NWW, NS, ##__VA_ARGS__>), grid, dim3(64 * NWW), 0, stream, q, kf,     \
                      vf_blk, ks, vs, ksc, vsc, k16, v16, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, \
-                     c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
+                     c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml)
 #define PC_WIDE_P(DD, PP)                                                                                                       \
   hipLaunchKernelGGL((reuse_attention_wide_kernel<DD, PP>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev, tbl_stride, \
-                     t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
+                     t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml)
 #define PC_WIDE(DD) do { if (pair) PC_WIDE_P(DD, true); else PC_WIDE_P(DD, false); } while (0)
   if (use8 && mixed) {
     if (c.head_dim == 128) {
@@ -1761,7 +1772,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   } else if (use8 && c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64 && c.slot_capacity / TK <= 32) {
     hipLaunchKernelGGL((reuse_attention_wide8_kernel<128>), grid, dim3(512), 0, stream, q, kf, vf_blk, (const uint8_t *)ks,
                        (const uint8_t *)vs, ksc, vsc, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads,
-                       c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml);
+                       c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml);
   } else if (use8) {
     if (c.head_dim == 128) {
       if (wide) PC_ATTN(128, 8, 2, true); else PC_ATTN(128, 4, 2, true);
@@ -1782,7 +1793,9 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
 #undef PC_ATTN
   prof_end(ctx, PC_KERNEL_ATTENTION, stream);
   PC_HIP(ctx, hipGetLastError());
-  return n_splits > 1 ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
+  if (n_splits == 1) return PC_OK;
+  return part_f32 ? launch_combine(ctx, (const float *)part_o, part_ml, n_splits, batch, t_fresh, out, stream)
+                  : launch_combine(ctx, (const __bf16 *)part_o, part_ml, n_splits, batch, t_fresh, out, stream);
 }
 
 }  // namespace pc

@@ -278,6 +278,41 @@ def test_partition_counts_chosen_by_the_library(t_fresh, Hq, Hkv, D, batch, n_ch
     pc.close()
 
 
+# (fresh rows, heads, kv heads, head size, queries, chunks, chunk tokens, 8-bit slots, count): counts that two workgroups a CU and four tiles a partition
+# call for on 256 CUs; the library's own counts there are 4, 9, 4, 2 | 2, 4, 4 | 12
+@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch,n_chunks,C,n8,count", [
+    (55, 16, 8, 128, 1, 5, 64, 3, 1), (27, 14, 2, 64, 1, 4, 128, 4, 1), (41, 24, 8, 128, 2, 6, 64, 12, 1), (60, 16, 8, 128, 3, 5, 64, 15, 1),
+    (256, 28, 4, 128, 3, 2, 512, 0, 3), (220, 28, 4, 128, 1, 5, 512, 0, 9), (111, 24, 8, 128, 1, 6, 1024, 0, 21), (64, 16, 8, 128, 1, 4, 512, 0, 8)])
+def test_partition_counts_keep_the_precision(t_fresh, Hq, Hkv, D, batch, n_chunks, C, n8, count):
+    """The library's own count against 64 bits: no further off than attention in ``count`` partitions (bf16 partials: a rounding more than one partition
+    has, a fifth of its error).  Squares over n = 2.4e4 to 2.8e6
+    values, rounded anew: where the arithmetic is the same (the last case, 1.3e5 of them) they agree to about sqrt(2 / n) = 0.4 %, bound three times that."""
+    S = batch * n_chunks
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=S, slot_capacity=C, max_pos=t_fresh + C * n_chunks, n_slots_8bit=n8,
+                  device=DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(t_fresh + D)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    for s in range(S):
+        pc.percache_kv_put(0, s, rnd(Hkv, C, D), rnd(Hkv, C, D))
+    q, kf, vf = rnd(batch, Hq, t_fresh, D), rnd(batch, Hkv, t_fresh, D), rnd(batch, Hkv, t_fresh, D)
+    ids = np.arange(S, dtype=np.int32).reshape(batch, n_chunks)
+    outs = [pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=n).view(batch, t_fresh, Hq, D).double() for n in (0, count)]
+    err = [0.0, 0.0]
+    for b in range(batch):
+        kv = [pc.percache_kv_get(0, int(s)) for s in ids[b]]
+        K, V = (torch.cat([c[i].double() for c in kv] + [f[b].double()], 1) for i, f in ((0, kf), (1, vf)))
+        later = torch.arange(K.shape[1], device=DEV)[None] > K.shape[1] - t_fresh + torch.arange(t_fresh, device=DEV)[:, None]
+        for h in range(Hq):
+            scores = (q[b, h].double() @ K[h // (Hq // Hkv)].t() / D ** 0.5).masked_fill(later, float("-inf"))
+            ref = torch.softmax(scores, -1) @ V[h // (Hq // Hkv)]
+            for i, o in enumerate(outs):
+                err[i] += (o[b, :, h] - ref).pow(2).sum().item()
+    pc.close()
+    print(f"root mean square error: own {(err[0] / outs[0].numel()) ** 0.5:.3e}, {count} partitions {(err[1] / outs[0].numel()) ** 0.5:.3e}", flush=True)
+    assert err[0] <= 1.012 * err[1]   # (squares)
+
+
 @pytest.mark.parametrize("n_splits", [0, 1, 5])
 def test_long_chunk_lists(n_splits):
     """70 and 64 short chunks per query (the kernel keeps the first 64 list entries in registers and reads the
