@@ -675,7 +675,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   __shared__ uint2 cand_more[kCandidates];   // group, ordered second
   __shared__ unsigned long long sel[kMaxTopK];
   __shared__ uint2 sel_more[kMaxTopK];
-  __shared__ int bin_rank[64], n_cand;
+  __shared__ int bin_rank[64], n_cand, n_rows;   // (a count of their own for the rows: a late wavefront may still be reading the groups')
   __shared__ float norm_part[4];
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const Group *const groups = gm.g + (size_t)p * gm.pitch;
@@ -694,7 +694,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     if (i * kSelectThreads + tid < gm.n) held[i] = group_at(i * kSelectThreads + tid);
   }
   if (tid < 64) bin_rank[tid] = 0;
-  if (tid == 0) n_cand = 0;
+  if (tid == 0) n_cand = n_rows = 0;
   const float inv = inverse_norm(probe_squares(probe, d, tid), tid, norm_part);
   unsigned best = 0;
 #pragma unroll
@@ -807,10 +807,9 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
 #pragma unroll
     for (int h = 0; h < 2; ++h)
       if (rank[h] < k) cand[rank[h]] = key[h];
-    if (tid == 0) n_cand = min(n, k);
+    if (tid == 0) n_rows = min(n, k);
     __syncthreads();
   };
-  if (tid == 0) n_cand = 0;
   __syncthreads();
   const unsigned kth = n == k ? (unsigned)(sel[k - 1] >> 32) : 1u;   // (fewer groups than rows asked for: every row that is a number)
   bool doubt = n < k;
@@ -823,14 +822,14 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     return;
   }
   const int best_groups = n, per = gm.jobs(), l32 = lane & 31, g2 = lane >> 5, r16 = lane & 15, g = lane >> 4;
-  if (tid < best_groups && sel_more[tid].y < kth) cand[atomicAdd(&n_cand, 1)] = sel[tid];
+  if (tid < best_groups && sel_more[tid].y < kth) cand[atomicAdd(&n_rows, 1)] = sel[tid];
   int doubted = 0;
   for (int s = 0; s < best_groups; ++s) doubted += sel_more[s].y >= kth;
   __syncthreads();
   const u32x4 *const b = (const u32x4 *)probe;
   auto offer_row = [&](float v, int row) __attribute__((always_inline)) {
     const unsigned o = row < N ? ordered(v) : 0u;
-    if (o >= kth) cand[atomicAdd(&n_cand, 1)] = key_of(o, row);
+    if (o >= kth) cand[atomicAdd(&n_rows, 1)] = key_of(o, row);
   };
   for (int job0 = 0; job0 < doubted * per; job0 += WAVES) {
     const int job = job0 + wave;
@@ -891,12 +890,12 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     }
     __syncthreads();
     static_assert(kCandidates == 2 * kSelectThreads && kCandidates >= 2 * 32 * WAVES, "two a thread; a round of jobs has room behind the k best");
-    if (n_cand > kCandidates - 32 * WAVES) {
-      keep_best(n_cand);
+    if (n_rows > kCandidates - 32 * WAVES) {
+      keep_best(n_rows);
       __syncthreads();
     }
   }
-  n = n_cand;
+  n = n_rows;
   keep_best(n);
   if (tid < k) {   // (perhaps fewer rows than asked for)
     idx_out[(size_t)p * k + tid] = tid < n ? row_of(cand[tid]) : -1;

@@ -327,6 +327,30 @@ def test_topk_groups(rows, dim, n_probes, k):
     pc.close()
 
 
+@pytest.mark.parametrize("rows,dim,n_probes", [(70001, 128, 16), (70001, 512, 40), (70001, 512, 128), (20011, 64, 300), (3001, 64, 200)])
+@pytest.mark.parametrize("copies", [9, 65, 300, 1000])
+def test_topk_many_equal_groups(rows, dim, n_probes, copies):
+    """Copies of a row in as many groups or nearly so: more candidates than a wavefront ranks, up to nearly as many as there is room for.  The lowest rows,
+    for a probe that is the row, for one near it and, of all rows, for a zero probe."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + copies)
+    bank = torch.randn((rows, dim), generator=g, device=DEV).half()
+    probes = torch.randn((n_probes, dim), generator=g, device=DEV).half()
+    at = torch.unique((torch.arange(copies, device=DEV) * (rows - 40) // copies) + 3)
+    bank[at] = bank[3].clone()
+    near = [i for i in range(0, n_probes, 3)]
+    probes[near] = bank[3].clone()
+    probes[near[1:]] += (0.02 * torch.randn((len(near) - 1, dim), generator=g, device=DEV)).half()
+    probes[1] = 0
+    pc = _ctx(rows, dim)
+    pc.percache_bank_put(0, bank)
+    idx, sim = pc.percache_lookup_topk(probes, 8)
+    torch.cuda.synchronize()
+    assert (idx[near] == at[:8][None]).all() and (sim[near] == sim[near][:, :1]).all()
+    assert idx[1].tolist() == list(range(8)) and (sim[1] == 0).all()
+    pc.close()
+
+
 # from 32 768 rows on (256 CUs) 33 to 64 probes take blocks of two sets of 32 rows; the last block without a second set, with one row of it, whole
 @pytest.mark.parametrize("rows,dim,n_probes", [(32768, 512, 33), (32769, 1024, 64), (32801, 768, 64), (49152, 512, 40), (33000, 384, 50)])
 def test_two_sets_of_rows_a_block(rows, dim, n_probes):
