@@ -890,9 +890,10 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     }
     __syncthreads();
     static_assert(kCandidates == 2 * kSelectThreads && kCandidates >= 2 * 32 * WAVES, "two a thread; a round of jobs has room behind the k best");
-    if (n_rows > kCandidates - 32 * WAVES) {
-      keep_best(n_rows);
-      __syncthreads();
+    if (job0 + WAVES < doubted * per) {   // (another round)
+      const int have = n_rows;
+      __syncthreads();   // (nobody adds to it before all have read it)
+      if (have > kCandidates - 32 * WAVES) keep_best(have);
     }
   }
   n = n_rows;

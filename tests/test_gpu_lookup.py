@@ -351,6 +351,28 @@ def test_topk_many_equal_groups(rows, dim, n_probes, copies):
     pc.close()
 
 
+# groups of 128 rows and more of each kind: the k groups in doubt hold more rows than there is room for, so the best are kept in between
+@pytest.mark.parametrize("rows,dim,n_probes", [(530001, 64, 20), (225001, 512, 64), (225001, 512, 100), (200001, 64, 512), (16384, 64, 129)])
+def test_topk_more_equal_rows_than_room(rows, dim, n_probes):
+    """All rows alike but the first and one in the middle: the lowest ones, for the row itself, its opposite (the two other rows first) and a zero probe."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows)
+    bank = torch.randn((1, dim), generator=g, device=DEV).half().repeat(rows, 1)
+    bank[0], bank[rows // 2] = -bank[1], -bank[1]
+    probes = bank[1:2].repeat(n_probes, 1)
+    probes[2::3] = -bank[1]
+    probes[1] = 0
+    pc = _ctx(rows, dim)
+    pc.percache_bank_put(0, bank)
+    idx, _ = pc.percache_lookup_topk(probes, 8)
+    torch.cuda.synchronize()
+    want = torch.arange(1, 9, dtype=torch.int32, device=DEV).repeat(n_probes, 1)
+    want[2::3] = torch.tensor([0, rows // 2, 1, 2, 3, 4, 5, 6], dtype=torch.int32, device=DEV)
+    want[1] = torch.arange(8, dtype=torch.int32, device=DEV)
+    assert torch.equal(idx, want)
+    pc.close()
+
+
 # from 32 768 rows on (256 CUs) 33 to 64 probes take blocks of two sets of 32 rows; the last block without a second set, with one row of it, whole
 @pytest.mark.parametrize("rows,dim,n_probes", [(32768, 512, 33), (32769, 1024, 64), (32801, 768, 64), (49152, 512, 40), (33000, 384, 50)])
 def test_two_sets_of_rows_a_block(rows, dim, n_probes):
