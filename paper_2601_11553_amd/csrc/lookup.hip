@@ -104,6 +104,15 @@ __device__ __forceinline__ void lds_barrier() {   // (not __syncthreads, which w
   asm volatile("" ::: "memory");
 }
 
+// The value of lane ^ 1 and lane ^ 2; of the mirrored lane of eight and of sixteen, which stands for the other quad and the other eight lanes where the
+// lanes of a quad (of eight) agree.  Register moves: a shuffle goes through LDS.
+template <int CTRL>
+__device__ __forceinline__ float dpp(float v) { return __int_as_float(__builtin_amdgcn_mov_dpp(__float_as_int(v), CTRL, 0xf, 0xf, true)); }
+__device__ __forceinline__ float lane_xor1(float v) { return dpp<0xb1>(v); }              // quad_perm [1,0,3,2]
+__device__ __forceinline__ float lane_xor2(float v) { return dpp<0x4e>(v); }              // quad_perm [2,3,0,1]
+__device__ __forceinline__ float lane_other_quad(float v) { return dpp<0x141>(v); }       // row_half_mirror
+__device__ __forceinline__ float lane_other_eight(float v) { return dpp<0x140>(v); }      // row_mirror
+
 template <int CHB>
 __device__ __forceinline__ int row_swz(int row) { return CHB >= 256 ? (row & 15) : ((row >> 1) & 7); }
 
@@ -432,23 +441,32 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
     }
   }
   // per-row mode: the product is taken the other way round (probes on the M side), so a lane holds ONE row (r16) and
-  // the probes pb*16 + 4g + 0..3; their inverse norms (a padding probe's is a NaN, which no comparison picks).  Sixteen (eight) lanes add up
-  // a probe's squares, from LDS while the ring's first stages are on their way; the norms go to the rows' padding.
+  // the probes pb*16 + 4g + 0..3; their inverse norms (a padding probe's is a NaN, which no comparison picks), added up from LDS while the ring's
+  // first stages are on their way; the norms go to the rows' padding.  A probe's squares are sixteen sums, of every sixteenth 16 bytes, in a
+  // pass of 32 (eight lanes of two sums) as in one of 16 (sixteen lanes): equal embeddings of a call have equal norms whichever pass they are in.
   float pinv[NPB][4];
   if constexpr (K == 0) {
     constexpr int LP = 16 / NPB;
     const int p = tid / LP;
-    {
-      float ss = 0.f;
-      for (int v = tid % LP; v < vec_per_row; v += LP) {
+    float ss[NPB] = {};
+    for (int v0 = tid % LP; v0 < vec_per_row; v0 += 16) {
+#pragma unroll
+      for (int j = 0; j < NPB; ++j) {
+        const int v = v0 + j * LP;
+        if (j > 0 && v >= vec_per_row) continue;   // (rows are whole multiples of 128 bytes)
         const f16x8 h = *(const f16x8 *)(smem + (size_t)p * row_bytes + v * 16);
 #pragma unroll
-        for (int e = 0; e < 8; ++e) ss += (float)h[e] * (float)h[e];
+        for (int e = 0; e < 8; ++e) ss[j] += (float)h[e] * (float)h[e];
       }
-#pragma unroll
-      for (int o = 1; o < LP; o <<= 1) ss += __shfl_xor(ss, o, 64);
-      if (tid % LP == 0) lds_put(smem + (size_t)p * row_bytes + d * 2, p >= n_probes ? __builtin_nanf("") : ss > 0.f ? 1.0f / sqrtf(ss) : 0.f);
     }
+#pragma unroll
+    for (int j = 0; j < NPB; ++j) {
+      ss[j] += lane_xor1(ss[j]);
+      ss[j] += lane_xor2(ss[j]);
+      ss[j] += lane_other_quad(ss[j]);
+    }
+    const float tot = NPB == 1 ? ss[0] + lane_other_eight(ss[0]) : ss[0] + ss[NPB - 1];
+    if (tid % LP == 0) lds_put(smem + (size_t)p * row_bytes + d * 2, p >= n_probes ? __builtin_nanf("") : tot > 0.f ? 1.0f / sqrtf(tot) : 0.f);
     lds_barrier();
 #pragma unroll
     for (int pb = 0; pb < NPB; ++pb)

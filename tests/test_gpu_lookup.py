@@ -409,6 +409,24 @@ def test_two_sets_of_rows_a_block(rows, dim, n_probes):
     pc.close()
 
 
+@pytest.mark.parametrize("dim,n_first,n_last", [(64, 32, 16), (128, 32, 16), (256, 64, 5), (640, 32, 16), (640, 96, 16), (2048, 16, 16), (384, 128, 16), (1024, 128, 40)])
+def test_refresh_scan_equal_chunks_in_different_passes(dim, n_first, n_last):
+    """The last pass of a call takes fewer new chunks than the others; copies of earlier ones in it have the same similarities, so that the lower index
+    stands."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(dim + n_first)
+    rows = 40
+    pc = _ctx(rows, dim)
+    for _ in range(20):
+        new = torch.randn((n_first + n_last, dim), generator=g, device=DEV)
+        new = (new / new.norm(dim=1, keepdim=True)).half()
+        new[n_first:] = new[:n_last].clone()
+        pc.percache_bank_put(0, new[torch.arange(rows, device=DEV) % n_last].clone())   # (the best new chunk of a row is its copy)
+        best, which, _ = pc.percache_bank_refresh_scan(new, torch.zeros(rows, device=DEV))
+        assert which.tolist() == [r % n_last for r in range(rows)]
+    pc.close()
+
+
 def test_topk_ties_small_bank_and_errors():
     d = 128
     g = np.random.default_rng(12)
