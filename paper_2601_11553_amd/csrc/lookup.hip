@@ -248,18 +248,18 @@ struct RowScan {
 // one of these may hold two of the k rows does it look at rows again.  Sorted lists of eight in every lane, which this replaces, cost ten
 // instructions an entry for nearly every row, because one of a wavefront's 64 lists takes nearly every row in.
 // us a call, 8 best, lists | groups (3 best in brackets): 8 probes, 50 000 rows of width 1024 33.0 | 25.6 (25.9 | 25.3), 200 000 rows 78.9 | 71.6 (71.2 | 71.0),
-// 32 probes 88.9 | 76.6; 64 probes 179 | 78 (175 | 77), 1024 probes 712 | 437 (708 | 432); 2000 rows of width 768, 32 probes 22.3 | 16.2, 1024 probes
-// 43.8 | 43 (39.2 | 41).
-// A group is what one lane or two meet in a stretch of the bank; which rows these are only Groups::row knows.  A workgroup has about four a
+// 32 probes 88.9 | 76.6; 64 probes 179 | 78 (175 | 77), 1024 probes 712 | 437 (708 | 432).
+// Over a few thousand rows every row is a group (see groups_of).
+// A group is what one lane or two meet in a stretch of the bank; which rows these are only Groups::first_row knows.  A workgroup has about four a
 // wavefront: under many probes their bytes count, but over a small bank two of the k best rows would often share a large one.
-constexpr int kGroups = -1;
+constexpr int kGroups = -1, kRows = -2;   // (kRows: lookup_big_kernel where every row is a group)
 struct Group {
   float best, second;   // without the probe's norm; best: a NaN where no row has a similarity that is a number
   int row, unused;
 };
 struct Groups {
-  enum Kind { stream, wide, wide_rows, big, big_fine };
-  Group *g;      // [probes][pitch] (wide_rows: the similarities alone, four to a Group's place)
+  enum Kind { stream, wide, big, big_fine, rows };   // (rows: every row a group)
+  Group *g;      // [probes][pitch] (rows: the similarities alone, four to a Group's place; a last place's rest is not a number)
   int n;         // of a probe
   int pitch;     // an odd number of 128-byte lines: 32 probes' groups go to as many places
   int p0;        // this pass's first probe
@@ -270,17 +270,16 @@ struct Groups {
   int blocks;    // (tiles) of the bank
   int sets;      // wide: sets of 32 rows in a block, a group of its own each
 
-  __device__ float *rows(int p) const { return (float *)(g + (size_t)p * pitch); }
+  __device__ float *of_rows(int p) const { return (float *)(g + (size_t)p * pitch); }
   __host__ Groups from_probe(int p) const {
     Groups o = *this;
     o.p0 += p;
     return o;
   }
   // A group's rows in jobs of 16 (stream) or 32 consecutive ones: how many jobs, the first row of one (negative: none), and whether row i of it counts.
-  __host__ __device__ int jobs() const { return kind == big ? 2 * stretch : kind == big_fine || kind == wide_rows ? 1 : stretch; }
+  __host__ __device__ int jobs() const { return kind == big ? 2 * stretch : kind == big_fine ? 1 : stretch; }
   __host__ __device__ int first_row(int group, int job) const {
     if (kind == big_fine) return (group >> 1) * 32;
-    if (kind == wide_rows) return group / 32 * 32;
     const int j = group % per, w = group / per;   // of wavefront (workgroup) w
     if (kind == stream) {
       const int block = w % 4 + 4 * (j * stretch + job);
@@ -293,7 +292,7 @@ struct Groups {
     const int tile = big_begin(w / 4) + j * stretch + job / 2;
     return tile < big_begin(w / 4 + 1) ? tile * 256 + w % 4 * 64 + job % 2 * 32 : -1;
   }
-  __host__ __device__ bool counts(int group, int i) const { return kind == big_fine ? (i >> 2 & 1) == (group & 1) : kind != wide_rows || i == group % 32; }
+  __host__ __device__ bool counts(int group, int i) const { return kind == big_fine ? (i >> 2 & 1) == (group & 1) : true; }
   __host__ __device__ int big_begin(int wg) const { return (int)((long)wg * blocks / per_wg); }   // a workgroup's first tile
 };
 // The best and the second best of numbers offered in the order of their rows.
@@ -527,8 +526,14 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
         for (int r = 0; r < 4; ++r) {
           const int row = rb * 16 + g * 4 + r;
           v[r] = row < N ? acc[pb][r] * inv4[r] : __builtin_nanf("");
-          top[pb].add(v[r], row);
         }
+        if (gm.kind == Groups::rows) {
+          const int p = pb * 16 + r16, row0 = rb * 16 + g * 4;
+          if (p < n_probes && row0 < N) *(f32x4 *)(gm.of_rows(gm.p0 + p) + row0) = f32x4{v[0], v[1], v[2], v[3]};
+          continue;
+        }
+#pragma unroll
+        for (int r = 0; r < 4; ++r) top[pb].add(v[r], rb * 16 + g * 4 + r);
         if (__ballot(top[pb].i == INT_MAX)) {
           if (top[pb].i == INT_MAX)
 #pragma unroll
@@ -590,7 +595,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
   PC_LOOKUP_WAIT_VMCNT(0);
 
-  if (K == kGroups) {   // groups that this wavefront has no rows for
+  if (K == kGroups && gm.kind != Groups::rows) {   // groups that this wavefront has no rows for
     const int mine = rb_end > rb_begin + wave ? (rb_end - rb_begin - wave + 3) / 4 : 0;
     for (int j = (mine + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
       if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.pitch + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
@@ -672,6 +677,7 @@ __global__ __launch_bounds__(kFinalizeThreads) void lookup_finalize_kernel(const
 // ---------------------------------------------------------------------------------------------------
 constexpr int kMaxTopK = 8;
 constexpr int kSelectThreads = 512, kSelectHeld = 8, kCandidates = 1024;
+constexpr int kRowsUpTo = 8192;   // rows of the bank that may be groups of their own
 // similarities as numbers that rise with them; 0: not a number
 __device__ __forceinline__ unsigned ordered(float v) {
   const unsigned u = __float_as_uint(v + 0.f);   // (-0 becomes 0)
@@ -684,6 +690,7 @@ __device__ __forceinline__ float value_of(unsigned long long key) {   // (-0 com
   const unsigned o = (unsigned)(key >> 32);
   return __uint_as_float(o & 0x80000000u ? o & 0x7fffffffu : ~o);
 }
+template <bool ROWS>
 __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups gm, const _Float16 *__restrict__ bank, const float *__restrict__ inv_norm, int N, int d,
                                                                      const _Float16 *__restrict__ probes, int k, int32_t *__restrict__ idx_out,
                                                                      float *__restrict__ sim_out) {
@@ -698,27 +705,40 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const Group *const groups = gm.g + (size_t)p * gm.pitch;
   const _Float16 *const probe = probes + (size_t)p * d;
-  // the groups: the first kSelectHeld a thread stay in registers
-  const float *const rows = gm.rows(p);
+  // the groups: the first kSelectHeld a thread stay in registers; of rows all do, four of them next to each other
+  const float *const rows = gm.of_rows(p);
   auto group_at = [&](int at) __attribute__((always_inline)) {
-    if (gm.kind != Groups::wide_rows) return groups[at];
-    const float v = rows[at];
-    return Group{v, v == -INFINITY ? INFINITY : -INFINITY, at, 0};
+    if (!ROWS) return groups[at];
+    return Group{rows[at], 0.f, at, 0};
   };
-  Group held[kSelectHeld];
+  constexpr int HELD = ROWS ? kRowsUpTo / kSelectThreads : kSelectHeld;
+  Group held[HELD];
+  auto held_at = [&](int i) __attribute__((always_inline)) { return ROWS ? (i / 4 * kSelectThreads + tid) * 4 + i % 4 : i * kSelectThreads + tid; };
+  if constexpr (ROWS) {
+    static_assert(HELD % 4 == 0 && HELD * kSelectThreads == kRowsUpTo, "all of them");
 #pragma unroll
-  for (int i = 0; i < kSelectHeld; ++i) {
-    held[i].best = __builtin_nanf("");
-    if (i * kSelectThreads + tid < gm.n) held[i] = group_at(i * kSelectThreads + tid);
+    for (int i = 0; i < HELD; i += 4) {
+      f32x4 v;
+      v[0] = v[1] = v[2] = v[3] = __builtin_nanf("");
+      if (held_at(i) < gm.n) v = *(const f32x4 *)(rows + held_at(i));
+#pragma unroll
+      for (int e = 0; e < 4; ++e) held[i + e] = Group{v[e], 0.f, held_at(i + e), 0};
+    }
+  } else {
+#pragma unroll
+    for (int i = 0; i < HELD; ++i) {
+      held[i].best = __builtin_nanf("");
+      if (held_at(i) < gm.n) held[i] = group_at(held_at(i));
+    }
   }
   if (tid < 64) bin_rank[tid] = 0;
   if (tid == 0) n_cand = n_rows = 0;
   const float inv = inverse_norm(probe_squares(probe, d, tid), tid, norm_part);
   unsigned best = 0;
 #pragma unroll
-  for (int i = 0; i < kSelectHeld; ++i) best = max(best, ordered(held[i].best));
+  for (int i = 0; i < HELD; ++i) best = max(best, ordered(held[i].best));
 #pragma unroll 8
-  for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) best = max(best, ordered(group_at(at).best));
+  for (int at = HELD * kSelectThreads + tid; at < gm.n; at += kSelectThreads) best = max(best, ordered(group_at(at).best));
   top[tid] = best;
   __syncthreads();
   // the k-th best of 64 bins; a wavefront compares all of them with eight
@@ -747,8 +767,8 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   };
   if (best >= bound) {
 #pragma unroll
-    for (int i = 0; i < kSelectHeld; ++i) offer(held[i], i * kSelectThreads + tid);
-    for (int at = kSelectHeld * kSelectThreads + tid; at < gm.n; at += kSelectThreads) offer(group_at(at), at);
+    for (int i = 0; i < HELD; ++i) offer(held[i], held_at(i));
+    for (int at = HELD * kSelectThreads + tid; at < gm.n; at += kSelectThreads) offer(group_at(at), at);
   }
   __syncthreads();
   int n = n_cand;
@@ -829,6 +849,13 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     __syncthreads();
   };
   __syncthreads();
+  if constexpr (ROWS) {   // (perhaps fewer rows than asked for)
+    if (tid < k) {
+      idx_out[(size_t)p * k + tid] = tid < n ? row_of(sel[tid]) : -1;
+      sim_out[(size_t)p * k + tid] = tid < n ? value_of(sel[tid]) * inv : -INFINITY;
+    }
+    return;
+  }
   const unsigned kth = n == k ? (unsigned)(sel[k - 1] >> 32) : 1u;   // (fewer groups than rows asked for: every row that is a number)
   bool doubt = n < k;
   for (int j = 0; j < n; ++j) doubt = doubt || sel_more[j].y >= kth;
@@ -892,7 +919,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
           for (int u = 0; u < U; ++u) {
             if (s0 + u >= d / 16) continue;
             const f16x8 x = __builtin_bit_cast(f16x8, av[u]), y = __builtin_bit_cast(f16x8, bv[u]);
-            if ((u & 1) && (gm.kind == Groups::wide || gm.kind == Groups::wide_rows)) acc[1] = pc::gemm::mma(x, y, acc[1]);
+            if ((u & 1) && gm.kind == Groups::wide) acc[1] = pc::gemm::mma(x, y, acc[1]);
             else acc[0] = pc::gemm::mma(x, y, acc[0]);
           }
         }
@@ -900,7 +927,7 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
 #pragma unroll
           for (int r = 0; r < 16; ++r) {
             const int i = (r >> 2) * 8 + g2 * 4 + (r & 3);
-            const float v = gm.kind == Groups::wide || gm.kind == Groups::wide_rows ? acc[0][r] + acc[1][r] : acc[0][r];
+            const float v = gm.kind == Groups::wide ? acc[0][r] + acc[1][r] : acc[0][r];
             if (gm.counts(group, i)) offer_row(v * inv_norm[min(row0 + i, N - 1)], row0 + i);
           }
         }
@@ -1147,6 +1174,23 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
         best[t].s[0] = up ? ls[t] : best[t].s[0];
         best[t].i[0] = up ? row : best[t].i[0];
       }
+    } else if constexpr (K == kRows) {
+#pragma unroll
+      for (int a = 0; a < NA; ++a)
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int in = a * 32 + q4 * 8 + g * 4, row = r0 + NA * wa * 32 + in;
+          float inv[4];
+#pragma unroll
+          for (int e = 0; e < 4; ++e) inv[e] = __shfl(inv_mine, in + e, 64);
+#pragma unroll
+          for (int t = 0; t < NB; ++t) {
+            const int p = m0 + (NB * wb + t) * 32 + l32;
+            if (p < n_probes && row < N)
+              *(f32x4 *)(gm.of_rows(gm.p0 + p) + row) = f32x4{acc[a][t][q4 * 4] * inv[0], acc[a][t][q4 * 4 + 1] * inv[1], acc[a][t][q4 * 4 + 2] * inv[2], acc[a][t][q4 * 4 + 3] * inv[3]};
+          }
+          __builtin_amdgcn_sched_barrier(0);
+        }
     } else {
       // lane (l32, 0) has rows 0..3, 8..11, 16..19, 24..27 of a block, lane (l32, 1) the others
       const int base = r0 + NA * wa * 32 + g * 4;
@@ -1188,9 +1232,9 @@ __global__ __launch_bounds__(512, 1) void lookup_big_kernel(const _Float16 *__re
       }
     }
   }
-  if constexpr (K == kGroups) {
+  if constexpr (K != 1) {
     pc::gemm::wait_vmcnt0();  // (the surplus requests)
-    if (gm.kind == Groups::big)   // groups that this wavefront has no rows for
+    if (K == kGroups && gm.kind == Groups::big)   // groups that this wavefront has no rows for
       for (int j = (tile_end - tile_begin + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
         for (int t = 0; t < NB; ++t) {
           const int p = m0 + (NB * wb + t) * 32 + l32;
@@ -1458,18 +1502,19 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
           for (int e = 0; e < 4; ++e) {
             const int r = q4 * 4 + e, row = rb * BR + set * 32 + rin + e;
             v[r] = row < N ? (acc[0][r] + acc[1][r]) * inv4[e] : __builtin_nanf("");
-            top.add(v[r], row);
           }
         }
-        if (gm.kind == Groups::wide_rows) {
+        if (gm.kind == Groups::rows) {
           const int p = pg * 32 + l32, row0 = rb * BR + set * 32 + g2 * 4;   // (the pitch leaves room for the last block's quad)
           if (p < n_probes) {
 #pragma unroll
             for (int q4 = 0; q4 < 4; ++q4)
-              if (row0 + q4 * 8 < N) *(f32x4 *)(gm.rows(gm.p0 + p) + row0 + q4 * 8) = f32x4{v[q4 * 4], v[q4 * 4 + 1], v[q4 * 4 + 2], v[q4 * 4 + 3]};
+              if (row0 + q4 * 8 < N) *(f32x4 *)(gm.of_rows(gm.p0 + p) + row0 + q4 * 8) = f32x4{v[q4 * 4], v[q4 * 4 + 1], v[q4 * 4 + 2], v[q4 * 4 + 3]};
           }
           continue;
         }
+#pragma unroll
+        for (int r = 0; r < 16; ++r) top.add(v[r], rb * BR + set * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3));
         if (__ballot(top.i == INT_MAX)) {
           const bool none = top.i == INT_MAX;
 #pragma unroll
@@ -1687,7 +1732,7 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
 int probe_tile(int n_probes) { return big_tiles_pay(n_probes) ? 256 : 128; }
 // The groups of a pass of so many probes (see Groups): about four a wavefront, in the matrix-product kernel at least 1024 in all; there, over a
 // small bank, the 16 rows that a lane has in a block of 32. 
-constexpr int kRowsUpTo = 8192, kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
+constexpr int kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
 Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
   auto cut = [](Groups &g, int blocks, int into) {   // a wavefront's (workgroup's) blocks into that many groups
     g.stretch = (blocks + into - 1) / into;
@@ -1710,12 +1755,6 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     g.blocks = (N + 32 * w.sets - 1) / (32 * w.sets);
     cut(g, w.per_wg, kGroupsPerWide / w.sets);
     g.n = w.grid * w.sets * g.per;
-    // Every row a group: no probe is ever in doubt, which over so few rows one of them would nearly always be.  us a call, 8 best, groups | rows: 67 probes
-    // over 2273 rows of width 768 23.0 | 14.9, over 6000 22.8 | 18.0; past 8192 rows topk_groups_kernel reads the similarities twice and gains nothing.
-    if (N <= kRowsUpTo) {
-      g.kind = Groups::wide_rows;
-      g.n = N;
-    }
   } else {
     const BigShape bg = big_shape(ctx->n_cu, N, n_probes, probe_tile(n_probes));
     g.kind = N <= kFineGroupsUpTo ? Groups::big_fine : Groups::big;
@@ -1725,7 +1764,16 @@ Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
     cut(g, (g.blocks + bg.groups - 1) / bg.groups, least > kGroupsPerWave ? least : kGroupsPerWave);
     g.n = g.kind == Groups::big_fine ? g.blocks * 16 : bg.groups * 4 * g.per;
   }
-  const int places = g.kind == Groups::wide_rows ? (g.n + 3) / 4 : g.n;
+  // Every row a group: no probe is ever in doubt, which over so few rows one of them would nearly always be.  us a call, lists in every lane | groups | rows:
+  // 9 probes, 2 best of 200 rows of width 768 11.3 | 13.1 | 9.2, 8 best of 1000 of width 1024 19.5 | 14.9 | 10.2, 3 best of 8000 of width 384 11.0 | 12.3 | 8.9; 128
+  // probes, 3 best of 8000 of width 768 21.8 | (22.7) | 17.5; 1024 probes, 8 best of 200 44.2 | 66.9 | 28.2, of 2500 of width 1024 47.4 | 51.7 | 39.5, of
+  // 4000 of width 768 44.8 | 42.5 | 37.0.  Under more than 128 probes the similarities' bytes weigh more: 600 probes, 3 best of 8000 of width 384
+  // 35.7 | 26.9 | 30.6, so there half as many rows.
+  if (N <= (r == Route::big ? kRowsUpTo / 2 : kRowsUpTo)) {
+    g.kind = Groups::rows;
+    g.n = N;
+  }
+  const int places = g.kind == Groups::rows ? (g.n + 3) / 4 : g.n;
   g.pitch = ((places + 7) / 8 | 1) * 8;
   return g;
 }
@@ -1775,6 +1823,8 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
       PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, 1>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
       PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<256, kGroups>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<256>::LDS));
       PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, kGroups>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<256, kRows>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<256>::LDS));
+      PC_HIP(ctx, hipFuncSetAttribute((const void *)lookup_big_kernel<128, kRows>, hipFuncAttributeMaxDynamicSharedMemorySize, BigTile<128>::LDS));
       big_lds_set = true;
     }
     const dim3 grid((unsigned)((bg.groups + 7) / 8 * 8 * bg.p_tiles));
@@ -1783,6 +1833,7 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
   hipLaunchKernelGGL((lookup_big_kernel<PP, KK>), grid, dim3(512), (BigTile<PP>::LDS), st, ctx->bank, ctx->bank_inv, N, d, probes, n_probes, \
                      bg.p_tiles * pt, bg.groups, bg.p_tiles, partial, gm ? *gm : Groups{})
     if (!gm) { if (pt == 256) PC_BIG(256, 1); else PC_BIG(128, 1); }
+    else if (gm->kind == Groups::rows) { if (pt == 256) PC_BIG(256, kRows); else PC_BIG(128, kRows); }
     else { if (pt == 256) PC_BIG(256, kGroups); else PC_BIG(128, kGroups); }
 #undef PC_BIG
     pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
@@ -1868,7 +1919,8 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
     gm.g = (Group *)workspace_dev;
     const pc_status ls = run_passes(ctx, st, N, probes + (size_t)p0 * d, np, tau, k, nullptr, nullptr, nullptr, nullptr, InLaunch{}, &gm);
     if (ls != PC_OK) return ls;
-    hipLaunchKernelGGL(topk_groups_kernel, dim3(np), dim3(kSelectThreads), 0, st, gm, ctx->bank, ctx->bank_inv, N, d, probes + (size_t)p0 * d, k,
+    auto *const select = gm.kind == Groups::rows ? topk_groups_kernel<true> : topk_groups_kernel<false>;
+    hipLaunchKernelGGL(select, dim3(np), dim3(kSelectThreads), 0, st, gm, ctx->bank, ctx->bank_inv, N, d, probes + (size_t)p0 * d, k,
                        idx_out_dev + (size_t)p0 * k, sim_out_dev + (size_t)p0 * k);
     PC_HIP(ctx, hipGetLastError());
   }

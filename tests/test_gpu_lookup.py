@@ -279,11 +279,11 @@ def test_topk_vs_oracle(dim, n_probes, k):
     print(f"top-{k}: {loose} near-tie entries judged by similarity", flush=True)
 
 
-# rows around the kernels' groups: one block, a group's worth more and less, groups of several blocks (stream and wide from 65 536 rows on, tiles from
+# rows around the kernels' groups: every row one (up to 8192, past 128 probes 4096), one block, a group's worth more and less, groups of several blocks (stream and wide from 65 536 rows on, tiles from
 # 16 384), the last workgroup's part empty or ragged; 32 | 33, 128 | 129 and 192 probes are other kernels
 @pytest.mark.parametrize("rows,dim,n_probes,k", [
     (3, 128, 2, 8), (16, 64, 9, 8), (17, 384, 33, 5), (1025, 512, 64, 8), (8192, 512, 33, 3), (8193, 768, 128, 8), (5003, 1024, 70, 8), (4097, 64, 200, 8), (16384, 64, 130, 8), (16385, 64, 130, 8),
-    (65536, 128, 16, 3), (65553, 64, 32, 8), (140001, 64, 5, 2), (70001, 512, 40, 8), (70001, 768, 128, 3), (40001, 1024, 8, 8), (33000, 64, 300, 5)])
+    (8191, 64, 32, 5), (8192, 640, 7, 8), (8193, 64, 20, 8), (4093, 128, 260, 8), (4096, 64, 129, 3), (65536, 128, 16, 3), (65553, 64, 32, 8), (140001, 64, 5, 2), (70001, 512, 40, 8), (70001, 768, 128, 3), (40001, 1024, 8, 8), (33000, 64, 300, 5)])
 def test_topk_groups(rows, dim, n_probes, k):
     """Planted beside random rows: copies of a row in its group and far away, zero rows, rows that are not numbers; probes near the copies (two of the
     best in one group) and a zero probe (every similarity the same).  In a workspace that holds the groups and in the smallest one taken.
