@@ -125,8 +125,10 @@ pc_status percache_lookup_noalloc(percache_ctx *ctx, const void *probes_dev, int
  * "top-k_refresh") and dense retrieval over chunk embeddings need.  Same similarity, same tie rule (equal
  * similarities: lower row first), sorted best first.
  *   idx_out_dev int32[n_probes * k], sim_out_dev float[n_probes * k]; entries beyond the bank size: idx -1, sim -inf.
- * Same workspace as percache_lookup.  A smaller one, down to 64 bytes for each of 32 probes (256 past 32 probes) and a
- * workgroup per CU or per 2048 rows, is taken too and costs passes over the bank. */
+ *   workspace_dev >= percache_lookup_workspace_bytes.  One of percache_lookup_topk_workspace_bytes (k > 1; at 256 CUs 2.1 MB for 32
+ * probes, 21 MB for 1024, 72 MB from 4096 on) divides the bank into smaller parts, of which fewer hold several of a probe's
+ * best rows and are read again: the same results, up to a third sooner for many probes. */
+size_t percache_lookup_topk_workspace_bytes(const percache_ctx *ctx, int32_t n_probes);
 pc_status percache_lookup_topk(percache_ctx *ctx, const void *probes_dev, int32_t n_probes, int32_t k,
                                int32_t *idx_out_dev, float *sim_out_dev, void *workspace_dev,
                                size_t workspace_bytes, void *stream);
@@ -141,7 +143,8 @@ pc_status percache_lookup_topk(percache_ctx *ctx, const void *probes_dev, int32_
  * A similarity that is not a number (an embedding holds NaN or infinity) takes no part; a row with no other has
  * best_sim -inf, best_new -1 and stale 0.
  *   new_emb_dev [n_new, d] fp16;  kth_sim_dev, best_sim_out_dev float[bank size];  best_new_out_dev int32[bank size];
- *   stale_out_dev uint8[bank size];  workspace as for percache_lookup (it also bounds n_new: 4 bytes per new row). */
+ *   stale_out_dev uint8[bank size];  workspace as for percache_lookup (it also bounds n_new: 4 bytes per new row; the call
+ *   checks it, and the present kernels put nothing there). */
 pc_status percache_bank_refresh_scan(percache_ctx *ctx, const void *new_emb_dev, int32_t n_new,
                                      const float *kth_sim_dev, float *best_sim_out_dev, int32_t *best_new_out_dev,
                                      uint8_t *stale_out_dev, void *workspace_dev, size_t workspace_bytes,

@@ -23,7 +23,7 @@ STATUS_NAMES = {0: "PC_OK", -1: "PC_EINVAL", -2: "PC_ESHAPE", -3: "PC_ESLOT", -4
 EXPORTS = [
     "percache_arena_bytes", "percache_create", "percache_destroy", "percache_last_error",
     "percache_bank_put", "percache_bank_size", "percache_lookup_workspace_bytes", "percache_lookup",
-    "percache_lookup_noalloc", "percache_lookup_topk", "percache_bank_refresh_scan",
+    "percache_lookup_noalloc", "percache_lookup_topk_workspace_bytes", "percache_lookup_topk", "percache_bank_refresh_scan",
     "percache_kv_put", "percache_kv_put_batch", "percache_kv_get", "percache_kv_get_batch", "percache_kv_evict", "percache_kv_len",
     "percache_kv_slice", "percache_kv_append", "percache_stack_workspace_bytes", "percache_stack_reuse",
     "percache_stack_decode",
@@ -82,6 +82,7 @@ def load_library() -> ctypes.CDLL:
         "percache_bank_put": (_i32, [_vp, _i32, _vp, _i32, _vp]),
         "percache_bank_size": (_i32, [_vp]),
         "percache_lookup_workspace_bytes": (_sz, [_vp, _i32]),
+        "percache_lookup_topk_workspace_bytes": (_sz, [_vp, _i32]),
         "percache_lookup": (_i32, [_vp, _vp, _i32, ctypes.c_float, _vp, _vp, _vp, _vp, _sz, _vp]),
         "percache_lookup_noalloc": (_i32, [_vp, _vp, _i32, ctypes.c_float, _vp, _vp, _vp, _vp]),
         "percache_lookup_topk": (_i32, [_vp, _vp, _i32, _i32, _vp, _vp, _vp, _sz, _vp]),
@@ -178,6 +179,7 @@ class Percache:
         self._ws = None
         self._step_ws = None
         self._lookup_ws = None
+        self._topk_ws = None
 
     # ------------------------------------------------------------------ helpers
     def _check(self, st: int):
@@ -288,10 +290,17 @@ class Percache:
         n = probes.shape[0]
         idx_out = torch.empty((n, k), dtype=torch.int32, device=self.device)
         sim_out = torch.empty((n, k), dtype=torch.float32, device=self.device)
-        need = self.lib.percache_lookup_workspace_bytes(self.ctx, n)
-        if self._lookup_ws is None or self._lookup_ws.numel() < need + 256:
-            self._lookup_ws = torch.empty(need + 256, dtype=torch.uint8, device=self.device)
-        ws = (self._lookup_ws.data_ptr() + 255) // 256 * 256
+        need = (self.lib.percache_lookup_topk_workspace_bytes if k > 1 else self.lib.percache_lookup_workspace_bytes)(self.ctx, n)
+        # (a workspace of its own beside a smaller one of the lookups: a captured lookup may hold that)
+        own = k > 1 and self._lookup_ws is not None and self._lookup_ws.numel() < need + 256
+        ws = self._topk_ws if own else self._lookup_ws
+        if ws is None or ws.numel() < need + 256:
+            ws = torch.empty(need + 256, dtype=torch.uint8, device=self.device)
+            if own:
+                self._topk_ws = ws
+            else:
+                self._lookup_ws = ws
+        ws = (ws.data_ptr() + 255) // 256 * 256
         self._check(self.lib.percache_lookup_topk(self.ctx, _ptr(probes), n, k, _ptr(idx_out), _ptr(sim_out), ws, need, _stream()))
         return idx_out, sim_out
 

@@ -252,7 +252,7 @@ struct RowScan {
 // Over a few thousand rows every row is a group (see groups_of).
 // A group is what one lane or two meet in a stretch of the bank; which rows these are only Groups::first_row knows.  A workgroup has about four a
 // wavefront: under many probes their bytes count, but over a small bank two of the k best rows would often share a large one.
-constexpr int kGroups = -1, kRows = -2;   // (kRows: lookup_big_kernel where every row is a group)
+constexpr int kGroups = -1, kRows = -2;   // (kRows: every row is a group)
 struct Group {
   float best, second;   // without the probe's norm; best: a NaN where no row has a similarity that is a number
   int row, unused;
@@ -514,6 +514,16 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
           if (ok) best[pb].insert(s, row);
         }
       }
+    } else if (K == kRows) {
+      const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 16 + g * 4);
+      const int row0 = rb * 16 + g * 4;
+#pragma unroll
+      for (int pb = 0; pb < NPB; ++pb) {
+        f32x4 v;
+#pragma unroll
+        for (int r = 0; r < 4; ++r) v[r] = row0 + r < N ? acc[pb][r] * inv4[r] : __builtin_nanf("");
+        if (pb * 16 + r16 < n_probes && row0 < N) *(f32x4 *)(gm.of_rows(gm.p0 + pb * 16 + r16) + row0) = v;
+      }
     } else if (K == kGroups) {
       // this lane's four rows of the block per probe; at the end of a stretch the four lanes of the probe
       const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * 16 + g * 4);
@@ -526,14 +536,8 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
         for (int r = 0; r < 4; ++r) {
           const int row = rb * 16 + g * 4 + r;
           v[r] = row < N ? acc[pb][r] * inv4[r] : __builtin_nanf("");
+          top[pb].add(v[r], row);
         }
-        if (gm.kind == Groups::rows) {
-          const int p = pb * 16 + r16, row0 = rb * 16 + g * 4;
-          if (p < n_probes && row0 < N) *(f32x4 *)(gm.of_rows(gm.p0 + p) + row0) = f32x4{v[0], v[1], v[2], v[3]};
-          continue;
-        }
-#pragma unroll
-        for (int r = 0; r < 4; ++r) top[pb].add(v[r], rb * 16 + g * 4 + r);
         if (__ballot(top[pb].i == INT_MAX)) {
           if (top[pb].i == INT_MAX)
 #pragma unroll
@@ -595,7 +599,7 @@ __global__ __launch_bounds__(256) void lookup_stream_kernel(const _Float16 *__re
   }
   PC_LOOKUP_WAIT_VMCNT(0);
 
-  if (K == kGroups && gm.kind != Groups::rows) {   // groups that this wavefront has no rows for
+  if (K == kGroups) {   // groups that this wavefront has no rows for
     const int mine = rb_end > rb_begin + wave ? (rb_end - rb_begin - wave + 3) / 4 : 0;
     for (int j = (mine + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
       if (lane < n_probes && lane < NPB * 16) write_group(gm.g + (size_t)(gm.p0 + lane) * gm.pitch + (blockIdx.x * 4 + wave) * gm.per + j, Top2{});
@@ -705,7 +709,8 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
   const int p = blockIdx.x, tid = threadIdx.x, lane = tid & 63, wave = tid >> 6;
   const Group *const groups = gm.g + (size_t)p * gm.pitch;
   const _Float16 *const probe = probes + (size_t)p * d;
-  // the groups: the first kSelectHeld a thread stay in registers; of rows all do, four of them next to each other
+  // the groups: the first kSelectHeld a thread stay in registers; of rows all do, four of them next to each other.  (No branch around a load: it would be
+  // waited for before the next one goes out.)
   const float *const rows = gm.of_rows(p);
   auto group_at = [&](int at) __attribute__((always_inline)) {
     if (!ROWS) return groups[at];
@@ -718,17 +723,15 @@ __global__ __launch_bounds__(kSelectThreads, 4) void topk_groups_kernel(Groups g
     static_assert(HELD % 4 == 0 && HELD * kSelectThreads == kRowsUpTo, "all of them");
 #pragma unroll
     for (int i = 0; i < HELD; i += 4) {
-      f32x4 v;
-      v[0] = v[1] = v[2] = v[3] = __builtin_nanf("");
-      if (held_at(i) < gm.n) v = *(const f32x4 *)(rows + held_at(i));
+      const f32x4 v = *(const f32x4 *)(rows + min(held_at(i), (gm.n - 1) & ~3));
 #pragma unroll
-      for (int e = 0; e < 4; ++e) held[i + e] = Group{v[e], 0.f, held_at(i + e), 0};
+      for (int e = 0; e < 4; ++e) held[i + e] = Group{held_at(i + e) < gm.n ? v[e] : __builtin_nanf(""), 0.f, held_at(i + e), 0};
     }
   } else {
 #pragma unroll
     for (int i = 0; i < HELD; ++i) {
-      held[i].best = __builtin_nanf("");
-      if (held_at(i) < gm.n) held[i] = group_at(held_at(i));
+      held[i] = group_at(min(held_at(i), gm.n - 1));
+      if (held_at(i) >= gm.n) held[i].best = __builtin_nanf("");
     }
   }
   if (tid < 64) bin_rank[tid] = 0;
@@ -1492,6 +1495,19 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
         continue;
       }
       // element r of the product: row (r/4)*8 + 4*g2 + r%4 of the block, probe wave*32 + l32
+      if constexpr (K == kRows) {
+        const int p = pg * 32 + l32;
+#pragma unroll
+        for (int q4 = 0; q4 < 4; ++q4) {
+          const int rin = set * 32 + q4 * 8 + g2 * 4, row0 = rb * BR + rin;
+          const f32x4 inv4 = *(const f32x4 *)(inv_lds + (rb - rb_begin) * BR + rin);
+          f32x4 v;
+#pragma unroll
+          for (int e = 0; e < 4; ++e) v[e] = row0 + e < N ? (acc[0][q4 * 4 + e] + acc[1][q4 * 4 + e]) * inv4[e] : __builtin_nanf("");
+          if (p < n_probes && row0 < N) *(f32x4 *)(gm.of_rows(gm.p0 + p) + row0) = v;
+        }
+        continue;
+      }
       if constexpr (K == kGroups) {
         float v[16];
 #pragma unroll
@@ -1502,19 +1518,9 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
           for (int e = 0; e < 4; ++e) {
             const int r = q4 * 4 + e, row = rb * BR + set * 32 + rin + e;
             v[r] = row < N ? (acc[0][r] + acc[1][r]) * inv4[e] : __builtin_nanf("");
+            top.add(v[r], row);
           }
         }
-        if (gm.kind == Groups::rows) {
-          const int p = pg * 32 + l32, row0 = rb * BR + set * 32 + g2 * 4;   // (the pitch leaves room for the last block's quad)
-          if (p < n_probes) {
-#pragma unroll
-            for (int q4 = 0; q4 < 4; ++q4)
-              if (row0 + q4 * 8 < N) *(f32x4 *)(gm.of_rows(gm.p0 + p) + row0 + q4 * 8) = f32x4{v[q4 * 4], v[q4 * 4 + 1], v[q4 * 4 + 2], v[q4 * 4 + 3]};
-          }
-          continue;
-        }
-#pragma unroll
-        for (int r = 0; r < 16; ++r) top.add(v[r], rb * BR + set * 32 + (r >> 2) * 8 + g2 * 4 + (r & 3));
         if (__ballot(top.i == INT_MAX)) {
           const bool none = top.i == INT_MAX;
 #pragma unroll
@@ -1548,7 +1554,7 @@ __global__ __launch_bounds__(256, 1) void lookup_wide_kernel(const _Float16 *__r
   PC_LOOKUP_WAIT_VMCNT(0);
   if constexpr (K == kGroups) {   // groups that this workgroup has no rows for
     const int p = pg * 32 + l32;
-    for (int j = gm.kind == Groups::wide ? (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch : gm.per; j < gm.per; ++j)
+    for (int j = (max(rb_end - rb_begin, 0) + gm.stretch - 1) / gm.stretch; j < gm.per; ++j)
       if (g2 == 0 && p < n_probes) write_group(gm.g + (size_t)(gm.p0 + p) * gm.pitch + (blockIdx.x * RS + set) * gm.per + j, Top2{});
   }
   if constexpr (K <= 0) return;  // per-row mode and groups: everything has been written
@@ -1655,7 +1661,7 @@ pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStre
 
 
 // What a call of n_probes needs at least: eight rows a workgroup and probe, of which a call for the best row uses one.  A top-k call that is given no
-// more than this keeps the groups of as many probes as fit and takes its probes in several turns.
+// more than this makes its groups as large as they have to be: four a workgroup always fit.
 size_t list_bytes(const percache_ctx *ctx, int32_t n_probes) {
   size_t lists = (size_t)max_stream_grid(ctx) * kPassProbes;
   if (n_probes > kBatchedFrom) {
@@ -1687,11 +1693,10 @@ unsigned long long next_mark() {
 
 // The kernel that a pass of so many probes takes.
 enum class Route { stream, wide, big };
-Route route_of(const percache_ctx *ctx, int n_probes, int N) {
+Route route_of(const percache_ctx *ctx, int n_probes) {
   const int d = ctx->cfg.emb_dim;
   if (n_probes > kBatchedFrom && n_probes <= kWideUpTo && (d == 512 || d == 768 || d == 1024)) return Route::wide;
-  // (a workspace may hold the groups of so few probes that a call of many comes here with few: rows too wide for a streaming pass)
-  return n_probes > kBatchedFrom || stream_shape(ctx, 1, N).lds > kMaxLds ? Route::big : Route::stream;
+  return n_probes > kBatchedFrom ? Route::big : Route::stream;
 }
 struct WideShape {
   int sets, grid, per_wg;   // per_wg: blocks of sets x 32 rows
@@ -1730,59 +1735,83 @@ pc_status launch_scan_wide(percache_ctx *ctx, hipStream_t st, int N, int d, cons
 }
 
 int probe_tile(int n_probes) { return big_tiles_pay(n_probes) ? 256 : 128; }
-// The groups of a pass of so many probes (see Groups): about four a wavefront, in the matrix-product kernel at least 1024 in all; there, over a
-// small bank, the 16 rows that a lane has in a block of 32. 
+// The groups of a call of so many probes (see Groups) that has room for so many of a probe: about four a wavefront, in the matrix-product kernel at least
+// 1024 in all; there, over a small bank, the 16 rows that a lane has in a block of 32.  Fewer, larger ones where there is no room for these.
+// us a call, 8 best of 200 000 rows of width 1024, room for all | in the least workspace: 32 probes 83 | 88, 128 103 | 103, 512 249 | 299, 1024 455 | 643 (lists
+// in every lane, which needed no more, 89, 179, 420, 723).
 constexpr int kFineGroupsUpTo = 16384, kLeastGroups = 1024, kGroupsPerWave = 4, kGroupsPerWide = 8;
-Groups groups_of(const percache_ctx *ctx, int n_probes, int N) {
-  auto cut = [](Groups &g, int blocks, int into) {   // a wavefront's (workgroup's) blocks into that many groups
-    g.stretch = (blocks + into - 1) / into;
-    g.per = (blocks + g.stretch - 1) / g.stretch;
-  };
+constexpr int kRowsUpToBig = kRowsUpTo / 2;
+Groups groups_of(const percache_ctx *ctx, int n_probes, int N, size_t room) {
   Groups g{};
-  const Route r = route_of(ctx, n_probes, N);
+  int blocks, into, parts;   // the blocks of a wavefront (workgroup) into so many groups or a few less; wavefronts (workgroups)
+  const Route r = route_of(ctx, n_probes);
   if (r == Route::stream) {
     const StreamShape sh = stream_shape(ctx, 1, N);
     g.kind = Groups::stream;
     g.per_wg = sh.per_wg;
     g.blocks = (N + 15) / 16;
-    cut(g, (sh.per_wg + 3) / 4, kGroupsPerWave);
-    g.n = sh.grid * 4 * g.per;
+    blocks = (sh.per_wg + 3) / 4, into = kGroupsPerWave, parts = sh.grid * 4;
   } else if (r == Route::wide) {
     const WideShape w = wide_shape(ctx->n_cu, N, n_probes);
     g.kind = Groups::wide;
     g.per_wg = w.per_wg;
     g.sets = w.sets;
     g.blocks = (N + 32 * w.sets - 1) / (32 * w.sets);
-    cut(g, w.per_wg, kGroupsPerWide / w.sets);
-    g.n = w.grid * w.sets * g.per;
+    blocks = w.per_wg, into = kGroupsPerWide / w.sets, parts = w.grid * w.sets;
   } else {
     const BigShape bg = big_shape(ctx->n_cu, N, n_probes, probe_tile(n_probes));
-    g.kind = N <= kFineGroupsUpTo ? Groups::big_fine : Groups::big;
+    g.kind = Groups::big;
     g.per_wg = bg.groups;
     g.blocks = (N + kBigRows - 1) / kBigRows;
     const int least = (kLeastGroups / 4 + bg.groups - 1) / bg.groups;
-    cut(g, (g.blocks + bg.groups - 1) / bg.groups, least > kGroupsPerWave ? least : kGroupsPerWave);
-    g.n = g.kind == Groups::big_fine ? g.blocks * 16 : bg.groups * 4 * g.per;
+    blocks = (g.blocks + bg.groups - 1) / bg.groups, into = least > kGroupsPerWave ? least : kGroupsPerWave, parts = bg.groups * 4;
+  }
+  do {
+    g.stretch = (blocks + into - 1) / into;
+    g.per = (blocks + g.stretch - 1) / g.stretch;
+    g.n = parts * g.per;
+  } while ((size_t)g.n > room && into-- > 1);
+  if (r == Route::big && N <= kFineGroupsUpTo && (size_t)g.blocks * 16 <= room) {
+    g.kind = Groups::big_fine;
+    g.n = g.blocks * 16;
   }
   // Every row a group: no probe is ever in doubt, which over so few rows one of them would nearly always be.  us a call, lists in every lane | groups | rows:
   // 9 probes, 2 best of 200 rows of width 768 11.3 | 13.1 | 9.2, 8 best of 1000 of width 1024 19.5 | 14.9 | 10.2, 3 best of 8000 of width 384 11.0 | 12.3 | 8.9; 128
   // probes, 3 best of 8000 of width 768 21.8 | (22.7) | 17.5; 1024 probes, 8 best of 200 44.2 | 66.9 | 28.2, of 2500 of width 1024 47.4 | 51.7 | 39.5, of
   // 4000 of width 768 44.8 | 42.5 | 37.0.  Under more than 128 probes the similarities' bytes weigh more: 600 probes, 3 best of 8000 of width 384
   // 35.7 | 26.9 | 30.6, so there half as many rows.
-  if (N <= (r == Route::big ? kRowsUpTo / 2 : kRowsUpTo)) {
+  if (N <= (r == Route::big ? kRowsUpToBig : kRowsUpTo) && (size_t)(N + 3) / 4 <= room) {
     g.kind = Groups::rows;
     g.n = N;
   }
-  const int places = g.kind == Groups::rows ? (g.n + 3) / 4 : g.n;
-  g.pitch = ((places + 7) / 8 | 1) * 8;
+  const int places = g.kind == Groups::rows ? (g.n + 3) / 4 : g.n, odd_lines = ((places + 7) / 8 | 1) * 8;
+  g.pitch = (size_t)odd_lines <= room ? odd_lines : places;
   return g;
+}
+// The places of a probe's groups that a call of so many probes has a use for, over whatever the bank holds.
+size_t group_places(const percache_ctx *ctx, int n_probes) {
+  const int d = ctx->cfg.emb_dim, cus = ctx->n_cu;
+  size_t n;
+  if (n_probes <= kBatchedFrom) {
+    n = (size_t)max_stream_grid(ctx) * 4 * kGroupsPerWave;
+  } else if (n_probes <= kWideUpTo && (d == 512 || d == 768 || d == 1024)) {
+    const size_t grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
+    n = (grid > (size_t)cus ? grid : (size_t)cus) * kGroupsPerWide;
+  } else {   // (no fewer tiles than that, so no more groups of them: see big_shape)
+    const int tiles = (n_probes + 255) / 256, groups = cus / tiles > 8 ? cus / tiles : 8;
+    n = 4 * (size_t)groups * kGroupsPerWave;
+    const size_t least = kLeastGroups + 4 * (size_t)groups;
+    n = n > least ? n : least;
+  }
+  const size_t rows = kRowsUpTo / 4;
+  return (n > rows || n_probes > kWideUpTo ? n : rows) + 16;
 }
 
 // The passes over the bank: the best row of every probe and its hit flag (or, with il.marks, the k best), or (gm) the group maxima.
 pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *probes, int n_probes, float tau, int k, int32_t *idx_out_dev, float *sim_out_dev,
                      uint8_t *hit_out_dev, Best *partial, const InLaunch &il, const Groups *gm) {
   const int d = ctx->cfg.emb_dim;
-  const Route route = route_of(ctx, n_probes, N);
+  const Route route = route_of(ctx, n_probes);
   if (route == Route::wide) {
     // up to 128 probes: one pass of the bank
     const WideShape w = wide_shape(ctx->n_cu, N, n_probes);
@@ -1800,6 +1829,8 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     if (!gm) {
       if (d == 512) PC_WIDE(512, 1); else if (d == 768) PC_WIDE(768, 1); else PC_WIDE(1024, 1);
+    } else if (gm->kind == Groups::rows) {
+      if (d == 512) PC_WIDE(512, kRows); else if (d == 768) PC_WIDE(768, kRows); else PC_WIDE(1024, kRows);
     } else {
       if (d == 512) PC_WIDE(512, kGroups); else if (d == 768) PC_WIDE(768, kGroups); else PC_WIDE(1024, kGroups);
     }
@@ -1853,9 +1884,11 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
     const _Float16 *pp = probes + (size_t)p0 * d;
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
     // (up to four best rows in one launch: lists of four)
-    pc_status ls = gm       ? launch_pass<kGroups>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, gm->from_probe(p0))
-                   : k == 1 ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
-                            : launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il);
+    const Groups here = gm ? gm->from_probe(p0) : Groups{};
+    pc_status ls = !gm                           ? (k == 1 ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
+                                                           : launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il))
+                   : here.kind == Groups::rows ? launch_pass<kRows>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here)
+                                                 : launch_pass<kGroups>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here);
     if (ls != PC_OK) return ls;
     pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
     PC_HIP(ctx, hipGetLastError());
@@ -1908,14 +1941,16 @@ pc_status run_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes
       il = InLaunch{(unsigned long long *)(partial + (size_t)sh.grid * 16 * (k == 1 ? 1 : 4)), next_mark(), tau, k, idx_out_dev, sim_out_dev, hit_out_dev};
   }
   if (k == 1 || il.marks) return run_passes(ctx, st, N, probes, n_probes, tau, k, idx_out_dev, sim_out_dev, hit_out_dev, partial, il, nullptr);
-  // the groups of as many probes at a time as the workspace holds, then their best rows
-  for (int p0 = 0, np; p0 < n_probes; p0 += np) {
-    np = n_probes - p0;
-    Groups gm = groups_of(ctx, np, N);
-    while (np > 1 && (size_t)np * gm.pitch * sizeof(Group) > workspace_bytes) {
-      np = np > 256 ? (np - 1) / 256 * 256 : (np + 1) / 2;
-      gm = groups_of(ctx, np, N);
-    }
+  // A workspace with room for less than 256 groups of a probe takes the probes in turns (of equal size, 64 or more, so that none is another kernel's): 4096
+  // probes, 8 best of 200 000 rows of width 1024 in the least workspace, at once 4870 us, in turns 2390 (lists in every lane 2290, room for all 1640).
+  constexpr int kLeastRoom = 256, kTurnRoom = 512;
+  const size_t places = workspace_bytes / sizeof(Group);
+  const int per_probe = N < kTurnRoom * 16 ? (N + 15) / 16 : kTurnRoom;
+  long turns = places / (size_t)n_probes >= (size_t)kLeastRoom ? 1 : (long)(((size_t)n_probes * per_probe + places - 1) / places);
+  if (turns > n_probes / 64) turns = n_probes < 64 ? 1 : n_probes / 64;
+  for (long t = 0; t < turns; ++t) {
+    const int p0 = (int)(t * n_probes / turns), np = (int)((t + 1) * n_probes / turns) - p0;
+    Groups gm = groups_of(ctx, np, N, places / (size_t)np);
     gm.g = (Group *)workspace_dev;
     const pc_status ls = run_passes(ctx, st, N, probes + (size_t)p0 * d, np, tau, k, nullptr, nullptr, nullptr, nullptr, InLaunch{}, &gm);
     if (ls != PC_OK) return ls;
@@ -1949,20 +1984,20 @@ pc_status percache_bank_put(percache_ctx *ctx, int32_t index, const void *emb_de
 
 size_t percache_lookup_workspace_bytes(const percache_ctx *ctx, int32_t n_probes) {
   if (!ctx || n_probes < 0) return 0;
-  // Top-k: the groups of all probes of a call (of up to 4096 at a time), for whatever the bank holds; a smaller workspace takes fewer probes at a time.
-  auto grow = [](size_t &a, size_t b) { a = a > b ? a : b; };
-  const size_t n = (size_t)n_probes, cus = (size_t)ctx->n_cu, wide_grid = (size_t)ctx->cfg.bank_capacity / (32 * kWideMaxBlocksPerWg) + 1;
-  auto pitch = [](size_t groups) { return groups + 16; };
-  size_t groups = (n < 32 ? n : 32) * pitch(max_stream_grid(ctx) * 4 * kGroupsPerWave);
-  if (n > kBatchedFrom) {
-    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * pitch((wide_grid > cus ? wide_grid : cus) * kGroupsPerWide));
-    grow(groups, (n < kWideUpTo ? n : kWideUpTo) * pitch(kRowsUpTo / 4));
-    grow(groups, (n < 256 ? n : 256) * pitch(cus * 4 * kGroupsPerWave + 2 * kLeastGroups));
-    grow(groups, (n < 4096 ? n : 4096) * pitch(2 * kLeastGroups));
+  return list_bytes(ctx, n_probes);
+}
+
+size_t percache_lookup_topk_workspace_bytes(const percache_ctx *ctx, int32_t n_probes) {
+  if (!ctx || n_probes < 0) return 0;
+  // (not less for more probes, so that the workspace of a longer call is as good; past 4096 the groups are larger instead)
+  size_t places = 0;
+  for (const int upto : {kBatchedFrom, kWideUpTo, 256, 512, 768, 1024, 4096}) {
+    const int n = n_probes < upto ? n_probes : upto;
+    const size_t p = (size_t)n * group_places(ctx, n);
+    places = places > p ? places : p;
   }
-  size_t bytes = list_bytes(ctx, n_probes);
-  grow(bytes, groups * sizeof(Group));
-  return pc::align_up(bytes);
+  const size_t bytes = places * sizeof(Group), lists = list_bytes(ctx, n_probes);
+  return pc::align_up(bytes > lists ? bytes : lists);
 }
 
 pc_status percache_lookup(percache_ctx *ctx, const void *probes_dev, int32_t n_probes, float tau, int32_t *idx_out_dev,

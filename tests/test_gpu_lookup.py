@@ -9,7 +9,7 @@ import torch
 
 import oracle
 from paper_2601_11553_amd import workloads as wl
-from paper_2601_11553_amd.binding import Percache, PercacheError
+from paper_2601_11553_amd.binding import KERNEL_LOOKUP, Percache, PercacheError
 
 from gpu_util import DEV, f16, host
 
@@ -348,6 +348,45 @@ def test_topk_many_equal_groups(rows, dim, n_probes, copies):
     torch.cuda.synchronize()
     assert (idx[near] == at[:8][None]).all() and (sim[near] == sim[near][:, :1]).all()
     assert idx[1].tolist() == list(range(8)) and (sim[1] == 0).all()
+    pc.close()
+
+
+@pytest.mark.parametrize("rows,dim,n_probes", [(200, 64, 1024), (6000, 768, 1), (70001, 512, 40), (140001, 64, 20), (20011, 64, 300), (33001, 64, 1024), (33001, 64, 1200), (3001, 64, 2500), (9001, 640, 100)])
+def test_topk_in_the_lookups_workspace(rows, dim, n_probes):
+    """The workspace of a call for the best row is as large as lists in every workgroup take, on any bank, and a call for 8 rows takes it as well: one
+    pass of the bank for up to 1024 probes, a few more for more of them, and the rows it finds in the larger one."""
+    g = torch.Generator(device=DEV)
+    g.manual_seed(rows + dim)
+    bank = torch.randn((rows, dim), generator=g, device=DEV).half()
+    bank[5:: 997] = bank[5].clone()
+    probes = torch.randn((n_probes, dim), generator=g, device=DEV).half()
+    probes[0] = bank[5]
+    pc = _ctx(rows, dim)
+    pc.percache_bank_put(0, bank)
+    n_cu = torch.cuda.get_device_properties(0).multi_processor_count
+    least = n_cu * (256 if n_probes > 32 else 32) * 64
+    small, large = pc.lib.percache_lookup_workspace_bytes(pc.ctx, n_probes), pc.lib.percache_lookup_topk_workspace_bytes(pc.ctx, n_probes)
+    assert small == least <= large <= n_probes * 4096 * 17 + least
+    pc.percache_lookup(probes, 0.5)
+    held = pc._lookup_ws.data_ptr()
+    assert pc._lookup_ws.numel() == small + 256
+    idx, sim = pc.percache_lookup_topk(probes, 8)
+    pc.percache_lookup(probes, 0.5)
+    assert pc._lookup_ws.data_ptr() == held
+    ws = torch.full((small + 512,), 255, dtype=torch.uint8, device=DEV)
+    at = (ws.data_ptr() + 255) // 256 * 256
+    i2, s2 = torch.empty_like(idx), torch.empty_like(sim)
+    pc.percache_profile_enable(True, kernels=[KERNEL_LOOKUP])
+    pc._check(pc.lib.percache_lookup_topk(pc.ctx, probes.data_ptr(), n_probes, 8, i2.data_ptr(), s2.data_ptr(), at, small, torch.cuda.current_stream().cuda_stream))
+    _, passes = pc.percache_profile_read(KERNEL_LOOKUP)
+    pc.percache_profile_enable(False)
+    assert passes == 1 if n_probes <= 4 * n_cu else passes <= -(-n_probes // 512)
+    assert torch.equal(idx, i2) and torch.equal(sim, s2)
+    assert (ws[at - ws.data_ptr() + small:] == 255).all()
+    ref = torch.nn.functional.normalize(probes.double(), dim=1) @ torch.nn.functional.normalize(bank.double(), dim=1).t()
+    want = torch.sort(ref, dim=1, descending=True, stable=True).values[:, :8]
+    assert (torch.gather(ref, 1, idx.long()) - want).abs().max().item() < 2e-6    # (fp32 sums of at most 1024 exact products of unit vectors)
+    assert pc.lib.percache_lookup_topk(pc.ctx, probes.data_ptr(), n_probes, 8, i2.data_ptr(), s2.data_ptr(), at, small - 1, 0) < 0
     pc.close()
 
 
