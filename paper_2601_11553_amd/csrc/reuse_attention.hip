@@ -1595,12 +1595,16 @@ struct TilePace {
 // 76 launches against choose_splits: 1.074 times as fast on average (1.078 with bf16 partials everywhere).  us a call of attention alone, its count | this
 // one: 16 heads over 8, 55 rows over 6 tiles, mixed slots 24.5 | 18.0, 116 over 14 of 8 bits 23.2 | 20.0; 28 over 4, 8 rows over 29 tiles 21.3 | 16.2, 3 x 256
 // over 20 52.5 | 41.2 (bf16 38.4; choose_splits' 252 workgroups are 35 on the fullest XCD), 220 over 44 43.4 | 34.8 (33.2); 14 over 2 of 64, 25 over 9, 8 bits 19.8 | 16.0.
+// least_cut: under so many tiles a call that choose_splits leaves whole stays whole.  The merge is a launch more, 2.6 us of the host, which calls this short
+// wait for.  us a call, whole | cut: 14 heads over 2 of 64, 40 rows, 8-bit slots, 4 tiles 15.1 | 17.7, 5 16.5 | 18.2, 6 17.9 | 18.6, 7 19.3 | 18.9, 9 22.4 | 17.9; 28
+// over 4, 9 rows, 6 tiles 16.9 | 17.9; 16 over 8, 60 rows, 7 tiles 18.2 | 17.4; 8-bit slots at head size 128, 4 tiles 18.1 | 19.6, 5 21.5 | 17.9.
 struct Partitions {
   int n;
   bool f32;
 };
-static Partitions choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_tiles, int tiles, double merge_us, int cap) {
+static Partitions choose_partitions(const TilePace &pace, int n_cu, long n_bg, int q_tiles, int tiles, int least_cut, double merge_us, int cap) {
   const int least_bf16 = choose_splits(pace.second == 0 ? n_cu : 2 * n_cu, n_bg * q_tiles, tiles, cap);
+  if (least_bf16 == 1 && tiles < least_cut) return {1, false};
   auto in_f32 = [&](int ns) { return ns > 1 && (least_bf16 == 1 || ns < least_bf16); };
   auto estimate = [&](int ns) {
     const long wgs = (n_bg * ns + 7) / 8 * 8 * q_tiles;
@@ -1732,7 +1736,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
                           : halved ? TilePace{0.79, 1.58}
                           : d128 ? (use8 ? TilePace{1.17, 1.12} : TilePace{1.16, 1.51}) : use8 ? TilePace{1.12, 1.05} : TilePace{0.68, 1.07};
     const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's bf16 partials, written and read at 5.4 TB/s
-    const Partitions parts = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, merge_us, cap);
+    const Partitions parts = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, d128 && use8 ? 5 : 7, merge_us, cap);
     n_splits = parts.n;
     part_f32 = parts.f32;
   }

@@ -313,6 +313,24 @@ def test_partition_counts_keep_the_precision(t_fresh, Hq, Hkv, D, batch, n_chunk
     assert err[0] <= 1.012 * err[1]   # (squares)
 
 
+@pytest.mark.parametrize("n_chunks,n8,whole", [(1, 0, True), (3, 3, True), (4, 2, True), (5, 5, True), (6, 6, False), (8, 8, False)])
+def test_short_ranges_at_head_size_64_stay_whole(n_chunks, n8, whole):
+    """One more tile than chunks: up to 6 of them one partition, bit for bit, on 256 CUs."""
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=14, n_kv_heads=2, head_dim=64, n_slots=n_chunks, slot_capacity=64, max_pos=64 * n_chunks + 40, n_slots_8bit=n8,
+                  device=DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n_chunks)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    for s in range(n_chunks):
+        pc.percache_kv_put(0, s, rnd(2, 64, 64), rnd(2, 64, 64))
+    q, kf, vf = rnd(1, 14, 40, 64), rnd(1, 2, 40, 64), rnd(1, 2, 40, 64)
+    own, one = (pc.percache_attention_reuse(0, q, kf, vf, [list(range(n_chunks))], n_splits=n).clone() for n in (0, 1))
+    pc.close()
+    check_close(host(own), host(one), f"{n_chunks} chunks")
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert torch.equal(own, one) == whole
+
+
 @pytest.mark.parametrize("n_splits", [0, 1, 5])
 def test_long_chunk_lists(n_splits):
     """70 and 64 short chunks per query (the kernel keeps the first 64 list entries in registers and reads the
