@@ -1616,7 +1616,9 @@ static Partitions choose_partitions(const TilePace &pace, int n_cu, long n_bg, i
       const long rounds = wgs / (2 * n_cu), rest = wgs % (2 * n_cu);
       t = rounds * two + (rest == 0 ? 0.0 : rest <= n_cu ? one : two) + (wgs > 2 * n_cu ? 3.0 : 0.0);
     }
-    if (ns > 1) t += (ns <= 4 ? 2.2 : ns <= 16 ? 3.3 : 4.5) + merge_us * ns * (in_f32(ns) ? 2 : 1);   // (how many partials a lane of the merge has in flight)
+    // (the merge: a round of loads for up to four partials a row, else one for every sixteen: 14 heads over 2 of 64, 2 x 22 rows over 129 tiles, 32 partitions
+    // 22.0 us a call, 33 23.3, 60 24.4)
+    if (ns > 1) t += (ns <= 4 ? 2.2 : 2.1 + 1.2 * ((ns + 15) / 16)) + merge_us * ns * (in_f32(ns) ? 2 : 1);
     return t;
   };
   // (the count of the rule before it unless another one promises more than the estimate errs by)

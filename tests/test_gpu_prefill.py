@@ -331,6 +331,26 @@ def test_short_ranges_at_head_size_64_stay_whole(n_chunks, n8, whole):
         assert torch.equal(own, one) == whole
 
 
+@pytest.mark.parametrize("batch,n8", [(2, 8), (2, 16), (1, 4)])
+def test_no_more_partitions_than_two_rounds_of_the_merge(batch, n8):
+    """22 rows of 14 heads over 2 of 64 and 129 tiles, slots of 8 bits and of both kinds: 32 partitions, bit for bit, on 256 CUs (48 of one query)."""
+    S = batch * 8
+    pc = Percache(n_layers=1, hidden=64, n_q_heads=14, n_kv_heads=2, head_dim=64, n_slots=S, slot_capacity=1024, max_pos=8 * 1024 + 22, n_slots_8bit=n8, device=DEV)
+    g = torch.Generator(device=DEV)
+    g.manual_seed(n8)
+    rnd = lambda *s: torch.randn(s, generator=g, device=DEV).bfloat16()  # noqa: E731
+    for s in range(S):
+        pc.percache_kv_put(0, s, rnd(2, 1024, 64), rnd(2, 1024, 64))
+    q, kf, vf = rnd(batch, 14, 22, 64), rnd(batch, 2, 22, 64), rnd(batch, 2, 22, 64)
+    ids = np.arange(S, dtype=np.int32).reshape(batch, 8)
+    own = pc.percache_attention_reuse(0, q, kf, vf, ids).clone()
+    same = [n for n in range(1, 65) if torch.equal(own, pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=n))]
+    pc.close()
+    print("partitions", same, flush=True)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert len(same) == 1 and same[0] <= (32 if batch == 2 else 48)
+
+
 @pytest.mark.parametrize("n_splits", [0, 1, 5])
 def test_long_chunk_lists(n_splits):
     """70 and 64 short chunks per query (the kernel keeps the first 64 list entries in registers and reads the
