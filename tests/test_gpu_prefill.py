@@ -256,11 +256,12 @@ def test_seeded_random_shapes(seed):
 
 
 # (fresh rows, heads, kv heads, head size, queries, chunks, chunk tokens, 8-bit slots): partitions of one or two tiles, as many as tiles, past 16, kv heads
-# that do not come out even over the XCDs, 256-row blocks
-@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch,n_chunks,C,n8", [
-    (100, 16, 8, 128, 1, 3, 256, 0), (40, 4, 2, 128, 1, 6, 64, 0), (23, 14, 2, 64, 1, 3, 256, 6), (45, 16, 8, 128, 1, 5, 1024, 6), (55, 16, 8, 128, 1, 3, 128, 2),
-    (20, 16, 8, 128, 1, 16, 256, 0), (256, 28, 4, 128, 3, 2, 512, 0), (203, 24, 8, 128, 6, 2, 192, 12)])
-def test_partition_counts_chosen_by_the_library(t_fresh, Hq, Hkv, D, batch, n_chunks, C, n8):
+# that do not come out even over the XCDs, 256-row blocks left whole and cut
+@pytest.mark.parametrize("t_fresh,Hq,Hkv,D,batch,n_chunks,C,n8,cut", [
+    (100, 16, 8, 128, 1, 3, 256, 0, True), (40, 4, 2, 128, 1, 6, 64, 0, True), (23, 14, 2, 64, 1, 3, 256, 6, True), (45, 16, 8, 128, 1, 5, 1024, 6, True),
+    (55, 16, 8, 128, 1, 3, 128, 2, True), (20, 16, 8, 128, 1, 16, 256, 0, True), (256, 28, 4, 128, 3, 2, 512, 0, True), (203, 24, 8, 128, 6, 2, 192, 12, False),
+    (203, 24, 8, 128, 6, 13, 256, 78, True)])
+def test_partition_counts_chosen_by_the_library(t_fresh, Hq, Hkv, D, batch, n_chunks, C, n8, cut):
     """The library's own partition counts against one partition: the same attention up to the rounding of partials to bf16."""
     S = batch * n_chunks
     pc = Percache(n_layers=1, hidden=64, n_q_heads=Hq, n_kv_heads=Hkv, head_dim=D, n_slots=S, slot_capacity=C, max_pos=t_fresh + C * n_chunks, n_slots_8bit=min(n8, S),
@@ -273,9 +274,14 @@ def test_partition_counts_chosen_by_the_library(t_fresh, Hq, Hkv, D, batch, n_ch
         pc.percache_kv_put(0, s, rnd(Hkv, n, D), rnd(Hkv, n, D))
     q, kf, vf = rnd(batch, Hq, t_fresh, D), rnd(batch, Hkv, t_fresh, D), rnd(batch, Hkv, t_fresh, D)
     ids = np.arange(S, dtype=np.int32).reshape(batch, n_chunks)
-    own, one = (pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=n) for n in (0, 1))
-    check_close(host(own), host(one), f"T={t_fresh} heads {Hq} over {Hkv} of {D}, {batch} x {n_chunks} chunks")
+    cap = min(64, max(4, -(-512 // (batch * Hkv * -(-(Hq // Hkv) * t_fresh // 128)))))       # the library's counts stay within it on 256 CUs
+    own, one, *fixed = (pc.percache_attention_reuse(0, q, kf, vf, ids, n_splits=n).clone() for n in [0, 1] + sorted({2, 4, min(17, cap), cap}))
+    for i, o in enumerate([own] + fixed):
+        check_close(host(o), host(one), f"T={t_fresh} heads {Hq} over {Hkv} of {D}, {batch} x {n_chunks} chunks, {i}")
     pc.close()
+    # (another count gives other bits: where the library's is not one, the comparison above is not of a call with itself)
+    if torch.cuda.get_device_properties(0).multi_processor_count == 256:
+        assert torch.equal(own, one) != cut
 
 
 # (fresh rows, heads, kv heads, head size, queries, chunks, chunk tokens, 8-bit slots, count): counts that two workgroups a CU and four tiles a partition
