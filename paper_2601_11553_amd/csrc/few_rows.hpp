@@ -222,7 +222,8 @@ inline Choice choose_tile(int n_cu, int M, int n16, int min_nf, bool three = fal
 // tiles win.  us at width 1024: gate and up projections of ffn 3072 20 in two rounds (320 rows), 29 in three (512), 55 in six (1000)
 // against 14 to 21 and 5 for the norm; QKV of 4096 features 13 | 21 | 30 in one, two, three rounds (256, 512, 640 rows) against 17
 // and 5; width 3072, 200 rows: gate and up (four rounds) 75 against 49 and 6, QKV (two) 38 against 49 and 6.  Up to 128 rows a
-// token tile of the other kernels is mostly padding.
+// token tile of the other kernels is mostly padding.  (The tiles of 48 weight rows change none of these answers: what costs up to 16 with them, two
+// rounds, does so on the larger tiles too.)
 inline bool pays(int n_cu, long M, int n16, int min_nf, long max_cost) { return M <= 128 || choose_tile(n_cu, (int)M, n16, min_nf).cost <= max_cost; }
 // wavefronts and stages of a tile: what fits beside a second workgroup on the CU at one token block, else one per CU
 template <int NF, int NT>

@@ -1608,7 +1608,7 @@ int max_stream_grid(const percache_ctx *ctx) {
 
 constexpr int kBatchedFrom = 32;  // more probes than one streaming pass takes: the 128-probe pass or the matrix-product kernel
 // Per-row scan: more new embeddings than one streaming pass takes go through 128-probe passes.  200k rows, streaming passes | 128-probe
-// passes, us: width 384 75 | 43 at 33 to 64, 164 | 70 at 128; width 1024 138 | 73 at 64, 280 | 113 at 128, 490 | 228 at 200.
+// passes, us: width 384 69 | 42 at 33, 79 | 43 at 64, 161 | 67 at 128; width 1024 141 | 72 at 64, 288 | 111 at 128, 495 | 227 at 200.
 constexpr int kScanWideFrom = 32;
 constexpr int kWideUpTo = 128;    // one such pass; beyond it the matrix-product kernel is the faster one
 
@@ -1647,18 +1647,21 @@ pc_status launch_stream(percache_ctx *ctx, const StreamShape &sh, hipStream_t st
 }
 
 template <int K>
+pc_status launch_one_block(percache_ctx *ctx, const StreamShape &sh, hipStream_t st, int N, int d, const _Float16 *pp, int np, Best *partial, const RowScan &rs,
+                           const InLaunch &il, const Groups &gm) {
+  return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+         : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
+                         : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
+}
+template <int K>
 pc_status launch_pass(percache_ctx *ctx, const StreamShape &sh, int npb, hipStream_t st, int N, int d, const _Float16 *pp, int np,
                       Best *partial, const RowScan &rs = RowScan{}, const InLaunch &il = InLaunch{}, const Groups &gm = Groups{}) {
-  if (npb == 1 && sh.nstg == 3)
-    return sh.chb == 128   ? launch_stream<1, 128, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
-           : sh.chb == 256 ? launch_stream<1, 256, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
-                           : launch_stream<1, 512, 3, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
+  if (npb == 1 && sh.nstg == 3) return launch_one_block<K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
   if (npb == 1) return launch_stream<1, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);  // only the widest rows (512-byte chunks) get here
   return sh.chb == 128   ? launch_stream<2, 128, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
          : sh.chb == 256 ? launch_stream<2, 256, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm)
                          : launch_stream<2, 512, 2, K>(ctx, sh, st, N, d, pp, np, partial, rs, il, gm);
 }
-
 
 // What a call of n_probes needs at least: eight rows a workgroup and probe, of which a call for the best row uses one.  A top-k call that is given no
 // more than this makes its groups as large as they have to be: four a workgroup always fit.
@@ -1883,12 +1886,12 @@ pc_status run_passes(percache_ctx *ctx, hipStream_t st, int N, const _Float16 *p
     StreamShape sh = stream_shape(ctx, npb, N);
     const _Float16 *pp = probes + (size_t)p0 * d;
     pc::prof_begin(ctx, PC_KERNEL_LOOKUP, st);
-    // (up to four best rows in one launch: lists of four)
     const Groups here = gm ? gm->from_probe(p0) : Groups{};
-    pc_status ls = !gm                           ? (k == 1 ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
-                                                           : launch_pass<4>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il))
-                   : here.kind == Groups::rows ? launch_pass<kRows>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here)
-                                                 : launch_pass<kGroups>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here);
+    // (up to four best rows in one launch: lists of four; kInLaunchProbes and 1024 elements leave room for three stages)
+    pc_status ls = gm && here.kind == Groups::rows ? launch_pass<kRows>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here)
+                   : gm                             ? launch_pass<kGroups>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il, here)
+                   : k == 1                         ? launch_pass<1>(ctx, sh, npb, st, N, d, pp, np, partial, RowScan{}, il)
+                                                    : launch_one_block<4>(ctx, sh, st, N, d, pp, np, partial, RowScan{}, il, Groups{});
     if (ls != PC_OK) return ls;
     pc::prof_end(ctx, PC_KERNEL_LOOKUP, st);
     PC_HIP(ctx, hipGetLastError());
