@@ -72,12 +72,12 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(unsigned w0, unsigned w1, float 
   return u.v;
 }
 
-// A lane's part of one partition's output for row prow, normalised: in fp32 or (a rounding more, half the bytes of the merge) in bf16; which of them is
-// choose_partitions' matter.
+// A lane's part of one partition's output for row prow, normalised: to part_f32, or where that is null to part_o, in bf16 (a rounding more, half the
+// bytes of the merge).  Which of them is choose_partitions' matter.
 template <int D>
-__device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], float inv, void *part_o, bool f32, size_t prow, int g2) {
-  if (f32) {
-    float *po = (float *)part_o + prow * D;
+__device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], float inv, __bf16 *part_o, float *part_f32, size_t prow, int g2) {
+  if (part_f32) {
+    float *po = part_f32 + prow * D;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -85,7 +85,7 @@ __device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], flo
         *(pc::f32x4 *)(po + db * 32 + q4 * 8 + g2 * 4) =
             pc::f32x4{o_acc[db][q4 * 4 + 0] * inv, o_acc[db][q4 * 4 + 1] * inv, o_acc[db][q4 * 4 + 2] * inv, o_acc[db][q4 * 4 + 3] * inv};
   } else {
-    __bf16 *po = (__bf16 *)part_o + prow * D;
+    __bf16 *po = part_o + prow * D;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -113,7 +113,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
     const float *__restrict__ v_scale, const __bf16 *__restrict__ k_store16, const __bf16 *__restrict__ v_store16, int n_slots16,
     const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
   static_assert(!KV8 || NSTAGE == 2, "8-bit slots: two stages (the waits assume one tile in flight)");
   const __bf16 *k_store = (const __bf16 *)k_store_any, *v_store = (const __bf16 *)v_store_any;
   const uint8_t *k8_store = (const uint8_t *)k_store_any, *v8_store = (const uint8_t *)v_store_any;
@@ -631,7 +631,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const __bf16 *__restrict__ k_store, const __bf16 *__restrict__ v_store, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NLD = 4, NSTAGE = PAIR ? 4 : 3, KS = D / 16, DB = D / 32, QROWS = PAIR ? 128 : 256;
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
@@ -1029,7 +1029,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
     const uint8_t *__restrict__ k_store, const uint8_t *__restrict__ v_store, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, void *__restrict__ part_o, bool part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NW = 8, NLD = 4, KS = D / 16, DB = D / 32, QROWS = 32 * NW;
   constexpr int K8_ROW = D, V8_ROW = TK, K8_BYTES = TK * K8_ROW, V8_BYTES = D * V8_ROW, CST = K8_BYTES + V8_BYTES, NCST = 3;
@@ -1707,8 +1707,8 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     if (left_splits) *left_splits = left ? n_splits : 1;
     return n_splits > 1 && !left ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
-  void *const part_o = part_dev;
-  bool part_f32 = false;   // (a count that the caller asked for: bf16)
+  __bf16 *const part_o = (__bf16 *)part_dev;
+  float *part_f32 = nullptr;   // (a count that the caller asked for: bf16)
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
   // variant that tells the formats apart tile by tile only when it names chunks of both formats
   const bool use8 = (formats & 1) && ctx->n_slots8 > 0;
@@ -1740,7 +1740,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's bf16 partials, written and read at 5.4 TB/s
     const Partitions parts = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, d128 && use8 ? 5 : 7, merge_us, cap);
     n_splits = parts.n;
-    part_f32 = parts.f32;
+    if (parts.f32) part_f32 = (float *)part_dev;
   }
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;
@@ -1800,8 +1800,8 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   prof_end(ctx, PC_KERNEL_ATTENTION, stream);
   PC_HIP(ctx, hipGetLastError());
   if (n_splits == 1) return PC_OK;
-  return part_f32 ? launch_combine(ctx, (const float *)part_o, part_ml, n_splits, batch, t_fresh, out, stream)
-                  : launch_combine(ctx, (const __bf16 *)part_o, part_ml, n_splits, batch, t_fresh, out, stream);
+  return part_f32 ? launch_combine(ctx, part_f32, part_ml, n_splits, batch, t_fresh, out, stream)
+                  : launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream);
 }
 
 }  // namespace pc
