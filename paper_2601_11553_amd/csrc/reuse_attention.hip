@@ -72,12 +72,12 @@ __device__ __forceinline__ bf16x8 codes_to_bf16(unsigned w0, unsigned w1, float 
   return u.v;
 }
 
-// A lane's part of one partition's output for row prow, normalised: to part_f32, or where that is null to part_o, in bf16 (a rounding more, half the
-// bytes of the merge).  Which of them is choose_partitions' matter.
-template <int D>
-__device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], float inv, __bf16 *part_o, float *part_f32, size_t prow, int g2) {
-  if (part_f32) {
-    float *po = part_f32 + prow * D;
+// A lane's part of one partition's output for row prow, normalised: in fp32 or (a rounding more, half the bytes of the merge) in bf16.  Which of them is
+// choose_partitions' matter; a flag at run time costs the 256-row kernels' loop 1 %.
+template <int D, bool PART32>
+__device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], float inv, __bf16 *part_o, size_t prow, int g2) {
+  if constexpr (PART32) {
+    float *po = (float *)part_o + prow * D;
 #pragma unroll
     for (int db = 0; db < D / 32; ++db)
 #pragma unroll
@@ -106,14 +106,14 @@ __device__ __forceinline__ void write_partial(const f32x16 (&o_acc)[D / 32], flo
 // KSP = 2: two wavefronts share a 32-row block and take one 32-key block of every tile each (separate running
 // maximum / sum / output, merged through LDS at the end); for launches of few workgroups over bf16 slots, where the
 // per-tile chain of one wavefront, not the key stream, would set the pace.
-template <int D, int NW, int NSTAGE, bool KV8 = false, int KSP = 1, bool MIXED = false>
+template <int D, int NW, int NSTAGE, bool KV8, int KSP, bool MIXED, bool PART32>
 __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const void *__restrict__ k_store_any, const void *__restrict__ v_store_any, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, const __bf16 *__restrict__ k_store16, const __bf16 *__restrict__ v_store16, int n_slots16,
     const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
   static_assert(!KV8 || NSTAGE == 2, "8-bit slots: two stages (the waits assume one tile in flight)");
   const __bf16 *k_store = (const __bf16 *)k_store_any, *v_store = (const __bf16 *)v_store_any;
   const uint8_t *k8_store = (const uint8_t *)k_store_any, *v8_store = (const uint8_t *)v_store_any;
@@ -595,7 +595,7 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
+    write_partial<D, PART32>(o_acc, inv, part_o, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -626,12 +626,12 @@ __global__ __launch_bounds__(64 * NW, 2) void reuse_attention_kernel(
 // two pairs, and merge through LDS.  For prompts whose row blocks see very different numbers of keys (a whole prompt prefilled): twice the
 // workgroups, each half as long, even out where the longest 256-row block alone takes twice the mean
 // (the rule and its figures: launch_attention).
-template <int D, bool PAIR = false>
+template <int D, bool PAIR, bool PART32>
 __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const __bf16 *__restrict__ k_store, const __bf16 *__restrict__ v_store, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NLD = 4, NSTAGE = PAIR ? 4 : 3, KS = D / 16, DB = D / 32, QROWS = PAIR ? 128 : 256;
   __shared__ __align__(16) char lds[NSTAGE * L::STAGE];
@@ -1006,7 +1006,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
+    write_partial<D, PART32>(o_acc, inv, part_o, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -1023,13 +1023,13 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide_kernel(
 // bf16 already and are requested straight into their bf16 stage.  The converted values are stored with ds_write
 // instructions the compiler does not see as stores to the LDS array: with ordinary stores to it, it waits for every
 // outstanding request before each operand read.
-template <int D>
+template <int D, bool PART32>
 __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
     const __bf16 *__restrict__ Q, const __bf16 *__restrict__ Kf, const __bf16 *__restrict__ Vf_blk,
     const uint8_t *__restrict__ k_store, const uint8_t *__restrict__ v_store, const float *__restrict__ k_scale,
     const float *__restrict__ v_scale, int n_slots16, const int32_t *__restrict__ table,
     int tbl_stride, int T, int Hq, int Hkv, int C, int n_splits, int q_tiles, int n_groups, float scale_log2e,
-    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_f32, float *__restrict__ part_ml) {
+    __bf16 *__restrict__ out, __bf16 *__restrict__ part_o, float *__restrict__ part_ml) {
   using L = Lds<D>;
   constexpr int NW = 8, NLD = 4, KS = D / 16, DB = D / 32, QROWS = 32 * NW;
   constexpr int K8_ROW = D, V8_ROW = TK, K8_BYTES = TK * K8_ROW, V8_BYTES = D * V8_ROW, CST = K8_BYTES + V8_BYTES, NCST = 3;
@@ -1434,7 +1434,7 @@ __global__ __launch_bounds__(512, 2) void reuse_attention_wide8_kernel(
       }
   } else {
     const size_t prow = (((size_t)b * Hkv + gkv) * R + my_row) * n_splits + split;
-    write_partial<D>(o_acc, inv, part_o, part_f32, prow, g2);
+    write_partial<D, PART32>(o_acc, inv, part_o, prow, g2);
     if (g2 == 0) {
       part_ml[prow * 2] = m_ref;
       part_ml[prow * 2 + 1] = l_tot;
@@ -1708,7 +1708,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     return n_splits > 1 && !left ? launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream) : PC_OK;
   }
   __bf16 *const part_o = (__bf16 *)part_dev;
-  float *part_f32 = nullptr;   // (a count that the caller asked for: bf16)
+  bool part32 = false;   // (a count that the caller asked for: bf16)
   // the kernels that can read 8-bit tiles are taken only when the call names a chunk in an 8-bit slot, and their
   // variant that tells the formats apart tile by tile only when it names chunks of both formats
   const bool use8 = (formats & 1) && ctx->n_slots8 > 0;
@@ -1740,7 +1740,7 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
     const double merge_us = (double)batch * c.n_q_heads * t_fresh * c.head_dim * 4 / 5.4e6;   // a partition's bf16 partials, written and read at 5.4 TB/s
     const Partitions parts = choose_partitions(pace, ctx->n_cu, (long)batch * c.n_kv_heads, q_tiles, min_tiles, d128 && use8 ? 5 : 7, merge_us, cap);
     n_splits = parts.n;
-    if (parts.f32) part_f32 = (float *)part_dev;
+    part32 = parts.f32;
   }
   if (n_splits > cap) n_splits = cap;
   const void *ks, *vs;
@@ -1761,14 +1761,19 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
   const int blocks = pair ? (q_tiles + G - 1) / G * G : q_tiles;   // (a few more than there are: as many for every head of the group)
   dim3 grid((unsigned)(((n_groups + 7) / 8) * 8 * blocks));
   prof_begin(ctx, PC_KERNEL_ATTENTION, stream);
-#define PC_ATTN(DD, NWW, NS, ...)                                                                                     \
-  hipLaunchKernelGGL((reuse_attention_kernel<DD, NWW, NS, ##__VA_ARGS__>), grid, dim3(64 * NWW), 0, stream, q, kf,     \
-                     vf_blk, ks, vs, ksc, vsc, k16, v16, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, \
-                     c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml)
-#define PC_WIDE_P(DD, PP)                                                                                                       \
-  hipLaunchKernelGGL((reuse_attention_wide_kernel<DD, PP>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev, tbl_stride, \
-                     t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml)
-#define PC_WIDE(DD) do { if (pair) PC_WIDE_P(DD, true); else PC_WIDE_P(DD, false); } while (0)
+#define PC_ATTN_P(DD, NWW, NS, KV, KS, MX, PP)                                                                                \
+  hipLaunchKernelGGL((reuse_attention_kernel<DD, NWW, NS, KV, KS, MX, PP>), grid, dim3(64 * NWW), 0, stream, q, kf, vf_blk, ks, vs, ksc, vsc, k16, v16, \
+                     ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, \
+                     out, part_o, part_ml)
+#define PC_ATTN(DD, NWW, NS, KV, KS, MX) do { if (part32) PC_ATTN_P(DD, NWW, NS, KV, KS, MX, true); else PC_ATTN_P(DD, NWW, NS, KV, KS, MX, false); } while (0)
+#define PC_WIDE_P(DD, PAIR, PP)                                                                                                       \
+  hipLaunchKernelGGL((reuse_attention_wide_kernel<DD, PAIR, PP>), grid, dim3(512), 0, stream, q, kf, vf_blk, k16, v16, table_dev, tbl_stride, \
+                     t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_ml)
+#define PC_WIDE(DD) do { if (pair) PC_WIDE_P(DD, true, false); else if (part32) PC_WIDE_P(DD, false, true); else PC_WIDE_P(DD, false, false); } while (0)
+#define PC_WIDE8_P(PP)                                                                                                                \
+  hipLaunchKernelGGL((reuse_attention_wide8_kernel<128, PP>), grid, dim3(512), 0, stream, q, kf, vf_blk, (const uint8_t *)ks, (const uint8_t *)vs, ksc, vsc, \
+                     ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads, c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, \
+                     out, part_o, part_ml)
   if (use8 && mixed) {
     if (c.head_dim == 128) {
       if (wide) PC_ATTN(128, 8, 2, true, 1, true); else PC_ATTN(128, 4, 2, true, 1, true);
@@ -1776,32 +1781,32 @@ pc_status launch_attention(percache_ctx *ctx, int layer, const __bf16 *q, const 
       PC_ATTN(64, 4, 2, true, 1, true);
     }
   } else if (use8 && c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64 && c.slot_capacity / TK <= 32) {
-    hipLaunchKernelGGL((reuse_attention_wide8_kernel<128>), grid, dim3(512), 0, stream, q, kf, vf_blk, (const uint8_t *)ks,
-                       (const uint8_t *)vs, ksc, vsc, ctx->n_slots16, table_dev, tbl_stride, t_fresh, c.n_q_heads, c.n_kv_heads,
-                       c.slot_capacity, n_splits, q_tiles, n_groups, scale_log2e, out, part_o, part_f32, part_ml);
+    if (part32) PC_WIDE8_P(true); else PC_WIDE8_P(false);
   } else if (use8) {
     if (c.head_dim == 128) {
-      if (wide) PC_ATTN(128, 8, 2, true); else PC_ATTN(128, 4, 2, true);
+      if (wide) PC_ATTN(128, 8, 2, true, 1, false); else PC_ATTN(128, 4, 2, true, 1, false);
     } else {
-      PC_ATTN(64, 4, 2, true);
+      PC_ATTN(64, 4, 2, true, 1, false);
     }
   } else if (c.head_dim == 128 && wide && (tbl_stride - kTblHeader) / 2 <= 64) {
     PC_WIDE(128);
   } else if (c.head_dim == 128) {
-    if (wide) PC_ATTN(128, 8, 2); else if (halved) PC_ATTN(128, 4, 2, false, 2); else PC_ATTN(128, 4, 2);
+    if (wide) PC_ATTN(128, 8, 2, false, 1, false); else if (halved) PC_ATTN(128, 4, 2, false, 2, false); else PC_ATTN(128, 4, 2, false, 1, false);
   } else if (wide && (tbl_stride - kTblHeader) / 2 <= 64) {
     PC_WIDE(64);
   } else {
-    if (wide) PC_ATTN(64, 8, 4); else PC_ATTN(64, 4, 4);
+    if (wide) PC_ATTN(64, 8, 4, false, 1, false); else PC_ATTN(64, 4, 4, false, 1, false);
   }
+#undef PC_WIDE8_P
+#undef PC_ATTN_P
 #undef PC_WIDE
 #undef PC_WIDE_P
 #undef PC_ATTN
   prof_end(ctx, PC_KERNEL_ATTENTION, stream);
   PC_HIP(ctx, hipGetLastError());
   if (n_splits == 1) return PC_OK;
-  return part_f32 ? launch_combine(ctx, part_f32, part_ml, n_splits, batch, t_fresh, out, stream)
-                  : launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream);
+  return part32 ? launch_combine(ctx, (const float *)part_dev, part_ml, n_splits, batch, t_fresh, out, stream)
+                : launch_combine(ctx, part_o, part_ml, n_splits, batch, t_fresh, out, stream);
 }
 
 }  // namespace pc
