@@ -284,22 +284,24 @@ class Percache:
                                                      _ptr(sim_out), _ptr(hit_out), _stream()))
         return idx_out, sim_out, hit_out
 
+    def _topk_workspace(self, nbytes: int, own: bool):
+        """A larger one than the lookups have: theirs, or beside it one of its own (a captured lookup may hold theirs)."""
+        import torch
+        name = "_topk_ws" if own and self._lookup_ws is not None else "_lookup_ws"
+        if getattr(self, name) is None or getattr(self, name).numel() < nbytes:
+            setattr(self, name, torch.empty(nbytes, dtype=torch.uint8, device=self.device))
+        return getattr(self, name)
+
     def percache_lookup_topk(self, probes, k: int):
         """(idx [P, k] int32, sim [P, k] float32): the k best bank rows per probe, best first."""
         import torch
         n = probes.shape[0]
         idx_out = torch.empty((n, k), dtype=torch.int32, device=self.device)
         sim_out = torch.empty((n, k), dtype=torch.float32, device=self.device)
-        need = (self.lib.percache_lookup_topk_workspace_bytes if k > 1 else self.lib.percache_lookup_workspace_bytes)(self.ctx, n)
-        # (a workspace of its own beside a smaller one of the lookups: a captured lookup may hold that)
-        own = k > 1 and self._lookup_ws is not None and self._lookup_ws.numel() < need + 256
-        ws = self._topk_ws if own else self._lookup_ws
+        need = self.lib.percache_lookup_topk_workspace_bytes(self.ctx, n) if k > 1 else self.lib.percache_lookup_workspace_bytes(self.ctx, n)
+        ws = self._lookup_ws
         if ws is None or ws.numel() < need + 256:
-            ws = torch.empty(need + 256, dtype=torch.uint8, device=self.device)
-            if own:
-                self._topk_ws = ws
-            else:
-                self._lookup_ws = ws
+            ws = self._topk_workspace(need + 256, k > 1)
         ws = (ws.data_ptr() + 255) // 256 * 256
         self._check(self.lib.percache_lookup_topk(self.ctx, _ptr(probes), n, k, _ptr(idx_out), _ptr(sim_out), ws, need, _stream()))
         return idx_out, sim_out
