@@ -1606,15 +1606,21 @@ static Partitions choose_partitions(const TilePace &pace, int n_cu, long n_bg, i
   const int least_bf16 = choose_splits(pace.second == 0 ? n_cu : 2 * n_cu, n_bg * q_tiles, tiles, cap);
   if (least_bf16 == 1 && tiles < least_cut) return {1, false};
   auto in_f32 = [&](int ns) { return ns > 1 && (least_bf16 == 1 || ns < least_bf16); };
-  auto estimate = [&](int ns) {
-    const long wgs = (n_bg * ns + 7) / 8 * 8 * q_tiles;
+  const long step = 2L * n_cu;
+  auto estimate = [&](int ns) {   // (the host's time: a call looks at up to 64 counts)
+    const double share = (double)tiles / ns;
+    const long wgs = ((n_bg * ns + 7) & ~7L) * q_tiles;
     double t;
     if (pace.second == 0) {
-      t = (double)((wgs + n_cu - 1) / n_cu) * (pace.tile * tiles / ns + 4.0);   // (4: from a workgroup's start to its first tile, and its epilogue)
+      t = (double)((wgs + n_cu - 1) / n_cu) * (pace.tile * share + 4.0);   // (4: from a workgroup's start to its first tile, and its epilogue)
     } else {
-      const double one = pace.tile * (0.42 * ((tiles + ns - 1) / ns) + 0.58 * tiles / ns), two = one * pace.second;   // (the longest partition, and the mean one)
-      const long rounds = wgs / (2 * n_cu), rest = wgs % (2 * n_cu);
-      t = rounds * two + (rest == 0 ? 0.0 : rest <= n_cu ? one : two) + (wgs > 2 * n_cu ? 3.0 : 0.0);
+      const double one = pace.tile * (0.42 * ((tiles + ns - 1) / ns) + 0.58 * share), two = one * pace.second;   // (the longest partition, and the mean one)
+      if (wgs <= step) {
+        t = wgs <= n_cu ? one : two;
+      } else {
+        const long rounds = wgs / step, rest = wgs - rounds * step;
+        t = rounds * two + (rest == 0 ? 0.0 : rest <= n_cu ? one : two) + 3.0;
+      }
     }
     // (the merge: a round of loads for up to four partials a row, else one for every sixteen: 14 heads over 2 of 64, 2 x 22 rows over 129 tiles, 32 partitions
     // 22.0 us a call, 33 23.3, 60 24.4)
